@@ -196,6 +196,8 @@ typedef struct {
  *   M <- beta M + G;  U = M (nesterov: U = G + beta M)
  *   X = U / (||U||_F + eps); the iteration runs on the wide orientation
  *   ns_steps times: A = X X^T; B = b A + c A A; X <- a X + B X
+ *   (in bf16 mode wide matrices of 1536 and more rows take two or three of these steps at a time: the later A as
+ *   polynomials of the first, X multiplied once with the product; same result to the rounding of single steps or better)
  *   O = X; scale = 1 | sqrt(max(1, rows/cols)) | 0.2 sqrt(max(rows, cols))
  *   CANZ_OUT_PARAM: P <- P (1 - lr weight_decay) - lr scale O
  *   CANZ_OUT_DELTA: Delta W = - lr scale O
@@ -216,8 +218,8 @@ typedef struct {
  * dtypes and equal shape up to a transpose, at most 128 / tp of them and at most 2^30
  * padded elements per batch unless one matrix alone is larger; up to four consecutive small
  * batches run side by side within the same 2^30 elements, otherwise batches run one after
- * another on the stream, so for matrices below 2^30 elements at most about 10 GB are
- * asked for in bf16 mode, twice that in fp32 mode, whatever the share).
+ * another on the stream, so for matrices below 2^30 elements at most about 13 GB are
+ * asked for in bf16 mode, 20 GB in fp32 mode, whatever the share).
  * g: host array [n_groups]; pointer tables inside may be NULL for this call.
  */
 int canz_muon_workspace_bytes(const canz_group* g, int32_t n_groups,

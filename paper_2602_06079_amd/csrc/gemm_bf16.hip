@@ -53,16 +53,21 @@ constexpr int GROUP_M = 4;       // tile rows per raster band
 constexpr int N_XCD = 8;
 static_assert(BM == PANEL_ROWS && BK == PANEL_K, "tile = panel");
 
-enum { EPI_GRAM = 0, EPI_POLY = 1, EPI_UPDATE = 2, EPI_FINAL = 3, EPI_FINAL_SYM = 4 };
+enum { EPI_GRAM = 0, EPI_POLY = 1, EPI_UPDATE = 2, EPI_FINAL = 3, EPI_FINAL_SYM = 4, EPI_MUL = 5, EPI_POLY_APART = 6, EPI_GRAM_APART = 7 };
 // EPI_FINAL_SYM: the last-product epilogue (the caller's dense buffers) over the tiles on and above the diagonal of a
 // symmetric result only; the caller mirrors them into the lower triangle afterwards.
-constexpr bool epi_symmetric(int epi) { return epi == EPI_GRAM || epi == EPI_POLY || epi == EPI_FINAL_SYM; }
+// EPI_GRAM_APART, EPI_POLY_APART: the diagonals of the matrices are kept apart (kernels.h: SymSpec).
+// EPI_MUL: product of two symmetric matrices that commute (polynomials in one Gram matrix): symmetric as well.
+constexpr bool epi_poly(int epi) { return epi == EPI_POLY || epi == EPI_POLY_APART; }
+constexpr bool epi_apart(int epi) { return epi == EPI_POLY_APART || epi == EPI_MUL; }   // reads diagonals
+constexpr bool epi_mspace(int epi) { return epi == EPI_GRAM || epi == EPI_GRAM_APART || epi_poly(epi) || epi == EPI_MUL; }
+constexpr bool epi_symmetric(int epi) { return epi_mspace(epi) || epi == EPI_FINAL_SYM; }
 constexpr bool epi_final(int epi) { return epi == EPI_FINAL || epi == EPI_FINAL_SYM; }
 
 struct EpiArgs {
   void* c;                 // GRAM/POLY: [nb][M][N] panels; UPDATE: straight output [nb][M][N] panels
   void* ct;                // UPDATE: transposed output [nb][N][M] panels
-  const void* aux;         // POLY: A [nb][M][N] panels
+  SymSpec sym;             // GRAM/POLY/MUL: how the symmetric matrices are represented (kernels.h)
   const float* scale;      // per-matrix factor applied to the accumulator, or nullptr
   float ca, cb, cc;        // POLY coefficients
   // schedule of the persistent blocks (see launch()): full rounds of whole tiles, then the
@@ -129,55 +134,105 @@ __device__ __forceinline__ void decode_tile(int logical, int tiles_m, int tiles_
 
 }
 
+// Weight of a factor's element in the terms that carry a diagonal (kernels.h: SymSpec), and the diagonal element itself.
+// Written once with the roundings pinned, so that both kernels produce the same bits.
+template <int EPI>
+__device__ __forceinline__ float poly_weight(const EpiArgs& e, float x, float y) {
+  return EPI == EPI_POLY_APART ? __builtin_fmaf(e.cc, x + y, e.cb) : e.cb;
+}
+template <int EPI>
+__device__ __forceinline__ float sym_diagonal(float acc, float dx, float dy, const EpiArgs& e) {
+  if (EPI == EPI_MUL) return __builtin_fmaf(dx, dy, acc);
+  return EPI == EPI_POLY_APART ? acc + __builtin_fmaf(__builtin_fmaf(e.cc, dx, e.cb), dx, e.ca) : acc + e.ca;
+}
+
 // Epilogue of one 256 x 256 tile held in the accumulators of the block's four wavefronts
 // (shared by the GEMM kernel and by the kernel that finishes k-split tiles).
-// `stage`: this wavefront's private 32 KiB of LDS.
+// `stage`: this wavefront's private 32 KiB of LDS; `vec`: 128 floats of its own (POLY_APART and MUL).
 template <int EPI>
 __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage, int lane, int wm, int wn, int b,
                                               int tm, int tn, const GemmDims& d, const EpiArgs& e, const Shape& s,
-                                              const OutSpec& o) {
+                                              const OutSpec& o, float* vec) {
   // ---- epilogue.  Accumulator register r of lane l in MFMA tile (it, jt) is element
   //      row = 32 it + 8 (r / 4) + 4 (l / 32) + (r % 4),  col = 32 jt + (l % 32)
   //      of the wavefront's 128 x 128 part.  Each wavefront stages through its own 32 KiB.
   const int lj = lane & 31, lh = lane >> 5;
 
-  // scale (first iteration: folded normalisation), or the polynomial in A for EPI_POLY
-  if (EPI == EPI_POLY) {
-    // A is symmetric bit for bit (the Gram epilogue writes both halves from the same
-    // accumulators), so element (i, j) is read as (j, i): the wavefront's part of the mirrored
-    // tile is copied linearly into its staging area (global -> LDS, 16 bytes per lane) and is
-    // then the transposed image, in which a lane's four consecutive rows are four consecutive k.
-    const __bf16* A = static_cast<const __bf16*>(e.aux) + static_cast<int64_t>(b) * d.M * d.N;
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
-      const __bf16* src = A + (static_cast<int64_t>(tn) * (d.M >> 5) + 8 * tm + 4 * wm + kb) * PANEL_ELEMS +
-                          wn * 128 * PANEL_K + lane * 8;
-#pragma unroll
-      for (int x = 0; x < 8; ++x)
-        __builtin_amdgcn_global_load_lds(CANZ_GLB(src + x * 512), CANZ_LDS(stage + kb * 4096 + x * 512), 16, 0, 0);
-    }
+  // scale (first iteration: folded normalisation); for POLY and MUL the terms that carry a diagonal, which is kept
+  // apart in fp32 (kernels.h: SymSpec), and the element-wise term of the polynomial
+  if constexpr (epi_poly(EPI) || EPI == EPI_MUL) {
+    // The factors are symmetric (off-diagonal tiles bit for bit: both halves are written from the same
+    // accumulators), so element (i, j) is read as (j, i): the wavefront's part of the mirrored tile is copied linearly
+    // into its staging area (global -> LDS, 16 bytes per lane) and is then the transposed image, in which a lane's
+    // four consecutive rows are four consecutive k.  fold(M, f): acc(i, j) <- f(acc(i, j), M(i, j), i, j).
     int a_base[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) a_base[g] = lj * 32 + ((g ^ ((lj >> 2) & 3)) << 3) + 4 * lh;
-    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0): the copy has landed
+    const int row_w = tm * BM + wm * 128 + 4 * lh, col_w = tn * BN + wn * 128 + lj;
+    constexpr bool APART = epi_apart(EPI);
+    const float* const xv = APART ? e.sym.x + static_cast<int64_t>(b) * d.M : nullptr;
+    const float* const yv = APART ? e.sym.y + static_cast<int64_t>(b) * d.M : nullptr;
+    // the diagonal elements of the part's 128 rows, once per tile (a load per group of rows would cost a memory latency each)
+    if (APART) vec[lane] = xv[tm * BM + wm * 128 + lane], vec[64 + lane] = xv[tm * BM + wm * 128 + 64 + lane];
+    auto fold = [&](const void* matrix, auto weight_of) {
+      constexpr int W = decltype(weight_of)::value;   // 0: the polynomial's, 1: the row's diagonal element, 2: the column's
+      const __bf16* A = static_cast<const __bf16*>(matrix) + static_cast<int64_t>(b) * d.M * d.N;
 #pragma unroll
-    for (int it = 0; it < 4; ++it)
+      for (int kb = 0; kb < 4; ++kb) {
+        const __bf16* src = A + (static_cast<int64_t>(tn) * (d.M >> 5) + 8 * tm + 4 * wm + kb) * PANEL_ELEMS +
+                            wn * 128 * PANEL_K + lane * 8;
 #pragma unroll
-      for (int jt = 0; jt < 4; ++jt) {
-        const int col = tn * BN + wn * 128 + jt * 32 + lj;
-        const int row0 = tm * BM + wm * 128 + it * 32 + 4 * lh;
+        for (int x = 0; x < 8; ++x)
+          __builtin_amdgcn_global_load_lds(CANZ_GLB(src + x * 512), CANZ_LDS(stage + kb * 4096 + x * 512), 16, 0, 0);
+      }
+      float cw[4];
+#pragma unroll
+      for (int jt = 0; jt < 4; ++jt) cw[jt] = APART && W != 1 ? yv[col_w + jt * 32] : 0.f;
+      __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0): the copy has landed
+#pragma unroll
+      for (int it = 0; it < 4; ++it)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const bf16x4 av = *reinterpret_cast<const bf16x4*>(stage + it * 4096 + jt * 32 * 32 + a_base[g]);
+          f32x4 rw = {0.f, 0.f, 0.f, 0.f};
+          if (APART && W != 2) rw = *reinterpret_cast<const f32x4*>(vec + it * 32 + 8 * g + 4 * lh);
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            acc[it][jt][4 * g + q] =
-                poly_value(static_cast<float>(av[q]), acc[it][jt][4 * g + q], e.ca, e.cb, e.cc, row0 + 8 * g + q == col);
+          for (int jt = 0; jt < 4; ++jt) {
+            const bf16x4 av = *reinterpret_cast<const bf16x4*>(stage + it * 4096 + jt * 32 * 32 + a_base[g]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              acc[it][jt][4 * g + q] = __builtin_fmaf(W == 0 ? poly_weight<EPI>(e, rw[q], cw[jt]) : W == 1 ? rw[q] : cw[jt], static_cast<float>(av[q]),
+                                                      acc[it][jt][4 * g + q]);
           }
+          if (APART) __builtin_amdgcn_sched_barrier(0);   // one group's reads at a time: the accumulators leave few registers
         }
+      // every read of the staging area is done before it is written again
+      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    };
+    if constexpr (epi_poly(EPI)) {
+      // always, but a branch: as straight-line code behind the k loop the fold is spilled by the hundred
+#pragma unroll
+      for (int it = 0; it < 4; ++it)
+#pragma unroll
+        for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[it][jt][r] *= e.cc;
+      if (e.sym.aux) fold(e.sym.aux, std::integral_constant<int, 0>{});
+    } else {
+      if (e.sym.aux) fold(e.sym.aux, std::integral_constant<int, 1>{});
+      if (e.sym.aux2) fold(e.sym.aux2, std::integral_constant<int, 2>{});
+    }
+    if (tm == tn && wm == wn) {
+      // the diagonal: the lane that holds element (i, i)
+#pragma unroll
+      for (int it = 0; it < 4; ++it) {
+        const int col = col_w + it * 32;
+        const float dx = APART ? xv[col] : 0.f, dy = APART ? yv[col] : 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (row_w + it * 32 + 8 * (r >> 2) + (r & 3) == col)
+            acc[it][it][r] = sym_diagonal<EPI>(acc[it][it][r], dx, dy, e);
       }
-    // every read of the staging area is done before the images below overwrite it
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    }
   } else if (e.scale) {
     const float sc = e.scale[b];
 #pragma unroll
@@ -186,6 +241,19 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
       for (int jt = 0; jt < 4; ++jt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[it][jt][r] *= sc;
+  }
+  if constexpr (epi_apart(EPI) || EPI == EPI_GRAM_APART) {
+    if (e.sym.diag && tm == tn && wm == wn) {   // the diagonal goes to its own fp32 vector, the images hold zeros there
+      float* dv = e.sym.diag + static_cast<int64_t>(b) * d.M;
+#pragma unroll
+      for (int it = 0; it < 4; ++it)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int row = tm * BM + wm * 128 + it * 32 + 4 * lh + 8 * (r >> 2) + (r & 3);
+          const int col = tn * BN + wn * 128 + it * 32 + lj;
+          if (row == col) dv[row] = acc[it][it][r], acc[it][it][r] = 0.f;
+        }
+    }
   }
 
   // the wavefront's part of an output tile in panel layout: four pieces of 8 KiB (the four
@@ -238,12 +306,15 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
           const int fixed = jt * 4096 + (it * 32 + 8 * g + 2 * p) * 32;
           *reinterpret_cast<unsigned*>(stage + fixed + s_base[g & 1]) = pk;
         }
-    flush_stage(C, tm, d.N, 8 * tn + 4 * wn, wm);
+    // In a diagonal tile the lower left quarter is the mirror image of the upper right one, as in the small kernel: the
+    // two are equal bit for bit when both factors are the same matrix, but only to rounding in a product of two.
+    const bool diagonal_tile = epi_mspace(EPI) && tm == tn;
+    if (!diagonal_tile || wm <= wn) flush_stage(C, tm, d.N, 8 * tn + 4 * wn, wm);
 
     // ---- transposed image: element (i, j) is (row j, k = i) of CT (UPDATE) or of the mirror
     // tile of C (symmetric products).  A lane's 4 consecutive rows are half a chunk.
-    const bool mirror = (EPI == EPI_GRAM || EPI == EPI_POLY);
-    if (!mirror || tm != tn) {
+    const bool mirror = epi_mspace(EPI);
+    if (!diagonal_tile || wm < wn) {
       __bf16* CT = mirror ? C : static_cast<__bf16*>(e.ct) + static_cast<int64_t>(b) * d.M * d.N;
       // element (i_l, j_l) goes to row j_l = 32 jt + lj, k = i_l = 32 it + 8 g + 4 lh + q:
       // k-block it, chunk g, swizzle (lj >> 2) & 3: one lane base per g, the rest immediate
@@ -438,8 +509,8 @@ struct OneProblem {
 struct ManyProblems {
   static constexpr bool multi = true;
   int n;
-  int begin[MAX_KINDS + 1];  // first logical tile of each problem, then the total
-  GemmProblem pr[MAX_KINDS];
+  int begin[MAX_PROBLEMS + 1];  // first logical tile of each problem, then the total
+  GemmProblem pr[MAX_PROBLEMS];
 };
 
 template <int EPI, bool SPLIT, typename Args>
@@ -477,6 +548,7 @@ __global__ __launch_bounds__(NTHREADS) void k_gemm_nt_bf16(Args args, EpiArgs e_
   const int wm = wave >> 1, wn = wave & 1;
 
   int nk_all = static_cast<int>(d.K / BK);  // multiple of 8: K is a multiple of 256
+  __shared__ __attribute__((aligned(16))) float vec[epi_apart(EPI) ? 4 * 128 : 4];
 
   for (int work = 0;; ++work) {
   // ---- what to do in this round: a whole tile, or one k-slice of a left-over tile.  When
@@ -510,7 +582,7 @@ __global__ __launch_bounds__(NTHREADS) void k_gemm_nt_bf16(Args args, EpiArgs e_
     const GemmProblem& pr = args.pr[j];
     d = pr.d;
     P = static_cast<const __bf16*>(pr.p), Q = static_cast<const __bf16*>(pr.q);
-    e.c = pr.c, e.ct = pr.ct, e.aux = pr.aux, e.scale = pr.scale;
+    e.c = pr.c, e.ct = pr.ct, e.sym = pr.sym, e.scale = pr.scale;
     logical -= args.begin[j];
     tiles_n = static_cast<int>(d.N / BN), tiles_m = static_cast<int>(d.M / BM);
     per_batch = epi_symmetric(EPI) ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
@@ -661,7 +733,7 @@ __global__ __launch_bounds__(NTHREADS) void k_gemm_nt_bf16(Args args, EpiArgs e_
 
   {
     __bf16* stage = wave == 0 ? st0 : wave == 1 ? st1 : wave == 2 ? st2 : st3;
-    tile_epilogue<EPI>(acc, stage, lane, wm, wn, b, tm, tn, d, e, s, o);
+    tile_epilogue<EPI>(acc, stage, lane, wm, wn, b, tm, tn, d, e, s, o, epi_apart(EPI) ? vec + 128 * wave : vec);
   }
 
   // the next tile's loads overwrite every wavefront's staging area: wait for all of them.
@@ -676,6 +748,7 @@ __global__ __launch_bounds__(NTHREADS) void k_gemm_nt_bf16(Args args, EpiArgs e_
 template <int EPI>
 __global__ __launch_bounds__(NTHREADS) void k_split_finish(GemmDims d, EpiArgs e, Shape s, OutSpec o) {
   __shared__ __attribute__((aligned(1024))) __bf16 stg[4][(BM + BN) * BK];
+  __shared__ __attribute__((aligned(16))) float vec[4][128];
   const int tiles_n = static_cast<int>(d.N / BN);
   const int tiles_m = static_cast<int>(d.M / BM);
   const int per_batch = epi_symmetric(EPI) ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
@@ -701,7 +774,7 @@ __global__ __launch_bounds__(NTHREADS) void k_split_finish(GemmDims d, EpiArgs e
       }
       acc[i][j] = sum;
     }
-  tile_epilogue<EPI>(acc, stg[wave], lane, wave >> 1, wave & 1, b, tm, tn, d, e, s, o);
+  tile_epilogue<EPI>(acc, stg[wave], lane, wave >> 1, wave & 1, b, tm, tn, d, e, s, o, vec[wave]);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -756,7 +829,7 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
     const GemmProblem& pr = args.pr[j];
     d = pr.d;
     P = static_cast<const __bf16*>(pr.p), Q = static_cast<const __bf16*>(pr.q);
-    e.c = pr.c, e.ct = pr.ct, e.aux = pr.aux, e.scale = pr.scale;
+    e.c = pr.c, e.ct = pr.ct, e.sym = pr.sym, e.scale = pr.scale;
     logical -= args.begin[j];
   } else {
     d = args.d, P = args.P, Q = args.Q;
@@ -842,24 +915,78 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
   //      column 32 j + (l % 32) of the wavefront's 64 x 64 part.
   const int lj = lane & 31, lh = lane >> 5;
   const int row_w = tm * SM + wm * 64, col_w = tn * SM + wn * 64;
-  if (EPI == EPI_POLY) {
-    // A(i, j) is read as A(j, i) (symmetric bit for bit): the lane's four consecutive rows are
-    // four consecutive k of row j, one 8-byte load
-    const __bf16* A = static_cast<const __bf16*>(e.aux) + static_cast<int64_t>(b) * d.M * d.N;
+  // Where the elements of 32 x 32 tile (i, j) of the wavefront's part lie in a panel image: a part that is the same for
+  // all lanes, a lane's own offset (two for the straight image, by the parity of the group of 8 rows; four for the
+  // transposed one, by group) and a constant.
+  auto straight_at = [&](int i, int j) {
+    return (static_cast<int64_t>(row_w >> 8) * (d.N >> 5) + ((col_w + 32 * j) >> 5)) * PANEL_ELEMS + ((row_w & 255) + 32 * i) * PANEL_K;
+  };
+  auto transposed_at = [&](int i, int j) {
+    return (static_cast<int64_t>(col_w >> 8) * (d.M >> 5) + ((row_w + 32 * i) >> 5)) * PANEL_ELEMS + ((col_w & 255) + 32 * j) * PANEL_K;
+  };
+  int s_lane[2], t_lane[4];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+  for (int g1 = 0; g1 < 2; ++g1)
+    s_lane[g1] = (4 * lh + (lane & 1)) * PANEL_K + ((((lj >> 3) ^ (2 * g1 + lh)) & 3) << 3) + (lj & 6);
+#pragma unroll
+  for (int g = 0; g < 4; ++g) t_lane[g] = lj * PANEL_K + ((g ^ ((lj >> 2) & 3)) << 3) + 4 * lh;
+  if constexpr (epi_poly(EPI) || EPI == EPI_MUL) {
+    // as in the large kernel: element (i, j) of a symmetric factor is read as (j, i), so the lane's four
+    // consecutive rows are four consecutive k of row j, one 8-byte load
+    constexpr bool APART = epi_apart(EPI);
+    const float* const xv = APART ? e.sym.x + static_cast<int64_t>(b) * d.M : nullptr;
+    const float* const yv = APART ? e.sym.y + static_cast<int64_t>(b) * d.M : nullptr;
+    const __bf16* const m1 = static_cast<const __bf16*>(e.sym.aux) + static_cast<int64_t>(b) * d.M * d.N;
+    const __bf16* const m3 = static_cast<const __bf16*>(e.sym.aux2) + static_cast<int64_t>(b) * d.M * d.N;
+    if (m1 != nullptr) {   // always: keeps this apart from the k loop's block, see the large kernel
+    // all loads of a 32 x 32 tile at once: a few memory latencies for the whole epilogue, within the registers that
+    // three blocks per CU leave
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        const int col = col_w + 32 * j + lj;
+        asm volatile("" ::: "memory");   // or the compiler brings the loads of all four tiles together and spills
+        bf16x4 v1[4], v3[4];
+        f32x4 rw[4];
+        const float cw = APART ? yv[col_w + 32 * j + lj] : 0.f;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const int row0 = row_w + 32 * i + 8 * g + 4 * lh;
-          const bf16x4 av = *reinterpret_cast<const bf16x4*>(A + panel_chunk_off(col, row0 & ~7, d.M) + (row0 & 7));
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            acc[i][j][4 * g + q] = poly_value(static_cast<float>(av[q]), acc[i][j][4 * g + q], e.ca, e.cb, e.cc, row0 + q == col);
+          const int64_t at = transposed_at(i, j) + t_lane[g];
+          rw[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+          if (APART) rw[g] = *reinterpret_cast<const f32x4*>(xv + row_w + 32 * i + 8 * g + 4 * lh);
+          v1[g] = *reinterpret_cast<const bf16x4*>(m1 + at);
+          if constexpr (EPI == EPI_MUL) v3[g] = *reinterpret_cast<const bf16x4*>(m3 + at);
         }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            float v = acc[i][j][4 * g + q];
+            if constexpr (epi_poly(EPI)) {
+              const float w = poly_weight<EPI>(e, rw[g][q], cw);
+              v = __builtin_fmaf(w, static_cast<float>(v1[g][q]), v * e.cc);
+            } else {
+              v = __builtin_fmaf(rw[g][q], static_cast<float>(v1[g][q]), v);
+              v = __builtin_fmaf(cw, static_cast<float>(v3[g][q]), v);
+            }
+            acc[i][j][4 * g + q] = v;
+          }
+        __builtin_amdgcn_sched_barrier(0);
       }
+    }
+    }
+    if (tm == tn && wm == wn) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int col = col_w + 32 * i + lj;
+        const float dx = APART ? xv[col] : 0.f, dy = APART ? yv[col] : 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (row_w + 32 * i + 4 * lh + 8 * (r >> 2) + (r & 3) == col)
+            acc[i][i][r] = sym_diagonal<EPI>(acc[i][i][r], dx, dy, e);
+      }
+    }
   } else if (e.scale) {
     const float sc1 = e.scale[b];
 #pragma unroll
@@ -868,6 +995,18 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] *= sc1;
+  }
+  if constexpr (epi_apart(EPI) || EPI == EPI_GRAM_APART) {
+    if (e.sym.diag && tm == tn && wm == wn) {
+      float* dv = e.sym.diag + static_cast<int64_t>(b) * d.M;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int row = row_w + 32 * i + 4 * lh + 8 * (r >> 2) + (r & 3), col = col_w + 32 * i + lj;
+          if (row == col) dv[row] = acc[i][i][r], acc[i][i][r] = 0.f;
+        }
+    }
   }
 
   if (epi_final(EPI)) {
@@ -952,7 +1091,7 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int col = col_w + 32 * j + (lj & ~1);
+      __bf16* const at = C + straight_at(i, j);
 #pragma unroll
       for (int rp = 0; rp < 8; ++rp) {
         bf16x2 own;
@@ -961,8 +1100,7 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
         const unsigned mine = __builtin_bit_cast(unsigned, own);
         const unsigned theirs = lane_xor1(mine);
         const unsigned pk = __builtin_amdgcn_perm(theirs, mine, pair_sel);
-        const int row = row_w + 32 * i + 8 * (rp >> 1) + 4 * lh + 2 * (rp & 1) + (lane & 1);
-        *reinterpret_cast<unsigned*>(C + panel_chunk_off(row, col & ~7, d.N) + (col & 7)) = pk;
+        *reinterpret_cast<unsigned*>(at + s_lane[(rp >> 1) & 1] + (8 * (rp >> 1) + 2 * (rp & 1)) * PANEL_K) = pk;
       }
     }
   // transposed image: (row j, k = i) of CT (UPDATE) or of the mirror tile of C (symmetric products)
@@ -972,14 +1110,13 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        const int col = col_w + 32 * j + lj;
+        __bf16* const at = CT + transposed_at(i, j);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const int row0 = row_w + 32 * i + 8 * g + 4 * lh;
           bf16x4 pk;
 #pragma unroll
           for (int q = 0; q < 4; ++q) pk[q] = static_cast<__bf16>(acc[i][j][4 * g + q]);
-          *reinterpret_cast<bf16x4*>(CT + panel_chunk_off(col, row0 & ~7, d.M) + (row0 & 7)) = pk;
+          *reinterpret_cast<bf16x4*>(at + t_lane[g]) = pk;
         }
       }
   }
@@ -1006,6 +1143,8 @@ int cu_count() {
 // small kernel when they would leave at least half of the chip idle for a whole tile time -
 // which includes launches with no full round at all.
 constexpr int64_t SMALL_MAX_K = 4096;
+// ... except the products of m x m matrices, whose left-over tiles gain up to here (4 x 5120^2, 840 tiles on 256 CUs)
+constexpr int64_t SMALL_MAX_K_MSPACE = 8192;
 constexpr int64_t SMALL_ALL_MAX_K = 2048;   // polynomial products up to this k and under two rounds: small tiles only
 
 template <int EPI>
@@ -1018,10 +1157,11 @@ int64_t tile_count(const GemmDims& d) {
 template <int EPI>
 int64_t large_share(int64_t tiles, int64_t cus, int64_t longest_k) {
   const int64_t left = tiles % cus;
-  if (longest_k > SMALL_MAX_K) return tiles;
+  constexpr bool msquare = epi_poly(EPI) || EPI == EPI_MUL;
+  if (longest_k > (msquare ? SMALL_MAX_K_MSPACE : SMALL_MAX_K)) return tiles;
   // a polynomial product (k = m, the shortest k range of the step) of less than two rounds runs faster on small
   // tiles throughout: 59.6 -> 52.4 us on 26 matrices of 1024 x 1024; the same rule costs the Gram product 7 %
-  if (EPI == EPI_POLY && tiles < 2 * cus && longest_k <= SMALL_ALL_MAX_K) return 0;
+  if (msquare && tiles < 2 * cus && longest_k <= SMALL_ALL_MAX_K) return 0;
   if (left == 0 || 2 * left > cus) return tiles;
   return tiles - left;
 }
@@ -1092,7 +1232,7 @@ hipError_t launch_multi(const GemmBatch& g, EpiArgs e, hipStream_t st) {
     tiles += tile_count<EPI>(d);
     longest_k = std::max(longest_k, d.K);
   }
-  for (int j = g.n; j <= MAX_KINDS; ++j) many.begin[j] = static_cast<int>(tiles);
+  for (int j = g.n; j <= MAX_PROBLEMS; ++j) many.begin[j] = static_cast<int>(tiles);
   if (tiles == 0) return hipSuccess;
   const int64_t whole_large = large_share<EPI>(tiles, cus, longest_k);
   e.splits = 1;
@@ -1114,31 +1254,33 @@ hipError_t launch_multi(const GemmBatch& g, EpiArgs e, hipStream_t st) {
 
 }  // namespace
 
-hipError_t launch_gram_bf16_multi(const GemmBatch& g, hipStream_t st) { return launch_multi<EPI_GRAM>(g, EpiArgs{}, st); }
+namespace {
+template <int EPI>
+hipError_t launch_problems(const GemmBatch& g, EpiArgs e, const SplitWs& w, hipStream_t st) {
+  if (g.n != 1) return launch_multi<EPI>(g, e, st);
+  const GemmProblem& pr = g.pr[0];
+  e.c = pr.c, e.ct = pr.ct, e.sym = pr.sym, e.scale = pr.scale;
+  return launch<EPI>(pr.d, pr.p, pr.q, e, w, Shape{}, OutSpec{}, st);
+}
+}  // namespace
 
-hipError_t launch_poly_bf16_multi(const GemmBatch& g, float ca, float cb, float cc, hipStream_t st) {
-  EpiArgs e{};
-  e.ca = ca, e.cb = cb, e.cc = cc;
-  return launch_multi<EPI_POLY>(g, e, st);
+hipError_t launch_gram_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st) {
+  return g.n > 0 && g.pr[0].sym.diag ? launch_problems<EPI_GRAM_APART>(g, EpiArgs{}, w, st)
+                                     : launch_problems<EPI_GRAM>(g, EpiArgs{}, w, st);
 }
 
-hipError_t launch_update_bf16_multi(const GemmBatch& g, hipStream_t st) { return launch_multi<EPI_UPDATE>(g, EpiArgs{}, st); }
-
-hipError_t launch_gram_bf16(const GemmDims& d, const void* xw, void* a_out, const float* scale2, const SplitWs& w,
-                            hipStream_t st) {
+hipError_t launch_poly_bf16(const GemmBatch& g, float ca, float cb, float cc, const SplitWs& w, hipStream_t st) {
   EpiArgs e{};
-  e.c = a_out;
-  e.scale = scale2;
-  return launch<EPI_GRAM>(d, xw, xw, e, w, Shape{}, OutSpec{}, st);
+  e.ca = ca, e.cb = cb, e.cc = cc;
+  return g.n > 0 && g.pr[0].sym.x ? launch_problems<EPI_POLY_APART>(g, e, w, st) : launch_problems<EPI_POLY>(g, e, w, st);
 }
 
-hipError_t launch_poly_bf16(const GemmDims& d, const void* a_in, void* b_out, float ca, float cb, float cc,
-                            const SplitWs& w, hipStream_t st) {
-  EpiArgs e{};
-  e.c = b_out;
-  e.aux = a_in;
-  e.ca = ca, e.cb = cb, e.cc = cc;
-  return launch<EPI_POLY>(d, a_in, a_in, e, w, Shape{}, OutSpec{}, st);
+hipError_t launch_mul_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st) {
+  return launch_problems<EPI_MUL>(g, EpiArgs{}, w, st);
+}
+
+hipError_t launch_update_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st) {
+  return launch_problems<EPI_UPDATE>(g, EpiArgs{}, w, st);
 }
 
 hipError_t launch_update_bf16(const GemmDims& d, const void* b_in, const void* xt_in, void* xw_out, void* xt_out,

@@ -93,33 +93,46 @@ struct SplitWs {
 };
 constexpr int SPLIT_MAX_BLOCKS = 256;                       // CU count of MI355X; fewer blocks split on a smaller part
 constexpr size_t SPLIT_BLOCK_BYTES = 256 * 256 * sizeof(float);
-// Several products of one kind in one launch (matrices of different shapes): the persistent
-// blocks walk the tiles of problem 0, then of problem 1, ...  Used for shares whose shape
-// classes are too small to fill the chip on their own.
-constexpr int MAX_KINDS = 4;
+// How the products of the symmetric m x m matrices (all of them polynomials in one Gram matrix) take their factors
+// and leave their result.  A matrix is a bf16 image in the panel layout; optionally its diagonal is kept apart as an fp32
+// vector (the image then holds zeros there).  The MFMA products use the images; everything that multiplies a diagonal,
+// and the element-wise terms, are added in the epilogue in fp32:
+//   (D_P + H_P)(D_Y + H_Y) = D_P D_Y + D_P H_Y + H_P D_Y + H_P H_Y.
+// The diagonals are what all these matrices consist of once X is close to orthogonal, and their nearly equal elements
+// round alike: kept in bf16 they would cost several times the error of all other roundings together.
+struct SymSpec {
+  const void* aux;      // POLY: A;  MUL: the second factor Y
+  const void* aux2;     // MUL: the first factor P
+  const float* x;       // POLY: the diagonal of A, or nullptr (the image holds it);  MUL: the diagonal of P   [nb][M]
+  const float* y;       // POLY: as x;  MUL: the diagonal of Y
+  float* diag;          // result: diagonal, or nullptr (the image holds it)
+};
+// Several products of one kind in one launch: matrices of different shapes, or independent products of one chain.
+// The persistent blocks walk the tiles of problem 0, then of problem 1, ...
+constexpr int MAX_KINDS = 4;                  // shape classes that run side by side
+constexpr int MAX_PROBLEMS = 2 * MAX_KINDS;   // two independent products of each
 struct GemmProblem {
   GemmDims d;
   const void* p;       // first operand  [nb][M][K] panels
   const void* q;       // second operand [nb][N][K] panels
   void* c;             // output (UPDATE: the straight image)
   void* ct;            // UPDATE: the transposed image
-  const void* aux;     // POLY: A
+  SymSpec sym;         // GRAM, POLY, MUL
   const float* scale;  // per-matrix factor or nullptr
 };
 struct GemmBatch {
   int n;
-  GemmProblem pr[MAX_KINDS];
+  GemmProblem pr[MAX_PROBLEMS];
 };
-hipError_t launch_gram_bf16_multi(const GemmBatch& g, hipStream_t st);
-hipError_t launch_poly_bf16_multi(const GemmBatch& g, float ca, float cb, float cc, hipStream_t st);
-hipError_t launch_update_bf16_multi(const GemmBatch& g, hipStream_t st);
+// A = scale2[b] * X X^T                      (P = Q = XW); all problems with sym.diag, or none
+hipError_t launch_gram_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st);
+// B = ca I + cb A + cc A A                   (P = Q = A, symmetric); all problems with sym.x and sym.y, or none
+hipError_t launch_poly_bf16(const GemmBatch& g, float ca, float cb, float cc, const SplitWs& w, hipStream_t st);
+// C = P Y, P and Y symmetric and commuting   (Q = Y)
+hipError_t launch_mul_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st);
+// as launch_update_bf16 below, for several problems
+hipError_t launch_update_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st);
 
-// A = scale2[b] * X X^T                      (P = Q = XW)
-hipError_t launch_gram_bf16(const GemmDims& d, const void* xw, void* a_out, const float* scale2, const SplitWs& w,
-                            hipStream_t st);
-// B = ca I + cb A + cc A A                   (P = Q = A, symmetric)
-hipError_t launch_poly_bf16(const GemmDims& d, const void* a_in, void* b_out, float ca, float cb, float cc,
-                            const SplitWs& w, hipStream_t st);
 // X' = scale[b] * B X: XW' [mp][np] straight and XT' [np][mp] transposed  (P = B, Q = XT)
 hipError_t launch_update_bf16(const GemmDims& d, const void* b_in, const void* xt_in, void* xw_out, void* xt_out,
                               const float* scale, const SplitWs& w, hipStream_t st);

@@ -3,8 +3,8 @@
 // Sec. 3.3 stage (2)).  Validates the groups, carves the caller's workspace and enqueues
 // the kernels of each micro-group on the caller's stream:
 //   momentum (+ TP gather, cast, norm partials) -> norm scale ->
-//   ns_steps x { Gram, polynomial, update }  with the last update writing the caller's
-//   buffers (+ TP scatter).  Nothing here allocates, copies to the device or synchronises.
+//   ns_steps x { Gram, polynomial, update }, or several steps at a time (stage_plan), with the
+//   last update writing the caller's buffers (+ TP scatter).  Nothing here allocates, copies to the device or synchronises.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -223,20 +223,54 @@ int collect_batches(const canz_group* g, int n_groups, int out_mode, bool with_p
   });
 }
 
+// Stages of the iteration.  One Newton-Schulz step needs A = X X^T (m^2 n products, upper half), B = aI + bA + cAA (m^3)
+// and X <- B X (2 m^2 n).  The next Gram matrix is A' = B A B, so several steps can stay among the m x m matrices,
+//   B_1 = p(A_1),  A_2 = B_1 (B_1 A_1),  B_2 = p(A_2),  Q = B_2 B_1, ...        (3 m^3 per step after the first)
+// and X be touched once, X <- Q X: with r = m / n and in units of m^2 n, five steps cost 15 + 5 r one by one and
+// 6 + 14 r in stages of 3 + 2.
+// Precision decides how far a stage can go: an error in A_k is not seen by X and grows with a^2 per step in the small
+// singular values.  With the diagonals in fp32 (SymSpec) the update's error against 64 bits is 0.33 to 1.0 of that of
+// single steps in stages of 3, 2, 2, ... over flat, power-law, low-rank and outlier spectra of 2048 and more rows (0.45 on
+// the 4096 x 12288 and 25600 x 5120 shares).  A rounding error of A is a random matrix, whose norm against A's falls
+// like 1 / sqrt(m): at 1024 rows the factor reaches 1.1 on outlier spectra, at 333 rows 1.9.  Almost square matrices have
+// singular values near zero: up to 1.4 there.  A stage of 5 is up to 6 times worse on decaying spectra; a stage of 2 that
+// ends the iteration (nothing corrects X afterwards) up to 1.2 times: at least three steps.  Only for coefficients no
+// more expanding than the quintic's a = 3.4445; the cubic (c = 0) keeps single steps.
+// Speed (us, single steps -> stages): 4 x 25600 x 5120 35000 -> 20900, 5 x 4096 x 12288 14400 -> 10340, 2 x 2048 x 5632 1240 ->
+// 970, 1 x 1536 x 6144 795 -> 570, 1 x 5120 x 8192 3500 -> 3075, 1 x 3000 x 5000 1130 -> 1040; but 1 x 2048 x 3072 463 -> 482,
+// 1 x 1536 x 2304 329 -> 366 (the products of one small matrix leave most of the chip idle, and there are more of them):
+// hence m <= n / 2, from 2560 rows on m <= 2 n / 3.  The rule looks at the shape alone, so that a matrix's result does not
+// depend on what shares its launch.
+std::vector<int> stage_plan(const Shape& s, const canz_muon_hparams& hp) {
+  std::vector<int> stages;
+  const bool wide = s.m >= 2560 ? 3 * s.m <= 2 * s.n : s.m >= 1536 && 2 * s.m <= s.n;
+  const bool merge = hp.precision == CANZ_PREC_BF16 && hp.ns_steps >= 3 && hp.c != 0.f && hp.a > 0.f && hp.a <= 3.5f && wide;
+  for (int left = hp.ns_steps; left > 0;) {
+    int len = 1;
+    if (merge) len = stages.empty() ? (hp.ns_steps >= 4 ? 3 : 2) : std::min(2, left);
+    stages.push_back(len);
+    left -= len;
+  }
+  return stages;
+}
+bool merges(const std::vector<int>& stages) { return !stages.empty() && stages[0] > 1; }
+
 // Launch batches that are too small to fill the chip on their own for long (fewer than 8
 // rounds of update tiles on 256 CUs) are run together, up to MAX_KINDS of them: their Gram,
-// polynomial and update products then share launches.  first[i] .. first[i + 1] are the
-// batches of run i.  Only in bf16 mode; the fp32 verification path keeps one batch per run.
+// polynomial and update products then share launches, so they must agree in their stages (which
+// depend on the shape alone: a matrix's result does not depend on what shares its launch).
+// first[i] .. first[i + 1] are the batches of run i.  Only in bf16 mode; the fp32 verification path keeps one batch per run.
 constexpr int64_t SMALL_BATCH_TILES = 8 * 256;
-std::vector<int> group_runs(const std::vector<Batch>& batches, int precision) {
+std::vector<int> group_runs(const std::vector<Batch>& batches, const canz_muon_hparams& hp) {
   std::vector<int> first;
   const int n = static_cast<int>(batches.size());
   for (int i = 0; i < n;) {
     first.push_back(i);
     int j = i + 1;
-    if (precision == CANZ_PREC_BF16 && batches[i].update_tiles() < SMALL_BATCH_TILES) {
+    if (hp.precision == CANZ_PREC_BF16 && batches[i].update_tiles() < SMALL_BATCH_TILES) {
       int64_t elems = batches[i].s0.mp * batches[i].s0.np * batches[i].nb;
-      while (j < n && j - i < MAX_KINDS && batches[j].update_tiles() < SMALL_BATCH_TILES) {
+      while (j < n && j - i < MAX_KINDS && batches[j].update_tiles() < SMALL_BATCH_TILES &&
+             stage_plan(batches[j].s0, hp) == stage_plan(batches[i].s0, hp)) {
         const int64_t more = batches[j].s0.mp * batches[j].s0.np * batches[j].nb;
         if (elems + more > MAX_BATCH_ELEMS) break;
         elems += more;
@@ -249,10 +283,30 @@ std::vector<int> group_runs(const std::vector<Batch>& batches, int precision) {
   return first;
 }
 
-size_t run_bytes(const std::vector<Batch>& batches, int lo, int hi, int precision) {
-  size_t total = 0;
-  for (int k = lo; k < hi; ++k) total += carve(batches[k].s0, batches[k].nb, precision).total;
-  return total + split_bytes(precision);
+// Further m x m arrays of a batch whose steps are merged, as offsets into its part of the tail: B A, two more images for the
+// polynomials and their products, four diagonals.  They live between two Gram products.  The diagonal of A, which the
+// Gram product itself leaves, lies in the X^T buffer that is not in use.
+struct Extra {
+  size_t t, b1, b2, diag, total;
+};
+Extra extra(const Shape& s, int nb) {
+  const size_t img = align_up(static_cast<size_t>(nb) * s.mp * s.mp * 2);
+  Extra x{};
+  x.t = 0, x.b1 = img, x.b2 = 2 * img, x.diag = 3 * img;
+  x.total = 3 * img + align_up(static_cast<size_t>(4) * nb * s.mp * sizeof(float));
+  return x;
+}
+
+// The tail of a run's workspace is the k-split scratch, which only Gram products use (the other products have k = m), and
+// between two Gram products the extra arrays.
+size_t run_bytes(const std::vector<Batch>& batches, int lo, int hi, const canz_muon_hparams& hp) {
+  size_t total = 0, more = 0;
+  for (int k = lo; k < hi; ++k) {
+    total += carve(batches[k].s0, batches[k].nb, hp.precision).total;
+    more += extra(batches[k].s0, batches[k].nb).total;
+  }
+  if (!merges(stage_plan(batches[lo].s0, hp))) more = 0;
+  return total + std::max(split_bytes(hp.precision), more);
 }
 
 // One run: the batches lo .. hi-1 side by side in the workspace, then the split scratch.
@@ -261,8 +315,12 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
                 hipStream_t st) {
   constexpr bool is_bf16 = sizeof(T) == 2;
   const int nk = hi - lo;
+  const std::vector<int> stages = stage_plan(batches[lo].s0, hp);   // the same for all batches of a run
+  const bool merged = merges(stages);
   struct Kind {
     T *xw, *xt[2], *a, *bm;
+    void *t, *b[3];            // merged steps: B A, three images for polynomials and their products
+    float *dt, *db[3];         // ... and the diagonals
     float *partial, *scale, *scale2;
     int64_t x_elems, a_elems;
     int tiles, nb;
@@ -294,6 +352,17 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
     kd.upd = GemmDims{s.mp, s.np, s.mp, s.mp, s.mp, kd.a_elems, kd.x_elems, bt.nb};
   }
   const SplitWs split{reinterpret_cast<float*>(ws + base), SPLIT_MAX_BLOCKS};
+  for (int k = 0; merged && k < nk; ++k) {   // the extra arrays share the tail with the split scratch
+    Kind& kd = kind[k];
+    const Extra x = extra(kd.s0, kd.nb);
+    char* w = ws + base;
+    kd.t = w + x.t;
+    kd.b[0] = kd.bm, kd.b[1] = w + x.b1, kd.b[2] = w + x.b2;
+    float* dv = reinterpret_cast<float*>(w + x.diag);
+    const int64_t len = static_cast<int64_t>(kd.nb) * kd.s0.mp;
+    kd.dt = dv, kd.db[0] = dv + len, kd.db[1] = dv + 2 * len, kd.db[2] = dv + 3 * len;
+    base += x.total;
+  }
 
   // momentum (+ gather, cast, both orientations, tile sums of U^2) per part, norm per batch
   for (int k = 0; k < nk; ++k) {
@@ -341,45 +410,88 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
     return CANZ_OK;
   }
 
-  const bool together = is_bf16 && nk > 1;   // shared launches for Gram, polynomial and update
-  int cur = 0;
-  for (int it = 0; it < hp.ns_steps; ++it) {
-    const bool first_it = it == 0, last = it + 1 == hp.ns_steps;
-    if (together) {
-      GemmBatch gb{};
+  // The products of one stage (see stage_plan) among the m x m matrices, every shape class of the run side by side;
+  // returns through q[k] the image that X is multiplied with.  `cur`: which X^T buffer is in use.
+  auto stage_bf16 = [&](int len, bool first, int cur, const void* (&q)[MAX_KINDS]) -> int {
+    GemmBatch gb{};
+    const bool apart = len > 1;   // diagonals kept apart
+    auto da = [&](const Kind& kd) { return apart ? reinterpret_cast<float*>(kd.xt[cur ^ 1]) : nullptr; };
+    gb.n = nk;
+    for (int k = 0; k < nk; ++k) {
+      const Kind& kd = kind[k];
+      GemmProblem& pr = gb.pr[k] = GemmProblem{};
+      pr.d = kd.gram, pr.p = kd.xw, pr.q = kd.xw, pr.c = kd.a, pr.scale = first ? kd.scale2 : nullptr;
+      pr.sym.diag = da(kd);
+    }
+    CANZ_HIP(CANZ_KERNEL_GRAM, launch_gram_bf16(gb, split, st), "gram kernel");
+    // the product of the symmetric images P (index ip of b) and Y with their diagonals
+    auto mul = [&](const Kind& kd, int ip, const void* y, const float* dy, void* c, float* dc) {
+      GemmProblem pr{};
+      pr.d = kd.poly, pr.p = kd.b[ip], pr.q = y, pr.c = c;
+      pr.sym.aux = y, pr.sym.aux2 = kd.b[ip], pr.sym.x = kd.db[ip], pr.sym.y = dy, pr.sym.diag = dc;
+      return pr;
+    };
+    int iq = -1;   // where the product of the polynomials so far lies
+    for (int i = 0; i < len; ++i) {
+      const bool last = i + 1 == len;
+      const int ib = iq == 0 ? 1 : 0, in = 3 - ib - (iq < 0 ? 3 - ib : iq);   // B_i, and (from the second on) the new product
+      for (int k = 0; k < nk; ++k) {
+        const Kind& kd = kind[k];
+        GemmProblem& pr = gb.pr[k] = GemmProblem{};
+        pr.d = kd.poly, pr.p = kd.a, pr.q = kd.a, pr.c = apart ? kd.b[ib] : static_cast<void*>(kd.bm);
+        pr.sym.aux = kd.a, pr.sym.x = da(kd), pr.sym.y = da(kd);
+        pr.sym.diag = apart ? kd.db[ib] : nullptr;
+      }
+      gb.n = nk;
+      CANZ_HIP(CANZ_KERNEL_POLY, launch_poly_bf16(gb, hp.a, hp.b, hp.c, split, st), "poly kernel");
+      gb.n = 0;
+      if (!last)
+        for (int k = 0; k < nk; ++k)
+          gb.pr[gb.n++] = mul(kind[k], ib, kind[k].a, da(kind[k]), kind[k].t, kind[k].dt);
+      if (iq >= 0)
+        for (int k = 0; k < nk; ++k)
+          gb.pr[gb.n++] = mul(kind[k], ib, kind[k].b[iq], kind[k].db[iq], kind[k].b[in], last ? nullptr : kind[k].db[in]);
+      if (gb.n > 0) CANZ_HIP(CANZ_KERNEL_POLY, launch_mul_bf16(gb, split, st), "product kernel (B A, Q)");
+      iq = iq < 0 ? ib : in;
+      if (last) break;
       gb.n = nk;
       for (int k = 0; k < nk; ++k)
-        gb.pr[k] = GemmProblem{kind[k].gram, kind[k].xw, kind[k].xw, kind[k].a, nullptr, nullptr,
-                               first_it ? kind[k].scale2 : nullptr};
-      CANZ_HIP(CANZ_KERNEL_GRAM, launch_gram_bf16_multi(gb, st), "gram kernel");
-      for (int k = 0; k < nk; ++k)
-        gb.pr[k] = GemmProblem{kind[k].poly, kind[k].a, kind[k].a, kind[k].bm, nullptr, kind[k].a, nullptr};
-      CANZ_HIP(CANZ_KERNEL_POLY, launch_poly_bf16_multi(gb, hp.a, hp.b, hp.c, st), "poly kernel");
+        gb.pr[k] = mul(kind[k], ib, kind[k].t, kind[k].dt, kind[k].a, da(kind[k]));
+      CANZ_HIP(CANZ_KERNEL_POLY, launch_mul_bf16(gb, split, st), "product kernel (B A B)");
+    }
+    for (int k = 0; k < nk; ++k) q[k] = apart ? kind[k].b[iq] : static_cast<const void*>(kind[k].bm);
+    return CANZ_OK;
+  };
+
+  int cur = 0;
+  for (size_t sg = 0; sg < stages.size(); ++sg) {
+    const bool first_it = sg == 0, last = sg + 1 == stages.size();
+    const void* q[MAX_KINDS] = {};
+    if (is_bf16) {
+      if (int rc = stage_bf16(stages[sg], first_it, cur, q)) return rc;
       if (!last) {
-        for (int k = 0; k < nk; ++k)
-          gb.pr[k] = GemmProblem{kind[k].upd, kind[k].bm, kind[k].xt[cur], kind[k].xw, kind[k].xt[cur ^ 1], nullptr,
-                                 first_it ? kind[k].scale : nullptr};
-        CANZ_HIP(CANZ_KERNEL_UPDATE, launch_update_bf16_multi(gb, st), "update kernel");
+        GemmBatch gb{};
+        gb.n = nk;
+        for (int k = 0; k < nk; ++k) {
+          const Kind& kd = kind[k];
+          GemmProblem& pr = gb.pr[k];
+          pr.d = kd.upd, pr.p = q[k], pr.q = kd.xt[cur], pr.c = kd.xw, pr.ct = kd.xt[cur ^ 1];
+          pr.scale = first_it ? kd.scale : nullptr;
+        }
+        CANZ_HIP(CANZ_KERNEL_UPDATE, launch_update_bf16(gb, split, st), "update kernel");
       }
     }
     for (int k = 0; k < nk; ++k) {
       const Kind& kd = kind[k];
       const float* sc1 = first_it ? kd.scale : nullptr;
       const float* sc2 = first_it ? kd.scale2 : nullptr;
-      if (!together) {
-        if (is_bf16) {
-          CANZ_HIP(CANZ_KERNEL_GRAM, launch_gram_bf16(kd.gram, kd.xw, kd.a, sc2, split, st), "gram kernel");
-          CANZ_HIP(CANZ_KERNEL_POLY, launch_poly_bf16(kd.poly, kd.a, kd.bm, hp.a, hp.b, hp.c, split, st), "poly kernel");
-          if (!last)
-            CANZ_HIP(CANZ_KERNEL_UPDATE,
-                     launch_update_bf16(kd.upd, kd.bm, kd.xt[cur], kd.xw, kd.xt[cur ^ 1], sc1, split, st), "update kernel");
-        } else {
-          CANZ_HIP(CANZ_KERNEL_GRAM, launch_gram_f32(kd.gram, kd.xw, kd.a, sc2, st), "gram kernel");
-          CANZ_HIP(CANZ_KERNEL_POLY, launch_poly_f32(kd.poly, kd.a, kd.bm, hp.a, hp.b, hp.c, st), "poly kernel");
-          if (!last)
-            CANZ_HIP(CANZ_KERNEL_UPDATE, launch_update_f32(kd.upd, kd.bm, kd.xt[cur], kd.xw, kd.xt[cur ^ 1], sc1, st),
-                     "update kernel");
-        }
+      if (!is_bf16) {
+        CANZ_HIP(CANZ_KERNEL_GRAM, launch_gram_f32(kd.gram, kd.xw, kd.a, sc2, st), "gram kernel");
+        CANZ_HIP(CANZ_KERNEL_POLY, launch_poly_f32(kd.poly, kd.a, kd.bm, hp.a, hp.b, hp.c, st), "poly kernel");
+        if (!last)
+          CANZ_HIP(CANZ_KERNEL_UPDATE, launch_update_f32(kd.upd, kd.bm, kd.xt[cur], kd.xw, kd.xt[cur ^ 1], sc1, st),
+                   "update kernel");
+        q[k] = kd.bm;
       }
       if (!last) continue;
       // last product, written in the caller's orientation: for the tall part the roles of
@@ -388,7 +500,7 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
         const int n = batches[lo + k].part[h].n();
         if (n == 0) continue;
         const Shape& s = kd.s0;
-        const T* bk = kd.bm + kd.first[h] * kd.a_elems;
+        const T* bk = static_cast<const T*>(q[k]) + kd.first[h] * kd.a_elems;
         const T* xk = kd.xt[cur] + kd.first[h] * kd.x_elems;
         const float* sk = sc1 ? sc1 + kd.first[h] : nullptr;
         const bool tall = kd.shape[h].tall;
@@ -421,9 +533,9 @@ extern "C" int canz_muon_workspace_bytes(const canz_group* g, int32_t n_groups, 
     if (int rc = check_group(g[i], i, false, hp->out_mode)) return rc;
   std::vector<Batch> batches;
   if (int rc = collect_batches(g, n_groups, hp->out_mode, false, batches)) return rc;
-  const std::vector<int> first = group_runs(batches, hp->precision);
+  const std::vector<int> first = group_runs(batches, *hp);
   for (size_t r = 0; r + 1 < first.size(); ++r)
-    need = std::max(need, run_bytes(batches, first[r], first[r + 1], hp->precision));
+    need = std::max(need, run_bytes(batches, first[r], first[r + 1], *hp));
   *bytes_out = need;
   return CANZ_OK;
 }
@@ -451,7 +563,7 @@ int muon_step_on(const canz_group* g, int32_t n_groups, const canz_muon_hparams*
   char* ws = static_cast<char*>(workspace);
   std::vector<Batch> batches;
   if (int rc = collect_batches(g, n_groups, hp->out_mode, true, batches)) return rc;
-  const std::vector<int> first = group_runs(batches, hp->precision);
+  const std::vector<int> first = group_runs(batches, *hp);
   for (size_t r = 0; r + 1 < first.size(); ++r) {
     const int rc = hp->precision == CANZ_PREC_BF16 ? run_batches<__bf16>(batches, first[r], first[r + 1], *hp, ws, st)
                                                    : run_batches<float>(batches, first[r], first[r + 1], *hp, ws, st);
