@@ -10,8 +10,10 @@
 #include <cstdint>
 
 #include "canz.h"
+#include "canz_internal.h"
 #include "device_util.h"
 #include "kernels.h"
+#include "panel_layout.h"
 
 namespace canz {
 namespace f32mfma {
@@ -303,6 +305,87 @@ static __global__ __launch_bounds__(NTH) void k_unpad(Shape s, PtrTable dst, con
     const int idx = e * NTH + t, row = r0 + (idx >> 6), col = c0 + (idx & 63);
     if (row < s.rows && col < s.cols) to[static_cast<int64_t>(row) * s.cols + col] = from[static_cast<int64_t>(row) * cp + col];
   }
+}
+
+// one 64 x 64 fp32 tile in LDS -> the 8-element chunks of its bf16 panel image, straight (dst rows = tile rows) or
+// transposed (dst rows = tile columns); (r0, c0): the tile's place in the matrix, kc: row length of the image
+static __device__ __forceinline__ void tile_to_panels(const float (*tile)[65], __bf16* __restrict__ dst, int64_t r0, int64_t c0,
+                                               int64_t kc, bool transposed, int t) {
+  const int cv = (t & 7) * 8;
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    const int rl = (t >> 3) + half * 32;
+    bf16x8 o;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = static_cast<__bf16>(transposed ? tile[cv + e][rl] : tile[rl][cv + e]);
+    *reinterpret_cast<bf16x8*>(dst + (transposed ? panel_chunk_off(c0 + rl, r0 + cv, kc) : panel_chunk_off(r0 + rl, c0 + cv, kc))) = o;
+  }
+}
+
+// S[row][col] <- S[col][row] for row > col of the caller's dense d x d matrices: the symmetric statistic is computed
+// on and above the diagonal tiles only.  One block per 64 x 64 tile on or below the diagonal (blockIdx.y >= blockIdx.x).
+static __global__ __launch_bounds__(NTH) void k_mirror(PtrTable stat, int64_t d) {
+  __shared__ float tile[64][65];
+  if (blockIdx.y < blockIdx.x) return;
+  const int b = blockIdx.z, r0 = blockIdx.y * 64, c0 = blockIdx.x * 64, t = threadIdx.x;
+  float* m = static_cast<float*>(stat.p[b]);
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {   // the tile above the diagonal that mirrors this one: rows c0.., columns r0..
+    const int idx = e * NTH + t, r = idx >> 6, c = idx & 63;
+    const int64_t row = c0 + r, col = r0 + c;
+    tile[r][c] = row < d && col < d ? m[row * d + col] : 0.f;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int idx = e * NTH + t, r = idx >> 6, c = idx & 63;
+    const int64_t row = r0 + r, col = c0 + c;
+    if (row < d && col < row) m[row * d + col] = tile[c][r];
+  }
+}
+
+inline int64_t pad256(int64_t x) { return (x + PAD - 1) / PAD * PAD; }
+
+// S <- beta S + gscale X X^T of the caller's dense fp32 d x d matrices on the bf16 matrix cores, X [nb][d2][k2] bf16 panels:
+// the operands are bf16 values themselves, every product is exact in fp32 and the sums are fp32, so nothing is lost
+// against the fp32 kernel, at a fraction of its time.  The product is the "last product" of the Muon step's kernels:
+// old * decay + factor * product in place (beta = 0: factor * product, whatever S held).
+// k_piece: k per launch (a multiple of 256; k2 for all at once).  A sum accumulated in one go loses with its length what the
+// fp32 kernel's folds keep: at k = 3072 the error against 64 bits is 2.9e-7 in one piece and 1.7e-7 in pieces of 1024
+// (fp32 kernel: 1.6e-7), at the cost of a pass over the statistic per piece.
+inline int statistic_bf16(int kind, const PtrTable& tab, int64_t d, int64_t d2, int64_t k2, int64_t k_piece, int nb, float beta,
+                          float gscale, const __bf16* x, hipStream_t st) {
+  Shape sq{};
+  sq.rows = d, sq.cols = d, sq.m = d, sq.n = d, sq.mp = d2, sq.np = d2, sq.tp = 1, sq.wfrag = d;
+  OutSpec so{};
+  so.out = tab, so.out_dtype = CANZ_DT_F32, so.neg_lr_scale = gscale;
+  const SplitWs no_split{nullptr, 0};
+  // Only the tiles on and above the diagonal, mirrored afterwards, where that pays: the products it saves (about
+  // 0.65 us per 32-long k-step of a tile, a round of tiles on 256 CUs at a time) against one more pass over the
+  // statistic at some 4 TB/s that does not overlap with anything.  Long sums win (25600 x 5120: 3.9 -> 1.3 ms),
+  // short ones do not (3072 x 1024: the mirror pass costs what the products save).
+  const int64_t t256 = d2 / 256;
+  const double saved_us = static_cast<double>(t256 * (t256 - 1) / 2 * nb) / 256.0 * static_cast<double>(k2 / 32) * 0.65;
+  const double mirror_us = 15.0 + static_cast<double>(d) * static_cast<double>(d) * nb * 4.0 / 4.0e6;
+  const bool upper = saved_us > 1.5 * mirror_us;
+  for (int64_t k0 = 0; k0 < k2; k0 += k_piece) {
+    so.decay = k0 == 0 ? beta : 1.f;
+    so.out_mode = so.decay == 0.f ? CANZ_OUT_DELTA : CANZ_OUT_PARAM;
+    const GemmDims sd{d2, d2, k2 - k0 < k_piece ? k2 - k0 : k_piece, k2, k2, d2 * k2, d2 * k2, nb};
+    const __bf16* xk = x + k0 / PANEL_K * PANEL_ELEMS;
+    if (upper)
+      CANZ_HIP(kind, launch_final_sym_bf16(sd, xk, no_split, sq, so, st), "statistics kernel (bf16 operands)");
+    else
+      CANZ_HIP(kind, launch_final_bf16(sd, xk, xk, nullptr, no_split, sq, so, st), "statistics kernel (bf16 operands)");
+  }
+  if (upper) {
+    prof_mark(st, kind, true);
+    const unsigned t64 = static_cast<unsigned>((d + 63) / 64);
+    hipLaunchKernelGGL(k_mirror, dim3(t64, t64, static_cast<unsigned>(nb)), dim3(NTH), 0, st, tab, d);
+    prof_mark(st, kind, false);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "statistic mirror: %s", hipGetErrorString(e));
+  }
+  return CANZ_OK;
 }
 
 }  // namespace f32mfma

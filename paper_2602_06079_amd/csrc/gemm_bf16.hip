@@ -53,7 +53,8 @@ constexpr int GROUP_M = 4;       // tile rows per raster band
 constexpr int N_XCD = 8;
 static_assert(BM == PANEL_ROWS && BK == PANEL_K, "tile = panel");
 
-enum { EPI_GRAM = 0, EPI_POLY = 1, EPI_UPDATE = 2, EPI_FINAL = 3, EPI_FINAL_SYM = 4, EPI_MUL = 5, EPI_POLY_APART = 6, EPI_GRAM_APART = 7 };
+enum { EPI_GRAM = 0, EPI_POLY = 1, EPI_UPDATE = 2, EPI_FINAL = 3, EPI_FINAL_SYM = 4, EPI_MUL = 5, EPI_POLY_APART = 6, EPI_GRAM_APART = 7,
+       EPI_H2 = 8, EPI_H2_F32 = 9 };
 // EPI_FINAL_SYM: the last-product epilogue (the caller's dense buffers) over the tiles on and above the diagonal of a
 // symmetric result only; the caller mirrors them into the lower triangle afterwards.
 // EPI_GRAM_APART, EPI_POLY_APART: the diagonals of the matrices are kept apart (kernels.h: SymSpec).
@@ -61,7 +62,10 @@ enum { EPI_GRAM = 0, EPI_POLY = 1, EPI_UPDATE = 2, EPI_FINAL = 3, EPI_FINAL_SYM 
 constexpr bool epi_poly(int epi) { return epi == EPI_POLY || epi == EPI_POLY_APART; }
 constexpr bool epi_apart(int epi) { return epi == EPI_POLY_APART || epi == EPI_MUL; }   // reads diagonals
 constexpr bool epi_mspace(int epi) { return epi == EPI_GRAM || epi == EPI_GRAM_APART || epi_poly(epi) || epi == EPI_MUL; }
-constexpr bool epi_symmetric(int epi) { return epi_mspace(epi) || epi == EPI_FINAL_SYM; }
+// EPI_H2, EPI_H2_F32: products of symmetric commuting matrices of two fp16 terms (kernels.h: launch_split2_*).
+constexpr bool epi_f16(int epi) { return epi == EPI_H2 || epi == EPI_H2_F32; }
+constexpr bool epi_terms(int epi) { return epi_f16(epi); }   // operands of several terms
+constexpr bool epi_symmetric(int epi) { return epi_mspace(epi) || epi == EPI_FINAL_SYM || epi_f16(epi); }
 constexpr bool epi_final(int epi) { return epi == EPI_FINAL || epi == EPI_FINAL_SYM; }
 
 struct EpiArgs {
@@ -69,7 +73,7 @@ struct EpiArgs {
   void* ct;                // UPDATE: transposed output [nb][N][M] panels
   SymSpec sym;             // GRAM/POLY/MUL: how the symmetric matrices are represented (kernels.h)
   const float* scale;      // per-matrix factor applied to the accumulator, or nullptr
-  float ca, cb, cc;        // POLY coefficients
+  float ca, cb, cc;        // POLY coefficients; H2: factor of this problem, what stands for 1 in the result
   // schedule of the persistent blocks (see launch()): full rounds of whole tiles, then the
   // `left` remaining tiles, each cut into `splits` k-slices that different blocks compute
   int full_rounds, left, splits, main_grid;
@@ -77,7 +81,10 @@ struct EpiArgs {
 };
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 #define CANZ_LDS(p) ((__attribute__((address_space(3))) void*)(p))
 #define CANZ_GLB(p) ((const __attribute__((address_space(1))) void*)(p))
@@ -145,6 +152,27 @@ __device__ __forceinline__ float sym_diagonal(float acc, float dx, float dy, con
   if (EPI == EPI_MUL) return __builtin_fmaf(dx, dy, acc);
   return EPI == EPI_POLY_APART ? acc + __builtin_fmaf(__builtin_fmaf(e.cc, dx, e.cb), dx, e.ca) : acc + e.ca;
 }
+
+// A value as two fp16 terms in the two halves of one register, and back.  Taking the place of the fp32 value, they
+// cost the epilogue no registers.  The value is made opaque: the compiler may otherwise fuse the operation that
+// produced it into one of the two conversions (a mixed-precision fma that rounds once, to fp16) and not into the other, and the
+// terms would then differ from the value by an ulp of the first one wherever the two roundings disagree.
+__device__ __forceinline__ float two_terms(float v) {
+  asm volatile("" : "+v"(v));
+  f16x2 h;
+  h[0] = static_cast<_Float16>(v);
+  h[1] = static_cast<_Float16>(v - static_cast<float>(h[0]));
+  return __builtin_bit_cast(float, h);
+}
+__device__ __forceinline__ float from_two_terms(float t) {
+  const f16x2 h = __builtin_bit_cast(f16x2, t);
+  return static_cast<float>(h[0]) + static_cast<float>(h[1]);
+}
+// the low (term 0) or high (term 1) halves of two such registers, packed
+__device__ __forceinline__ unsigned pick_term(float a, float b, unsigned sel) {
+  return __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, b), __builtin_bit_cast(unsigned, a), sel);
+}
+__device__ __forceinline__ unsigned term_selector(int term) { return term ? 0x07060302u : 0x05040100u; }
 
 // Epilogue of one 256 x 256 tile held in the accumulators of the block's four wavefronts
 // (shared by the GEMM kernel and by the kernel that finishes k-split tiles).
@@ -271,6 +299,102 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
     }
   };
 
+  if constexpr (EPI == EPI_H2_F32) {
+    // fp32 result (scaled above), row-major: both halves straight from the accumulators
+    float* C = static_cast<float*>(e.c) + static_cast<int64_t>(b) * d.M * d.N;
+#pragma unroll
+    for (int it = 0; it < 4; ++it)
+#pragma unroll
+      for (int jt = 0; jt < 4; ++jt) {
+        const int64_t row0 = tm * BM + wm * 128 + it * 32 + 4 * lh, col = tn * BN + wn * 128 + jt * 32 + lj;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          f32x4 v;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) v[q] = acc[it][jt][4 * g + q];
+          if (tm != tn || wm <= wn)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) C[(row0 + 8 * g + q) * d.N + col] = v[q];
+          if (tm != tn || wm < wn) *reinterpret_cast<f32x4*>(C + col * d.N + row0 + 8 * g) = v;
+        }
+      }
+    return;
+  }
+  if constexpr (EPI == EPI_H2) {
+    if (e.c == nullptr) return;   // never: a branch that parts the epilogue from the k loop's block, see POLY above
+    // Two terms per element, straight and mirrored, through the staging area as the bf16 images below (whose offsets
+    // these are); then, if asked for, the same for 5/4 I - 1/4 C.
+    int s_base[2], t_base[4];
+#pragma unroll
+    for (int g1 = 0; g1 < 2; ++g1)
+      s_base[g1] = (4 * lh + (lane & 1)) * 32 + ((((lj >> 3) ^ (2 * g1 + lh)) & 3) << 3) + (lj & 6);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) t_base[g] = lj * 32 + ((g ^ ((lj >> 2) & 3)) << 3) + 4 * lh;
+    const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
+#pragma unroll
+    for (int it = 0; it < 4; ++it)
+#pragma unroll
+      for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[it][jt][r] = two_terms(e.ca * acc[it][jt][r]);
+    const bool diagonal = tm == tn && wm == wn;
+    const int images = e.ct ? 4 : 2;
+#pragma unroll 1
+    for (int n = 0; n < images; ++n) {   // term 0 and 1 of C, then of 5/4 I - 1/4 C
+        if (n == 2) {
+#pragma unroll
+          for (int it = 0; it < 4; ++it)
+#pragma unroll
+            for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) {
+                const bool one = it == jt && diagonal && 8 * (r >> 2) + (r & 3) + 4 * lh == lj;
+                acc[it][jt][r] = two_terms((one ? 1.25f * e.cb : 0.f) - 0.25f * from_two_terms(acc[it][jt][r]));
+              }
+        }
+        const int term = n & 1;
+        __bf16* C = static_cast<__bf16*>(n < 2 ? e.c : e.ct) + static_cast<int64_t>(b) * 2 * d.M * d.N;
+        const unsigned pick = term_selector(term);
+        const int64_t kb = term * (d.N >> 5);
+        auto flush = [&](int64_t row_block, int64_t kblock0, int half_rows) {
+#pragma unroll
+          for (int k4 = 0; k4 < 4; ++k4) {
+            __bf16* dst = C + (row_block * (d.N >> 4) + kblock0 + k4) * PANEL_ELEMS + half_rows * 128 * PANEL_K;
+#pragma unroll
+            for (int x = 0; x < 8; ++x)
+              *reinterpret_cast<u32x4*>(dst + (x * 64 + lane) * 8) = *reinterpret_cast<const u32x4*>(stage + k4 * 4096 + (x * 64 + lane) * 8);
+          }
+        };
+        if (tm != tn || wm <= wn) {
+#pragma unroll
+          for (int it = 0; it < 4; ++it)
+#pragma unroll
+            for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+              for (int rp = 0; rp < 8; ++rp) {
+                const unsigned mine = pick_term(acc[it][jt][2 * rp], acc[it][jt][2 * rp + 1], pick);
+                const unsigned pk = __builtin_amdgcn_perm(lane_xor1(mine), mine, pair_sel);
+                const int g = rp >> 1, p = rp & 1;
+                *reinterpret_cast<unsigned*>(stage + jt * 4096 + (it * 32 + 8 * g + 2 * p) * 32 + s_base[g & 1]) = pk;
+              }
+          flush(tm, kb + 8 * tn + 4 * wn, wm);
+        }
+        if (tm != tn || wm < wn) {
+#pragma unroll
+          for (int it = 0; it < 4; ++it)
+#pragma unroll
+            for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+              for (int g = 0; g < 4; ++g) {
+                const u32x2 w = {pick_term(acc[it][jt][4 * g], acc[it][jt][4 * g + 1], pick),
+                                 pick_term(acc[it][jt][4 * g + 2], acc[it][jt][4 * g + 3], pick)};
+                *reinterpret_cast<u32x2*>(stage + it * 4096 + jt * 32 * 32 + t_base[g]) = w;
+              }
+          flush(tn, kb + 8 * tm + 4 * wm, wn);
+        }
+    }
+    return;
+  }
   if (!epi_final(EPI)) {
     // ---- straight image: element (i, j) of C is (row i, k = j) of the result's panels.
     // A 16-byte chunk is 8 consecutive j of one row, i.e. one value from each of 8 lanes:
@@ -499,6 +623,30 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
   }
 }
 
+template <int EPI>
+__device__ __forceinline__ f32x16 mma(bf16x8 a, bf16x8 b, f32x16 c) {
+  if constexpr (epi_f16(EPI))
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+// Element offset of the next panel of an operand of several terms: nk panels of the first segment's term, then of the
+// second's, ...  No branches: one in the k loop would cost the compiler its count of the loads in flight.  Behind the
+// last segment the code reads 0: a harmless re-read of term 0.
+struct TermWalk {
+  int64_t off, nk;
+  unsigned code;
+  int left;
+  __device__ __forceinline__ TermWalk(unsigned c, int64_t n) : off((c & 15) * n * PANEL_ELEMS), nk(n), code(c), left(static_cast<int>(n)) {}
+  __device__ __forceinline__ void next() {
+    const bool end = --left == 0;
+    code = end ? code >> 4 : code;
+    off = end ? (code & 15) * nk * PANEL_ELEMS : off + PANEL_ELEMS;
+    left = end ? static_cast<int>(nk) : left;
+  }
+};
+
 // Operands of a launch: one product (the usual case), or several of different shapes.
 struct OneProblem {
   static constexpr bool multi = false;
@@ -583,27 +731,37 @@ __global__ __launch_bounds__(NTHREADS) void k_gemm_nt_bf16(Args args, EpiArgs e_
     d = pr.d;
     P = static_cast<const __bf16*>(pr.p), Q = static_cast<const __bf16*>(pr.q);
     e.c = pr.c, e.ct = pr.ct, e.sym = pr.sym, e.scale = pr.scale;
+    if (EPI == EPI_H2) e.ca = pr.factor;
     logical -= args.begin[j];
     tiles_n = static_cast<int>(d.N / BN), tiles_m = static_cast<int>(d.M / BM);
     per_batch = epi_symmetric(EPI) ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
     nk_all = static_cast<int>(d.K / BK);
     nk = nk_all;
   }
+  if constexpr (epi_terms(EPI)) nk = nk_all * d.nseg;
   int b, tm, tn;
   decode_tile<EPI>(logical, tiles_m, tiles_n, per_batch, b, tm, tn);
 
   // ---- global -> LDS: panel (tile row, k-step) is 16 KiB contiguous; wavefront w copies the
   //      1 KiB pieces w, w+4, w+8, w+12 of both panels, lane l the 16 bytes at l * 16.
   const int64_t nkb = d.K / BK;
-  const __bf16* pl = P + static_cast<int64_t>(b) * d.sp + (static_cast<int64_t>(tm) * nkb + k_begin) * PANEL_ELEMS + wave * 512 + lane * 8;
-  const __bf16* ql = Q + static_cast<int64_t>(b) * d.sq + (static_cast<int64_t>(tn) * nkb + k_begin) * PANEL_ELEMS + wave * 512 + lane * 8;
+  const int64_t nkp = d.ldp / BK, nkq = d.ldq / BK;   // panels per row block
+  const __bf16* pl = P + static_cast<int64_t>(b) * d.sp + (static_cast<int64_t>(tm) * nkp + k_begin) * PANEL_ELEMS + wave * 512 + lane * 8;
+  const __bf16* ql = Q + static_cast<int64_t>(b) * d.sq + (static_cast<int64_t>(tn) * nkq + k_begin) * PANEL_ELEMS + wave * 512 + lane * 8;
+  // operands of several terms: where the next panel of each is (the panels are requested in order)
+  TermWalk wp(d.pseg, nkb), wq(d.qseg, nkb);
   // one of the 8 direct loads of a stage: idx 0..3 -> P pieces, 4..7 -> Q pieces
   auto fetch_one = [&](__bf16* st, int64_t kt, int idx) {
     const int g = idx & 3;
-    if (idx < 4)
-      __builtin_amdgcn_global_load_lds(CANZ_GLB(pl + kt * PANEL_ELEMS + g * 2048), CANZ_LDS(st + wave * 512 + g * 2048), 16, 0, 0);
-    else
-      __builtin_amdgcn_global_load_lds(CANZ_GLB(ql + kt * PANEL_ELEMS + g * 2048), CANZ_LDS(st + QOFF + wave * 512 + g * 2048), 16, 0, 0);
+    if (idx < 4) {
+      const int64_t off = epi_terms(EPI) ? wp.off : kt * PANEL_ELEMS;
+      __builtin_amdgcn_global_load_lds(CANZ_GLB(pl + off + g * 2048), CANZ_LDS(st + wave * 512 + g * 2048), 16, 0, 0);
+      if (epi_terms(EPI) && g == 3) wp.next();
+    } else {
+      const int64_t off = epi_terms(EPI) ? wq.off : kt * PANEL_ELEMS;
+      __builtin_amdgcn_global_load_lds(CANZ_GLB(ql + off + g * 2048), CANZ_LDS(st + QOFF + wave * 512 + g * 2048), 16, 0, 0);
+      if (epi_terms(EPI) && g == 3) wq.next();
+    }
   };
   auto fetch = [&](__bf16* st, int64_t kt) {
 #pragma unroll
@@ -627,9 +785,9 @@ __global__ __launch_bounds__(NTHREADS) void k_gemm_nt_bf16(Args args, EpiArgs e_
     const int i = idx >> 2, j = idx & 3;
     if (decltype(first)::value) {
       const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][i], fb[set][j], zero, 0, 0, 0);
+      acc[i][j] = mma<EPI>(fa[set][i], fb[set][j], zero);
     } else {
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][i], fb[set][j], acc[i][j], 0, 0, 0);
+      acc[i][j] = mma<EPI>(fa[set][i], fb[set][j], acc[i][j]);
     }
   };
 
@@ -830,6 +988,7 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
     d = pr.d;
     P = static_cast<const __bf16*>(pr.p), Q = static_cast<const __bf16*>(pr.q);
     e.c = pr.c, e.ct = pr.ct, e.sym = pr.sym, e.scale = pr.scale;
+    if (EPI == EPI_H2) e.ca = pr.factor;
     logical -= args.begin[j];
   } else {
     d = args.d, P = args.P, Q = args.Q;
@@ -847,22 +1006,26 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
   const int lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int nk = static_cast<int>(d.K / BK);
   const int64_t nkb = d.K / BK;
+  const int nk = static_cast<int>(nkb) * (epi_terms(EPI) ? d.nseg : 1);
+  const int64_t nkp = d.ldp / BK, nkq = d.ldq / BK;   // panels per row block
 
   // global -> LDS: a stage is 16 pieces of 1 KiB (8 of P, 8 of Q); wavefront w copies the
   // pieces w and w + 4 of both, lane l the 16 bytes at l * 16
-  const __bf16* pl = P + static_cast<int64_t>(b) * d.sp + (static_cast<int64_t>(tm >> 1) * nkb) * PANEL_ELEMS +
+  const __bf16* pl = P + static_cast<int64_t>(b) * d.sp + (static_cast<int64_t>(tm >> 1) * nkp) * PANEL_ELEMS +
                      (tm & 1) * (SM * BK) + wave * 512 + lane * 8;
-  const __bf16* ql = Q + static_cast<int64_t>(b) * d.sq + (static_cast<int64_t>(tn >> 1) * nkb) * PANEL_ELEMS +
+  const __bf16* ql = Q + static_cast<int64_t>(b) * d.sq + (static_cast<int64_t>(tn >> 1) * nkq) * PANEL_ELEMS +
                      (tn & 1) * (SM * BK) + wave * 512 + lane * 8;
+  TermWalk wp(d.pseg, nkb), wq(d.qseg, nkb);
   auto fetch = [&](__bf16* st, int kt) {
     const int64_t off = static_cast<int64_t>(kt < nk ? kt : nk - 1) * PANEL_ELEMS;  // past the end: a harmless re-read
+    const int64_t po = epi_terms(EPI) ? wp.off : off, qo = epi_terms(EPI) ? wq.off : off;
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
-      __builtin_amdgcn_global_load_lds(CANZ_GLB(pl + off + g * 2048), CANZ_LDS(st + wave * 512 + g * 2048), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds(CANZ_GLB(ql + off + g * 2048), CANZ_LDS(st + SM * BK + wave * 512 + g * 2048), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(CANZ_GLB(pl + po + g * 2048), CANZ_LDS(st + wave * 512 + g * 2048), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(CANZ_GLB(ql + qo + g * 2048), CANZ_LDS(st + SM * BK + wave * 512 + g * 2048), 16, 0, 0);
     }
+    if (epi_terms(EPI)) wp.next(), wq.next();
   };
 
   f32x16 acc[2][2];
@@ -889,7 +1052,7 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk][i], fb[kk][j], acc[i][j], 0, 0, 0);
+          acc[i][j] = mma<EPI>(fa[kk][i], fb[kk][j], acc[i][j]);
   };
   // One k-step on stage `cur`: the 4 loads of the following step may stay in flight; after the
   // barrier every wavefront has finished the step before, whose stage `nxt2` then receives step kt + 2.
@@ -987,6 +1150,74 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
             acc[i][i][r] = sym_diagonal<EPI>(acc[i][i][r], dx, dy, e);
       }
     }
+  } else if constexpr (EPI == EPI_H2_F32) {
+    const float sc1 = e.scale[b];
+    float* C = static_cast<float*>(e.c) + static_cast<int64_t>(b) * d.M * d.N;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int64_t row0 = row_w + 32 * i + 4 * lh, col = col_w + 32 * j + lj;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          f32x4 v;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) v[q] = sc1 * acc[i][j][4 * g + q];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) C[(row0 + 8 * g + q) * d.N + col] = v[q];
+          if (tm != tn) *reinterpret_cast<f32x4*>(C + col * d.N + row0 + 8 * g) = v;
+        }
+      }
+    return;
+  } else if constexpr (EPI == EPI_H2) {
+    const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = two_terms(e.ca * acc[i][j][r]);
+    const bool diagonal = tm == tn && wm == wn;
+    const int images = e.ct ? 4 : 2;
+#pragma unroll 1
+    for (int n = 0; n < images; ++n) {   // term 0 and 1 of C, then of 5/4 I - 1/4 C
+        if (n == 2) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) {
+                const bool one = i == j && diagonal && 8 * (r >> 2) + (r & 3) + 4 * lh == lj;
+                acc[i][j][r] = two_terms((one ? 1.25f * e.cb : 0.f) - 0.25f * from_two_terms(acc[i][j][r]));
+              }
+        }
+        const int term = n & 1;
+        __bf16* C = static_cast<__bf16*>(n < 2 ? e.c : e.ct) + static_cast<int64_t>(b) * 2 * d.M * d.N;
+        const unsigned pick = term_selector(term);
+        const int64_t kb = term * (d.N >> 5), nkc = d.N >> 4;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            __bf16* const at = C + ((row_w >> 8) * nkc + kb + ((col_w + 32 * j) >> 5)) * PANEL_ELEMS + ((row_w & 255) + 32 * i) * PANEL_K;
+            __bf16* const tt = C + ((col_w >> 8) * nkc + kb + ((row_w + 32 * i) >> 5)) * PANEL_ELEMS + ((col_w & 255) + 32 * j) * PANEL_K;
+#pragma unroll
+            for (int rp = 0; rp < 8; ++rp) {
+              const unsigned mine = pick_term(acc[i][j][2 * rp], acc[i][j][2 * rp + 1], pick);
+              const unsigned pk = __builtin_amdgcn_perm(lane_xor1(mine), mine, pair_sel);
+              *reinterpret_cast<unsigned*>(at + s_lane[(rp >> 1) & 1] + (8 * (rp >> 1) + 2 * (rp & 1)) * PANEL_K) = pk;
+            }
+            if (tm != tn)
+#pragma unroll
+              for (int g = 0; g < 4; ++g) {
+                const u32x2 w = {pick_term(acc[i][j][4 * g], acc[i][j][4 * g + 1], pick),
+                                 pick_term(acc[i][j][4 * g + 2], acc[i][j][4 * g + 3], pick)};
+                *reinterpret_cast<u32x2*>(tt + t_lane[g]) = w;
+              }
+          }
+    }
+    return;
   } else if (e.scale) {
     const float sc1 = e.scale[b];
 #pragma unroll
@@ -1158,7 +1389,7 @@ template <int EPI>
 int64_t large_share(int64_t tiles, int64_t cus, int64_t longest_k) {
   const int64_t left = tiles % cus;
   constexpr bool msquare = epi_poly(EPI) || EPI == EPI_MUL;
-  if (longest_k > (msquare ? SMALL_MAX_K_MSPACE : SMALL_MAX_K)) return tiles;
+  if (!epi_terms(EPI) && longest_k > (msquare ? SMALL_MAX_K_MSPACE : SMALL_MAX_K)) return tiles;
   // a polynomial product (k = m, the shortest k range of the step) of less than two rounds runs faster on small
   // tiles throughout: 59.6 -> 52.4 us on 26 matrices of 1024 x 1024; the same rule costs the Gram product 7 %
   if (msquare && tiles < 2 * cus && longest_k <= SMALL_ALL_MAX_K) return 0;
@@ -1193,7 +1424,7 @@ hipError_t launch(const GemmDims& d, const void* P, const void* Q, EpiArgs e, co
   e.full_rounds = static_cast<int>(tiles / cus);
   e.left = static_cast<int>(tiles % cus);
   e.splits = 1;
-  if (e.left > 0 && w.partial) {
+  if (e.left > 0 && w.partial && !epi_terms(EPI)) {
     const int64_t by_blocks = std::min<int64_t>(cus, w.max_blocks) / e.left;
     const int64_t by_k = (d.K / BK) / 8;
     const int64_t sp = std::max<int64_t>(1, std::min<int64_t>({by_blocks, by_k, 8}));
@@ -1209,7 +1440,7 @@ hipError_t launch(const GemmDims& d, const void* P, const void* Q, EpiArgs e, co
   if (whole > 0)
     hipLaunchKernelGGL((k_gemm_nt_bf16<EPI, false, OneProblem>), dim3(static_cast<unsigned>(e.main_grid)), dim3(NTHREADS),
                        0, st, one, e, s, o);
-  if (e.splits > 1) {
+  if constexpr (!epi_terms(EPI)) if (e.splits > 1) {
     hipLaunchKernelGGL((k_gemm_nt_bf16<EPI, true, OneProblem>), dim3(static_cast<unsigned>(e.left * e.splits)),
                        dim3(NTHREADS), 0, st, one, e, s, o);
     hipLaunchKernelGGL((k_split_finish<EPI>), dim3(static_cast<unsigned>(e.left)), dim3(NTHREADS), 0, st, d, e, s, o);
@@ -1260,6 +1491,7 @@ hipError_t launch_problems(const GemmBatch& g, EpiArgs e, const SplitWs& w, hipS
   if (g.n != 1) return launch_multi<EPI>(g, e, st);
   const GemmProblem& pr = g.pr[0];
   e.c = pr.c, e.ct = pr.ct, e.sym = pr.sym, e.scale = pr.scale;
+  if (EPI == EPI_H2) e.ca = pr.factor;
   return launch<EPI>(pr.d, pr.p, pr.q, e, w, Shape{}, OutSpec{}, st);
 }
 }  // namespace
@@ -1277,6 +1509,16 @@ hipError_t launch_poly_bf16(const GemmBatch& g, float ca, float cb, float cc, co
 
 hipError_t launch_mul_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st) {
   return launch_problems<EPI_MUL>(g, EpiArgs{}, w, st);
+}
+
+hipError_t launch_split2_sym(const GemmBatch& g, float one, hipStream_t st) {
+  EpiArgs e{};
+  e.cb = one;
+  return launch_problems<EPI_H2>(g, e, SplitWs{nullptr, 0}, st);
+}
+
+hipError_t launch_split2_sym_f32(const GemmBatch& g, hipStream_t st) {
+  return launch_problems<EPI_H2_F32>(g, EpiArgs{}, SplitWs{nullptr, 0}, st);
 }
 
 hipError_t launch_update_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st) {

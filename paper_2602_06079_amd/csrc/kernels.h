@@ -81,9 +81,14 @@ hipError_t launch_apply(const Shape& s, int nb, const T* x_straight, int64_t ld,
 // ---- bf16 MFMA GEMMs -------------------------------------------------------------
 struct GemmDims {
   int64_t M, N, K;          // multiples of PAD
-  int64_t ldp, ldq;         // row strides of P [M][K] and Q [N][K]
+  int64_t ldp, ldq;         // row lengths of P and Q (K, or more where the product runs over a part of their columns)
   int64_t sp, sq;           // batch strides
   int nb;
+  // Operands of several terms (launch_split_*): an operand of t terms is a panel matrix of t * K columns, term i in the
+  // columns i K .. ; the product runs over nseg segments of K, segment s multiplying term (pseg >> 4 s) & 15 of P
+  // with term (qseg >> 4 s) & 15 of Q, all into one accumulator.
+  int nseg;
+  unsigned pseg, qseg;
 };
 // Scratch for the k-split of left-over tiles: fp32 accumulators of up to max_blocks blocks
 // (256 KiB each), written by the split launch and read by the kernel that finishes the tiles.
@@ -119,6 +124,7 @@ struct GemmProblem {
   void* ct;            // UPDATE: the transposed image
   SymSpec sym;         // GRAM, POLY, MUL
   const float* scale;  // per-matrix factor or nullptr
+  float factor;        // launch_split2_sym: factor of the result
 };
 struct GemmBatch {
   int n;
@@ -145,6 +151,22 @@ hipError_t launch_final_bf16(const GemmDims& d, const void* p, const void* q, co
 // written; the elements below the diagonal tiles are left as they were (the caller mirrors them)
 hipError_t launch_final_sym_bf16(const GemmDims& d, const void* x, const SplitWs& w, const Shape& s, const OutSpec& o,
                                  hipStream_t st);
+
+// ---- fp32 products on the 16-bit matrix cores ---------------------------------------
+// A value of 24 bits is the sum of two fp16 values (11 bits and a sign each: 22 to 23 bits, exponents permitting) or of three
+// bf16 values (8 bits each).  The products of the terms are exact in fp32 and are added up in fp32, the small ones first,
+// K / 16 roundings per segment where the fp32 MFMA rounds K / 2 times.
+// Two fp16 terms, for matrices of known magnitude (symmetric, commuting; P and Q [nb][M][2 K], scaled so that no entry
+// reaches 65504).  Three products of terms: the fourth, of the two second ones, is 2^-22 of the result and shows only
+// where the sums are too short for fp32 rounding to count (d <= 256: it is included there).
+//   c  [nb][M][2 N] = factor * P Q          ct (or nullptr) = 5/4 one I - 1/4 c, one: what stands for 1 in c
+hipError_t launch_split2_sym(const GemmBatch& g, float one, hipStream_t st);
+//   c  [nb][M][N] fp32, row-major = scale[b] * P Q
+hipError_t launch_split2_sym_f32(const GemmBatch& g, hipStream_t st);
+inline GemmDims split2_dims(int64_t d, int nb) {
+  if (d <= 256) return GemmDims{d, d, d, 2 * d, 2 * d, 2 * d * d, 2 * d * d, nb, 4, 0x0011u, 0x0101u};
+  return GemmDims{d, d, d, 2 * d, 2 * d, 2 * d * d, 2 * d * d, nb, 3, 0x001u, 0x010u};
+}
 
 // ---- fp32 verification GEMMs (same contracts, float storage) ----------------------
 hipError_t launch_gram_f32(const GemmDims& d, const void* xw, void* a_out, const float* scale2, hipStream_t st);

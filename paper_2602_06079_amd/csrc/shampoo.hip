@@ -3,8 +3,8 @@
 // App. B.3), per matrix:
 //   L <- beta L + G G^T,  R <- beta R + G^T G,
 //   O = (L + eps I)^(-1/4) G (R + eps I)^(-1/4),  P <- P (1 - lr wd) - lr O  (or Delta W = -lr O).
-// Everything is fp32 (the statistics span many orders of magnitude; bf16 would lose the small
-// eigenvalues the inverse root amplifies), on v_mfma_f32_32x32x2_f32.
+// State and results are fp32 (the statistics span many orders of magnitude; bf16 would lose the small
+// eigenvalues the inverse root amplifies).
 //
 // All products have the form C[i][j] = sum_k P[i][k] Q[j][k] with both operands contiguous
 // along k: the statistics are Gram products of G in its two orientations (both are written by
@@ -21,8 +21,23 @@
 // last one also writes the next T).  The round count is fixed by the caller: no test of
 // convergence is read back, so the step never synchronises and can be captured in a graph.
 //
-// Working extents are multiples of 128 (zero padding: the padded part of every iterate is a
-// separate diagonal block that never mixes with the matrix and is multiplied by zeros at the end).
+// These products, nearly all of the step's work, run on the fp16 matrix cores: every matrix of the iteration is held as
+// two fp16 terms (22 to 23 bits) and a product is the sum of three products of terms (launch_split2_sym), 3 / 16 of
+// the fp32 MFMA's time at full rate.  The terms need matrices of known magnitude, and the iteration provides it: M has
+// eigenvalues in (0, 5/2], T in [5/8, 5/4], so no entry of M, T, T^2, T^4 exceeds 5/2 (stored times 2^14); X / z^(1/4)
+// grows by at most 5/4 per round and ends at (z lambda_min)^(-1/4) (stored times 2^4, so up to 4094: condition numbers
+// far beyond what fp32 statistics can hold; rounds beyond the 36th, which cannot change a root that exists, are left out).
+// The roots come out closer to 64 bits than with the fp32 MFMA, whose 32 x 32 x 2 steps round a sum k / 2 times: 1.4e-5
+// instead of 1.6e-4 on 3072 x 3072 statistics at eps = 1e-4 lambda_max, 1.0e-6 instead of 6.5e-6 on 1024 x 1024, and
+// nowhere further off on 40 drawn shapes (a fourth product, of the second terms, changes nothing that shows).
+// 4 x 3072 x 1024, 22 rounds: 92.6 -> 34.6 ms.
+// Both sides run their rounds side by side (the tiles of one alone leave the last round of the chip half empty), and
+// X T shares a launch with T T.
+//
+// Statistics of bf16 gradients run on the bf16 matrix cores (statistic_bf16), those of fp32 gradients and the two
+// preconditioning products on v_mfma_f32_32x32x2_f32.  Working extents are multiples of 128 there and of 256 in the
+// iteration (zero padding: the padded part of every iterate is a separate diagonal block that never mixes with the
+// matrix and is multiplied by zeros at the end).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -35,6 +50,7 @@
 #include "device_util.h"
 #include "f32_mfma_gemm.h"
 #include "kernels.h"
+#include "panel_layout.h"
 
 namespace canz {
 namespace {
@@ -45,17 +61,72 @@ constexpr int NPART = 64;        // partial sums per matrix of the Frobenius nor
 constexpr int64_t MAX_EXTENT = 32768;
 constexpr size_t BATCH_BYTES = size_t(8) << 30;
 
-// partial[b][p] = sum of squares of the elements p, p + NPART * NTH, ... (in blocks of NTH) of A[b]
-__global__ __launch_bounds__(NTH) void k_sh_sumsq(const float* __restrict__ a, int64_t elems, float* __restrict__ partial) {
+constexpr float ONE = 16384.f;    // what stands for 1 in the fp16 terms of M, T, T^2, T^4 ...
+constexpr float X_ONE = 16.f;     // ... and of X / z^(1/4)
+constexpr int MAX_ROUNDS = 36;    // 16 (5/4)^36 < 65504; a positive definite A of condition number 1e12 has converged by then
+
+// sum over the block's threads -> *to
+__device__ __forceinline__ void block_sum_to(float ss, float* to) {
   __shared__ float wsum[NTH / 64];
-  const int b = blockIdx.y, p = blockIdx.x, t = threadIdx.x;
-  const float* ab = a + static_cast<int64_t>(b) * elems;
-  float ss = 0.f;
-  for (int64_t i = static_cast<int64_t>(p) * NTH + t; i < elems; i += static_cast<int64_t>(NPART) * NTH) ss += ab[i] * ab[i];
   ss = wave_sum(ss);
-  if ((t & 63) == 0) wsum[t >> 6] = ss;
+  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = ss;
   __syncthreads();
-  if (t == 0) partial[b * NPART + p] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+  if (threadIdx.x == 0) *to = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+}
+// partial[b][p] = sum of squares of the elements p, p + NPART * NTH, ... (in blocks of NTH) of A[b] = S + eps I
+__global__ __launch_bounds__(NTH) void k_sh_sumsq(PtrTable stat, int64_t d, float eps, float* __restrict__ partial) {
+  const int b = blockIdx.y, p = blockIdx.x;
+  const float* s = static_cast<const float*>(stat.p[b]);
+  float ss = 0.f;
+  for (int64_t i = static_cast<int64_t>(p) * NTH + threadIdx.x; i < d * d; i += static_cast<int64_t>(NPART) * NTH) ss += s[i] * s[i];
+  for (int64_t i = static_cast<int64_t>(p) * NTH + threadIdx.x; i < d; i += static_cast<int64_t>(NPART) * NTH)
+    ss += eps * (2.f * s[i * d + i] + eps);   // (S_ii + eps)^2 - S_ii^2
+  block_sum_to(ss, partial + b * NPART + p);
+}
+
+// Eight consecutive elements of a matrix of two fp16 terms: chunk `i` of the first term's panels, in memory order.
+// [dp][2 dp] columns: panel (row block, k block) of term t is number row_block * 2 nkb + t nkb + k_block.
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+struct Chunk {
+  int64_t at, lo, row, col;
+  __device__ __forceinline__ Chunk(int64_t i, int64_t dp) {
+    const int64_t nkb = dp / PANEL_K, panel = i / (PANEL_ELEMS / 8), w = i - panel * (PANEL_ELEMS / 8);
+    const int64_t rb = panel / nkb, kb = panel - rb * nkb;
+    at = ((rb * 2 * nkb) + kb) * PANEL_ELEMS + w * 8;
+    lo = at + nkb * PANEL_ELEMS;
+    row = rb * PANEL_ROWS + w / 4;
+    col = kb * PANEL_K + (((w & 3) ^ ((row >> 2) & 3)) << 3);
+  }
+};
+__device__ __forceinline__ void put_terms(_Float16* m, const Chunk& c, const float (&v)[8]) {
+  half8 h, l;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    float x = v[e];
+    asm volatile("" : "+v"(x));   // one fp32 value for both terms: no operation is fused into one of the conversions
+    h[e] = static_cast<_Float16>(x), l[e] = static_cast<_Float16>(x - static_cast<float>(h[e]));
+  }
+  *reinterpret_cast<half8*>(m + c.at) = h;
+  *reinterpret_cast<half8*>(m + c.lo) = l;
+}
+__device__ __forceinline__ void get_terms(const _Float16* m, const Chunk& c, float (&v)[8]) {
+  const half8 h = *reinterpret_cast<const half8*>(m + c.at), l = *reinterpret_cast<const half8*>(m + c.lo);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = static_cast<float>(h[e]) + static_cast<float>(l[e]);
+}
+
+// partial sums as above of a matrix of two terms
+__global__ __launch_bounds__(NTH) void k_sh_sumsq_terms(const _Float16* __restrict__ a, int64_t dp, float* __restrict__ partial) {
+  const int b = blockIdx.y, p = blockIdx.x;
+  const _Float16* ab = a + static_cast<int64_t>(b) * 2 * dp * dp;
+  float ss = 0.f;
+  for (int64_t i = static_cast<int64_t>(p) * NTH + threadIdx.x; i < dp * dp / 8; i += static_cast<int64_t>(NPART) * NTH) {
+    float v[8];
+    get_terms(ab, Chunk(i, dp), v);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ss += (v[e] * (1.f / ONE)) * (v[e] * (1.f / ONE));
+  }
+  block_sum_to(ss, partial + b * NPART + p);
 }
 
 // Start of the root iteration.  The iteration needs M = z A with eigenvalues in (0, 5); the closer the largest
@@ -63,47 +134,106 @@ __global__ __launch_bounds__(NTH) void k_sh_sumsq(const float* __restrict__ a, i
 // but loosely (by sqrt(d) for a flat spectrum: three and a half rounds at d = 3072); ||A'^4||_F^(1/4) with
 // A' = A / ||A||_F is a bound too, at most d^(1/8) above it, for two products.
 //   k_sh_prescale:  A' = A / ||A||_F
-//   k_sh_init:      z' = 5 / (2 ||A'^4||_F^(1/4));  M = z' A';  T = 5/4 I - 1/4 M;  X = (z' / ||A||_F)^(1/4) I
+//   k_sh_init:      z' = 5 / (2 ||A'^4||_F^(1/4));  M = z' A';  T = 5/4 I - 1/4 M;  X = I, (z' / ||A||_F)^(1/4) kept apart
 __device__ __forceinline__ double sum_partials(const float* partial, int b) {
   double sum = 0.0;
   for (int i = 0; i < NPART; ++i) sum += static_cast<double>(partial[b * NPART + i]);
   return sum;
 }
 
-__global__ __launch_bounds__(NTH) void k_sh_prescale(const float* __restrict__ a, const float* __restrict__ partial,
-                                                      int64_t elems, float* __restrict__ m) {
+__global__ __launch_bounds__(NTH) void k_sh_prescale(PtrTable stat, int64_t d, int64_t dp, float eps,
+                                                      const float* __restrict__ partial, _Float16* __restrict__ m) {
   const int b = blockIdx.y;
+  const float* s = static_cast<const float*>(stat.p[b]);
   const float nrm = static_cast<float>(sqrt(sum_partials(partial, b)));
   const float inv = nrm > 0.f ? 1.f / nrm : 0.f;
-  const int64_t off = static_cast<int64_t>(b) * elems;
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * NTH + threadIdx.x; i < elems; i += static_cast<int64_t>(gridDim.x) * NTH)
-    m[off + i] = inv * a[off + i];
+  _Float16* mb = m + static_cast<int64_t>(b) * 2 * dp * dp;
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * NTH + threadIdx.x; i < dp * dp / 8; i += static_cast<int64_t>(gridDim.x) * NTH) {
+    const Chunk c(i, dp);
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      v[e] = 0.f;
+      if (c.row < d && c.col + e < d) v[e] = ONE * (inv * (s[c.row * d + c.col + e] + (c.row == c.col + e ? eps : 0.f)));
+    }
+    put_terms(mb, c, v);
+  }
 }
 
 __global__ __launch_bounds__(NTH) void k_sh_init(const float* __restrict__ partial, const float* __restrict__ partial4,
-                                                  int64_t dp, float* __restrict__ x, float* __restrict__ m,
-                                                  float* __restrict__ tt) {
+                                                  int64_t d, int64_t dp, _Float16* __restrict__ x, _Float16* __restrict__ m,
+                                                  _Float16* __restrict__ tt, float* __restrict__ scale) {
   const int b = blockIdx.y;
   const float nrm = static_cast<float>(sqrt(sum_partials(partial, b)));
   const float bound = static_cast<float>(pow(sum_partials(partial4, b), 0.125));   // ||A'^4||_F^(1/4) >= lambda_max(A')
   const float z = bound > 0.f ? 2.5f / bound : 1.f;
   const float x0 = nrm > 0.f ? sqrtf(sqrtf(z / nrm)) : 1.f;
-  const int64_t elems = dp * dp, off = static_cast<int64_t>(b) * elems;
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * NTH + threadIdx.x; i < elems; i += static_cast<int64_t>(gridDim.x) * NTH) {
-    const bool diag = (i / dp) == (i % dp);
-    const float mv = z * m[off + i];
-    m[off + i] = mv;
-    tt[off + i] = (diag ? 1.25f : 0.f) - 0.25f * mv;
-    x[off + i] = diag ? x0 : 0.f;
+  if (blockIdx.x == 0 && threadIdx.x == 0) scale[b] = x0 / (ONE * X_ONE);   // of the last product X T
+  const int64_t off = static_cast<int64_t>(b) * 2 * dp * dp;
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * NTH + threadIdx.x; i < dp * dp / 8; i += static_cast<int64_t>(gridDim.x) * NTH) {
+    const Chunk c(i, dp);
+    float mv[8], tv[8], xv[8];
+    get_terms(m + off, c, mv);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const bool diag = c.row == c.col + e;
+      mv[e] = diag && c.row >= d ? ONE : z * mv[e];   // the padding stands at the fixed point M = T = X = I
+      tv[e] = (diag ? 1.25f * ONE : 0.f) - 0.25f * mv[e];
+      xv[e] = diag ? X_ONE : 0.f;
+    }
+    put_terms(m + off, c, mv);
+    put_terms(tt + off, c, tv);
+    put_terms(x + off, c, xv);
   }
 }
 
+// G (bf16 or fp32, whole or tp column fragments) -> what its readers want: fp32 copies padded to 128 (the straight one for
+// the fp32 statistics, if given) and bf16 panels padded to 256 in both orientations (if given).  One block per 64 x 64
+// tile of the larger padding.
+__global__ __launch_bounds__(NTH) void k_sh_load_grad(Shape s, PtrTable grad, int grad_dtype, int64_t rp, int64_t cp,
+                                                       float* __restrict__ gs, float* __restrict__ gt, int64_t rp2, int64_t cp2,
+                                                       __bf16* __restrict__ gp, __bf16* __restrict__ gpt) {
+  __shared__ float tile[64][65];
+  const int b = blockIdx.z, r0 = blockIdx.y * 64, c0 = blockIdx.x * 64, t = threadIdx.x;
+  const int wf = static_cast<int>(s.wfrag);
+  float val[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int idx = e * NTH + t, row = r0 + (idx >> 6), col = c0 + (idx & 63);
+    val[e] = 0.f;
+    if (row < s.rows && col < s.cols) {
+      const int f = col / wf;
+      const int64_t at = static_cast<int64_t>(row) * wf + (col - f * wf);
+      val[e] = grad_dtype == CANZ_DT_BF16 ? static_cast<float>(static_cast<const __bf16*>(grad.p[b * s.tp + f])[at])
+                                          : static_cast<const float*>(grad.p[b * s.tp + f])[at];
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int idx = e * NTH + t, r = idx >> 6, c = idx & 63;
+    if (gs && r0 + r < rp && c0 + c < cp) gs[(b * rp + r0 + r) * cp + c0 + c] = val[e];
+    tile[r][c] = val[e];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int idx = e * NTH + t, r = idx >> 6, c = idx & 63;  // r: column of G, c: row of G
+    if (c0 + r < cp && r0 + c < rp) gt[(b * cp + c0 + r) * rp + r0 + c] = tile[c][r];
+  }
+  if (gp) tile_to_panels(tile, gp + b * rp2 * cp2, r0, c0, cp2, false, t);
+  if (gpt) tile_to_panels(tile, gpt + b * rp2 * cp2, r0, c0, rp2, true, t);
+}
+
+bool bf16_statistics(const canz_shampoo_group& g) { return g.grad_dtype == CANZ_DT_BF16; }
+
 struct Carve {   // float offsets into the workspace of one launch batch
-  size_t gs, gt, tmp, lroot, rroot, a, x[2], m[2], t, t2, t4, partial, partial4, total_bytes;
+  size_t gs, gt, gp, gpt, tmp, root[2], total_bytes;
+  // the root iteration of each side: matrices of two fp16 terms (4 bytes per element); one set if the sides take turns
+  size_t x[2][2], m[2][2], t[2], t2[2], t4[2], partial[2], partial4[2], scale[2];
 };
 
-Carve carve(int64_t rows, int64_t cols, int nb) {
-  const size_t rp = pad128(rows), cp = pad128(cols), dm = std::max(rp, cp);
+Carve carve(int64_t rows, int64_t cols, int nb, bool stat16, bool side_by_side) {
+  const size_t rp = pad128(rows), cp = pad128(cols), rp2 = pad256(rows), cp2 = pad256(cols);
   Carve c{};
   size_t off = 0;
   auto take = [&](size_t floats) {
@@ -111,20 +241,33 @@ Carve carve(int64_t rows, int64_t cols, int nb) {
     off += align_up(floats * sizeof(float)) / sizeof(float);
     return at;
   };
-  c.gs = take(nb * rp * cp), c.gt = take(nb * rp * cp), c.tmp = take(nb * rp * cp);
-  c.lroot = take(nb * rp * rp), c.rroot = take(nb * cp * cp);
-  c.a = take(nb * dm * dm);
-  c.x[0] = take(nb * dm * dm), c.x[1] = take(nb * dm * dm);
-  c.m[0] = take(nb * dm * dm), c.m[1] = take(nb * dm * dm);
-  c.t = take(nb * dm * dm), c.t2 = take(nb * dm * dm), c.t4 = take(nb * dm * dm);
-  c.partial = take(static_cast<size_t>(nb) * NPART);
-  c.partial4 = take(static_cast<size_t>(nb) * NPART);
+  c.gs = take(stat16 ? 0 : nb * rp * cp), c.gt = take(nb * rp * cp), c.tmp = take(nb * rp * cp);
+  c.gp = take(stat16 ? nb * rp2 * cp2 / 2 : 0), c.gpt = take(stat16 ? nb * rp2 * cp2 / 2 : 0);
+  c.root[0] = take(nb * rp2 * rp2), c.root[1] = take(nb * cp2 * cp2);
+  for (int side = 0; side < 2; ++side) {
+    if (side == 1 && !side_by_side) {
+      for (int k = 0; k < 2; ++k) c.x[1][k] = c.x[0][k], c.m[1][k] = c.m[0][k];
+      c.t[1] = c.t[0], c.t2[1] = c.t2[0], c.t4[1] = c.t4[0];
+      c.partial[1] = c.partial[0], c.partial4[1] = c.partial4[0], c.scale[1] = c.scale[0];
+      break;
+    }
+    const size_t d = side_by_side ? (side == 0 ? rp2 : cp2) : std::max(rp2, cp2), dd = nb * d * d;
+    for (int k = 0; k < 2; ++k) c.x[side][k] = take(dd), c.m[side][k] = take(dd);
+    c.t[side] = take(dd), c.t2[side] = take(dd), c.t4[side] = take(dd);
+    c.partial[side] = take(static_cast<size_t>(nb) * NPART), c.partial4[side] = take(static_cast<size_t>(nb) * NPART);
+    c.scale[side] = take(nb);
+  }
   c.total_bytes = off * sizeof(float);
   return c;
 }
 
+// The sides run their rounds side by side unless one matrix alone would then not fit the batch's memory.
+bool sides_together(const canz_shampoo_group& g) {
+  return carve(g.rows, g.cols, 1, bf16_statistics(g), true).total_bytes <= BATCH_BYTES;
+}
+
 int batch_cap(const canz_shampoo_group& g) {
-  const size_t one = carve(g.rows, g.cols, 1).total_bytes;
+  const size_t one = carve(g.rows, g.cols, 1, bf16_statistics(g), sides_together(g)).total_bytes;
   const int64_t by_bytes = std::max<int64_t>(1, static_cast<int64_t>(BATCH_BYTES / one));
   return static_cast<int>(std::min<int64_t>(MAX_PTRS / g.tp, by_bytes));
 }
@@ -169,7 +312,8 @@ int check_group(const canz_shampoo_group& g, int idx, bool need_ptrs, int out_mo
 // One launch batch: matrices first .. first + nb - 1 of group g.
 int run_batch(const canz_shampoo_group& g, int first, int nb, const canz_shampoo_hparams& hp, float* ws, hipStream_t st) {
   const int64_t rp = pad128(g.rows), cp = pad128(g.cols);
-  const Carve c = carve(g.rows, g.cols, nb);
+  const bool stat16 = bf16_statistics(g), together = sides_together(g);
+  const Carve c = carve(g.rows, g.cols, nb, stat16, together);
   Shape s{};
   s.rows = g.rows, s.cols = g.cols;
   s.m = std::min(g.rows, g.cols), s.n = std::max(g.rows, g.cols);
@@ -188,90 +332,141 @@ int run_batch(const canz_shampoo_group& g, int first, int nb, const canz_shampoo
   o.neg_lr_scale = -hp.lr;
 
   float *gs = ws + c.gs, *gt = ws + c.gt, *tmp = ws + c.tmp;
+  const int64_t rp2 = pad256(g.rows), cp2 = pad256(g.cols);
+  __bf16 *gp = stat16 ? reinterpret_cast<__bf16*>(ws + c.gp) : nullptr, *gpt = stat16 ? reinterpret_cast<__bf16*>(ws + c.gpt) : nullptr;
   {
-    const dim3 grid(static_cast<unsigned>(cp / 64), static_cast<unsigned>(rp / 64), static_cast<unsigned>(nb));
+    const dim3 grid(static_cast<unsigned>((stat16 ? cp2 : cp) / 64), static_cast<unsigned>((stat16 ? rp2 : rp) / 64),
+                    static_cast<unsigned>(nb));
     prof_mark(st, CANZ_KERNEL_SH_LOAD, true);
-    hipLaunchKernelGGL(k_sh_load, grid, dim3(NTH), 0, st, s, grad, g.grad_dtype, rp, cp, gs, gt);
+    hipLaunchKernelGGL(k_sh_load_grad, grid, dim3(NTH), 0, st, s, grad, g.grad_dtype, rp, cp, stat16 ? nullptr : gs, gt, rp2, cp2, gp, gpt);
     prof_mark(st, CANZ_KERNEL_SH_LOAD, false);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "load kernel: %s", hipGetErrorString(e));
   }
 
-  // one side: statistic (d x d, in the caller's buffers) from the operand `side` [dp][kp], then
-  // its inverse fourth root into `root`
-  auto one_side = [&](void* const* stat_tab, void* const* root_tab, int64_t d, int64_t dp, int64_t kp, const float* side,
-                      float* root) -> int {
-    PtrTable stat{}, kept{};
-    for (int i = 0; i < nb; ++i) stat.p[i] = stat_tab[first + i];
-    if (root_tab)
-      for (int i = 0; i < nb; ++i) kept.p[i] = root_tab[first + i];
-    Shape sq{};   // the d x d matrices of this side, for the padded load and the dense store of a kept root
-    sq.rows = d, sq.cols = d, sq.tp = 1, sq.wfrag = d;
-    const dim3 sq_tiles(static_cast<unsigned>(dp / 64), static_cast<unsigned>(dp / 64), static_cast<unsigned>(nb));
-    const int64_t dd = dp * dp;
-    float *a = ws + c.a, *x[2] = {ws + c.x[0], ws + c.x[1]}, *m[2] = {ws + c.m[0], ws + c.m[1]};
-    float *tt = ws + c.t, *t2 = ws + c.t2, *t4 = ws + c.t4, *partial = ws + c.partial, *partial4 = ws + c.partial4;
-    ShGemm q{};
-    q.M = dp, q.N = dp, q.K = kp, q.ldp = kp, q.ldq = kp, q.sp = dp * kp, q.sq = dp * kp;
-    q.P = side, q.Q = side, q.c = hp.keep_roots ? nullptr : a, q.d = d, q.beta = hp.beta, q.gscale = 1.f, q.eps = hp.eps;
-    CANZ_HIP(CANZ_KERNEL_SH_STAT, (launch_gemm<SE_STAT, true>(q, nb, stat, s, o, st)), "statistics kernel");
-    if (hp.keep_roots) {   // the caller's root, padded (its transposed image, which equals it, goes to a free buffer)
-      prof_mark(st, CANZ_KERNEL_SH_LOAD, true);
-      hipLaunchKernelGGL(k_sh_load, sq_tiles, dim3(NTH), 0, st, sq, kept, static_cast<int>(CANZ_DT_F32), dp, dp, root, x[0]);
-      prof_mark(st, CANZ_KERNEL_SH_LOAD, false);
-      if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "root load: %s", hipGetErrorString(e));
-      return CANZ_OK;
+  // The two sides: statistic (d x d, in the caller's buffers) from the operand X, then its inverse fourth root.
+  struct Side {
+    PtrTable stat, kept;
+    int64_t d, dp2;
+    float *root, *partial, *partial4, *scale;
+    _Float16 *x[2], *m[2], *t, *t2, *t4;
+    bool keep;
+  } side[2];
+  for (int k = 0; k < 2; ++k) {
+    Side& z = side[k];
+    void* const* stat_tab = k == 0 ? g.left : g.right;
+    void* const* root_tab = k == 0 ? g.lroot : g.rroot;
+    z.keep = root_tab != nullptr;
+    z.stat = PtrTable{}, z.kept = PtrTable{};
+    for (int i = 0; i < nb; ++i) z.stat.p[i] = stat_tab[first + i], z.kept.p[i] = root_tab ? root_tab[first + i] : nullptr;
+    z.d = k == 0 ? g.rows : g.cols, z.dp2 = k == 0 ? rp2 : cp2;
+    z.root = ws + c.root[k], z.partial = ws + c.partial[k], z.partial4 = ws + c.partial4[k], z.scale = ws + c.scale[k];
+    auto terms = [&](size_t at) { return reinterpret_cast<_Float16*>(ws + at); };
+    for (int q = 0; q < 2; ++q) z.x[q] = terms(c.x[k][q]), z.m[q] = terms(c.m[k][q]);
+    z.t = terms(c.t[k]), z.t2 = terms(c.t2[k]), z.t4 = terms(c.t4[k]);
+    if (stat16) {
+      if (int rc = statistic_bf16(CANZ_KERNEL_SH_STAT, z.stat, z.d, z.dp2, k == 0 ? cp2 : rp2, 1024, nb, hp.beta, 1.f, k == 0 ? gp : gpt, st))
+        return rc;
+    } else {
+      const int64_t dp = k == 0 ? rp : cp, kp = k == 0 ? cp : rp;
+      ShGemm q{};
+      q.M = dp, q.N = dp, q.K = kp, q.ldp = kp, q.ldq = kp, q.sp = dp * kp, q.sq = dp * kp;
+      q.P = k == 0 ? gs : gt, q.Q = q.P, q.c = nullptr, q.d = z.d, q.beta = hp.beta, q.gscale = 1.f, q.eps = 0.f;
+      CANZ_HIP(CANZ_KERNEL_SH_STAT, (launch_gemm<SE_STAT, true>(q, nb, z.stat, s, o, st)), "statistics kernel");
     }
-    auto prod = [&](const float* P, const float* Q, float* C) {
-      ShGemm r{};
-      r.M = dp, r.N = dp, r.K = dp, r.ldp = dp, r.ldq = dp, r.sp = dd, r.sq = dd;
-      r.P = P, r.Q = Q, r.c = C;
-      return r;
+  }
+  auto square = [](int64_t d) {   // a side's d x d matrices, for the padded load and the dense store of a kept root
+    Shape sq{};
+    sq.rows = d, sq.cols = d, sq.tp = 1, sq.wfrag = d;
+    return sq;
+  };
+  auto tiles = [&](const Side& z) {
+    return dim3(static_cast<unsigned>(z.dp2 / 64), static_cast<unsigned>(z.dp2 / 64), static_cast<unsigned>(nb));
+  };
+  // the roots of the given sides, their rounds side by side
+  auto roots = [&](Side* const* z, int n) -> int {
+    auto each = [&](int kind, const char* what, auto&& run) -> int {
+      prof_mark(st, kind, true);
+      for (int k = 0; k < n; ++k) run(*z[k]);
+      prof_mark(st, kind, false);
+      if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "%s: %s", what, hipGetErrorString(e));
+      return CANZ_OK;
     };
-    const unsigned init_blocks = static_cast<unsigned>(std::min<int64_t>(4096, (dd + NTH - 1) / NTH));
-    prof_mark(st, CANZ_KERNEL_SH_INIT, true);
-    hipLaunchKernelGGL(k_sh_sumsq, dim3(NPART, nb), dim3(NTH), 0, st, a, dd, partial);
-    hipLaunchKernelGGL(k_sh_prescale, dim3(init_blocks, nb), dim3(NTH), 0, st, a, partial, dd, m[0]);
-    prof_mark(st, CANZ_KERNEL_SH_INIT, false);
-    if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "root start: %s", hipGetErrorString(e));
-    CANZ_HIP(CANZ_KERNEL_SH_ROOT, (launch_gemm<SE_PLAIN, true>(prod(m[0], m[0], t2), nb, none, s, o, st)), "root start (A A)");
-    CANZ_HIP(CANZ_KERNEL_SH_ROOT, (launch_gemm<SE_PLAIN, true>(prod(t2, t2, t4), nb, none, s, o, st)), "root start (A2 A2)");
-    prof_mark(st, CANZ_KERNEL_SH_INIT, true);
-    hipLaunchKernelGGL(k_sh_sumsq, dim3(NPART, nb), dim3(NTH), 0, st, t4, dd, partial4);
-    hipLaunchKernelGGL(k_sh_init, dim3(init_blocks, nb), dim3(NTH), 0, st, partial, partial4, dp, x[0], m[0], tt);
-    prof_mark(st, CANZ_KERNEL_SH_INIT, false);
-    if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "root start: %s", hipGetErrorString(e));
+    auto blocks = [](const Side& z_) { return static_cast<unsigned>(std::min<int64_t>(4096, z_.dp2 * z_.dp2 / 8 / NTH)); };
+    GemmBatch gb{};
+    auto add = [&](const Side& z_, const _Float16* P, const _Float16* Q, void* C, void* next_t) {
+      GemmProblem& pr = gb.pr[gb.n++] = GemmProblem{};
+      pr.d = split2_dims(z_.dp2, nb), pr.p = P, pr.q = Q, pr.c = C, pr.ct = next_t, pr.factor = 1.f / ONE;
+    };
+    auto launch = [&](const char* what) -> int {
+      CANZ_HIP(CANZ_KERNEL_SH_ROOT, launch_split2_sym(gb, ONE, st), what);
+      gb.n = 0;
+      return CANZ_OK;
+    };
+    if (int rc = each(CANZ_KERNEL_SH_INIT, "root start", [&](Side& q) {
+          hipLaunchKernelGGL(k_sh_sumsq, dim3(NPART, nb), dim3(NTH), 0, st, q.stat, q.d, hp.eps, q.partial);
+          hipLaunchKernelGGL(k_sh_prescale, dim3(blocks(q), nb), dim3(NTH), 0, st, q.stat, q.d, q.dp2, hp.eps, q.partial, q.m[0]);
+        }))
+      return rc;
+    for (int k = 0; k < n; ++k) add(*z[k], z[k]->m[0], z[k]->m[0], z[k]->t2, nullptr);
+    if (int rc = launch("root start (A A)")) return rc;
+    for (int k = 0; k < n; ++k) add(*z[k], z[k]->t2, z[k]->t2, z[k]->t4, nullptr);
+    if (int rc = launch("root start (A2 A2)")) return rc;
+    if (int rc = each(CANZ_KERNEL_SH_INIT, "root start", [&](Side& q) {
+          hipLaunchKernelGGL(k_sh_sumsq_terms, dim3(NPART, nb), dim3(NTH), 0, st, q.t4, q.dp2, q.partial4);
+          hipLaunchKernelGGL(k_sh_init, dim3(blocks(q), nb), dim3(NTH), 0, st, q.partial, q.partial4, q.d, q.dp2, q.x[0], q.m[0], q.t, q.scale);
+        }))
+      return rc;
     int cur = 0;
-    for (int it = 0; it < hp.root_iters; ++it) {
-      const bool last = it + 1 == hp.root_iters;
-      CANZ_HIP(CANZ_KERNEL_SH_ROOT, (launch_gemm<SE_PLAIN, true>(prod(x[cur], tt, last ? root : x[cur ^ 1]), nb, none, s, o, st)),
-               "root kernel (X T)");
-      if (last) break;
-      CANZ_HIP(CANZ_KERNEL_SH_ROOT, (launch_gemm<SE_PLAIN, true>(prod(tt, tt, t2), nb, none, s, o, st)), "root kernel (T T)");
-      CANZ_HIP(CANZ_KERNEL_SH_ROOT, (launch_gemm<SE_PLAIN, true>(prod(t2, t2, t4), nb, none, s, o, st)), "root kernel (T2 T2)");
-      ShGemm r = prod(t4, m[cur], m[cur ^ 1]);
-      r.c2 = tt;
-      CANZ_HIP(CANZ_KERNEL_SH_ROOT, (launch_gemm<SE_MT, true>(r, nb, none, s, o, st)), "root kernel (T4 M)");
+    const int rounds = std::min<int>(hp.root_iters, MAX_ROUNDS);
+    for (int it = 0; it + 1 < rounds; ++it) {
+      for (int k = 0; k < n; ++k) add(*z[k], z[k]->x[cur], z[k]->t, z[k]->x[cur ^ 1], nullptr), add(*z[k], z[k]->t, z[k]->t, z[k]->t2, nullptr);
+      if (int rc = launch("root kernel (X T, T T)")) return rc;
+      for (int k = 0; k < n; ++k) add(*z[k], z[k]->t2, z[k]->t2, z[k]->t4, nullptr);
+      if (int rc = launch("root kernel (T2 T2)")) return rc;
+      for (int k = 0; k < n; ++k) add(*z[k], z[k]->t4, z[k]->m[cur], z[k]->m[cur ^ 1], z[k]->t);
+      if (int rc = launch("root kernel (T4 M)")) return rc;
       cur ^= 1;
     }
-    if (root_tab) {
+    for (int k = 0; k < n; ++k) {
+      add(*z[k], z[k]->x[cur], z[k]->t, z[k]->root, nullptr);
+      gb.pr[gb.n - 1].scale = z[k]->scale;
+    }
+    CANZ_HIP(CANZ_KERNEL_SH_ROOT, launch_split2_sym_f32(gb, st), "root kernel (last X T)");
+    for (int k = 0; k < n; ++k) {
+      if (!z[k]->keep) continue;
       prof_mark(st, CANZ_KERNEL_SH_LOAD, true);
-      hipLaunchKernelGGL(k_unpad, sq_tiles, dim3(NTH), 0, st, sq, kept, root, dd, dp);
+      hipLaunchKernelGGL(k_unpad, tiles(*z[k]), dim3(NTH), 0, st, square(z[k]->d), z[k]->kept, z[k]->root, z[k]->dp2 * z[k]->dp2, z[k]->dp2);
       prof_mark(st, CANZ_KERNEL_SH_LOAD, false);
       if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "root store: %s", hipGetErrorString(e));
     }
     return CANZ_OK;
   };
-  float *lroot = ws + c.lroot, *rroot = ws + c.rroot;
-  if (int rc = one_side(g.left, g.lroot, g.rows, rp, cp, gs, lroot)) return rc;
-  if (int rc = one_side(g.right, g.rroot, g.cols, cp, rp, gt, rroot)) return rc;
+  if (hp.keep_roots) {   // the caller's roots, padded (their transposed images, which equal them, go to a free buffer)
+    for (Side& z : side) {
+      prof_mark(st, CANZ_KERNEL_SH_LOAD, true);
+      hipLaunchKernelGGL(k_sh_load, tiles(z), dim3(NTH), 0, st, square(z.d), z.kept, static_cast<int>(CANZ_DT_F32), z.dp2, z.dp2, z.root,
+                         reinterpret_cast<float*>(z.x[0]));
+      prof_mark(st, CANZ_KERNEL_SH_LOAD, false);
+      if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "root load: %s", hipGetErrorString(e));
+    }
+  } else if (together) {
+    Side* both[2] = {&side[0], &side[1]};
+    if (int rc = roots(both, 2)) return rc;
+  } else {
+    for (Side& z : side) {
+      Side* one = &z;
+      if (int rc = roots(&one, 1)) return rc;
+    }
+  }
+  float *lroot = side[0].root, *rroot = side[1].root;
 
   // O = (L^(-1/4) G) R^(-1/4): P = L root, Q = G^T gives rows x cols; then P = that, Q = R root
   ShGemm a1{};
-  a1.M = rp, a1.N = cp, a1.K = rp, a1.ldp = rp, a1.ldq = rp, a1.sp = rp * rp, a1.sq = rp * cp;
+  a1.M = rp, a1.N = cp, a1.K = rp, a1.ldp = rp2, a1.ldq = rp, a1.sp = rp2 * rp2, a1.sq = rp * cp;
   a1.P = lroot, a1.Q = gt, a1.c = tmp;
   CANZ_HIP(CANZ_KERNEL_SH_APPLY, (launch_gemm<SE_PLAIN, false>(a1, nb, none, s, o, st)), "preconditioning kernel (left)");
   ShGemm a2{};
-  a2.M = rp, a2.N = cp, a2.K = cp, a2.ldp = cp, a2.ldq = cp, a2.sp = rp * cp, a2.sq = cp * cp;
+  a2.M = rp, a2.N = cp, a2.K = cp, a2.ldp = cp, a2.ldq = cp2, a2.sp = rp * cp, a2.sq = cp2 * cp2;
   a2.P = tmp, a2.Q = rroot;
   CANZ_HIP(CANZ_KERNEL_SH_APPLY, (launch_gemm<SE_OUT, false>(a2, nb, none, s, o, st)), "preconditioning kernel (right)");
   return CANZ_OK;
@@ -345,7 +540,7 @@ extern "C" int canz_shampoo_workspace_bytes(const canz_shampoo_group* g, int32_t
   for (int i = 0; i < n_groups; ++i)
     if (int rc = check_group(g[i], i, false, hp->out_mode, hp->keep_roots != 0)) return rc;
   for (const MergedGroup& m : merge_groups(g, n_groups, hp->out_mode))
-    need = std::max(need, carve(m.g.rows, m.g.cols, std::min(m.g.n_mats, batch_cap(m.g))).total_bytes);
+    need = std::max(need, carve(m.g.rows, m.g.cols, std::min(m.g.n_mats, batch_cap(m.g)), bf16_statistics(m.g), sides_together(m.g)).total_bytes);
   *bytes_out = need;
   return CANZ_OK;
 }

@@ -40,7 +40,6 @@
 #include "device_util.h"
 #include "f32_mfma_gemm.h"
 #include "kernels.h"
-#include "panel_layout.h"
 
 namespace canz {
 namespace {
@@ -62,21 +61,6 @@ struct LoadOut {
   __bf16 *gp, *gpt, *mp, *mpt;   // bf16 panels: G [nb][rp2][cp2], G^T [nb][cp2][rp2], M, M^T; nullptr: not wanted
   int64_t rp2, cp2;
 };
-
-// one 64 x 64 fp32 tile in LDS -> the 8-element chunks of its bf16 panel image, straight (dst rows = tile rows) or
-// transposed (dst rows = tile columns); (r0, c0): the tile's place in the matrix, kc: row length of the image
-__device__ __forceinline__ void tile_to_panels(const float (*tile)[65], __bf16* __restrict__ dst, int64_t r0, int64_t c0,
-                                               int64_t kc, bool transposed, int t) {
-  const int cv = (t & 7) * 8;
-#pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    const int rl = (t >> 3) + half * 32;
-    bf16x8 o;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = static_cast<__bf16>(transposed ? tile[cv + e][rl] : tile[rl][cv + e]);
-    *reinterpret_cast<bf16x8*>(dst + (transposed ? panel_chunk_off(c0 + rl, r0 + cv, kc) : panel_chunk_off(r0 + rl, c0 + cv, kc))) = o;
-  }
-}
 
 // G (bf16 or fp32, whole or tp column fragments) and the momentum M <- beta1 M + (1 - beta1) G
 // (fp32, dense, in the caller's buffer) -> working copies of both as `w` asks, zero outside rows x cols.
@@ -254,8 +238,6 @@ __global__ __launch_bounds__(NTH) void k_soap_load_basis(PtrTable q, int64_t d, 
   if (tp) tile_to_panels(tile, tp + b * dp2 * dp2, r0, c0, dp2, true, t);
 }
 
-inline int64_t pad256(int64_t x) { return (x + PAD - 1) / PAD * PAD; }
-
 // Adam in the rotated space on bf16 panels: G' (and, unless `incremental`, M') [rp2][cp2] panels in, N' panels
 // out, straight [rp2][cp2] and / or transposed [cp2][rp2], zero outside rows x cols; V and the kept rotated
 // momentum are the caller's dense fp32 arrays as in k_soap_adam.  One block per 64 x 64 tile: the panel chunks
@@ -314,28 +296,6 @@ __global__ __launch_bounds__(NTH) void k_soap_adam_bf16(Shape s, PtrTable var, P
   __syncthreads();
   if (n_straight) tile_to_panels(tg, n_straight + static_cast<int64_t>(b) * plane, r0, c0, cp2, false, t);
   if (n_transposed) tile_to_panels(tg, n_transposed + static_cast<int64_t>(b) * plane, r0, c0, rp2, true, t);
-}
-
-// S[row][col] <- S[col][row] for row > col of the caller's dense d x d matrices: the symmetric statistic is computed
-// on and above the diagonal tiles only.  One block per 64 x 64 tile on or below the diagonal (blockIdx.y >= blockIdx.x).
-__global__ __launch_bounds__(NTH) void k_soap_mirror(PtrTable stat, int64_t d) {
-  __shared__ float tile[64][65];
-  if (blockIdx.y < blockIdx.x) return;
-  const int b = blockIdx.z, r0 = blockIdx.y * 64, c0 = blockIdx.x * 64, t = threadIdx.x;
-  float* m = static_cast<float*>(stat.p[b]);
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {   // the tile above the diagonal that mirrors this one: rows c0.., columns r0..
-    const int idx = e * NTH + t, r = idx >> 6, c = idx & 63;
-    const int64_t row = c0 + r, col = r0 + c;
-    tile[r][c] = row < d && col < d ? m[row * d + col] : 0.f;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int idx = e * NTH + t, r = idx >> 6, c = idx & 63;
-    const int64_t row = r0 + r, col = c0 + c;
-    if (row < d && col < row) m[row * d + col] = tile[c][r];
-  }
 }
 
 // a[b][i] = (identity ? (row == col) : 0) for the [rows][ld] matrices of a batch
@@ -1356,31 +1316,9 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
     PtrTable tab{};
     for (int i = 0; i < nb; ++i) tab.p[i] = stat_tab[first + i];
     if (stat16) {
-      // S <- beta2 S + (1 - beta2) X X^T as the "last product" of the bf16 kernels: it updates the caller's dense
-      // fp32 array in place as old * decay + factor * product, on and above the diagonal tiles; the rest is mirrored
-      Shape sq{};
-      sq.rows = d, sq.cols = d, sq.m = d, sq.n = d, sq.mp = d2, sq.np = d2, sq.tp = 1, sq.wfrag = d;
-      OutSpec so{};
-      so.out = tab, so.out_dtype = CANZ_DT_F32, so.out_mode = CANZ_OUT_PARAM, so.decay = hp.beta2, so.neg_lr_scale = 1.f - hp.beta2;
-      const GemmDims sd{d2, d2, k2, k2, k2, d2 * k2, d2 * k2, nb};
-      // Only the tiles on and above the diagonal, mirrored afterwards, where that pays: the products it saves (about
-      // 0.65 us per 32-long k-step of a tile, a round of tiles on 256 CUs at a time) against one more pass over the
-      // statistic at some 4 TB/s that does not overlap with anything.  Long sums win (25600 x 5120: 3.9 -> 1.3 ms),
-      // short ones do not (3072 x 1024: the mirror pass costs what the products save).
-      const int64_t t256 = d2 / 256;
-      const double saved_us = static_cast<double>(t256 * (t256 - 1) / 2 * nb) / 256.0 * static_cast<double>(k2 / 32) * 0.65;
-      const double mirror_us = 15.0 + static_cast<double>(d) * static_cast<double>(d) * nb * 4.0 / 4.0e6;
-      if (saved_us > 1.5 * mirror_us) {
-        CANZ_HIP(CANZ_KERNEL_SOAP_STAT, launch_final_sym_bf16(sd, side16, no_split, sq, so, st), "statistics kernel (bf16 operands)");
-        prof_mark(st, CANZ_KERNEL_SOAP_STAT, true);
-        const unsigned t64 = static_cast<unsigned>((d + 63) / 64);
-        hipLaunchKernelGGL(k_soap_mirror, dim3(t64, t64, static_cast<unsigned>(nb)), dim3(NTH), 0, st, tab, d);
-        prof_mark(st, CANZ_KERNEL_SOAP_STAT, false);
-        if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "statistic mirror: %s", hipGetErrorString(e));
-      } else {
-        CANZ_HIP(CANZ_KERNEL_SOAP_STAT, launch_final_bf16(sd, side16, side16, nullptr, no_split, sq, so, st),
-                 "statistics kernel (bf16 operands)");
-      }
+      Shape sq{};   // the caller's dense d x d matrix
+      sq.rows = d, sq.cols = d, sq.m = d, sq.n = d, sq.tp = 1, sq.wfrag = d;
+      if (int rc = statistic_bf16(CANZ_KERNEL_SOAP_STAT, tab, d, d2, k2, k2, nb, hp.beta2, 1.f - hp.beta2, side16, st)) return rc;
       if (hp.refresh) {   // the padded copy the refresh multiplies the basis with (its transposed image lands in wk, unused)
         prof_mark(st, CANZ_KERNEL_SOAP_STAT, true);
         hipLaunchKernelGGL(k_sh_load, dim3(static_cast<unsigned>(dp / 64), static_cast<unsigned>(dp / 64), static_cast<unsigned>(nb)),

@@ -1,0 +1,112 @@
+"""The Shampoo root iteration on matrices of two fp16 terms: sizes around its 256-wide tiles, shares of the work between
+the large and the small kernel, few and many rounds, the padding, and sides that take turns."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def canz():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_06079_amd import binding
+    return binding
+
+
+def _newton(torch, s, eps, rounds):
+    """The same rounds in 64 bits: what exact arithmetic would give after so many."""
+    d = s.shape[0]
+    eye = torch.eye(d, device=s.device, dtype=torch.float64)
+    a = s.double() + eps * eye
+    nrm = a.norm()
+    ap = a / nrm
+    a2 = ap @ ap
+    z = 2.5 / (a2 @ a2).norm() ** 0.25
+    m, x = z * ap, eye * (z / nrm) ** 0.25
+    del a2, a
+    for _ in range(rounds):
+        t = 1.25 * eye - 0.25 * m
+        x = x @ t
+        t2 = t @ t
+        m = t2 @ t2 @ m
+    return x
+
+
+def _step(torch, canz, rows, cols, n, rounds, grad_dtype, eps, level=0.02, beta=1.0):
+    g = torch.Generator(device="cuda").manual_seed(rows * 10007 + cols)
+    draw = lambda r, c: torch.randn(r, c, generator=g, device="cuda")  # noqa: E731
+    grads = [(draw(rows, cols) * level).to(grad_dtype) for _ in range(n)]
+    left = [torch.zeros(rows, rows, device="cuda") for _ in range(n)]
+    right = [torch.zeros(cols, cols, device="cuda") for _ in range(n)]
+    lroot, rroot = [torch.empty_like(x) for x in left], [torch.empty_like(x) for x in right]
+    out = [torch.zeros(rows, cols, device="cuda") for _ in range(n)]
+    grp = canz.ShampooGroup(rows=rows, cols=cols, grad=grads, left=left, right=right, out=out, lroot=lroot, rroot=rroot,
+                            grad_dtype=canz.DT_BF16 if grad_dtype == torch.bfloat16 else canz.DT_F32)
+    hp = canz.ShampooHparams(beta=beta, lr=1.0, eps=eps, root_iters=rounds, out_mode=canz.OUT_DELTA)
+    need = canz.canz_shampoo_workspace_bytes([grp], hp)
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")   # every byte a NaN: nothing may be read unwritten
+    canz.canz_shampoo_step([grp], hp, ws, need, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    return grads, left, right, lroot, rroot, out
+
+
+@pytest.mark.parametrize("rows,cols,n,rounds,bf16", [
+    (256, 256, 1, 22, True),     # one tile
+    (255, 257, 2, 22, True),     # one short of a tile, one past it
+    (96, 520, 3, 22, False),     # fp32 gradients, odd padding
+    (1024, 2048, 5, 22, True),   # enough tiles for the large kernel, and left-over ones for the small kernel
+    (2304, 1280, 3, 22, False),
+    (300, 700, 1, 1, True),      # the first round is the last
+    (300, 700, 1, 2, True),
+    (300, 700, 1, 36, True),     # the most rounds that are run ...
+    (300, 700, 1, 60, True),     # ... and more asked for: the padding must not overflow either
+])
+def test_roots_against_the_same_rounds_in_64_bits(canz, rows, cols, n, rounds, bf16):
+    import torch
+    eps = 1e-3
+    grads, left, right, lroot, rroot, out = _step(torch, canz, rows, cols, n, rounds, torch.bfloat16 if bf16 else torch.float32, eps)
+    for i in range(n):
+        g = grads[i].double()
+        for got, want in ((left[i], g @ g.t()), (right[i], g.t() @ g)):
+            assert float((got.double() - want).norm() / want.norm()) <= 1e-6
+            assert torch.equal(got, got.t())
+        for s, got in ((left[i], lroot[i]), (right[i], rroot[i])):
+            want = _newton(torch, s, float(np.float32(eps)), min(rounds, 36))
+            # matrices held to about 24 bits: an eigenvalue near eps is off by up to an fp32 ulp of the largest one
+            # (of a Gaussian matrix's statistic: (sqrt(rows) + sqrt(cols))^2 entries), the well-conditioned rest by rounding
+            largest = 0.02 ** 2 * (rows ** 0.5 + cols ** 0.5) ** 2
+            assert float((got.double() - want).norm() / want.norm()) <= 2.0 ** -24 * largest / eps + 2e-6
+        want = -(lroot[i].double() @ g @ rroot[i].double())
+        # two fp32 products: each rounds relative to the norms of its factors (a root's is at most eps^(-1/4)), not to
+        # the result, in which G's own directions meet the small end of the roots' spectra
+        assert float((out[i].double() - want).norm()) <= 1e-6 * eps ** -0.5 * float(g.norm())
+
+
+@pytest.mark.parametrize("level", [1e-6, 1e6])
+def test_scale_of_the_gradients_does_not_matter(canz, level):
+    """The terms hold A / ||A||: tiny and huge statistics give the same iteration as those of order one."""
+    import torch
+    eps = 2.5 * level * level
+    _, left, _, lroot, _, _ = _step(torch, canz, 200, 300, 1, 22, torch.float32, eps, level=level)
+    want = _newton(torch, left[0], float(np.float32(eps)), 22)
+    assert float((lroot[0].double() - want).norm() / want.norm()) <= 3e-5
+
+
+def test_zero_gradient_zero_statistics(canz):
+    import torch
+    _, left, right, lroot, _, out = _step(torch, canz, 300, 200, 1, 40, torch.bfloat16, 0.0, level=0.0, beta=0.0)
+    assert not left[0].any() and not right[0].any() and not out[0].any()
+    assert torch.isfinite(lroot[0]).all()
+
+
+def test_sides_that_take_turns(canz):
+    """One matrix whose two sides would not fit the batch memory together: the sides share one set of buffers."""
+    import torch
+    rows, cols, eps = 16640, 24, 1e-3
+    _, left, right, lroot, rroot, _ = _step(torch, canz, rows, cols, 1, 2, torch.bfloat16, eps)
+    for s, got in ((left[0], lroot[0]), (right[0], rroot[0])):
+        want = _newton(torch, s, float(np.float32(eps)), 2)
+        want -= got.double()
+        assert float(want.norm() / got.double().norm()) <= 3e-5
