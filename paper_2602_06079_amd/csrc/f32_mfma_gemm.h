@@ -29,9 +29,9 @@ inline int64_t pad128(int64_t x) { return (x + SB - 1) / SB * SB; }
 inline size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
 // Epilogues: SE_STAT  S <- beta S + gscale C into the caller's dense statistic, S + eps I to c;
-//            SE_PLAIN c = C;   SE_MT  c = C and c2 = 5/4 I - 1/4 C;   SE_OUT  the optimizer update
+//            SE_PLAIN c = C;   SE_OUT  the optimizer update
 //            into the caller's parameters or Delta W fragments;   SE_SUB  c <- c - C.
-enum { SE_STAT = 0, SE_PLAIN = 1, SE_MT = 2, SE_OUT = 3, SE_SUB = 4 };
+enum { SE_STAT = 0, SE_PLAIN = 1, SE_OUT = 3, SE_SUB = 4 };
 
 struct ShGemm {
   int64_t M, N, K;      // multiples of 128, 128, 32
@@ -42,7 +42,6 @@ struct ShGemm {
   const float* Q;
   float* c;             // output
   int64_t ldc, sc;      // its row and batch strides; 0, 0 means dense: N and M * N
-  float* c2;            // SE_MT: the next T = 5/4 I - 1/4 C (strides as c)
   // SE_STAT: the caller's statistic (d x d, dense) is updated in place and A = S + eps I is written to c
   int64_t d;
   float beta, gscale, eps;
@@ -197,11 +196,6 @@ __device__ __forceinline__ void sh_gemm_body(const ShGemm& g, const PtrTable& st
 #pragma unroll
         for (int r = 0; r < 16; ++r) v[r] = old[r] - v[r];
         put16(C, g.ldc, row0, col, v, false);
-      } else if (EPI == SE_MT) {
-        put16(g.c + cb, g.ldc, row0, col, v, mirror);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) v[r] = (row0 + 8 * (r >> 2) + (r & 3) == col ? 1.25f : 0.f) - 0.25f * v[r];
-        put16(g.c2 + cb, g.ldc, row0, col, v, mirror);
       } else {  // SE_STAT
         float* S = static_cast<float*>(stat.p[b]);
         const int d = static_cast<int>(g.d);
@@ -320,6 +314,45 @@ static __device__ __forceinline__ void tile_to_panels(const float (*tile)[65], _
     for (int e = 0; e < 8; ++e) o[e] = static_cast<__bf16>(transposed ? tile[cv + e][rl] : tile[rl][cv + e]);
     *reinterpret_cast<bf16x8*>(dst + (transposed ? panel_chunk_off(c0 + rl, r0 + cv, kc) : panel_chunk_off(r0 + rl, c0 + cv, kc))) = o;
   }
+}
+
+// The same tile as three bf16 terms per element (kernels.h: launch_split3): term i of a matrix of kc columns lies in the
+// columns i kc .. of a panel matrix of 3 kc columns.
+static __device__ __forceinline__ void tile_to_terms3(const float (*tile)[65], __bf16* __restrict__ dst, int64_t r0, int64_t c0,
+                                                      int64_t kc, bool transposed, int t) {
+  const int cv = (t & 7) * 8;
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    const int rl = (t >> 3) + half * 32;
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = transposed ? tile[cv + e][rl] : tile[rl][cv + e];
+    const int64_t row = (transposed ? c0 : r0) + rl, col = (transposed ? r0 : c0) + cv;
+#pragma unroll
+    for (int term = 0; term < 3; ++term) {
+      bf16x8 o;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] = static_cast<__bf16>(v[e]), v[e] -= static_cast<float>(o[e]);
+      *reinterpret_cast<bf16x8*>(dst + panel_chunk_off(row, term * kc + col, 3 * kc)) = o;
+    }
+  }
+}
+
+// fp32 matrices of d x d elements (row length ld) -> three bf16 terms per element, [dp2][3 dp2] panels, straight and / or
+// transposed, zero outside d x d.  One block per 64 x 64 tile.
+static __global__ __launch_bounds__(NTH) void k_terms3(PtrTable src, int64_t d, int64_t ld, int64_t dp2, __bf16* __restrict__ straight,
+                                                      __bf16* __restrict__ transposed) {
+  __shared__ float tile[64][65];
+  const int b = blockIdx.z, r0 = blockIdx.y * 64, c0 = blockIdx.x * 64, t = threadIdx.x;
+  const float* m = static_cast<const float*>(src.p[b]);
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int idx = e * NTH + t, r = idx >> 6, c = idx & 63;
+    tile[r][c] = r0 + r < d && c0 + c < d ? m[static_cast<int64_t>(r0 + r) * ld + c0 + c] : 0.f;
+  }
+  __syncthreads();
+  if (straight) tile_to_terms3(tile, straight + static_cast<int64_t>(b) * 3 * dp2 * dp2, r0, c0, dp2, false, t);
+  if (transposed) tile_to_terms3(tile, transposed + static_cast<int64_t>(b) * 3 * dp2 * dp2, r0, c0, dp2, true, t);
 }
 
 // S[row][col] <- S[col][row] for row > col of the caller's dense d x d matrices: the symmetric statistic is computed

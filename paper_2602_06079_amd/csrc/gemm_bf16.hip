@@ -54,7 +54,7 @@ constexpr int N_XCD = 8;
 static_assert(BM == PANEL_ROWS && BK == PANEL_K, "tile = panel");
 
 enum { EPI_GRAM = 0, EPI_POLY = 1, EPI_UPDATE = 2, EPI_FINAL = 3, EPI_FINAL_SYM = 4, EPI_MUL = 5, EPI_POLY_APART = 6, EPI_GRAM_APART = 7,
-       EPI_H2 = 8, EPI_H2_F32 = 9 };
+       EPI_H2 = 8, EPI_H2_F32 = 9, EPI_B3 = 10, EPI_OUT_B3 = 11 };
 // EPI_FINAL_SYM: the last-product epilogue (the caller's dense buffers) over the tiles on and above the diagonal of a
 // symmetric result only; the caller mirrors them into the lower triangle afterwards.
 // EPI_GRAM_APART, EPI_POLY_APART: the diagonals of the matrices are kept apart (kernels.h: SymSpec).
@@ -64,9 +64,11 @@ constexpr bool epi_apart(int epi) { return epi == EPI_POLY_APART || epi == EPI_M
 constexpr bool epi_mspace(int epi) { return epi == EPI_GRAM || epi == EPI_GRAM_APART || epi_poly(epi) || epi == EPI_MUL; }
 // EPI_H2, EPI_H2_F32: products of symmetric commuting matrices of two fp16 terms (kernels.h: launch_split2_*).
 constexpr bool epi_f16(int epi) { return epi == EPI_H2 || epi == EPI_H2_F32; }
-constexpr bool epi_terms(int epi) { return epi_f16(epi); }   // operands of several terms
+// EPI_B3, EPI_OUT_B3: products of matrices of up to three bf16 terms (launch_split3*): the result as three terms, and the
+// last-product epilogue.
+constexpr bool epi_terms(int epi) { return epi_f16(epi) || epi == EPI_B3 || epi == EPI_OUT_B3; }   // operands of several terms
 constexpr bool epi_symmetric(int epi) { return epi_mspace(epi) || epi == EPI_FINAL_SYM || epi_f16(epi); }
-constexpr bool epi_final(int epi) { return epi == EPI_FINAL || epi == EPI_FINAL_SYM; }
+constexpr bool epi_final(int epi) { return epi == EPI_FINAL || epi == EPI_FINAL_SYM || epi == EPI_OUT_B3; }
 
 struct EpiArgs {
   void* c;                 // GRAM/POLY: [nb][M][N] panels; UPDATE: straight output [nb][M][N] panels
@@ -318,6 +320,43 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
           if (tm != tn || wm < wn) *reinterpret_cast<f32x4*>(C + col * d.N + row0 + 8 * g) = v;
         }
       }
+    return;
+  }
+  if constexpr (EPI == EPI_B3) {
+    // Three terms per element, straight image only: each pass rounds what is left to bf16, writes it and takes it away.
+    int s_base[2];
+#pragma unroll
+    for (int g1 = 0; g1 < 2; ++g1)
+      s_base[g1] = (4 * lh + (lane & 1)) * 32 + ((((lj >> 3) ^ (2 * g1 + lh)) & 3) << 3) + (lj & 6);
+    const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
+    const int64_t nkb = d.N >> 5;
+#pragma unroll 1
+    for (int term = 0; term < 3; ++term) {
+#pragma unroll
+      for (int it = 0; it < 4; ++it)
+#pragma unroll
+        for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+          for (int rp = 0; rp < 8; ++rp) {
+            bf16x2 own;
+            own[0] = static_cast<__bf16>(acc[it][jt][2 * rp]);
+            own[1] = static_cast<__bf16>(acc[it][jt][2 * rp + 1]);
+            acc[it][jt][2 * rp] -= static_cast<float>(own[0]);
+            acc[it][jt][2 * rp + 1] -= static_cast<float>(own[1]);
+            const unsigned mine = __builtin_bit_cast(unsigned, own);
+            const int g = rp >> 1, p = rp & 1;
+            *reinterpret_cast<unsigned*>(stage + jt * 4096 + (it * 32 + 8 * g + 2 * p) * 32 + s_base[g & 1]) =
+                __builtin_amdgcn_perm(lane_xor1(mine), mine, pair_sel);
+          }
+      __bf16* C = static_cast<__bf16*>(e.c) + static_cast<int64_t>(b) * 3 * d.M * d.N;
+#pragma unroll
+      for (int k4 = 0; k4 < 4; ++k4) {
+        __bf16* dst = C + (tm * 3 * nkb + term * nkb + 8 * tn + 4 * wn + k4) * PANEL_ELEMS + wm * 128 * PANEL_K;
+#pragma unroll
+        for (int x = 0; x < 8; ++x)
+          *reinterpret_cast<u32x4*>(dst + (x * 64 + lane) * 8) = *reinterpret_cast<const u32x4*>(stage + k4 * 4096 + (x * 64 + lane) * 8);
+      }
+    }
     return;
   }
   if constexpr (EPI == EPI_H2) {
@@ -1169,6 +1208,30 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
         }
       }
     return;
+  } else if constexpr (EPI == EPI_B3) {
+    const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
+    const int64_t nkb = d.N >> 5;
+    __bf16* C = static_cast<__bf16*>(e.c) + static_cast<int64_t>(b) * 3 * d.M * d.N;
+#pragma unroll 1
+    for (int term = 0; term < 3; ++term)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          __bf16* const at = C + ((row_w >> 8) * 3 * nkb + term * nkb + ((col_w + 32 * j) >> 5)) * PANEL_ELEMS + ((row_w & 255) + 32 * i) * PANEL_K;
+#pragma unroll
+          for (int rp = 0; rp < 8; ++rp) {
+            bf16x2 own;
+            own[0] = static_cast<__bf16>(acc[i][j][2 * rp]);
+            own[1] = static_cast<__bf16>(acc[i][j][2 * rp + 1]);
+            acc[i][j][2 * rp] -= static_cast<float>(own[0]);
+            acc[i][j][2 * rp + 1] -= static_cast<float>(own[1]);
+            const unsigned mine = __builtin_bit_cast(unsigned, own);
+            *reinterpret_cast<unsigned*>(at + s_lane[(rp >> 1) & 1] + (8 * (rp >> 1) + 2 * (rp & 1)) * PANEL_K) =
+                __builtin_amdgcn_perm(lane_xor1(mine), mine, pair_sel);
+          }
+        }
+    return;
   } else if constexpr (EPI == EPI_H2) {
     const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
 #pragma unroll
@@ -1532,6 +1595,16 @@ hipError_t launch_update_bf16(const GemmDims& d, const void* b_in, const void* x
   e.ct = xt_out;
   e.scale = scale;
   return launch<EPI_UPDATE>(d, b_in, xt_in, e, w, Shape{}, OutSpec{}, st);
+}
+
+hipError_t launch_split3(const GemmDims& d, const void* p, const void* q, void* c, hipStream_t st) {
+  EpiArgs e{};
+  e.c = c;
+  return launch<EPI_B3>(d, p, q, e, SplitWs{nullptr, 0}, Shape{}, OutSpec{}, st);
+}
+
+hipError_t launch_split3_final(const GemmDims& d, const void* p, const void* q, const Shape& s, const OutSpec& o, hipStream_t st) {
+  return launch<EPI_OUT_B3>(d, p, q, EpiArgs{}, SplitWs{nullptr, 0}, s, o, st);
 }
 
 hipError_t launch_final_bf16(const GemmDims& d, const void* p, const void* q, const float* scale, const SplitWs& w,

@@ -34,9 +34,9 @@
 // Both sides run their rounds side by side (the tiles of one alone leave the last round of the chip half empty), and
 // X T shares a launch with T T.
 //
-// Statistics of bf16 gradients run on the bf16 matrix cores (statistic_bf16), those of fp32 gradients and the two
-// preconditioning products on v_mfma_f32_32x32x2_f32.  Working extents are multiples of 128 there and of 256 in the
-// iteration (zero padding: the padded part of every iterate is a separate diagonal block that never mixes with the
+// Statistics of bf16 gradients run on the bf16 matrix cores (statistic_bf16), those of fp32 gradients on
+// v_mfma_f32_32x32x2_f32; the two preconditioning products on the bf16 cores with three terms per fp32 element
+// (launch_split3).  Working extents are multiples of 128 for the fp32 MFMA and of 256 elsewhere (zero padding: the padded part of every iterate is a separate diagonal block that never mixes with the
 // matrix and is multiplied by zeros at the end).
 #include <hip/hip_runtime.h>
 
@@ -187,12 +187,13 @@ __global__ __launch_bounds__(NTH) void k_sh_init(const float* __restrict__ parti
   }
 }
 
-// G (bf16 or fp32, whole or tp column fragments) -> what its readers want: fp32 copies padded to 128 (the straight one for
-// the fp32 statistics, if given) and bf16 panels padded to 256 in both orientations (if given).  One block per 64 x 64
-// tile of the larger padding.
+// G (bf16 or fp32, whole or tp column fragments) -> what its readers want.  bf16: panels padded to 256 in both
+// orientations, for the statistics and the preconditioning product.  fp32: copies padded to 128 in both orientations for
+// the statistics, and the transposed one as three bf16 terms for the product.  One block per 64 x 64 tile of the larger padding.
 __global__ __launch_bounds__(NTH) void k_sh_load_grad(Shape s, PtrTable grad, int grad_dtype, int64_t rp, int64_t cp,
                                                        float* __restrict__ gs, float* __restrict__ gt, int64_t rp2, int64_t cp2,
-                                                       __bf16* __restrict__ gp, __bf16* __restrict__ gpt) {
+                                                       __bf16* __restrict__ gp, __bf16* __restrict__ gpt,
+                                                       __bf16* __restrict__ g3t) {
   __shared__ float tile[64][65];
   const int b = blockIdx.z, r0 = blockIdx.y * 64, c0 = blockIdx.x * 64, t = threadIdx.x;
   const int wf = static_cast<int>(s.wfrag);
@@ -218,8 +219,9 @@ __global__ __launch_bounds__(NTH) void k_sh_load_grad(Shape s, PtrTable grad, in
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
     const int idx = e * NTH + t, r = idx >> 6, c = idx & 63;  // r: column of G, c: row of G
-    if (c0 + r < cp && r0 + c < rp) gt[(b * cp + c0 + r) * rp + r0 + c] = tile[c][r];
+    if (gt && c0 + r < cp && r0 + c < rp) gt[(b * cp + c0 + r) * rp + r0 + c] = tile[c][r];
   }
+  if (g3t) tile_to_terms3(tile, g3t + b * 3 * rp2 * cp2, r0, c0, rp2, true, t);
   if (gp) tile_to_panels(tile, gp + b * rp2 * cp2, r0, c0, cp2, false, t);
   if (gpt) tile_to_panels(tile, gpt + b * rp2 * cp2, r0, c0, rp2, true, t);
 }
@@ -227,7 +229,7 @@ __global__ __launch_bounds__(NTH) void k_sh_load_grad(Shape s, PtrTable grad, in
 bool bf16_statistics(const canz_shampoo_group& g) { return g.grad_dtype == CANZ_DT_BF16; }
 
 struct Carve {   // float offsets into the workspace of one launch batch
-  size_t gs, gt, gp, gpt, tmp, root[2], total_bytes;
+  size_t gs, gt, g3t, gp, gpt, tmp, root[2], root3[2], total_bytes;   // g3t, tmp, root3: three bf16 terms per element
   // the root iteration of each side: matrices of two fp16 terms (4 bytes per element); one set if the sides take turns
   size_t x[2][2], m[2][2], t[2], t2[2], t4[2], partial[2], partial4[2], scale[2];
 };
@@ -241,7 +243,9 @@ Carve carve(int64_t rows, int64_t cols, int nb, bool stat16, bool side_by_side) 
     off += align_up(floats * sizeof(float)) / sizeof(float);
     return at;
   };
-  c.gs = take(stat16 ? 0 : nb * rp * cp), c.gt = take(nb * rp * cp), c.tmp = take(nb * rp * cp);
+  c.gs = take(stat16 ? 0 : nb * rp * cp), c.gt = take(stat16 ? 0 : nb * rp * cp), c.g3t = take(stat16 ? 0 : nb * rp2 * cp2 * 3 / 2);
+  c.tmp = take(nb * rp2 * cp2 * 3 / 2);
+  c.root3[0] = take(nb * rp2 * rp2 * 3 / 2), c.root3[1] = take(nb * cp2 * cp2 * 3 / 2);
   c.gp = take(stat16 ? nb * rp2 * cp2 / 2 : 0), c.gpt = take(stat16 ? nb * rp2 * cp2 / 2 : 0);
   c.root[0] = take(nb * rp2 * rp2), c.root[1] = take(nb * cp2 * cp2);
   for (int side = 0; side < 2; ++side) {
@@ -321,7 +325,7 @@ int run_batch(const canz_shampoo_group& g, int first, int nb, const canz_shampoo
   s.tall = g.rows > g.cols;
   s.tp = g.tp;
   s.wfrag = g.cols / g.tp;
-  PtrTable grad{}, none{};
+  PtrTable grad{};
   for (int i = 0; i < nb * g.tp; ++i) grad.p[i] = const_cast<void*>(g.grad[first * g.tp + i]);
   OutSpec o{};
   const int per_out = hp.out_mode == CANZ_OUT_DELTA ? g.tp : 1;
@@ -331,14 +335,14 @@ int run_batch(const canz_shampoo_group& g, int first, int nb, const canz_shampoo
   o.decay = static_cast<float>(1.0 - static_cast<double>(hp.lr) * static_cast<double>(hp.weight_decay));
   o.neg_lr_scale = -hp.lr;
 
-  float *gs = ws + c.gs, *gt = ws + c.gt, *tmp = ws + c.tmp;
+  float *gs = stat16 ? nullptr : ws + c.gs, *gt = stat16 ? nullptr : ws + c.gt;
   const int64_t rp2 = pad256(g.rows), cp2 = pad256(g.cols);
   __bf16 *gp = stat16 ? reinterpret_cast<__bf16*>(ws + c.gp) : nullptr, *gpt = stat16 ? reinterpret_cast<__bf16*>(ws + c.gpt) : nullptr;
   {
-    const dim3 grid(static_cast<unsigned>((stat16 ? cp2 : cp) / 64), static_cast<unsigned>((stat16 ? rp2 : rp) / 64),
-                    static_cast<unsigned>(nb));
+    const dim3 grid(static_cast<unsigned>(cp2 / 64), static_cast<unsigned>(rp2 / 64), static_cast<unsigned>(nb));
     prof_mark(st, CANZ_KERNEL_SH_LOAD, true);
-    hipLaunchKernelGGL(k_sh_load_grad, grid, dim3(NTH), 0, st, s, grad, g.grad_dtype, rp, cp, stat16 ? nullptr : gs, gt, rp2, cp2, gp, gpt);
+    hipLaunchKernelGGL(k_sh_load_grad, grid, dim3(NTH), 0, st, s, grad, g.grad_dtype, rp, cp, gs, gt, rp2, cp2, gp, gpt,
+                       stat16 ? nullptr : reinterpret_cast<__bf16*>(ws + c.g3t));
     prof_mark(st, CANZ_KERNEL_SH_LOAD, false);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "load kernel: %s", hipGetErrorString(e));
   }
@@ -441,14 +445,8 @@ int run_batch(const canz_shampoo_group& g, int first, int nb, const canz_shampoo
     }
     return CANZ_OK;
   };
-  if (hp.keep_roots) {   // the caller's roots, padded (their transposed images, which equal them, go to a free buffer)
-    for (Side& z : side) {
-      prof_mark(st, CANZ_KERNEL_SH_LOAD, true);
-      hipLaunchKernelGGL(k_sh_load, tiles(z), dim3(NTH), 0, st, square(z.d), z.kept, static_cast<int>(CANZ_DT_F32), z.dp2, z.dp2, z.root,
-                         reinterpret_cast<float*>(z.x[0]));
-      prof_mark(st, CANZ_KERNEL_SH_LOAD, false);
-      if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "root load: %s", hipGetErrorString(e));
-    }
+  if (hp.keep_roots) {
+    // the caller's roots, below
   } else if (together) {
     Side* both[2] = {&side[0], &side[1]};
     if (int rc = roots(both, 2)) return rc;
@@ -458,17 +456,28 @@ int run_batch(const canz_shampoo_group& g, int first, int nb, const canz_shampoo
       if (int rc = roots(&one, 1)) return rc;
     }
   }
-  float *lroot = side[0].root, *rroot = side[1].root;
-
-  // O = (L^(-1/4) G) R^(-1/4): P = L root, Q = G^T gives rows x cols; then P = that, Q = R root
-  ShGemm a1{};
-  a1.M = rp, a1.N = cp, a1.K = rp, a1.ldp = rp2, a1.ldq = rp, a1.sp = rp2 * rp2, a1.sq = rp * cp;
-  a1.P = lroot, a1.Q = gt, a1.c = tmp;
-  CANZ_HIP(CANZ_KERNEL_SH_APPLY, (launch_gemm<SE_PLAIN, false>(a1, nb, none, s, o, st)), "preconditioning kernel (left)");
-  ShGemm a2{};
-  a2.M = rp, a2.N = cp, a2.K = cp, a2.ldp = cp, a2.ldq = cp2, a2.sp = rp * cp, a2.sq = cp2 * cp2;
-  a2.P = tmp, a2.Q = rroot;
-  CANZ_HIP(CANZ_KERNEL_SH_APPLY, (launch_gemm<SE_OUT, false>(a2, nb, none, s, o, st)), "preconditioning kernel (right)");
+  // O = (L^(-1/4) G) R^(-1/4) on the bf16 cores, the roots and L^(-1/4) G as three terms per element (six products of
+  // terms, three where G is bf16 itself): a step of 14 x 3072 x 1024 on kept roots 4.34 -> 2.26 ms against the fp32 MFMA.
+  __bf16* root3[2];
+  for (int k = 0; k < 2; ++k) {
+    const Side& z = side[k];
+    root3[k] = reinterpret_cast<__bf16*>(ws + c.root3[k]);
+    PtrTable from = z.kept;
+    if (!hp.keep_roots)
+      for (int i = 0; i < nb; ++i) from.p[i] = z.root + static_cast<int64_t>(i) * z.dp2 * z.dp2;
+    prof_mark(st, CANZ_KERNEL_SH_LOAD, true);
+    hipLaunchKernelGGL(k_terms3, tiles(z), dim3(NTH), 0, st, from, z.d, hp.keep_roots ? z.d : z.dp2, z.dp2, root3[k],
+                       static_cast<__bf16*>(nullptr));
+    prof_mark(st, CANZ_KERNEL_SH_LOAD, false);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "root load: %s", hipGetErrorString(e));
+  }
+  // P = L root, Q = G^T gives rows x cols; then P = that, Q = R root
+  __bf16* tmp = reinterpret_cast<__bf16*>(ws + c.tmp);
+  const __bf16* gt_terms = stat16 ? gpt : reinterpret_cast<const __bf16*>(ws + c.g3t);
+  CANZ_HIP(CANZ_KERNEL_SH_APPLY, launch_split3(split3_dims(rp2, cp2, rp2, stat16 ? 1 : 3, nb), root3[0], gt_terms, tmp, st),
+           "preconditioning kernel (left)");
+  CANZ_HIP(CANZ_KERNEL_SH_APPLY, launch_split3_final(split3_dims(rp2, cp2, cp2, 3, nb), tmp, root3[1], s, o, st),
+           "preconditioning kernel (right)");
   return CANZ_OK;
 }
 
