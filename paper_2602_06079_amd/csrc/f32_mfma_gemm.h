@@ -29,15 +29,14 @@ inline int64_t pad128(int64_t x) { return (x + SB - 1) / SB * SB; }
 inline size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
 // Epilogues: SE_STAT  S <- beta S + gscale C into the caller's dense statistic, S + eps I to c;
-//            SE_PLAIN c = C;   SE_OUT  the optimizer update
+//            SE_PLAIN c = C
 //            into the caller's parameters or Delta W fragments;   SE_SUB  c <- c - C.
-enum { SE_STAT = 0, SE_PLAIN = 1, SE_OUT = 3, SE_SUB = 4 };
+enum { SE_STAT = 0, SE_PLAIN = 1, SE_SUB = 4 };
 
 struct ShGemm {
   int64_t M, N, K;      // multiples of 128, 128, 32
   int64_t ldp, ldq;     // row strides of P [M][K] and Q [N][K]
-  int64_t sp, sq;       // batch strides: matrix b reads P + (b / pdiv) sp and Q + (b / qdiv) sq
-  int pdiv, qdiv;       // 0 means 1; 2 lets two consecutive problems share an operand
+  int64_t sp, sq;       // batch strides
   const float* P;
   const float* Q;
   float* c;             // output
@@ -91,8 +90,8 @@ __device__ __forceinline__ void sh_gemm_body(const ShGemm& g, const PtrTable& st
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
   const int wm = BN == SB ? wave >> 1 : wave, wn = BN == SB ? wave & 1 : 0;
-  const float* Pg = g.P + static_cast<int64_t>(b / g.pdiv) * g.sp + static_cast<int64_t>(tm) * SB * g.ldp;
-  const float* Qg = g.Q + static_cast<int64_t>(b / g.qdiv) * g.sq + static_cast<int64_t>(tn) * BN * g.ldq;
+  const float* Pg = g.P + static_cast<int64_t>(b) * g.sp + static_cast<int64_t>(tm) * SB * g.ldp;
+  const float* Qg = g.Q + static_cast<int64_t>(b) * g.sq + static_cast<int64_t>(tn) * BN * g.ldq;
 
   const int ld_row = t >> 3, ld_k = (t & 7) * 4;  // rows ld_row + 32 x (x = 0..3), 4 consecutive k
   // Long sums of the statistics (k up to the other extent of the matrix, terms of one sign on the
@@ -184,9 +183,7 @@ __device__ __forceinline__ void sh_gemm_body(const ShGemm& g, const PtrTable& st
       float v[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) v[r] = tot[i][j][r];
-      if (EPI == SE_OUT) {
-        store_out_tile(o, s, b, row0, col, v);
-      } else if (EPI == SE_PLAIN) {
+      if (EPI == SE_PLAIN) {
         put16(g.c + cb, g.ldc, row0, col, v, mirror);
       } else if (EPI == SE_SUB) {
         float* C = g.c + cb;
@@ -246,8 +243,6 @@ template <int EPI, bool SYM, int BN = SB>
 hipError_t launch_gemm(ShGemm g, int nb, const PtrTable& stat, const Shape& s, const OutSpec& o, hipStream_t st) {
   if (g.M < SB || g.N < BN || g.K < SK || g.M % SB || g.N % BN || g.K % SK || (SYM && g.M != g.N)) return hipErrorInvalidValue;
   if (g.ldc == 0) g.ldc = g.N, g.sc = g.M * g.N;
-  if (g.pdiv == 0) g.pdiv = 1;
-  if (g.qdiv == 0) g.qdiv = 1;
   const int64_t tm = g.M / SB, tn = g.N / BN;
   const int64_t blocks = (SYM ? tm * (tm + 1) / 2 : tm * tn) * nb;
   if constexpr (EPI == SE_STAT)

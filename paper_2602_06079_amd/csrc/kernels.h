@@ -168,14 +168,15 @@ inline GemmDims split2_dims(int64_t d, int nb) {
   return GemmDims{d, d, d, 2 * d, 2 * d, 2 * d * d, 2 * d * d, nb, 3, 0x001u, 0x010u};
 }
 
-// Three bf16 terms, for matrices of any magnitude (bf16 has fp32's exponents): six products of terms, three if the second
+// Three bf16 terms, for matrices of any magnitude (bf16 has fp32's exponents): six products of terms, three if one
 // operand is a matrix of bf16 values, i.e. of one term.  C = P Q^T, P [nb][M][3 K], Q [nb][N][qterms K]:
 //   c [nb][M][3 N], the result as three terms
 hipError_t launch_split3(const GemmDims& d, const void* p, const void* q, void* c, hipStream_t st);
 //   the result as the last product of launch_final_bf16 (o: the caller's buffers)
 hipError_t launch_split3_final(const GemmDims& d, const void* p, const void* q, const Shape& s, const OutSpec& o, hipStream_t st);
-inline GemmDims split3_dims(int64_t M, int64_t N, int64_t K, int qterms, int nb) {
+inline GemmDims split3_dims(int64_t M, int64_t N, int64_t K, int qterms, int nb, int pterms = 3) {
   // terms 2 0, 0 2, 1 1, 1 0, 0 1, 0 0 of P and Q, or 2, 1, 0 of P: the small products first
+  if (pterms == 1) return GemmDims{M, N, K, K, 3 * K, M * K, 3 * N * K, nb, 3, 0u, 0x012u};
   if (qterms == 1) return GemmDims{M, N, K, 3 * K, K, 3 * M * K, N * K, nb, 3, 0x012u, 0u};
   return GemmDims{M, N, K, 3 * K, 3 * K, 3 * M * K, 3 * N * K, nb, 6, 0x001102u, 0x010120u};
 }

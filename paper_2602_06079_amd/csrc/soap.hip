@@ -6,16 +6,16 @@
 //   P <- P (1 - lr wd) - lr N  (or Delta W = -lr N);
 //   L <- beta2 L + (1 - beta2) G G^T,  R <- beta2 R + (1 - beta2) G^T G;
 //   on a refresh step  Q_L <- orthogonal factor of QR(L Q_L),  Q_R likewise.
-// State and sums are fp32; the products run on v_mfma_f32_32x32x2_f32, with two exceptions on the bf16 matrix
-// cores (the kernels of the Muon step, operands in its panel layout): the statistics of gradients that arrive as
-// bf16 (their own values are the operands, every product is exact in fp32, the sums stay fp32), and, if the caller
-// asks for it (bf16_rotations), the rotations with the bases, M and N' rounded to bf16.
+// State and sums are fp32.  On the bf16 matrix cores (the kernels of the Muon step, operands in its panel layout) run
+// the rotations, on fp32 values held as three bf16 terms (or, if the caller asks for it with bf16_rotations, with the
+// bases, M and N' rounded to bf16), and the statistics of gradients that arrive as bf16 (their own values are the
+// operands, every product is exact in fp32).  The statistics of fp32 gradients and the refresh run on
+// v_mfma_f32_32x32x2_f32.
 //
 // The products all take the form C[i][j] = sum_k P[i][k] Q[j][k].  The rotation into the basis
 // runs right side first with its result written transposed, (G Q_R)^T = Q_R^T-rows times G-rows,
 // so that the left side finds its second operand contiguous along k; the rotation back runs
-// the same way round.  G and M travel through the rotation as two problems of one launch that
-// share the basis operand; with a rotated momentum kept by the caller (mom_rot) only G is rotated
+// the same way round.  G is rotated first, then M; with a rotated momentum kept by the caller (mom_rot) only G is rotated
 // and M' follows M' <- beta1 M' + (1 - beta1) G' in the Adam kernel.
 //
 // QR refresh: blocked Householder factorisation with panels of 32 columns, on the transposed
@@ -56,15 +56,15 @@ constexpr int QWAVES = QTH / 64;
 // Where k_soap_load leaves its results: fp32 working copies and / or bf16 images in the panel layout
 // (panel_layout.h; padded to multiples of 256, operands of the bf16 MFMA kernels), each in both orientations.
 struct LoadOut {
-  float *gm, *gmt;               // fp32: gm [nb][2][rp][cp] (G, then M) and gmt [nb][2][cp][rp]
-  bool g32, m32;                 // which of their two planes are wanted
+  float *gm, *gmt;               // fp32 G [nb][rp][cp] and G^T [nb][cp][rp]; nullptr: not wanted
+  __bf16 *g3, *g3t, *m3, *m3t;   // three bf16 terms: G [nb][rp2][3 cp2], G^T [nb][cp2][3 rp2], M, M^T; nullptr: not wanted
   __bf16 *gp, *gpt, *mp, *mpt;   // bf16 panels: G [nb][rp2][cp2], G^T [nb][cp2][rp2], M, M^T; nullptr: not wanted
   int64_t rp2, cp2;
 };
 
 // G (bf16 or fp32, whole or tp column fragments) and the momentum M <- beta1 M + (1 - beta1) G
 // (fp32, dense, in the caller's buffer) -> working copies of both as `w` asks, zero outside rows x cols.
-// One block per 64 x 64 tile of the padded matrix (padded to 256 if a bf16 image is wanted, else to 128).
+// One block per 64 x 64 tile of the matrix padded to multiples of 256.
 // VEC: cols and cols / tp are multiples of 8, so a lane's 8 consecutive elements lie in one fragment and every
 // access of the caller's arrays is a 16-byte vector.
 template <bool VEC>
@@ -74,8 +74,8 @@ __global__ __launch_bounds__(NTH) void k_soap_load(Shape s, PtrTable grad, int g
   const int b = blockIdx.z, r0 = blockIdx.y * 64, c0 = blockIdx.x * 64, t = threadIdx.x;
   const int wf = static_cast<int>(s.wfrag);
   const int64_t plane = rp * cp;
-  float* gs = w.gm + static_cast<int64_t>(b) * 2 * plane;
-  float* gt = w.gmt + static_cast<int64_t>(b) * 2 * plane;
+  float* gs = w.gm ? w.gm + static_cast<int64_t>(b) * plane : nullptr;
+  float* gt = w.gm ? w.gmt + static_cast<int64_t>(b) * plane : nullptr;
   float* m = static_cast<float*>(mom.p[b]);
   if (VEC) {
     const int cv = (t & 7) * 8;
@@ -116,13 +116,9 @@ __global__ __launch_bounds__(NTH) void k_soap_load(Shape s, PtrTable grad, int g
         m4[0] = mv[half][0], m4[1] = mv[half][1];
       }
       if (row < rp && col < cp) {
-        if (w.g32) {
+        if (gs) {
           f32x4* o = reinterpret_cast<f32x4*>(gs + static_cast<int64_t>(row) * cp + col);
           o[0] = gv[half][0], o[1] = gv[half][1];
-        }
-        if (w.m32) {
-          f32x4* o = reinterpret_cast<f32x4*>(gs + plane + static_cast<int64_t>(row) * cp + col);
-          o[0] = mv[half][0], o[1] = mv[half][1];
         }
       }
     }
@@ -142,22 +138,18 @@ __global__ __launch_bounds__(NTH) void k_soap_load(Shape s, PtrTable grad, int g
       m[am] = mv;
     }
     if (row < rp && col < cp) {
-      if (w.g32) gs[static_cast<int64_t>(row) * cp + col] = g;
-      if (w.m32) gs[plane + static_cast<int64_t>(row) * cp + col] = mv;
+      if (gs) gs[static_cast<int64_t>(row) * cp + col] = g;
     }
     tg[r][c] = g;
     tm[r][c] = mv;
   }
   }
   __syncthreads();
-  if (w.g32 || w.m32) {
+  if (gs) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int idx = e * NTH + t, r = idx >> 6, c = idx & 63;  // r: column of G, c: row of G
-      if (c0 + r < cp && r0 + c < rp) {
-        if (w.g32) gt[static_cast<int64_t>(c0 + r) * rp + r0 + c] = tg[c][r];
-        if (w.m32) gt[plane + static_cast<int64_t>(c0 + r) * rp + r0 + c] = tm[c][r];
-      }
+      if (c0 + r < cp && r0 + c < rp) gt[static_cast<int64_t>(c0 + r) * rp + r0 + c] = tg[c][r];
     }
   }
   const int64_t p2 = static_cast<int64_t>(b) * w.rp2 * w.cp2;
@@ -165,56 +157,63 @@ __global__ __launch_bounds__(NTH) void k_soap_load(Shape s, PtrTable grad, int g
   if (w.gpt) tile_to_panels(tg, w.gpt + p2, r0, c0, w.rp2, true, t);
   if (w.mp) tile_to_panels(tm, w.mp + p2, r0, c0, w.cp2, false, t);
   if (w.mpt) tile_to_panels(tm, w.mpt + p2, r0, c0, w.rp2, true, t);
+  if (w.g3) tile_to_terms3(tg, w.g3 + 3 * p2, r0, c0, w.cp2, false, t);
+  if (w.g3t) tile_to_terms3(tg, w.g3t + 3 * p2, r0, c0, w.rp2, true, t);
+  if (w.m3) tile_to_terms3(tm, w.m3 + 3 * p2, r0, c0, w.cp2, false, t);
+  if (w.m3t) tile_to_terms3(tm, w.m3t + 3 * p2, r0, c0, w.rp2, true, t);
 }
 
-// Adam in the rotated space.  rot [nb][2][rp][cp] holds G' and (unless `incremental`) M'; V (dense,
-// caller's) is updated in place; N' = (c1 M') / (sqrt(c2 V) + eps) goes to np [nb][rp][cp], or
-// transposed to [nb][cp][rp]; zero outside rows x cols.  If the caller keeps the rotated momentum
-// (`keep`, dense, mrot): incremental: M' = beta1 mrot + (1 - beta1) G'; either way mrot <- M'.
+// Adam in the rotated space.  G' and (unless `incremental`) M' are dense fp32 [rows][cols], `stride` floats apart; V (dense, caller's) is
+// updated in place; N' = (c1 M') / (sqrt(c2 V) + eps) leaves as three bf16 terms per element, [rp2][3 cp2] panels or
+// transposed [cp2][3 rp2], zero outside rows x cols.  If the caller keeps the rotated momentum (`keep`, dense, mrot):
+// incremental: M' = beta1 mrot + (1 - beta1) G'; either way mrot <- M'.
 __global__ __launch_bounds__(NTH) void k_soap_adam(Shape s, PtrTable var, PtrTable mrot, bool keep, bool incremental,
-                                                    const float* __restrict__ rot, int64_t rp, int64_t cp, float beta1,
-                                                    float beta2, float c1, float c2, float eps, int transposed,
-                                                    float* __restrict__ np) {
+                                                    const float* __restrict__ grot, const float* __restrict__ m_rot, int64_t stride,
+                                                    int64_t rp2, int64_t cp2, float beta1, float beta2, float c1, float c2, float eps,
+                                                    int transposed, __bf16* __restrict__ np) {
   __shared__ float tile[64][65];
   const int b = blockIdx.z, r0 = blockIdx.y * 64, c0 = blockIdx.x * 64, t = threadIdx.x;
-  const int64_t plane = rp * cp;
-  const float* gr = rot + static_cast<int64_t>(b) * 2 * plane;
+  const int64_t at = b * stride;
+  const float* gr = grot + at;
   float* v = static_cast<float*>(var.p[b]);
-  float* out = np + static_cast<int64_t>(b) * plane;
+  float* mr = static_cast<float*>(mrot.p[b]);
+  float go[16], vo[16], mo[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {   // all old values first: one memory latency for the tile
+    const int idx = e * NTH + t, row = r0 + (idx >> 6), col = c0 + (idx & 63);
+    const bool in = row < s.rows && col < s.cols;
+    const int64_t av = static_cast<int64_t>(row) * s.cols + col;
+    go[e] = in ? gr[av] : 0.f;
+    vo[e] = in ? v[av] : 0.f;
+    mo[e] = !in ? 0.f : incremental ? mr[av] : m_rot[at + av];
+  }
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
-    const int idx = e * NTH + t, r = idx >> 6, c = idx & 63;
-    const int row = r0 + r, col = c0 + c;
+    const int idx = e * NTH + t, r = idx >> 6, c = idx & 63, row = r0 + r, col = c0 + c;
     float n = 0.f;
     if (row < s.rows && col < s.cols) {
-      const int64_t at = static_cast<int64_t>(row) * cp + col, av = static_cast<int64_t>(row) * s.cols + col;
-      const float g = gr[at];
-      float* mr = static_cast<float*>(mrot.p[b]);
-      const float m = incremental ? __builtin_fmaf(beta1, mr[av], (1.f - beta1) * g) : gr[plane + at];
+      const int64_t av = static_cast<int64_t>(row) * s.cols + col;
+      const float g = go[e];
+      const float m = incremental ? __builtin_fmaf(beta1, mo[e], (1.f - beta1) * g) : mo[e];
       if (keep) mr[av] = m;
-      const float vn = __builtin_fmaf(beta2, v[av], (1.f - beta2) * (g * g));
+      const float vn = __builtin_fmaf(beta2, vo[e], (1.f - beta2) * (g * g));
       v[av] = vn;
       n = (c1 * m) / (sqrtf(c2 * vn) + eps);
     }
-    if (transposed)
-      tile[r][c] = n;
-    else
-      out[static_cast<int64_t>(row) * cp + col] = n;
+    tile[r][c] = n;
   }
-  if (!transposed) return;
   __syncthreads();
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int idx = e * NTH + t, r = idx >> 6, c = idx & 63;
-    out[static_cast<int64_t>(c0 + r) * rp + r0 + c] = tile[c][r];
-  }
+  tile_to_terms3(tile, np + static_cast<int64_t>(b) * 3 * rp2 * cp2, r0, c0, transposed ? rp2 : cp2, transposed != 0, t);
 }
 
-// The caller's basis Q (d x d, dense fp32) -> padded working copies in both orientations, zero outside d x d: fp32
-// [dp][dp] (if `f32`) and / or bf16 panels [dp2][dp2] (if given).  One block per 64 x 64 tile of the larger padding.
-__global__ __launch_bounds__(NTH) void k_soap_load_basis(PtrTable q, int64_t d, int64_t dp, bool f32, float* __restrict__ straight,
-                                                          float* __restrict__ transposed, int64_t dp2, __bf16* __restrict__ sp,
-                                                          __bf16* __restrict__ tp) {
+// The caller's basis Q (d x d, dense fp32) -> what its readers want, zero outside d x d: its transpose in fp32 [dp][dp]
+// (for the refresh), and in both orientations bf16 panels [dp2][dp2] or three bf16 terms [dp2][3 dp2]; nullptr: not
+// wanted.  One block per 64 x 64 tile of the larger padding.
+struct BasisOut {
+  float* t32;
+  __bf16 *sp, *tp, *s3, *t3;
+};
+__global__ __launch_bounds__(NTH) void k_soap_load_basis(PtrTable q, int64_t d, int64_t dp, int64_t dp2, BasisOut w) {
   __shared__ float tile[64][65];
   const int b = blockIdx.z, r0 = blockIdx.y * 64, c0 = blockIdx.x * 64, t = threadIdx.x;
   const float* src = static_cast<const float*>(q.p[b]);
@@ -222,20 +221,21 @@ __global__ __launch_bounds__(NTH) void k_soap_load_basis(PtrTable q, int64_t d, 
   for (int e = 0; e < 16; ++e) {
     const int idx = e * NTH + t, r = idx >> 6, c = idx & 63;
     const int64_t row = r0 + r, col = c0 + c;
-    const float val = row < d && col < d ? src[row * d + col] : 0.f;
-    if (f32 && row < dp && col < dp) straight[(b * dp + row) * dp + col] = val;
-    tile[r][c] = val;
+    tile[r][c] = row < d && col < d ? src[row * d + col] : 0.f;
   }
   __syncthreads();
-  if (f32) {
+  if (w.t32) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int idx = e * NTH + t, r = idx >> 6, c = idx & 63;  // r: column of Q, c: row of Q
-      if (c0 + r < dp && r0 + c < dp) transposed[(b * dp + c0 + r) * dp + r0 + c] = tile[c][r];
+      if (c0 + r < dp && r0 + c < dp) w.t32[(b * dp + c0 + r) * dp + r0 + c] = tile[c][r];
     }
   }
-  if (sp) tile_to_panels(tile, sp + b * dp2 * dp2, r0, c0, dp2, false, t);
-  if (tp) tile_to_panels(tile, tp + b * dp2 * dp2, r0, c0, dp2, true, t);
+  const int64_t p2 = b * dp2 * dp2;
+  if (w.sp) tile_to_panels(tile, w.sp + p2, r0, c0, dp2, false, t);
+  if (w.tp) tile_to_panels(tile, w.tp + p2, r0, c0, dp2, true, t);
+  if (w.s3) tile_to_terms3(tile, w.s3 + 3 * p2, r0, c0, dp2, false, t);
+  if (w.t3) tile_to_terms3(tile, w.t3 + 3 * p2, r0, c0, dp2, true, t);
 }
 
 // Adam in the rotated space on bf16 panels: G' (and, unless `incremental`, M') [rp2][cp2] panels in, N' panels
@@ -874,7 +874,10 @@ __global__ __launch_bounds__(QTH) void k_qr_block_u(const float* __restrict__ cb
 }
 
 struct Carve {   // float offsets into the workspace of one launch batch
-  size_t gm, gmt, t1, rot, np, yt, ql, qlt, qr, qrt, stat, wk, vall, y2, ybuf, tau, wt, qt, tb, cb, ub, u2, total_bytes;
+  size_t gm, gmt, qlt, qrt, stat, wk, vall, y2, ybuf, tau, wt, qt, tb, cb, ub, u2, total_bytes;
+  // fp32 rotations: G', M' dense; three bf16 terms per element, padded to 256 (offsets in floats as well): G (if it is not
+  // bf16 itself) and M in the orientations wanted, X Q_R transposed, N', its half-rotated image, the bases
+  size_t rotg, rotm, g3, g3t, m3, m3t, t3, n3, y3, ql3, ql3t, qr3, qr3t;
   // bf16 rotations (offsets in floats as well; each array holds bf16 panels padded to 256)
   size_t gp, gpt, mp, mpt, as_g, at_g, as_m, at_m, rg, rgt, rm, rmt, npn, npt, ys, yst, qlp, qltp, qrp, qrtp;
 };
@@ -890,6 +893,9 @@ Sides sides(const canz_soap_group& g, const canz_soap_hparams& hp) {
 // a fraction of its time.
 bool bf16_statistics(const canz_soap_group& g) { return g.grad_dtype == CANZ_DT_BF16; }
 
+// floats from one dense rows x cols working matrix to the next: each starts aligned, as the callers' own buffers do
+inline int64_t dense_stride(int64_t rows, int64_t cols) { return (rows * cols + 63) / 64 * 64; }
+
 Carve carve(int64_t rows, int64_t cols, int nb, Sides u, bool refresh, bool bf16, bool stat16) {
   const size_t rp = pad128(rows), cp = pad128(cols);
   const size_t dm = std::max(u.left ? rp : 0, u.right ? cp : 0);
@@ -901,13 +907,8 @@ Carve carve(int64_t rows, int64_t cols, int nb, Sides u, bool refresh, bool bf16
     return at;
   };
   const size_t plane = rp * cp;
-  c.gm = take(2 * nb * plane), c.gmt = take(2 * nb * plane);
-  c.t1 = take(u.left && u.right ? 2 * nb * plane : 0);
-  c.rot = take(2 * nb * plane);
-  c.np = take(nb * plane);
-  c.yt = take(u.left && u.right ? nb * plane : 0);
-  c.ql = take(u.left ? nb * rp * rp : 0), c.qlt = take(u.left ? nb * rp * rp : 0);
-  c.qr = take(u.right ? nb * cp * cp : 0), c.qrt = take(u.right ? nb * cp * cp : 0);
+  c.gm = take(stat16 ? 0 : nb * plane), c.gmt = take(stat16 ? 0 : nb * plane);
+  c.qlt = take(refresh && u.left ? nb * rp * rp : 0), c.qrt = take(refresh && u.right ? nb * cp * cp : 0);
   c.stat = take(nb * dm * dm);
   if (refresh) {
     c.wk = take(nb * dm * dm);
@@ -923,7 +924,17 @@ Carve carve(int64_t rows, int64_t cols, int nb, Sides u, bool refresh, bool bf16
     c.u2 = take(nb * dm * QBLK);       // U2^T of every block
   }
   const size_t rp2 = pad256(rows), cp2 = pad256(cols), p2 = nb * rp2 * cp2 / 2;   // floats that hold a batch of panels
-  if (bf16 || stat16) c.gp = take(bf16 || u.left ? p2 : 0), c.gpt = take(bf16 || u.right ? p2 : 0);
+  if (bf16 || stat16) c.gp = take(p2), c.gpt = take(p2);
+  if (!bf16) {
+    const size_t p3 = nb * rp2 * cp2 * 3 / 2, l3 = nb * rp2 * rp2 * 3 / 2, r3 = nb * cp2 * cp2 * 3 / 2;
+    const bool both = u.left && u.right;
+    c.rotg = take(nb * dense_stride(rows, cols)), c.rotm = take(nb * dense_stride(rows, cols));
+    c.g3 = take(!stat16 && u.right ? p3 : 0), c.g3t = take(!stat16 && !u.right ? p3 : 0);
+    c.m3 = take(u.right ? p3 : 0), c.m3t = take(u.right ? 0 : p3);
+    c.t3 = c.y3 = take(both ? p3 : 0), c.n3 = take(p3);   // t3 is done with before y3 is written
+    c.ql3 = take(u.left ? l3 : 0), c.ql3t = take(u.left ? l3 : 0);
+    c.qr3 = take(u.right ? r3 : 0), c.qr3t = take(u.right ? r3 : 0);
+  }
   if (bf16) {
     const bool both = u.left && u.right;
     c.mp = take(p2), c.mpt = take(p2);
@@ -993,16 +1004,14 @@ int check_group(const canz_soap_group& g, int idx, bool need_ptrs, const canz_so
   return CANZ_OK;
 }
 
-inline int64_t floor128(int64_t x) { return x / SB * SB; }
-
 // Basis refresh of one side: q (caller's, d x d) <- Q factor of QR(S q), S = the padded statistic in
 // `stat` [nb][dp][dp], qt_old [nb][dp][dp] the transposed padded copy of the current basis.
 int refresh_side(void* const* q_tab, int first, int nb, int64_t d, int64_t dp, const float* stat, const float* qt_old,
                  float* ws, const Carve& c, const Shape& s, const OutSpec& o, hipStream_t st) {
   const PtrTable none{};
   const int64_t dd = dp * dp;
-  float *wk = ws + c.wk, *vall = ws + c.vall, *y2 = ws + c.y2, *ybuf = ws + c.ybuf, *wt = ws + c.wt, *qt = ws + c.qt;
-  const int64_t s_vall = dp * dp, s_y = dp * QB;
+  float *wk = ws + c.wk, *vall = ws + c.vall, *y2 = ws + c.y2, *qt = ws + c.qt;
+  const int64_t s_vall = dp * dp;
   auto fill = [&](float* p, int64_t elems, int64_t ld, int identity) {
     const unsigned blocks = static_cast<unsigned>(std::min<int64_t>(2048, (elems + NTH - 1) / NTH));
     hipLaunchKernelGGL(k_soap_fill, dim3(blocks, nb), dim3(NTH), 0, st, p, elems, ld, identity);
@@ -1133,7 +1142,7 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
   s.tall = g.rows > g.cols;
   s.tp = g.tp;
   s.wfrag = g.cols / g.tp;
-  PtrTable grad{}, mom{}, var{}, none{};
+  PtrTable grad{}, mom{}, var{};
   for (int i = 0; i < nb * g.tp; ++i) grad.p[i] = const_cast<void*>(g.grad[first * g.tp + i]);
   for (int i = 0; i < nb; ++i) mom.p[i] = g.mom[first + i], var.p[i] = g.var[first + i];
   OutSpec o{};
@@ -1144,9 +1153,8 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
   o.decay = static_cast<float>(1.0 - static_cast<double>(hp.lr) * static_cast<double>(hp.weight_decay));
   o.neg_lr_scale = -hp.lr;
 
-  float *gm = ws + c.gm, *gmt = ws + c.gmt, *t1 = ws + c.t1, *rot = ws + c.rot, *np = ws + c.np, *yt = ws + c.yt;
-  float *ql = ws + c.ql, *qlt = ws + c.qlt, *qr = ws + c.qr, *qrt = ws + c.qrt, *stat = ws + c.stat;
-  const dim3 tiles(static_cast<unsigned>(cp / 64), static_cast<unsigned>(rp / 64), static_cast<unsigned>(nb));
+  float *gm = ws + c.gm, *gmt = ws + c.gmt;
+  float *qlt = ws + c.qlt, *qrt = ws + c.qrt, *stat = ws + c.stat;
 
   // With a valid rotated momentum from the caller only G is rotated (M' follows its own recurrence in the rotated
   // space, which is the same linear map as long as the bases stand still); otherwise G and M.
@@ -1158,66 +1166,64 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
 
   prof_mark(st, CANZ_KERNEL_SOAP_LOAD, true);
   {
-    // fp32 copies: G for the fp32 rotations and the fp32 statistics, M for the fp32 rotations; bf16 images: G for the
-    // bf16 rotations and statistics, M for the bf16 rotations of a step that rotates it (also the re-rotation of a
-    // kept M' after a refresh)
+    // fp32 copies: G for the fp32 statistics; bf16 images: G for the bf16 statistics and for either kind of rotation if it
+    // arrives as bf16, M for the bf16 rotations of a step that rotates it (also the re-rotation of a kept M' after a
+    // refresh); three terms: G that is fp32 and M for the fp32 rotations, in the orientation of the first product
     LoadOut w{};
-    w.gm = gm, w.gmt = gmt;
-    w.g32 = !bf16 || !stat16;
-    w.m32 = !bf16;
+    if (!stat16) w.gm = gm, w.gmt = gmt;
+    const bool rotate_m = !incremental || (hp.refresh && g.mom_rot != nullptr);
+    if (!bf16 && !stat16) (u.right ? w.g3 : w.g3t) = pan(u.right ? c.g3 : c.g3t);
+    if (!bf16 && rotate_m) (u.right ? w.m3 : w.m3t) = pan(u.right ? c.m3 : c.m3t);
     w.rp2 = rp2, w.cp2 = cp2;
-    if (bf16 || (stat16 && u.left)) w.gp = pan(c.gp);
-    if (bf16 || (stat16 && u.right)) w.gpt = pan(c.gpt);
-    if (bf16 && (!incremental || (hp.refresh && g.mom_rot != nullptr))) w.mp = pan(c.mp), w.mpt = pan(c.mpt);
-    const bool images = w.gp || w.gpt;
-    const dim3 grid(static_cast<unsigned>((images ? cp2 : cp) / 64), static_cast<unsigned>((images ? rp2 : rp) / 64),
-                    static_cast<unsigned>(nb));
+    if (bf16 || stat16) w.gp = pan(c.gp), w.gpt = pan(c.gpt);
+    if (bf16 && rotate_m) w.mp = pan(c.mp), w.mpt = pan(c.mpt);
+    const dim3 grid(static_cast<unsigned>(cp2 / 64), static_cast<unsigned>(rp2 / 64), static_cast<unsigned>(nb));
     if (g.cols % 8 == 0 && s.wfrag % 8 == 0)
       hipLaunchKernelGGL(k_soap_load<true>, grid, dim3(NTH), 0, st, s, grad, g.grad_dtype, mom, hp.beta1, rp, cp, w);
     else
       hipLaunchKernelGGL(k_soap_load<false>, grid, dim3(NTH), 0, st, s, grad, g.grad_dtype, mom, hp.beta1, rp, cp, w);
   }
-  // the bases: padded copies in both orientations, zero outside d x d: fp32 for the fp32 rotations and for the
-  // refresh (which multiplies the new statistic with the old basis), bf16 images for the bf16 rotations
-  auto load_basis = [&](void* const* tab, int64_t d, int64_t dp, float* straight, float* transposed, bool f32, int64_t dp2,
-                        __bf16* sp, __bf16* tp) {
+  // the bases, zero outside d x d: three terms for the fp32 rotations, bf16 images for the bf16 rotations, both in both
+  // orientations; fp32 and transposed for the refresh (which multiplies the new statistic with the old basis)
+  auto load_basis = [&](void* const* tab, int64_t d, int64_t dp, int64_t dp2, BasisOut w) {
     PtrTable q{};
     for (int i = 0; i < nb; ++i) q.p[i] = tab[first + i];
-    const unsigned side = static_cast<unsigned>((sp || tp ? dp2 : dp) / 64);
-    hipLaunchKernelGGL(k_soap_load_basis, dim3(side, side, static_cast<unsigned>(nb)), dim3(NTH), 0, st, q, d, dp, f32, straight,
-                       transposed, dp2, sp, tp);
+    const unsigned side = static_cast<unsigned>(dp2 / 64);
+    hipLaunchKernelGGL(k_soap_load_basis, dim3(side, side, static_cast<unsigned>(nb)), dim3(NTH), 0, st, q, d, dp, dp2, w);
   };
-  const bool basis32 = !bf16 || hp.refresh;
-  if (u.left) load_basis(g.qleft, g.rows, rp, ql, qlt, basis32, rp2, bf16 ? pan(c.qlp) : nullptr, bf16 ? pan(c.qltp) : nullptr);
-  if (u.right) load_basis(g.qright, g.cols, cp, qr, qrt, basis32, cp2, bf16 ? pan(c.qrp) : nullptr, bf16 ? pan(c.qrtp) : nullptr);
+  auto basis_out = [&](float* t32, size_t sp, size_t tp, size_t s3, size_t t3) {
+    return bf16 ? BasisOut{t32, pan(sp), pan(tp), nullptr, nullptr} : BasisOut{t32, nullptr, nullptr, pan(s3), pan(t3)};
+  };
+  if (u.left) load_basis(g.qleft, g.rows, rp, rp2, basis_out(hp.refresh ? qlt : nullptr, c.qlp, c.qltp, c.ql3, c.ql3t));
+  if (u.right) load_basis(g.qright, g.cols, cp, cp2, basis_out(hp.refresh ? qrt : nullptr, c.qrp, c.qrtp, c.qr3, c.qr3t));
   prof_mark(st, CANZ_KERNEL_SOAP_LOAD, false);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "load kernels: %s", hipGetErrorString(e));
 
-  // rotation into the bases of `per` planes of each matrix's (G, M) pair, from plane `p0` on: problem p is
-  // plane p0 + p % per of matrix p / per; consecutive problems of a matrix share the basis operand
-  auto rotate_in = [&](int p0, int per) -> int {
-    const int64_t step_ = per == 2 ? plane : 2 * plane, at = p0 * plane;
-    const int count = per * nb;
-    if (u.left && u.right) {
-      ShGemm a{};   // t1 = (X Q_R)^T: [cp][rp]
-      a.M = cp, a.N = rp, a.K = cp, a.ldp = cp, a.ldq = cp, a.sp = cp * cp, a.pdiv = per, a.sq = step_;
-      a.P = qrt, a.Q = gm + at, a.c = t1 + at, a.ldc = rp, a.sc = step_;
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false>(a, count, none, s, o, st)), "rotation (right)");
-      ShGemm bq{};  // rot = Q_L^T (X Q_R): [rp][cp]
-      bq.M = rp, bq.N = cp, bq.K = rp, bq.ldp = rp, bq.ldq = rp, bq.sp = rp * rp, bq.pdiv = per, bq.sq = step_;
-      bq.P = qlt, bq.Q = t1 + at, bq.c = rot + at, bq.ldc = cp, bq.sc = step_;
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false>(bq, count, none, s, o, st)), "rotation (left)");
-    } else if (u.left) {
-      ShGemm bq{};  // rot = Q_L^T X with X^T as the second operand
-      bq.M = rp, bq.N = cp, bq.K = rp, bq.ldp = rp, bq.ldq = rp, bq.sp = rp * rp, bq.pdiv = per, bq.sq = step_;
-      bq.P = qlt, bq.Q = gmt + at, bq.c = rot + at, bq.ldc = cp, bq.sc = step_;
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false>(bq, count, none, s, o, st)), "rotation (left)");
-    } else {
-      ShGemm a{};   // rot = X Q_R
-      a.M = rp, a.N = cp, a.K = cp, a.ldp = cp, a.ldq = cp, a.sp = step_, a.sq = cp * cp, a.qdiv = per;
-      a.P = gm + at, a.Q = qrt, a.c = rot + at, a.ldc = cp, a.sc = step_;
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false>(a, count, none, s, o, st)), "rotation (right)");
+  // The fp32 rotations run on the bf16 cores as well: the bases, M, N' and the intermediates are three bf16 terms per
+  // element (G too, if it is not bf16 itself), a product is six products of terms (three with a bf16 G) with fp32 sums
+  // (launch_split3).  At the rates the two kinds of core reach here (1.3 PFLOP/s against 150 TFLOP/s) that is 0.7 (0.35) of
+  // the fp32 MFMA's time, and closer to 64 bits, since that core rounds its sum every two k.  A plain step of
+  // 8 x 3072 x 1024 with bf16 gradients takes 2.78 ms against 4.00 ms with fp32 MFMA products; error of the update
+  // 0.9e-7 against 2.7e-7.
+  // X' = Q_L^T X Q_R for X [rp2][cp2] (two-sided or right side only) or X^T (left side only) of `terms` terms, dense
+  // rows x cols to the buffers of `to`
+  auto rotate_in = [&](const __bf16* x, int terms, const PtrTable& to) -> int {
+    Shape whole = s;
+    whole.tp = 1, whole.wfrag = g.cols;
+    OutSpec ro{};
+    ro.out = to, ro.out_dtype = CANZ_DT_F32, ro.out_mode = CANZ_OUT_DELTA, ro.decay = 1.f, ro.neg_lr_scale = 1.f;
+    if (!u.left) {   // X Q_R
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, launch_split3_final(split3_dims(rp2, cp2, cp2, 3, nb, terms), x, pan(c.qr3t), whole, ro, st),
+               "rotation (right)");
+      return CANZ_OK;
     }
+    if (u.right) {   // (X Q_R)^T [cp2][3 rp2]
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, launch_split3(split3_dims(cp2, rp2, cp2, terms, nb), pan(c.qr3t), x, pan(c.t3), st),
+               "rotation (right)");
+      x = pan(c.t3), terms = 3;
+    }
+    CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, launch_split3_final(split3_dims(rp2, cp2, rp2, terms, nb), pan(c.ql3t), x, whole, ro, st),
+             "rotation (left)");
     return CANZ_OK;
   };
   PtrTable mrot{};
@@ -1275,39 +1281,37 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
                "back rotation (right, bf16)");
     }
   } else {
-    if (int rc = rotate_in(0, incremental ? 1 : 2)) return rc;
-
-    {
-      const int transposed = u.left && !u.right;
-      prof_mark(st, CANZ_KERNEL_SOAP_ADAM, true);
-      hipLaunchKernelGGL(k_soap_adam, tiles, dim3(NTH), 0, st, s, var, mrot, g.mom_rot != nullptr, incremental, rot, rp, cp,
-                         hp.beta1, hp.beta2, static_cast<float>(c1), static_cast<float>(c2), hp.eps, transposed, np);
-      prof_mark(st, CANZ_KERNEL_SOAP_ADAM, false);
-      if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "adam kernel: %s", hipGetErrorString(e));
-    }
+    auto dense = [&](size_t at) {   // the batch's dense rows x cols matrices in the workspace
+      PtrTable t{};
+      for (int i = 0; i < nb; ++i) t.p[i] = ws + at + i * dense_stride(g.rows, g.cols);
+      return t;
+    };
+    const __bf16* gx = stat16 ? pan(u.right ? c.gp : c.gpt) : pan(u.right ? c.g3 : c.g3t);
+    if (int rc = rotate_in(gx, stat16 ? 1 : 3, dense(c.rotg))) return rc;
+    if (!incremental)
+      if (int rc = rotate_in(pan(u.right ? c.m3 : c.m3t), 3, dense(c.rotm))) return rc;
+    const int transposed = u.left && !u.right;   // the left side alone takes N'^T as its second operand
+    const dim3 tiles2(static_cast<unsigned>(cp2 / 64), static_cast<unsigned>(rp2 / 64), static_cast<unsigned>(nb));
+    prof_mark(st, CANZ_KERNEL_SOAP_ADAM, true);
+    hipLaunchKernelGGL(k_soap_adam, tiles2, dim3(NTH), 0, st, s, var, mrot, g.mom_rot != nullptr, incremental, ws + c.rotg, ws + c.rotm,
+                       dense_stride(g.rows, g.cols), rp2, cp2, hp.beta1, hp.beta2, static_cast<float>(c1), static_cast<float>(c2), hp.eps, transposed, pan(c.n3));
+    prof_mark(st, CANZ_KERNEL_SOAP_ADAM, false);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "adam kernel: %s", hipGetErrorString(e));
 
     // rotation back, the last product writes the update
-    if (u.left && u.right) {
-      ShGemm cq{};  // yt = (N' Q_R^T)^T: [cp][rp]
-      cq.M = cp, cq.N = rp, cq.K = cp, cq.ldp = cp, cq.ldq = cp, cq.sp = cp * cp, cq.sq = plane;
-      cq.P = qr, cq.Q = np, cq.c = yt;
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false>(cq, nb, none, s, o, st)), "back rotation (right)");
-      ShGemm dq{};
-      dq.M = rp, dq.N = cp, dq.K = rp, dq.ldp = rp, dq.ldq = rp, dq.sp = rp * rp, dq.sq = plane;
-      dq.P = ql, dq.Q = yt;
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_OUT, false>(dq, nb, none, s, o, st)), "back rotation (left)");
-    } else if (u.left) {
-      ShGemm dq{};  // np holds N'^T
-      dq.M = rp, dq.N = cp, dq.K = rp, dq.ldp = rp, dq.ldq = rp, dq.sp = rp * rp, dq.sq = plane;
-      dq.P = ql, dq.Q = np;
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_OUT, false>(dq, nb, none, s, o, st)), "back rotation (left)");
+    if (!u.left) {
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, launch_split3_final(split3_dims(rp2, cp2, cp2, 3, nb), pan(c.n3), pan(c.qr3), s, o, st),
+               "back rotation (right)");
     } else {
-      ShGemm cq{};
-      cq.M = rp, cq.N = cp, cq.K = cp, cq.ldp = cp, cq.ldq = cp, cq.sp = plane, cq.sq = cp * cp;
-      cq.P = np, cq.Q = qr;
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_OUT, false>(cq, nb, none, s, o, st)), "back rotation (right)");
+      const __bf16* n = pan(c.n3);
+      if (u.right) {   // (N' Q_R^T)^T [cp2][3 rp2]
+        CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, launch_split3(split3_dims(cp2, rp2, cp2, 3, nb), pan(c.qr3), n, pan(c.y3), st),
+                 "back rotation (right)");
+        n = pan(c.y3);
+      }
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, launch_split3_final(split3_dims(rp2, cp2, rp2, 3, nb), pan(c.ql3), n, s, o, st),
+               "back rotation (left)");
     }
-
   }
 
   // statistics (and, on a refresh step, the new basis) side by side
@@ -1328,7 +1332,7 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
       }
     } else {
       ShGemm q{};
-      q.M = dp, q.N = dp, q.K = kp, q.ldp = kp, q.ldq = kp, q.sp = 2 * plane, q.sq = 2 * plane;
+      q.M = dp, q.N = dp, q.K = kp, q.ldp = kp, q.ldq = kp, q.sp = plane, q.sq = plane;
       q.P = side, q.Q = side, q.c = hp.refresh ? stat : nullptr, q.d = d, q.beta = hp.beta2, q.gscale = 1.f - hp.beta2, q.eps = 0.f;
       CANZ_HIP(CANZ_KERNEL_SOAP_STAT, (launch_gemm<SE_STAT, true>(q, nb, tab, s, o, st)), "statistics kernel");
     }
@@ -1343,8 +1347,8 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
     // the caller's rotated momentum follows the new bases, M' = Q_L^T M Q_R once more with the M of this step: bf16
     // operands as for every rotation of this mode; the last product leaves its fp32 sums in the caller's array
     prof_mark(st, CANZ_KERNEL_SOAP_LOAD, true);
-    if (u.left) load_basis(g.qleft, g.rows, rp, ql, qlt, false, rp2, nullptr, pan(c.qltp));
-    if (u.right) load_basis(g.qright, g.cols, cp, qr, qrt, false, cp2, nullptr, pan(c.qrtp));
+    if (u.left) load_basis(g.qleft, g.rows, rp, rp2, BasisOut{nullptr, nullptr, pan(c.qltp), nullptr, nullptr});
+    if (u.right) load_basis(g.qright, g.cols, cp, cp2, BasisOut{nullptr, nullptr, pan(c.qrtp), nullptr, nullptr});
     prof_mark(st, CANZ_KERNEL_SOAP_LOAD, false);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "basis load: %s", hipGetErrorString(e));
     Shape whole = s;
@@ -1366,16 +1370,13 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
                "momentum re-rotation (right, bf16)");
     }
   } else if (hp.refresh && g.mom_rot) {
-    // the same in fp32
+    // the same with the fp32 rotations
     prof_mark(st, CANZ_KERNEL_SOAP_LOAD, true);
-    if (u.left) load_basis(g.qleft, g.rows, rp, ql, qlt, true, rp2, nullptr, nullptr);
-    if (u.right) load_basis(g.qright, g.cols, cp, qr, qrt, true, cp2, nullptr, nullptr);
+    if (u.left) load_basis(g.qleft, g.rows, rp, rp2, BasisOut{nullptr, nullptr, nullptr, nullptr, pan(c.ql3t)});
+    if (u.right) load_basis(g.qright, g.cols, cp, cp2, BasisOut{nullptr, nullptr, nullptr, nullptr, pan(c.qr3t)});
     prof_mark(st, CANZ_KERNEL_SOAP_LOAD, false);
-    if (int rc = rotate_in(1, 1)) return rc;
-    prof_mark(st, CANZ_KERNEL_SOAP_ADAM, true);
-    hipLaunchKernelGGL(k_unpad, tiles, dim3(NTH), 0, st, s, mrot, rot + plane, 2 * plane, cp);
-    prof_mark(st, CANZ_KERNEL_SOAP_ADAM, false);
-    if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "momentum re-rotation: %s", hipGetErrorString(e));
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "basis load: %s", hipGetErrorString(e));
+    if (int rc = rotate_in(pan(u.right ? c.m3 : c.m3t), 3, mrot)) return rc;
   }
   return CANZ_OK;
 }

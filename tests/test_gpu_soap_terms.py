@@ -1,0 +1,81 @@
+"""The SOAP rotations on matrices of three bf16 terms: one and two sides, bf16 and fp32 gradients, sizes around the
+256-wide tiles, a kept rotated momentum, a refresh, and gradients of any magnitude."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def canz():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_06079_amd import binding
+    return binding
+
+
+def _step(torch, canz, rows, cols, n, limit, grad_dtype, keep, valid, refresh, level):
+    """One step from seeded state; (state before, state after) as dicts of tensor lists."""
+    g = torch.Generator(device="cuda").manual_seed(rows * 10007 + cols)
+    draw = lambda r, c: torch.randn(r, c, generator=g, device="cuda") * level  # noqa: E731
+    basis = lambda d: torch.linalg.qr(torch.randn(d, d, generator=g, device="cuda", dtype=torch.float64))[0].float().contiguous()  # noqa: E731
+    stat = lambda d: (lambda x: x @ x.t() / d)(draw(d, 2 * d))  # noqa: E731
+    left, right = rows <= limit, cols <= limit
+    st = dict(grad=[draw(rows, cols).to(grad_dtype) for _ in range(n)], mom=[draw(rows, cols) for _ in range(n)],
+              var=[sum(draw(rows, cols) ** 2 for _ in range(4)) / 4 for _ in range(n)],
+              left=[stat(rows) for _ in range(n)] if left else [], right=[stat(cols) for _ in range(n)] if right else [],
+              qleft=[basis(rows) for _ in range(n)] if left else [], qright=[basis(cols) for _ in range(n)] if right else [],
+              out=[torch.zeros(rows, cols, device="cuda") for _ in range(n)],
+              mom_rot=[draw(rows, cols) for _ in range(n)] if keep else [])
+    before = {k: [t.clone() for t in v] for k, v in st.items()}
+    grp = canz.SoapGroup(rows=rows, cols=cols, grad_dtype=canz.DT_BF16 if grad_dtype == torch.bfloat16 else canz.DT_F32, **st)
+    hp = canz.SoapHparams(beta1=0.75, beta2=0.5, lr=1.0, eps=1e-3 * level, step=5, refresh=int(refresh), mom_rot_valid=int(valid),
+                          max_precond_dim=limit, bias_correction=0, out_mode=canz.OUT_DELTA)
+    need = canz.canz_soap_workspace_bytes([grp], hp)
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")   # every byte a NaN: nothing may be read unwritten
+    canz.canz_soap_step([grp], hp, ws, need, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    return before, st
+
+
+def _rotate(q_left, q_right, x):
+    x = x.double()
+    if q_left is not None:
+        x = q_left.double().t() @ x
+    return x if q_right is None else x @ q_right.double()
+
+
+@pytest.mark.parametrize("rows,cols,n,limit,bf16,keep,valid,refresh,level", [
+    (256, 256, 1, 4096, True, False, False, False, 1.0),       # one tile
+    (255, 257, 2, 4096, True, True, False, False, 1.0),        # one short of a tile, one past it
+    (257, 255, 2, 4096, False, True, True, False, 1.0),
+    (1000, 2100, 3, 4096, False, False, False, False, 1.0),    # large and left-over small tiles
+    (300, 520, 3, 400, True, True, False, False, 1.0),         # left side only
+    (300, 520, 3, 400, False, True, True, True, 1.0),
+    (520, 301, 2, 400, True, True, True, True, 1.0),           # right side only
+    (521, 301, 3, 400, False, False, False, False, 1.0),       # odd strides between the working matrices
+    (1, 40, 2, 4096, True, True, False, False, 1.0),
+    (200, 300, 1, 4096, False, True, False, True, 1e-6),       # the terms have fp32's exponents
+    (200, 300, 1, 4096, False, True, False, True, 1e6),
+])
+def test_rotations_against_64_bits(canz, rows, cols, n, limit, bf16, keep, valid, refresh, level):
+    import torch
+    was, now = _step(torch, canz, rows, cols, n, limit, torch.bfloat16 if bf16 else torch.float32, keep, valid, refresh, level)
+    rel = lambda got, want: float((got.double() - want).norm() / want.norm())  # noqa: E731
+    pick = lambda t, i: t[i] if t else None  # noqa: E731
+    for i in range(n):
+        ql, qr = pick(was["qleft"], i), pick(was["qright"], i)
+        g_rot = _rotate(ql, qr, was["grad"][i])
+        m = 0.75 * was["mom"][i].double() + 0.25 * was["grad"][i].double()
+        m_rot = 0.75 * was["mom_rot"][i].double() + 0.25 * g_rot if valid else _rotate(ql, qr, m)
+        v = 0.5 * was["var"][i].double() + 0.5 * g_rot ** 2
+        n_rot = m_rot / (v.sqrt() + 1e-3 * level)
+        want = -_rotate(ql.t() if ql is not None else None, qr.t() if qr is not None else None, n_rot)
+        # three terms hold 24 bits, so an operand is off by 2^-24 and every fp32 sum by some 2^-24 of its terms: a
+        # rotation is within 5e-7 of its norm, two of them and the squares within 1e-6
+        assert rel(now["var"][i], v) <= 1e-6
+        assert rel(now["out"][i], want) <= 1e-6
+        if keep:
+            if refresh:   # the kept momentum follows the new bases
+                m_rot = _rotate(pick(now["qleft"], i), pick(now["qright"], i), now["mom"][i])
+            assert rel(now["mom_rot"][i], m_rot) <= 5e-7
