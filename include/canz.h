@@ -218,8 +218,8 @@ typedef struct {
  * dtypes and equal shape up to a transpose, at most 128 / tp of them and at most 2^30
  * padded elements per batch unless one matrix alone is larger; up to four consecutive small
  * batches run side by side within the same 2^30 elements, otherwise batches run one after
- * another on the stream, so for matrices below 2^30 elements at most about 13 GB are
- * asked for in bf16 mode, 20 GB in fp32 mode, whatever the share).
+ * another on the stream, so for matrices below 2^30 elements at most about 10 GB are
+ * asked for in bf16 mode, twice that in fp32 mode, whatever the share).
  * g: host array [n_groups]; pointer tables inside may be NULL for this call.
  */
 int canz_muon_workspace_bytes(const canz_group* g, int32_t n_groups,

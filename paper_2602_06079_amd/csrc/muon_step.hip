@@ -78,8 +78,8 @@ Carve carve(const Shape& s, int nb, int precision) {
   const size_t a_bytes = align_up(static_cast<size_t>(nb) * s.mp * s.mp * esz);
   Carve c{};
   size_t off = 0;
+  c.xt0 = off, off += x_bytes;   // X lies between the two X^T: with the unused one it is one free piece (see Spare)
   c.xw = off, off += x_bytes;
-  c.xt0 = off, off += x_bytes;
   c.xt1 = off, off += x_bytes;
   c.a = off, off += a_bytes;
   c.b = off, off += a_bytes;
@@ -239,11 +239,11 @@ int collect_batches(const canz_group* g, int n_groups, int out_mode, bool with_p
 // Speed (us, single steps -> stages): 4 x 25600 x 5120 35000 -> 20900, 5 x 4096 x 12288 14400 -> 10340, 2 x 2048 x 5632 1240 ->
 // 970, 1 x 1536 x 6144 795 -> 570, 1 x 5120 x 8192 3500 -> 3075, 1 x 3000 x 5000 1130 -> 1040; but 1 x 2048 x 3072 463 -> 482,
 // 1 x 1536 x 2304 329 -> 366 (the products of one small matrix leave most of the chip idle, and there are more of them):
-// hence m <= n / 2, from 2560 rows on m <= 2 n / 3.  The rule looks at the shape alone, so that a matrix's result does not
+// hence m <= n / 2, from 2560 rows on m <= 2 n / 3; and the spare arrays (Spare) have to fit.  The rule looks at the shape alone, so that a matrix's result does not
 // depend on what shares its launch.
 std::vector<int> stage_plan(const Shape& s, const canz_muon_hparams& hp) {
   std::vector<int> stages;
-  const bool wide = s.m >= 2560 ? 3 * s.m <= 2 * s.n : s.m >= 1536 && 2 * s.m <= s.n;
+  const bool wide = (s.m >= 2560 ? 3 * s.m <= 2 * s.n : s.m >= 1536 && 2 * s.m <= s.n) && 3 * s.mp < 2 * s.np;
   const bool merge = hp.precision == CANZ_PREC_BF16 && hp.ns_steps >= 3 && hp.c != 0.f && hp.a > 0.f && hp.a <= 3.5f && wide;
   for (int left = hp.ns_steps; left > 0;) {
     int len = 1;
@@ -253,7 +253,6 @@ std::vector<int> stage_plan(const Shape& s, const canz_muon_hparams& hp) {
   }
   return stages;
 }
-bool merges(const std::vector<int>& stages) { return !stages.empty() && stages[0] > 1; }
 
 // Launch batches that are too small to fill the chip on their own for long (fewer than 8
 // rounds of update tiles on 256 CUs) are run together, up to MAX_KINDS of them: their Gram,
@@ -283,30 +282,26 @@ std::vector<int> group_runs(const std::vector<Batch>& batches, const canz_muon_h
   return first;
 }
 
-// Further m x m arrays of a batch whose steps are merged, as offsets into its part of the tail: B A, two more images for the
-// polynomials and their products, four diagonals.  They live between two Gram products.  The diagonal of A, which the
-// Gram product itself leaves, lies in the X^T buffer that is not in use.
-struct Extra {
-  size_t t, b1, b2, diag, total;
+// Where the further m x m arrays of a batch whose steps are merged lie: B A, two more images for the polynomials and their
+// products, five diagonals.  Between a Gram product and the next update neither X nor the X^T that is not in use (xt[cur ^ 1])
+// is read, and they lie side by side: 2 m n elements of two bytes, of which 3 m m images leave at least 512 m bytes
+// (3 m < 2 n, both multiples of 256).  The diagonals are at the end that belongs to X^T, since the Gram product leaves that
+// of A while it reads X.  The image that the update multiplies X with must not lie there: it takes the place of A.
+struct Spare {
+  size_t t, b1, b2, diag;   // byte offsets from the start of the free piece
 };
-Extra extra(const Shape& s, int nb) {
+Spare spare(const Shape& s, int nb, int cur) {
   const size_t img = align_up(static_cast<size_t>(nb) * s.mp * s.mp * 2);
-  Extra x{};
-  x.t = 0, x.b1 = img, x.b2 = 2 * img, x.diag = 3 * img;
-  x.total = 3 * img + align_up(static_cast<size_t>(4) * nb * s.mp * sizeof(float));
-  return x;
+  const size_t diag = align_up(static_cast<size_t>(5) * nb * s.mp * sizeof(float));
+  const size_t all = 2 * align_up(static_cast<size_t>(nb) * s.mp * s.np * 2);
+  const size_t at = cur == 0 ? 0 : diag;   // X, X^T  or  X^T, X
+  return Spare{at, at + img, at + 2 * img, cur == 0 ? all - diag : 0};
 }
 
-// The tail of a run's workspace is the k-split scratch, which only Gram products use (the other products have k = m), and
-// between two Gram products the extra arrays.
 size_t run_bytes(const std::vector<Batch>& batches, int lo, int hi, const canz_muon_hparams& hp) {
-  size_t total = 0, more = 0;
-  for (int k = lo; k < hi; ++k) {
-    total += carve(batches[k].s0, batches[k].nb, hp.precision).total;
-    more += extra(batches[k].s0, batches[k].nb).total;
-  }
-  if (!merges(stage_plan(batches[lo].s0, hp))) more = 0;
-  return total + std::max(split_bytes(hp.precision), more);
+  size_t total = split_bytes(hp.precision);
+  for (int k = lo; k < hi; ++k) total += carve(batches[k].s0, batches[k].nb, hp.precision).total;
+  return total;
 }
 
 // One run: the batches lo .. hi-1 side by side in the workspace, then the split scratch.
@@ -316,11 +311,10 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
   constexpr bool is_bf16 = sizeof(T) == 2;
   const int nk = hi - lo;
   const std::vector<int> stages = stage_plan(batches[lo].s0, hp);   // the same for all batches of a run
-  const bool merged = merges(stages);
   struct Kind {
     T *xw, *xt[2], *a, *bm;
     void *t, *b[3];            // merged steps: B A, three images for polynomials and their products
-    float *dt, *db[3];         // ... and the diagonals
+    float *da, *dt, *db[3];    // ... and the diagonals
     float *partial, *scale, *scale2;
     int64_t x_elems, a_elems;
     int tiles, nb;
@@ -352,17 +346,6 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
     kd.upd = GemmDims{s.mp, s.np, s.mp, s.mp, s.mp, kd.a_elems, kd.x_elems, bt.nb};
   }
   const SplitWs split{reinterpret_cast<float*>(ws + base), SPLIT_MAX_BLOCKS};
-  for (int k = 0; merged && k < nk; ++k) {   // the extra arrays share the tail with the split scratch
-    Kind& kd = kind[k];
-    const Extra x = extra(kd.s0, kd.nb);
-    char* w = ws + base;
-    kd.t = w + x.t;
-    kd.b[0] = kd.bm, kd.b[1] = w + x.b1, kd.b[2] = w + x.b2;
-    float* dv = reinterpret_cast<float*>(w + x.diag);
-    const int64_t len = static_cast<int64_t>(kd.nb) * kd.s0.mp;
-    kd.dt = dv, kd.db[0] = dv + len, kd.db[1] = dv + 2 * len, kd.db[2] = dv + 3 * len;
-    base += x.total;
-  }
 
   // momentum (+ gather, cast, both orientations, tile sums of U^2) per part, norm per batch
   for (int k = 0; k < nk; ++k) {
@@ -415,7 +398,16 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
   auto stage_bf16 = [&](int len, bool first, int cur, const void* (&q)[MAX_KINDS]) -> int {
     GemmBatch gb{};
     const bool apart = len > 1;   // diagonals kept apart
-    auto da = [&](const Kind& kd) { return apart ? reinterpret_cast<float*>(kd.xt[cur ^ 1]) : nullptr; };
+    for (int k = 0; apart && k < nk; ++k) {
+      Kind& kd = kind[k];
+      const Spare x = spare(kd.s0, kd.nb, cur);
+      char* w = reinterpret_cast<char*>(cur == 0 ? kd.xw : kd.xt[0]);
+      kd.t = w + x.t, kd.b[0] = kd.bm, kd.b[1] = w + x.b1, kd.b[2] = w + x.b2;
+      float* dv = reinterpret_cast<float*>(w + x.diag);
+      const int64_t len_d = static_cast<int64_t>(kd.nb) * kd.s0.mp;
+      kd.da = dv, kd.dt = dv + len_d, kd.db[0] = dv + 2 * len_d, kd.db[1] = dv + 3 * len_d, kd.db[2] = dv + 4 * len_d;
+    }
+    auto da = [&](const Kind& kd) { return apart ? kd.da : nullptr; };
     gb.n = nk;
     for (int k = 0; k < nk; ++k) {
       const Kind& kd = kind[k];
@@ -450,7 +442,7 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
           gb.pr[gb.n++] = mul(kind[k], ib, kind[k].a, da(kind[k]), kind[k].t, kind[k].dt);
       if (iq >= 0)
         for (int k = 0; k < nk; ++k)
-          gb.pr[gb.n++] = mul(kind[k], ib, kind[k].b[iq], kind[k].db[iq], kind[k].b[in], last ? nullptr : kind[k].db[in]);
+          gb.pr[gb.n++] = mul(kind[k], ib, kind[k].b[iq], kind[k].db[iq], last ? kind[k].a : kind[k].b[in], last ? nullptr : kind[k].db[in]);
       if (gb.n > 0) CANZ_HIP(CANZ_KERNEL_POLY, launch_mul_bf16(gb, split, st), "product kernel (B A, Q)");
       iq = iq < 0 ? ib : in;
       if (last) break;
@@ -459,7 +451,7 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
         gb.pr[k] = mul(kind[k], ib, kind[k].t, kind[k].dt, kind[k].a, da(kind[k]));
       CANZ_HIP(CANZ_KERNEL_POLY, launch_mul_bf16(gb, split, st), "product kernel (B A B)");
     }
-    for (int k = 0; k < nk; ++k) q[k] = apart ? kind[k].b[iq] : static_cast<const void*>(kind[k].bm);
+    for (int k = 0; k < nk; ++k) q[k] = apart ? kind[k].a : kind[k].bm;
     return CANZ_OK;
   };
 

@@ -46,7 +46,8 @@ def _check(dg, ins, hp, name):
     (1535, 3072, 5),   # just below: single steps
     (3075, 1537, 5),   # odd, tall: padding in every matrix, the swapped last product
     (1536, 3071, 5),   # just too square: single steps
-    (2560, 3840, 5),   # the wider rule from 2560 rows on
+    (2560, 3840, 5),   # the spare arrays would just not fit: single steps
+    (2560, 3900, 5),   # the wider rule from 2560 rows on, the spare arrays just fit
     (1600, 3300, 3),   # stages 2 + 1
     (1600, 3300, 4),   # stages 3 + 1
     (1600, 3300, 6),   # stages 3 + 2 + 1
