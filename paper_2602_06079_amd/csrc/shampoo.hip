@@ -235,7 +235,7 @@ struct Carve {   // float offsets into the workspace of one launch batch
 };
 
 Carve carve(int64_t rows, int64_t cols, int nb, bool stat16, bool side_by_side) {
-  const size_t rp = pad128(rows), cp = pad128(cols), rp2 = pad256(rows), cp2 = pad256(cols);
+  const size_t rp2 = pad256(rows), cp2 = pad256(cols), plane = pad128(rows) * pad128(cols);
   Carve c{};
   size_t off = 0;
   auto take = [&](size_t floats) {
@@ -243,9 +243,7 @@ Carve carve(int64_t rows, int64_t cols, int nb, bool stat16, bool side_by_side) 
     off += align_up(floats * sizeof(float)) / sizeof(float);
     return at;
   };
-  c.gs = take(stat16 ? 0 : nb * rp * cp), c.gt = take(stat16 ? 0 : nb * rp * cp), c.g3t = take(stat16 ? 0 : nb * rp2 * cp2 * 3 / 2);
-  c.tmp = take(nb * rp2 * cp2 * 3 / 2);
-  c.root3[0] = take(nb * rp2 * rp2 * 3 / 2), c.root3[1] = take(nb * cp2 * cp2 * 3 / 2);
+  c.gs = take(stat16 ? 0 : nb * plane), c.gt = take(stat16 ? 0 : nb * plane), c.g3t = take(stat16 ? 0 : nb * rp2 * cp2 * 3 / 2);
   c.gp = take(stat16 ? nb * rp2 * cp2 / 2 : 0), c.gpt = take(stat16 ? nb * rp2 * cp2 / 2 : 0);
   c.root[0] = take(nb * rp2 * rp2), c.root[1] = take(nb * cp2 * cp2);
   for (int side = 0; side < 2; ++side) {
@@ -261,7 +259,15 @@ Carve carve(int64_t rows, int64_t cols, int nb, bool stat16, bool side_by_side) 
     c.partial[side] = take(static_cast<size_t>(nb) * NPART), c.partial4[side] = take(static_cast<size_t>(nb) * NPART);
     c.scale[side] = take(nb);
   }
-  c.total_bytes = off * sizeof(float);
+  // the preconditioning's operands lie where the root iteration was: at most 4.5 of its 7 or more matrices
+  const size_t end = off;
+  off = c.x[0][0];
+  c.root3[0] = take(nb * rp2 * rp2 * 3 / 2), c.root3[1] = take(nb * cp2 * cp2 * 3 / 2), c.tmp = take(nb * rp2 * cp2 * 3 / 2);
+  // Never less than the all-fp32 layout took (three planes, the roots and eight matrices of the larger side, padded to
+  // 128): what callers measured once stays what they are asked for, wherever the arrays above fit it.
+  const size_t rp = pad128(rows), cp = pad128(cols), dm = std::max(rp, cp);
+  const size_t before = nb * (3 * rp * cp + rp * rp + cp * cp + 8 * dm * dm) + 2 * nb * NPART;
+  c.total_bytes = std::max({off, end, before}) * sizeof(float);
   return c;
 }
 

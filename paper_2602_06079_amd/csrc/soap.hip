@@ -874,7 +874,7 @@ __global__ __launch_bounds__(QTH) void k_qr_block_u(const float* __restrict__ cb
 }
 
 struct Carve {   // float offsets into the workspace of one launch batch
-  size_t gm, gmt, qlt, qrt, stat, wk, vall, y2, ybuf, tau, wt, qt, tb, cb, ub, u2, total_bytes;
+  size_t gm, gmt, stat, wk, vall, y2, ybuf, tau, wt, qt, tb, cb, ub, u2, total_bytes;
   // fp32 rotations: G', M' dense; three bf16 terms per element, padded to 256 (offsets in floats as well): G (if it is not
   // bf16 itself) and M in the orientations wanted, X Q_R transposed, N', its half-rotated image, the bases
   size_t rotg, rotm, g3, g3t, m3, m3t, t3, n3, y3, ql3, ql3t, qr3, qr3t;
@@ -908,8 +908,7 @@ Carve carve(int64_t rows, int64_t cols, int nb, Sides u, bool refresh, bool bf16
   };
   const size_t plane = rp * cp;
   c.gm = take(stat16 ? 0 : nb * plane), c.gmt = take(stat16 ? 0 : nb * plane);
-  c.qlt = take(refresh && u.left ? nb * rp * rp : 0), c.qrt = take(refresh && u.right ? nb * cp * cp : 0);
-  c.stat = take(nb * dm * dm);
+  if (bf16) c.stat = take(nb * dm * dm);
   if (refresh) {
     c.wk = take(nb * dm * dm);
     c.vall = take(nb * dm * dm);
@@ -931,9 +930,11 @@ Carve carve(int64_t rows, int64_t cols, int nb, Sides u, bool refresh, bool bf16
     c.rotg = take(nb * dense_stride(rows, cols)), c.rotm = take(nb * dense_stride(rows, cols));
     c.g3 = take(!stat16 && u.right ? p3 : 0), c.g3t = take(!stat16 && !u.right ? p3 : 0);
     c.m3 = take(u.right ? p3 : 0), c.m3t = take(u.right ? 0 : p3);
-    c.t3 = c.y3 = take(both ? p3 : 0), c.n3 = take(p3);   // t3 is done with before y3 is written
-    c.ql3 = take(u.left ? l3 : 0), c.ql3t = take(u.left ? l3 : 0);
-    c.qr3 = take(u.right ? r3 : 0), c.qr3t = take(u.right ? r3 : 0);
+    c.t3 = c.y3 = take(both ? p3 : 0);   // t3 is done with before y3 is written, and G's terms before those of N'
+    c.n3 = stat16 ? take(p3) : u.right ? c.g3 : c.g3t;
+    c.ql3 = take(u.left ? l3 : 0), c.qr3 = take(u.right ? r3 : 0);
+    c.stat = c.ql3;                      // the update is out before the statistics begin; 1.5 d^2 on each side
+    c.ql3t = take(u.left ? l3 : 0), c.qr3t = take(u.right ? r3 : 0);
   }
   if (bf16) {
     const bool both = u.left && u.right;
@@ -945,7 +946,15 @@ Carve carve(int64_t rows, int64_t cols, int nb, Sides u, bool refresh, bool bf16
     c.qlp = take(u.left ? nb * rp2 * rp2 / 2 : 0), c.qltp = take(u.left ? nb * rp2 * rp2 / 2 : 0);
     c.qrp = take(u.right ? nb * cp2 * cp2 / 2 : 0), c.qrtp = take(u.right ? nb * cp2 * cp2 / 2 : 0);
   }
-  c.total_bytes = off * sizeof(float);
+  // Never less than the layout with rotations on the fp32 MFMA took (planes padded to 128, both orientations of the bases,
+  // the statistic): what callers measured once stays what they are asked for, wherever the arrays above fit it.
+  const bool both = u.left && u.right;
+  size_t before = (both ? 10 : 7) * nb * plane + (u.left ? 2 * nb * rp * rp : 0) + (u.right ? 2 * nb * cp * cp : 0) + nb * dm * dm;
+  if (refresh) before += nb * (4 * dm * dm + (4 * QBLK + QB) * dm + 3 * QBLK * QBLK) + align_up(nb * QB * sizeof(float)) / sizeof(float);
+  if (bf16 || stat16) before += (bf16 || u.left ? p2 : 0) + (bf16 || u.right ? p2 : 0);
+  if (bf16)
+    before += p2 * (4 + (u.right ? 4 : 0) + (u.left ? 4 : 0) + (both ? 2 : 0)) + (u.left ? nb * rp2 * rp2 : 0) + (u.right ? nb * cp2 * cp2 : 0);
+  c.total_bytes = std::max(off, before) * sizeof(float);
   return c;
 }
 
@@ -1154,7 +1163,7 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
   o.neg_lr_scale = -hp.lr;
 
   float *gm = ws + c.gm, *gmt = ws + c.gmt;
-  float *qlt = ws + c.qlt, *qrt = ws + c.qrt, *stat = ws + c.stat;
+  float* stat = ws + c.stat;
 
   // With a valid rotated momentum from the caller only G is rotated (M' follows its own recurrence in the rotated
   // space, which is the same linear map as long as the bases stand still); otherwise G and M.
@@ -1184,18 +1193,18 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
       hipLaunchKernelGGL(k_soap_load<false>, grid, dim3(NTH), 0, st, s, grad, g.grad_dtype, mom, hp.beta1, rp, cp, w);
   }
   // the bases, zero outside d x d: three terms for the fp32 rotations, bf16 images for the bf16 rotations, both in both
-  // orientations; fp32 and transposed for the refresh (which multiplies the new statistic with the old basis)
+  // orientations; later, fp32 and transposed, for the refresh (which multiplies the new statistic with the old basis)
   auto load_basis = [&](void* const* tab, int64_t d, int64_t dp, int64_t dp2, BasisOut w) {
     PtrTable q{};
     for (int i = 0; i < nb; ++i) q.p[i] = tab[first + i];
     const unsigned side = static_cast<unsigned>(dp2 / 64);
     hipLaunchKernelGGL(k_soap_load_basis, dim3(side, side, static_cast<unsigned>(nb)), dim3(NTH), 0, st, q, d, dp, dp2, w);
   };
-  auto basis_out = [&](float* t32, size_t sp, size_t tp, size_t s3, size_t t3) {
-    return bf16 ? BasisOut{t32, pan(sp), pan(tp), nullptr, nullptr} : BasisOut{t32, nullptr, nullptr, pan(s3), pan(t3)};
+  auto basis_out = [&](size_t sp, size_t tp, size_t s3, size_t t3) {
+    return bf16 ? BasisOut{nullptr, pan(sp), pan(tp), nullptr, nullptr} : BasisOut{nullptr, nullptr, nullptr, pan(s3), pan(t3)};
   };
-  if (u.left) load_basis(g.qleft, g.rows, rp, rp2, basis_out(hp.refresh ? qlt : nullptr, c.qlp, c.qltp, c.ql3, c.ql3t));
-  if (u.right) load_basis(g.qright, g.cols, cp, cp2, basis_out(hp.refresh ? qrt : nullptr, c.qrp, c.qrtp, c.qr3, c.qr3t));
+  if (u.left) load_basis(g.qleft, g.rows, rp, rp2, basis_out(c.qlp, c.qltp, c.ql3, c.ql3t));
+  if (u.right) load_basis(g.qright, g.cols, cp, cp2, basis_out(c.qrp, c.qrtp, c.qr3, c.qr3t));
   prof_mark(st, CANZ_KERNEL_SOAP_LOAD, false);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "load kernels: %s", hipGetErrorString(e));
 
@@ -1316,7 +1325,7 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
 
   // statistics (and, on a refresh step, the new basis) side by side
   auto one_side = [&](void* const* stat_tab, void* const* q_tab, int64_t d, int64_t dp, int64_t kp, const float* side,
-                      const float* qt_old, const __bf16* side16, int64_t d2, int64_t k2) -> int {
+                      const __bf16* side16, int64_t d2, int64_t k2) -> int {
     PtrTable tab{};
     for (int i = 0; i < nb; ++i) tab.p[i] = stat_tab[first + i];
     if (stat16) {
@@ -1337,12 +1346,17 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
       CANZ_HIP(CANZ_KERNEL_SOAP_STAT, (launch_gemm<SE_STAT, true>(q, nb, tab, s, o, st)), "statistics kernel");
     }
     if (!hp.refresh) return CANZ_OK;
+    float* qt_old = ws + c.vall;   // read by the refresh's first product, before any reflector is written there
+    prof_mark(st, CANZ_KERNEL_SOAP_LOAD, true);
+    load_basis(q_tab, d, dp, dp, BasisOut{qt_old, nullptr, nullptr, nullptr, nullptr});
+    prof_mark(st, CANZ_KERNEL_SOAP_LOAD, false);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "basis load: %s", hipGetErrorString(e));
     return refresh_side(q_tab, first, nb, d, dp, stat, qt_old, ws, c, s, o, st);
   };
   if (u.left)
-    if (int rc = one_side(g.left, g.qleft, g.rows, rp, cp, gm, qlt, pan(c.gp), rp2, cp2)) return rc;
+    if (int rc = one_side(g.left, g.qleft, g.rows, rp, cp, gm, pan(c.gp), rp2, cp2)) return rc;
   if (u.right)
-    if (int rc = one_side(g.right, g.qright, g.cols, cp, rp, gmt, qrt, pan(c.gpt), cp2, rp2)) return rc;
+    if (int rc = one_side(g.right, g.qright, g.cols, cp, rp, gmt, pan(c.gpt), cp2, rp2)) return rc;
   if (hp.refresh && g.mom_rot && bf16) {
     // the caller's rotated momentum follows the new bases, M' = Q_L^T M Q_R once more with the M of this step: bf16
     // operands as for every rotation of this mode; the last product leaves its fp32 sums in the caller's array

@@ -94,7 +94,7 @@ def test_cubic_and_expanding_coefficients_keep_single_steps(canz):
 
 
 def test_workspace_of_small_merged_batches_is_unchanged(canz):
-    """The extra arrays share the k-split scratch: a batch whose arrays fit there asks for no more than before."""
+    """The merged steps' arrays lie in X and the X^T that is not in use: no more is asked for than for single steps."""
     one = canz.Group(rows=1536, cols=3072, mom=[], n_mats=1)
     rows, cols = 1536, 3072
     need = canz.canz_muon_workspace_bytes([one], canz.Hparams())
