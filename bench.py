@@ -204,12 +204,13 @@ def main_shampoo(args, canz, W, np, torch):
 
     # FLOPs.  A product of two commuting symmetric d x d matrices has d (d + 1) / 2 distinct entries of
     # 2 d FLOPs each: that is the algorithmic count of the statistics and of the four products of a
-    # root round; the kernels compute whole 128 x 128 tiles on or above the diagonal ("issued").
+    # root round; the kernels compute whole 256 x 256 tiles on or above the diagonal ("issued"), in the
+    # root rounds as three products of fp16 terms, in the preconditioning as six of bf16 terms (three with a bf16 G).
     def pad(x):
-        return (x + 127) // 128 * 128
+        return (x + 255) // 256 * 256
 
     def sym(d, k):
-        return d * (d + 1) * k, (pad(d) // 128) * (pad(d) // 128 + 1) // 2 * 128 * 128 * 2 * pad(k)
+        return d * (d + 1) * k, (pad(d) // 256) * (pad(d) // 256 + 1) // 2 * 256 * 256 * 2 * pad(k)
 
     alg = dict(sh_stat=0.0, sh_root=0.0, sh_apply=0.0)
     iss = dict(sh_stat=0.0, sh_root=0.0, sh_apply=0.0)
@@ -224,9 +225,9 @@ def main_shampoo(args, canz, W, np, torch):
             iss["sh_stat"] += n * i
             a, i = sym(d, d)
             alg["sh_root"] += n * a * (4 * hp.root_iters - 3 + 2) * root_share      # + A'A' and A'^2 A'^2 for the starting bound
-            iss["sh_root"] += n * i * (4 * hp.root_iters - 3 + 2) * root_share
+            iss["sh_root"] += 3 * n * i * (4 * hp.root_iters - 3 + 2) * root_share
         alg["sh_apply"] += n * (2.0 * r * r * c + 2.0 * r * c * c)
-        iss["sh_apply"] += n * (2.0 * pad(r) * pad(r) * pad(c) + 2.0 * pad(r) * pad(c) * pad(c))
+        iss["sh_apply"] += n * (3 * 2.0 * pad(r) * pad(r) * pad(c) + 6 * 2.0 * pad(r) * pad(c) * pad(c))
     kernels = {}
     for k, (ms, n) in prof.items():
         if n:
@@ -235,11 +236,11 @@ def main_shampoo(args, canz, W, np, torch):
                 kernels[k]["tflops_algorithmic"] = alg[k] * args.steps / (ms * 1e-3) / 1e12
                 kernels[k]["tflops_issued"] = iss[k] * args.steps / (ms * 1e-3) / 1e12
     dom = max((k for k in kernels if k in alg), key=lambda k: kernels[k]["ms_per_step"])
-    peak = 157.3
+    peak = PEAK_BF16_TFLOPS   # of one product: an fp32-accurate one is three or six of them
     per_launch = alg[dom] / kernels[dom]["launches_per_step"]
     achieved = per_launch / (kernels[dom]["avg_ms"] * 1e-3) / 1e12
     issued = iss[dom] / kernels[dom]["launches_per_step"] / (kernels[dom]["avg_ms"] * 1e-3) / 1e12
-    roofline = dict(bound="mfma", kernel="k_sh_gemm (%s)" % dom, achieved=achieved, peak=peak, unit="TFLOP/s",
+    roofline = dict(bound="mfma", kernel="k_gemm_nt_bf16 (%s)" % dom, achieved=achieved, peak=peak, unit="TFLOP/s",
                     frac=achieved / peak, traffic=None, achieved_issued=issued, frac_issued=issued / peak,
                     flops_per_launch=per_launch, avg_launch_ms=kernels[dom]["avg_ms"])
     cpu = None
@@ -386,12 +387,15 @@ def main_soap(args, canz, W, np, torch):
         n = len(g)
         use_l, use_r = r <= limit, c <= limit
         per_rot = (2.0 * r * r * c if use_l else 0.0) + (2.0 * r * c * c if use_r else 0.0)
-        pr, pc = (pad(r, 256), pad(c, 256)) if args.bf16_rotations else (pad(r), pad(c))   # the bf16 kernels' tiles are 256 wide
+        pr, pc = pad(r, 256), pad(c, 256)   # the kernels' tiles are 256 wide
         per_rot_iss = (2.0 * pr * pr * pc if use_l else 0.0) + (2.0 * pr * pc * pc if use_r else 0.0)
+        # fp32 rotations: six products of bf16 terms, three for the first product of a bf16 G
+        less_iss = 0.0 if args.bf16_rotations else 3.0 * (2.0 * pr * pc * pc if use_r else 2.0 * pr * pr * pc)
+        terms = 1 if args.bf16_rotations else 6
         # G (and M, unless its rotated image is kept) in, the direction back; M again after a refresh if it is kept
         n_rot = (2 * args.steps + n_refresh) if keep_rot else 3 * args.steps
         alg["soap_rotate"] += n_rot * n * per_rot
-        iss["soap_rotate"] += n_rot * n * per_rot_iss
+        iss["soap_rotate"] += n * (n_rot * terms * per_rot_iss - args.steps * less_iss)
         for d, k, used in ((r, c, use_l), (c, r, use_r)):
             if used:
                 # like-shaped consecutive groups run as one launch batch
@@ -409,14 +413,14 @@ def main_soap(args, canz, W, np, torch):
                 kernels[k]["tflops_issued"] = iss[k] / (ms * 1e-3) / 1e12
     refresh_ms = sum(kernels[k]["ms_per_step"] * args.steps for k in ("soap_qr", "soap_panel") if k in kernels) / max(n_refresh, 1)
     plain_ms = sum(v["ms_per_step"] for k, v in kernels.items() if k not in ("soap_qr", "soap_panel"))
-    # the dominant kernel: the rotations, unless they run on the bf16 matrix cores and the fp32 statistics take longer
+    # the dominant kernel: the rotations, unless the statistics take longer
     dom = max(("soap_rotate", "soap_stat"), key=lambda k: kernels[k]["ms_per_step"])
-    peak = 2500.0 if (dom == "soap_stat" or args.bf16_rotations) else 157.3
+    peak = PEAK_BF16_TFLOPS   # of one product: an fp32-accurate one is three or six of them
     launches = kernels[dom]["launches_per_step"] * args.steps
     per_launch = alg[dom] / launches
     achieved = per_launch / (kernels[dom]["avg_ms"] * 1e-3) / 1e12
     issued = iss[dom] / launches / (kernels[dom]["avg_ms"] * 1e-3) / 1e12
-    roofline = dict(bound="mfma", kernel="%s (%s)" % ("k_gemm_nt_bf16" if peak > 1000 else "k_sh_gemm", dom), achieved=achieved, peak=peak, unit="TFLOP/s",
+    roofline = dict(bound="mfma", kernel="k_gemm_nt_bf16 (%s)" % dom, achieved=achieved, peak=peak, unit="TFLOP/s",
                     frac=achieved / peak, traffic=None, achieved_issued=issued, frac_issued=issued / peak,
                     flops_per_launch=per_launch, avg_launch_ms=kernels[dom]["avg_ms"])
     cpu = None

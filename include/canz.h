@@ -304,7 +304,7 @@ typedef struct {
 /*
  * canz_shampoo_workspace_bytes - device scratch canz_shampoo_step needs for these groups (the
  * largest of its launch batches: same-shape matrices of one group, as many as fit in about
- * 8 GB of fp32 working matrices, at least one).  Pointer tables may be NULL for this call.
+ * 8 GB of working matrices, at least one).  Pointer tables may be NULL for this call.
  */
 int canz_shampoo_workspace_bytes(const canz_shampoo_group* g, int32_t n_groups,
                                  const canz_shampoo_hparams* hp, size_t* bytes_out);
