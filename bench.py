@@ -205,7 +205,7 @@ def main_shampoo(args, canz, W, np, torch):
     # FLOPs.  A product of two commuting symmetric d x d matrices has d (d + 1) / 2 distinct entries of
     # 2 d FLOPs each: that is the algorithmic count of the statistics and of the four products of a
     # root round; the kernels compute whole 256 x 256 tiles on or above the diagonal ("issued"), in the
-    # root rounds as three products of fp16 terms, in the preconditioning as six of bf16 terms (three with a bf16 G).
+    # root rounds and the preconditioning as six products of bf16 terms (three with a bf16 G).
     def pad(x):
         return (x + 255) // 256 * 256
 
@@ -225,7 +225,7 @@ def main_shampoo(args, canz, W, np, torch):
             iss["sh_stat"] += n * i
             a, i = sym(d, d)
             alg["sh_root"] += n * a * (4 * hp.root_iters - 3 + 2) * root_share      # + A'A' and A'^2 A'^2 for the starting bound
-            iss["sh_root"] += 3 * n * i * (4 * hp.root_iters - 3 + 2) * root_share
+            iss["sh_root"] += 6 * n * i * (4 * hp.root_iters - 3 + 2) * root_share
         alg["sh_apply"] += n * (2.0 * r * r * c + 2.0 * r * c * c)
         iss["sh_apply"] += n * (3 * 2.0 * pad(r) * pad(r) * pad(c) + 6 * 2.0 * pad(r) * pad(c) * pad(c))
     kernels = {}

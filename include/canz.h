@@ -258,7 +258,7 @@ int canz_muon_step(const canz_group* g, int32_t n_groups, const canz_muon_hparam
  *   CANZ_OUT_PARAM: P <- P (1 - lr weight_decay) - lr O;   CANZ_OUT_DELTA: Delta W = - lr O
  * beta = 1 gives the running sums of the original algorithm (initialise L and R to eps0 I for
  * its L_0 = eps0 I, or to zero and pass eps).  The inverse fourth roots are computed to fp32
- * accuracy by root_iters rounds (at most 36 count) of a matmul-only coupled Newton iteration
+ * accuracy by root_iters rounds of a matmul-only coupled Newton iteration
  * (T = (5 I - M) / 4; X <- X T; M <- T^4 M; from M = z A, X = z^(1/4) I, z = 5 / (2 b) with
  * b = ||A|| ||A'^4||^(1/4), A' = A / ||A||, Frobenius norms: an upper bound of the largest eigenvalue
  * that is at most d^(1/8) above it, for two products before the first round),

@@ -333,10 +333,9 @@ static __device__ __forceinline__ void tile_to_terms3(const float (*tile)[65], _
   }
 }
 
-// fp32 matrices of d x d elements (row length ld) -> three bf16 terms per element, [dp2][3 dp2] panels, straight and / or
-// transposed, zero outside d x d.  One block per 64 x 64 tile.
-static __global__ __launch_bounds__(NTH) void k_terms3(PtrTable src, int64_t d, int64_t ld, int64_t dp2, __bf16* __restrict__ straight,
-                                                      __bf16* __restrict__ transposed) {
+// fp32 matrices of d x d elements (row length ld) -> three bf16 terms per element, [dp2][3 dp2] panels, zero outside d x d.
+// One block per 64 x 64 tile.
+static __global__ __launch_bounds__(NTH) void k_terms3(PtrTable src, int64_t d, int64_t ld, int64_t dp2, __bf16* __restrict__ to) {
   __shared__ float tile[64][65];
   const int b = blockIdx.z, r0 = blockIdx.y * 64, c0 = blockIdx.x * 64, t = threadIdx.x;
   const float* m = static_cast<const float*>(src.p[b]);
@@ -346,8 +345,7 @@ static __global__ __launch_bounds__(NTH) void k_terms3(PtrTable src, int64_t d, 
     tile[r][c] = r0 + r < d && c0 + c < d ? m[static_cast<int64_t>(r0 + r) * ld + c0 + c] : 0.f;
   }
   __syncthreads();
-  if (straight) tile_to_terms3(tile, straight + static_cast<int64_t>(b) * 3 * dp2 * dp2, r0, c0, dp2, false, t);
-  if (transposed) tile_to_terms3(tile, transposed + static_cast<int64_t>(b) * 3 * dp2 * dp2, r0, c0, dp2, true, t);
+  tile_to_terms3(tile, to + static_cast<int64_t>(b) * 3 * dp2 * dp2, r0, c0, dp2, false, t);
 }
 
 // S[row][col] <- S[col][row] for row > col of the caller's dense d x d matrices: the symmetric statistic is computed

@@ -54,7 +54,7 @@ constexpr int N_XCD = 8;
 static_assert(BM == PANEL_ROWS && BK == PANEL_K, "tile = panel");
 
 enum { EPI_GRAM = 0, EPI_POLY = 1, EPI_UPDATE = 2, EPI_FINAL = 3, EPI_FINAL_SYM = 4, EPI_MUL = 5, EPI_POLY_APART = 6, EPI_GRAM_APART = 7,
-       EPI_H2 = 8, EPI_H2_F32 = 9, EPI_B3 = 10, EPI_OUT_B3 = 11 };
+       EPI_B3 = 8, EPI_B3_SYM = 9, EPI_OUT_B3 = 10 };
 // EPI_FINAL_SYM: the last-product epilogue (the caller's dense buffers) over the tiles on and above the diagonal of a
 // symmetric result only; the caller mirrors them into the lower triangle afterwards.
 // EPI_GRAM_APART, EPI_POLY_APART: the diagonals of the matrices are kept apart (kernels.h: SymSpec).
@@ -62,20 +62,18 @@ enum { EPI_GRAM = 0, EPI_POLY = 1, EPI_UPDATE = 2, EPI_FINAL = 3, EPI_FINAL_SYM 
 constexpr bool epi_poly(int epi) { return epi == EPI_POLY || epi == EPI_POLY_APART; }
 constexpr bool epi_apart(int epi) { return epi == EPI_POLY_APART || epi == EPI_MUL; }   // reads diagonals
 constexpr bool epi_mspace(int epi) { return epi == EPI_GRAM || epi == EPI_GRAM_APART || epi_poly(epi) || epi == EPI_MUL; }
-// EPI_H2, EPI_H2_F32: products of symmetric commuting matrices of two fp16 terms (kernels.h: launch_split2_*).
-constexpr bool epi_f16(int epi) { return epi == EPI_H2 || epi == EPI_H2_F32; }
-// EPI_B3, EPI_OUT_B3: products of matrices of up to three bf16 terms (launch_split3*): the result as three terms, and the
-// last-product epilogue.
-constexpr bool epi_terms(int epi) { return epi_f16(epi) || epi == EPI_B3 || epi == EPI_OUT_B3; }   // operands of several terms
-constexpr bool epi_symmetric(int epi) { return epi_mspace(epi) || epi == EPI_FINAL_SYM || epi_f16(epi); }
+// EPI_B3, EPI_B3_SYM, EPI_OUT_B3: products of matrices of up to three bf16 terms (launch_split3*): the result as three
+// terms, the same for symmetric matrices that commute, and the last-product epilogue.
+constexpr bool epi_terms(int epi) { return epi == EPI_B3 || epi == EPI_B3_SYM || epi == EPI_OUT_B3; }
+constexpr bool epi_symmetric(int epi) { return epi_mspace(epi) || epi == EPI_FINAL_SYM || epi == EPI_B3_SYM; }
 constexpr bool epi_final(int epi) { return epi == EPI_FINAL || epi == EPI_FINAL_SYM || epi == EPI_OUT_B3; }
 
 struct EpiArgs {
   void* c;                 // GRAM/POLY: [nb][M][N] panels; UPDATE: straight output [nb][M][N] panels
-  void* ct;                // UPDATE: transposed output [nb][N][M] panels
+  void* ct;                // UPDATE: transposed output [nb][N][M] panels; B3_SYM: 5/4 I - 1/4 C, or nullptr
   SymSpec sym;             // GRAM/POLY/MUL: how the symmetric matrices are represented (kernels.h)
   const float* scale;      // per-matrix factor applied to the accumulator, or nullptr
-  float ca, cb, cc;        // POLY coefficients; H2: factor of this problem, what stands for 1 in the result
+  float ca, cb, cc;        // POLY coefficients
   // schedule of the persistent blocks (see launch()): full rounds of whole tiles, then the
   // `left` remaining tiles, each cut into `splits` k-slices that different blocks compute
   int full_rounds, left, splits, main_grid;
@@ -85,8 +83,6 @@ struct EpiArgs {
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 #define CANZ_LDS(p) ((__attribute__((address_space(3))) void*)(p))
 #define CANZ_GLB(p) ((const __attribute__((address_space(1))) void*)(p))
@@ -155,26 +151,21 @@ __device__ __forceinline__ float sym_diagonal(float acc, float dx, float dy, con
   return EPI == EPI_POLY_APART ? acc + __builtin_fmaf(__builtin_fmaf(e.cc, dx, e.cb), dx, e.ca) : acc + e.ca;
 }
 
-// A value as two fp16 terms in the two halves of one register, and back.  Taking the place of the fp32 value, they
-// cost the epilogue no registers.  The value is made opaque: the compiler may otherwise fuse the operation that
-// produced it into one of the two conversions (a mixed-precision fma that rounds once, to fp16) and not into the other, and the
-// terms would then differ from the value by an ulp of the first one wherever the two roundings disagree.
-__device__ __forceinline__ float two_terms(float v) {
-  asm volatile("" : "+v"(v));
-  f16x2 h;
-  h[0] = static_cast<_Float16>(v);
-  h[1] = static_cast<_Float16>(v - static_cast<float>(h[0]));
-  return __builtin_bit_cast(float, h);
+// two bf16 values, packed, times -1/4
+__device__ __forceinline__ unsigned minus_quarter(unsigned pair) {
+  bf16x2 t;
+  t[0] = static_cast<__bf16>(-0.25f * __builtin_bit_cast(float, pair << 16));
+  t[1] = static_cast<__bf16>(-0.25f * __builtin_bit_cast(float, pair & 0xffff0000u));
+  return __builtin_bit_cast(unsigned, t);
 }
-__device__ __forceinline__ float from_two_terms(float t) {
-  const f16x2 h = __builtin_bit_cast(f16x2, t);
-  return static_cast<float>(h[0]) + static_cast<float>(h[1]);
+// the three bf16 terms of one element, `step` apart
+__device__ __forceinline__ void put_three_terms(__bf16* to, int64_t step, float v) {
+#pragma unroll
+  for (int term = 0; term < 3; ++term) {
+    to[term * step] = static_cast<__bf16>(v);
+    v -= static_cast<float>(static_cast<__bf16>(v));
+  }
 }
-// the low (term 0) or high (term 1) halves of two such registers, packed
-__device__ __forceinline__ unsigned pick_term(float a, float b, unsigned sel) {
-  return __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, b), __builtin_bit_cast(unsigned, a), sel);
-}
-__device__ __forceinline__ unsigned term_selector(int term) { return term ? 0x07060302u : 0x05040100u; }
 
 // Epilogue of one 256 x 256 tile held in the accumulators of the block's four wavefronts
 // (shared by the GEMM kernel and by the kernel that finishes k-split tiles).
@@ -301,68 +292,12 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
     }
   };
 
-  if constexpr (EPI == EPI_H2_F32) {
-    // fp32 result (scaled above), row-major: both halves straight from the accumulators
-    float* C = static_cast<float*>(e.c) + static_cast<int64_t>(b) * d.M * d.N;
-#pragma unroll
-    for (int it = 0; it < 4; ++it)
-#pragma unroll
-      for (int jt = 0; jt < 4; ++jt) {
-        const int64_t row0 = tm * BM + wm * 128 + it * 32 + 4 * lh, col = tn * BN + wn * 128 + jt * 32 + lj;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          f32x4 v;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) v[q] = acc[it][jt][4 * g + q];
-          if (tm != tn || wm <= wn)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) C[(row0 + 8 * g + q) * d.N + col] = v[q];
-          if (tm != tn || wm < wn) *reinterpret_cast<f32x4*>(C + col * d.N + row0 + 8 * g) = v;
-        }
-      }
-    return;
-  }
-  if constexpr (EPI == EPI_B3) {
-    // Three terms per element, straight image only: each pass rounds what is left to bf16, writes it and takes it away.
-    int s_base[2];
-#pragma unroll
-    for (int g1 = 0; g1 < 2; ++g1)
-      s_base[g1] = (4 * lh + (lane & 1)) * 32 + ((((lj >> 3) ^ (2 * g1 + lh)) & 3) << 3) + (lj & 6);
-    const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
-    const int64_t nkb = d.N >> 5;
-#pragma unroll 1
-    for (int term = 0; term < 3; ++term) {
-#pragma unroll
-      for (int it = 0; it < 4; ++it)
-#pragma unroll
-        for (int jt = 0; jt < 4; ++jt)
-#pragma unroll
-          for (int rp = 0; rp < 8; ++rp) {
-            bf16x2 own;
-            own[0] = static_cast<__bf16>(acc[it][jt][2 * rp]);
-            own[1] = static_cast<__bf16>(acc[it][jt][2 * rp + 1]);
-            acc[it][jt][2 * rp] -= static_cast<float>(own[0]);
-            acc[it][jt][2 * rp + 1] -= static_cast<float>(own[1]);
-            const unsigned mine = __builtin_bit_cast(unsigned, own);
-            const int g = rp >> 1, p = rp & 1;
-            *reinterpret_cast<unsigned*>(stage + jt * 4096 + (it * 32 + 8 * g + 2 * p) * 32 + s_base[g & 1]) =
-                __builtin_amdgcn_perm(lane_xor1(mine), mine, pair_sel);
-          }
-      __bf16* C = static_cast<__bf16*>(e.c) + static_cast<int64_t>(b) * 3 * d.M * d.N;
-#pragma unroll
-      for (int k4 = 0; k4 < 4; ++k4) {
-        __bf16* dst = C + (tm * 3 * nkb + term * nkb + 8 * tn + 4 * wn + k4) * PANEL_ELEMS + wm * 128 * PANEL_K;
-#pragma unroll
-        for (int x = 0; x < 8; ++x)
-          *reinterpret_cast<u32x4*>(dst + (x * 64 + lane) * 8) = *reinterpret_cast<const u32x4*>(stage + k4 * 4096 + (x * 64 + lane) * 8);
-      }
-    }
-    return;
-  }
-  if constexpr (EPI == EPI_H2) {
+  if constexpr (EPI == EPI_B3 || EPI == EPI_B3_SYM) {
+    // Three terms per element, through the staging area as the bf16 images below (whose offsets these are): each pass rounds
+    // what is left to bf16, writes it (for a symmetric result also mirrored) and takes it away.  5/4 I - 1/4 C, where it is
+    // asked for, has -1/4 of the terms of C off the diagonal, exactly; its diagonal is put in place at the end.
+    constexpr bool SYM = EPI == EPI_B3_SYM;
     if (e.c == nullptr) return;   // never: a branch that parts the epilogue from the k loop's block, see POLY above
-    // Two terms per element, straight and mirrored, through the staging area as the bf16 images below (whose offsets
-    // these are); then, if asked for, the same for 5/4 I - 1/4 C.
     int s_base[2], t_base[4];
 #pragma unroll
     for (int g1 = 0; g1 < 2; ++g1)
@@ -370,54 +305,46 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
 #pragma unroll
     for (int g = 0; g < 4; ++g) t_base[g] = lj * 32 + ((g ^ ((lj >> 2) & 3)) << 3) + 4 * lh;
     const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
+    const int64_t nkb = d.N >> 5, elems = 3 * d.M * d.N;
+    __bf16* const C = static_cast<__bf16*>(e.c) + static_cast<int64_t>(b) * elems;
+    __bf16* const T = SYM && e.ct ? static_cast<__bf16*>(e.ct) + static_cast<int64_t>(b) * elems : nullptr;
+    const bool diagonal = SYM && tm == tn && wm == wn;
+    float dv[4];
+    if (T && diagonal) {
 #pragma unroll
-    for (int it = 0; it < 4; ++it)
+      for (int it = 0; it < 4; ++it)
 #pragma unroll
-      for (int jt = 0; jt < 4; ++jt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[it][jt][r] = two_terms(e.ca * acc[it][jt][r]);
-    const bool diagonal = tm == tn && wm == wn;
-    const int images = e.ct ? 4 : 2;
+        for (int r = 0; r < 16; ++r)
+          if (8 * (r >> 2) + (r & 3) + 4 * lh == lj) dv[it] = acc[it][it][r];
+    }
 #pragma unroll 1
-    for (int n = 0; n < images; ++n) {   // term 0 and 1 of C, then of 5/4 I - 1/4 C
-        if (n == 2) {
+    for (int term = 0; term < 3; ++term) {
+      auto flush = [&](int64_t row_block, int64_t kblock0, int half_rows) {
+        const int64_t at = (row_block * 3 * nkb + term * nkb + kblock0) * PANEL_ELEMS + half_rows * 128 * PANEL_K + lane * 8;
 #pragma unroll
-          for (int it = 0; it < 4; ++it)
+        for (int k4 = 0; k4 < 4; ++k4)
 #pragma unroll
-            for (int jt = 0; jt < 4; ++jt)
+          for (int x = 0; x < 8; ++x)
+            *reinterpret_cast<u32x4*>(C + at + k4 * PANEL_ELEMS + x * 512) = *reinterpret_cast<const u32x4*>(stage + k4 * 4096 + (x * 64 + lane) * 8);
+        if (T) {
 #pragma unroll
-              for (int r = 0; r < 16; ++r) {
-                const bool one = it == jt && diagonal && 8 * (r >> 2) + (r & 3) + 4 * lh == lj;
-                acc[it][jt][r] = two_terms((one ? 1.25f * e.cb : 0.f) - 0.25f * from_two_terms(acc[it][jt][r]));
-              }
+          for (int k4 = 0; k4 < 4; ++k4)
+#pragma unroll
+            for (int x = 0; x < 8; ++x) {
+              u32x4 v = *reinterpret_cast<const u32x4*>(stage + k4 * 4096 + (x * 64 + lane) * 8);
+#pragma unroll
+              for (int q = 0; q < 4; ++q) v[q] = minus_quarter(v[q]);
+              *reinterpret_cast<u32x4*>(T + at + k4 * PANEL_ELEMS + x * 512) = v;
+            }
         }
-        const int term = n & 1;
-        __bf16* C = static_cast<__bf16*>(n < 2 ? e.c : e.ct) + static_cast<int64_t>(b) * 2 * d.M * d.N;
-        const unsigned pick = term_selector(term);
-        const int64_t kb = term * (d.N >> 5);
-        auto flush = [&](int64_t row_block, int64_t kblock0, int half_rows) {
-#pragma unroll
-          for (int k4 = 0; k4 < 4; ++k4) {
-            __bf16* dst = C + (row_block * (d.N >> 4) + kblock0 + k4) * PANEL_ELEMS + half_rows * 128 * PANEL_K;
-#pragma unroll
-            for (int x = 0; x < 8; ++x)
-              *reinterpret_cast<u32x4*>(dst + (x * 64 + lane) * 8) = *reinterpret_cast<const u32x4*>(stage + k4 * 4096 + (x * 64 + lane) * 8);
-          }
-        };
-        if (tm != tn || wm <= wn) {
-#pragma unroll
-          for (int it = 0; it < 4; ++it)
-#pragma unroll
-            for (int jt = 0; jt < 4; ++jt)
-#pragma unroll
-              for (int rp = 0; rp < 8; ++rp) {
-                const unsigned mine = pick_term(acc[it][jt][2 * rp], acc[it][jt][2 * rp + 1], pick);
-                const unsigned pk = __builtin_amdgcn_perm(lane_xor1(mine), mine, pair_sel);
-                const int g = rp >> 1, p = rp & 1;
-                *reinterpret_cast<unsigned*>(stage + jt * 4096 + (it * 32 + 8 * g + 2 * p) * 32 + s_base[g & 1]) = pk;
-              }
-          flush(tm, kb + 8 * tn + 4 * wn, wm);
-        }
+      };
+      auto pair = [&](int it, int jt, int r) {
+        bf16x2 own;
+        own[0] = static_cast<__bf16>(acc[it][jt][r]);
+        own[1] = static_cast<__bf16>(acc[it][jt][r + 1]);
+        return own;
+      };
+      if (SYM) {
         if (tm != tn || wm < wn) {
 #pragma unroll
           for (int it = 0; it < 4; ++it)
@@ -425,12 +352,40 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
             for (int jt = 0; jt < 4; ++jt)
 #pragma unroll
               for (int g = 0; g < 4; ++g) {
-                const u32x2 w = {pick_term(acc[it][jt][4 * g], acc[it][jt][4 * g + 1], pick),
-                                 pick_term(acc[it][jt][4 * g + 2], acc[it][jt][4 * g + 3], pick)};
+                const u32x2 w = {__builtin_bit_cast(unsigned, pair(it, jt, 4 * g)), __builtin_bit_cast(unsigned, pair(it, jt, 4 * g + 2))};
                 *reinterpret_cast<u32x2*>(stage + it * 4096 + jt * 32 * 32 + t_base[g]) = w;
               }
-          flush(tn, kb + 8 * tm + 4 * wm, wn);
+          flush(tn, 8 * tm + 4 * wm, wn);
         }
+        // the straight image rounds anew: kept from the mirrored one, the pairs would be spilled by the hundred
+#pragma unroll
+        for (int it = 0; it < 4; ++it)
+#pragma unroll
+          for (int jt = 0; jt < 4; ++jt) asm volatile("" : "+a"(acc[it][jt]));
+      }
+#pragma unroll
+      for (int it = 0; it < 4; ++it)
+#pragma unroll
+        for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+          for (int rp = 0; rp < 8; ++rp) {
+            const bf16x2 own = pair(it, jt, 2 * rp);
+            acc[it][jt][2 * rp] -= static_cast<float>(own[0]);
+            acc[it][jt][2 * rp + 1] -= static_cast<float>(own[1]);
+            const unsigned mine = __builtin_bit_cast(unsigned, own);
+            const int g = rp >> 1, p = rp & 1;
+            *reinterpret_cast<unsigned*>(stage + jt * 4096 + (it * 32 + 8 * g + 2 * p) * 32 + s_base[g & 1]) =
+                __builtin_amdgcn_perm(lane_xor1(mine), mine, pair_sel);
+          }
+      if (!SYM || tm != tn || wm <= wn) flush(tm, 8 * tn + 4 * wn, wm);
+    }
+    if (T && diagonal && ((lj >> 2) & 1) == lh) {
+      __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0): the images are written, these elements go over theirs
+#pragma unroll
+      for (int it = 0; it < 4; ++it) {
+        const int64_t i = tm * BM + wm * 128 + 32 * it + lj;
+        put_three_terms(T + panel_chunk_off(i, i & ~7, 3 * d.N) + (i & 7), nkb * PANEL_ELEMS, 1.25f - 0.25f * dv[it]);
+      }
     }
     return;
   }
@@ -662,13 +617,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
   }
 }
 
-template <int EPI>
-__device__ __forceinline__ f32x16 mma(bf16x8 a, bf16x8 b, f32x16 c) {
-  if constexpr (epi_f16(EPI))
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-  else
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
+__device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
 
 // Element offset of the next panel of an operand of several terms: nk panels of the first segment's term, then of the
 // second's, ...  No branches: one in the k loop would cost the compiler its count of the loads in flight.  Behind the
@@ -770,7 +719,6 @@ __global__ __launch_bounds__(NTHREADS) void k_gemm_nt_bf16(Args args, EpiArgs e_
     d = pr.d;
     P = static_cast<const __bf16*>(pr.p), Q = static_cast<const __bf16*>(pr.q);
     e.c = pr.c, e.ct = pr.ct, e.sym = pr.sym, e.scale = pr.scale;
-    if (EPI == EPI_H2) e.ca = pr.factor;
     logical -= args.begin[j];
     tiles_n = static_cast<int>(d.N / BN), tiles_m = static_cast<int>(d.M / BM);
     per_batch = epi_symmetric(EPI) ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
@@ -824,9 +772,9 @@ __global__ __launch_bounds__(NTHREADS) void k_gemm_nt_bf16(Args args, EpiArgs e_
     const int i = idx >> 2, j = idx & 3;
     if (decltype(first)::value) {
       const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      acc[i][j] = mma<EPI>(fa[set][i], fb[set][j], zero);
+      acc[i][j] = mfma(fa[set][i], fb[set][j], zero);
     } else {
-      acc[i][j] = mma<EPI>(fa[set][i], fb[set][j], acc[i][j]);
+      acc[i][j] = mfma(fa[set][i], fb[set][j], acc[i][j]);
     }
   };
 
@@ -1027,7 +975,6 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
     d = pr.d;
     P = static_cast<const __bf16*>(pr.p), Q = static_cast<const __bf16*>(pr.q);
     e.c = pr.c, e.ct = pr.ct, e.sym = pr.sym, e.scale = pr.scale;
-    if (EPI == EPI_H2) e.ca = pr.factor;
     logical -= args.begin[j];
   } else {
     d = args.d, P = args.P, Q = args.Q;
@@ -1091,7 +1038,7 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          acc[i][j] = mma<EPI>(fa[kk][i], fb[kk][j], acc[i][j]);
+          acc[i][j] = mfma(fa[kk][i], fb[kk][j], acc[i][j]);
   };
   // One k-step on stage `cur`: the 4 loads of the following step may stay in flight; after the
   // barrier every wavefront has finished the step before, whose stage `nxt2` then receives step kt + 2.
@@ -1189,36 +1136,31 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
             acc[i][i][r] = sym_diagonal<EPI>(acc[i][i][r], dx, dy, e);
       }
     }
-  } else if constexpr (EPI == EPI_H2_F32) {
-    const float sc1 = e.scale[b];
-    float* C = static_cast<float*>(e.c) + static_cast<int64_t>(b) * d.M * d.N;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int64_t row0 = row_w + 32 * i + 4 * lh, col = col_w + 32 * j + lj;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          f32x4 v;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) v[q] = sc1 * acc[i][j][4 * g + q];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) C[(row0 + 8 * g + q) * d.N + col] = v[q];
-          if (tm != tn) *reinterpret_cast<f32x4*>(C + col * d.N + row0 + 8 * g) = v;
-        }
-      }
-    return;
-  } else if constexpr (EPI == EPI_B3) {
+  } else if constexpr (EPI == EPI_B3 || EPI == EPI_B3_SYM) {
+    // as in the large kernel, straight from the accumulators
+    constexpr bool SYM = EPI == EPI_B3_SYM;
     const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
-    const int64_t nkb = d.N >> 5;
-    __bf16* C = static_cast<__bf16*>(e.c) + static_cast<int64_t>(b) * 3 * d.M * d.N;
+    const int64_t nkb = d.N >> 5, elems = 3 * d.M * d.N;
+    __bf16* const C = static_cast<__bf16*>(e.c) + static_cast<int64_t>(b) * elems;
+    __bf16* const T = SYM && e.ct ? static_cast<__bf16*>(e.ct) + static_cast<int64_t>(b) * elems : nullptr;
+    const bool diagonal = SYM && tm == tn && wm == wn;
+    float dv[2];
+    if (T && diagonal) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (8 * (r >> 2) + (r & 3) + 4 * lh == lj) dv[i] = acc[i][i][r];
+    }
 #pragma unroll 1
     for (int term = 0; term < 3; ++term)
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-          __bf16* const at = C + ((row_w >> 8) * 3 * nkb + term * nkb + ((col_w + 32 * j) >> 5)) * PANEL_ELEMS + ((row_w & 255) + 32 * i) * PANEL_K;
+          const int64_t at = ((row_w >> 8) * 3 * nkb + term * nkb + ((col_w + 32 * j) >> 5)) * PANEL_ELEMS + ((row_w & 255) + 32 * i) * PANEL_K;
+          const int64_t tt = ((col_w >> 8) * 3 * nkb + term * nkb + ((row_w + 32 * i) >> 5)) * PANEL_ELEMS + ((col_w & 255) + 32 * j) * PANEL_K;
+          unsigned mine[8];
 #pragma unroll
           for (int rp = 0; rp < 8; ++rp) {
             bf16x2 own;
@@ -1226,59 +1168,31 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
             own[1] = static_cast<__bf16>(acc[i][j][2 * rp + 1]);
             acc[i][j][2 * rp] -= static_cast<float>(own[0]);
             acc[i][j][2 * rp + 1] -= static_cast<float>(own[1]);
-            const unsigned mine = __builtin_bit_cast(unsigned, own);
-            *reinterpret_cast<unsigned*>(at + s_lane[(rp >> 1) & 1] + (8 * (rp >> 1) + 2 * (rp & 1)) * PANEL_K) =
-                __builtin_amdgcn_perm(lane_xor1(mine), mine, pair_sel);
+            mine[rp] = __builtin_bit_cast(unsigned, own);
+          }
+          auto put = [&](__bf16* to) {
+#pragma unroll
+            for (int rp = 0; rp < 8; ++rp)
+              *reinterpret_cast<unsigned*>(to + at + s_lane[(rp >> 1) & 1] + (8 * (rp >> 1) + 2 * (rp & 1)) * PANEL_K) =
+                  __builtin_amdgcn_perm(lane_xor1(mine[rp]), mine[rp], pair_sel);
+            if (SYM && tm != tn)
+#pragma unroll
+              for (int g = 0; g < 4; ++g) *reinterpret_cast<u32x2*>(to + tt + t_lane[g]) = u32x2{mine[2 * g], mine[2 * g + 1]};
+          };
+          put(C);
+          if (T) {
+#pragma unroll
+            for (int rp = 0; rp < 8; ++rp) mine[rp] = minus_quarter(mine[rp]);
+            put(T);
           }
         }
-    return;
-  } else if constexpr (EPI == EPI_H2) {
-    const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
+    if (T && diagonal && ((lj >> 2) & 1) == lh) {
+      __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0): the images are written, these elements go over theirs
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = two_terms(e.ca * acc[i][j][r]);
-    const bool diagonal = tm == tn && wm == wn;
-    const int images = e.ct ? 4 : 2;
-#pragma unroll 1
-    for (int n = 0; n < images; ++n) {   // term 0 and 1 of C, then of 5/4 I - 1/4 C
-        if (n == 2) {
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) {
-                const bool one = i == j && diagonal && 8 * (r >> 2) + (r & 3) + 4 * lh == lj;
-                acc[i][j][r] = two_terms((one ? 1.25f * e.cb : 0.f) - 0.25f * from_two_terms(acc[i][j][r]));
-              }
-        }
-        const int term = n & 1;
-        __bf16* C = static_cast<__bf16*>(n < 2 ? e.c : e.ct) + static_cast<int64_t>(b) * 2 * d.M * d.N;
-        const unsigned pick = term_selector(term);
-        const int64_t kb = term * (d.N >> 5), nkc = d.N >> 4;
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            __bf16* const at = C + ((row_w >> 8) * nkc + kb + ((col_w + 32 * j) >> 5)) * PANEL_ELEMS + ((row_w & 255) + 32 * i) * PANEL_K;
-            __bf16* const tt = C + ((col_w >> 8) * nkc + kb + ((row_w + 32 * i) >> 5)) * PANEL_ELEMS + ((col_w & 255) + 32 * j) * PANEL_K;
-#pragma unroll
-            for (int rp = 0; rp < 8; ++rp) {
-              const unsigned mine = pick_term(acc[i][j][2 * rp], acc[i][j][2 * rp + 1], pick);
-              const unsigned pk = __builtin_amdgcn_perm(lane_xor1(mine), mine, pair_sel);
-              *reinterpret_cast<unsigned*>(at + s_lane[(rp >> 1) & 1] + (8 * (rp >> 1) + 2 * (rp & 1)) * PANEL_K) = pk;
-            }
-            if (tm != tn)
-#pragma unroll
-              for (int g = 0; g < 4; ++g) {
-                const u32x2 w = {pick_term(acc[i][j][4 * g], acc[i][j][4 * g + 1], pick),
-                                 pick_term(acc[i][j][4 * g + 2], acc[i][j][4 * g + 3], pick)};
-                *reinterpret_cast<u32x2*>(tt + t_lane[g]) = w;
-              }
-          }
+      for (int i = 0; i < 2; ++i) {
+        const int64_t at = row_w + 32 * i + lj;
+        put_three_terms(T + panel_chunk_off(at, at & ~7, 3 * d.N) + (at & 7), nkb * PANEL_ELEMS, 1.25f - 0.25f * dv[i]);
+      }
     }
     return;
   } else if (e.scale) {
@@ -1554,7 +1468,6 @@ hipError_t launch_problems(const GemmBatch& g, EpiArgs e, const SplitWs& w, hipS
   if (g.n != 1) return launch_multi<EPI>(g, e, st);
   const GemmProblem& pr = g.pr[0];
   e.c = pr.c, e.ct = pr.ct, e.sym = pr.sym, e.scale = pr.scale;
-  if (EPI == EPI_H2) e.ca = pr.factor;
   return launch<EPI>(pr.d, pr.p, pr.q, e, w, Shape{}, OutSpec{}, st);
 }
 }  // namespace
@@ -1574,14 +1487,8 @@ hipError_t launch_mul_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st)
   return launch_problems<EPI_MUL>(g, EpiArgs{}, w, st);
 }
 
-hipError_t launch_split2_sym(const GemmBatch& g, float one, hipStream_t st) {
-  EpiArgs e{};
-  e.cb = one;
-  return launch_problems<EPI_H2>(g, e, SplitWs{nullptr, 0}, st);
-}
-
-hipError_t launch_split2_sym_f32(const GemmBatch& g, hipStream_t st) {
-  return launch_problems<EPI_H2_F32>(g, EpiArgs{}, SplitWs{nullptr, 0}, st);
+hipError_t launch_split3_sym(const GemmBatch& g, hipStream_t st) {
+  return launch_problems<EPI_B3_SYM>(g, EpiArgs{}, SplitWs{nullptr, 0}, st);
 }
 
 hipError_t launch_update_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st) {

@@ -84,7 +84,7 @@ struct GemmDims {
   int64_t ldp, ldq;         // row lengths of P and Q (K, or more where the product runs over a part of their columns)
   int64_t sp, sq;           // batch strides
   int nb;
-  // Operands of several terms (launch_split_*): an operand of t terms is a panel matrix of t * K columns, term i in the
+  // Operands of several terms (launch_split3*): an operand of t terms is a panel matrix of t * K columns, term i in the
   // columns i K .. ; the product runs over nseg segments of K, segment s multiplying term (pseg >> 4 s) & 15 of P
   // with term (qseg >> 4 s) & 15 of Q, all into one accumulator.
   int nseg;
@@ -124,7 +124,6 @@ struct GemmProblem {
   void* ct;            // UPDATE: the transposed image
   SymSpec sym;         // GRAM, POLY, MUL
   const float* scale;  // per-matrix factor or nullptr
-  float factor;        // launch_split2_sym: factor of the result
 };
 struct GemmBatch {
   int n;
@@ -153,25 +152,17 @@ hipError_t launch_final_sym_bf16(const GemmDims& d, const void* x, const SplitWs
                                  hipStream_t st);
 
 // ---- fp32 products on the 16-bit matrix cores ---------------------------------------
-// A value of 24 bits is the sum of two fp16 values (11 bits and a sign each: 22 to 23 bits, exponents permitting) or of three
-// bf16 values (8 bits each).  The products of the terms are exact in fp32 and are added up in fp32, the small ones first,
-// K / 16 roundings per segment where the fp32 MFMA rounds K / 2 times.
-// Two fp16 terms, for matrices of known magnitude (symmetric, commuting; P and Q [nb][M][2 K], scaled so that no entry
-// reaches 65504).  Three products of terms: the fourth, of the two second ones, is 2^-22 of the result and shows only
-// where the sums are too short for fp32 rounding to count (d <= 256: it is included there).
-//   c  [nb][M][2 N] = factor * P Q          ct (or nullptr) = 5/4 one I - 1/4 c, one: what stands for 1 in c
-hipError_t launch_split2_sym(const GemmBatch& g, float one, hipStream_t st);
-//   c  [nb][M][N] fp32, row-major = scale[b] * P Q
-hipError_t launch_split2_sym_f32(const GemmBatch& g, hipStream_t st);
-inline GemmDims split2_dims(int64_t d, int nb) {
-  if (d <= 256) return GemmDims{d, d, d, 2 * d, 2 * d, 2 * d * d, 2 * d * d, nb, 4, 0x0011u, 0x0101u};
-  return GemmDims{d, d, d, 2 * d, 2 * d, 2 * d * d, 2 * d * d, nb, 3, 0x001u, 0x010u};
-}
-
-// Three bf16 terms, for matrices of any magnitude (bf16 has fp32's exponents): six products of terms, three if one
-// operand is a matrix of bf16 values, i.e. of one term.  C = P Q^T, P [nb][M][3 K], Q [nb][N][qterms K]:
+// A value of 24 bits is the sum of three bf16 values (8 bits each), which have fp32's exponents: matrices of any magnitude and
+// of elements of any ratio keep the accuracy they have in fp32.  The products of the terms are exact in fp32 and are
+// added up in fp32, the small ones first, K / 16 roundings per product where the fp32 MFMA rounds K / 2 times.  Six products
+// (those left out are at most 2^-26 of the result), three if one operand is a matrix of bf16 values, i.e. of one term.
+// An infinity in an operand gives NaN where the fp32 product would give an infinity.
+// C = P Q^T, P [nb][M][3 K], Q [nb][N][qterms K]:
 //   c [nb][M][3 N], the result as three terms
 hipError_t launch_split3(const GemmDims& d, const void* p, const void* q, void* c, hipStream_t st);
+//   the same for symmetric P and Q that commute: the tiles on and above the diagonal, mirrored.  ct of a problem, or
+//   nullptr: 5/4 I - 1/4 c as three terms
+hipError_t launch_split3_sym(const GemmBatch& g, hipStream_t st);
 //   the result as the last product of launch_final_bf16 (o: the caller's buffers)
 hipError_t launch_split3_final(const GemmDims& d, const void* p, const void* q, const Shape& s, const OutSpec& o, hipStream_t st);
 inline GemmDims split3_dims(int64_t M, int64_t N, int64_t K, int qterms, int nb, int pterms = 3) {

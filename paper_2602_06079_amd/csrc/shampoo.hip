@@ -21,23 +21,21 @@
 // last one also writes the next T).  The round count is fixed by the caller: no test of
 // convergence is read back, so the step never synchronises and can be captured in a graph.
 //
-// These products, nearly all of the step's work, run on the fp16 matrix cores: every matrix of the iteration is held as
-// two fp16 terms (22 to 23 bits) and a product is the sum of three products of terms (launch_split2_sym), 3 / 16 of
-// the fp32 MFMA's time at full rate.  The terms need matrices of known magnitude, and the iteration provides it: M has
-// eigenvalues in (0, 5/2], T in [5/8, 5/4], so no entry of M, T, T^2, T^4 exceeds 5/2 (stored times 2^14); X / z^(1/4)
-// grows by at most 5/4 per round and ends at (z lambda_min)^(-1/4) (stored times 2^4, so up to 4094: condition numbers
-// far beyond what fp32 statistics can hold; rounds beyond the 36th, which cannot change a root that exists, are left out).
-// The roots come out closer to 64 bits than with the fp32 MFMA, whose 32 x 32 x 2 steps round a sum k / 2 times: 1.4e-5
-// instead of 1.6e-4 on 3072 x 3072 statistics at eps = 1e-4 lambda_max, 1.0e-6 instead of 6.5e-6 on 1024 x 1024, and
-// nowhere further off on 40 drawn shapes (a fourth product, of the second terms, changes nothing that shows).
-// 4 x 3072 x 1024, 22 rounds: 92.6 -> 34.6 ms.
+// These products, nearly all of the step's work, run on the bf16 matrix cores: every matrix of the iteration is held as
+// three bf16 terms per element (fp32's 24 bits and its exponents) and a product is the sum of six products of terms with fp32
+// sums (launch_split3_sym), 6 / 16 of the fp32 MFMA's time at full rate.  The exponents matter: rows without signal, or
+// scales that differ from row to row, give elements many orders of magnitude below ||A|| that the root is made of, and a
+// representation with an absolute resolution loses them (two fp16 terms took half the products; half the rows empty at eps =
+// 1e-8 lambda_max gave a root error of 6e-5 where fp32 has 1e-7).  Against fp32 matrices on the fp32 MFMA, whose 32 x 32 x 2
+// steps round a sum k / 2 times, the roots are closer to 64 bits: 1.4e-5 instead of 1.6e-4 on 3072 x 3072 statistics at
+// eps = 1e-4 lambda_max.
 // Both sides run their rounds side by side (the tiles of one alone leave the last round of the chip half empty), and
 // X T shares a launch with T T.
 //
 // Statistics of bf16 gradients run on the bf16 matrix cores (statistic_bf16), those of fp32 gradients on
 // v_mfma_f32_32x32x2_f32; the two preconditioning products on the bf16 cores with three terms per fp32 element
-// (launch_split3).  Working extents are multiples of 128 for the fp32 MFMA and of 256 elsewhere (zero padding: the padded part of every iterate is a separate diagonal block that never mixes with the
-// matrix and is multiplied by zeros at the end).
+// (launch_split3).  Working extents are multiples of 128 for the fp32 MFMA and of 256 elsewhere (zero padding: the padded part
+// of every iterate is a separate diagonal block that never mixes with the matrix and is multiplied by zeros at the end).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -61,10 +59,6 @@ constexpr int NPART = 64;        // partial sums per matrix of the Frobenius nor
 constexpr int64_t MAX_EXTENT = 32768;
 constexpr size_t BATCH_BYTES = size_t(8) << 30;
 
-constexpr float ONE = 16384.f;    // what stands for 1 in the fp16 terms of M, T, T^2, T^4 ...
-constexpr float X_ONE = 16.f;     // ... and of X / z^(1/4)
-constexpr int MAX_ROUNDS = 36;    // 16 (5/4)^36 < 65504; a positive definite A of condition number 1e12 has converged by then
-
 // sum over the block's threads -> *to
 __device__ __forceinline__ void block_sum_to(float ss, float* to) {
   __shared__ float wsum[NTH / 64];
@@ -84,49 +78,64 @@ __global__ __launch_bounds__(NTH) void k_sh_sumsq(PtrTable stat, int64_t d, floa
   block_sum_to(ss, partial + b * NPART + p);
 }
 
-// Eight consecutive elements of a matrix of two fp16 terms: chunk `i` of the first term's panels, in memory order.
-// [dp][2 dp] columns: panel (row block, k block) of term t is number row_block * 2 nkb + t nkb + k_block.
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+// Eight consecutive elements of a matrix of three bf16 terms: chunk `i` of the first term's panels, in memory order.
+// [dp][3 dp] columns: panel (row block, k block) of term t is number row_block * 3 nkb + t nkb + k_block.
 struct Chunk {
-  int64_t at, lo, row, col;
+  int64_t at, step, row, col;   // the first term's place, from one term to the next; the elements
   __device__ __forceinline__ Chunk(int64_t i, int64_t dp) {
     const int64_t nkb = dp / PANEL_K, panel = i / (PANEL_ELEMS / 8), w = i - panel * (PANEL_ELEMS / 8);
     const int64_t rb = panel / nkb, kb = panel - rb * nkb;
-    at = ((rb * 2 * nkb) + kb) * PANEL_ELEMS + w * 8;
-    lo = at + nkb * PANEL_ELEMS;
+    at = ((rb * 3 * nkb) + kb) * PANEL_ELEMS + w * 8;
+    step = nkb * PANEL_ELEMS;
     row = rb * PANEL_ROWS + w / 4;
     col = kb * PANEL_K + (((w & 3) ^ ((row >> 2) & 3)) << 3);
   }
 };
-__device__ __forceinline__ void put_terms(_Float16* m, const Chunk& c, const float (&v)[8]) {
-  half8 h, l;
+__device__ __forceinline__ void put_terms(__bf16* m, const Chunk& c, float (&v)[8]) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    float x = v[e];
-    asm volatile("" : "+v"(x));   // one fp32 value for both terms: no operation is fused into one of the conversions
-    h[e] = static_cast<_Float16>(x), l[e] = static_cast<_Float16>(x - static_cast<float>(h[e]));
+  for (int term = 0; term < 3; ++term) {
+    bf16x8 t;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) t[e] = static_cast<__bf16>(v[e]), v[e] -= static_cast<float>(t[e]);
+    *reinterpret_cast<bf16x8*>(m + c.at + term * c.step) = t;
   }
-  *reinterpret_cast<half8*>(m + c.at) = h;
-  *reinterpret_cast<half8*>(m + c.lo) = l;
 }
-__device__ __forceinline__ void get_terms(const _Float16* m, const Chunk& c, float (&v)[8]) {
-  const half8 h = *reinterpret_cast<const half8*>(m + c.at), l = *reinterpret_cast<const half8*>(m + c.lo);
+__device__ __forceinline__ void get_terms(const __bf16* m, const Chunk& c, float (&v)[8]) {
+  bf16x8 t[3];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = static_cast<float>(h[e]) + static_cast<float>(l[e]);
+  for (int term = 0; term < 3; ++term) t[term] = *reinterpret_cast<const bf16x8*>(m + c.at + term * c.step);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = (static_cast<float>(t[0][e]) + static_cast<float>(t[1][e])) + static_cast<float>(t[2][e]);
 }
 
-// partial sums as above of a matrix of two terms
-__global__ __launch_bounds__(NTH) void k_sh_sumsq_terms(const _Float16* __restrict__ a, int64_t dp, float* __restrict__ partial) {
+// partial sums as above of a matrix of three terms
+__global__ __launch_bounds__(NTH) void k_sh_sumsq_terms(const __bf16* __restrict__ a, int64_t dp, float* __restrict__ partial) {
   const int b = blockIdx.y, p = blockIdx.x;
-  const _Float16* ab = a + static_cast<int64_t>(b) * 2 * dp * dp;
+  const __bf16* ab = a + static_cast<int64_t>(b) * 3 * dp * dp;
   float ss = 0.f;
   for (int64_t i = static_cast<int64_t>(p) * NTH + threadIdx.x; i < dp * dp / 8; i += static_cast<int64_t>(NPART) * NTH) {
     float v[8];
     get_terms(ab, Chunk(i, dp), v);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) ss += (v[e] * (1.f / ONE)) * (v[e] * (1.f / ONE));
+    for (int e = 0; e < 8; ++e) ss += v[e] * v[e];
   }
   block_sum_to(ss, partial + b * NPART + p);
+}
+
+// the caller's dense d x d matrices <- matrices of three terms [dp][3 dp] (the sum of the terms is the fp32 value, exactly)
+__global__ __launch_bounds__(NTH) void k_sh_store_terms(const __bf16* __restrict__ a, PtrTable to, int64_t d, int64_t dp) {
+  const int b = blockIdx.y;
+  const __bf16* ab = a + static_cast<int64_t>(b) * 3 * dp * dp;
+  float* m = static_cast<float*>(to.p[b]);
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * NTH + threadIdx.x; i < dp * dp / 8; i += static_cast<int64_t>(gridDim.x) * NTH) {
+    const Chunk c(i, dp);
+    if (c.row >= d || c.col >= d) continue;
+    float v[8];
+    get_terms(ab, c, v);
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (c.col + e < d) m[c.row * d + c.col + e] = v[e];
+  }
 }
 
 // Start of the root iteration.  The iteration needs M = z A with eigenvalues in (0, 5); the closer the largest
@@ -134,7 +143,7 @@ __global__ __launch_bounds__(NTH) void k_sh_sumsq_terms(const _Float16* __restri
 // but loosely (by sqrt(d) for a flat spectrum: three and a half rounds at d = 3072); ||A'^4||_F^(1/4) with
 // A' = A / ||A||_F is a bound too, at most d^(1/8) above it, for two products.
 //   k_sh_prescale:  A' = A / ||A||_F
-//   k_sh_init:      z' = 5 / (2 ||A'^4||_F^(1/4));  M = z' A';  T = 5/4 I - 1/4 M;  X = I, (z' / ||A||_F)^(1/4) kept apart
+//   k_sh_init:      z' = 5 / (2 ||A'^4||_F^(1/4));  M = z' A';  T = 5/4 I - 1/4 M;  X = (z' / ||A||_F)^(1/4) I
 __device__ __forceinline__ double sum_partials(const float* partial, int b) {
   double sum = 0.0;
   for (int i = 0; i < NPART; ++i) sum += static_cast<double>(partial[b * NPART + i]);
@@ -142,44 +151,43 @@ __device__ __forceinline__ double sum_partials(const float* partial, int b) {
 }
 
 __global__ __launch_bounds__(NTH) void k_sh_prescale(PtrTable stat, int64_t d, int64_t dp, float eps,
-                                                      const float* __restrict__ partial, _Float16* __restrict__ m) {
+                                                      const float* __restrict__ partial, __bf16* __restrict__ m) {
   const int b = blockIdx.y;
   const float* s = static_cast<const float*>(stat.p[b]);
   const float nrm = static_cast<float>(sqrt(sum_partials(partial, b)));
   const float inv = nrm > 0.f ? 1.f / nrm : 0.f;
-  _Float16* mb = m + static_cast<int64_t>(b) * 2 * dp * dp;
+  __bf16* mb = m + static_cast<int64_t>(b) * 3 * dp * dp;
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * NTH + threadIdx.x; i < dp * dp / 8; i += static_cast<int64_t>(gridDim.x) * NTH) {
     const Chunk c(i, dp);
     float v[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       v[e] = 0.f;
-      if (c.row < d && c.col + e < d) v[e] = ONE * (inv * (s[c.row * d + c.col + e] + (c.row == c.col + e ? eps : 0.f)));
+      if (c.row < d && c.col + e < d) v[e] = inv * (s[c.row * d + c.col + e] + (c.row == c.col + e ? eps : 0.f));
     }
     put_terms(mb, c, v);
   }
 }
 
 __global__ __launch_bounds__(NTH) void k_sh_init(const float* __restrict__ partial, const float* __restrict__ partial4,
-                                                  int64_t d, int64_t dp, _Float16* __restrict__ x, _Float16* __restrict__ m,
-                                                  _Float16* __restrict__ tt, float* __restrict__ scale) {
+                                                  int64_t d, int64_t dp, __bf16* __restrict__ x, __bf16* __restrict__ m,
+                                                  __bf16* __restrict__ tt) {
   const int b = blockIdx.y;
   const float nrm = static_cast<float>(sqrt(sum_partials(partial, b)));
   const float bound = static_cast<float>(pow(sum_partials(partial4, b), 0.125));   // ||A'^4||_F^(1/4) >= lambda_max(A')
   const float z = bound > 0.f ? 2.5f / bound : 1.f;
   const float x0 = nrm > 0.f ? sqrtf(sqrtf(z / nrm)) : 1.f;
-  if (blockIdx.x == 0 && threadIdx.x == 0) scale[b] = x0 / (ONE * X_ONE);   // of the last product X T
-  const int64_t off = static_cast<int64_t>(b) * 2 * dp * dp;
+  const int64_t off = static_cast<int64_t>(b) * 3 * dp * dp;
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * NTH + threadIdx.x; i < dp * dp / 8; i += static_cast<int64_t>(gridDim.x) * NTH) {
     const Chunk c(i, dp);
     float mv[8], tv[8], xv[8];
     get_terms(m + off, c, mv);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const bool diag = c.row == c.col + e;
-      mv[e] = diag && c.row >= d ? ONE : z * mv[e];   // the padding stands at the fixed point M = T = X = I
-      tv[e] = (diag ? 1.25f * ONE : 0.f) - 0.25f * mv[e];
-      xv[e] = diag ? X_ONE : 0.f;
+      const bool diag = c.row == c.col + e, pad = diag && c.row >= d;
+      mv[e] = pad ? 1.f : z * mv[e];   // the padding stands at the fixed point M = T = X = I
+      tv[e] = (diag ? 1.25f : 0.f) - 0.25f * mv[e];
+      xv[e] = pad ? 1.f : diag ? x0 : 0.f;
     }
     put_terms(m + off, c, mv);
     put_terms(tt + off, c, tv);
@@ -228,14 +236,17 @@ __global__ __launch_bounds__(NTH) void k_sh_load_grad(Shape s, PtrTable grad, in
 
 bool bf16_statistics(const canz_shampoo_group& g) { return g.grad_dtype == CANZ_DT_BF16; }
 
-struct Carve {   // float offsets into the workspace of one launch batch
-  size_t gs, gt, g3t, gp, gpt, tmp, root[2], root3[2], total_bytes;   // g3t, tmp, root3: three bf16 terms per element
-  // the root iteration of each side: matrices of two fp16 terms (4 bytes per element); one set if the sides take turns
-  size_t x[2][2], m[2][2], t[2], t2[2], t4[2], partial[2], partial4[2], scale[2];
+// Float offsets into the workspace of one launch batch.  root3, slot, tmp, g3t: three bf16 terms per element, 1.5 floats.
+struct Carve {
+  size_t gs, gt, g3t, gp, gpt;         // G as its readers want it; gs, gt, gp are done with when the iteration begins
+  size_t slot[2][5];                   // root iteration of each side; one set if the sides take turns
+  size_t partial[2], partial4[2];
+  size_t left3;                        // the sides take turns: the left root, kept over the right side's iteration
+  size_t total_bytes;
 };
 
 Carve carve(int64_t rows, int64_t cols, int nb, bool stat16, bool side_by_side) {
-  const size_t rp2 = pad256(rows), cp2 = pad256(cols), plane = pad128(rows) * pad128(cols);
+  const size_t rp2 = pad256(rows), cp2 = pad256(cols), plane = pad128(rows) * pad128(cols), p2 = nb * rp2 * cp2;
   Carve c{};
   size_t off = 0;
   auto take = [&](size_t floats) {
@@ -243,26 +254,22 @@ Carve carve(int64_t rows, int64_t cols, int nb, bool stat16, bool side_by_side) 
     off += align_up(floats * sizeof(float)) / sizeof(float);
     return at;
   };
-  c.gs = take(stat16 ? 0 : nb * plane), c.gt = take(stat16 ? 0 : nb * plane), c.g3t = take(stat16 ? 0 : nb * rp2 * cp2 * 3 / 2);
-  c.gp = take(stat16 ? nb * rp2 * cp2 / 2 : 0), c.gpt = take(stat16 ? nb * rp2 * cp2 / 2 : 0);
-  c.root[0] = take(nb * rp2 * rp2), c.root[1] = take(nb * cp2 * cp2);
+  c.g3t = take(stat16 ? 0 : p2 * 3 / 2), c.gpt = take(stat16 ? p2 / 2 : 0);
+  c.left3 = take(side_by_side ? 0 : nb * rp2 * rp2 * 3 / 2);
+  const size_t begin = off;
   for (int side = 0; side < 2; ++side) {
     if (side == 1 && !side_by_side) {
-      for (int k = 0; k < 2; ++k) c.x[1][k] = c.x[0][k], c.m[1][k] = c.m[0][k];
-      c.t[1] = c.t[0], c.t2[1] = c.t2[0], c.t4[1] = c.t4[0];
-      c.partial[1] = c.partial[0], c.partial4[1] = c.partial4[0], c.scale[1] = c.scale[0];
+      for (int k = 0; k < 5; ++k) c.slot[1][k] = c.slot[0][k];
+      c.partial[1] = c.partial[0], c.partial4[1] = c.partial4[0];
       break;
     }
     const size_t d = side_by_side ? (side == 0 ? rp2 : cp2) : std::max(rp2, cp2), dd = nb * d * d;
-    for (int k = 0; k < 2; ++k) c.x[side][k] = take(dd), c.m[side][k] = take(dd);
-    c.t[side] = take(dd), c.t2[side] = take(dd), c.t4[side] = take(dd);
+    for (int k = 0; k < 5; ++k) c.slot[side][k] = take(dd * 3 / 2);
     c.partial[side] = take(static_cast<size_t>(nb) * NPART), c.partial4[side] = take(static_cast<size_t>(nb) * NPART);
-    c.scale[side] = take(nb);
   }
-  // the preconditioning's operands lie where the root iteration was: at most 4.5 of its 7 or more matrices
   const size_t end = off;
-  off = c.x[0][0];
-  c.root3[0] = take(nb * rp2 * rp2 * 3 / 2), c.root3[1] = take(nb * cp2 * cp2 * 3 / 2), c.tmp = take(nb * rp2 * cp2 * 3 / 2);
+  off = begin;   // the statistics' operands, where the iteration will be
+  c.gs = take(stat16 ? 0 : nb * plane), c.gt = take(stat16 ? 0 : nb * plane), c.gp = take(stat16 ? p2 / 2 : 0);
   // Never less than the all-fp32 layout took (three planes, the roots and eight matrices of the larger side, padded to
   // 128): what callers measured once stays what they are asked for, wherever the arrays above fit it.
   const size_t rp = pad128(rows), cp = pad128(cols), dm = std::max(rp, cp);
@@ -344,11 +351,12 @@ int run_batch(const canz_shampoo_group& g, int first, int nb, const canz_shampoo
   float *gs = stat16 ? nullptr : ws + c.gs, *gt = stat16 ? nullptr : ws + c.gt;
   const int64_t rp2 = pad256(g.rows), cp2 = pad256(g.cols);
   __bf16 *gp = stat16 ? reinterpret_cast<__bf16*>(ws + c.gp) : nullptr, *gpt = stat16 ? reinterpret_cast<__bf16*>(ws + c.gpt) : nullptr;
+  auto terms = [&](size_t at) { return reinterpret_cast<__bf16*>(ws + at); };
   {
     const dim3 grid(static_cast<unsigned>(cp2 / 64), static_cast<unsigned>(rp2 / 64), static_cast<unsigned>(nb));
     prof_mark(st, CANZ_KERNEL_SH_LOAD, true);
     hipLaunchKernelGGL(k_sh_load_grad, grid, dim3(NTH), 0, st, s, grad, g.grad_dtype, rp, cp, gs, gt, rp2, cp2, gp, gpt,
-                       stat16 ? nullptr : reinterpret_cast<__bf16*>(ws + c.g3t));
+                       stat16 ? nullptr : terms(c.g3t));
     prof_mark(st, CANZ_KERNEL_SH_LOAD, false);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "load kernel: %s", hipGetErrorString(e));
   }
@@ -357,8 +365,9 @@ int run_batch(const canz_shampoo_group& g, int first, int nb, const canz_shampoo
   struct Side {
     PtrTable stat, kept;
     int64_t d, dp2;
-    float *root, *partial, *partial4, *scale;
-    _Float16 *x[2], *m[2], *t, *t2, *t4;
+    float *partial, *partial4;
+    __bf16* slot[5];
+    __bf16* root3;       // the root as three terms: where the iteration left it, or loaded from the caller
     bool keep;
   } side[2];
   for (int k = 0; k < 2; ++k) {
@@ -369,10 +378,9 @@ int run_batch(const canz_shampoo_group& g, int first, int nb, const canz_shampoo
     z.stat = PtrTable{}, z.kept = PtrTable{};
     for (int i = 0; i < nb; ++i) z.stat.p[i] = stat_tab[first + i], z.kept.p[i] = root_tab ? root_tab[first + i] : nullptr;
     z.d = k == 0 ? g.rows : g.cols, z.dp2 = k == 0 ? rp2 : cp2;
-    z.root = ws + c.root[k], z.partial = ws + c.partial[k], z.partial4 = ws + c.partial4[k], z.scale = ws + c.scale[k];
-    auto terms = [&](size_t at) { return reinterpret_cast<_Float16*>(ws + at); };
-    for (int q = 0; q < 2; ++q) z.x[q] = terms(c.x[k][q]), z.m[q] = terms(c.m[k][q]);
-    z.t = terms(c.t[k]), z.t2 = terms(c.t2[k]), z.t4 = terms(c.t4[k]);
+    z.partial = ws + c.partial[k], z.partial4 = ws + c.partial4[k];
+    for (int q = 0; q < 5; ++q) z.slot[q] = terms(c.slot[k][q]);
+    z.root3 = k == 0 && !together ? terms(c.left3) : nullptr;
     if (stat16) {
       if (int rc = statistic_bf16(CANZ_KERNEL_SH_STAT, z.stat, z.d, z.dp2, k == 0 ? cp2 : rp2, 1024, nb, hp.beta, 1.f, k == 0 ? gp : gpt, st))
         return rc;
@@ -384,15 +392,8 @@ int run_batch(const canz_shampoo_group& g, int first, int nb, const canz_shampoo
       CANZ_HIP(CANZ_KERNEL_SH_STAT, (launch_gemm<SE_STAT, true>(q, nb, z.stat, s, o, st)), "statistics kernel");
     }
   }
-  auto square = [](int64_t d) {   // a side's d x d matrices, for the padded load and the dense store of a kept root
-    Shape sq{};
-    sq.rows = d, sq.cols = d, sq.tp = 1, sq.wfrag = d;
-    return sq;
-  };
-  auto tiles = [&](const Side& z) {
-    return dim3(static_cast<unsigned>(z.dp2 / 64), static_cast<unsigned>(z.dp2 / 64), static_cast<unsigned>(nb));
-  };
-  // the roots of the given sides, their rounds side by side
+  // The roots of the given sides, their rounds side by side.  Five matrices per side take turns: X, M and T, and two that
+  // are free when a round begins.  X' and T^2 go there; T^4 takes X's place, M' that of T^2, the next T that of T.
   auto roots = [&](Side* const* z, int n) -> int {
     auto each = [&](int kind, const char* what, auto&& run) -> int {
       prof_mark(st, kind, true);
@@ -403,56 +404,70 @@ int run_batch(const canz_shampoo_group& g, int first, int nb, const canz_shampoo
     };
     auto blocks = [](const Side& z_) { return static_cast<unsigned>(std::min<int64_t>(4096, z_.dp2 * z_.dp2 / 8 / NTH)); };
     GemmBatch gb{};
-    auto add = [&](const Side& z_, const _Float16* P, const _Float16* Q, void* C, void* next_t) {
+    auto add = [&](const Side& z_, const __bf16* P, const __bf16* Q, __bf16* C, __bf16* next_t) {
       GemmProblem& pr = gb.pr[gb.n++] = GemmProblem{};
-      pr.d = split2_dims(z_.dp2, nb), pr.p = P, pr.q = Q, pr.c = C, pr.ct = next_t, pr.factor = 1.f / ONE;
+      pr.d = split3_dims(z_.dp2, z_.dp2, z_.dp2, 3, nb), pr.p = P, pr.q = Q, pr.c = C, pr.ct = next_t;
     };
     auto launch = [&](const char* what) -> int {
-      CANZ_HIP(CANZ_KERNEL_SH_ROOT, launch_split2_sym(gb, ONE, st), what);
+      CANZ_HIP(CANZ_KERNEL_SH_ROOT, launch_split3_sym(gb, st), what);
       gb.n = 0;
       return CANZ_OK;
     };
+    int x = 0, m = 1, f = 3, e = 4;
+    const int t = 2;
     if (int rc = each(CANZ_KERNEL_SH_INIT, "root start", [&](Side& q) {
           hipLaunchKernelGGL(k_sh_sumsq, dim3(NPART, nb), dim3(NTH), 0, st, q.stat, q.d, hp.eps, q.partial);
-          hipLaunchKernelGGL(k_sh_prescale, dim3(blocks(q), nb), dim3(NTH), 0, st, q.stat, q.d, q.dp2, hp.eps, q.partial, q.m[0]);
+          hipLaunchKernelGGL(k_sh_prescale, dim3(blocks(q), nb), dim3(NTH), 0, st, q.stat, q.d, q.dp2, hp.eps, q.partial, q.slot[m]);
         }))
       return rc;
-    for (int k = 0; k < n; ++k) add(*z[k], z[k]->m[0], z[k]->m[0], z[k]->t2, nullptr);
+    for (int k = 0; k < n; ++k) add(*z[k], z[k]->slot[m], z[k]->slot[m], z[k]->slot[f], nullptr);
     if (int rc = launch("root start (A A)")) return rc;
-    for (int k = 0; k < n; ++k) add(*z[k], z[k]->t2, z[k]->t2, z[k]->t4, nullptr);
+    for (int k = 0; k < n; ++k) add(*z[k], z[k]->slot[f], z[k]->slot[f], z[k]->slot[e], nullptr);
     if (int rc = launch("root start (A2 A2)")) return rc;
     if (int rc = each(CANZ_KERNEL_SH_INIT, "root start", [&](Side& q) {
-          hipLaunchKernelGGL(k_sh_sumsq_terms, dim3(NPART, nb), dim3(NTH), 0, st, q.t4, q.dp2, q.partial4);
-          hipLaunchKernelGGL(k_sh_init, dim3(blocks(q), nb), dim3(NTH), 0, st, q.partial, q.partial4, q.d, q.dp2, q.x[0], q.m[0], q.t, q.scale);
+          hipLaunchKernelGGL(k_sh_sumsq_terms, dim3(NPART, nb), dim3(NTH), 0, st, q.slot[e], q.dp2, q.partial4);
+          hipLaunchKernelGGL(k_sh_init, dim3(blocks(q), nb), dim3(NTH), 0, st, q.partial, q.partial4, q.d, q.dp2, q.slot[x], q.slot[m],
+                             q.slot[t]);
         }))
       return rc;
-    int cur = 0;
-    const int rounds = std::min<int>(hp.root_iters, MAX_ROUNDS);
-    for (int it = 0; it + 1 < rounds; ++it) {
-      for (int k = 0; k < n; ++k) add(*z[k], z[k]->x[cur], z[k]->t, z[k]->x[cur ^ 1], nullptr), add(*z[k], z[k]->t, z[k]->t, z[k]->t2, nullptr);
+    for (int it = 0; it + 1 < hp.root_iters; ++it) {
+      for (int k = 0; k < n; ++k) {
+        __bf16* const* w = z[k]->slot;
+        add(*z[k], w[x], w[t], w[f], nullptr), add(*z[k], w[t], w[t], w[e], nullptr);
+      }
       if (int rc = launch("root kernel (X T, T T)")) return rc;
-      for (int k = 0; k < n; ++k) add(*z[k], z[k]->t2, z[k]->t2, z[k]->t4, nullptr);
+      for (int k = 0; k < n; ++k) add(*z[k], z[k]->slot[e], z[k]->slot[e], z[k]->slot[x], nullptr);
       if (int rc = launch("root kernel (T2 T2)")) return rc;
-      for (int k = 0; k < n; ++k) add(*z[k], z[k]->t4, z[k]->m[cur], z[k]->m[cur ^ 1], z[k]->t);
+      for (int k = 0; k < n; ++k) add(*z[k], z[k]->slot[x], z[k]->slot[m], z[k]->slot[e], z[k]->slot[t]);
       if (int rc = launch("root kernel (T4 M)")) return rc;
-      cur ^= 1;
+      const int was_x = x, was_m = m;
+      x = f, m = e, f = was_x, e = was_m;
     }
     for (int k = 0; k < n; ++k) {
-      add(*z[k], z[k]->x[cur], z[k]->t, z[k]->root, nullptr);
-      gb.pr[gb.n - 1].scale = z[k]->scale;
+      if (z[k]->root3 == nullptr) z[k]->root3 = z[k]->slot[f];
+      add(*z[k], z[k]->slot[x], z[k]->slot[t], z[k]->root3, nullptr);
     }
-    CANZ_HIP(CANZ_KERNEL_SH_ROOT, launch_split2_sym_f32(gb, st), "root kernel (last X T)");
+    if (int rc = launch("root kernel (last X T)")) return rc;
     for (int k = 0; k < n; ++k) {
       if (!z[k]->keep) continue;
+      const Side& q = *z[k];
       prof_mark(st, CANZ_KERNEL_SH_LOAD, true);
-      hipLaunchKernelGGL(k_unpad, tiles(*z[k]), dim3(NTH), 0, st, square(z[k]->d), z[k]->kept, z[k]->root, z[k]->dp2 * z[k]->dp2, z[k]->dp2);
+      hipLaunchKernelGGL(k_sh_store_terms, dim3(blocks(q), nb), dim3(NTH), 0, st, q.root3, q.kept, q.d, q.dp2);
       prof_mark(st, CANZ_KERNEL_SH_LOAD, false);
-      if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "root store: %s", hipGetErrorString(e));
+      if (hipError_t err = hipGetLastError(); err != hipSuccess) return fail(CANZ_EHIP, "root store: %s", hipGetErrorString(err));
     }
     return CANZ_OK;
   };
-  if (hp.keep_roots) {
-    // the caller's roots, below
+  if (hp.keep_roots) {   // the caller's roots as three terms
+    for (int k = 0; k < 2; ++k) {
+      Side& z = side[k];
+      if (z.root3 == nullptr) z.root3 = z.slot[0];
+      prof_mark(st, CANZ_KERNEL_SH_LOAD, true);
+      const unsigned t64 = static_cast<unsigned>(z.dp2 / 64);
+      hipLaunchKernelGGL(k_terms3, dim3(t64, t64, static_cast<unsigned>(nb)), dim3(NTH), 0, st, z.kept, z.d, z.d, z.dp2, z.root3);
+      prof_mark(st, CANZ_KERNEL_SH_LOAD, false);
+      if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "root load: %s", hipGetErrorString(e));
+    }
   } else if (together) {
     Side* both[2] = {&side[0], &side[1]};
     if (int rc = roots(both, 2)) return rc;
@@ -464,25 +479,14 @@ int run_batch(const canz_shampoo_group& g, int first, int nb, const canz_shampoo
   }
   // O = (L^(-1/4) G) R^(-1/4) on the bf16 cores, the roots and L^(-1/4) G as three terms per element (six products of
   // terms, three where G is bf16 itself): a step of 14 x 3072 x 1024 on kept roots 4.34 -> 2.26 ms against the fp32 MFMA.
-  __bf16* root3[2];
-  for (int k = 0; k < 2; ++k) {
-    const Side& z = side[k];
-    root3[k] = reinterpret_cast<__bf16*>(ws + c.root3[k]);
-    PtrTable from = z.kept;
-    if (!hp.keep_roots)
-      for (int i = 0; i < nb; ++i) from.p[i] = z.root + static_cast<int64_t>(i) * z.dp2 * z.dp2;
-    prof_mark(st, CANZ_KERNEL_SH_LOAD, true);
-    hipLaunchKernelGGL(k_terms3, tiles(z), dim3(NTH), 0, st, from, z.d, hp.keep_roots ? z.d : z.dp2, z.dp2, root3[k],
-                       static_cast<__bf16*>(nullptr));
-    prof_mark(st, CANZ_KERNEL_SH_LOAD, false);
-    if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "root load: %s", hipGetErrorString(e));
-  }
+  // L^(-1/4) G takes a place of the larger side that its root does not lie in.
+  const Side& larger = side[rp2 >= cp2 ? 0 : 1];
+  __bf16* const tmp = larger.slot[larger.root3 == larger.slot[2] || (!together && side[1].root3 == side[1].slot[2]) ? 1 : 2];
   // P = L root, Q = G^T gives rows x cols; then P = that, Q = R root
-  __bf16* tmp = reinterpret_cast<__bf16*>(ws + c.tmp);
-  const __bf16* gt_terms = stat16 ? gpt : reinterpret_cast<const __bf16*>(ws + c.g3t);
-  CANZ_HIP(CANZ_KERNEL_SH_APPLY, launch_split3(split3_dims(rp2, cp2, rp2, stat16 ? 1 : 3, nb), root3[0], gt_terms, tmp, st),
+  const __bf16* gt_terms = stat16 ? gpt : terms(c.g3t);
+  CANZ_HIP(CANZ_KERNEL_SH_APPLY, launch_split3(split3_dims(rp2, cp2, rp2, stat16 ? 1 : 3, nb), side[0].root3, gt_terms, tmp, st),
            "preconditioning kernel (left)");
-  CANZ_HIP(CANZ_KERNEL_SH_APPLY, launch_split3_final(split3_dims(rp2, cp2, cp2, 3, nb), tmp, root3[1], s, o, st),
+  CANZ_HIP(CANZ_KERNEL_SH_APPLY, launch_split3_final(split3_dims(rp2, cp2, cp2, 3, nb), tmp, side[1].root3, s, o, st),
            "preconditioning kernel (right)");
   return CANZ_OK;
 }

@@ -1,5 +1,5 @@
-"""The Shampoo root iteration on matrices of two fp16 terms: sizes around its 256-wide tiles, shares of the work between
-the large and the small kernel, few and many rounds, the padding, and sides that take turns."""
+"""The Shampoo root iteration on matrices of three bf16 terms: sizes around its 256-wide tiles, shares of the work between
+the large and the small kernel, few and many rounds, the padding, sides that take turns, and statistics of mixed scale."""
 import numpy as np
 import pytest
 
@@ -60,8 +60,8 @@ def _step(torch, canz, rows, cols, n, rounds, grad_dtype, eps, level=0.02, beta=
     (2304, 1280, 3, 22, False),
     (300, 700, 1, 1, True),      # the first round is the last
     (300, 700, 1, 2, True),
-    (300, 700, 1, 36, True),     # the most rounds that are run ...
-    (300, 700, 1, 60, True),     # ... and more asked for: the padding must not overflow either
+    (300, 700, 1, 36, True),     # converged long ago: nothing drifts ...
+    (300, 700, 1, 60, True),     # ... however many rounds are asked for, and the padding does not overflow
 ])
 def test_roots_against_the_same_rounds_in_64_bits(canz, rows, cols, n, rounds, bf16):
     import torch
@@ -110,3 +110,51 @@ def test_sides_that_take_turns(canz):
         want = _newton(torch, s, float(np.float32(eps)), 2)
         want -= got.double()
         assert float(want.norm() / got.double().norm()) <= 3e-5
+
+
+def _statistic(torch, kind, d):
+    """Symmetric d x d fp32 statistics whose elements differ by many orders of magnitude, largest eigenvalue about 1."""
+    g = torch.Generator(device="cuda").manual_seed(d)
+    h = torch.randn(d, 2 * d, generator=g, device="cuda", dtype=torch.float64)
+    decades = torch.arange(d, device="cuda", dtype=torch.float64) / (d - 1)
+    if kind == "empty":                      # half of the rows have seen no gradient
+        h[d // 2:] = 0
+    elif kind.startswith("rows"):            # row scales 1 .. 10^-n
+        h *= (10.0 ** (-float(kind[4:]) * decades))[:, None]
+    s = torch.diag(10.0 ** (-float(kind[4:]) * decades)) if kind.startswith("diag") else h @ h.t() / (6 * d)
+    s = s.float()
+    return torch.triu(s) + torch.triu(s, 1).t()
+
+
+@pytest.mark.parametrize("kind,d,eps,rounds", [
+    ("empty", 300, 1e-6, 34),
+    ("empty", 300, 1e-8, 25),
+    ("empty", 513, 1e-10, 34),
+    ("rows4", 300, 0.0, 30),
+    ("rows5", 256, 0.0, 30),
+    ("rows6", 300, 0.0, 36),
+    ("diag12", 300, 0.0, 36),
+    ("diag12", 1000, 0.0, 45),   # the bound of the largest eigenvalue is loose: more rounds
+])
+def test_statistics_of_mixed_scale(canz, kind, d, eps, rounds):
+    """What is small against ||A|| makes up the root.  As long as the matrix is well conditioned once its rows and columns
+    are scaled to one size, relative rounding per element (fp32) moves the root by that much per product and no more:
+    4 products a round, 2^-24 each, adding up like random errors over at most 45 rounds: 8e-7; bound 2.5e-6.  An absolute
+    resolution of 2^-38 ||A|| is off by 1e-4 to 1 here."""
+    import torch
+    s = _statistic(torch, kind, d)
+    cols = 40
+    left, right = [s.clone()], [torch.eye(cols, device="cuda")]
+    lroot, rroot = [torch.empty_like(s)], [torch.empty_like(right[0])]
+    grp = canz.ShampooGroup(rows=d, cols=cols, grad=[torch.zeros(d, cols, device="cuda")], left=left, right=right,
+                            out=[torch.zeros(d, cols, device="cuda")], lroot=lroot, rroot=rroot, grad_dtype=canz.DT_F32)
+    hp = canz.ShampooHparams(beta=1.0, lr=1.0, eps=eps, root_iters=rounds, out_mode=canz.OUT_DELTA)
+    need = canz.canz_shampoo_workspace_bytes([grp], hp)
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+    canz.canz_shampoo_step([grp], hp, ws, need, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(left[0], s)
+    want = _newton(torch, s, float(np.float32(eps)), rounds)
+    err = float((lroot[0].double() - want).norm() / want.norm())
+    print("%s d %d eps %g rounds %d: %.3g" % (kind, d, eps, rounds, err))
+    assert err <= 2.5e-6
