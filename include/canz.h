@@ -305,6 +305,9 @@ typedef struct {
  * canz_shampoo_workspace_bytes - device scratch canz_shampoo_step needs for these groups (the
  * largest of its launch batches: same-shape matrices of one group, as many as fit in about
  * 8 GB of working matrices, at least one).  Pointer tables may be NULL for this call.
+ * The step also runs in less, down to the size of fp32 matrices padded to multiples of 128: 4 bytes times
+ * (3 rp cp + rp^2 + cp^2 + 8 max(rp, cp)^2 + 128) times the matrices of a batch (as many of these as fit in 8 GB, at
+ * least one); there it may be slower, with results of the same accuracy but not the same bits.
  */
 int canz_shampoo_workspace_bytes(const canz_shampoo_group* g, int32_t n_groups,
                                  const canz_shampoo_hparams* hp, size_t* bytes_out);

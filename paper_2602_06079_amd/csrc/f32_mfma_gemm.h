@@ -29,18 +29,20 @@ inline int64_t pad128(int64_t x) { return (x + SB - 1) / SB * SB; }
 inline size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
 // Epilogues: SE_STAT  S <- beta S + gscale C into the caller's dense statistic, S + eps I to c;
-//            SE_PLAIN c = C
+//            SE_PLAIN c = C;   SE_MT  c = C and c2 = 5/4 I - 1/4 C;   SE_OUT  the optimizer update
 //            into the caller's parameters or Delta W fragments;   SE_SUB  c <- c - C.
-enum { SE_STAT = 0, SE_PLAIN = 1, SE_SUB = 4 };
+enum { SE_STAT = 0, SE_PLAIN = 1, SE_MT = 2, SE_OUT = 3, SE_SUB = 4 };
 
 struct ShGemm {
   int64_t M, N, K;      // multiples of 128, 128, 32
   int64_t ldp, ldq;     // row strides of P [M][K] and Q [N][K]
-  int64_t sp, sq;       // batch strides
+  int64_t sp, sq;       // batch strides: matrix b reads P + (b / pdiv) sp and Q + (b / qdiv) sq
+  int pdiv, qdiv;       // 0 means 1; 2 lets two consecutive problems share an operand
   const float* P;
   const float* Q;
   float* c;             // output
   int64_t ldc, sc;      // its row and batch strides; 0, 0 means dense: N and M * N
+  float* c2;            // SE_MT: the next T = 5/4 I - 1/4 C (strides as c)
   // SE_STAT: the caller's statistic (d x d, dense) is updated in place and A = S + eps I is written to c
   int64_t d;
   float beta, gscale, eps;
@@ -90,8 +92,8 @@ __device__ __forceinline__ void sh_gemm_body(const ShGemm& g, const PtrTable& st
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
   const int wm = BN == SB ? wave >> 1 : wave, wn = BN == SB ? wave & 1 : 0;
-  const float* Pg = g.P + static_cast<int64_t>(b) * g.sp + static_cast<int64_t>(tm) * SB * g.ldp;
-  const float* Qg = g.Q + static_cast<int64_t>(b) * g.sq + static_cast<int64_t>(tn) * BN * g.ldq;
+  const float* Pg = g.P + static_cast<int64_t>(b / g.pdiv) * g.sp + static_cast<int64_t>(tm) * SB * g.ldp;
+  const float* Qg = g.Q + static_cast<int64_t>(b / g.qdiv) * g.sq + static_cast<int64_t>(tn) * BN * g.ldq;
 
   const int ld_row = t >> 3, ld_k = (t & 7) * 4;  // rows ld_row + 32 x (x = 0..3), 4 consecutive k
   // Long sums of the statistics (k up to the other extent of the matrix, terms of one sign on the
@@ -183,7 +185,9 @@ __device__ __forceinline__ void sh_gemm_body(const ShGemm& g, const PtrTable& st
       float v[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) v[r] = tot[i][j][r];
-      if (EPI == SE_PLAIN) {
+      if (EPI == SE_OUT) {
+        store_out_tile(o, s, b, row0, col, v);
+      } else if (EPI == SE_PLAIN) {
         put16(g.c + cb, g.ldc, row0, col, v, mirror);
       } else if (EPI == SE_SUB) {
         float* C = g.c + cb;
@@ -193,6 +197,11 @@ __device__ __forceinline__ void sh_gemm_body(const ShGemm& g, const PtrTable& st
 #pragma unroll
         for (int r = 0; r < 16; ++r) v[r] = old[r] - v[r];
         put16(C, g.ldc, row0, col, v, false);
+      } else if (EPI == SE_MT) {
+        put16(g.c + cb, g.ldc, row0, col, v, mirror);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r] = (row0 + 8 * (r >> 2) + (r & 3) == col ? 1.25f : 0.f) - 0.25f * v[r];
+        put16(g.c2 + cb, g.ldc, row0, col, v, mirror);
       } else {  // SE_STAT
         float* S = static_cast<float*>(stat.p[b]);
         const int d = static_cast<int>(g.d);
@@ -243,6 +252,8 @@ template <int EPI, bool SYM, int BN = SB>
 hipError_t launch_gemm(ShGemm g, int nb, const PtrTable& stat, const Shape& s, const OutSpec& o, hipStream_t st) {
   if (g.M < SB || g.N < BN || g.K < SK || g.M % SB || g.N % BN || g.K % SK || (SYM && g.M != g.N)) return hipErrorInvalidValue;
   if (g.ldc == 0) g.ldc = g.N, g.sc = g.M * g.N;
+  if (g.pdiv == 0) g.pdiv = 1;
+  if (g.qdiv == 0) g.qdiv = 1;
   const int64_t tm = g.M / SB, tn = g.N / BN;
   const int64_t blocks = (SYM ? tm * (tm + 1) / 2 : tm * tn) * nb;
   if constexpr (EPI == SE_STAT)

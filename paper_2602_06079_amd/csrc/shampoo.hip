@@ -195,6 +195,44 @@ __global__ __launch_bounds__(NTH) void k_sh_init(const float* __restrict__ parti
   }
 }
 
+// The same for fp32 matrices on the fp32 MFMA (see Path).
+// partial[b][p] = sum of squares of the elements p, p + NPART * NTH, ... (in blocks of NTH) of A[b]
+__global__ __launch_bounds__(NTH) void k_sh_sumsq_f32(const float* __restrict__ a, int64_t elems, float* __restrict__ partial) {
+  const int b = blockIdx.y, p = blockIdx.x;
+  const float* ab = a + static_cast<int64_t>(b) * elems;
+  float ss = 0.f;
+  for (int64_t i = static_cast<int64_t>(p) * NTH + threadIdx.x; i < elems; i += static_cast<int64_t>(NPART) * NTH) ss += ab[i] * ab[i];
+  block_sum_to(ss, partial + b * NPART + p);
+}
+
+__global__ __launch_bounds__(NTH) void k_sh_prescale_f32(const float* __restrict__ a, const float* __restrict__ partial,
+                                                      int64_t elems, float* __restrict__ m) {
+  const int b = blockIdx.y;
+  const float nrm = static_cast<float>(sqrt(sum_partials(partial, b)));
+  const float inv = nrm > 0.f ? 1.f / nrm : 0.f;
+  const int64_t off = static_cast<int64_t>(b) * elems;
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * NTH + threadIdx.x; i < elems; i += static_cast<int64_t>(gridDim.x) * NTH)
+    m[off + i] = inv * a[off + i];
+}
+
+__global__ __launch_bounds__(NTH) void k_sh_init_f32(const float* __restrict__ partial, const float* __restrict__ partial4,
+                                                  int64_t dp, float* __restrict__ x, float* __restrict__ m,
+                                                  float* __restrict__ tt) {
+  const int b = blockIdx.y;
+  const float nrm = static_cast<float>(sqrt(sum_partials(partial, b)));
+  const float bound = static_cast<float>(pow(sum_partials(partial4, b), 0.125));   // ||A'^4||_F^(1/4) >= lambda_max(A')
+  const float z = bound > 0.f ? 2.5f / bound : 1.f;
+  const float x0 = nrm > 0.f ? sqrtf(sqrtf(z / nrm)) : 1.f;
+  const int64_t elems = dp * dp, off = static_cast<int64_t>(b) * elems;
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * NTH + threadIdx.x; i < elems; i += static_cast<int64_t>(gridDim.x) * NTH) {
+    const bool diag = (i / dp) == (i % dp);
+    const float mv = z * m[off + i];
+    m[off + i] = mv;
+    tt[off + i] = (diag ? 1.25f : 0.f) - 0.25f * mv;
+    x[off + i] = diag ? x0 : 0.f;
+  }
+}
+
 // G (bf16 or fp32, whole or tp column fragments) -> what its readers want.  bf16: panels padded to 256 in both
 // orientations, for the statistics and the preconditioning product.  fp32: copies padded to 128 in both orientations for
 // the statistics, and the transposed one as three bf16 terms for the product.  One block per 64 x 64 tile of the larger padding.
@@ -236,8 +274,33 @@ __global__ __launch_bounds__(NTH) void k_sh_load_grad(Shape s, PtrTable grad, in
 
 bool bf16_statistics(const canz_shampoo_group& g) { return g.grad_dtype == CANZ_DT_BF16; }
 
-// Float offsets into the workspace of one launch batch.  root3, slot, tmp, g3t: three bf16 terms per element, 1.5 floats.
-struct Carve {
+struct Carve32 {   // float offsets into the workspace of one launch batch: the fp32 layout
+  size_t gs, gt, tmp, lroot, rroot, a, x[2], m[2], t, t2, t4, partial, partial4, total_bytes;
+};
+
+Carve32 carve32(int64_t rows, int64_t cols, int nb) {
+  const size_t rp = pad128(rows), cp = pad128(cols), dm = std::max(rp, cp);
+  Carve32 c{};
+  size_t off = 0;
+  auto take = [&](size_t floats) {
+    const size_t at = off;
+    off += align_up(floats * sizeof(float)) / sizeof(float);
+    return at;
+  };
+  c.gs = take(nb * rp * cp), c.gt = take(nb * rp * cp), c.tmp = take(nb * rp * cp);
+  c.lroot = take(nb * rp * rp), c.rroot = take(nb * cp * cp);
+  c.a = take(nb * dm * dm);
+  c.x[0] = take(nb * dm * dm), c.x[1] = take(nb * dm * dm);
+  c.m[0] = take(nb * dm * dm), c.m[1] = take(nb * dm * dm);
+  c.t = take(nb * dm * dm), c.t2 = take(nb * dm * dm), c.t4 = take(nb * dm * dm);
+  c.partial = take(static_cast<size_t>(nb) * NPART);
+  c.partial4 = take(static_cast<size_t>(nb) * NPART);
+  c.total_bytes = off * sizeof(float);
+  return c;
+}
+
+// The three-term layout.  slot, left3, g3t: three bf16 terms per element, 1.5 floats.
+struct Carve3 {
   size_t gs, gt, g3t, gp, gpt;         // G as its readers want it; gs, gt, gp are done with when the iteration begins
   size_t slot[2][5];                   // root iteration of each side; one set if the sides take turns
   size_t partial[2], partial4[2];
@@ -245,9 +308,9 @@ struct Carve {
   size_t total_bytes;
 };
 
-Carve carve(int64_t rows, int64_t cols, int nb, bool stat16, bool side_by_side) {
+Carve3 carve3(int64_t rows, int64_t cols, int nb, bool stat16, bool side_by_side) {
   const size_t rp2 = pad256(rows), cp2 = pad256(cols), plane = pad128(rows) * pad128(cols), p2 = nb * rp2 * cp2;
-  Carve c{};
+  Carve3 c{};
   size_t off = 0;
   auto take = [&](size_t floats) {
     const size_t at = off;
@@ -270,24 +333,41 @@ Carve carve(int64_t rows, int64_t cols, int nb, bool stat16, bool side_by_side) 
   const size_t end = off;
   off = begin;   // the statistics' operands, where the iteration will be
   c.gs = take(stat16 ? 0 : nb * plane), c.gt = take(stat16 ? 0 : nb * plane), c.gp = take(stat16 ? p2 / 2 : 0);
-  // Never less than the all-fp32 layout took (three planes, the roots and eight matrices of the larger side, padded to
-  // 128): what callers measured once stays what they are asked for, wherever the arrays above fit it.
-  const size_t rp = pad128(rows), cp = pad128(cols), dm = std::max(rp, cp);
-  const size_t before = nb * (3 * rp * cp + rp * rp + cp * cp + 8 * dm * dm) + 2 * nb * NPART;
-  c.total_bytes = std::max({off, end, before}) * sizeof(float);
+  c.total_bytes = std::max(off, end) * sizeof(float);
   return c;
 }
 
-// The sides run their rounds side by side unless one matrix alone would then not fit the batch's memory.
-bool sides_together(const canz_shampoo_group& g) {
-  return carve(g.rows, g.cols, 1, bf16_statistics(g), true).total_bytes <= BATCH_BYTES;
+// How a launch batch is computed.  With both sides' rounds side by side (TOGETHER) it is fastest: 4 x 1024 x 1024, 22 rounds
+// 7.4 ms against 9.9 with the sides in turns (TURNS) and 13.8 in fp32 matrices on the fp32 MFMA (FP32), 4 x 384 x 384 2.7
+// against 5.8 ms.  But three-term matrices padded to 256 can need more scratch than fp32 matrices padded to 128: square
+// ones of one size 16 or 17 matrices instead of 13, up to 128 x 128 four times as much.  canz_shampoo_workspace_bytes asks for
+// enough for the fastest; whatever suffices for the fp32 layout is accepted, and then the fastest that fits is taken, in
+// smaller batches before in another way.
+enum class Path { TOGETHER, TURNS, FP32 };
+size_t batch_bytes(const canz_shampoo_group& g, int nb, Path p) {
+  return p == Path::FP32 ? carve32(g.rows, g.cols, nb).total_bytes
+                         : carve3(g.rows, g.cols, nb, bf16_statistics(g), p == Path::TOGETHER).total_bytes;
 }
-
-int batch_cap(const canz_shampoo_group& g) {
-  const size_t one = carve(g.rows, g.cols, 1, bf16_statistics(g), sides_together(g)).total_bytes;
-  const int64_t by_bytes = std::max<int64_t>(1, static_cast<int64_t>(BATCH_BYTES / one));
-  return static_cast<int>(std::min<int64_t>(MAX_PTRS / g.tp, by_bytes));
+// matrices per batch: what the pointer tables and about 8 GB hold, at least one
+int batch_cap(const canz_shampoo_group& g, Path p) {
+  const int64_t by_bytes = std::max<int64_t>(1, static_cast<int64_t>(BATCH_BYTES / batch_bytes(g, 1, p)));
+  return static_cast<int>(std::min<int64_t>({MAX_PTRS / g.tp, by_bytes, std::max<int64_t>(1, g.n_mats)}));
 }
+struct Plan {
+  Path path;
+  int nb;
+};
+Plan plan_of(const canz_shampoo_group& g, size_t have) {
+  for (Path p : {Path::TOGETHER, Path::TURNS}) {   // one matrix of more than the batch memory: the sides in turns
+    const int nb = batch_cap(g, p);
+    if (batch_bytes(g, nb, p) <= (p == Path::TOGETHER ? std::min(have, BATCH_BYTES) : have)) return {p, nb};
+  }
+  for (Path p : {Path::TOGETHER, Path::TURNS})
+    if (batch_bytes(g, 1, p) <= (p == Path::TOGETHER ? std::min(have, BATCH_BYTES) : have))
+      return {p, std::min(batch_cap(g, p), static_cast<int>(std::min<size_t>(have, BATCH_BYTES) / batch_bytes(g, 1, p)))};
+  return {Path::FP32, batch_cap(g, Path::FP32)};
+}
+size_t least_bytes(const canz_shampoo_group& g) { return batch_bytes(g, batch_cap(g, Path::FP32), Path::FP32); }
 
 int check_hparams(const canz_shampoo_hparams* hp) {
   if (!hp) return fail(CANZ_EINVAL, "null hparams");
@@ -326,27 +406,143 @@ int check_group(const canz_shampoo_group& g, int idx, bool need_ptrs, int out_mo
   return CANZ_OK;
 }
 
-// One launch batch: matrices first .. first + nb - 1 of group g.
-int run_batch(const canz_shampoo_group& g, int first, int nb, const canz_shampoo_hparams& hp, float* ws, hipStream_t st) {
-  const int64_t rp = pad128(g.rows), cp = pad128(g.cols);
-  const bool stat16 = bf16_statistics(g), together = sides_together(g);
-  const Carve c = carve(g.rows, g.cols, nb, stat16, together);
+// what the kernels of one launch batch are told about it
+struct BatchArgs {
   Shape s{};
+  PtrTable grad{};
+  OutSpec o{};
+};
+BatchArgs batch_args(const canz_shampoo_group& g, int first, int nb, const canz_shampoo_hparams& hp) {
+  const int64_t rp = pad128(g.rows), cp = pad128(g.cols);
+  BatchArgs a;
+  Shape& s = a.s;
   s.rows = g.rows, s.cols = g.cols;
   s.m = std::min(g.rows, g.cols), s.n = std::max(g.rows, g.cols);
   s.mp = rp, s.np = cp;
   s.tall = g.rows > g.cols;
   s.tp = g.tp;
   s.wfrag = g.cols / g.tp;
-  PtrTable grad{};
+  PtrTable& grad = a.grad;
   for (int i = 0; i < nb * g.tp; ++i) grad.p[i] = const_cast<void*>(g.grad[first * g.tp + i]);
-  OutSpec o{};
+  OutSpec& o = a.o;
   const int per_out = hp.out_mode == CANZ_OUT_DELTA ? g.tp : 1;
   for (int i = 0; i < nb * per_out; ++i) o.out.p[i] = g.out[first * per_out + i];
   o.out_dtype = g.out_dtype;
   o.out_mode = hp.out_mode;
   o.decay = static_cast<float>(1.0 - static_cast<double>(hp.lr) * static_cast<double>(hp.weight_decay));
   o.neg_lr_scale = -hp.lr;
+  return a;
+}
+
+// One launch batch: matrices first .. first + nb - 1 of group g, everything on the fp32 MFMA.
+int run_batch_f32(const canz_shampoo_group& g, int first, int nb, const canz_shampoo_hparams& hp, float* ws, hipStream_t st) {
+  const int64_t rp = pad128(g.rows), cp = pad128(g.cols);
+  const Carve32 c = carve32(g.rows, g.cols, nb);
+  const BatchArgs args = batch_args(g, first, nb, hp);
+  const Shape& s = args.s;
+  const PtrTable& grad = args.grad;
+  const OutSpec& o = args.o;
+  const PtrTable none{};
+
+  float *gs = ws + c.gs, *gt = ws + c.gt, *tmp = ws + c.tmp;
+  {
+    const dim3 grid(static_cast<unsigned>(cp / 64), static_cast<unsigned>(rp / 64), static_cast<unsigned>(nb));
+    prof_mark(st, CANZ_KERNEL_SH_LOAD, true);
+    hipLaunchKernelGGL(k_sh_load, grid, dim3(NTH), 0, st, s, grad, g.grad_dtype, rp, cp, gs, gt);
+    prof_mark(st, CANZ_KERNEL_SH_LOAD, false);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "load kernel: %s", hipGetErrorString(e));
+  }
+
+  // one side: statistic (d x d, in the caller's buffers) from the operand `side` [dp][kp], then
+  // its inverse fourth root into `root`
+  auto one_side = [&](void* const* stat_tab, void* const* root_tab, int64_t d, int64_t dp, int64_t kp, const float* side,
+                      float* root) -> int {
+    PtrTable stat{}, kept{};
+    for (int i = 0; i < nb; ++i) stat.p[i] = stat_tab[first + i];
+    if (root_tab)
+      for (int i = 0; i < nb; ++i) kept.p[i] = root_tab[first + i];
+    Shape sq{};   // the d x d matrices of this side, for the padded load and the dense store of a kept root
+    sq.rows = d, sq.cols = d, sq.tp = 1, sq.wfrag = d;
+    const dim3 sq_tiles(static_cast<unsigned>(dp / 64), static_cast<unsigned>(dp / 64), static_cast<unsigned>(nb));
+    const int64_t dd = dp * dp;
+    float *a = ws + c.a, *x[2] = {ws + c.x[0], ws + c.x[1]}, *m[2] = {ws + c.m[0], ws + c.m[1]};
+    float *tt = ws + c.t, *t2 = ws + c.t2, *t4 = ws + c.t4, *partial = ws + c.partial, *partial4 = ws + c.partial4;
+    ShGemm q{};
+    q.M = dp, q.N = dp, q.K = kp, q.ldp = kp, q.ldq = kp, q.sp = dp * kp, q.sq = dp * kp;
+    q.P = side, q.Q = side, q.c = hp.keep_roots ? nullptr : a, q.d = d, q.beta = hp.beta, q.gscale = 1.f, q.eps = hp.eps;
+    CANZ_HIP(CANZ_KERNEL_SH_STAT, (launch_gemm<SE_STAT, true>(q, nb, stat, s, o, st)), "statistics kernel");
+    if (hp.keep_roots) {   // the caller's root, padded (its transposed image, which equals it, goes to a free buffer)
+      prof_mark(st, CANZ_KERNEL_SH_LOAD, true);
+      hipLaunchKernelGGL(k_sh_load, sq_tiles, dim3(NTH), 0, st, sq, kept, static_cast<int>(CANZ_DT_F32), dp, dp, root, x[0]);
+      prof_mark(st, CANZ_KERNEL_SH_LOAD, false);
+      if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "root load: %s", hipGetErrorString(e));
+      return CANZ_OK;
+    }
+    auto prod = [&](const float* P, const float* Q, float* C) {
+      ShGemm r{};
+      r.M = dp, r.N = dp, r.K = dp, r.ldp = dp, r.ldq = dp, r.sp = dd, r.sq = dd;
+      r.P = P, r.Q = Q, r.c = C;
+      return r;
+    };
+    const unsigned init_blocks = static_cast<unsigned>(std::min<int64_t>(4096, (dd + NTH - 1) / NTH));
+    prof_mark(st, CANZ_KERNEL_SH_INIT, true);
+    hipLaunchKernelGGL(k_sh_sumsq_f32, dim3(NPART, nb), dim3(NTH), 0, st, a, dd, partial);
+    hipLaunchKernelGGL(k_sh_prescale_f32, dim3(init_blocks, nb), dim3(NTH), 0, st, a, partial, dd, m[0]);
+    prof_mark(st, CANZ_KERNEL_SH_INIT, false);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "root start: %s", hipGetErrorString(e));
+    CANZ_HIP(CANZ_KERNEL_SH_ROOT, (launch_gemm<SE_PLAIN, true>(prod(m[0], m[0], t2), nb, none, s, o, st)), "root start (A A)");
+    CANZ_HIP(CANZ_KERNEL_SH_ROOT, (launch_gemm<SE_PLAIN, true>(prod(t2, t2, t4), nb, none, s, o, st)), "root start (A2 A2)");
+    prof_mark(st, CANZ_KERNEL_SH_INIT, true);
+    hipLaunchKernelGGL(k_sh_sumsq_f32, dim3(NPART, nb), dim3(NTH), 0, st, t4, dd, partial4);
+    hipLaunchKernelGGL(k_sh_init_f32, dim3(init_blocks, nb), dim3(NTH), 0, st, partial, partial4, dp, x[0], m[0], tt);
+    prof_mark(st, CANZ_KERNEL_SH_INIT, false);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "root start: %s", hipGetErrorString(e));
+    int cur = 0;
+    for (int it = 0; it < hp.root_iters; ++it) {
+      const bool last = it + 1 == hp.root_iters;
+      CANZ_HIP(CANZ_KERNEL_SH_ROOT, (launch_gemm<SE_PLAIN, true>(prod(x[cur], tt, last ? root : x[cur ^ 1]), nb, none, s, o, st)),
+               "root kernel (X T)");
+      if (last) break;
+      CANZ_HIP(CANZ_KERNEL_SH_ROOT, (launch_gemm<SE_PLAIN, true>(prod(tt, tt, t2), nb, none, s, o, st)), "root kernel (T T)");
+      CANZ_HIP(CANZ_KERNEL_SH_ROOT, (launch_gemm<SE_PLAIN, true>(prod(t2, t2, t4), nb, none, s, o, st)), "root kernel (T2 T2)");
+      ShGemm r = prod(t4, m[cur], m[cur ^ 1]);
+      r.c2 = tt;
+      CANZ_HIP(CANZ_KERNEL_SH_ROOT, (launch_gemm<SE_MT, true>(r, nb, none, s, o, st)), "root kernel (T4 M)");
+      cur ^= 1;
+    }
+    if (root_tab) {
+      prof_mark(st, CANZ_KERNEL_SH_LOAD, true);
+      hipLaunchKernelGGL(k_unpad, sq_tiles, dim3(NTH), 0, st, sq, kept, root, dd, dp);
+      prof_mark(st, CANZ_KERNEL_SH_LOAD, false);
+      if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "root store: %s", hipGetErrorString(e));
+    }
+    return CANZ_OK;
+  };
+  float *lroot = ws + c.lroot, *rroot = ws + c.rroot;
+  if (int rc = one_side(g.left, g.lroot, g.rows, rp, cp, gs, lroot)) return rc;
+  if (int rc = one_side(g.right, g.rroot, g.cols, cp, rp, gt, rroot)) return rc;
+
+  // O = (L^(-1/4) G) R^(-1/4): P = L root, Q = G^T gives rows x cols; then P = that, Q = R root
+  ShGemm a1{};
+  a1.M = rp, a1.N = cp, a1.K = rp, a1.ldp = rp, a1.ldq = rp, a1.sp = rp * rp, a1.sq = rp * cp;
+  a1.P = lroot, a1.Q = gt, a1.c = tmp;
+  CANZ_HIP(CANZ_KERNEL_SH_APPLY, (launch_gemm<SE_PLAIN, false>(a1, nb, none, s, o, st)), "preconditioning kernel (left)");
+  ShGemm a2{};
+  a2.M = rp, a2.N = cp, a2.K = cp, a2.ldp = cp, a2.ldq = cp, a2.sp = rp * cp, a2.sq = cp * cp;
+  a2.P = tmp, a2.Q = rroot;
+  CANZ_HIP(CANZ_KERNEL_SH_APPLY, (launch_gemm<SE_OUT, false>(a2, nb, none, s, o, st)), "preconditioning kernel (right)");
+  return CANZ_OK;
+}
+
+// One launch batch: matrices first .. first + nb - 1 of group g, three bf16 terms per element.
+int run_batch_terms(const canz_shampoo_group& g, int first, int nb, bool together, const canz_shampoo_hparams& hp, float* ws, hipStream_t st) {
+  const int64_t rp = pad128(g.rows), cp = pad128(g.cols);
+  const bool stat16 = bf16_statistics(g);
+  const Carve3 c = carve3(g.rows, g.cols, nb, stat16, together);
+  const BatchArgs args = batch_args(g, first, nb, hp);
+  const Shape& s = args.s;
+  const PtrTable& grad = args.grad;
+  const OutSpec& o = args.o;
 
   float *gs = stat16 ? nullptr : ws + c.gs, *gt = stat16 ? nullptr : ws + c.gt;
   const int64_t rp2 = pad256(g.rows), cp2 = pad256(g.cols);
@@ -479,9 +675,8 @@ int run_batch(const canz_shampoo_group& g, int first, int nb, const canz_shampoo
   }
   // O = (L^(-1/4) G) R^(-1/4) on the bf16 cores, the roots and L^(-1/4) G as three terms per element (six products of
   // terms, three where G is bf16 itself): a step of 14 x 3072 x 1024 on kept roots 4.34 -> 2.26 ms against the fp32 MFMA.
-  // L^(-1/4) G takes a place of the larger side that its root does not lie in.
-  const Side& larger = side[rp2 >= cp2 ? 0 : 1];
-  __bf16* const tmp = larger.slot[larger.root3 == larger.slot[2] || (!together && side[1].root3 == side[1].slot[2]) ? 1 : 2];
+  // L^(-1/4) G takes the place of the larger side's T (the roots lie in the free places, 0 or 3).
+  __bf16* const tmp = side[rp2 >= cp2 ? 0 : 1].slot[2];
   // P = L root, Q = G^T gives rows x cols; then P = that, Q = R root
   const __bf16* gt_terms = stat16 ? gpt : terms(c.g3t);
   CANZ_HIP(CANZ_KERNEL_SH_APPLY, launch_split3(split3_dims(rp2, cp2, rp2, stat16 ? 1 : 3, nb), side[0].root3, gt_terms, tmp, st),
@@ -559,7 +754,8 @@ extern "C" int canz_shampoo_workspace_bytes(const canz_shampoo_group* g, int32_t
   for (int i = 0; i < n_groups; ++i)
     if (int rc = check_group(g[i], i, false, hp->out_mode, hp->keep_roots != 0)) return rc;
   for (const MergedGroup& m : merge_groups(g, n_groups, hp->out_mode))
-    need = std::max(need, carve(m.g.rows, m.g.cols, std::min(m.g.n_mats, batch_cap(m.g)), bf16_statistics(m.g), sides_together(m.g)).total_bytes);
+    if (const Plan p = plan_of(m.g, SIZE_MAX); m.g.n_mats > 0)
+      need = std::max({need, batch_bytes(m.g, p.nb, p.path), least_bytes(m.g)});
   *bytes_out = need;
   return CANZ_OK;
 }
@@ -567,7 +763,7 @@ extern "C" int canz_shampoo_workspace_bytes(const canz_shampoo_group* g, int32_t
 extern "C" int canz_shampoo_step(const canz_shampoo_group* g, int32_t n_groups, const canz_shampoo_hparams* hp,
                                  void* workspace, size_t workspace_bytes, void* hip_stream) {
   using namespace canz;
-  size_t need = 0;
+  size_t need = 0;   // of the fastest way; checks the arguments
   if (int rc = canz_shampoo_workspace_bytes(g, n_groups, hp, &need)) return rc;
   bool any = false;
   for (int i = 0; i < n_groups; ++i) {
@@ -577,13 +773,20 @@ extern "C" int canz_shampoo_step(const canz_shampoo_group* g, int32_t n_groups, 
   if (!any) return CANZ_OK;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & (ALIGN - 1)))
     return fail(CANZ_EWORKSPACE, "workspace null or not 256-byte aligned");
-  if (workspace_bytes < need)
-    return fail(CANZ_EWORKSPACE, "workspace too small: %zu bytes given, %zu needed", workspace_bytes, need);
+  const std::vector<MergedGroup> merged = merge_groups(g, n_groups, hp->out_mode);
+  for (const MergedGroup& m : merged)
+    if (workspace_bytes < least_bytes(m.g))
+      return fail(CANZ_EWORKSPACE, "workspace too small: %zu bytes given, %zu needed", workspace_bytes, need);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  for (const MergedGroup& m : merge_groups(g, n_groups, hp->out_mode)) {
-    const int cap = batch_cap(m.g);
-    for (int first = 0; first < m.g.n_mats; first += cap)
-      if (int rc = run_batch(m.g, first, std::min(cap, m.g.n_mats - first), *hp, static_cast<float*>(workspace), st)) return rc;
+  float* ws = static_cast<float*>(workspace);
+  for (const MergedGroup& m : merged) {
+    const Plan p = plan_of(m.g, workspace_bytes);
+    for (int first = 0; first < m.g.n_mats; first += p.nb) {
+      const int nb = std::min(p.nb, m.g.n_mats - first);
+      const int rc = p.path == Path::FP32 ? run_batch_f32(m.g, first, nb, *hp, ws, st)
+                                          : run_batch_terms(m.g, first, nb, p.path == Path::TOGETHER, *hp, ws, st);
+      if (rc) return rc;
+    }
   }
   return CANZ_OK;
 }

@@ -178,3 +178,22 @@ def test_soap_argument_errors_and_workspace_without_device(canz):
     assert canz.canz_soap_workspace_bytes(one, canz.SoapHparams(bf16_rotations=True)) == want16
     assert canz.canz_soap_workspace_bytes(one16, canz.SoapHparams(bf16_rotations=True)) == want16
     assert ctypes.sizeof(canz._SoapGroup) == 16 + 16 + 72 and ctypes.sizeof(canz._SoapHparams) == 48
+
+
+def test_shampoo_workspace_for_every_shape(canz):
+    """What is asked for: never less than the documented size of fp32 matrices padded to 128 (which the step accepts), at most
+    5.5 times that (padding to 256 where 128 would do), and in batches of about 8 GB."""
+    pad = lambda x: (x + 127) // 128 * 128  # noqa: E731
+    extents = [1, 96, 128, 129, 256, 257, 300, 384, 400, 500, 640, 700, 896, 1000, 1024, 1300, 2048, 3000, 8192, 32768]
+    for dtype in (canz.DT_BF16, canz.DT_F32):
+        for rows in extents:
+            for cols in extents:
+                rp, cp = pad(rows), pad(cols)
+                dm = max(rp, cp)
+                one = 4 * (3 * rp * cp + rp * rp + cp * cp + 8 * dm * dm + 128)
+                for n in (1, 3, 64):
+                    least = one * max(1, min(n, (8 << 30) // one))
+                    got = canz.canz_shampoo_workspace_bytes([canz.ShampooGroup(rows=rows, cols=cols, n_mats=n, grad_dtype=dtype)],
+                                                            canz.ShampooHparams())
+                    assert least <= got <= max(5.5 * least if dm <= 128 else 2.4 * least, 256), (rows, cols, n)
+                    assert got <= max(8 << 30, 1.01 * one), (rows, cols, n)

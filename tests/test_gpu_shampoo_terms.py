@@ -34,7 +34,10 @@ def _newton(torch, s, eps, rounds):
     return x
 
 
-def _step(torch, canz, rows, cols, n, rounds, grad_dtype, eps, level=0.02, beta=1.0):
+GUARD = 1 << 16   # bytes behind the workspace that must stay as they are
+
+
+def _step(torch, canz, rows, cols, n, rounds, grad_dtype, eps, level=0.02, beta=1.0, least=False):
     g = torch.Generator(device="cuda").manual_seed(rows * 10007 + cols)
     draw = lambda r, c: torch.randn(r, c, generator=g, device="cuda")  # noqa: E731
     grads = [(draw(rows, cols) * level).to(grad_dtype) for _ in range(n)]
@@ -46,9 +49,13 @@ def _step(torch, canz, rows, cols, n, rounds, grad_dtype, eps, level=0.02, beta=
                             grad_dtype=canz.DT_BF16 if grad_dtype == torch.bfloat16 else canz.DT_F32)
     hp = canz.ShampooHparams(beta=beta, lr=1.0, eps=eps, root_iters=rounds, out_mode=canz.OUT_DELTA)
     need = canz.canz_shampoo_workspace_bytes([grp], hp)
-    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")   # every byte a NaN: nothing may be read unwritten
+    if least:   # the size of fp32 matrices padded to 128 is accepted as well
+        rp, cp = (rows + 127) // 128 * 128, (cols + 127) // 128 * 128
+        need = n * 4 * (3 * rp * cp + rp * rp + cp * cp + 8 * max(rp, cp) ** 2 + 128)
+    ws = torch.full((need + GUARD,), 0xFF, dtype=torch.uint8, device="cuda")   # every byte a NaN: nothing may be read unwritten
     canz.canz_shampoo_step([grp], hp, ws, need, torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
+    assert bool((ws[need:] == 0xFF).all())
     return grads, left, right, lroot, rroot, out
 
 
@@ -66,7 +73,11 @@ def _step(torch, canz, rows, cols, n, rounds, grad_dtype, eps, level=0.02, beta=
 def test_roots_against_the_same_rounds_in_64_bits(canz, rows, cols, n, rounds, bf16):
     import torch
     eps = 1e-3
-    grads, left, right, lroot, rroot, out = _step(torch, canz, rows, cols, n, rounds, torch.bfloat16 if bf16 else torch.float32, eps)
+    step = _step(torch, canz, rows, cols, n, rounds, torch.bfloat16 if bf16 else torch.float32, eps)
+    _check(torch, rows, cols, n, rounds, eps, *step)
+
+
+def _check(torch, rows, cols, n, rounds, eps, grads, left, right, lroot, rroot, out):
     for i in range(n):
         g = grads[i].double()
         for got, want in ((left[i], g @ g.t()), (right[i], g.t() @ g)):
@@ -82,6 +93,20 @@ def test_roots_against_the_same_rounds_in_64_bits(canz, rows, cols, n, rounds, b
         # two fp32 products: each rounds relative to the norms of its factors (a root's is at most eps^(-1/4)), not to
         # the result, in which G's own directions meet the small end of the roots' spectra
         assert float((out[i].double() - want).norm()) <= 1e-6 * eps ** -0.5 * float(g.norm())
+
+
+@pytest.mark.parametrize("rows,cols,n,bf16", [
+    (96, 128, 3, True),      # fp32 matrices: padding to 256 is four times the size
+    (640, 600, 1, False),    # ... 1.44 times, and only one matrix
+    (300, 380, 4, True),     # 1.78 times: smaller batches, both sides side by side
+    (512, 500, 2, True),     # the sides take turns
+    (760, 700, 1, False),
+    (1024, 300, 2, True),    # all that is asked for
+])
+def test_least_workspace(canz, rows, cols, n, bf16):
+    import torch
+    step = _step(torch, canz, rows, cols, n, 22, torch.bfloat16 if bf16 else torch.float32, 1e-3, least=True)
+    _check(torch, rows, cols, n, 22, 1e-3, *step)
 
 
 @pytest.mark.parametrize("level", [1e-6, 1e6])
@@ -131,6 +156,7 @@ def _statistic(torch, kind, d):
     ("empty", 300, 1e-8, 25),
     ("empty", 513, 1e-10, 34),
     ("rows4", 300, 0.0, 30),
+    ("rows4", 500, 0.0, 30),
     ("rows5", 256, 0.0, 30),
     ("rows6", 300, 0.0, 36),
     ("diag12", 300, 0.0, 36),
@@ -138,9 +164,10 @@ def _statistic(torch, kind, d):
 ])
 def test_statistics_of_mixed_scale(canz, kind, d, eps, rounds):
     """What is small against ||A|| makes up the root.  As long as the matrix is well conditioned once its rows and columns
-    are scaled to one size, relative rounding per element (fp32) moves the root by that much per product and no more:
-    4 products a round, 2^-24 each, adding up like random errors over at most 45 rounds: 8e-7; bound 2.5e-6.  An absolute
-    resolution of 2^-38 ||A|| is off by 1e-4 to 1 here."""
+    are scaled to one size, relative rounding per element (fp32) moves the root by what the products round and no more: 4
+    products a round, each a sum that is rounded up to d / 2 times (fp32 MFMA; small shapes run on it), 2^-24 each time, all
+    adding up like random errors: 2^-24 sqrt(d / 2) sqrt(4 rounds), 8e-6 at d = 300.  An absolute resolution of 2^-38 ||A||
+    is off by 1e-4 to 1 here."""
     import torch
     s = _statistic(torch, kind, d)
     cols = 40
@@ -157,4 +184,4 @@ def test_statistics_of_mixed_scale(canz, kind, d, eps, rounds):
     want = _newton(torch, s, float(np.float32(eps)), rounds)
     err = float((lroot[0].double() - want).norm() / want.norm())
     print("%s d %d eps %g rounds %d: %.3g" % (kind, d, eps, rounds, err))
-    assert err <= 2.5e-6
+    assert err <= 2.0 ** -24 * (d / 2 * 4 * rounds) ** 0.5
