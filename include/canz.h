@@ -396,12 +396,15 @@ typedef struct {
   int32_t max_precond_dim;  /* >= 1 */
   int32_t out_mode;         /* CANZ_OUT_* */
   int32_t mom_rot_valid;    /* 1: mom_rot holds Q_L^T M Q_R of the M and the bases passed in */
-  int32_t bf16_rotations;   /* 0: everything in fp32; 1: the rotations of steps 3 and 6 on bf16 operands */
+  int32_t bf16_rotations;   /* 0: everything at fp32 accuracy; 1: the rotations of steps 3 and 6 on bf16 operands */
 } canz_soap_hparams;
 
 /*
  * canz_soap_workspace_bytes - device scratch canz_soap_step needs for these groups and these
  * hyper-parameters (a refresh step needs more).  Pointer tables may be NULL for this call.
+ * The step also runs in less, down to what fp32 matrices padded to multiples of 128 take: per matrix 10 planes of rp x cp
+ * (7 if one side keeps no basis), two of d x d for each side with a basis and one of the larger of them, plus the
+ * refresh's matrices and bf16 images; there it may be slower, with results of the same accuracy but not the same bits.
  */
 int canz_soap_workspace_bytes(const canz_soap_group* g, int32_t n_groups, const canz_soap_hparams* hp,
                               size_t* bytes_out);

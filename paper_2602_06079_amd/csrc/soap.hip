@@ -56,7 +56,8 @@ constexpr int QWAVES = QTH / 64;
 // Where k_soap_load leaves its results: fp32 working copies and / or bf16 images in the panel layout
 // (panel_layout.h; padded to multiples of 256, operands of the bf16 MFMA kernels), each in both orientations.
 struct LoadOut {
-  float *gm, *gmt;               // fp32 G [nb][rp][cp] and G^T [nb][cp][rp]; nullptr: not wanted
+  float *gm, *gmt, *mm, *mmt;    // fp32 G [rp][cp] and G^T [cp][rp] of each matrix, `stride` floats apart, and M; nullptr: not wanted
+  int64_t stride;
   __bf16 *g3, *g3t, *m3, *m3t;   // three bf16 terms: G [nb][rp2][3 cp2], G^T [nb][cp2][3 rp2], M, M^T; nullptr: not wanted
   __bf16 *gp, *gpt, *mp, *mpt;   // bf16 panels: G [nb][rp2][cp2], G^T [nb][cp2][rp2], M, M^T; nullptr: not wanted
   int64_t rp2, cp2;
@@ -73,9 +74,10 @@ __global__ __launch_bounds__(NTH) void k_soap_load(Shape s, PtrTable grad, int g
   __shared__ float tg[64][65], tm[64][65];
   const int b = blockIdx.z, r0 = blockIdx.y * 64, c0 = blockIdx.x * 64, t = threadIdx.x;
   const int wf = static_cast<int>(s.wfrag);
-  const int64_t plane = rp * cp;
-  float* gs = w.gm ? w.gm + static_cast<int64_t>(b) * plane : nullptr;
-  float* gt = w.gm ? w.gmt + static_cast<int64_t>(b) * plane : nullptr;
+  float* gs = w.gm ? w.gm + b * w.stride : nullptr;
+  float* gt = w.gm ? w.gmt + b * w.stride : nullptr;
+  float* ms = w.mm ? w.mm + b * w.stride : nullptr;
+  float* mt = w.mm ? w.mmt + b * w.stride : nullptr;
   float* m = static_cast<float*>(mom.p[b]);
   if (VEC) {
     const int cv = (t & 7) * 8;
@@ -120,6 +122,10 @@ __global__ __launch_bounds__(NTH) void k_soap_load(Shape s, PtrTable grad, int g
           f32x4* o = reinterpret_cast<f32x4*>(gs + static_cast<int64_t>(row) * cp + col);
           o[0] = gv[half][0], o[1] = gv[half][1];
         }
+        if (ms) {
+          f32x4* o = reinterpret_cast<f32x4*>(ms + static_cast<int64_t>(row) * cp + col);
+          o[0] = mv[half][0], o[1] = mv[half][1];
+        }
       }
     }
   } else {
@@ -139,17 +145,21 @@ __global__ __launch_bounds__(NTH) void k_soap_load(Shape s, PtrTable grad, int g
     }
     if (row < rp && col < cp) {
       if (gs) gs[static_cast<int64_t>(row) * cp + col] = g;
+      if (ms) ms[static_cast<int64_t>(row) * cp + col] = mv;
     }
     tg[r][c] = g;
     tm[r][c] = mv;
   }
   }
   __syncthreads();
-  if (gs) {
+  if (gs || ms) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int idx = e * NTH + t, r = idx >> 6, c = idx & 63;  // r: column of G, c: row of G
-      if (c0 + r < cp && r0 + c < rp) gt[static_cast<int64_t>(c0 + r) * rp + r0 + c] = tg[c][r];
+      if (c0 + r < cp && r0 + c < rp) {
+        if (gs) gt[static_cast<int64_t>(c0 + r) * rp + r0 + c] = tg[c][r];
+        if (ms) mt[static_cast<int64_t>(c0 + r) * rp + r0 + c] = tm[c][r];
+      }
     }
   }
   const int64_t p2 = static_cast<int64_t>(b) * w.rp2 * w.cp2;
@@ -163,14 +173,14 @@ __global__ __launch_bounds__(NTH) void k_soap_load(Shape s, PtrTable grad, int g
   if (w.m3t) tile_to_terms3(tm, w.m3t + 3 * p2, r0, c0, w.rp2, true, t);
 }
 
-// Adam in the rotated space.  G' and (unless `incremental`) M' are dense fp32 [rows][cols], `stride` floats apart; V (dense, caller's) is
-// updated in place; N' = (c1 M') / (sqrt(c2 V) + eps) leaves as three bf16 terms per element, [rp2][3 cp2] panels or
-// transposed [cp2][3 rp2], zero outside rows x cols.  If the caller keeps the rotated momentum (`keep`, dense, mrot):
-// incremental: M' = beta1 mrot + (1 - beta1) G'; either way mrot <- M'.
+// Adam in the rotated space.  G' and (unless `incremental`) M' are fp32 of row length `ld`, `stride` floats apart; V (dense, caller's)
+// is updated in place; N' = (c1 M') / (sqrt(c2 V) + eps) leaves as three bf16 terms per element, [rp2][3 cp2] panels or
+// transposed [cp2][3 rp2] (np), or in fp32, [rp][cp] or transposed [cp][rp] (n32), zero outside rows x cols.  If the caller
+// keeps the rotated momentum (`keep`, dense, mrot): incremental: M' = beta1 mrot + (1 - beta1) G'; either way mrot <- M'.
 __global__ __launch_bounds__(NTH) void k_soap_adam(Shape s, PtrTable var, PtrTable mrot, bool keep, bool incremental,
-                                                    const float* __restrict__ grot, const float* __restrict__ m_rot, int64_t stride,
+                                                    const float* __restrict__ grot, const float* __restrict__ m_rot, int64_t ld, int64_t stride,
                                                     int64_t rp2, int64_t cp2, float beta1, float beta2, float c1, float c2, float eps,
-                                                    int transposed, __bf16* __restrict__ np) {
+                                                    int transposed, __bf16* __restrict__ np, float* __restrict__ n32) {
   __shared__ float tile[64][65];
   const int b = blockIdx.z, r0 = blockIdx.y * 64, c0 = blockIdx.x * 64, t = threadIdx.x;
   const int64_t at = b * stride;
@@ -182,10 +192,10 @@ __global__ __launch_bounds__(NTH) void k_soap_adam(Shape s, PtrTable var, PtrTab
   for (int e = 0; e < 16; ++e) {   // all old values first: one memory latency for the tile
     const int idx = e * NTH + t, row = r0 + (idx >> 6), col = c0 + (idx & 63);
     const bool in = row < s.rows && col < s.cols;
-    const int64_t av = static_cast<int64_t>(row) * s.cols + col;
-    go[e] = in ? gr[av] : 0.f;
+    const int64_t av = static_cast<int64_t>(row) * s.cols + col, ar = row * ld + col;
+    go[e] = in ? gr[ar] : 0.f;
     vo[e] = in ? v[av] : 0.f;
-    mo[e] = !in ? 0.f : incremental ? mr[av] : m_rot[at + av];
+    mo[e] = !in ? 0.f : incremental ? mr[av] : m_rot[at + ar];
   }
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
@@ -203,14 +213,28 @@ __global__ __launch_bounds__(NTH) void k_soap_adam(Shape s, PtrTable var, PtrTab
     tile[r][c] = n;
   }
   __syncthreads();
+  if (n32) {
+    const int64_t rp = s.mp, cp = s.np;   // the fp32 padding
+    float* out = n32 + b * rp * cp;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int idx = e * NTH + t, r = idx >> 6, c = idx & 63;
+      if (transposed) {
+        if (c0 + r < cp && r0 + c < rp) out[(c0 + r) * rp + r0 + c] = tile[c][r];
+      } else if (r0 + r < rp && c0 + c < cp) {
+        out[(r0 + r) * cp + c0 + c] = tile[r][c];
+      }
+    }
+    return;
+  }
   tile_to_terms3(tile, np + static_cast<int64_t>(b) * 3 * rp2 * cp2, r0, c0, transposed ? rp2 : cp2, transposed != 0, t);
 }
 
-// The caller's basis Q (d x d, dense fp32) -> what its readers want, zero outside d x d: its transpose in fp32 [dp][dp]
-// (for the refresh), and in both orientations bf16 panels [dp2][dp2] or three bf16 terms [dp2][3 dp2]; nullptr: not
+// The caller's basis Q (d x d, dense fp32) -> what its readers want, zero outside d x d, in both orientations: fp32 [dp][dp]
+// (transposed also for the refresh), bf16 panels [dp2][dp2] or three bf16 terms [dp2][3 dp2]; nullptr: not
 // wanted.  One block per 64 x 64 tile of the larger padding.
 struct BasisOut {
-  float* t32;
+  float *s32, *t32;
   __bf16 *sp, *tp, *s3, *t3;
 };
 __global__ __launch_bounds__(NTH) void k_soap_load_basis(PtrTable q, int64_t d, int64_t dp, int64_t dp2, BasisOut w) {
@@ -221,7 +245,9 @@ __global__ __launch_bounds__(NTH) void k_soap_load_basis(PtrTable q, int64_t d, 
   for (int e = 0; e < 16; ++e) {
     const int idx = e * NTH + t, r = idx >> 6, c = idx & 63;
     const int64_t row = r0 + r, col = c0 + c;
-    tile[r][c] = row < d && col < d ? src[row * d + col] : 0.f;
+    const float val = row < d && col < d ? src[row * d + col] : 0.f;
+    if (w.s32 && row < dp && col < dp) w.s32[(b * dp + row) * dp + col] = val;
+    tile[r][c] = val;
   }
   __syncthreads();
   if (w.t32) {
@@ -873,9 +899,13 @@ __global__ __launch_bounds__(QTH) void k_qr_block_u(const float* __restrict__ cb
   }
 }
 
+// How the rotations of a launch batch are computed (plan_of): on fp32 matrices, on three bf16 terms per element, or on bf16
+// operands.
+enum class Rot { F32, TERMS, BF16 };
+
 struct Carve {   // float offsets into the workspace of one launch batch
-  size_t gm, gmt, stat, wk, vall, y2, ybuf, tau, wt, qt, tb, cb, ub, u2, total_bytes;
-  // fp32 rotations: G', M' dense; three bf16 terms per element, padded to 256 (offsets in floats as well): G (if it is not
+  size_t gm, gmt, t1, rot, np, yt, ql, qlt, qr, qrt, stat, wk, vall, y2, ybuf, tau, wt, qt, tb, cb, ub, u2, total_bytes;
+  // rotations on three bf16 terms: G', M' dense; three bf16 terms per element, padded to 256 (offsets in floats as well): G (if it is not
   // bf16 itself) and M in the orientations wanted, X Q_R transposed, N', its half-rotated image, the bases
   size_t rotg, rotm, g3, g3t, m3, m3t, t3, n3, y3, ql3, ql3t, qr3, qr3t;
   // bf16 rotations (offsets in floats as well; each array holds bf16 panels padded to 256)
@@ -896,9 +926,10 @@ bool bf16_statistics(const canz_soap_group& g) { return g.grad_dtype == CANZ_DT_
 // floats from one dense rows x cols working matrix to the next: each starts aligned, as the callers' own buffers do
 inline int64_t dense_stride(int64_t rows, int64_t cols) { return (rows * cols + 63) / 64 * 64; }
 
-Carve carve(int64_t rows, int64_t cols, int nb, Sides u, bool refresh, bool bf16, bool stat16) {
+Carve carve(int64_t rows, int64_t cols, int nb, Sides u, bool refresh, Rot rot, bool stat16) {
   const size_t rp = pad128(rows), cp = pad128(cols);
   const size_t dm = std::max(u.left ? rp : 0, u.right ? cp : 0);
+  const bool both = u.left && u.right, bf16 = rot == Rot::BF16;
   Carve c{};
   size_t off = 0;
   auto take = [&](size_t floats) {
@@ -907,8 +938,18 @@ Carve carve(int64_t rows, int64_t cols, int nb, Sides u, bool refresh, bool bf16
     return at;
   };
   const size_t plane = rp * cp;
-  c.gm = take(stat16 ? 0 : nb * plane), c.gmt = take(stat16 ? 0 : nb * plane);
-  if (bf16) c.stat = take(nb * dm * dm);
+  if (rot == Rot::TERMS) {
+    c.gm = take(stat16 ? 0 : nb * plane), c.gmt = take(stat16 ? 0 : nb * plane);
+  } else {   // the bf16 rotations use G, G^T and the statistic of these only
+    c.gm = take(2 * nb * plane), c.gmt = take(2 * nb * plane);
+    c.t1 = take(both ? 2 * nb * plane : 0);
+    c.rot = take(2 * nb * plane);
+    c.np = take(nb * plane);
+    c.yt = take(both ? nb * plane : 0);
+    c.ql = take(u.left ? nb * rp * rp : 0), c.qlt = take(u.left ? nb * rp * rp : 0);
+    c.qr = take(u.right ? nb * cp * cp : 0), c.qrt = take(u.right ? nb * cp * cp : 0);
+    c.stat = take(nb * dm * dm);
+  }
   if (refresh) {
     c.wk = take(nb * dm * dm);
     c.vall = take(nb * dm * dm);
@@ -923,10 +964,10 @@ Carve carve(int64_t rows, int64_t cols, int nb, Sides u, bool refresh, bool bf16
     c.u2 = take(nb * dm * QBLK);       // U2^T of every block
   }
   const size_t rp2 = pad256(rows), cp2 = pad256(cols), p2 = nb * rp2 * cp2 / 2;   // floats that hold a batch of panels
-  if (bf16 || stat16) c.gp = take(p2), c.gpt = take(p2);
-  if (!bf16) {
+  const bool all_of_g = bf16 || rot == Rot::TERMS;   // G is an operand of the rotations, too
+  if (bf16 || stat16) c.gp = take(all_of_g || u.left ? p2 : 0), c.gpt = take(all_of_g || u.right ? p2 : 0);
+  if (rot == Rot::TERMS) {
     const size_t p3 = nb * rp2 * cp2 * 3 / 2, l3 = nb * rp2 * rp2 * 3 / 2, r3 = nb * cp2 * cp2 * 3 / 2;
-    const bool both = u.left && u.right;
     c.rotg = take(nb * dense_stride(rows, cols)), c.rotm = take(nb * dense_stride(rows, cols));
     c.g3 = take(!stat16 && u.right ? p3 : 0), c.g3t = take(!stat16 && !u.right ? p3 : 0);
     c.m3 = take(u.right ? p3 : 0), c.m3t = take(u.right ? 0 : p3);
@@ -937,7 +978,6 @@ Carve carve(int64_t rows, int64_t cols, int nb, Sides u, bool refresh, bool bf16
     c.ql3t = take(u.left ? l3 : 0), c.qr3t = take(u.right ? r3 : 0);
   }
   if (bf16) {
-    const bool both = u.left && u.right;
     c.mp = take(p2), c.mpt = take(p2);
     c.as_g = take(u.right ? p2 : 0), c.at_g = take(u.right ? p2 : 0), c.as_m = take(u.right ? p2 : 0), c.at_m = take(u.right ? p2 : 0);
     c.rg = take(u.left ? p2 : 0), c.rgt = take(u.left ? p2 : 0), c.rm = take(u.left ? p2 : 0), c.rmt = take(u.left ? p2 : 0);
@@ -946,22 +986,39 @@ Carve carve(int64_t rows, int64_t cols, int nb, Sides u, bool refresh, bool bf16
     c.qlp = take(u.left ? nb * rp2 * rp2 / 2 : 0), c.qltp = take(u.left ? nb * rp2 * rp2 / 2 : 0);
     c.qrp = take(u.right ? nb * cp2 * cp2 / 2 : 0), c.qrtp = take(u.right ? nb * cp2 * cp2 / 2 : 0);
   }
-  // Never less than the layout with rotations on the fp32 MFMA took (planes padded to 128, both orientations of the bases,
-  // the statistic): what callers measured once stays what they are asked for, wherever the arrays above fit it.
-  const bool both = u.left && u.right;
-  size_t before = (both ? 10 : 7) * nb * plane + (u.left ? 2 * nb * rp * rp : 0) + (u.right ? 2 * nb * cp * cp : 0) + nb * dm * dm;
-  if (refresh) before += nb * (4 * dm * dm + (4 * QBLK + QB) * dm + 3 * QBLK * QBLK) + align_up(nb * QB * sizeof(float)) / sizeof(float);
-  if (bf16 || stat16) before += (bf16 || u.left ? p2 : 0) + (bf16 || u.right ? p2 : 0);
-  if (bf16)
-    before += p2 * (4 + (u.right ? 4 : 0) + (u.left ? 4 : 0) + (both ? 2 : 0)) + (u.left ? nb * rp2 * rp2 : 0) + (u.right ? nb * cp2 * cp2 : 0);
-  c.total_bytes = std::max(off, before) * sizeof(float);
+  c.total_bytes = off * sizeof(float);
   return c;
 }
 
-int batch_cap(const canz_soap_group& g, const canz_soap_hparams& hp) {
-  const size_t one = carve(g.rows, g.cols, 1, sides(g, hp), hp.refresh != 0, hp.bf16_rotations != 0, bf16_statistics(g)).total_bytes;
-  const int64_t by_bytes = std::max<int64_t>(1, static_cast<int64_t>(BATCH_BYTES / one));
-  return static_cast<int>(std::min<int64_t>(MAX_PTRS / g.tp, by_bytes));
+size_t batch_bytes(const canz_soap_group& g, const canz_soap_hparams& hp, int nb, Rot rot) {
+  return carve(g.rows, g.cols, nb, sides(g, hp), hp.refresh != 0, rot, bf16_statistics(g)).total_bytes;
+}
+// matrices per batch: what the pointer tables and the batch memory hold, at least one
+int batch_cap(const canz_soap_group& g, const canz_soap_hparams& hp, Rot rot) {
+  const int64_t by_bytes = std::max<int64_t>(1, static_cast<int64_t>(BATCH_BYTES / batch_bytes(g, hp, 1, rot)));
+  return static_cast<int>(std::min<int64_t>({MAX_PTRS / g.tp, by_bytes, std::max<int64_t>(1, g.n_mats)}));
+}
+// The rotations in fp32 accuracy run on three bf16 terms, except up to 128 x 128, where fp32 matrices padded to 128 are
+// faster than terms padded to 256 (8 x 128 x 128: 111 us against 122 with bf16 gradients, 133 against 160 with fp32 ones; from
+// 129 rows or columns on terms win, 4 x 300 x 384 with fp32 gradients 268 us against 286).
+// Terms can need more scratch than fp32 matrices do (where 256 is a poor padding): canz_soap_workspace_bytes asks for enough;
+// whatever suffices for fp32 matrices is accepted, and then the batches are smaller, or if not even one matrix fits, the
+// rotations run on fp32 matrices.
+struct Plan {
+  Rot rot;
+  int nb;
+};
+Plan plan_of(const canz_soap_group& g, const canz_soap_hparams& hp, size_t have) {
+  if (hp.bf16_rotations) return {Rot::BF16, batch_cap(g, hp, Rot::BF16)};
+  if (g.rows <= SB && g.cols <= SB) return {Rot::F32, batch_cap(g, hp, Rot::F32)};
+  const int nb = batch_cap(g, hp, Rot::TERMS);
+  if (batch_bytes(g, hp, nb, Rot::TERMS) <= have) return {Rot::TERMS, nb};
+  if (const size_t one = batch_bytes(g, hp, 1, Rot::TERMS); one <= have) return {Rot::TERMS, std::min(nb, static_cast<int>(have / one))};
+  return {Rot::F32, batch_cap(g, hp, Rot::F32)};
+}
+size_t least_bytes(const canz_soap_group& g, const canz_soap_hparams& hp) {
+  const Rot rot = hp.bf16_rotations ? Rot::BF16 : Rot::F32;
+  return batch_bytes(g, hp, batch_cap(g, hp, rot), rot);
 }
 
 int check_hparams(const canz_soap_hparams* hp) {
@@ -1138,12 +1195,12 @@ int refresh_side(void* const* q_tab, int first, int nb, int64_t d, int64_t dp, c
 }
 
 // One launch batch: matrices first .. first + nb - 1 of group g.
-int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hparams& hp, float* ws, hipStream_t st) {
+int run_batch(const canz_soap_group& g, int first, int nb, Rot rot, const canz_soap_hparams& hp, float* ws, hipStream_t st) {
   const int64_t rp = pad128(g.rows), cp = pad128(g.cols), plane = rp * cp;
   const Sides u = sides(g, hp);
-  const bool bf16 = hp.bf16_rotations != 0;
+  const bool bf16 = rot == Rot::BF16, terms3 = rot == Rot::TERMS, f32 = rot == Rot::F32;
   const bool stat16 = bf16_statistics(g);
-  const Carve c = carve(g.rows, g.cols, nb, u, hp.refresh != 0, bf16, stat16);
+  const Carve c = carve(g.rows, g.cols, nb, u, hp.refresh != 0, rot, stat16);
   Shape s{};
   s.rows = g.rows, s.cols = g.cols;
   s.m = std::min(g.rows, g.cols), s.n = std::max(g.rows, g.cols);
@@ -1151,7 +1208,7 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
   s.tall = g.rows > g.cols;
   s.tp = g.tp;
   s.wfrag = g.cols / g.tp;
-  PtrTable grad{}, mom{}, var{};
+  PtrTable grad{}, mom{}, var{}, none{};
   for (int i = 0; i < nb * g.tp; ++i) grad.p[i] = const_cast<void*>(g.grad[first * g.tp + i]);
   for (int i = 0; i < nb; ++i) mom.p[i] = g.mom[first + i], var.p[i] = g.var[first + i];
   OutSpec o{};
@@ -1172,19 +1229,23 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
   const int64_t rp2 = pad256(g.rows), cp2 = pad256(g.cols), p2 = rp2 * cp2;
   const SplitWs no_split{nullptr, 0};
   auto pan = [&](size_t at) { return reinterpret_cast<__bf16*>(ws + at); };
+  const int64_t g_stride = f32 ? 2 * plane : plane;   // from one matrix's fp32 copy of G to the next
 
   prof_mark(st, CANZ_KERNEL_SOAP_LOAD, true);
   {
-    // fp32 copies: G for the fp32 statistics; bf16 images: G for the bf16 statistics and for either kind of rotation if it
+    // fp32 copies: G for the fp32 statistics, G and M side by side for rotations on fp32 matrices; bf16 images: G for the bf16 statistics and for either kind of rotation if it
     // arrives as bf16, M for the bf16 rotations of a step that rotates it (also the re-rotation of a kept M' after a
     // refresh); three terms: G that is fp32 and M for the fp32 rotations, in the orientation of the first product
     LoadOut w{};
-    if (!stat16) w.gm = gm, w.gmt = gmt;
+    if (f32 || !stat16) w.gm = gm, w.gmt = gmt;
+    if (f32) w.mm = gm + plane, w.mmt = gmt + plane;
+    w.stride = g_stride;
     const bool rotate_m = !incremental || (hp.refresh && g.mom_rot != nullptr);
-    if (!bf16 && !stat16) (u.right ? w.g3 : w.g3t) = pan(u.right ? c.g3 : c.g3t);
-    if (!bf16 && rotate_m) (u.right ? w.m3 : w.m3t) = pan(u.right ? c.m3 : c.m3t);
+    if (terms3 && !stat16) (u.right ? w.g3 : w.g3t) = pan(u.right ? c.g3 : c.g3t);
+    if (terms3 && rotate_m) (u.right ? w.m3 : w.m3t) = pan(u.right ? c.m3 : c.m3t);
     w.rp2 = rp2, w.cp2 = cp2;
-    if (bf16 || stat16) w.gp = pan(c.gp), w.gpt = pan(c.gpt);
+    if (bf16 || (stat16 && (terms3 || u.left))) w.gp = pan(c.gp);
+    if (bf16 || (stat16 && (terms3 || u.right))) w.gpt = pan(c.gpt);
     if (bf16 && rotate_m) w.mp = pan(c.mp), w.mpt = pan(c.mpt);
     const dim3 grid(static_cast<unsigned>(cp2 / 64), static_cast<unsigned>(rp2 / 64), static_cast<unsigned>(nb));
     if (g.cols % 8 == 0 && s.wfrag % 8 == 0)
@@ -1192,7 +1253,7 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
     else
       hipLaunchKernelGGL(k_soap_load<false>, grid, dim3(NTH), 0, st, s, grad, g.grad_dtype, mom, hp.beta1, rp, cp, w);
   }
-  // the bases, zero outside d x d: three terms for the fp32 rotations, bf16 images for the bf16 rotations, both in both
+  // the bases, zero outside d x d: three terms, fp32 copies or bf16 images for the three kinds of rotations, in both
   // orientations; later, fp32 and transposed, for the refresh (which multiplies the new statistic with the old basis)
   auto load_basis = [&](void* const* tab, int64_t d, int64_t dp, int64_t dp2, BasisOut w) {
     PtrTable q{};
@@ -1200,11 +1261,15 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
     const unsigned side = static_cast<unsigned>(dp2 / 64);
     hipLaunchKernelGGL(k_soap_load_basis, dim3(side, side, static_cast<unsigned>(nb)), dim3(NTH), 0, st, q, d, dp, dp2, w);
   };
-  auto basis_out = [&](size_t sp, size_t tp, size_t s3, size_t t3) {
-    return bf16 ? BasisOut{nullptr, pan(sp), pan(tp), nullptr, nullptr} : BasisOut{nullptr, nullptr, nullptr, pan(s3), pan(t3)};
+  auto basis_out = [&](size_t s32, size_t t32, size_t sp, size_t tp, size_t s3, size_t t3) {
+    BasisOut w{};
+    if (f32) w.s32 = ws + s32, w.t32 = ws + t32;
+    if (bf16) w.sp = pan(sp), w.tp = pan(tp);
+    if (terms3) w.s3 = pan(s3), w.t3 = pan(t3);
+    return w;
   };
-  if (u.left) load_basis(g.qleft, g.rows, rp, rp2, basis_out(c.qlp, c.qltp, c.ql3, c.ql3t));
-  if (u.right) load_basis(g.qright, g.cols, cp, cp2, basis_out(c.qrp, c.qrtp, c.qr3, c.qr3t));
+  if (u.left) load_basis(g.qleft, g.rows, rp, f32 ? rp : rp2, basis_out(c.ql, c.qlt, c.qlp, c.qltp, c.ql3, c.ql3t));
+  if (u.right) load_basis(g.qright, g.cols, cp, f32 ? cp : cp2, basis_out(c.qr, c.qrt, c.qrp, c.qrtp, c.qr3, c.qr3t));
   prof_mark(st, CANZ_KERNEL_SOAP_LOAD, false);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "load kernels: %s", hipGetErrorString(e));
 
@@ -1235,11 +1300,50 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
              "rotation (left)");
     return CANZ_OK;
   };
+  // On fp32 matrices (plan_of): rotation into the bases of `per` planes of each matrix's (G, M) pair, from plane `p0` on: problem p is
+  // plane p0 + p % per of matrix p / per; consecutive problems of a matrix share the basis operand
+  float *t1 = ws + c.t1, *rot32 = ws + c.rot, *ql = ws + c.ql, *qlt = ws + c.qlt, *qr = ws + c.qr, *qrt = ws + c.qrt;
+  auto rotate_in32 = [&](int p0, int per) -> int {
+    const int64_t step_ = per == 2 ? plane : 2 * plane, at = p0 * plane;
+    const int count = per * nb;
+    if (u.left && u.right) {
+      ShGemm a{};   // t1 = (X Q_R)^T: [cp][rp]
+      a.M = cp, a.N = rp, a.K = cp, a.ldp = cp, a.ldq = cp, a.sp = cp * cp, a.pdiv = per, a.sq = step_;
+      a.P = qrt, a.Q = gm + at, a.c = t1 + at, a.ldc = rp, a.sc = step_;
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false>(a, count, none, s, o, st)), "rotation (right)");
+      ShGemm bq{};  // rot32 = Q_L^T (X Q_R): [rp][cp]
+      bq.M = rp, bq.N = cp, bq.K = rp, bq.ldp = rp, bq.ldq = rp, bq.sp = rp * rp, bq.pdiv = per, bq.sq = step_;
+      bq.P = qlt, bq.Q = t1 + at, bq.c = rot32 + at, bq.ldc = cp, bq.sc = step_;
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false>(bq, count, none, s, o, st)), "rotation (left)");
+    } else if (u.left) {
+      ShGemm bq{};  // rot32 = Q_L^T X with X^T as the second operand
+      bq.M = rp, bq.N = cp, bq.K = rp, bq.ldp = rp, bq.ldq = rp, bq.sp = rp * rp, bq.pdiv = per, bq.sq = step_;
+      bq.P = qlt, bq.Q = gmt + at, bq.c = rot32 + at, bq.ldc = cp, bq.sc = step_;
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false>(bq, count, none, s, o, st)), "rotation (left)");
+    } else {
+      ShGemm a{};   // rot32 = X Q_R
+      a.M = rp, a.N = cp, a.K = cp, a.ldp = cp, a.ldq = cp, a.sp = step_, a.sq = cp * cp, a.qdiv = per;
+      a.P = gm + at, a.Q = qrt, a.c = rot32 + at, a.ldc = cp, a.sc = step_;
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false>(a, count, none, s, o, st)), "rotation (right)");
+    }
+    return CANZ_OK;
+  };
   PtrTable mrot{};
   if (g.mom_rot)
     for (int i = 0; i < nb; ++i) mrot.p[i] = g.mom_rot[first + i];
   const double c1 = hp.bias_correction ? 1.0 / (1.0 - std::pow(static_cast<double>(hp.beta1), hp.step)) : 1.0;
   const double c2 = hp.bias_correction ? 1.0 / (1.0 - std::pow(static_cast<double>(hp.beta2), hp.step)) : 1.0;
+
+  const int want_transposed = u.left && !u.right;   // the left side alone takes N'^T as its second operand
+  const dim3 tiles2(static_cast<unsigned>(cp2 / 64), static_cast<unsigned>(rp2 / 64), static_cast<unsigned>(nb));
+  auto adam = [&](const float* g_rot, const float* m_rot, int64_t ld, int64_t stride, __bf16* n3, float* n32) -> int {
+    prof_mark(st, CANZ_KERNEL_SOAP_ADAM, true);
+    hipLaunchKernelGGL(k_soap_adam, tiles2, dim3(NTH), 0, st, s, var, mrot, g.mom_rot != nullptr, incremental, g_rot, m_rot, ld, stride, rp2,
+                       cp2, hp.beta1, hp.beta2, static_cast<float>(c1), static_cast<float>(c2), hp.eps, want_transposed, n3, n32);
+    prof_mark(st, CANZ_KERNEL_SOAP_ADAM, false);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "adam kernel: %s", hipGetErrorString(e));
+    return CANZ_OK;
+  };
 
   // shapes of the bf16 rotation products (first operand: a basis)
   const GemmDims right_dims{cp2, rp2, cp2, cp2, cp2, cp2 * cp2, p2, nb};   // (basis rows) x (matrix rows), k over columns
@@ -1267,12 +1371,10 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
     if (int rc = rotate_in16(pan(c.gp), pan(c.gpt), c.as_g, c.at_g, c.rg, c.rgt, &g_rot)) return rc;
     if (!incremental)
       if (int rc = rotate_in16(pan(c.mp), pan(c.mpt), c.as_m, c.at_m, c.rm, c.rmt, &m_rot)) return rc;
-    const bool want_t = u.left && !u.right;   // the left side alone takes N'^T as its second operand
-    const dim3 tiles2(static_cast<unsigned>(cp2 / 64), static_cast<unsigned>(rp2 / 64), static_cast<unsigned>(nb));
     prof_mark(st, CANZ_KERNEL_SOAP_ADAM, true);
     hipLaunchKernelGGL(k_soap_adam_bf16, tiles2, dim3(NTH), 0, st, s, var, mrot, g.mom_rot != nullptr, incremental, g_rot, m_rot,
                        rp2, cp2, hp.beta1, hp.beta2, static_cast<float>(c1), static_cast<float>(c2), hp.eps,
-                       want_t ? nullptr : pan(c.npn), want_t ? pan(c.npt) : nullptr);
+                       want_transposed ? nullptr : pan(c.npn), want_transposed ? pan(c.npt) : nullptr);
     prof_mark(st, CANZ_KERNEL_SOAP_ADAM, false);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "adam kernel: %s", hipGetErrorString(e));
     if (u.left && u.right) {
@@ -1289,6 +1391,31 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
       CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, launch_final_bf16(d, pan(c.npn), pan(c.qrp), nullptr, no_split, s, o, st),
                "back rotation (right, bf16)");
     }
+  } else if (f32) {
+    float *np = ws + c.np, *yt = ws + c.yt;
+    if (int rc = rotate_in32(0, incremental ? 1 : 2)) return rc;
+    if (int rc = adam(rot32, rot32 + plane, cp, 2 * plane, nullptr, np)) return rc;
+    // rotation back, the last product writes the update
+    if (u.left && u.right) {
+      ShGemm cq{};  // yt = (N' Q_R^T)^T: [cp][rp]
+      cq.M = cp, cq.N = rp, cq.K = cp, cq.ldp = cp, cq.ldq = cp, cq.sp = cp * cp, cq.sq = plane;
+      cq.P = qr, cq.Q = np, cq.c = yt;
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false>(cq, nb, none, s, o, st)), "back rotation (right)");
+      ShGemm dq{};
+      dq.M = rp, dq.N = cp, dq.K = rp, dq.ldp = rp, dq.ldq = rp, dq.sp = rp * rp, dq.sq = plane;
+      dq.P = ql, dq.Q = yt;
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_OUT, false>(dq, nb, none, s, o, st)), "back rotation (left)");
+    } else if (u.left) {
+      ShGemm dq{};  // np holds N'^T
+      dq.M = rp, dq.N = cp, dq.K = rp, dq.ldp = rp, dq.ldq = rp, dq.sp = rp * rp, dq.sq = plane;
+      dq.P = ql, dq.Q = np;
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_OUT, false>(dq, nb, none, s, o, st)), "back rotation (left)");
+    } else {
+      ShGemm cq{};
+      cq.M = rp, cq.N = cp, cq.K = cp, cq.ldp = cp, cq.ldq = cp, cq.sp = plane, cq.sq = cp * cp;
+      cq.P = np, cq.Q = qr;
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_OUT, false>(cq, nb, none, s, o, st)), "back rotation (right)");
+    }
   } else {
     auto dense = [&](size_t at) {   // the batch's dense rows x cols matrices in the workspace
       PtrTable t{};
@@ -1299,13 +1426,7 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
     if (int rc = rotate_in(gx, stat16 ? 1 : 3, dense(c.rotg))) return rc;
     if (!incremental)
       if (int rc = rotate_in(pan(u.right ? c.m3 : c.m3t), 3, dense(c.rotm))) return rc;
-    const int transposed = u.left && !u.right;   // the left side alone takes N'^T as its second operand
-    const dim3 tiles2(static_cast<unsigned>(cp2 / 64), static_cast<unsigned>(rp2 / 64), static_cast<unsigned>(nb));
-    prof_mark(st, CANZ_KERNEL_SOAP_ADAM, true);
-    hipLaunchKernelGGL(k_soap_adam, tiles2, dim3(NTH), 0, st, s, var, mrot, g.mom_rot != nullptr, incremental, ws + c.rotg, ws + c.rotm,
-                       dense_stride(g.rows, g.cols), rp2, cp2, hp.beta1, hp.beta2, static_cast<float>(c1), static_cast<float>(c2), hp.eps, transposed, pan(c.n3));
-    prof_mark(st, CANZ_KERNEL_SOAP_ADAM, false);
-    if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "adam kernel: %s", hipGetErrorString(e));
+    if (int rc = adam(ws + c.rotg, ws + c.rotm, g.cols, dense_stride(g.rows, g.cols), pan(c.n3), nullptr)) return rc;
 
     // rotation back, the last product writes the update
     if (!u.left) {
@@ -1341,14 +1462,14 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
       }
     } else {
       ShGemm q{};
-      q.M = dp, q.N = dp, q.K = kp, q.ldp = kp, q.ldq = kp, q.sp = plane, q.sq = plane;
+      q.M = dp, q.N = dp, q.K = kp, q.ldp = kp, q.ldq = kp, q.sp = g_stride, q.sq = g_stride;
       q.P = side, q.Q = side, q.c = hp.refresh ? stat : nullptr, q.d = d, q.beta = hp.beta2, q.gscale = 1.f - hp.beta2, q.eps = 0.f;
       CANZ_HIP(CANZ_KERNEL_SOAP_STAT, (launch_gemm<SE_STAT, true>(q, nb, tab, s, o, st)), "statistics kernel");
     }
     if (!hp.refresh) return CANZ_OK;
     float* qt_old = ws + c.vall;   // read by the refresh's first product, before any reflector is written there
     prof_mark(st, CANZ_KERNEL_SOAP_LOAD, true);
-    load_basis(q_tab, d, dp, dp, BasisOut{qt_old, nullptr, nullptr, nullptr, nullptr});
+    load_basis(q_tab, d, dp, dp, BasisOut{nullptr, qt_old, nullptr, nullptr, nullptr, nullptr});
     prof_mark(st, CANZ_KERNEL_SOAP_LOAD, false);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "basis load: %s", hipGetErrorString(e));
     return refresh_side(q_tab, first, nb, d, dp, stat, qt_old, ws, c, s, o, st);
@@ -1361,8 +1482,8 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
     // the caller's rotated momentum follows the new bases, M' = Q_L^T M Q_R once more with the M of this step: bf16
     // operands as for every rotation of this mode; the last product leaves its fp32 sums in the caller's array
     prof_mark(st, CANZ_KERNEL_SOAP_LOAD, true);
-    if (u.left) load_basis(g.qleft, g.rows, rp, rp2, BasisOut{nullptr, nullptr, pan(c.qltp), nullptr, nullptr});
-    if (u.right) load_basis(g.qright, g.cols, cp, cp2, BasisOut{nullptr, nullptr, pan(c.qrtp), nullptr, nullptr});
+    if (u.left) load_basis(g.qleft, g.rows, rp, rp2, BasisOut{nullptr, nullptr, nullptr, pan(c.qltp), nullptr, nullptr});
+    if (u.right) load_basis(g.qright, g.cols, cp, cp2, BasisOut{nullptr, nullptr, nullptr, pan(c.qrtp), nullptr, nullptr});
     prof_mark(st, CANZ_KERNEL_SOAP_LOAD, false);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "basis load: %s", hipGetErrorString(e));
     Shape whole = s;
@@ -1383,11 +1504,23 @@ int run_batch(const canz_soap_group& g, int first, int nb, const canz_soap_hpara
       CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, launch_final_bf16(d, pan(c.mp), pan(c.qrtp), nullptr, no_split, whole, mo, st),
                "momentum re-rotation (right, bf16)");
     }
-  } else if (hp.refresh && g.mom_rot) {
-    // the same with the fp32 rotations
+  } else if (hp.refresh && g.mom_rot && f32) {
+    // the same on fp32 matrices
     prof_mark(st, CANZ_KERNEL_SOAP_LOAD, true);
-    if (u.left) load_basis(g.qleft, g.rows, rp, rp2, BasisOut{nullptr, nullptr, nullptr, nullptr, pan(c.ql3t)});
-    if (u.right) load_basis(g.qright, g.cols, cp, cp2, BasisOut{nullptr, nullptr, nullptr, nullptr, pan(c.qr3t)});
+    if (u.left) load_basis(g.qleft, g.rows, rp, rp, BasisOut{nullptr, qlt, nullptr, nullptr, nullptr, nullptr});
+    if (u.right) load_basis(g.qright, g.cols, cp, cp, BasisOut{nullptr, qrt, nullptr, nullptr, nullptr, nullptr});
+    prof_mark(st, CANZ_KERNEL_SOAP_LOAD, false);
+    if (int rc = rotate_in32(1, 1)) return rc;
+    prof_mark(st, CANZ_KERNEL_SOAP_ADAM, true);
+    hipLaunchKernelGGL(k_unpad, dim3(static_cast<unsigned>(cp / 64), static_cast<unsigned>(rp / 64), static_cast<unsigned>(nb)), dim3(NTH), 0, st,
+                       s, mrot, rot32 + plane, 2 * plane, cp);
+    prof_mark(st, CANZ_KERNEL_SOAP_ADAM, false);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "momentum re-rotation: %s", hipGetErrorString(e));
+  } else if (hp.refresh && g.mom_rot) {
+    // the same on three terms
+    prof_mark(st, CANZ_KERNEL_SOAP_LOAD, true);
+    if (u.left) load_basis(g.qleft, g.rows, rp, rp2, BasisOut{nullptr, nullptr, nullptr, nullptr, nullptr, pan(c.ql3t)});
+    if (u.right) load_basis(g.qright, g.cols, cp, cp2, BasisOut{nullptr, nullptr, nullptr, nullptr, nullptr, pan(c.qr3t)});
     prof_mark(st, CANZ_KERNEL_SOAP_LOAD, false);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "basis load: %s", hipGetErrorString(e));
     if (int rc = rotate_in(pan(u.right ? c.m3 : c.m3t), 3, mrot)) return rc;
@@ -1468,9 +1601,10 @@ extern "C" int canz_soap_workspace_bytes(const canz_soap_group* g, int32_t n_gro
   size_t need = ALIGN;
   for (int i = 0; i < n_groups; ++i)
     if (int rc = check_group(g[i], i, false, *hp)) return rc;
-  for (const MergedGroup& m : merge_groups(g, n_groups, *hp))
-    need = std::max(need, carve(m.g.rows, m.g.cols, std::min(m.g.n_mats, batch_cap(m.g, *hp)), sides(m.g, *hp), hp->refresh != 0,
-                                hp->bf16_rotations != 0, bf16_statistics(m.g)).total_bytes);
+  for (const MergedGroup& m : merge_groups(g, n_groups, *hp)) {
+    const Plan p = plan_of(m.g, *hp, SIZE_MAX);
+    need = std::max({need, batch_bytes(m.g, *hp, p.nb, p.rot), least_bytes(m.g, *hp)});
+  }
   *bytes_out = need;
   return CANZ_OK;
 }
@@ -1478,7 +1612,7 @@ extern "C" int canz_soap_workspace_bytes(const canz_soap_group* g, int32_t n_gro
 extern "C" int canz_soap_step(const canz_soap_group* g, int32_t n_groups, const canz_soap_hparams* hp, void* workspace,
                               size_t workspace_bytes, void* hip_stream) {
   using namespace canz;
-  size_t need = 0;
+  size_t need = 0;   // of the fastest way; checks the arguments
   if (int rc = canz_soap_workspace_bytes(g, n_groups, hp, &need)) return rc;
   bool any = false;
   for (int i = 0; i < n_groups; ++i) {
@@ -1488,13 +1622,15 @@ extern "C" int canz_soap_step(const canz_soap_group* g, int32_t n_groups, const 
   if (!any) return CANZ_OK;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & (ALIGN - 1)))
     return fail(CANZ_EWORKSPACE, "workspace null or not 256-byte aligned");
-  if (workspace_bytes < need)
-    return fail(CANZ_EWORKSPACE, "workspace too small: %zu bytes given, %zu needed", workspace_bytes, need);
+  const std::vector<MergedGroup> merged = merge_groups(g, n_groups, *hp);
+  for (const MergedGroup& m : merged)
+    if (workspace_bytes < least_bytes(m.g, *hp))
+      return fail(CANZ_EWORKSPACE, "workspace too small: %zu bytes given, %zu needed", workspace_bytes, need);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  for (const MergedGroup& m : merge_groups(g, n_groups, *hp)) {
-    const int cap = batch_cap(m.g, *hp);
-    for (int first = 0; first < m.g.n_mats; first += cap)
-      if (int rc = run_batch(m.g, first, std::min(cap, m.g.n_mats - first), *hp, static_cast<float*>(workspace), st)) return rc;
+  for (const MergedGroup& m : merged) {
+    const Plan p = plan_of(m.g, *hp, workspace_bytes);
+    for (int first = 0; first < m.g.n_mats; first += p.nb)
+      if (int rc = run_batch(m.g, first, std::min(p.nb, m.g.n_mats - first), p.rot, *hp, static_cast<float*>(workspace), st)) return rc;
   }
   return CANZ_OK;
 }

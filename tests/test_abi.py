@@ -197,3 +197,30 @@ def test_shampoo_workspace_for_every_shape(canz):
                                                             canz.ShampooHparams())
                     assert least <= got <= max(5.5 * least if dm <= 128 else 2.4 * least, 256), (rows, cols, n)
                     assert got <= max(8 << 30, 1.01 * one), (rows, cols, n)
+
+
+def test_soap_workspace_for_every_shape(canz):
+    """What is asked for: never less than the documented size of fp32 matrices padded to 128 (which the step accepts), at most
+    2.6 times that (padding to 256 where 128 would do), and in batches of about 32 GB."""
+    pad = lambda x: (x + 127) // 128 * 128  # noqa: E731
+    pad2 = lambda x: (x + 255) // 256 * 256  # noqa: E731
+    extents = [1, 96, 128, 129, 256, 257, 300, 384, 400, 500, 640, 700, 896, 1000, 1024, 1300, 2048, 3000, 8192]
+    for dtype in (canz.DT_BF16, canz.DT_F32):
+        for rows in extents:
+            for cols in extents:
+                for limit in (10000, 700):
+                    left, right = rows <= limit, cols <= limit
+                    if not (left or right):
+                        continue
+                    rp, cp = pad(rows), pad(cols)
+                    one = (10 if left and right else 7) * rp * cp + left * 2 * rp * rp + right * 2 * cp * cp
+                    one += max(left * rp, right * cp) ** 2
+                    if dtype == canz.DT_BF16:
+                        one += (left + right) * pad2(rows) * pad2(cols) // 2
+                    one *= 4
+                    for n in (1, 3, 64):
+                        least = one * max(1, min(n, (32 << 30) // one))
+                        got = canz.canz_soap_workspace_bytes([canz.SoapGroup(rows=rows, cols=cols, n_mats=n, grad_dtype=dtype)],
+                                                             canz.SoapHparams(max_precond_dim=limit))
+                        assert least <= got <= 2.6 * least, (rows, cols, limit, n)
+                        assert got <= max(32 << 30, 1.01 * one), (rows, cols, n)

@@ -14,7 +14,23 @@ def canz():
     return binding
 
 
-def _step(torch, canz, rows, cols, n, limit, grad_dtype, keep, valid, refresh, level):
+GUARD = 1 << 16   # bytes behind the workspace that must stay as they are
+
+
+def _least_bytes(rows, cols, n, limit, bf16, refresh):
+    """What fp32 matrices padded to 128 take (the documented least workspace)."""
+    pad, pad2 = (lambda x: (x + 127) // 128 * 128), (lambda x: (x + 255) // 256 * 256)
+    left, right, rp, cp = rows <= limit, cols <= limit, pad(rows), pad(cols)
+    dm = max(left * rp, right * cp)
+    one = (10 if left and right else 7) * rp * cp + left * 2 * rp * rp + right * 2 * cp * cp + dm * dm
+    if bf16:
+        one += (left + right) * pad2(rows) * pad2(cols) // 2
+    if refresh:
+        one += 4 * dm * dm + (128 + 2 * 128 + 32 + 128) * dm + 3 * 128 * 128
+    return 4 * one * n + (refresh and (n * 32 * 4 + 255) // 256 * 256)
+
+
+def _step(torch, canz, rows, cols, n, limit, grad_dtype, keep, valid, refresh, level, least=False):
     """One step from seeded state; (state before, state after) as dicts of tensor lists."""
     g = torch.Generator(device="cuda").manual_seed(rows * 10007 + cols)
     draw = lambda r, c: torch.randn(r, c, generator=g, device="cuda") * level  # noqa: E731
@@ -32,9 +48,12 @@ def _step(torch, canz, rows, cols, n, limit, grad_dtype, keep, valid, refresh, l
     hp = canz.SoapHparams(beta1=0.75, beta2=0.5, lr=1.0, eps=1e-3 * level, step=5, refresh=int(refresh), mom_rot_valid=int(valid),
                           max_precond_dim=limit, bias_correction=0, out_mode=canz.OUT_DELTA)
     need = canz.canz_soap_workspace_bytes([grp], hp)
-    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")   # every byte a NaN: nothing may be read unwritten
+    if least:
+        need = _least_bytes(rows, cols, n, limit, grad_dtype == torch.bfloat16, refresh)
+    ws = torch.full((need + GUARD,), 0xFF, dtype=torch.uint8, device="cuda")   # every byte a NaN: nothing may be read unwritten
     canz.canz_soap_step([grp], hp, ws, need, torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
+    assert bool((ws[need:] == 0xFF).all())
     return before, st
 
 
@@ -61,6 +80,10 @@ def _rotate(q_left, q_right, x):
 def test_rotations_against_64_bits(canz, rows, cols, n, limit, bf16, keep, valid, refresh, level):
     import torch
     was, now = _step(torch, canz, rows, cols, n, limit, torch.bfloat16 if bf16 else torch.float32, keep, valid, refresh, level)
+    _check(was, now, n, keep, valid, refresh, level)
+
+
+def _check(was, now, n, keep, valid, refresh, level):
     rel = lambda got, want: float((got.double() - want).norm() / want.norm())  # noqa: E731
     pick = lambda t, i: t[i] if t else None  # noqa: E731
     for i in range(n):
@@ -79,3 +102,18 @@ def test_rotations_against_64_bits(canz, rows, cols, n, limit, bf16, keep, valid
             if refresh:   # the kept momentum follows the new bases
                 m_rot = _rotate(pick(now["qleft"], i), pick(now["qright"], i), now["mom"][i])
             assert rel(now["mom_rot"][i], m_rot) <= 5e-7
+
+
+@pytest.mark.parametrize("rows,cols,n,limit,bf16,keep,valid,refresh", [
+    (300, 380, 1, 4096, True, True, True, False),     # 256 is 1.8 times 128: not even one matrix of terms fits
+    (300, 380, 1, 4096, False, False, False, False),
+    (380, 290, 1, 4096, False, True, False, True),    # ... with a refresh and the kept momentum rotated again
+    (600, 380, 2, 400, False, True, True, True),      # right side only
+    (380, 600, 1, 400, True, False, False, False),    # left side only
+    (900, 850, 4, 4096, False, True, True, False),    # fits, in smaller batches
+    (128, 100, 3, 4096, True, True, True, True),      # fp32 matrices are what is asked for
+])
+def test_least_workspace(canz, rows, cols, n, limit, bf16, keep, valid, refresh):
+    import torch
+    was, now = _step(torch, canz, rows, cols, n, limit, torch.bfloat16 if bf16 else torch.float32, keep, valid, refresh, 1.0, least=True)
+    _check(was, now, n, keep, valid, refresh, 1.0)
