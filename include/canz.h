@@ -356,6 +356,8 @@ int canz_shampoo_step(const canz_shampoo_group* g, int32_t n_groups, const canz_
  * sums in mom_rot.  Momentum, second moment, the statistics' sums and the refresh stay in fp32.  Independently
  * of this switch, gradients that arrive as bf16 have their statistics G G^T and G^T G computed on the bf16 matrix
  * cores: their values are the exact operands, each product is exact in fp32 and the sums are kept in fp32.
+ * An element of G that is not finite makes every element of V, M' and the update that depends on it infinite or NaN (as a
+ * rule NaN), the statistics' elements likewise; other matrices of the call are not touched.
  * The caller owns all state and decides when to refresh (every f-th step) and how the bases
  * start (identity, or eigenvectors of the first statistics computed elsewhere).  The QR step is
  * a blocked Householder factorisation: the basis it writes is orthonormal to fp32 rounding and

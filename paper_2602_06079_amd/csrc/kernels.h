@@ -156,7 +156,8 @@ hipError_t launch_final_sym_bf16(const GemmDims& d, const void* x, const SplitWs
 // of elements of any ratio keep the accuracy they have in fp32.  The products of the terms are exact in fp32 and are
 // added up in fp32, the small ones first, K / 16 roundings per product where the fp32 MFMA rounds K / 2 times.  Six products
 // (those left out are at most 2^-26 of the result), three if one operand is a matrix of bf16 values, i.e. of one term.
-// An infinity in an operand gives NaN where the fp32 product would give an infinity.
+// An infinity in an operand (or a value above 3.39e38, which bf16 rounds to one) gives NaN where the fp32 product would
+// give an infinity or NaN: it is inf - inf in the terms, and inf * 0 against terms that are zero.
 // C = P Q^T, P [nb][M][3 K], Q [nb][N][qterms K]:
 //   c [nb][M][3 N], the result as three terms
 hipError_t launch_split3(const GemmDims& d, const void* p, const void* q, void* c, hipStream_t st);

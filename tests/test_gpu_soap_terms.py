@@ -30,7 +30,7 @@ def _least_bytes(rows, cols, n, limit, bf16, refresh):
     return 4 * one * n + (refresh and (n * 32 * 4 + 255) // 256 * 256)
 
 
-def _step(torch, canz, rows, cols, n, limit, grad_dtype, keep, valid, refresh, level, least=False):
+def _step(torch, canz, rows, cols, n, limit, grad_dtype, keep, valid, refresh, level, least=False, spoil=None):
     """One step from seeded state; (state before, state after) as dicts of tensor lists."""
     g = torch.Generator(device="cuda").manual_seed(rows * 10007 + cols)
     draw = lambda r, c: torch.randn(r, c, generator=g, device="cuda") * level  # noqa: E731
@@ -43,6 +43,8 @@ def _step(torch, canz, rows, cols, n, limit, grad_dtype, keep, valid, refresh, l
               qleft=[basis(rows) for _ in range(n)] if left else [], qright=[basis(cols) for _ in range(n)] if right else [],
               out=[torch.zeros(rows, cols, device="cuda") for _ in range(n)],
               mom_rot=[draw(rows, cols) for _ in range(n)] if keep else [])
+    if spoil is not None:
+        st["grad"][0][spoil[0], spoil[1]] = spoil[2]
     before = {k: [t.clone() for t in v] for k, v in st.items()}
     grp = canz.SoapGroup(rows=rows, cols=cols, grad_dtype=canz.DT_BF16 if grad_dtype == torch.bfloat16 else canz.DT_F32, **st)
     hp = canz.SoapHparams(beta1=0.75, beta2=0.5, lr=1.0, eps=1e-3 * level, step=5, refresh=int(refresh), mom_rot_valid=int(valid),
@@ -117,3 +119,22 @@ def test_least_workspace(canz, rows, cols, n, limit, bf16, keep, valid, refresh)
     import torch
     was, now = _step(torch, canz, rows, cols, n, limit, torch.bfloat16 if bf16 else torch.float32, keep, valid, refresh, 1.0, least=True)
     _check(was, now, n, keep, valid, refresh, 1.0)
+
+
+@pytest.mark.parametrize("rows,cols,bf16,limit", [(300, 520, True, 4096), (300, 520, False, 4096), (300, 520, False, 400), (520, 301, False, 400)])
+def test_infinite_gradient_element(canz, rows, cols, bf16, limit):
+    """An infinity spreads to exactly the elements that depend on it, as NaN or infinity, and to no other matrix."""
+    import torch
+    was, now = _step(torch, canz, rows, cols, 2, limit, torch.bfloat16 if bf16 else torch.float32, True, False, False, 1.0,
+                     spoil=(7, 11, float("inf")))
+    touched = torch.ones(rows, cols, dtype=torch.bool, device="cuda")
+    if rows > limit:     # the right side alone: the element's row
+        touched[:7] = touched[8:] = False
+    elif cols > limit:   # the left side alone: its column
+        touched[:, :11] = touched[:, 12:] = False
+    for key in ("var", "mom_rot", "out"):
+        assert torch.equal(torch.isfinite(now[key][0]), ~touched), key
+        assert bool(torch.isfinite(now[key][1]).all()), key
+    only = torch.zeros_like(touched)
+    only[7, 11] = True
+    assert torch.equal(torch.isfinite(now["mom"][0]), ~only)
