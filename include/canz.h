@@ -196,8 +196,11 @@ typedef struct {
  *   M <- beta M + G;  U = M (nesterov: U = G + beta M)
  *   X = U / (||U||_F + eps); the iteration runs on the wide orientation
  *   ns_steps times: A = X X^T; B = b A + c A A; X <- a X + B X
- *   (in bf16 mode wide matrices of 1536 and more rows take two or three of these steps at a time: the later A as
- *   polynomials of the first, X multiplied once with the product; same result to the rounding of single steps or better)
+ *   (in bf16 mode the first three and the last two of three and more steps are taken together, the later A as polynomials of
+ *   the first and X multiplied once with the product, where m = min(rows, cols) and n = max(rows, cols) satisfy m >= 1536, m n >= 2^24
+ *   and m <= 0.45 n (m >= 5120: m <= n / 2), and a, b, c keep the singular values in [0, 1.3] with |a + b t + c t^2| <= 3.5 for
+ *   their squares t, c != 0; no further from exact arithmetic than single steps, on inputs of many comparable directions
+ *   about half as far)
  *   O = X; scale = 1 | sqrt(max(1, rows/cols)) | 0.2 sqrt(max(rows, cols))
  *   CANZ_OUT_PARAM: P <- P (1 - lr weight_decay) - lr scale O
  *   CANZ_OUT_DELTA: Delta W = - lr scale O

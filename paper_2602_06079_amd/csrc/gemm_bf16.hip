@@ -53,25 +53,29 @@ constexpr int GROUP_M = 4;       // tile rows per raster band
 constexpr int N_XCD = 8;
 static_assert(BM == PANEL_ROWS && BK == PANEL_K, "tile = panel");
 
-enum { EPI_GRAM = 0, EPI_POLY = 1, EPI_UPDATE = 2, EPI_FINAL = 3, EPI_FINAL_SYM = 4, EPI_MUL = 5, EPI_POLY_APART = 6, EPI_GRAM_APART = 7,
-       EPI_B3 = 8, EPI_B3_SYM = 9, EPI_OUT_B3 = 10 };
+enum { EPI_GRAM = 0, EPI_POLY = 1, EPI_UPDATE = 2, EPI_FINAL = 3, EPI_FINAL_SYM = 4, EPI_MUL = 5, EPI_MUL_Q = 6, EPI_MUL_Q2 = 7,
+       EPI_POLY_APART = 8, EPI_GRAM_APART = 9, EPI_UPDATE_APART = 10, EPI_B3 = 11, EPI_B3_SYM = 12, EPI_OUT_TERMS = 13 };
 // EPI_FINAL_SYM: the last-product epilogue (the caller's dense buffers) over the tiles on and above the diagonal of a
 // symmetric result only; the caller mirrors them into the lower triangle afterwards.
-// EPI_GRAM_APART, EPI_POLY_APART: the diagonals of the matrices are kept apart (kernels.h: SymSpec).
+// EPI_*_APART, EPI_MUL*: the diagonals of the symmetric matrices are kept apart and their images are fp16 (kernels.h: SymSpec).
 // EPI_MUL: product of two symmetric matrices that commute (polynomials in one Gram matrix): symmetric as well.
-constexpr bool epi_poly(int epi) { return epi == EPI_POLY || epi == EPI_POLY_APART; }
-constexpr bool epi_apart(int epi) { return epi == EPI_POLY_APART || epi == EPI_MUL; }   // reads diagonals
-constexpr bool epi_mspace(int epi) { return epi == EPI_GRAM || epi == EPI_GRAM_APART || epi_poly(epi) || epi == EPI_MUL; }
-// EPI_B3, EPI_B3_SYM, EPI_OUT_B3: products of matrices of up to three bf16 terms (launch_split3*): the result as three
+// EPI_MUL_Q: its result leaves as bf16 image and diagonal, for the update (EPI_UPDATE_APART); EPI_MUL_Q2: as two bf16 terms, diagonal
+// included, for the last product (EPI_OUT_TERMS).
+constexpr bool epi_mul(int epi) { return epi == EPI_MUL || epi == EPI_MUL_Q || epi == EPI_MUL_Q2; }
+constexpr bool epi_f16_in(int epi) { return epi == EPI_POLY_APART || epi_mul(epi); }
+constexpr bool epi_f16_out(int epi) { return epi == EPI_GRAM_APART || epi == EPI_POLY_APART || epi == EPI_MUL; }
+constexpr bool epi_apart(int epi) { return epi_f16_in(epi) || epi == EPI_UPDATE_APART; }   // reads diagonals
+constexpr bool epi_mspace(int epi) { return epi == EPI_GRAM || epi == EPI_GRAM_APART || epi == EPI_POLY || epi == EPI_POLY_APART || epi_mul(epi); }
+// EPI_B3, EPI_B3_SYM, EPI_OUT_TERMS: products of matrices of up to three bf16 terms (launch_split3*): the result as three
 // terms, the same for symmetric matrices that commute, and the last-product epilogue.
-constexpr bool epi_terms(int epi) { return epi == EPI_B3 || epi == EPI_B3_SYM || epi == EPI_OUT_B3; }
+constexpr bool epi_terms(int epi) { return epi == EPI_B3 || epi == EPI_B3_SYM || epi == EPI_OUT_TERMS; }
 constexpr bool epi_symmetric(int epi) { return epi_mspace(epi) || epi == EPI_FINAL_SYM || epi == EPI_B3_SYM; }
-constexpr bool epi_final(int epi) { return epi == EPI_FINAL || epi == EPI_FINAL_SYM || epi == EPI_OUT_B3; }
+constexpr bool epi_final(int epi) { return epi == EPI_FINAL || epi == EPI_FINAL_SYM || epi == EPI_OUT_TERMS; }
 
 struct EpiArgs {
   void* c;                 // GRAM/POLY: [nb][M][N] panels; UPDATE: straight output [nb][M][N] panels
   void* ct;                // UPDATE: transposed output [nb][N][M] panels; B3_SYM: 5/4 I - 1/4 C, or nullptr
-  SymSpec sym;             // GRAM/POLY/MUL: how the symmetric matrices are represented (kernels.h)
+  SymSpec sym;             // GRAM/POLY/MUL/UPDATE_APART: how the symmetric matrices are represented (kernels.h)
   const float* scale;      // per-matrix factor applied to the accumulator, or nullptr
   float ca, cb, cc;        // POLY coefficients
   // schedule of the persistent blocks (see launch()): full rounds of whole tiles, then the
@@ -82,6 +86,9 @@ struct EpiArgs {
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 #define CANZ_LDS(p) ((__attribute__((address_space(3))) void*)(p))
@@ -139,17 +146,61 @@ __device__ __forceinline__ void decode_tile(int logical, int tiles_m, int tiles_
 
 }
 
-// Weight of a factor's element in the terms that carry a diagonal (kernels.h: SymSpec), and the diagonal element itself.
+// Matrices with their diagonal apart (kernels.h: SymSpec).  An image holds UNIT_A or UNIT_B times the off-diagonal elements;
+// a product of two images is scaled to the unit of its result, and what a diagonal multiplies is added in the epilogue.
 // Written once with the roundings pinned, so that both kernels produce the same bits.
+//   factor of the accumulator
 template <int EPI>
-__device__ __forceinline__ float poly_weight(const EpiArgs& e, float x, float y) {
-  return EPI == EPI_POLY_APART ? __builtin_fmaf(e.cc, x + y, e.cb) : e.cb;
+__device__ __forceinline__ float apart_factor(const EpiArgs& e) {
+  return EPI == EPI_POLY_APART ? e.cc * (UNIT_B / (UNIT_A * UNIT_A)) : EPI == EPI_GRAM_APART ? UNIT_A : 1.f / UNIT_B;
+}
+//   weights of the elements of the first (row) and second (column) image: POLY has one image with both diagonals
+template <int EPI>
+__device__ __forceinline__ float apart_weight(const EpiArgs& e, float x, float y, bool second) {
+  if (EPI == EPI_POLY_APART) return __builtin_fmaf(e.cc, x + y, e.cb) * (UNIT_B / UNIT_A);
+  if (epi_mul(EPI) && second) return y * (e.sym.unit * (1.f / UNIT_B));
+  return x;
+}
+//   the diagonal element itself, from what the accumulator holds after all of the above
+template <int EPI>
+__device__ __forceinline__ float apart_diagonal(float acc, float dx, float dy, const EpiArgs& e) {
+  if (EPI == EPI_GRAM_APART) return acc * (1.f / UNIT_A);
+  if (EPI == EPI_POLY_APART) return __builtin_fmaf(acc, 1.f / UNIT_B, __builtin_fmaf(__builtin_fmaf(e.cc, dx, e.cb), dx, e.ca));
+  return __builtin_fmaf(acc, 1.f / e.sym.unit, dx * dy);
+}
+
+// two values of a 16-bit image, packed, and four of them
+template <int EPI>
+__device__ __forceinline__ unsigned image_pair(float a, float b) {
+  if constexpr (epi_f16_out(EPI)) {
+    const f16x2 t = {static_cast<_Float16>(a), static_cast<_Float16>(b)};
+    return __builtin_bit_cast(unsigned, t);
+  } else {
+    bf16x2 t;
+    t[0] = static_cast<__bf16>(a), t[1] = static_cast<__bf16>(b);
+    return __builtin_bit_cast(unsigned, t);
+  }
 }
 template <int EPI>
-__device__ __forceinline__ float sym_diagonal(float acc, float dx, float dy, const EpiArgs& e) {
-  if (EPI == EPI_MUL) return __builtin_fmaf(dx, dy, acc);
-  return EPI == EPI_POLY_APART ? acc + __builtin_fmaf(__builtin_fmaf(e.cc, dx, e.cb), dx, e.ca) : acc + e.ca;
-}
+struct ImageIn {   // four consecutive elements of the images the epilogue reads
+  typedef bf16x4 vec4;
+};
+template <>
+struct ImageIn<EPI_POLY_APART> {
+  typedef f16x4 vec4;
+};
+template <>
+struct ImageIn<EPI_MUL> {
+  typedef f16x4 vec4;
+};
+template <>
+struct ImageIn<EPI_MUL_Q> {
+  typedef f16x4 vec4;
+};
+template <>
+struct ImageIn<EPI_MUL_Q2> {
+  typedef f16x4 vec4;
+};
 
 // two bf16 values, packed, times -1/4
 __device__ __forceinline__ unsigned minus_quarter(unsigned pair) {
@@ -169,7 +220,7 @@ __device__ __forceinline__ void put_three_terms(__bf16* to, int64_t step, float 
 
 // Epilogue of one 256 x 256 tile held in the accumulators of the block's four wavefronts
 // (shared by the GEMM kernel and by the kernel that finishes k-split tiles).
-// `stage`: this wavefront's private 32 KiB of LDS; `vec`: 128 floats of its own (POLY_APART and MUL).
+// `stage`: this wavefront's private 32 KiB of LDS; `vec`: 128 floats of its own (epi_apart).
 template <int EPI>
 __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage, int lane, int wm, int wn, int b,
                                               int tm, int tn, const GemmDims& d, const EpiArgs& e, const Shape& s,
@@ -179,80 +230,143 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
   //      of the wavefront's 128 x 128 part.  Each wavefront stages through its own 32 KiB.
   const int lj = lane & 31, lh = lane >> 5;
 
-  // scale (first iteration: folded normalisation); for POLY and MUL the terms that carry a diagonal, which is kept
-  // apart in fp32 (kernels.h: SymSpec), and the element-wise term of the polynomial
-  if constexpr (epi_poly(EPI) || EPI == EPI_MUL) {
-    // The factors are symmetric (off-diagonal tiles bit for bit: both halves are written from the same
-    // accumulators), so element (i, j) is read as (j, i): the wavefront's part of the mirrored tile is copied linearly
-    // into its staging area (global -> LDS, 16 bytes per lane) and is then the transposed image, in which a lane's
-    // four consecutive rows are four consecutive k.  fold(M, f): acc(i, j) <- f(acc(i, j), M(i, j), i, j).
+  // scale (first iteration: folded normalisation), or the polynomial in A for EPI_POLY
+  if constexpr (EPI == EPI_POLY) {
+    // A is symmetric bit for bit (the Gram epilogue writes both halves from the same
+    // accumulators), so element (i, j) is read as (j, i): the wavefront's part of the mirrored
+    // tile is copied linearly into its staging area (global -> LDS, 16 bytes per lane) and is
+    // then the transposed image, in which a lane's four consecutive rows are four consecutive k.
+    const __bf16* A = static_cast<const __bf16*>(e.sym.aux) + static_cast<int64_t>(b) * d.M * d.N;
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      const __bf16* src = A + (static_cast<int64_t>(tn) * (d.M >> 5) + 8 * tm + 4 * wm + kb) * PANEL_ELEMS +
+                          wn * 128 * PANEL_K + lane * 8;
+#pragma unroll
+      for (int x = 0; x < 8; ++x)
+        __builtin_amdgcn_global_load_lds(CANZ_GLB(src + x * 512), CANZ_LDS(stage + kb * 4096 + x * 512), 16, 0, 0);
+    }
     int a_base[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) a_base[g] = lj * 32 + ((g ^ ((lj >> 2) & 3)) << 3) + 4 * lh;
-    const int row_w = tm * BM + wm * 128 + 4 * lh, col_w = tn * BN + wn * 128 + lj;
-    constexpr bool APART = epi_apart(EPI);
-    const float* const xv = APART ? e.sym.x + static_cast<int64_t>(b) * d.M : nullptr;
-    const float* const yv = APART ? e.sym.y + static_cast<int64_t>(b) * d.M : nullptr;
-    // the diagonal elements of the part's 128 rows, once per tile (a load per group of rows would cost a memory latency each)
-    if (APART) vec[lane] = xv[tm * BM + wm * 128 + lane], vec[64 + lane] = xv[tm * BM + wm * 128 + 64 + lane];
-    auto fold = [&](const void* matrix, auto weight_of) {
-      constexpr int W = decltype(weight_of)::value;   // 0: the polynomial's, 1: the row's diagonal element, 2: the column's
-      const __bf16* A = static_cast<const __bf16*>(matrix) + static_cast<int64_t>(b) * d.M * d.N;
+    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0): the copy has landed
 #pragma unroll
-      for (int kb = 0; kb < 4; ++kb) {
-        const __bf16* src = A + (static_cast<int64_t>(tn) * (d.M >> 5) + 8 * tm + 4 * wm + kb) * PANEL_ELEMS +
-                            wn * 128 * PANEL_K + lane * 8;
+    for (int it = 0; it < 4; ++it)
 #pragma unroll
-        for (int x = 0; x < 8; ++x)
-          __builtin_amdgcn_global_load_lds(CANZ_GLB(src + x * 512), CANZ_LDS(stage + kb * 4096 + x * 512), 16, 0, 0);
-      }
-      float cw[4];
-#pragma unroll
-      for (int jt = 0; jt < 4; ++jt) cw[jt] = APART && W != 1 ? yv[col_w + jt * 32] : 0.f;
-      __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0): the copy has landed
-#pragma unroll
-      for (int it = 0; it < 4; ++it)
+      for (int jt = 0; jt < 4; ++jt) {
+        const int col = tn * BN + wn * 128 + jt * 32 + lj;
+        const int row0 = tm * BM + wm * 128 + it * 32 + 4 * lh;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          f32x4 rw = {0.f, 0.f, 0.f, 0.f};
-          if (APART && W != 2) rw = *reinterpret_cast<const f32x4*>(vec + it * 32 + 8 * g + 4 * lh);
+          const bf16x4 av = *reinterpret_cast<const bf16x4*>(stage + it * 4096 + jt * 32 * 32 + a_base[g]);
 #pragma unroll
-          for (int jt = 0; jt < 4; ++jt) {
-            const bf16x4 av = *reinterpret_cast<const bf16x4*>(stage + it * 4096 + jt * 32 * 32 + a_base[g]);
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              acc[it][jt][4 * g + q] = __builtin_fmaf(W == 0 ? poly_weight<EPI>(e, rw[q], cw[jt]) : W == 1 ? rw[q] : cw[jt], static_cast<float>(av[q]),
-                                                      acc[it][jt][4 * g + q]);
+          for (int q = 0; q < 4; ++q) {
+            acc[it][jt][4 * g + q] =
+                poly_value(static_cast<float>(av[q]), acc[it][jt][4 * g + q], e.ca, e.cb, e.cc, row0 + 8 * g + q == col);
           }
-          if (APART) __builtin_amdgcn_sched_barrier(0);   // one group's reads at a time: the accumulators leave few registers
         }
-      // every read of the staging area is done before it is written again
-      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-    };
-    if constexpr (epi_poly(EPI)) {
-      // always, but a branch: as straight-line code behind the k loop the fold is spilled by the hundred
+      }
+    // every read of the staging area is done before the images below overwrite it
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+  } else if constexpr (epi_apart(EPI) || EPI == EPI_GRAM_APART) {
+    // The terms that carry a diagonal (SymSpec), and the element-wise term of the polynomial.  The images are
+    // symmetric (off-diagonal tiles bit for bit: both halves are written from the same accumulators) or, for UPDATE,
+    // there as X^T, so element (i, j) is read as (j, i), as above.
+    constexpr bool UPD = EPI == EPI_UPDATE_APART;
+    const int row_w = tm * BM + wm * 128 + 4 * lh, col_w = tn * BN + wn * 128 + lj;
+    const float* const xv = epi_apart(EPI) ? e.sym.x + static_cast<int64_t>(b) * d.M : nullptr;
+    const float* const yv = epi_f16_in(EPI) ? e.sym.y + static_cast<int64_t>(b) * d.M : nullptr;
+    if constexpr (!UPD) {
+      const float f = EPI == EPI_GRAM_APART && e.scale ? e.scale[b] * UNIT_A : apart_factor<EPI>(e);
 #pragma unroll
       for (int it = 0; it < 4; ++it)
 #pragma unroll
         for (int jt = 0; jt < 4; ++jt)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[it][jt][r] *= e.cc;
-      if (e.sym.aux) fold(e.sym.aux, std::integral_constant<int, 0>{});
-    } else {
-      if (e.sym.aux) fold(e.sym.aux, std::integral_constant<int, 1>{});
-      if (e.sym.aux2) fold(e.sym.aux2, std::integral_constant<int, 2>{});
+          for (int r = 0; r < 16; ++r) acc[it][jt][r] *= f;
     }
-    if (tm == tn && wm == wn) {
-      // the diagonal: the lane that holds element (i, i)
+    if constexpr (epi_apart(EPI)) {
+      int a_base[4];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) a_base[g] = lj * 32 + ((g ^ ((lj >> 2) & 3)) << 3) + 4 * lh;
+      // the diagonal elements of the part's 128 rows, once per tile (a load per group of rows would cost a memory latency each)
+      vec[lane] = xv[tm * BM + wm * 128 + lane], vec[64 + lane] = xv[tm * BM + wm * 128 + 64 + lane];
+      // acc(i, j) += weight(i, j) image(i, j)
+      auto fold = [&](const void* matrix, auto second) {
+        constexpr bool SECOND = decltype(second)::value;
+        const __bf16* A = static_cast<const __bf16*>(matrix) + static_cast<int64_t>(b) * d.M * d.N;
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+          const __bf16* src = A + (static_cast<int64_t>(tn) * (d.M >> 5) + 8 * tm + 4 * wm + kb) * PANEL_ELEMS +
+                              wn * 128 * PANEL_K + lane * 8;
+#pragma unroll
+          for (int x = 0; x < 8; ++x)
+            __builtin_amdgcn_global_load_lds(CANZ_GLB(src + x * 512), CANZ_LDS(stage + kb * 4096 + x * 512), 16, 0, 0);
+        }
+        float cw[4];
+#pragma unroll
+        for (int jt = 0; jt < 4; ++jt) cw[jt] = EPI == EPI_POLY_APART || SECOND ? yv[col_w + jt * 32] : 0.f;
+        __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0): the copy has landed
+#pragma unroll
+        for (int it = 0; it < 4; ++it)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            f32x4 rw = {0.f, 0.f, 0.f, 0.f};
+            if (!SECOND) rw = *reinterpret_cast<const f32x4*>(vec + it * 32 + 8 * g + 4 * lh);
+#pragma unroll
+            for (int jt = 0; jt < 4; ++jt) {
+              const auto av = *reinterpret_cast<const typename ImageIn<EPI>::vec4*>(stage + it * 4096 + jt * 32 * 32 + a_base[g]);
+#pragma unroll
+              for (int q = 0; q < 4; ++q)
+                acc[it][jt][4 * g + q] = __builtin_fmaf(apart_weight<EPI>(e, rw[q], cw[jt], SECOND), static_cast<float>(av[q]), acc[it][jt][4 * g + q]);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // one group's reads at a time: the accumulators leave few registers
+          }
+        // every read of the staging area is done before it is written again
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+      };
+      // always, but a branch: as straight-line code behind the k loop the fold is spilled by the hundred
+      if (e.sym.aux) fold(e.sym.aux, std::false_type{});
+      if constexpr (epi_mul(EPI))
+        if (e.sym.aux2) fold(e.sym.aux2, std::true_type{});
+    }
+    if constexpr (UPD) {
+      const float sc = e.scale ? e.scale[b] : 1.f;
+#pragma unroll
+      for (int it = 0; it < 4; ++it)
+#pragma unroll
+        for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[it][jt][r] *= sc;
+    } else if (tm == tn && wm == wn) {   // the diagonal goes to its own fp32 vector, the image holds zeros there (Q2: all in the image)
+      float* dv = EPI == EPI_MUL_Q2 ? nullptr : e.sym.diag + static_cast<int64_t>(b) * d.M;
 #pragma unroll
       for (int it = 0; it < 4; ++it) {
         const int col = col_w + it * 32;
-        const float dx = APART ? xv[col] : 0.f, dy = APART ? yv[col] : 0.f;
+        const float dx = xv ? xv[col] : 0.f, dy = yv ? yv[col] : 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          if (row_w + it * 32 + 8 * (r >> 2) + (r & 3) == col)
-            acc[it][it][r] = sym_diagonal<EPI>(acc[it][it][r], dx, dy, e);
+          if (row_w + it * 32 + 8 * (r >> 2) + (r & 3) == col) {
+            const float v = apart_diagonal<EPI>(acc[it][it][r], dx, dy, e);
+            if (EPI != EPI_MUL_Q2) dv[col] = v;
+            acc[it][it][r] = EPI == EPI_MUL_Q2 ? v * e.sym.unit : 0.f;
+          }
       }
+    }
+    if constexpr (EPI == EPI_MUL_Q || EPI == EPI_MUL_Q2) {
+      const float inv = 1.f / e.sym.unit;   // a power of two
+#pragma unroll
+      for (int it = 0; it < 4; ++it)
+#pragma unroll
+        for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[it][jt][r] *= inv;
+    }
+    if constexpr (epi_f16_out(EPI)) {
+      // one fp32 value for both images: no operation is fused into one of the two conversions and not into the other
+#pragma unroll
+      for (int it = 0; it < 4; ++it)
+#pragma unroll
+        for (int jt = 0; jt < 4; ++jt) asm volatile("" : "+a"(acc[it][jt]));
     }
   } else if (e.scale) {
     const float sc = e.scale[b];
@@ -262,19 +376,6 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
       for (int jt = 0; jt < 4; ++jt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[it][jt][r] *= sc;
-  }
-  if constexpr (epi_apart(EPI) || EPI == EPI_GRAM_APART) {
-    if (e.sym.diag && tm == tn && wm == wn) {   // the diagonal goes to its own fp32 vector, the images hold zeros there
-      float* dv = e.sym.diag + static_cast<int64_t>(b) * d.M;
-#pragma unroll
-      for (int it = 0; it < 4; ++it)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = tm * BM + wm * 128 + it * 32 + 4 * lh + 8 * (r >> 2) + (r & 3);
-          const int col = tn * BN + wn * 128 + it * 32 + lj;
-          if (row == col) dv[row] = acc[it][it][r], acc[it][it][r] = 0.f;
-        }
-    }
   }
 
   // the wavefront's part of an output tile in panel layout: four pieces of 8 KiB (the four
@@ -292,11 +393,12 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
     }
   };
 
-  if constexpr (EPI == EPI_B3 || EPI == EPI_B3_SYM) {
-    // Three terms per element, through the staging area as the bf16 images below (whose offsets these are): each pass rounds
+  if constexpr (EPI == EPI_B3 || EPI == EPI_B3_SYM || EPI == EPI_MUL_Q2) {
+    // Three terms per element (Q2: two), through the staging area as the bf16 images below (whose offsets these are): each pass rounds
     // what is left to bf16, writes it (for a symmetric result also mirrored) and takes it away.  5/4 I - 1/4 C, where it is
     // asked for, has -1/4 of the terms of C off the diagonal, exactly; its diagonal is put in place at the end.
-    constexpr bool SYM = EPI == EPI_B3_SYM;
+    constexpr bool SYM = EPI != EPI_B3;
+    constexpr int NT = EPI == EPI_MUL_Q2 ? 2 : 3;
     if (e.c == nullptr) return;   // never: a branch that parts the epilogue from the k loop's block, see POLY above
     int s_base[2], t_base[4];
 #pragma unroll
@@ -305,9 +407,9 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
 #pragma unroll
     for (int g = 0; g < 4; ++g) t_base[g] = lj * 32 + ((g ^ ((lj >> 2) & 3)) << 3) + 4 * lh;
     const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
-    const int64_t nkb = d.N >> 5, elems = 3 * d.M * d.N;
+    const int64_t nkb = d.N >> 5, elems = NT * d.M * d.N;
     __bf16* const C = static_cast<__bf16*>(e.c) + static_cast<int64_t>(b) * elems;
-    __bf16* const T = SYM && e.ct ? static_cast<__bf16*>(e.ct) + static_cast<int64_t>(b) * elems : nullptr;
+    __bf16* const T = EPI == EPI_B3_SYM && e.ct ? static_cast<__bf16*>(e.ct) + static_cast<int64_t>(b) * elems : nullptr;
     const bool diagonal = SYM && tm == tn && wm == wn;
     float dv[4];
     if (T && diagonal) {
@@ -318,9 +420,9 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
           if (8 * (r >> 2) + (r & 3) + 4 * lh == lj) dv[it] = acc[it][it][r];
     }
 #pragma unroll 1
-    for (int term = 0; term < 3; ++term) {
+    for (int term = 0; term < NT; ++term) {
       auto flush = [&](int64_t row_block, int64_t kblock0, int half_rows) {
-        const int64_t at = (row_block * 3 * nkb + term * nkb + kblock0) * PANEL_ELEMS + half_rows * 128 * PANEL_K + lane * 8;
+        const int64_t at = (row_block * NT * nkb + term * nkb + kblock0) * PANEL_ELEMS + half_rows * 128 * PANEL_K + lane * 8;
 #pragma unroll
         for (int k4 = 0; k4 < 4; ++k4)
 #pragma unroll
@@ -414,10 +516,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
         for (int rp = 0; rp < 8; ++rp) {  // register pairs (2 rp, 2 rp + 1): rows differ by one
           // both rows of this lane's column, packed; the even lane keeps the low halves of
           // the pair of lanes (row 2 rp), the odd lane the high halves (row 2 rp + 1)
-          bf16x2 own;
-          own[0] = static_cast<__bf16>(acc[it][jt][2 * rp]);
-          own[1] = static_cast<__bf16>(acc[it][jt][2 * rp + 1]);
-          const unsigned mine = __builtin_bit_cast(unsigned, own);
+          const unsigned mine = image_pair<EPI>(acc[it][jt][2 * rp], acc[it][jt][2 * rp + 1]);
           const unsigned theirs = lane_xor1(mine);
           const unsigned pk = __builtin_amdgcn_perm(theirs, mine, pair_sel);
           const int g = rp >> 1, p = rp & 1;
@@ -445,10 +544,8 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
         for (int jt = 0; jt < 4; ++jt)
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
-            bf16x4 pk;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) pk[q] = static_cast<__bf16>(acc[it][jt][4 * g + q]);
-            *reinterpret_cast<bf16x4*>(stage + it * 4096 + jt * 32 * 32 + t_base[g]) = pk;
+            const u32x2 pk = {image_pair<EPI>(acc[it][jt][4 * g], acc[it][jt][4 * g + 1]), image_pair<EPI>(acc[it][jt][4 * g + 2], acc[it][jt][4 * g + 3])};
+            *reinterpret_cast<u32x2*>(stage + it * 4096 + jt * 32 * 32 + t_base[g]) = pk;
           }
       flush_stage(CT, tn, d.M, 8 * tm + 4 * wm, wn);
     }
@@ -617,7 +714,13 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
   }
 }
 
-__device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
+template <int EPI>
+__device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
+  if constexpr (epi_f16_in(EPI))
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
 
 // Element offset of the next panel of an operand of several terms: nk panels of the first segment's term, then of the
 // second's, ...  No branches: one in the k loop would cost the compiler its count of the loads in flight.  Behind the
@@ -772,9 +875,9 @@ __global__ __launch_bounds__(NTHREADS) void k_gemm_nt_bf16(Args args, EpiArgs e_
     const int i = idx >> 2, j = idx & 3;
     if (decltype(first)::value) {
       const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      acc[i][j] = mfma(fa[set][i], fb[set][j], zero);
+      acc[i][j] = mfma<EPI>(fa[set][i], fb[set][j], zero);
     } else {
-      acc[i][j] = mfma(fa[set][i], fb[set][j], acc[i][j]);
+      acc[i][j] = mfma<EPI>(fa[set][i], fb[set][j], acc[i][j]);
     }
   };
 
@@ -1038,7 +1141,7 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          acc[i][j] = mfma(fa[kk][i], fb[kk][j], acc[i][j]);
+          acc[i][j] = mfma<EPI>(fa[kk][i], fb[kk][j], acc[i][j]);
   };
   // One k-step on stage `cur`: the 4 loads of the following step may stay in flight; after the
   // barrier every wavefront has finished the step before, whose stage `nxt2` then receives step kt + 2.
@@ -1079,70 +1182,120 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
     s_lane[g1] = (4 * lh + (lane & 1)) * PANEL_K + ((((lj >> 3) ^ (2 * g1 + lh)) & 3) << 3) + (lj & 6);
 #pragma unroll
   for (int g = 0; g < 4; ++g) t_lane[g] = lj * PANEL_K + ((g ^ ((lj >> 2) & 3)) << 3) + 4 * lh;
-  if constexpr (epi_poly(EPI) || EPI == EPI_MUL) {
-    // as in the large kernel: element (i, j) of a symmetric factor is read as (j, i), so the lane's four
-    // consecutive rows are four consecutive k of row j, one 8-byte load
-    constexpr bool APART = epi_apart(EPI);
-    const float* const xv = APART ? e.sym.x + static_cast<int64_t>(b) * d.M : nullptr;
-    const float* const yv = APART ? e.sym.y + static_cast<int64_t>(b) * d.M : nullptr;
-    const __bf16* const m1 = static_cast<const __bf16*>(e.sym.aux) + static_cast<int64_t>(b) * d.M * d.N;
-    const __bf16* const m3 = static_cast<const __bf16*>(e.sym.aux2) + static_cast<int64_t>(b) * d.M * d.N;
-    if (m1 != nullptr) {   // always: keeps this apart from the k loop's block, see the large kernel
-    // all loads of a 32 x 32 tile at once: a few memory latencies for the whole epilogue, within the registers that
-    // three blocks per CU leave
+  if constexpr (EPI == EPI_POLY) {
+    // A(i, j) is read as A(j, i) (symmetric bit for bit): the lane's four consecutive rows are
+    // four consecutive k of row j, one 8-byte load
+    const __bf16* A = static_cast<const __bf16*>(e.sym.aux) + static_cast<int64_t>(b) * d.M * d.N;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        asm volatile("" ::: "memory");   // or the compiler brings the loads of all four tiles together and spills
-        bf16x4 v1[4], v3[4];
-        f32x4 rw[4];
-        const float cw = APART ? yv[col_w + 32 * j + lj] : 0.f;
+        const int col = col_w + 32 * j + lj;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const int64_t at = transposed_at(i, j) + t_lane[g];
-          rw[g] = f32x4{0.f, 0.f, 0.f, 0.f};
-          if (APART) rw[g] = *reinterpret_cast<const f32x4*>(xv + row_w + 32 * i + 8 * g + 4 * lh);
-          v1[g] = *reinterpret_cast<const bf16x4*>(m1 + at);
-          if constexpr (EPI == EPI_MUL) v3[g] = *reinterpret_cast<const bf16x4*>(m3 + at);
+          const int row0 = row_w + 32 * i + 8 * g + 4 * lh;
+          const bf16x4 av = *reinterpret_cast<const bf16x4*>(A + panel_chunk_off(col, row0 & ~7, d.M) + (row0 & 7));
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            acc[i][j][4 * g + q] = poly_value(static_cast<float>(av[q]), acc[i][j][4 * g + q], e.ca, e.cb, e.cc, row0 + q == col);
         }
-        __builtin_amdgcn_sched_barrier(0);
+      }
+  } else if constexpr (epi_apart(EPI) || EPI == EPI_GRAM_APART) {
+    // as in the large kernel
+    constexpr bool UPD = EPI == EPI_UPDATE_APART;
+    typedef typename ImageIn<EPI>::vec4 vec4;
+    const float* const xv = epi_apart(EPI) ? e.sym.x + static_cast<int64_t>(b) * d.M : nullptr;
+    const float* const yv = epi_f16_in(EPI) ? e.sym.y + static_cast<int64_t>(b) * d.M : nullptr;
+    const float f = UPD ? 1.f : EPI == EPI_GRAM_APART && e.scale ? e.scale[b] * UNIT_A : apart_factor<EPI>(e);
+    if constexpr (!epi_apart(EPI)) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            float v = acc[i][j][4 * g + q];
-            if constexpr (epi_poly(EPI)) {
-              const float w = poly_weight<EPI>(e, rw[g][q], cw);
-              v = __builtin_fmaf(w, static_cast<float>(v1[g][q]), v * e.cc);
-            } else {
-              v = __builtin_fmaf(rw[g][q], static_cast<float>(v1[g][q]), v);
-              v = __builtin_fmaf(cw, static_cast<float>(v3[g][q]), v);
-            }
-            acc[i][j][4 * g + q] = v;
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] *= f;
+    } else if (const __bf16* const m1 = static_cast<const __bf16*>(e.sym.aux) + static_cast<int64_t>(b) * d.M * d.N; m1 != nullptr) {
+      // always: keeps this apart from the k loop's block, see the large kernel
+      const __bf16* const m3 = static_cast<const __bf16*>(e.sym.aux2) + static_cast<int64_t>(b) * d.M * d.N;
+      const float sc1 = UPD && e.scale ? e.scale[b] : 1.f;
+      // all loads of a 32 x 32 tile at once: a few memory latencies for the whole epilogue, within the registers that
+      // three blocks per CU leave
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          asm volatile("" ::: "memory");   // or the compiler brings the loads of all four tiles together and spills
+          vec4 v1[4], v3[4];
+          f32x4 rw[4];
+          const float cw = epi_f16_in(EPI) ? yv[col_w + 32 * j + lj] : 0.f;
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const int64_t at = transposed_at(i, j) + t_lane[g];
+            rw[g] = *reinterpret_cast<const f32x4*>(xv + row_w + 32 * i + 8 * g + 4 * lh);
+            v1[g] = *reinterpret_cast<const vec4*>(m1 + at);
+            if constexpr (epi_mul(EPI)) v3[g] = *reinterpret_cast<const vec4*>(m3 + at);
           }
-        __builtin_amdgcn_sched_barrier(0);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              float v = UPD ? acc[i][j][4 * g + q] : acc[i][j][4 * g + q] * f;
+              v = __builtin_fmaf(apart_weight<EPI>(e, rw[g][q], cw, false), static_cast<float>(v1[g][q]), v);
+              if constexpr (epi_mul(EPI)) v = __builtin_fmaf(apart_weight<EPI>(e, 0.f, cw, true), static_cast<float>(v3[g][q]), v);
+              acc[i][j][4 * g + q] = UPD ? v * sc1 : v;
+            }
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
     }
-    }
-    if (tm == tn && wm == wn) {
+    if (!UPD && tm == tn && wm == wn) {
+      float* dv = EPI == EPI_MUL_Q2 ? nullptr : e.sym.diag + static_cast<int64_t>(b) * d.M;
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const int col = col_w + 32 * i + lj;
-        const float dx = APART ? xv[col] : 0.f, dy = APART ? yv[col] : 0.f;
+        const float dx = xv ? xv[col] : 0.f, dy = yv ? yv[col] : 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          if (row_w + 32 * i + 4 * lh + 8 * (r >> 2) + (r & 3) == col)
-            acc[i][i][r] = sym_diagonal<EPI>(acc[i][i][r], dx, dy, e);
+          if (row_w + 32 * i + 4 * lh + 8 * (r >> 2) + (r & 3) == col) {
+            const float v = apart_diagonal<EPI>(acc[i][i][r], dx, dy, e);
+            if (EPI != EPI_MUL_Q2) dv[col] = v;
+            acc[i][i][r] = EPI == EPI_MUL_Q2 ? v * e.sym.unit : 0.f;
+          }
       }
     }
-  } else if constexpr (EPI == EPI_B3 || EPI == EPI_B3_SYM) {
+    if constexpr (EPI == EPI_MUL_Q || EPI == EPI_MUL_Q2) {
+      const float inv = 1.f / e.sym.unit;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] *= inv;
+    }
+    if constexpr (epi_f16_out(EPI)) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) asm volatile("" : "+v"(acc[i][j]));
+    }
+  } else if (e.scale) {
+    const float sc1 = e.scale[b];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] *= sc1;
+  }
+  if constexpr (EPI == EPI_B3 || EPI == EPI_B3_SYM || EPI == EPI_MUL_Q2) {
     // as in the large kernel, straight from the accumulators
-    constexpr bool SYM = EPI == EPI_B3_SYM;
+    constexpr bool SYM = EPI != EPI_B3;
+    constexpr int NT = EPI == EPI_MUL_Q2 ? 2 : 3;
     const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
-    const int64_t nkb = d.N >> 5, elems = 3 * d.M * d.N;
+    const int64_t nkb = d.N >> 5, elems = NT * d.M * d.N;
     __bf16* const C = static_cast<__bf16*>(e.c) + static_cast<int64_t>(b) * elems;
-    __bf16* const T = SYM && e.ct ? static_cast<__bf16*>(e.ct) + static_cast<int64_t>(b) * elems : nullptr;
+    __bf16* const T = EPI == EPI_B3_SYM && e.ct ? static_cast<__bf16*>(e.ct) + static_cast<int64_t>(b) * elems : nullptr;
     const bool diagonal = SYM && tm == tn && wm == wn;
     float dv[2];
     if (T && diagonal) {
@@ -1153,13 +1306,13 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
           if (8 * (r >> 2) + (r & 3) + 4 * lh == lj) dv[i] = acc[i][i][r];
     }
 #pragma unroll 1
-    for (int term = 0; term < 3; ++term)
+    for (int term = 0; term < NT; ++term)
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-          const int64_t at = ((row_w >> 8) * 3 * nkb + term * nkb + ((col_w + 32 * j) >> 5)) * PANEL_ELEMS + ((row_w & 255) + 32 * i) * PANEL_K;
-          const int64_t tt = ((col_w >> 8) * 3 * nkb + term * nkb + ((row_w + 32 * i) >> 5)) * PANEL_ELEMS + ((col_w & 255) + 32 * j) * PANEL_K;
+          const int64_t at = ((row_w >> 8) * NT * nkb + term * nkb + ((col_w + 32 * j) >> 5)) * PANEL_ELEMS + ((row_w & 255) + 32 * i) * PANEL_K;
+          const int64_t tt = ((col_w >> 8) * NT * nkb + term * nkb + ((row_w + 32 * i) >> 5)) * PANEL_ELEMS + ((col_w & 255) + 32 * j) * PANEL_K;
           unsigned mine[8];
 #pragma unroll
           for (int rp = 0; rp < 8; ++rp) {
@@ -1195,26 +1348,6 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
       }
     }
     return;
-  } else if (e.scale) {
-    const float sc1 = e.scale[b];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] *= sc1;
-  }
-  if constexpr (epi_apart(EPI) || EPI == EPI_GRAM_APART) {
-    if (e.sym.diag && tm == tn && wm == wn) {
-      float* dv = e.sym.diag + static_cast<int64_t>(b) * d.M;
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = row_w + 32 * i + 4 * lh + 8 * (r >> 2) + (r & 3), col = col_w + 32 * i + lj;
-          if (row == col) dv[row] = acc[i][i][r], acc[i][i][r] = 0.f;
-        }
-    }
   }
 
   if (epi_final(EPI)) {
@@ -1302,10 +1435,7 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
       __bf16* const at = C + straight_at(i, j);
 #pragma unroll
       for (int rp = 0; rp < 8; ++rp) {
-        bf16x2 own;
-        own[0] = static_cast<__bf16>(acc[i][j][2 * rp]);
-        own[1] = static_cast<__bf16>(acc[i][j][2 * rp + 1]);
-        const unsigned mine = __builtin_bit_cast(unsigned, own);
+        const unsigned mine = image_pair<EPI>(acc[i][j][2 * rp], acc[i][j][2 * rp + 1]);
         const unsigned theirs = lane_xor1(mine);
         const unsigned pk = __builtin_amdgcn_perm(theirs, mine, pair_sel);
         *reinterpret_cast<unsigned*>(at + s_lane[(rp >> 1) & 1] + (8 * (rp >> 1) + 2 * (rp & 1)) * PANEL_K) = pk;
@@ -1321,10 +1451,8 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
         __bf16* const at = CT + transposed_at(i, j);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          bf16x4 pk;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) pk[q] = static_cast<__bf16>(acc[i][j][4 * g + q]);
-          *reinterpret_cast<bf16x4*>(at + t_lane[g]) = pk;
+          const u32x2 pk = {image_pair<EPI>(acc[i][j][4 * g], acc[i][j][4 * g + 1]), image_pair<EPI>(acc[i][j][4 * g + 2], acc[i][j][4 * g + 3])};
+          *reinterpret_cast<u32x2*>(at + t_lane[g]) = pk;
         }
       }
   }
@@ -1351,7 +1479,8 @@ int cu_count() {
 // small kernel when they would leave at least half of the chip idle for a whole tile time -
 // which includes launches with no full round at all.
 constexpr int64_t SMALL_MAX_K = 4096;
-// ... except the products of m x m matrices, whose left-over tiles gain up to here (4 x 5120^2, 840 tiles on 256 CUs)
+// ... except the products of m x m matrices of merged steps, whose left-over tiles gain up to here (4 x 5120^2, 840 tiles on 256
+// CUs)
 constexpr int64_t SMALL_MAX_K_MSPACE = 8192;
 constexpr int64_t SMALL_ALL_MAX_K = 2048;   // polynomial products up to this k and under two rounds: small tiles only
 
@@ -1365,8 +1494,8 @@ int64_t tile_count(const GemmDims& d) {
 template <int EPI>
 int64_t large_share(int64_t tiles, int64_t cus, int64_t longest_k) {
   const int64_t left = tiles % cus;
-  constexpr bool msquare = epi_poly(EPI) || EPI == EPI_MUL;
-  if (!epi_terms(EPI) && longest_k > (msquare ? SMALL_MAX_K_MSPACE : SMALL_MAX_K)) return tiles;
+  constexpr bool msquare = EPI == EPI_POLY || epi_f16_in(EPI);
+  if (!epi_terms(EPI) && longest_k > (epi_f16_in(EPI) ? SMALL_MAX_K_MSPACE : SMALL_MAX_K)) return tiles;
   // a polynomial product (k = m, the shortest k range of the step) of less than two rounds runs faster on small
   // tiles throughout: 59.6 -> 52.4 us on 26 matrices of 1024 x 1024; the same rule costs the Gram product 7 %
   if (msquare && tiles < 2 * cus && longest_k <= SMALL_ALL_MAX_K) return 0;
@@ -1483,8 +1612,12 @@ hipError_t launch_poly_bf16(const GemmBatch& g, float ca, float cb, float cc, co
   return g.n > 0 && g.pr[0].sym.x ? launch_problems<EPI_POLY_APART>(g, e, w, st) : launch_problems<EPI_POLY>(g, e, w, st);
 }
 
-hipError_t launch_mul_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st) {
-  return launch_problems<EPI_MUL>(g, EpiArgs{}, w, st);
+hipError_t launch_mul_f16(const GemmBatch& g, MulResult result, const SplitWs& w, hipStream_t st) {
+  switch (result) {
+    case MulResult::Q: return launch_problems<EPI_MUL_Q>(g, EpiArgs{}, w, st);
+    case MulResult::Q2: return launch_problems<EPI_MUL_Q2>(g, EpiArgs{}, w, st);
+    default: return launch_problems<EPI_MUL>(g, EpiArgs{}, w, st);
+  }
 }
 
 hipError_t launch_split3_sym(const GemmBatch& g, hipStream_t st) {
@@ -1492,7 +1625,8 @@ hipError_t launch_split3_sym(const GemmBatch& g, hipStream_t st) {
 }
 
 hipError_t launch_update_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st) {
-  return launch_problems<EPI_UPDATE>(g, EpiArgs{}, w, st);
+  return g.n > 0 && g.pr[0].sym.x ? launch_problems<EPI_UPDATE_APART>(g, EpiArgs{}, w, st)
+                                  : launch_problems<EPI_UPDATE>(g, EpiArgs{}, w, st);
 }
 
 hipError_t launch_update_bf16(const GemmDims& d, const void* b_in, const void* xt_in, void* xw_out, void* xt_out,
@@ -1510,8 +1644,8 @@ hipError_t launch_split3(const GemmDims& d, const void* p, const void* q, void* 
   return launch<EPI_B3>(d, p, q, e, SplitWs{nullptr, 0}, Shape{}, OutSpec{}, st);
 }
 
-hipError_t launch_split3_final(const GemmDims& d, const void* p, const void* q, const Shape& s, const OutSpec& o, hipStream_t st) {
-  return launch<EPI_OUT_B3>(d, p, q, EpiArgs{}, SplitWs{nullptr, 0}, s, o, st);
+hipError_t launch_terms_final(const GemmDims& d, const void* p, const void* q, const Shape& s, const OutSpec& o, hipStream_t st) {
+  return launch<EPI_OUT_TERMS>(d, p, q, EpiArgs{}, SplitWs{nullptr, 0}, s, o, st);
 }
 
 hipError_t launch_final_bf16(const GemmDims& d, const void* p, const void* q, const float* scale, const SplitWs& w,

@@ -99,18 +99,23 @@ struct SplitWs {
 constexpr int SPLIT_MAX_BLOCKS = 256;                       // CU count of MI355X; fewer blocks split on a smaller part
 constexpr size_t SPLIT_BLOCK_BYTES = 256 * 256 * sizeof(float);
 // How the products of the symmetric m x m matrices (all of them polynomials in one Gram matrix) take their factors
-// and leave their result.  A matrix is a bf16 image in the panel layout; optionally its diagonal is kept apart as an fp32
-// vector (the image then holds zeros there).  The MFMA products use the images; everything that multiplies a diagonal,
-// and the element-wise terms, are added in the epilogue in fp32:
+// and leave their result.  In single steps a matrix is a bf16 image in the panel layout.  In merged steps, where several of them
+// follow each other without X in between, its diagonal is kept apart as an fp32 vector (the image holds zeros there), and the
+// image is fp16.  The MFMA products use the images; everything that multiplies a diagonal, and the element-wise terms, are
+// added in the epilogue in fp32:
 //   (D_P + H_P)(D_Y + H_Y) = D_P D_Y + D_P H_Y + H_P D_Y + H_P H_Y.
 // The diagonals are what all these matrices consist of once X is close to orthogonal, and their nearly equal elements
-// round alike: kept in bf16 they would cost several times the error of all other roundings together.
+// round alike.  fp16 has 11 bits where bf16 has 8; its exponents suffice, since these matrices have known magnitude (the caller
+// sees to it): the images hold UNIT_A times the elements of A, B A (eigenvalues up to 1.69) and UNIT_B times those of B and
+// of products of B (up to 3.5^3).  A and B A have elements down to 1 / (m sqrt(n)), far above 2^-14 / UNIT_A, where fp16 begins to lose bits.
+constexpr float UNIT_A = 16384.f, UNIT_B = 1024.f;
 struct SymSpec {
-  const void* aux;      // POLY: A;  MUL: the second factor Y
-  const void* aux2;     // MUL: the first factor P
-  const float* x;       // POLY: the diagonal of A, or nullptr (the image holds it);  MUL: the diagonal of P   [nb][M]
+  const void* aux;      // POLY: A;  MUL: the second factor Y;  UPDATE: X^T
+  const void* aux2;     // MUL: the first factor P (always a B)
+  const float* x;       // POLY: the diagonal of A, or nullptr (a bf16 image that holds it);  MUL: the diagonal of P;  UPDATE: of Q   [nb][M]
   const float* y;       // POLY: as x;  MUL: the diagonal of Y
-  float* diag;          // result: diagonal, or nullptr (the image holds it)
+  float* diag;          // result: diagonal, or nullptr (a bf16 image that holds it)
+  float unit;           // MUL: the unit of Y and of the result, UNIT_A or UNIT_B
 };
 // Several products of one kind in one launch: matrices of different shapes, or independent products of one chain.
 // The persistent blocks walk the tiles of problem 0, then of problem 1, ...
@@ -122,7 +127,7 @@ struct GemmProblem {
   const void* q;       // second operand [nb][N][K] panels
   void* c;             // output (UPDATE: the straight image)
   void* ct;            // UPDATE: the transposed image
-  SymSpec sym;         // GRAM, POLY, MUL
+  SymSpec sym;         // GRAM, POLY, MUL, UPDATE
   const float* scale;  // per-matrix factor or nullptr
 };
 struct GemmBatch {
@@ -133,9 +138,11 @@ struct GemmBatch {
 hipError_t launch_gram_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st);
 // B = ca I + cb A + cc A A                   (P = Q = A, symmetric); all problems with sym.x and sym.y, or none
 hipError_t launch_poly_bf16(const GemmBatch& g, float ca, float cb, float cc, const SplitWs& w, hipStream_t st);
-// C = P Y, P and Y symmetric and commuting   (Q = Y)
-hipError_t launch_mul_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st);
-// as launch_update_bf16 below, for several problems
+// C = P Y, P and Y symmetric and commuting   (Q = Y).  The result leaves as fp16 image and diagonal (CHAIN), as bf16 image and
+// diagonal for the update (Q), or as two bf16 terms [nb][M][2 M] for the last product (Q2)
+enum class MulResult { CHAIN, Q, Q2 };
+hipError_t launch_mul_f16(const GemmBatch& g, MulResult result, const SplitWs& w, hipStream_t st);
+// as launch_update_bf16 below, for several problems; with sym.x: Q's diagonal apart (and sym.aux = X^T)
 hipError_t launch_update_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st);
 
 // X' = scale[b] * B X: XW' [mp][np] straight and XT' [np][mp] transposed  (P = B, Q = XT)
@@ -164,8 +171,8 @@ hipError_t launch_split3(const GemmDims& d, const void* p, const void* q, void* 
 //   the same for symmetric P and Q that commute: the tiles on and above the diagonal, mirrored.  ct of a problem, or
 //   nullptr: 5/4 I - 1/4 c as three terms
 hipError_t launch_split3_sym(const GemmBatch& g, hipStream_t st);
-//   the result as the last product of launch_final_bf16 (o: the caller's buffers)
-hipError_t launch_split3_final(const GemmDims& d, const void* p, const void* q, const Shape& s, const OutSpec& o, hipStream_t st);
+//   the result as the last product of launch_final_bf16 (o: the caller's buffers); operands of one, two or three terms
+hipError_t launch_terms_final(const GemmDims& d, const void* p, const void* q, const Shape& s, const OutSpec& o, hipStream_t st);
 inline GemmDims split3_dims(int64_t M, int64_t N, int64_t K, int qterms, int nb, int pterms = 3) {
   // terms 2 0, 0 2, 1 1, 1 0, 0 1, 0 0 of P and Q, or 2, 1, 0 of P: the small products first
   if (pterms == 1) return GemmDims{M, N, K, K, 3 * K, M * K, 3 * N * K, nb, 3, 0u, 0x012u};

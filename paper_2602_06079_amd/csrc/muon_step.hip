@@ -223,33 +223,54 @@ int collect_batches(const canz_group* g, int n_groups, int out_mode, bool with_p
   });
 }
 
+// Merged steps keep their m x m matrices in fp16 (kernels.h: SymSpec), scaled to the magnitudes of an iteration that stays
+// bounded: f(s) = a s + b s^3 + c s^5 has to keep the singular values in [0, S], S <= 1.3 the largest value they reach from [0, 1] (with 5 % to
+// spare for rounding), and |a + b t + c t^2| <= 3.5 on [0, S^2].  The quintic (3.4445, -4.775, 2.0315) reaches S = 1.202.
+bool bounded_map(const canz_muon_hparams& hp) {
+  auto p = [&](float t) { return hp.a + t * (hp.b + t * hp.c); };
+  constexpr int N = 256;
+  float top = 1.f;
+  for (int i = 0; i <= N; ++i) {
+    const float s = static_cast<float>(i) / N;
+    top = std::max(top, std::fabs(s * p(s * s)));
+  }
+  top *= 1.05f;
+  bool ok = top <= 1.3f;
+  for (int i = 0; i <= N; ++i) {
+    const float s = top * static_cast<float>(i) / N, v = p(s * s);
+    ok = ok && std::fabs(s * v) <= top && std::fabs(v) <= 3.5f;   // NaN: false
+  }
+  return ok;
+}
+
 // Stages of the iteration.  One Newton-Schulz step needs A = X X^T (m^2 n products, upper half), B = aI + bA + cAA (m^3)
 // and X <- B X (2 m^2 n).  The next Gram matrix is A' = B A B, so several steps can stay among the m x m matrices,
 //   B_1 = p(A_1),  A_2 = B_1 (B_1 A_1),  B_2 = p(A_2),  Q = B_2 B_1, ...        (3 m^3 per step after the first)
 // and X be touched once, X <- Q X: with r = m / n and in units of m^2 n, five steps cost 15 + 5 r one by one and
-// 6 + 14 r in stages of 3 + 2.
-// Precision decides how far a stage can go: an error in A_k is not seen by X and grows with a^2 per step in the small
-// singular values.  With the diagonals in fp32 (SymSpec) the update's error against 64 bits is 0.33 to 1.0 of that of
-// single steps in stages of 3, 2, 2, ... over flat, power-law, low-rank and outlier spectra of 2048 and more rows (0.45 on
-// the 4096 x 12288 and 25600 x 5120 shares).  A rounding error of A is a random matrix, whose norm against A's falls
-// like 1 / sqrt(m): at 1024 rows the factor reaches 1.1 on outlier spectra, at 333 rows 1.9.  Almost square matrices have
-// singular values near zero: up to 1.4 there.  A stage of 5 is up to 6 times worse on decaying spectra; a stage of 2 that
-// ends the iteration (nothing corrects X afterwards) up to 1.2 times: at least three steps.  Only for coefficients no
-// more expanding than the quintic's a = 3.4445; the cubic (c = 0) keeps single steps.
-// Speed (us, single steps -> stages): 4 x 25600 x 5120 35000 -> 20900, 5 x 4096 x 12288 14400 -> 10340, 2 x 2048 x 5632 1240 ->
-// 970, 1 x 1536 x 6144 795 -> 570, 1 x 5120 x 8192 3500 -> 3075, 1 x 3000 x 5000 1130 -> 1040; but 1 x 2048 x 3072 463 -> 482,
-// 1 x 1536 x 2304 329 -> 366 (the products of one small matrix leave most of the chip idle, and there are more of them):
-// hence m <= n / 2, from 2560 rows on m <= 2 n / 3; and the spare arrays (Spare) have to fit.  The rule looks at the shape alone, so that a matrix's result does not
-// depend on what shares its launch.
+// 8 + 14 r merged as 3 + 2 (the two terms of the last Q among them).
+// Precision decides how.  An error in A_k is not seen by X and grows with a^2 per step in the small singular values, and Q = B_3 B_2 B_1
+// spans a range of a^3.  So the m x m matrices are fp16 images and fp32 diagonals (kernels.h: SymSpec), Q is a bf16 image and
+// an fp32 diagonal where a later step corrects what its rounding did, and two bf16 terms in the last product, where nothing
+// does.  The first three steps are merged and the last two, with single ones between.  The update's error against 64 bits is then
+// 0.3 to 0.5 of that of single steps for inputs of many comparable directions (Gaussian, plus a low-rank part, outliers,
+// row and column scales, one-sided), and below it, 0.97 at most, for all that were tried (also duplicated rows, rows in groups of eight
+// alike, a constant plus noise, low rank), at 1536 x 3072, 2560 x 3900, 2048 x 8192, 4096 x 12288 and 5120 x 25600, for 3 to
+// 8 steps.  With bf16 images it is up to 2 times that of single steps (columns falling like 1 / j); with a last Q of one term up to 1.7
+// times (groups of alike rows), in bf16 throughout 2.9 times; merging four steps 2 times (constant plus noise).
+// Speed (us, single steps -> merged): 4 x 25600 x 5120 34900 -> 25900, 5 x 4096 x 12288 14400 -> 12600, 1 x 5120 x 13824 5180 -> 4460, 2 x
+// 2048 x 4800 1070 -> 970, 1 x 5120 x 10240 4020 -> 3840; but 2 x 4096 x 6400 4090 -> 4210, 1 x 4096 x 8192 2230 ->
+// 2290, 4 x 2048 x 4096 1430 -> 1470: hence m <= 0.45 n, from 5120 rows on m <= n / 2.
+// The rule looks at the shape and the coefficients alone, so that a matrix's result does not depend on what
+// shares its launch.  The spare arrays (Spare) fit wherever it holds.
 std::vector<int> stage_plan(const Shape& s, const canz_muon_hparams& hp) {
+  const bool wide = s.m >= 1536 && (s.m >= 5120 ? 2 * s.m <= s.n : 20 * s.m <= 9 * s.n);
+  const bool merge = hp.precision == CANZ_PREC_BF16 && hp.ns_steps >= 3 && hp.c != 0.f && wide && bounded_map(hp);
   std::vector<int> stages;
-  const bool wide = (s.m >= 2560 ? 3 * s.m <= 2 * s.n : s.m >= 1536 && 2 * s.m <= s.n) && 3 * s.mp < 2 * s.np;
-  const bool merge = hp.precision == CANZ_PREC_BF16 && hp.ns_steps >= 3 && hp.c != 0.f && hp.a > 0.f && hp.a <= 3.5f && wide;
-  for (int left = hp.ns_steps; left > 0;) {
+  for (int left = hp.ns_steps; left > 0; left -= stages.back()) {
     int len = 1;
-    if (merge) len = stages.empty() ? (hp.ns_steps >= 4 ? 3 : 2) : std::min(2, left);
+    if (merge && stages.empty()) len = left >= 4 ? 3 : 2;
+    if (merge && !stages.empty() && left == 2) len = 2;
     stages.push_back(len);
-    left -= len;
   }
   return stages;
 }
@@ -283,10 +304,11 @@ std::vector<int> group_runs(const std::vector<Batch>& batches, const canz_muon_h
 }
 
 // Where the further m x m arrays of a batch whose steps are merged lie: B A, two more images for the polynomials and their
-// products, five diagonals.  Between a Gram product and the next update neither X nor the X^T that is not in use (xt[cur ^ 1])
-// is read, and they lie side by side: 2 m n elements of two bytes, of which 3 m m images leave at least 512 m bytes
+// products, five diagonals.  Between a Gram product and the next update (or last product) neither X nor the X^T that is not in use
+// (xt[cur ^ 1]) is read, and they lie side by side: 2 m n elements of two bytes, of which 3 m m images leave at least 512 m bytes
 // (3 m < 2 n, both multiples of 256).  The diagonals are at the end that belongs to X^T, since the Gram product leaves that
-// of A while it reads X.  The image that the update multiplies X with must not lie there: it takes the place of A.
+// of A while it reads X.  What X is multiplied with must not lie there: its image takes the place of A and its diagonal that of B,
+// two terms take both.
 struct Spare {
   size_t t, b1, b2, diag;   // byte offsets from the start of the free piece
 };
@@ -394,10 +416,13 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
   }
 
   // The products of one stage (see stage_plan) among the m x m matrices, every shape class of the run side by side;
-  // returns through q[k] the image that X is multiplied with.  `cur`: which X^T buffer is in use.
-  auto stage_bf16 = [&](int len, bool first, int cur, const void* (&q)[MAX_KINDS]) -> int {
+  // q[k]: the image that X is multiplied with (or its two terms, in a last stage of merged steps), dq[k]: its diagonal, if it
+  // is apart.  `cur`: which X^T buffer is in use.
+  const void* q[MAX_KINDS] = {};
+  const float* dq[MAX_KINDS] = {};
+  auto stage_bf16 = [&](int len, bool first, bool last_stage, int cur) -> int {
     GemmBatch gb{};
-    const bool apart = len > 1;   // diagonals kept apart
+    const bool apart = len > 1;
     for (int k = 0; apart && k < nk; ++k) {
       Kind& kd = kind[k];
       const Spare x = spare(kd.s0, kd.nb, cur);
@@ -407,60 +432,68 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
       const int64_t len_d = static_cast<int64_t>(kd.nb) * kd.s0.mp;
       kd.da = dv, kd.dt = dv + len_d, kd.db[0] = dv + 2 * len_d, kd.db[1] = dv + 3 * len_d, kd.db[2] = dv + 4 * len_d;
     }
-    auto da = [&](const Kind& kd) { return apart ? kd.da : nullptr; };
     gb.n = nk;
     for (int k = 0; k < nk; ++k) {
       const Kind& kd = kind[k];
       GemmProblem& pr = gb.pr[k] = GemmProblem{};
       pr.d = kd.gram, pr.p = kd.xw, pr.q = kd.xw, pr.c = kd.a, pr.scale = first ? kd.scale2 : nullptr;
-      pr.sym.diag = da(kd);
+      pr.sym.diag = apart ? kd.da : nullptr;
     }
     CANZ_HIP(CANZ_KERNEL_GRAM, launch_gram_bf16(gb, split, st), "gram kernel");
-    // the product of the symmetric images P (index ip of b) and Y with their diagonals
-    auto mul = [&](const Kind& kd, int ip, const void* y, const float* dy, void* c, float* dc) {
+    // the product of the symmetric images P (index ip of b, unit B) and Y with their diagonals
+    auto mul = [&](const Kind& kd, int ip, const void* y, const float* dy, float unit, void* c, float* dc) {
       GemmProblem pr{};
       pr.d = kd.poly, pr.p = kd.b[ip], pr.q = y, pr.c = c;
-      pr.sym.aux = y, pr.sym.aux2 = kd.b[ip], pr.sym.x = kd.db[ip], pr.sym.y = dy, pr.sym.diag = dc;
+      pr.sym.aux = y, pr.sym.aux2 = kd.b[ip], pr.sym.x = kd.db[ip], pr.sym.y = dy, pr.sym.diag = dc, pr.sym.unit = unit;
       return pr;
     };
+    // B_1 -> b[0] (or, of two steps, b[2]), the later ones -> b[1], the product of the first two -> b[2]: the last product
+    // reads b[1] and b[2], so that b[0], behind A, is free for its diagonal or second term
     int iq = -1;   // where the product of the polynomials so far lies
     for (int i = 0; i < len; ++i) {
       const bool last = i + 1 == len;
-      const int ib = iq == 0 ? 1 : 0, in = 3 - ib - (iq < 0 ? 3 - ib : iq);   // B_i, and (from the second on) the new product
+      const int ib = i > 0 ? 1 : len == 2 ? 2 : 0;
       for (int k = 0; k < nk; ++k) {
         const Kind& kd = kind[k];
         GemmProblem& pr = gb.pr[k] = GemmProblem{};
         pr.d = kd.poly, pr.p = kd.a, pr.q = kd.a, pr.c = apart ? kd.b[ib] : static_cast<void*>(kd.bm);
-        pr.sym.aux = kd.a, pr.sym.x = da(kd), pr.sym.y = da(kd);
-        pr.sym.diag = apart ? kd.db[ib] : nullptr;
+        pr.sym.aux = kd.a;
+        if (apart) pr.sym.x = kd.da, pr.sym.y = kd.da, pr.sym.diag = kd.db[ib];
       }
       gb.n = nk;
       CANZ_HIP(CANZ_KERNEL_POLY, launch_poly_bf16(gb, hp.a, hp.b, hp.c, split, st), "poly kernel");
+      if (!apart) break;
       gb.n = 0;
-      if (!last)
-        for (int k = 0; k < nk; ++k)
-          gb.pr[gb.n++] = mul(kind[k], ib, kind[k].a, da(kind[k]), kind[k].t, kind[k].dt);
+      if (last) {
+        for (int k = 0; k < nk; ++k) {
+          const Kind& kd = kind[k];
+          float* dlast = reinterpret_cast<float*>(kd.bm);
+          gb.pr[gb.n++] = mul(kd, ib, kd.b[iq], kd.db[iq], UNIT_B, kd.a, dlast);
+        }
+        CANZ_HIP(CANZ_KERNEL_POLY, launch_mul_f16(gb, last_stage ? MulResult::Q2 : MulResult::Q, split, st), "product kernel (Q)");
+        break;
+      }
+      for (int k = 0; k < nk; ++k) gb.pr[gb.n++] = mul(kind[k], ib, kind[k].a, kind[k].da, UNIT_A, kind[k].t, kind[k].dt);
       if (iq >= 0)
-        for (int k = 0; k < nk; ++k)
-          gb.pr[gb.n++] = mul(kind[k], ib, kind[k].b[iq], kind[k].db[iq], last ? kind[k].a : kind[k].b[in], last ? nullptr : kind[k].db[in]);
-      if (gb.n > 0) CANZ_HIP(CANZ_KERNEL_POLY, launch_mul_bf16(gb, split, st), "product kernel (B A, Q)");
-      iq = iq < 0 ? ib : in;
-      if (last) break;
+        for (int k = 0; k < nk; ++k) gb.pr[gb.n++] = mul(kind[k], ib, kind[k].b[iq], kind[k].db[iq], UNIT_B, kind[k].b[2], kind[k].db[2]);
+      CANZ_HIP(CANZ_KERNEL_POLY, launch_mul_f16(gb, MulResult::CHAIN, split, st), "product kernel (B A, Q)");
+      iq = iq < 0 ? ib : 2;
       gb.n = nk;
-      for (int k = 0; k < nk; ++k)
-        gb.pr[k] = mul(kind[k], ib, kind[k].t, kind[k].dt, kind[k].a, da(kind[k]));
-      CANZ_HIP(CANZ_KERNEL_POLY, launch_mul_bf16(gb, split, st), "product kernel (B A B)");
+      for (int k = 0; k < nk; ++k) gb.pr[k] = mul(kind[k], ib, kind[k].t, kind[k].dt, UNIT_A, kind[k].a, kind[k].da);
+      CANZ_HIP(CANZ_KERNEL_POLY, launch_mul_f16(gb, MulResult::CHAIN, split, st), "product kernel (B A B)");
     }
-    for (int k = 0; k < nk; ++k) q[k] = apart ? kind[k].a : kind[k].bm;
+    for (int k = 0; k < nk; ++k) {
+      q[k] = apart ? kind[k].a : kind[k].bm;
+      dq[k] = apart ? reinterpret_cast<const float*>(kind[k].bm) : nullptr;
+    }
     return CANZ_OK;
   };
 
   int cur = 0;
   for (size_t sg = 0; sg < stages.size(); ++sg) {
     const bool first_it = sg == 0, last = sg + 1 == stages.size();
-    const void* q[MAX_KINDS] = {};
     if (is_bf16) {
-      if (int rc = stage_bf16(stages[sg], first_it, cur, q)) return rc;
+      if (int rc = stage_bf16(stages[sg], first_it, last, cur)) return rc;
       if (!last) {
         GemmBatch gb{};
         gb.n = nk;
@@ -469,6 +502,7 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
           GemmProblem& pr = gb.pr[k];
           pr.d = kd.upd, pr.p = q[k], pr.q = kd.xt[cur], pr.c = kd.xw, pr.ct = kd.xt[cur ^ 1];
           pr.scale = first_it ? kd.scale : nullptr;
+          pr.sym.x = dq[k], pr.sym.aux = kd.xt[cur];
         }
         CANZ_HIP(CANZ_KERNEL_UPDATE, launch_update_bf16(gb, split, st), "update kernel");
       }
@@ -492,7 +526,8 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
         const int n = batches[lo + k].part[h].n();
         if (n == 0) continue;
         const Shape& s = kd.s0;
-        const T* bk = static_cast<const T*>(q[k]) + kd.first[h] * kd.a_elems;
+        const int terms = is_bf16 && stages[sg] > 1 ? 2 : 1;
+        const T* bk = static_cast<const T*>(q[k]) + kd.first[h] * kd.a_elems * terms;
         const T* xk = kd.xt[cur] + kd.first[h] * kd.x_elems;
         const float* sk = sc1 ? sc1 + kd.first[h] : nullptr;
         const bool tall = kd.shape[h].tall;
@@ -500,7 +535,11 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
         fin.nb = n;
         const void* P = tall ? static_cast<const void*>(xk) : static_cast<const void*>(bk);
         const void* Q = tall ? static_cast<const void*>(bk) : static_cast<const void*>(xk);
-        if (is_bf16)
+        if (terms == 2) {   // the second term first
+          (tall ? fin.ldq : fin.ldp) = 2 * s.mp, (tall ? fin.sq : fin.sp) = 2 * kd.a_elems;
+          fin.nseg = 2, (tall ? fin.qseg : fin.pseg) = 0x01u;
+          CANZ_HIP(CANZ_KERNEL_FINAL, launch_terms_final(fin, P, Q, kd.shape[h], kd.out[h], st), "final kernel");
+        } else if (is_bf16)
           CANZ_HIP(CANZ_KERNEL_FINAL, launch_final_bf16(fin, P, Q, sk, split, kd.shape[h], kd.out[h], st), "final kernel");
         else
           CANZ_HIP(CANZ_KERNEL_FINAL, launch_final_f32(fin, P, Q, sk, kd.shape[h], kd.out[h], st), "final kernel");

@@ -681,7 +681,7 @@ int run_batch_terms(const canz_shampoo_group& g, int first, int nb, bool togethe
   const __bf16* gt_terms = stat16 ? gpt : terms(c.g3t);
   CANZ_HIP(CANZ_KERNEL_SH_APPLY, launch_split3(split3_dims(rp2, cp2, rp2, stat16 ? 1 : 3, nb), side[0].root3, gt_terms, tmp, st),
            "preconditioning kernel (left)");
-  CANZ_HIP(CANZ_KERNEL_SH_APPLY, launch_split3_final(split3_dims(rp2, cp2, cp2, 3, nb), tmp, side[1].root3, s, o, st),
+  CANZ_HIP(CANZ_KERNEL_SH_APPLY, launch_terms_final(split3_dims(rp2, cp2, cp2, 3, nb), tmp, side[1].root3, s, o, st),
            "preconditioning kernel (right)");
   return CANZ_OK;
 }

@@ -1287,7 +1287,7 @@ int run_batch(const canz_soap_group& g, int first, int nb, Rot rot, const canz_s
     OutSpec ro{};
     ro.out = to, ro.out_dtype = CANZ_DT_F32, ro.out_mode = CANZ_OUT_DELTA, ro.decay = 1.f, ro.neg_lr_scale = 1.f;
     if (!u.left) {   // X Q_R
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, launch_split3_final(split3_dims(rp2, cp2, cp2, 3, nb, terms), x, pan(c.qr3t), whole, ro, st),
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, launch_terms_final(split3_dims(rp2, cp2, cp2, 3, nb, terms), x, pan(c.qr3t), whole, ro, st),
                "rotation (right)");
       return CANZ_OK;
     }
@@ -1296,7 +1296,7 @@ int run_batch(const canz_soap_group& g, int first, int nb, Rot rot, const canz_s
                "rotation (right)");
       x = pan(c.t3), terms = 3;
     }
-    CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, launch_split3_final(split3_dims(rp2, cp2, rp2, terms, nb), pan(c.ql3t), x, whole, ro, st),
+    CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, launch_terms_final(split3_dims(rp2, cp2, rp2, terms, nb), pan(c.ql3t), x, whole, ro, st),
              "rotation (left)");
     return CANZ_OK;
   };
@@ -1430,7 +1430,7 @@ int run_batch(const canz_soap_group& g, int first, int nb, Rot rot, const canz_s
 
     // rotation back, the last product writes the update
     if (!u.left) {
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, launch_split3_final(split3_dims(rp2, cp2, cp2, 3, nb), pan(c.n3), pan(c.qr3), s, o, st),
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, launch_terms_final(split3_dims(rp2, cp2, cp2, 3, nb), pan(c.n3), pan(c.qr3), s, o, st),
                "back rotation (right)");
     } else {
       const __bf16* n = pan(c.n3);
@@ -1439,7 +1439,7 @@ int run_batch(const canz_soap_group& g, int first, int nb, Rot rot, const canz_s
                  "back rotation (right)");
         n = pan(c.y3);
       }
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, launch_split3_final(split3_dims(rp2, cp2, rp2, 3, nb), pan(c.ql3), n, s, o, st),
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, launch_terms_final(split3_dims(rp2, cp2, rp2, 3, nb), pan(c.ql3), n, s, o, st),
                "back rotation (left)");
     }
   }

@@ -1,17 +1,17 @@
-"""Muon steps whose Newton-Schulz steps are merged (two or three at a time among the m x m matrices): parity with the
-oracle at the edges of the rule that selects them, for every split of the step count into stages, and the workspace."""
+"""Muon steps whose Newton-Schulz steps are merged (two or three at a time among the m x m matrices): which shapes and
+coefficients they are taken for (launches counted), parity with 64 bits at the edges of that rule and for every split of the step
+count into stages, accuracy on structured inputs against single steps, and the workspace."""
 import numpy as np
 import pytest
 
-from oracle import muon as OM
-from paper_2602_06079_amd import workloads as W
-from tests.gpu_harness import DeviceGroup, log, oracle_hparams, rel_fro, run_step, widen
+from tests.gpu_harness import log
 
 pytestmark = pytest.mark.gpu
 
-# The bound of single steps (each stored operand rounded once per step, 2^-9 relative, slope of the map at most 1.7: about
-# 1e-2 for Gaussian inputs) holds for merged ones, whose operands are rounded less often.
-TOL = 1.0e-2
+# The error of a step is compared with that of single steps on bf16 operands (every stored operand rounded once per step, products
+# in 64 bits), computed here: within 5 %, how far the error of one draw scatters.  Where all steps are merged it is about half.
+TOL = {False: 1.05, True: 0.6}
+QUINTIC = (3.4445, -4.7750, 2.0315)
 
 
 @pytest.fixture(scope="module")
@@ -23,79 +23,176 @@ def canz():
     return binding
 
 
-def _inputs(seed, rows, cols, n):
-    grads = [W.gen_grad(seed, i, rows, cols)[0] for i in range(n)]
-    moms = [W.gen_normal_f32(seed, i, 5, rows, cols, 0.01) for i in range(n)]
-    params = [W.gen_param(seed, i, rows, cols) for i in range(n)]
-    return grads, moms, params
+def _iterate(x, coef, steps):
+    """The iteration in the precision of x."""
+    for _ in range(steps):
+        a = x @ x.t()
+        x = coef[0] * x + (coef[1] * a + coef[2] * (a @ a)) @ x
+    return x
 
 
-def _check(dg, ins, hp, name):
-    ohp = oracle_hparams(hp)
-    for i, (g, m, p) in enumerate(zip(*ins)):
-        ref = OM.muon_step(widen(g), widen(m), ohp, widen(p))
-        got = dg.out_host(i) - (widen(p) * (1.0 - ohp.lr * ohp.weight_decay))
-        err = rel_fro(got, ref["delta"])
-        log("%s matrix %d: %.3g" % (name, i, err))
-        assert err <= TOL, "%s matrix %d: error %.3g" % (name, i, err)
-        assert rel_fro(dg.mom_host(i), ref["mom"]) <= 1e-6
+def _single_steps_bf16(x, coef, steps):
+    """Single steps on bf16 operands: X, A and B rounded to bf16, products in 64 bits."""
+    import torch
+    bf = lambda t: t.to(torch.float32).to(torch.bfloat16).double()  # noqa: E731
+    scale = 1.0 / float(x.norm())
+    x = bf(x)
+    for k in range(steps):
+        s = scale if k == 0 else 1.0
+        a = bf(x @ x.t() * (s * s))
+        b = coef[1] * a + coef[2] * (a @ a)
+        b.diagonal().add_(coef[0])
+        x = bf(b) @ x * s
+        if k + 1 < steps:
+            x = bf(x)
+    return x
 
 
-@pytest.mark.parametrize("rows,cols,steps", [
-    (1536, 3072, 5),   # the smallest, whole tiles
-    (1535, 3072, 5),   # just below: single steps
-    (3075, 1537, 5),   # odd, tall: padding in every matrix, the swapped last product
-    (1536, 3071, 5),   # just too square: single steps
-    (2560, 3840, 5),   # the spare arrays would just not fit: single steps
-    (2560, 3900, 5),   # the wider rule from 2560 rows on, the spare arrays just fit
-    (1600, 3300, 3),   # stages 2 + 1
-    (1600, 3300, 4),   # stages 3 + 1
-    (1600, 3300, 6),   # stages 3 + 2 + 1
-    (1600, 3300, 2),   # not merged
+def _step(canz, inputs, hp):
+    """One step from zero momentum on fp32 gradients, Delta W out; the launches of the step by kind."""
+    import torch
+    rows, cols = inputs[0].shape
+    grp = canz.Group(rows=rows, cols=cols, grad=inputs, mom=[torch.zeros_like(x) for x in inputs], out=[torch.zeros_like(x) for x in inputs],
+                     grad_dtype=canz.DT_F32, out_dtype=canz.DT_F32)
+    need = canz.canz_muon_workspace_bytes([grp], hp)
+    guard = 1 << 16
+    ws = torch.full((need + guard,), 0xFF, dtype=torch.uint8, device="cuda")   # every byte a NaN: nothing may be read unwritten
+    canz.canz_profile_enable(256)
+    try:
+        canz.canz_muon_step([grp], hp, ws, need, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        counts = {k: n for k, (_ms, n) in canz.canz_profile_collect().items()}
+    finally:
+        canz.canz_profile_disable()
+    assert bool((ws[need:] == 0xFF).all())
+    return grp.out, counts
+
+
+def _hparams(canz, coef=QUINTIC, steps=5):
+    return canz.Hparams(beta=0.0, lr=1.0, ns_steps=steps, a=coef[0], b=coef[1], c=coef[2], scale_mode=canz.SCALE_NONE, out_mode=canz.OUT_DELTA)
+
+
+def _expected(torch, x, coef, steps):
+    x64 = x.double()
+    x64 = x64.t() if x.shape[0] > x.shape[1] else x64
+    coef = [float(np.float32(v)) for v in coef]
+    want = _iterate((x64 / x64.norm()).contiguous(), coef, steps)
+    return -(want.t() if x.shape[0] > x.shape[1] else want)
+
+
+def _stages(steps):
+    """3, single ones, 2: how merged steps are split."""
+    if steps < 3:
+        return [1] * steps
+    first = 3 if steps >= 4 else 2
+    left = steps - first
+    return [first] + [1] * left if left < 2 else [first] + [1] * (left - 2) + [2]
+
+
+@pytest.mark.parametrize("rows,cols,steps,merged", [
+    (1536, 10923, 5, True),    # the fewest rows
+    (1535, 11000, 5, False),   # too few rows
+    (10925, 1537, 5, True),    # odd, tall: padding in every matrix, the swapped last product
+    (2754, 6120, 5, True),     # 0.45 of the columns ...
+    (2755, 6120, 5, False),    # ... and more
+    (5120, 10240, 5, True),    # half of the columns, from 5120 rows on
+    (5119, 10240, 5, False),
+    (10240, 5121, 5, False),
+    (2048, 8200, 1, False),
+    (2048, 8200, 2, False),
+    (2048, 8200, 3, True),     # stages 2 + 1
+    (2048, 8200, 4, True),     # 3 + 1
+    (8200, 2048, 6, True),     # 3 + 1 + 2: the second merged stage with the X^T buffers swapped
+    (2048, 8200, 7, True),     # 3 + 1 + 1 + 2
 ])
-def test_merged_steps(canz, rows, cols, steps):
-    ins = _inputs(81, rows, cols, 2)
-    hp = canz.Hparams(ns_steps=steps, nesterov=True, weight_decay=0.1)
-    dg = DeviceGroup(canz, rows, cols, ins[0], ins[1], outs=ins[2])
-    run_step(canz, [dg], hp)
-    _check(dg, ins, hp, "%dx%d, %d steps" % (rows, cols, steps))
+def test_merged_steps(canz, rows, cols, steps, merged):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(rows + cols + steps)
+    inputs = [torch.randn(rows, cols, generator=g, device="cuda") * 0.02 for _ in range(2 if rows * cols < 1 << 25 else 1)]
+    out, counts = _step(canz, inputs, _hparams(canz, steps=steps))
+    stages = _stages(steps) if merged else [1] * steps
+    # per stage one Gram product and one product with X (the last one writes the output); of n merged steps n polynomials, for
+    # every one but the last B A (with Q) and B A B, and Q
+    assert counts["gram"] == len(stages) and counts["update"] == len(stages) - 1 and counts["final"] == 1
+    assert counts["poly"] == sum(1 if n == 1 else n + 2 * (n - 1) + 1 for n in stages)
+    for x, got in zip(inputs, out):
+        want = _expected(torch, x, QUINTIC, steps)
+        err = float((got.double() - want).norm() / want.norm())
+        x64 = x.double() if rows <= cols else x.double().t().contiguous()
+        single = _single_steps_bf16(x64, QUINTIC, steps)
+        single = float((-(single if rows <= cols else single.t()) - want).norm() / want.norm())
+        log("%dx%d, %d steps: %.3g, single steps %.3g" % (rows, cols, steps, err, single))
+        assert err <= TOL[1 not in stages] * single
 
 
-def test_merged_steps_share_launches(canz):
-    """Wide and tall matrices of one class, a second merged class and one with single steps in one call: parity, and the
-    same bits as each group alone."""
-    shapes = [(1536, 3328, 2), (3328, 1536, 1), (1792, 3584, 1), (512, 768, 2)]
-    hp = canz.Hparams(weight_decay=0.1)
-    ins = [_inputs(90 + k, *s) for k, s in enumerate(shapes)]
-    make = lambda k: DeviceGroup(canz, shapes[k][0], shapes[k][1], ins[k][0], ins[k][1], outs=ins[k][2])  # noqa: E731
-    together = [make(k) for k in range(len(shapes))]
-    run_step(canz, together, hp)
-    for k, s in enumerate(shapes):
-        _check(together[k], ins[k], hp, "group %d" % k)
-        alone = make(k)
-        run_step(canz, [alone], hp)
-        for i in range(s[2]):
-            assert np.array_equal(alone.out_host(i), together[k].out_host(i))
+def _structured(torch, kind, rows, cols):
+    g = torch.Generator(device="cuda").manual_seed(len(kind) * 1000 + rows)
+    n = lambda *s: torch.randn(*s, generator=g, device="cuda")  # noqa: E731
+    j = torch.arange(1, cols + 1, device="cuda").float()
+    i = torch.arange(1, rows + 1, device="cuda").float()[:, None]
+    if kind == "columns fall like 1/j":
+        return n(rows, cols) / j
+    if kind == "rows fall like 1/i":
+        return n(rows, cols) / i
+    if kind == "pairs of alike rows":
+        return n((rows + 1) // 2, cols).repeat_interleave(2, 0)[:rows].contiguous()
+    if kind == "eight alike rows":
+        return n((rows + 7) // 8, cols).repeat_interleave(8, 0)[:rows].contiguous()
+    if kind == "constant and noise":
+        return 1.0 + 0.1 * n(rows, cols)
+    if kind == "one-sided":
+        return n(rows, cols).relu()
+    if kind == "one large row":
+        x = n(rows, cols)
+        x[0] *= 100
+        return x
+    if kind == "two levels":
+        x = n(rows, cols)
+        x[rows // 2:] *= 0.01
+        return x
+    assert kind == "low rank"
+    return n(rows, rows // 8) @ n(rows // 8, cols) + 5e-3 * n(rows, cols)
 
 
-def test_cubic_and_expanding_coefficients_keep_single_steps(canz):
-    rows, cols = 1536, 3072
-    ins = _inputs(83, rows, cols, 1)
-    for co in ((1.5, -0.5, 0.0), (3.6, -4.9, 2.05)):
-        hp = canz.Hparams(a=co[0], b=co[1], c=co[2])
-        dg = DeviceGroup(canz, rows, cols, ins[0], ins[1], outs=ins[2])
-        groups = [dg.group()]
-        # three X arrays, two m x m arrays and the k-split scratch: none of the merged steps' arrays
-        assert canz.canz_muon_workspace_bytes(groups, hp) < 2 * (3 * rows * cols + 2 * rows * rows) + (64 << 20) + (1 << 20)
-        run_step(canz, [dg], hp)
-        ohp = oracle_hparams(hp)
-        ref = OM.muon_step(widen(ins[0][0]), widen(ins[1][0]), ohp, widen(ins[2][0]))
-        assert rel_fro(dg.out_host(0) - widen(ins[2][0]), ref["delta"]) <= 2 * TOL
+@pytest.mark.parametrize("coef", [QUINTIC, (3.5, -5.2, 2.3)])
+@pytest.mark.parametrize("rows,cols", [(1536, 11000), (2754, 6120)])
+def test_structured_inputs_are_no_less_accurate_than_in_single_steps(canz, rows, cols, coef):
+    """Gram matrices with large off-diagonal elements, and singular values of every size: no further from 64 bits than five single
+    steps (the worst that was measured is 0.97 of theirs)."""
+    import torch
+    for kind in ("columns fall like 1/j", "rows fall like 1/i", "pairs of alike rows", "eight alike rows", "constant and noise", "one-sided",
+                 "one large row", "two levels", "low rank"):
+        x = _structured(torch, kind, rows, cols)
+        (got,), counts = _step(canz, [x], _hparams(canz, coef))
+        assert counts["gram"] == 2
+        want = _expected(torch, x, coef, 5)
+        err = float((got.double() - want).norm() / want.norm())
+        single = float((-_single_steps_bf16(x.double(), coef, 5) - want).norm() / want.norm())
+        log("%dx%d %s: %.3g, single steps %.3g" % (rows, cols, kind, err, single))
+        assert err <= TOL[False] * single, kind
 
 
-def test_workspace_of_small_merged_batches_is_unchanged(canz):
-    """The merged steps' arrays lie in X and the X^T that is not in use: no more is asked for than for single steps."""
-    one = canz.Group(rows=1536, cols=3072, mom=[], n_mats=1)
-    rows, cols = 1536, 3072
+@pytest.mark.parametrize("coef", [
+    (1.5, -0.5, 0.0),      # cubic
+    (3.6, -4.9, 2.05),     # more expanding than 3.5
+    (3.4, -2.0, 0.5),      # singular values leave [0, 1.3]
+    (3.4445, -9.0, 2.0),   # the polynomial itself does not stay small
+])
+def test_coefficients_that_keep_single_steps(canz, coef):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(83)
+    x = torch.randn(1536, 11000, generator=g, device="cuda")
+    (got,), counts = _step(canz, [x], _hparams(canz, coef, 3))
+    assert counts["gram"] == 3 and counts["poly"] == 3 and counts["update"] == 2
+    want = _expected(torch, x, coef, 3)
+    single = float((-_single_steps_bf16(x.double(), coef, 3) - want).norm() / want.norm())
+    assert float((got.double() - want).norm() / want.norm()) <= TOL[False] * single
+
+
+def test_workspace_of_merged_batches_is_that_of_single_steps(canz):
+    """The merged steps' arrays lie in X and the X^T that is not in use, and where A and B are."""
+    rows, cols = 2048, 8192
+    one = canz.Group(rows=rows, cols=cols, mom=[], n_mats=1)
     need = canz.canz_muon_workspace_bytes([one], canz.Hparams())
+    assert need == canz.canz_muon_workspace_bytes([one], canz.Hparams(a=1.5, b=-0.5, c=0.0))
     assert need < 2 * (3 * rows * cols + 2 * rows * rows) + (64 << 20) + (1 << 20)
