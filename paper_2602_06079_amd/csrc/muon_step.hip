@@ -259,11 +259,13 @@ bool bounded_map(const canz_muon_hparams& hp) {
 // times (groups of alike rows), in bf16 throughout 2.9 times; merging four steps 2 times (constant plus noise).
 // Speed (us, single steps -> merged): 4 x 25600 x 5120 34900 -> 25900, 5 x 4096 x 12288 14400 -> 12600, 1 x 5120 x 13824 5180 -> 4460, 2 x
 // 2048 x 4800 1070 -> 970, 1 x 5120 x 10240 4020 -> 3840; but 2 x 4096 x 6400 4090 -> 4210, 1 x 4096 x 8192 2230 ->
-// 2290, 4 x 2048 x 4096 1430 -> 1470: hence m <= 0.45 n, from 5120 rows on m <= n / 2.
-// The rule looks at the shape and the coefficients alone, so that a matrix's result does not depend on what
+// 2290, 4 x 2048 x 4096 1430 -> 1470: hence m <= 0.45 n, from 5120 rows on m <= n / 2.  Merged classes do not share launches with
+// single-step ones (group_runs): a matrix of fewer than 256 update tiles, which would have shared them, loses more by
+// that than it gains (1 x 2048 x 6144 with three smaller classes 1300 -> 1380, 1 x 4096 x 1536 550 -> 760; 1 x 9728 x 2560 1960 -> 1850): hence m n >=
+// 2^24.  The rule looks at the shape and the coefficients alone, so that a matrix's result does not depend on what
 // shares its launch.  The spare arrays (Spare) fit wherever it holds.
 std::vector<int> stage_plan(const Shape& s, const canz_muon_hparams& hp) {
-  const bool wide = s.m >= 1536 && (s.m >= 5120 ? 2 * s.m <= s.n : 20 * s.m <= 9 * s.n);
+  const bool wide = s.m >= 1536 && s.m * s.n >= (int64_t(1) << 24) && (s.m >= 5120 ? 2 * s.m <= s.n : 20 * s.m <= 9 * s.n);
   const bool merge = hp.precision == CANZ_PREC_BF16 && hp.ns_steps >= 3 && hp.c != 0.f && wide && bounded_map(hp);
   std::vector<int> stages;
   for (int left = hp.ns_steps; left > 0; left -= stages.back()) {
@@ -276,27 +278,31 @@ std::vector<int> stage_plan(const Shape& s, const canz_muon_hparams& hp) {
 }
 
 // Launch batches that are too small to fill the chip on their own for long (fewer than 8
-// rounds of update tiles on 256 CUs) are run together, up to MAX_KINDS of them: their Gram,
-// polynomial and update products then share launches, so they must agree in their stages (which
-// depend on the shape alone: a matrix's result does not depend on what shares its launch).
-// first[i] .. first[i + 1] are the batches of run i.  Only in bf16 mode; the fp32 verification path keeps one batch per run.
+// rounds of update tiles on 256 CUs) are run together, up to MAX_KINDS consecutive ones of them: their Gram,
+// polynomial and update products then share launches.  Batches that share launches must agree in their stages (which
+// depend on the shape alone: a matrix's result does not depend on what shares its launch), so merged and single-step batches of
+// such a window are two runs; they are put in that order.  first[i] .. first[i + 1] are the batches of run i.  Only in bf16
+// mode; the fp32 verification path keeps one batch per run.
 constexpr int64_t SMALL_BATCH_TILES = 8 * 256;
-std::vector<int> group_runs(const std::vector<Batch>& batches, const canz_muon_hparams& hp) {
+std::vector<int> group_runs(std::vector<Batch>& batches, const canz_muon_hparams& hp) {
   std::vector<int> first;
   const int n = static_cast<int>(batches.size());
   for (int i = 0; i < n;) {
-    first.push_back(i);
     int j = i + 1;
     if (hp.precision == CANZ_PREC_BF16 && batches[i].update_tiles() < SMALL_BATCH_TILES) {
       int64_t elems = batches[i].s0.mp * batches[i].s0.np * batches[i].nb;
-      while (j < n && j - i < MAX_KINDS && batches[j].update_tiles() < SMALL_BATCH_TILES &&
-             stage_plan(batches[j].s0, hp) == stage_plan(batches[i].s0, hp)) {
+      while (j < n && j - i < MAX_KINDS && batches[j].update_tiles() < SMALL_BATCH_TILES) {
         const int64_t more = batches[j].s0.mp * batches[j].s0.np * batches[j].nb;
         if (elems + more > MAX_BATCH_ELEMS) break;
         elems += more;
         ++j;
       }
     }
+    const std::vector<int> plan = stage_plan(batches[i].s0, hp);
+    const auto rest = std::stable_partition(batches.begin() + i, batches.begin() + j,
+                                            [&](const Batch& b) { return stage_plan(b.s0, hp) == plan; });
+    first.push_back(i);
+    if (const int k = static_cast<int>(rest - batches.begin()); k < j) first.push_back(k);   // there are two plans at most
     i = j;
   }
   first.push_back(n);

@@ -4,7 +4,8 @@ count into stages, accuracy on structured inputs against single steps, and the w
 import numpy as np
 import pytest
 
-from tests.gpu_harness import log
+from paper_2602_06079_amd import workloads as W
+from tests.gpu_harness import DeviceGroup, log, run_step
 
 pytestmark = pytest.mark.gpu
 
@@ -90,8 +91,9 @@ def _stages(steps):
 
 
 @pytest.mark.parametrize("rows,cols,steps,merged", [
-    (1536, 10923, 5, True),    # the fewest rows
+    (1536, 10923, 5, True),    # the smallest: 1536 rows and 2^24 elements
     (1535, 11000, 5, False),   # too few rows
+    (1536, 10922, 5, False),   # too few elements
     (10925, 1537, 5, True),    # odd, tall: padding in every matrix, the swapped last product
     (2754, 6120, 5, True),     # 0.45 of the columns ...
     (2755, 6120, 5, False),    # ... and more
@@ -187,6 +189,35 @@ def test_coefficients_that_keep_single_steps(canz, coef):
     want = _expected(torch, x, coef, 3)
     single = float((-_single_steps_bf16(x.double(), coef, 3) - want).norm() / want.norm())
     assert float((got.double() - want).norm() / want.norm()) <= TOL[False] * single
+
+
+def _inputs(seed, rows, cols, n):
+    grads = [W.gen_grad(seed, i, rows, cols)[0] for i in range(n)]
+    moms = [W.gen_normal_f32(seed, i, 5, rows, cols, 0.01) for i in range(n)]
+    params = [W.gen_param(seed, i, rows, cols) for i in range(n)]
+    return grads, moms, params
+
+
+def test_what_shares_a_call_changes_no_bits(canz):
+    """Wide and tall matrices of a merged class, a second merged class and single-step ones between them in one call: the same
+    bits as each group alone; the single-step classes share their launches, the merged ones theirs."""
+    shapes = [(512, 768, 2), (1536, 11008, 1), (11008, 1536, 1), (768, 640, 1), (2048, 8448, 1)]
+    hp = canz.Hparams(weight_decay=0.1)
+    ins = [_inputs(90 + k, *s) for k, s in enumerate(shapes)]
+    make = lambda k: DeviceGroup(canz, shapes[k][0], shapes[k][1], ins[k][0], ins[k][1], outs=ins[k][2])  # noqa: E731
+    together = [make(k) for k in range(len(shapes))]
+    canz.canz_profile_enable(256)
+    try:
+        run_step(canz, together, hp)
+        counts = {k: n for k, (_ms, n) in canz.canz_profile_collect().items()}
+    finally:
+        canz.canz_profile_disable()
+    assert counts["gram"] == 5 + 2
+    for k, s in enumerate(shapes):
+        alone = make(k)
+        run_step(canz, [alone], hp)
+        for i in range(s[2]):
+            assert np.array_equal(alone.out_host(i), together[k].out_host(i))
 
 
 def test_workspace_of_merged_batches_is_that_of_single_steps(canz):
