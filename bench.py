@@ -647,20 +647,19 @@ def main():
         (args.steps, ms_per_step, float(np.median(per_step)), min(per_step)))
 
     # ---- work accounting
-    flops_step = float(sum(ns_flops(s["rows"][p], s["cols"][p], hp.ns_steps) for g in groups for p in g))
-    tflops = flops_step / (ms_per_step * 1e-3) / 1e12
-    # FLOPs per launch kind and step: "algorithmic" as the method writes them (2 m^2 n for the
-    # Gram and update products, 2 m^3 for the square); "issued" = what the MFMA units execute:
-    # padded extents, only the tiles on or above the diagonal for the symmetric products, and where the library
-    # merges steps (canz.h) one Gram and update product per stage and three more m x m products per merged step.
+    # FLOPs per launch kind and step, of the products that are computed: "algorithmic" 2 m^2 n for a product with X,
+    # 2 m^3 for one of m x m matrices; "issued" = what the MFMA units execute: padded extents, only the tiles on or above
+    # the diagonal for the symmetric products, two products of terms in a merged last product.  Where the library merges
+    # steps (canz.h: the quintic of this benchmark keeps its iteration bounded) there is one Gram product and one product with X
+    # per stage, and n merged steps take n polynomials and n - 1 times B A, B A B and Q.
     def stages(m, n):
-        wide = 3 * m <= 2 * n if m >= 2560 else m >= 1536 and 2 * m <= n
-        if not (bf16 and hp.ns_steps >= 3 and hp.c != 0 and 0 < hp.a <= 3.5 and wide):
-            return hp.ns_steps, hp.ns_steps
-        lens = [3 if hp.ns_steps >= 4 else 2]
+        wide = m >= 1536 and m * n >= 1 << 24 and (2 * m <= n if m >= 5120 else 20 * m <= 9 * n)
+        lens = []
         while sum(lens) < hp.ns_steps:
-            lens.append(min(2, hp.ns_steps - sum(lens)))
-        return len(lens), sum(x + 3 * (x - 1) for x in lens)
+            left = hp.ns_steps - sum(lens)
+            merge = bf16 and hp.ns_steps >= 3 and wide
+            lens.append((3 if left >= 4 else 2) if merge and not lens else 2 if merge and left == 2 else 1)
+        return len(lens), sum(x + 3 * (x - 1) for x in lens), lens[-1] if lens else 0
 
     def pad(x):
         return (x + 255) // 256 * 256
@@ -673,16 +672,17 @@ def main():
         m, n = min(rows, cols), max(rows, cols)
         mp, np_ = pad(m), pad(n)
         tri = (mp // 256) * (mp // 256 + 1) // 2 * 65536 if bf16 else mp * mp
-        kind_flops["gram"] += 2.0 * m * m * n * len(g) * hp.ns_steps
-        kind_flops["poly"] += 2.0 * m ** 3 * len(g) * hp.ns_steps
-        kind_flops["update"] += 2.0 * m * m * n * len(g) * (hp.ns_steps - 1)
+        n_x, n_m, last = stages(m, n)   # Gram products (= products with X), products of m x m matrices, steps in the last stage
+        kind_flops["gram"] += 2.0 * m * m * n * len(g) * n_x
+        kind_flops["poly"] += 2.0 * m ** 3 * len(g) * n_m
+        kind_flops["update"] += 2.0 * m * m * n * len(g) * (n_x - 1)
         kind_flops["final"] += 2.0 * m * m * n * len(g)
-        n_x, n_m = stages(m, n)   # Gram products (= products with X), products of m x m matrices
         kind_issued["gram"] += 2.0 * tri * np_ * len(g) * n_x
         kind_issued["poly"] += 2.0 * tri * mp * len(g) * n_m
         kind_issued["update"] += 2.0 * mp * mp * np_ * len(g) * (n_x - 1)
-        kind_issued["final"] += 2.0 * mp * mp * np_ * len(g)
+        kind_issued["final"] += 2.0 * mp * mp * np_ * len(g) * (2 if last > 1 else 1)
     issued_step = sum(kind_issued.values())
+    tflops = sum(kind_flops.values()) / (ms_per_step * 1e-3) / 1e12
     kernels = {}
     for k, (ms, n) in prof.items():
         if n:
@@ -694,8 +694,8 @@ def main():
                 kernels[k]["tflops_issued"] = kind_issued[k] * args.steps / (ms * 1e-3) / 1e12
                 kernels[k]["tflops_effective"] = kind_flops[k] * args.steps / (ms * 1e-3) / 1e12
     dom = max((k for k in kernels if k in kind_flops), key=lambda k: kernels[k]["ms_per_step"])
-    # per launch: the update and final launches do what the method writes, the others by their issued share
-    dom_flops_per_launch = (kind_flops if dom == "final" or not bf16 else kind_issued)[dom] / kernels[dom]["launches_per_step"]
+    # per launch: update and final launches by what they compute, the others by their issued share
+    dom_flops_per_launch = (kind_flops if dom in ("update", "final") or not bf16 else kind_issued)[dom] / kernels[dom]["launches_per_step"]
     dom_issued_per_launch = kind_issued[dom] / kernels[dom]["launches_per_step"]
     achieved = dom_flops_per_launch / (kernels[dom]["avg_ms"] * 1e-3) / 1e12
     achieved_issued = dom_issued_per_launch / (kernels[dom]["avg_ms"] * 1e-3) / 1e12
@@ -768,7 +768,7 @@ def main():
                                 sorted({(s["rows"][p], s["cols"][p]) for g in groups for p in g}), len(groups),
                                 hp.ns_steps),
                    "tp": tp, "elements": total_elems},
-        "tflops_algorithmic": tflops, "ns_flops_per_step": flops_step,
+        "tflops_algorithmic": tflops, "ns_flops_per_step": sum(kind_flops.values()),
         "tflops_issued": issued_step / (ms_per_step * 1e-3) / 1e12, "issued_flops_per_step": issued_step,
         "frac_mfma_peak_issued": issued_step / (ms_per_step * 1e-3) / 1e12 / peak,
         "frac_mfma_peak_algorithmic": tflops / peak,
