@@ -745,12 +745,17 @@ struct OneProblem {
   const __bf16* P;
   const __bf16* Q;
 };
-struct ManyProblems {
+template <int MAX>
+struct ManyProblemsOf {
   static constexpr bool multi = true;
+  static constexpr int max = MAX;
   int n;
-  int begin[MAX_PROBLEMS + 1];  // first logical tile of each problem, then the total
-  GemmProblem pr[MAX_PROBLEMS];
+  int begin[MAX + 1];  // first logical tile of each problem, then the total
+  GemmProblem pr[MAX];
 };
+// Room for two problems of each shape class only where a launch holds two: every block reads the descriptor first.
+template <int EPI>
+using ManyProblems = ManyProblemsOf<EPI == EPI_MUL || EPI == EPI_B3_SYM ? MAX_PROBLEMS : MAX_KINDS>;
 
 template <int EPI, bool SPLIT, typename Args>
 __global__ __launch_bounds__(NTHREADS) void k_gemm_nt_bf16(Args args, EpiArgs e_launch, Shape s, OutSpec o) {
@@ -835,7 +840,8 @@ __global__ __launch_bounds__(NTHREADS) void k_gemm_nt_bf16(Args args, EpiArgs e_
   // ---- global -> LDS: panel (tile row, k-step) is 16 KiB contiguous; wavefront w copies the
   //      1 KiB pieces w, w+4, w+8, w+12 of both panels, lane l the 16 bytes at l * 16.
   const int64_t nkb = d.K / BK;
-  const int64_t nkp = d.ldp / BK, nkq = d.ldq / BK;   // panels per row block
+  // panels per row block (operands that are a part of longer rows: only of the last products and those of several terms)
+  const int64_t nkp = epi_terms(EPI) || epi_final(EPI) ? d.ldp / BK : nkb, nkq = epi_terms(EPI) || epi_final(EPI) ? d.ldq / BK : nkb;
   const __bf16* pl = P + static_cast<int64_t>(b) * d.sp + (static_cast<int64_t>(tm) * nkp + k_begin) * PANEL_ELEMS + wave * 512 + lane * 8;
   const __bf16* ql = Q + static_cast<int64_t>(b) * d.sq + (static_cast<int64_t>(tn) * nkq + k_begin) * PANEL_ELEMS + wave * 512 + lane * 8;
   // operands of several terms: where the next panel of each is (the panels are requested in order)
@@ -1097,7 +1103,8 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
   const int wm = wave >> 1, wn = wave & 1;
   const int64_t nkb = d.K / BK;
   const int nk = static_cast<int>(nkb) * (epi_terms(EPI) ? d.nseg : 1);
-  const int64_t nkp = d.ldp / BK, nkq = d.ldq / BK;   // panels per row block
+  // panels per row block (operands that are a part of longer rows: only of the last products and those of several terms)
+  const int64_t nkp = epi_terms(EPI) || epi_final(EPI) ? d.ldp / BK : nkb, nkq = epi_terms(EPI) || epi_final(EPI) ? d.ldq / BK : nkb;
 
   // global -> LDS: a stage is 16 pieces of 1 KiB (8 of P, 8 of Q); wavefront w copies the
   // pieces w and w + 4 of both, lane l the 16 bytes at l * 16
@@ -1170,9 +1177,6 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
   // Where the elements of 32 x 32 tile (i, j) of the wavefront's part lie in a panel image: a part that is the same for
   // all lanes, a lane's own offset (two for the straight image, by the parity of the group of 8 rows; four for the
   // transposed one, by group) and a constant.
-  auto straight_at = [&](int i, int j) {
-    return (static_cast<int64_t>(row_w >> 8) * (d.N >> 5) + ((col_w + 32 * j) >> 5)) * PANEL_ELEMS + ((row_w & 255) + 32 * i) * PANEL_K;
-  };
   auto transposed_at = [&](int i, int j) {
     return (static_cast<int64_t>(col_w >> 8) * (d.M >> 5) + ((row_w + 32 * i) >> 5)) * PANEL_ELEMS + ((col_w & 255) + 32 * j) * PANEL_K;
   };
@@ -1432,13 +1436,14 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      __bf16* const at = C + straight_at(i, j);
+      const int col = col_w + 32 * j + (lj & ~1);
 #pragma unroll
       for (int rp = 0; rp < 8; ++rp) {
         const unsigned mine = image_pair<EPI>(acc[i][j][2 * rp], acc[i][j][2 * rp + 1]);
         const unsigned theirs = lane_xor1(mine);
         const unsigned pk = __builtin_amdgcn_perm(theirs, mine, pair_sel);
-        *reinterpret_cast<unsigned*>(at + s_lane[(rp >> 1) & 1] + (8 * (rp >> 1) + 2 * (rp & 1)) * PANEL_K) = pk;
+        const int row = row_w + 32 * i + 8 * (rp >> 1) + 4 * lh + 2 * (rp & 1) + (lane & 1);
+        *reinterpret_cast<unsigned*>(C + panel_chunk_off(row, col & ~7, d.N) + (col & 7)) = pk;
       }
     }
   // transposed image: (row j, k = i) of CT (UPDATE) or of the mirror tile of C (symmetric products)
@@ -1448,11 +1453,12 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        __bf16* const at = CT + transposed_at(i, j);
+        const int col = col_w + 32 * j + lj;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
+          const int row0 = row_w + 32 * i + 8 * g + 4 * lh;
           const u32x2 pk = {image_pair<EPI>(acc[i][j][4 * g], acc[i][j][4 * g + 1]), image_pair<EPI>(acc[i][j][4 * g + 2], acc[i][j][4 * g + 3])};
-          *reinterpret_cast<u32x2*>(at + t_lane[g]) = pk;
+          *reinterpret_cast<u32x2*>(CT + panel_chunk_off(col, row0 & ~7, d.M) + (row0 & 7)) = pk;
         }
       }
   }
@@ -1558,7 +1564,8 @@ hipError_t launch(const GemmDims& d, const void* P, const void* Q, EpiArgs e, co
 template <int EPI>
 hipError_t launch_multi(const GemmBatch& g, EpiArgs e, hipStream_t st) {
   const int64_t cus = cu_count();
-  ManyProblems many{};
+  ManyProblems<EPI> many{};
+  if (g.n > many.max) return hipErrorInvalidValue;
   many.n = g.n;
   int64_t tiles = 0, longest_k = 0;
   for (int j = 0; j < g.n; ++j) {
@@ -1569,7 +1576,7 @@ hipError_t launch_multi(const GemmBatch& g, EpiArgs e, hipStream_t st) {
     tiles += tile_count<EPI>(d);
     longest_k = std::max(longest_k, d.K);
   }
-  for (int j = g.n; j <= MAX_PROBLEMS; ++j) many.begin[j] = static_cast<int>(tiles);
+  for (int j = g.n; j <= many.max; ++j) many.begin[j] = static_cast<int>(tiles);
   if (tiles == 0) return hipSuccess;
   const int64_t whole_large = large_share<EPI>(tiles, cus, longest_k);
   e.splits = 1;
@@ -1578,12 +1585,12 @@ hipError_t launch_multi(const GemmBatch& g, EpiArgs e, hipStream_t st) {
     e.full_rounds = static_cast<int>(whole_large / cus);
     e.left = static_cast<int>(whole_large % cus);
     e.main_grid = static_cast<int>(std::min<int64_t>(cus, whole_large));
-    hipLaunchKernelGGL((k_gemm_nt_bf16<EPI, false, ManyProblems>), dim3(static_cast<unsigned>(e.main_grid)), dim3(NTHREADS),
+    hipLaunchKernelGGL((k_gemm_nt_bf16<EPI, false, ManyProblems<EPI>>), dim3(static_cast<unsigned>(e.main_grid)), dim3(NTHREADS),
                        0, st, many, e, Shape{}, OutSpec{});
   }
   if (whole_large < tiles) {
     e.main_grid = static_cast<int>(whole_large);   // first tile of the small kernel
-    hipLaunchKernelGGL((k_gemm_nt_bf16_small<EPI, ManyProblems>), dim3(static_cast<unsigned>(4 * (tiles - whole_large))),
+    hipLaunchKernelGGL((k_gemm_nt_bf16_small<EPI, ManyProblems<EPI>>), dim3(static_cast<unsigned>(4 * (tiles - whole_large))),
                        dim3(NTHREADS), 0, st, many, e, Shape{}, OutSpec{});
   }
   return hipGetLastError();

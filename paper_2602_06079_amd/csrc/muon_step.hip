@@ -264,17 +264,16 @@ bool bounded_map(const canz_muon_hparams& hp) {
 // that than it gains (1 x 2048 x 6144 with three smaller classes 1300 -> 1380, 1 x 4096 x 1536 550 -> 760; 1 x 9728 x 2560 1960 -> 1850): hence m n >=
 // 2^24.  The rule looks at the shape and the coefficients alone, so that a matrix's result does not depend on what
 // shares its launch.  The spare arrays (Spare) fit wherever it holds.
-std::vector<int> stage_plan(const Shape& s, const canz_muon_hparams& hp) {
+struct StagePlan {
+  int steps, first, last;   // steps in all, in the first stage (if it is merged) and in the last one (if that is), 0 otherwise
+  int count() const { return steps - (first ? first - 1 : 0) - (last ? last - 1 : 0); }
+  int len(int i) const { return i == 0 && first ? first : i + 1 == count() && last ? last : 1; }
+  bool operator==(const StagePlan& o) const { return steps == o.steps && first == o.first && last == o.last; }
+};
+StagePlan stage_plan(const Shape& s, const canz_muon_hparams& hp) {
   const bool wide = s.m >= 1536 && s.m * s.n >= (int64_t(1) << 24) && (s.m >= 5120 ? 2 * s.m <= s.n : 20 * s.m <= 9 * s.n);
-  const bool merge = hp.precision == CANZ_PREC_BF16 && hp.ns_steps >= 3 && hp.c != 0.f && wide && bounded_map(hp);
-  std::vector<int> stages;
-  for (int left = hp.ns_steps; left > 0; left -= stages.back()) {
-    int len = 1;
-    if (merge && stages.empty()) len = left >= 4 ? 3 : 2;
-    if (merge && !stages.empty() && left == 2) len = 2;
-    stages.push_back(len);
-  }
-  return stages;
+  if (!(hp.precision == CANZ_PREC_BF16 && hp.ns_steps >= 3 && hp.c != 0.f && wide && bounded_map(hp))) return {hp.ns_steps, 0, 0};
+  return {hp.ns_steps, hp.ns_steps >= 4 ? 3 : 2, hp.ns_steps >= 5 ? 2 : 0};
 }
 
 // Launch batches that are too small to fill the chip on their own for long (fewer than 8
@@ -298,11 +297,13 @@ std::vector<int> group_runs(std::vector<Batch>& batches, const canz_muon_hparams
         ++j;
       }
     }
-    const std::vector<int> plan = stage_plan(batches[i].s0, hp);
-    const auto rest = std::stable_partition(batches.begin() + i, batches.begin() + j,
-                                            [&](const Batch& b) { return stage_plan(b.s0, hp) == plan; });
     first.push_back(i);
-    if (const int k = static_cast<int>(rest - batches.begin()); k < j) first.push_back(k);   // there are two plans at most
+    if (j > i + 1) {
+      const StagePlan plan = stage_plan(batches[i].s0, hp);
+      const auto rest = std::stable_partition(batches.begin() + i, batches.begin() + j,
+                                              [&](const Batch& b) { return stage_plan(b.s0, hp) == plan; });
+      if (const int k = static_cast<int>(rest - batches.begin()); k < j) first.push_back(k);   // there are two plans at most
+    }
     i = j;
   }
   first.push_back(n);
@@ -338,7 +339,7 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
                 hipStream_t st) {
   constexpr bool is_bf16 = sizeof(T) == 2;
   const int nk = hi - lo;
-  const std::vector<int> stages = stage_plan(batches[lo].s0, hp);   // the same for all batches of a run
+  const StagePlan stages = stage_plan(batches[lo].s0, hp);   // the same for all batches of a run
   struct Kind {
     T *xw, *xt[2], *a, *bm;
     void *t, *b[3];            // merged steps: B A, three images for polynomials and their products
@@ -427,7 +428,7 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
   const void* q[MAX_KINDS] = {};
   const float* dq[MAX_KINDS] = {};
   auto stage_bf16 = [&](int len, bool first, bool last_stage, int cur) -> int {
-    GemmBatch gb{};
+    GemmBatch gb;
     const bool apart = len > 1;
     for (int k = 0; apart && k < nk; ++k) {
       Kind& kd = kind[k];
@@ -496,16 +497,16 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
   };
 
   int cur = 0;
-  for (size_t sg = 0; sg < stages.size(); ++sg) {
-    const bool first_it = sg == 0, last = sg + 1 == stages.size();
+  for (int sg = 0; sg < stages.count(); ++sg) {
+    const bool first_it = sg == 0, last = sg + 1 == stages.count();
     if (is_bf16) {
-      if (int rc = stage_bf16(stages[sg], first_it, last, cur)) return rc;
+      if (int rc = stage_bf16(stages.len(sg), first_it, last, cur)) return rc;
       if (!last) {
-        GemmBatch gb{};
+        GemmBatch gb;
         gb.n = nk;
         for (int k = 0; k < nk; ++k) {
           const Kind& kd = kind[k];
-          GemmProblem& pr = gb.pr[k];
+          GemmProblem& pr = gb.pr[k] = GemmProblem{};
           pr.d = kd.upd, pr.p = q[k], pr.q = kd.xt[cur], pr.c = kd.xw, pr.ct = kd.xt[cur ^ 1];
           pr.scale = first_it ? kd.scale : nullptr;
           pr.sym.x = dq[k], pr.sym.aux = kd.xt[cur];
@@ -532,7 +533,7 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
         const int n = batches[lo + k].part[h].n();
         if (n == 0) continue;
         const Shape& s = kd.s0;
-        const int terms = is_bf16 && stages[sg] > 1 ? 2 : 1;
+        const int terms = is_bf16 && stages.len(sg) > 1 ? 2 : 1;
         const T* bk = static_cast<const T*>(q[k]) + kd.first[h] * kd.a_elems * terms;
         const T* xk = kd.xt[cur] + kd.first[h] * kd.x_elems;
         const float* sk = sc1 ? sc1 + kd.first[h] : nullptr;
