@@ -25,10 +25,17 @@ PEAK_HBM_GBS = 8000.0
 # HBM bytes per launch (read + written) of the GEMM kernels on the default workload, from the
 # two rocprofv3 --pmc runs summarised in profiles/hbm_traffic_config4.md (FETCH_SIZE scaled by
 # 2.000, WRITE_SIZE by 1.000, the factors a plain 1 GiB copy gives).  Counters cannot be read
-# from inside this process, so the figures are carried here, keyed by the library version they
-# were measured on (a library whose kernels changed since reports null until the profile is
+# from inside this process, so the figures are carried here, keyed by the digest of the kernels' source they
+# were measured on (a library whose GEMM kernels changed since reports null until the profile is
 # taken again); other workloads report null.
-MEASURED_TRAFFIC_BYTES = {("0.4.0", 4, "bf16", 1): {"update": 10.03e9 + 2.24e9, "final": 10.78e9 + 2.37e9}}
+MEASURED_TRAFFIC_BYTES = {}
+
+
+def gemm_digest():
+    import hashlib
+    csrc = os.path.join(ROOT, "paper_2602_06079_amd", "csrc")
+    text = b"".join(open(os.path.join(csrc, f), "rb").read() for f in ("gemm_bf16.hip", "panel_layout.h"))
+    return hashlib.sha256(text).hexdigest()[:12]
 
 
 def log(msg):
@@ -712,7 +719,7 @@ def main():
                   peak_tflops_at_sampled_clock=(cus * flop_per_clk_cu * seen_mhz * 1e6 / 1e12) if seen_mhz else None)
     roofline = dict(bound="mfma", kernel="k_gemm_nt_%s<%s>" % (args.precision, dom), achieved=achieved, peak=peak,
                     unit="TFLOP/s", frac=achieved / peak,
-                    traffic=MEASURED_TRAFFIC_BYTES.get((canz.canz_version(), cfg, args.precision, tp), {}).get(dom), traffic_unit="B",
+                    traffic=MEASURED_TRAFFIC_BYTES.get((gemm_digest(), cfg, args.precision, tp), {}).get(dom), traffic_unit="B",
                     achieved_issued=achieved_issued, frac_issued=achieved_issued / peak,
                     flops_per_launch=dom_flops_per_launch, issued_flops_per_launch=dom_issued_per_launch,
                     avg_launch_ms=kernels[dom]["avg_ms"])

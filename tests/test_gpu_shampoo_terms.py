@@ -15,11 +15,12 @@ def canz():
     return binding
 
 
-def _newton(torch, s, eps, rounds):
+def _newton(torch, s, eps, rounds, dtype=None):
     """The same rounds in 64 bits: what exact arithmetic would give after so many."""
     d = s.shape[0]
-    eye = torch.eye(d, device=s.device, dtype=torch.float64)
-    a = s.double() + eps * eye
+    dtype = dtype or torch.float64
+    eye = torch.eye(d, device=s.device, dtype=dtype)
+    a = s.to(dtype) + eps * eye
     nrm = a.norm()
     ap = a / nrm
     a2 = ap @ ap
@@ -185,3 +186,29 @@ def test_statistics_of_mixed_scale(canz, kind, d, eps, rounds):
     err = float((lroot[0].double() - want).norm() / want.norm())
     print("%s d %d eps %g rounds %d: %.3g" % (kind, d, eps, rounds, err))
     assert err <= 2.0 ** -24 * (d / 2 * 4 * rounds) ** 0.5
+
+
+@pytest.mark.parametrize("d,rank,eps,rounds", [(512, 64, 1e-5, 22), (512, 64, 1e-6, 25), (1000, 300, 1e-6, 25), (300, 1, 1e-6, 25), (96, 8, 1e-5, 22)])
+def test_rank_deficient_statistics(canz, d, rank, eps, rounds):
+    """S = H H^T of few columns, down to the eps of 1e-6 of the largest eigenvalue that is called safe: the rounds are no further
+    from 64 bits than the same rounds in fp32 (within half, the scatter where few products dominate)."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(d + rank)
+    h = torch.randn(d, rank, generator=g, device="cuda", dtype=torch.float64)
+    s = h @ h.t()
+    s = (s / torch.linalg.matrix_norm(s.cpu(), 2).to(s.device)).float()
+    s = torch.triu(s) + torch.triu(s, 1).t()
+    left, right = [s.clone()], [torch.eye(32, device="cuda")]
+    lroot, rroot = [torch.empty_like(s)], [torch.empty_like(right[0])]
+    grp = canz.ShampooGroup(rows=d, cols=32, grad=[torch.zeros(d, 32, device="cuda")], left=left, right=right,
+                            out=[torch.zeros(d, 32, device="cuda")], lroot=lroot, rroot=rroot, grad_dtype=canz.DT_F32)
+    hp = canz.ShampooHparams(beta=1.0, lr=1.0, eps=eps, root_iters=rounds, out_mode=canz.OUT_DELTA)
+    need = canz.canz_shampoo_workspace_bytes([grp], hp)
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+    canz.canz_shampoo_step([grp], hp, ws, need, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    want = _newton(torch, s, float(np.float32(eps)), rounds)
+    err = float((lroot[0].double() - want).norm() / want.norm())
+    fp32 = float((_newton(torch, s, float(np.float32(eps)), rounds, torch.float32).double() - want).norm() / want.norm())
+    print("d %d rank %d eps %g: %.3g, in fp32 %.3g" % (d, rank, eps, err, fp32))
+    assert err <= 1.5 * fp32
