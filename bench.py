@@ -10,6 +10,7 @@ printed on stdout; progress goes to stderr.
 from __future__ import annotations
 
 import argparse
+import gc
 import json
 import os
 import sys
@@ -200,6 +201,7 @@ def main_shampoo(args, canz, W, np, torch):
     t_now[0] = args.warmup
     canz.canz_profile_enable(launches_per_step * args.steps + 8)
     torch.cuda.synchronize()
+    gc.collect()   # or a full collection (some 40 ms) falls into the timed steps, depending on what was allocated before
     t_start = time.perf_counter()
     for _ in range(args.steps):
         step()
@@ -357,6 +359,7 @@ def main_soap(args, canz, W, np, torch):
     max_d = max(max(s["rows"][g[0]], s["cols"][g[0]]) for g in groups)
     per_refresh = len(groups) * 8 * (2 * (7 * (max_d // 32 + 1) + 8) + 16)
     torch.cuda.synchronize()
+    gc.collect()
     t_start = time.perf_counter()
     for _ in range(args.steps):
         step()
@@ -634,6 +637,7 @@ def main():
         canz.canz_profile_enable(launches_per_step * args.steps + 8)
     ev = [torch.cuda.Event(enable_timing=True) for _ in range(args.steps + 1)]
     torch.cuda.synchronize()
+    gc.collect()
     clock = ClockSampler()
     with clock:
         t_start = time.perf_counter()
