@@ -399,7 +399,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
     // asked for, has -1/4 of the terms of C off the diagonal, exactly; its diagonal is put in place at the end.
     constexpr bool SYM = EPI != EPI_B3;
     constexpr int NT = EPI == EPI_MUL_Q2 ? 2 : 3;
-    if (e.c == nullptr) return;   // never: a branch that parts the epilogue from the k loop's block, see POLY above
+    if (e.c == nullptr) return;   // never: a branch that parts the epilogue from the k loop's block, see the folds above
     int s_base[2], t_base[4];
 #pragma unroll
     for (int g1 = 0; g1 < 2; ++g1)

@@ -257,6 +257,7 @@ bool bounded_map(const canz_muon_hparams& hp) {
 // alike, a constant plus noise, low rank), at 1536 x 3072, 2560 x 3900, 2048 x 8192, 4096 x 12288 and 5120 x 25600, for 3 to
 // 8 steps.  With bf16 images it is up to 2 times that of single steps (columns falling like 1 / j); with a last Q of one term up to 1.7
 // times (groups of alike rows), in bf16 throughout 2.9 times; merging four steps 2 times (constant plus noise).
+// Of the 25.9 ms of 4 x 25600 x 5120 the diagonal of Q costs the update 0.2 and the second term the last product 4.2.
 // Speed (us, single steps -> merged): 4 x 25600 x 5120 34900 -> 25900, 5 x 4096 x 12288 14400 -> 12600, 1 x 5120 x 13824 5180 -> 4460, 2 x
 // 2048 x 4800 1070 -> 970, 1 x 5120 x 10240 4020 -> 3840; but 2 x 4096 x 6400 4090 -> 4210, 1 x 4096 x 8192 2230 ->
 // 2290, 4 x 2048 x 4096 1430 -> 1470: hence m <= 0.45 n, from 5120 rows on m <= n / 2.  Merged classes do not share launches with

@@ -28,7 +28,7 @@
 // representation with an absolute resolution loses them (two fp16 terms took half the products; half the rows empty at eps =
 // 1e-8 lambda_max gave a root error of 6e-5 where fp32 has 1e-7).  Against fp32 matrices on the fp32 MFMA, whose 32 x 32 x 2
 // steps round a sum k / 2 times, the roots are closer to 64 bits: 1.4e-5 instead of 1.6e-4 on 3072 x 3072 statistics at
-// eps = 1e-4 lambda_max.
+// eps = 1e-4 lambda_max.  4 x 3072 x 1024, 22 rounds: 92.3 ms on the fp32 MFMA, 65.8 ms on three terms.
 // Both sides run their rounds side by side (the tiles of one alone leave the last round of the chip half empty), and
 // X T shares a launch with T T.
 //
