@@ -36,16 +36,16 @@ enum { SE_STAT = 0, SE_PLAIN = 1, SE_MT = 2, SE_OUT = 3, SE_SUB = 4 };
 struct ShGemm {
   int64_t M, N, K;      // multiples of 128, 128, 32
   int64_t ldp, ldq;     // row strides of P [M][K] and Q [N][K]
-  int64_t sp, sq;       // batch strides: matrix b reads P + (b / pdiv) sp and Q + (b / qdiv) sq
-  int pdiv, qdiv;       // 0 means 1; 2 lets two consecutive problems share an operand
+  int64_t sp, sq;       // batch strides: matrix b reads P + b sp and Q + b sq
   const float* P;
   const float* Q;
   float* c;             // output
   int64_t ldc, sc;      // its row and batch strides; 0, 0 means dense: N and M * N
-  float* c2;            // SE_MT: the next T = 5/4 I - 1/4 C (strides as c)
   // SE_STAT: the caller's statistic (d x d, dense) is updated in place and A = S + eps I is written to c
   int64_t d;
   float beta, gscale, eps;
+  float* c2;            // SE_MT: the next T = 5/4 I - 1/4 C (strides as c)
+  int pshare, qshare;   // SHARE: 1 lets two consecutive problems read the same P (or Q): matrix (b >> pshare)
 };
 
 // Straight and (for off-diagonal tiles of a symmetric product) mirrored store of the 16 values
@@ -66,7 +66,9 @@ __device__ __forceinline__ void put16(float* C, int64_t ld, int row0, int col, c
 
 // BN = 128: 128 x 128 tiles, each wavefront a 64 x 64 quarter.  BN = 32 (for products whose N is 32, the
 // width of a QR panel): 128 x 32 tiles, each wavefront a 32 x 32 block of rows.
-template <int EPI, bool SYM, int BN>
+// SHARE is a variant of its own (the SOAP rotations of G and M): with the division of the problem number in every launch
+// the refresh, some 300 launches of 4 to 50 us, took 18.00 ms on 4 x 2048x1024, with a shift 17.93, without either 17.83.
+template <int EPI, bool SYM, int BN, bool SHARE>
 __device__ __forceinline__ void sh_gemm_body(const ShGemm& g, const PtrTable& stat, const Shape& s, const OutSpec& o) {
   static_assert(BN == SB || (BN == 32 && !SYM), "tile widths: 128, or 32 for plain products");
   constexpr int NI = BN == SB ? 2 : 1;   // 32 x 32 MFMA tiles per wavefront, along M and along N
@@ -92,8 +94,8 @@ __device__ __forceinline__ void sh_gemm_body(const ShGemm& g, const PtrTable& st
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
   const int wm = BN == SB ? wave >> 1 : wave, wn = BN == SB ? wave & 1 : 0;
-  const float* Pg = g.P + static_cast<int64_t>(b / g.pdiv) * g.sp + static_cast<int64_t>(tm) * SB * g.ldp;
-  const float* Qg = g.Q + static_cast<int64_t>(b / g.qdiv) * g.sq + static_cast<int64_t>(tn) * BN * g.ldq;
+  const float* Pg = g.P + static_cast<int64_t>(SHARE ? b >> g.pshare : b) * g.sp + static_cast<int64_t>(tm) * SB * g.ldp;
+  const float* Qg = g.Q + static_cast<int64_t>(SHARE ? b >> g.qshare : b) * g.sq + static_cast<int64_t>(tn) * BN * g.ldq;
 
   const int ld_row = t >> 3, ld_k = (t & 7) * 4;  // rows ld_row + 32 x (x = 0..3), 4 consecutive k
   // Long sums of the statistics (k up to the other extent of the matrix, terms of one sign on the
@@ -234,32 +236,31 @@ __device__ __forceinline__ void sh_gemm_body(const ShGemm& g, const PtrTable& st
   }
 }
 
-template <int EPI, bool SYM, int BN = SB>
+template <int EPI, bool SYM, int BN = SB, bool SHARE = false>
 __global__ __launch_bounds__(NTH) void k_sh_gemm(ShGemm g, PtrTable stat, Shape s, OutSpec o) {
-  sh_gemm_body<EPI, SYM, BN>(g, stat, s, o);
+  sh_gemm_body<EPI, SYM, BN, SHARE>(g, stat, s, o);
 }
 // The statistics variant carries a second set of accumulators; left to itself the register allocator takes
 // more than half of a SIMD's registers for it, which leaves one block per CU and nothing to cover its
 // barriers and epilogue with (MFMA pipe 40 % busy).  Held to two wavefronts per SIMD it fits without spills.
 // The other variants are left alone: under the same limit they lose their AGPR accumulators and 5 % of their rate.
-template <int EPI, bool SYM, int BN = SB>
+template <int EPI, bool SYM, int BN = SB, bool SHARE = false>
 __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_sh_gemm_2w(ShGemm g, PtrTable stat, Shape s,
                                                                                              OutSpec o) {
-  sh_gemm_body<EPI, SYM, BN>(g, stat, s, o);
+  sh_gemm_body<EPI, SYM, BN, SHARE>(g, stat, s, o);
 }
 
-template <int EPI, bool SYM, int BN = SB>
+template <int EPI, bool SYM, int BN = SB, bool SHARE = false>
 hipError_t launch_gemm(ShGemm g, int nb, const PtrTable& stat, const Shape& s, const OutSpec& o, hipStream_t st) {
-  if (g.M < SB || g.N < BN || g.K < SK || g.M % SB || g.N % BN || g.K % SK || (SYM && g.M != g.N)) return hipErrorInvalidValue;
+  if (g.M < SB || g.N < BN || g.K < SK || g.M % SB || g.N % BN || g.K % SK || (SYM && g.M != g.N) ||
+      (g.pshare | g.qshare) >> (SHARE ? 1 : 0)) return hipErrorInvalidValue;
   if (g.ldc == 0) g.ldc = g.N, g.sc = g.M * g.N;
-  if (g.pdiv == 0) g.pdiv = 1;
-  if (g.qdiv == 0) g.qdiv = 1;
   const int64_t tm = g.M / SB, tn = g.N / BN;
   const int64_t blocks = (SYM ? tm * (tm + 1) / 2 : tm * tn) * nb;
   if constexpr (EPI == SE_STAT)
-    hipLaunchKernelGGL((k_sh_gemm_2w<EPI, SYM, BN>), dim3(static_cast<unsigned>(blocks)), dim3(NTH), 0, st, g, stat, s, o);
+    hipLaunchKernelGGL((k_sh_gemm_2w<EPI, SYM, BN, SHARE>), dim3(static_cast<unsigned>(blocks)), dim3(NTH), 0, st, g, stat, s, o);
   else
-    hipLaunchKernelGGL((k_sh_gemm<EPI, SYM, BN>), dim3(static_cast<unsigned>(blocks)), dim3(NTH), 0, st, g, stat, s, o);
+    hipLaunchKernelGGL((k_sh_gemm<EPI, SYM, BN, SHARE>), dim3(static_cast<unsigned>(blocks)), dim3(NTH), 0, st, g, stat, s, o);
   return hipGetLastError();
 }
 

@@ -1308,23 +1308,23 @@ int run_batch(const canz_soap_group& g, int first, int nb, Rot rot, const canz_s
     const int count = per * nb;
     if (u.left && u.right) {
       ShGemm a{};   // t1 = (X Q_R)^T: [cp][rp]
-      a.M = cp, a.N = rp, a.K = cp, a.ldp = cp, a.ldq = cp, a.sp = cp * cp, a.pdiv = per, a.sq = step_;
+      a.M = cp, a.N = rp, a.K = cp, a.ldp = cp, a.ldq = cp, a.sp = cp * cp, a.pshare = per - 1, a.sq = step_;
       a.P = qrt, a.Q = gm + at, a.c = t1 + at, a.ldc = rp, a.sc = step_;
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false>(a, count, none, s, o, st)), "rotation (right)");
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false, SB, true>(a, count, none, s, o, st)), "rotation (right)");
       ShGemm bq{};  // rot32 = Q_L^T (X Q_R): [rp][cp]
-      bq.M = rp, bq.N = cp, bq.K = rp, bq.ldp = rp, bq.ldq = rp, bq.sp = rp * rp, bq.pdiv = per, bq.sq = step_;
+      bq.M = rp, bq.N = cp, bq.K = rp, bq.ldp = rp, bq.ldq = rp, bq.sp = rp * rp, bq.pshare = per - 1, bq.sq = step_;
       bq.P = qlt, bq.Q = t1 + at, bq.c = rot32 + at, bq.ldc = cp, bq.sc = step_;
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false>(bq, count, none, s, o, st)), "rotation (left)");
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false, SB, true>(bq, count, none, s, o, st)), "rotation (left)");
     } else if (u.left) {
       ShGemm bq{};  // rot32 = Q_L^T X with X^T as the second operand
-      bq.M = rp, bq.N = cp, bq.K = rp, bq.ldp = rp, bq.ldq = rp, bq.sp = rp * rp, bq.pdiv = per, bq.sq = step_;
+      bq.M = rp, bq.N = cp, bq.K = rp, bq.ldp = rp, bq.ldq = rp, bq.sp = rp * rp, bq.pshare = per - 1, bq.sq = step_;
       bq.P = qlt, bq.Q = gmt + at, bq.c = rot32 + at, bq.ldc = cp, bq.sc = step_;
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false>(bq, count, none, s, o, st)), "rotation (left)");
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false, SB, true>(bq, count, none, s, o, st)), "rotation (left)");
     } else {
       ShGemm a{};   // rot32 = X Q_R
-      a.M = rp, a.N = cp, a.K = cp, a.ldp = cp, a.ldq = cp, a.sp = step_, a.sq = cp * cp, a.qdiv = per;
+      a.M = rp, a.N = cp, a.K = cp, a.ldp = cp, a.ldq = cp, a.sp = step_, a.sq = cp * cp, a.qshare = per - 1;
       a.P = gm + at, a.Q = qrt, a.c = rot32 + at, a.ldc = cp, a.sc = step_;
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false>(a, count, none, s, o, st)), "rotation (right)");
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false, SB, true>(a, count, none, s, o, st)), "rotation (right)");
     }
     return CANZ_OK;
   };
