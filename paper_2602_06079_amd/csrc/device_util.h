@@ -12,6 +12,11 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+// consecutive elements of a caller's row of any length, aligned to an element: the global loads and stores of this chip take
+// 8 and 16 bytes from any such address
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef __bf16 bf16x4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef __bf16 bf16x8_any __attribute__((ext_vector_type(8), aligned(2)));
 
 template <typename T>
 __device__ __forceinline__ T from_f32(float v);
@@ -74,44 +79,46 @@ __device__ __forceinline__ void store_out(const OutSpec& o, const Shape& s, int 
 // The same for the 16 accumulator values one lane holds of a 32 x 32 MFMA tile: rows
 // row0 + 8 * (r / 4) + (r % 4), r = 0..15, one column.  All old parameter values are
 // loaded before the first store, so the 16 read-modify-writes overlap instead of
-// running as a chain of dependent memory round trips.
+// running as a chain of dependent memory round trips: from clamped rows, and with the type known at compile time, since a
+// predicate or a conversion at a load makes the compiler wait for that load there.
+template <bool PARAM, typename E>
+__device__ __forceinline__ void store_out_tile_as(E* base, int64_t ld, int rows, const OutSpec& o, int row0, const float (&ortho)[16]) {
+  E old[16];
+  if (PARAM)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int row = row0 + 8 * (r >> 2) + (r & 3);
+      old[r] = base[(row < rows ? row : rows - 1) * ld];
+    }
+  float val[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) val[r] = apply_update(PARAM ? static_cast<float>(old[r]) : 0.f, o.decay, o.neg_lr_scale, ortho[r]);
+  if (row0 + 27 < rows) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) base[(row0 + 8 * (r >> 2) + (r & 3)) * ld] = static_cast<E>(val[r]);
+  } else {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int row = row0 + 8 * (r >> 2) + (r & 3);
+      if (row < rows) base[row * ld] = static_cast<E>(val[r]);
+    }
+  }
+}
 __device__ __forceinline__ void store_out_tile(const OutSpec& o, const Shape& s, int b, int row0, int col,
                                                const float (&ortho)[16]) {
   if (col >= s.cols) return;
   const int rows = static_cast<int>(s.rows);
-  int ld = static_cast<int>(s.cols), c = col, tab = b;
-  if (o.out_mode == CANZ_OUT_DELTA) {
-    ld = static_cast<int>(s.wfrag);
-    const int f = col / ld;
-    c = col - f * ld;
-    tab = b * s.tp + f;
-  }
-  void* base = o.out.p[tab];
-  float val[16];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) val[r] = 0.f;
   if (o.out_mode == CANZ_OUT_PARAM) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = row0 + 8 * (r >> 2) + (r & 3);
-      if (row < rows) {
-        const int64_t idx = static_cast<int64_t>(row) * ld + c;
-        val[r] = o.out_dtype == CANZ_DT_F32 ? static_cast<const float*>(base)[idx]
-                                            : static_cast<float>(static_cast<const __bf16*>(base)[idx]);
-      }
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int row = row0 + 8 * (r >> 2) + (r & 3);
-    if (row < rows) {
-      const int64_t idx = static_cast<int64_t>(row) * ld + c;
-      const float v = apply_update(val[r], o.decay, o.neg_lr_scale, ortho[r]);
-      if (o.out_dtype == CANZ_DT_F32)
-        static_cast<float*>(base)[idx] = v;
-      else
-        static_cast<__bf16*>(base)[idx] = static_cast<__bf16>(v);
-    }
+    if (o.out_dtype == CANZ_DT_F32)
+      store_out_tile_as<true>(static_cast<float*>(o.out.p[b]) + col, s.cols, rows, o, row0, ortho);
+    else
+      store_out_tile_as<true>(static_cast<__bf16*>(o.out.p[b]) + col, s.cols, rows, o, row0, ortho);
+  } else {
+    const int ld = static_cast<int>(s.wfrag), f = col / ld, c = col - f * ld;
+    if (o.out_dtype == CANZ_DT_F32)
+      store_out_tile_as<false>(static_cast<float*>(o.out.p[b * s.tp + f]) + c, ld, rows, o, row0, ortho);
+    else
+      store_out_tile_as<false>(static_cast<__bf16*>(o.out.p[b * s.tp + f]) + c, ld, rows, o, row0, ortho);
   }
 }
 

@@ -3,6 +3,8 @@
 // scale; and the direct update used when no Newton-Schulz step is requested.
 // These passes are HBM-bound: every global access is a 16-byte vector per lane on
 // contiguous rows, the transpose goes through LDS, the reduction through wave shuffles.
+#include <type_traits>
+
 #include "device_util.h"
 #include "panel_layout.h"
 
@@ -23,6 +25,8 @@ struct alignas(16) Vec8<__bf16> {
   __bf16 v[8];
 };
 
+// VEC: rows and fragments of a multiple of 8 elements.  Otherwise (one fragment then: those of several are multiples of 8) the same
+// accesses, aligned to an element only, and element by element where the edge of the matrix cuts the eight.
 // One block = one 64 x 64 tile of one matrix in the caller's orientation, extended over
 // the padded extents (elements outside rows x cols are zeros and touch no caller memory).
 // Step 2 of the operator: M <- beta M + G, U = M (or G + beta M); step 1 (TP gather) is
@@ -31,6 +35,8 @@ template <typename T, bool VEC>
 __global__ __launch_bounds__(NTHREADS) void k_momentum(Shape s, PtrTable grad, int grad_dtype, PtrTable mom,
                                                         float beta, int nesterov, T* __restrict__ xw,
                                                         T* __restrict__ xt, float* __restrict__ partial) {
+  typedef typename std::conditional<VEC, f32x4, f32x4_any>::type f32x4v;
+  typedef typename std::conditional<VEC, bf16x8, bf16x8_any>::type bf16x8v;
   __shared__ float tile[TILE][TILE + 1];
   __shared__ float wsum[NTHREADS / 64];
 
@@ -59,36 +65,30 @@ __global__ __launch_bounds__(NTHREADS) void k_momentum(Shape s, PtrTable grad, i
 #pragma unroll
     for (int e = 0; e < 8; ++e) g[half][e] = 0.f, mo[half][e] = 0.f;
     if (!live[half]) continue;
-    if (VEC) {
-      // cols and wfrag are multiples of 8 here: the vector lies in one fragment
-      const int f = col / wf;
-      const int64_t gi = static_cast<int64_t>(row) * wf + (col - f * wf);
+    const int f = VEC ? col / wf : 0;
+    const int64_t gi = static_cast<int64_t>(row) * wf + (col - f * wf);
+    if (VEC || col + 8 <= cols) {
       if (grad_dtype == CANZ_DT_BF16) {
-        const bf16x8 gv = *reinterpret_cast<const bf16x8*>(static_cast<const __bf16*>(grad.p[b * s.tp + f]) + gi);
+        const bf16x8 gv = *reinterpret_cast<const bf16x8v*>(static_cast<const __bf16*>(grad.p[b * s.tp + f]) + gi);
 #pragma unroll
         for (int e = 0; e < 8; ++e) g[half][e] = static_cast<float>(gv[e]);
       } else {
-        const f32x4* gp = reinterpret_cast<const f32x4*>(static_cast<const float*>(grad.p[b * s.tp + f]) + gi);
+        const f32x4v* gp = reinterpret_cast<const f32x4v*>(static_cast<const float*>(grad.p[b * s.tp + f]) + gi);
         const f32x4 g0 = gp[0], g1 = gp[1];
 #pragma unroll
         for (int e = 0; e < 4; ++e) g[half][e] = g0[e], g[half][4 + e] = g1[e];
       }
-      const f32x4* mp4 = reinterpret_cast<const f32x4*>(mptr + static_cast<int64_t>(row) * cols + col);
+      const f32x4v* mp4 = reinterpret_cast<const f32x4v*>(mptr + static_cast<int64_t>(row) * cols + col);
       const f32x4 m0 = mp4[0], m1 = mp4[1];
 #pragma unroll
       for (int e = 0; e < 4; ++e) mo[half][e] = m0[e], mo[half][4 + e] = m1[e];
     } else {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int c = col + e;
-        if (c < cols) {
-          const int f = c / wf;
-          const int64_t gi = static_cast<int64_t>(row) * wf + (c - f * wf);
-          g[half][e] = grad_dtype == CANZ_DT_BF16
-                           ? static_cast<float>(static_cast<const __bf16*>(grad.p[b * s.tp + f])[gi])
-                           : static_cast<const float*>(grad.p[b * s.tp + f])[gi];
-          mo[half][e] = mptr[static_cast<int64_t>(row) * cols + c];
-        }
+      for (int e = 0; e < 7; ++e) {
+        if (col + e >= cols) break;
+        g[half][e] = grad_dtype == CANZ_DT_BF16 ? static_cast<float>(static_cast<const __bf16*>(grad.p[b])[gi + e])
+                                                : static_cast<const float*>(grad.p[b])[gi + e];
+        mo[half][e] = mptr[static_cast<int64_t>(row) * cols + col + e];
       }
     }
   }
@@ -104,16 +104,16 @@ __global__ __launch_bounds__(NTHREADS) void k_momentum(Shape s, PtrTable grad, i
       u[e] = nesterov ? g[half][e] + beta * mn[e] : mn[e];
     }
     if (live[half]) {
-      if (VEC) {
+      if (VEC || col + 8 <= cols) {
         f32x4 n0, n1;
 #pragma unroll
         for (int e = 0; e < 4; ++e) n0[e] = mn[e], n1[e] = mn[4 + e];
-        f32x4* mp4 = reinterpret_cast<f32x4*>(mptr + static_cast<int64_t>(row) * cols + col);
+        f32x4v* mp4 = reinterpret_cast<f32x4v*>(mptr + static_cast<int64_t>(row) * cols + col);
         mp4[0] = n0;
         mp4[1] = n1;
       } else {
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
+        for (int e = 0; e < 7; ++e)
           if (col + e < cols) mptr[static_cast<int64_t>(row) * cols + col + e] = mn[e];
       }
     }

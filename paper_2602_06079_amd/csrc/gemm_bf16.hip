@@ -70,6 +70,8 @@ constexpr bool epi_mspace(int epi) { return epi == EPI_GRAM || epi == EPI_GRAM_A
 // terms, the same for symmetric matrices that commute, and the last-product epilogue.
 constexpr bool epi_terms(int epi) { return epi == EPI_B3 || epi == EPI_B3_SYM || epi == EPI_OUT_TERMS; }
 constexpr bool epi_symmetric(int epi) { return epi_mspace(epi) || epi == EPI_FINAL_SYM || epi == EPI_B3_SYM; }
+// symmetric, but element (i, j) not bit for bit (j, i): of two different matrices, or (POLY_APART) with a term of such a product
+constexpr bool epi_two_factors(int epi) { return epi_f16_in(epi) || epi == EPI_B3_SYM; }
 constexpr bool epi_final(int epi) { return epi == EPI_FINAL || epi == EPI_FINAL_SYM || epi == EPI_OUT_TERMS; }
 
 struct EpiArgs {
@@ -552,164 +554,168 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
   } else {
     // ---- last product: O in the caller's orientation (the host orders the operands so).
     const int ld = static_cast<int>(o.out_mode == CANZ_OUT_DELTA ? s.wfrag : s.cols);
-    if ((ld & 3) == 0) {
-      // fp32 rows through LDS, 64 rows x 128 columns at a time; the column index is XOR-ed
-      // with 32 on rows whose bit 2 is set so that the two half-waves hit different banks.
-      // One instantiation per (output mode, output dtype): the branches stay outside the
-      // unrolled code.
-      auto run = [&](auto mode_tag, auto dtype_tag) {
-        constexpr int MODE = decltype(mode_tag)::value, DTYPE = decltype(dtype_tag)::value;
-        float* sf = reinterpret_cast<float*>(stage);
-        int f_base[2], r_base[2];
+    // whole 128 x 128 part inside the matrix (uniform over the wavefront): no predicates
+    const bool inside = tm * BM + wm * 128 + 128 <= s.rows && tn * BN + wn * 128 + 128 <= s.cols;
+    // fp32 rows through LDS, 64 rows x 128 columns at a time; the column index is XOR-ed
+    // with 32 on rows whose bit 2 is set so that the two half-waves hit different banks.
+    // A lane handles 4 columns, in rows of any length: aligned to an element only where that is no multiple of 4.
+    // One instantiation per (output mode, output dtype): the branches stay outside the
+    // unrolled code.
+    auto run = [&](auto mode_tag, auto dtype_tag) {
+      constexpr int MODE = decltype(mode_tag)::value, DTYPE = decltype(dtype_tag)::value;
+      float* sf = reinterpret_cast<float*>(stage);
+      int f_base[2], r_base[2];
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-          f_base[p] = 4 * lh * 128 + lj + 32 * (p ^ lh);
-          r_base[p] = lh * 128 + ((lj * 4) ^ (p << 5));
-        }
-        // per-lane element offset of (row 0 of the wavefront's part, its 4 columns) in the
-        // caller's buffer, and the buffer itself (TP: the fragment that holds these columns)
-        const int col = tn * BN + wn * 128 + lj * 4;
-        const bool col_ok = col < s.cols;
-        int c_in = col, tab = b;
-        if (MODE == CANZ_OUT_DELTA) {
-          const int f = col_ok ? col / ld : 0;
-          c_in = col - f * ld;
-          tab = b * s.tp + f;
-        }
-        char* base = static_cast<char*>(o.out.p[col_ok ? tab : b * (MODE == CANZ_OUT_DELTA ? s.tp : 1)]);
-        constexpr int ESZ = DTYPE == CANZ_DT_F32 ? 4 : 2;
-        // whole 128 x 128 part inside the matrix (uniform over the wavefront): no predicates
-        const bool inside = tm * BM + wm * 128 + 128 <= s.rows && tn * BN + wn * 128 + 128 <= s.cols;
+      for (int p = 0; p < 2; ++p) {
+        f_base[p] = 4 * lh * 128 + lj + 32 * (p ^ lh);
+        r_base[p] = lh * 128 + ((lj * 4) ^ (p << 5));
+      }
+      // per-lane element offset of (row 0 of the wavefront's part, its 4 columns) in the
+      // caller's buffer, and the buffer itself (TP: the fragment that holds these columns)
+      const int col = tn * BN + wn * 128 + lj * 4;
+      const bool col_ok = col + 4 <= s.cols;
+      const int n_tail = col_ok ? 0 : max(static_cast<int>(s.cols) - col, 0);   // columns before the edge that cuts the four
+      int c_in = col, tab = b;
+      if (MODE == CANZ_OUT_DELTA) {
+        const int f = col < s.cols ? col / ld : 0;
+        c_in = col - f * ld;
+        tab = b * s.tp + f;
+      }
+      char* base = static_cast<char*>(o.out.p[tab]);
+      constexpr int ESZ = DTYPE == CANZ_DT_F32 ? 4 : 2;
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          const int row_base = tm * BM + wm * 128 + half * 64 + lh;
-          auto stage_half = [&]() {
+      for (int half = 0; half < 2; ++half) {
+        const int row_base = tm * BM + wm * 128 + half * 64 + lh;
+        auto stage_half = [&]() {
 #pragma unroll
-            for (int i2 = 0; i2 < 2; ++i2)
+          for (int i2 = 0; i2 < 2; ++i2)
 #pragma unroll
-              for (int jt = 0; jt < 4; ++jt)
+            for (int jt = 0; jt < 4; ++jt)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                  // (32 jt + lj) ^ (32 lh) = lj + 32 (jt ^ lh): lane base per parity of jt
-                  const int fixed = (i2 * 32 + 8 * (r >> 2) + (r & 3)) * 128 + (jt & ~1) * 32;
-                  sf[fixed + f_base[jt & 1]] = acc[half * 2 + i2][jt][r];
-                }
-          };
-          if (inside) {
-            // The lane handles 4 columns of the 32 rows row_base + 2 i.  All old values of the
-            // half are requested at once and every one of them is consumed before the first
-            // store is issued: the half then costs one memory latency (with loads and stores
-            // interleaved, each group of rows would wait for the stores of the one before).
-            char* const ptr0 = base + (static_cast<int64_t>(row_base) * ld + c_in) * ESZ;
-            const int64_t pitch2 = static_cast<int64_t>(2) * ld * ESZ;
-            f32x4 val[32];
-            if (MODE == CANZ_OUT_PARAM) {
-#pragma unroll
-              for (int i = 0; i < 32; ++i) {
-                if (DTYPE == CANZ_DT_F32) {
-                  val[i] = *reinterpret_cast<const f32x4*>(ptr0 + i * pitch2);
-                } else {
-                  const bf16x4 ob = *reinterpret_cast<const bf16x4*>(ptr0 + i * pitch2);
-#pragma unroll
-                  for (int q = 0; q < 4; ++q) val[i][q] = static_cast<float>(ob[q]);
-                }
+              for (int r = 0; r < 16; ++r) {
+                // (32 jt + lj) ^ (32 lh) = lj + 32 (jt ^ lh): lane base per parity of jt
+                const int fixed = (i2 * 32 + 8 * (r >> 2) + (r & 3)) * 128 + (jt & ~1) * 32;
+                sf[fixed + f_base[jt & 1]] = acc[half * 2 + i2][jt][r];
               }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            stage_half();
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < 32; ++i) {
-              // row 2 i + lh of the staged half; bit 2 of that row is bit 1 of i
-              const f32x4 v = *reinterpret_cast<const f32x4*>(sf + 2 * i * 128 + r_base[(i >> 1) & 1]);
-#pragma unroll
-              for (int q = 0; q < 4; ++q)
-                val[i][q] = MODE == CANZ_OUT_PARAM ? apply_update(val[i][q], o.decay, o.neg_lr_scale, v[q])
-                                                   : o.neg_lr_scale * v[q];
-            }
-            __builtin_amdgcn_sched_barrier(0);
+        };
+        if (inside) {
+          // The lane handles 4 columns of the 32 rows row_base + 2 i.  All old values of the
+          // half are requested at once and every one of them is consumed before the first
+          // store is issued: the half then costs one memory latency (with loads and stores
+          // interleaved, each group of rows would wait for the stores of the one before).
+          char* const ptr0 = base + (static_cast<int64_t>(row_base) * ld + c_in) * ESZ;
+          const int64_t pitch2 = static_cast<int64_t>(2) * ld * ESZ;
+          f32x4 val[32];
+          if (MODE == CANZ_OUT_PARAM) {
 #pragma unroll
             for (int i = 0; i < 32; ++i) {
               if (DTYPE == CANZ_DT_F32) {
-                *reinterpret_cast<f32x4*>(ptr0 + i * pitch2) = val[i];
+                val[i] = *reinterpret_cast<const f32x4_any*>(ptr0 + i * pitch2);
               } else {
-                bf16x4 rb;
+                const bf16x4 ob = *reinterpret_cast<const bf16x4_any*>(ptr0 + i * pitch2);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) rb[q] = static_cast<__bf16>(val[i][q]);
-                *reinterpret_cast<bf16x4*>(ptr0 + i * pitch2) = rb;
+                for (int q = 0; q < 4; ++q) val[i][q] = static_cast<float>(ob[q]);
               }
             }
-            __builtin_amdgcn_sched_barrier(0);
-            continue;
           }
-          // ragged edge of the matrix: rows and columns checked one by one, 4 rows at a time
+          __builtin_amdgcn_sched_barrier(0);
           stage_half();
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int x4 = 0; x4 < 8; ++x4) {  // loads of old values first
-            f32x4 v[4], old[4];
-            char* ptr[4];
-            bool live[4];
+          for (int i = 0; i < 32; ++i) {
+            // row 2 i + lh of the staged half; bit 2 of that row is bit 1 of i
+            const f32x4 v = *reinterpret_cast<const f32x4*>(sf + 2 * i * 128 + r_base[(i >> 1) & 1]);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              // lane reads 4 columns of row 2 (4 x4 + u) + lh; bit 2 of that row is bit 1 of u
-              v[u] = *reinterpret_cast<const f32x4*>(sf + 2 * (x4 * 4 + u) * 128 + r_base[(u >> 1) & 1]);
-              const int row = row_base + 2 * (x4 * 4 + u);
-              live[u] = col_ok && row < s.rows;
-              ptr[u] = base + (static_cast<int64_t>(row) * ld + c_in) * ESZ;
+            for (int q = 0; q < 4; ++q)
+              val[i][q] = MODE == CANZ_OUT_PARAM ? apply_update(val[i][q], o.decay, o.neg_lr_scale, v[q])
+                                                 : o.neg_lr_scale * v[q];
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < 32; ++i) {
+            if (DTYPE == CANZ_DT_F32) {
+              *reinterpret_cast<f32x4_any*>(ptr0 + i * pitch2) = val[i];
+            } else {
+              bf16x4 rb;
+#pragma unroll
+              for (int q = 0; q < 4; ++q) rb[q] = static_cast<__bf16>(val[i][q]);
+              *reinterpret_cast<bf16x4_any*>(ptr0 + i * pitch2) = rb;
             }
-            if (MODE == CANZ_OUT_PARAM) {
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          continue;
+        }
+        // ragged edge of the matrix: rows and columns checked one by one, 4 rows at a time
+        stage_half();
 #pragma unroll
-              for (int u = 0; u < 4; ++u) {
-                if (!live[u]) continue;
-                if (DTYPE == CANZ_DT_F32) {
-                  old[u] = *reinterpret_cast<const f32x4*>(ptr[u]);
-                } else {
-                  const bf16x4 ob = *reinterpret_cast<const bf16x4*>(ptr[u]);
+        for (int x4 = 0; x4 < 8; ++x4) {  // loads of old values first
+          f32x4 v[4], old[4];
+          char* ptr[4];
+          bool live[4];
 #pragma unroll
-                  for (int q = 0; q < 4; ++q) old[u][q] = static_cast<float>(ob[q]);
-                }
-              }
-            }
+          for (int u = 0; u < 4; ++u) {
+            // lane reads 4 columns of row 2 (4 x4 + u) + lh; bit 2 of that row is bit 1 of u
+            v[u] = *reinterpret_cast<const f32x4*>(sf + 2 * (x4 * 4 + u) * 128 + r_base[(u >> 1) & 1]);
+            const int row = row_base + 2 * (x4 * 4 + u);
+            live[u] = col_ok && row < s.rows;
+            ptr[u] = base + (static_cast<int64_t>(row) * ld + c_in) * ESZ;
+          }
+          if (MODE == CANZ_OUT_PARAM) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
               if (!live[u]) continue;
-              f32x4 res;
-#pragma unroll
-              for (int q = 0; q < 4; ++q)
-                res[q] = MODE == CANZ_OUT_PARAM ? apply_update(old[u][q], o.decay, o.neg_lr_scale, v[u][q])
-                                                : o.neg_lr_scale * v[u][q];
               if (DTYPE == CANZ_DT_F32) {
-                *reinterpret_cast<f32x4*>(ptr[u]) = res;
+                old[u] = *reinterpret_cast<const f32x4_any*>(ptr[u]);
               } else {
-                bf16x4 rb;
+                const bf16x4 ob = *reinterpret_cast<const bf16x4_any*>(ptr[u]);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) rb[q] = static_cast<__bf16>(res[q]);
-                *reinterpret_cast<bf16x4*>(ptr[u]) = rb;
+                for (int q = 0; q < 4; ++q) old[u][q] = static_cast<float>(ob[q]);
               }
             }
           }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            if (!live[u]) continue;
+            f32x4 res;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              res[q] = MODE == CANZ_OUT_PARAM ? apply_update(old[u][q], o.decay, o.neg_lr_scale, v[u][q])
+                                              : o.neg_lr_scale * v[u][q];
+            if (DTYPE == CANZ_DT_F32) {
+              *reinterpret_cast<f32x4_any*>(ptr[u]) = res;
+            } else {
+              bf16x4 rb;
+#pragma unroll
+              for (int q = 0; q < 4; ++q) rb[q] = static_cast<__bf16>(res[q]);
+              *reinterpret_cast<bf16x4_any*>(ptr[u]) = rb;
+            }
+          }
         }
-      };
-      using P_ = std::integral_constant<int, CANZ_OUT_PARAM>;
-      using D_ = std::integral_constant<int, CANZ_OUT_DELTA>;
-      using F_ = std::integral_constant<int, CANZ_DT_F32>;
-      using B_ = std::integral_constant<int, CANZ_DT_BF16>;
-      if (o.out_mode == CANZ_OUT_PARAM) {
-        if (o.out_dtype == CANZ_DT_F32) run(P_{}, F_{}); else run(P_{}, B_{});
-      } else {
-        if (o.out_dtype == CANZ_DT_F32) run(D_{}, F_{}); else run(D_{}, B_{});
+        if (n_tail > 0) {
+          typedef typename std::conditional<DTYPE == CANZ_DT_F32, float, __bf16>::type elem;
+#pragma unroll 1
+          for (int i = 0; i < 32; ++i) {
+            const int row = row_base + 2 * i;
+            if (row >= s.rows) break;
+#pragma unroll 1
+            for (int q = 0; q < n_tail; ++q) {
+              elem* const at = reinterpret_cast<elem*>(base) + static_cast<int64_t>(row) * ld + c_in + q;
+              const float v = sf[2 * i * 128 + ((i & 2) ? r_base[1] : r_base[0]) + q];
+              *at = static_cast<elem>(MODE == CANZ_OUT_PARAM ? apply_update(static_cast<float>(*at), o.decay, o.neg_lr_scale, v)
+                                                             : o.neg_lr_scale * v);
+            }
+          }
+        }
       }
+    };
+    using P_ = std::integral_constant<int, CANZ_OUT_PARAM>;
+    using D_ = std::integral_constant<int, CANZ_OUT_DELTA>;
+    using F_ = std::integral_constant<int, CANZ_DT_F32>;
+    using B_ = std::integral_constant<int, CANZ_DT_BF16>;
+    if (o.out_mode == CANZ_OUT_PARAM) {
+      if (o.out_dtype == CANZ_DT_F32) run(P_{}, F_{}); else run(P_{}, B_{});
     } else {
-      // unaligned row length: element-wise stores straight from the accumulators
-#pragma unroll
-      for (int it = 0; it < 4; ++it)
-#pragma unroll
-        for (int jt = 0; jt < 4; ++jt) {
-          float v[16];
-#pragma unroll
-          for (int r = 0; r < 16; ++r) v[r] = acc[it][jt][r];
-          store_out_tile(o, s, b, tm * BM + wm * 128 + it * 32 + 4 * lh, tn * BN + wn * 128 + jt * 32 + lj, v);
-        }
+      if (o.out_dtype == CANZ_DT_F32) run(D_{}, F_{}); else run(D_{}, B_{});
     }
   }
 }
@@ -1032,7 +1038,7 @@ __global__ __launch_bounds__(NTHREADS) void k_split_finish(GemmDims d, EpiArgs e
 }
 
 // ---------------------------------------------------------------------------------------
-// Small-product variant: 128 x 128 tiles, one block per tile, three resident blocks per CU.
+// Small-product variant: 128 x 128 or 64 x 64 tiles, one block per tile, up to three resident blocks per CU.
 //
 // The persistent 256 x 256 kernel above is built for products with many rounds of long tiles.
 // A launch with few tiles (the 0.6B-shaped shares: 260 Gram tiles for 256 CUs) leaves most
@@ -1053,14 +1059,29 @@ __global__ __launch_bounds__(NTHREADS) void k_split_finish(GemmDims d, EpiArgs e
 // per CU, and the stores of one block drain under the work of the others.  Only the last
 // product, whose rows go to the caller's row-major buffers, stages them through the stages
 // the k loop has left free.
-constexpr int SM = 128;                  // tile rows and columns
-constexpr int S_STAGE = 2 * SM * BK;     // elements per stage: P half-panel + Q half-panel (16 KiB)
+// Three variants, by how many blocks a launch has (launch_small).  What bounds a block that has its CU to itself is the wait for
+// its panels: a k-step of 128 x 128 takes 0.12 us on the matrix cores, 0.15 us from L2 into LDS (110 to 140 KB/us per CU) and
+// 0.44 us with two k-steps of loads in flight.  So where there are no three blocks for every CU, the ring is eight stages deep and the
+// operands are double-buffered in registers (0.19 us), and where there are fewer than two tiles for every CU, tiles are
+// 64 x 64: four times as many blocks, two on a CU.  us a launch, 128 x 128 with three stages -> the variant that now runs:
+//   64 x 64, 8 stages     8 x 256^2, k 512: 7.9 -> 5.0;  2 x 512^2, k 4096: 38 -> 22;  a 1024 x 2048 update: 12.8 -> 9.3
+//   128 x 128, 8 stages   2048^2, k 4096: 38 -> 29.5;  seven 1024^2 with k 1024 to 3072: 38 -> 33
+// blocks that share a CU:
+constexpr int small_blocks(int sm, int nst) { return nst == 3 ? 3 : sm == 64 ? 2 : 1; }
 
-template <int EPI, typename Args>
-__global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, EpiArgs e_launch, Shape s, OutSpec o) {
+template <int EPI, int SM, int NST, typename Args>
+__global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf16_small(Args args, EpiArgs e_launch, Shape s, OutSpec o) {
+  static_assert((SM == 128 && NST == 3) || NST == 8, "variants");
+  constexpr int S_STAGE = 2 * SM * BK;   // elements per stage: the P and the Q part of a panel
+  constexpr int R = BM / SM;             // tiles per 256 rows
+  constexpr int TI = SM / 64;            // 32 x 32 MFMA tiles of a wavefront, along either side
+  constexpr int LPK = 2 * TI;            // direct loads of a wavefront per stage
+  // one array per stage, as in the large kernel
   __shared__ __attribute__((aligned(1024))) __bf16 sa[S_STAGE];
   __shared__ __attribute__((aligned(1024))) __bf16 sb[S_STAGE];
   __shared__ __attribute__((aligned(1024))) __bf16 sc[S_STAGE];
+  __shared__ __attribute__((aligned(1024))) __bf16 sd[NST > 3 ? S_STAGE : 8], se[NST > 3 ? S_STAGE : 8], sf_[NST > 3 ? S_STAGE : 8],
+      sg[NST > 3 ? S_STAGE : 8], sh[NST > 3 ? S_STAGE : 8];
 
   GemmDims d{};
   const __bf16 *P = nullptr, *Q = nullptr;
@@ -1073,10 +1094,15 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
     const int xcd = bid % N_XCD, q = bid / N_XCD;
     logical = xcd < rem ? xcd * (per + 1) + q : rem * (per + 1) + (xcd - rem) * per + q;
   }
-  // four consecutive blocks are the quadrants of one 256 x 256 tile of the large kernel's
-  // numbering, starting at tile e.main_grid (the launcher's "first tile" here)
-  const int quad = logical & 3;
-  logical = e.main_grid + (logical >> 2);
+  // A launch of small tiles alone (e.main_grid = 0) numbers those that there are, one block each.  Behind a launch of the
+  // large kernel R * R consecutive blocks are the parts of one 256 x 256 tile of its numbering, from tile e.main_grid on.
+  // A product of two symmetric matrices is symmetric only to rounding, and within 128 x 128 elements on the diagonal all of it is
+  // computed, here as in the large kernel: 64 x 64 tiles are then numbered as the quarters of 128 x 128 ones.
+  const bool behind = e.main_grid > 0;
+  constexpr bool QUARTERS = epi_two_factors(EPI) && SM == 64;
+  const int parts = behind ? R : QUARTERS ? 2 : 1;
+  const int part = logical % (parts * parts);
+  logical = e.main_grid + logical / (parts * parts);
   if constexpr (Args::multi) {
     int j = 0;
     while (j + 1 < args.n && logical >= args.begin[j + 1]) ++j;
@@ -1088,14 +1114,17 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
   } else {
     d = args.d, P = args.P, Q = args.Q;
   }
-  const int tiles_m = static_cast<int>(d.M / BM), tiles_n = static_cast<int>(d.N / BN);
+  const int tile = parts * SM;
+  const int tiles_m = static_cast<int>(d.M) / tile, tiles_n = static_cast<int>(d.N) / tile;
   const bool symmetric = epi_symmetric(EPI);
   const int per_batch = symmetric ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
   int b, tm, tn;
   decode_tile<EPI>(logical, tiles_m, tiles_n, per_batch, b, tm, tn);
-  // the lower-left quadrant of a diagonal tile of a symmetric product is the mirror of the upper-right one
-  if (symmetric && tm == tn && quad == 2) return;
-  tm = 2 * tm + (quad >> 1), tn = 2 * tn + (quad & 1);
+  // in a diagonal tile of a symmetric product what is below the diagonal is the mirror of what is above
+  constexpr int LEVEL = QUARTERS ? 1 : 0;   // what lies on the diagonal is counted in tiles of SM << LEVEL
+  tm = parts * tm + part / parts, tn = parts * tn + part % parts;
+  if (symmetric && tm >> LEVEL > tn >> LEVEL) return;
+  const bool mirrored = symmetric && tm >> LEVEL != tn >> LEVEL;
 
   const int t = threadIdx.x;
   const int lane = t & 63;
@@ -1106,74 +1135,145 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
   // panels per row block (operands that are a part of longer rows: only of the last products and those of several terms)
   const int64_t nkp = epi_terms(EPI) || epi_final(EPI) ? d.ldp / BK : nkb, nkq = epi_terms(EPI) || epi_final(EPI) ? d.ldq / BK : nkb;
 
-  // global -> LDS: a stage is 16 pieces of 1 KiB (8 of P, 8 of Q); wavefront w copies the
-  // pieces w and w + 4 of both, lane l the 16 bytes at l * 16
-  const __bf16* pl = P + static_cast<int64_t>(b) * d.sp + (static_cast<int64_t>(tm >> 1) * nkp) * PANEL_ELEMS +
-                     (tm & 1) * (SM * BK) + wave * 512 + lane * 8;
-  const __bf16* ql = Q + static_cast<int64_t>(b) * d.sq + (static_cast<int64_t>(tn >> 1) * nkq) * PANEL_ELEMS +
-                     (tn & 1) * (SM * BK) + wave * 512 + lane * 8;
+  // global -> LDS: the part of a panel is SM / 16 pieces of 1 KiB; wavefront w copies the pieces w (and w + 4) of both
+  // operands, lane l the 16 bytes at l * 16
+  const __bf16* pl = P + static_cast<int64_t>(b) * d.sp + (static_cast<int64_t>(tm / R) * nkp) * PANEL_ELEMS +
+                     (tm % R) * (SM * BK) + wave * 512 + lane * 8;
+  const __bf16* ql = Q + static_cast<int64_t>(b) * d.sq + (static_cast<int64_t>(tn / R) * nkq) * PANEL_ELEMS +
+                     (tn % R) * (SM * BK) + wave * 512 + lane * 8;
   TermWalk wp(d.pseg, nkb), wq(d.qseg, nkb);
   auto fetch = [&](__bf16* st, int kt) {
     const int64_t off = static_cast<int64_t>(kt < nk ? kt : nk - 1) * PANEL_ELEMS;  // past the end: a harmless re-read
     const int64_t po = epi_terms(EPI) ? wp.off : off, qo = epi_terms(EPI) ? wq.off : off;
 #pragma unroll
-    for (int g = 0; g < 2; ++g) {
+    for (int g = 0; g < TI; ++g) {
       __builtin_amdgcn_global_load_lds(CANZ_GLB(pl + po + g * 2048), CANZ_LDS(st + wave * 512 + g * 2048), 16, 0, 0);
       __builtin_amdgcn_global_load_lds(CANZ_GLB(ql + qo + g * 2048), CANZ_LDS(st + SM * BK + wave * 512 + g * 2048), 16, 0, 0);
     }
     if (epi_terms(EPI)) wp.next(), wq.next();
   };
 
-  f32x16 acc[2][2];
+  f32x16 acc[TI][TI];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < TI; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < TI; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   const int frag_row = lane & 31, frag_kg = lane >> 5;
-  auto multiply = [&](const __bf16* st) {
-    bf16x8 fa[2][2], fb[2][2];
+  bf16x8 fa[2][TI], fb[2][TI];
+  auto frag = [&](const __bf16* st, int kk, int idx) {   // idx 0 .. TI - 1: rows of P, then those of Q
+    const int chunk = kk * 2 + frag_kg, i = idx % TI;
+    if (idx < TI)
+      fa[kk][i] = *reinterpret_cast<const bf16x8*>(st + swz((wm * TI + i) * 32 + frag_row, chunk));
+    else
+      fb[kk][i] = *reinterpret_cast<const bf16x8*>(st + SM * BK + swz((wn * TI + i) * 32 + frag_row, chunk));
+  };
+  auto mma = [&](int kk, int idx) {
+    const int i = idx / TI, j = idx % TI;
+    acc[i][j] = mfma<EPI>(fa[kk][i], fb[kk][j], acc[i][j]);
+  };
+  if constexpr (NST == 3) {
+    auto multiply = [&](const __bf16* st) {
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk)
+      for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        fa[kk][i] = *reinterpret_cast<const bf16x8*>(st + swz(wm * 64 + i * 32 + frag_row, kk * 2 + frag_kg));
-        fb[kk][i] = *reinterpret_cast<const bf16x8*>(st + SM * BK + swz(wn * 64 + i * 32 + frag_row, kk * 2 + frag_kg));
+        for (int i = 0; i < TI; ++i) frag(st, kk, i), frag(st, kk, TI + i);
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int idx = 0; idx < TI * TI; ++idx) mma(kk, idx);
+    };
+    // One k-step on stage `cur`: the 4 loads of the following step may stay in flight; after the
+    // barrier every wavefront has finished the step before, whose stage `nxt2` then receives step kt + 2.
+    auto k_step = [&](const __bf16* cur, __bf16* nxt2, int kt) {
+      __builtin_amdgcn_s_waitcnt(0x0074);  // vmcnt(4) lgkmcnt(0)
+      __builtin_amdgcn_s_barrier();
+      fetch(nxt2, kt + 2);
+      multiply(cur);
+    };
+    fetch(sa, 0);
+    fetch(sb, 1);
+    int kt = 0;
+    for (; kt + 3 <= nk; kt += 3) {
+      k_step(sa, sc, kt);
+      k_step(sb, sa, kt + 1);
+      k_step(sc, sb, kt + 2);
+    }
+    if (kt < nk) k_step(sa, sc, kt), ++kt;
+    if (kt < nk) k_step(sb, sa, kt), ++kt;
+    __builtin_amdgcn_s_waitcnt(0x0070);  // the re-reads past the end have landed before the block leaves
+  } else {
+    // As in the large kernel: the operands are double-buffered in registers, those of a half-step read under the MFMAs of
+    // the one before.  In the middle of step kt every wavefront has read all of `cur`, which then receives step kt + 8, and
+    // step kt + 1 has landed, `younger` later ones still in flight.  nk is a multiple of 8; the last eight steps request nothing and
+    // the queue drains.
+    using Yes = std::true_type;
+    using No = std::false_type;
+#define CANZ_FENCE() __builtin_amdgcn_sched_barrier(0)
+    auto k_step = [&](auto fetches, auto younger, __bf16* cur, const __bf16* nxt, int kt) {
+      constexpr int left = decltype(younger)::value;   // -1: the last step
+#pragma unroll
+      for (int idx = 0; idx < TI * TI; ++idx) {
+        mma(0, idx);
+        CANZ_FENCE();
+#pragma unroll
+        for (int x = 0; x < 2 / TI; ++x) frag(cur, 1, idx * (2 / TI) + x);
+        CANZ_FENCE();
+      }
+      if constexpr (left >= 0) {
+        constexpr int vm = left * LPK;
+        __builtin_amdgcn_s_waitcnt((vm & 15) | 0x70 | (vm >> 4) << 14);  // vmcnt(vm) lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        CANZ_FENCE();
       }
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk)
+      for (int idx = 0; idx < TI * TI; ++idx) {
+        mma(1, idx);
+        CANZ_FENCE();
+        if (left >= 0)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = mfma<EPI>(fa[kk][i], fb[kk][j], acc[i][j]);
-  };
-  // One k-step on stage `cur`: the 4 loads of the following step may stay in flight; after the
-  // barrier every wavefront has finished the step before, whose stage `nxt2` then receives step kt + 2.
-  auto k_step = [&](const __bf16* cur, __bf16* nxt2, int kt) {
-    __builtin_amdgcn_s_waitcnt(0x0074);  // vmcnt(4) lgkmcnt(0)
+          for (int x = 0; x < 2 / TI; ++x) frag(nxt, 0, idx * (2 / TI) + x);
+        CANZ_FENCE();
+        if (decltype(fetches)::value && idx == 0) fetch(cur, kt + 8);
+        CANZ_FENCE();
+      }
+    };
+#undef CANZ_FENCE
+#define CANZ_LEFT(n) std::integral_constant<int, n> {}
+    fetch(sa, 0), fetch(sb, 1), fetch(sc, 2), fetch(sd, 3), fetch(se, 4), fetch(sf_, 5), fetch(sg, 6), fetch(sh, 7);
+    constexpr int vm0 = 7 * LPK;
+    __builtin_amdgcn_s_waitcnt((vm0 & 15) | 0x70 | (vm0 >> 4) << 14);
     __builtin_amdgcn_s_barrier();
-    fetch(nxt2, kt + 2);
-    multiply(cur);
-  };
-  fetch(sa, 0);
-  fetch(sb, 1);
-  int kt = 0;
-  for (; kt + 3 <= nk; kt += 3) {
-    k_step(sa, sc, kt);
-    k_step(sb, sa, kt + 1);
-    k_step(sc, sb, kt + 2);
+#pragma unroll
+    for (int idx = 0; idx < 2 * TI; ++idx) frag(sa, 0, idx);
+    int kt = 0;
+    for (; kt + 8 < nk; kt += 8) {
+      k_step(Yes{}, CANZ_LEFT(6), sa, sb, kt);
+      k_step(Yes{}, CANZ_LEFT(6), sb, sc, kt + 1);
+      k_step(Yes{}, CANZ_LEFT(6), sc, sd, kt + 2);
+      k_step(Yes{}, CANZ_LEFT(6), sd, se, kt + 3);
+      k_step(Yes{}, CANZ_LEFT(6), se, sf_, kt + 4);
+      k_step(Yes{}, CANZ_LEFT(6), sf_, sg, kt + 5);
+      k_step(Yes{}, CANZ_LEFT(6), sg, sh, kt + 6);
+      k_step(Yes{}, CANZ_LEFT(6), sh, sa, kt + 7);
+    }
+    k_step(No{}, CANZ_LEFT(6), sa, sb, kt);
+    k_step(No{}, CANZ_LEFT(5), sb, sc, kt);
+    k_step(No{}, CANZ_LEFT(4), sc, sd, kt);
+    k_step(No{}, CANZ_LEFT(3), sd, se, kt);
+    k_step(No{}, CANZ_LEFT(2), se, sf_, kt);
+    k_step(No{}, CANZ_LEFT(1), sf_, sg, kt);
+    k_step(No{}, CANZ_LEFT(0), sg, sh, kt);
+    k_step(No{}, CANZ_LEFT(-1), sh, sa, kt);
+#undef CANZ_LEFT
   }
-  if (kt < nk) k_step(sa, sc, kt), ++kt;
-  if (kt < nk) k_step(sb, sa, kt), ++kt;
-  __builtin_amdgcn_s_waitcnt(0x0070);  // the re-reads past the end have landed before the block leaves
 
   // ---- epilogue.  Accumulator register r of lane l in MFMA tile (i, j): row 32 i + 8 (r / 4) + 4 (l / 32) + (r % 4),
-  //      column 32 j + (l % 32) of the wavefront's 64 x 64 part.
+  //      column 32 j + (l % 32) of the wavefront's part, a quarter of the tile.
   const int lj = lane & 31, lh = lane >> 5;
-  const int row_w = tm * SM + wm * 64, col_w = tn * SM + wn * 64;
+  const int row_w = tm * SM + wm * 32 * TI, col_w = tn * SM + wn * 32 * TI;
   // Where the elements of 32 x 32 tile (i, j) of the wavefront's part lie in a panel image: a part that is the same for
   // all lanes, a lane's own offset (two for the straight image, by the parity of the group of 8 rows; four for the
   // transposed one, by group) and a constant.
@@ -1191,9 +1291,9 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
     // four consecutive k of row j, one 8-byte load
     const __bf16* A = static_cast<const __bf16*>(e.sym.aux) + static_cast<int64_t>(b) * d.M * d.N;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < TI; ++j) {
         const int col = col_w + 32 * j + lj;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -1213,9 +1313,9 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
     const float f = UPD ? 1.f : EPI == EPI_GRAM_APART && e.scale ? e.scale[b] * UNIT_A : apart_factor<EPI>(e);
     if constexpr (!epi_apart(EPI)) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < TI; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[i][j][r] *= f;
     } else if (const __bf16* const m1 = static_cast<const __bf16*>(e.sym.aux) + static_cast<int64_t>(b) * d.M * d.N; m1 != nullptr) {
@@ -1225,9 +1325,9 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
       // all loads of a 32 x 32 tile at once: a few memory latencies for the whole epilogue, within the registers that
       // three blocks per CU leave
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < TI; ++i) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < TI; ++j) {
           asm volatile("" ::: "memory");   // or the compiler brings the loads of all four tiles together and spills
           vec4 v1[4], v3[4];
           f32x4 rw[4];
@@ -1256,7 +1356,7 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
     if (!UPD && tm == tn && wm == wn) {
       float* dv = EPI == EPI_MUL_Q2 ? nullptr : e.sym.diag + static_cast<int64_t>(b) * d.M;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < TI; ++i) {
         const int col = col_w + 32 * i + lj;
         const float dx = xv ? xv[col] : 0.f, dy = yv ? yv[col] : 0.f;
 #pragma unroll
@@ -1271,24 +1371,24 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
     if constexpr (EPI == EPI_MUL_Q || EPI == EPI_MUL_Q2) {
       const float inv = 1.f / e.sym.unit;
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < TI; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[i][j][r] *= inv;
     }
     if constexpr (epi_f16_out(EPI)) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) asm volatile("" : "+v"(acc[i][j]));
+        for (int j = 0; j < TI; ++j) asm volatile("" : "+v"(acc[i][j]));
     }
   } else if (e.scale) {
     const float sc1 = e.scale[b];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < TI; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] *= sc1;
   }
@@ -1301,10 +1401,10 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
     __bf16* const C = static_cast<__bf16*>(e.c) + static_cast<int64_t>(b) * elems;
     __bf16* const T = EPI == EPI_B3_SYM && e.ct ? static_cast<__bf16*>(e.ct) + static_cast<int64_t>(b) * elems : nullptr;
     const bool diagonal = SYM && tm == tn && wm == wn;
-    float dv[2];
+    float dv[TI];
     if (T && diagonal) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
           if (8 * (r >> 2) + (r & 3) + 4 * lh == lj) dv[i] = acc[i][i][r];
@@ -1312,9 +1412,9 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
 #pragma unroll 1
     for (int term = 0; term < NT; ++term)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < TI; ++j) {
           const int64_t at = ((row_w >> 8) * NT * nkb + term * nkb + ((col_w + 32 * j) >> 5)) * PANEL_ELEMS + ((row_w & 255) + 32 * i) * PANEL_K;
           const int64_t tt = ((col_w >> 8) * NT * nkb + term * nkb + ((row_w + 32 * i) >> 5)) * PANEL_ELEMS + ((col_w & 255) + 32 * j) * PANEL_K;
           unsigned mine[8];
@@ -1332,7 +1432,7 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
             for (int rp = 0; rp < 8; ++rp)
               *reinterpret_cast<unsigned*>(to + at + s_lane[(rp >> 1) & 1] + (8 * (rp >> 1) + 2 * (rp & 1)) * PANEL_K) =
                   __builtin_amdgcn_perm(lane_xor1(mine[rp]), mine[rp], pair_sel);
-            if (SYM && tm != tn)
+            if (mirrored)
 #pragma unroll
               for (int g = 0; g < 4; ++g) *reinterpret_cast<u32x2*>(to + tt + t_lane[g]) = u32x2{mine[2 * g], mine[2 * g + 1]};
           };
@@ -1346,7 +1446,7 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
     if (T && diagonal && ((lj >> 2) & 1) == lh) {
       __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0): the images are written, these elements go over theirs
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < TI; ++i) {
         const int64_t at = row_w + 32 * i + lj;
         put_three_terms(T + panel_chunk_off(at, at & ~7, 3 * d.N) + (at & 7), nkb * PANEL_ELEMS, 1.25f - 0.25f * dv[i]);
       }
@@ -1355,75 +1455,93 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
   }
 
   if (epi_final(EPI)) {
+    // The stages are free once every wavefront has left the k loop: each wavefront turns its part
+    // through half a stage of LDS, 32 rows at a time, into rows of fp32 and updates the
+    // caller's buffer with 16-byte accesses (4 columns per lane, LPR lanes per row; at rows whose length is no multiple of 4
+    // they are aligned to an element only, and the last columns go one by one).  All old values of 32 rows are requested
+    // at once, from clamped addresses: a predicate or a switch of the type at each load would wait for it there and make the
+    // epilogue a chain of 16 memory latencies.
+    constexpr int W = 32 * TI, LPR = W / 4, RPP = 64 / LPR, NX = 32 / RPP;
     const int ld = static_cast<int>(o.out_mode == CANZ_OUT_DELTA ? s.wfrag : s.cols);
-    if ((ld & 3) != 0) {
-      // unaligned row length: element-wise accesses straight from the accumulators
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          float v[16];
-#pragma unroll
-          for (int r = 0; r < 16; ++r) v[r] = acc[i][j][r];
-          store_out_tile(o, s, b, row_w + 32 * i + 4 * lh, col_w + 32 * j + lj, v);
-        }
-      return;
-    }
-    // The stages are free once every wavefront has left the k loop: each wavefront turns its
-    // 64 x 64 part through 8 KiB of LDS, 32 rows at a time, into rows of fp32 and updates the
-    // caller's buffer with 16-byte accesses (4 columns per lane, 16 lanes per row).
     __syncthreads();
-    float* sf = reinterpret_cast<float*>(wave == 0 ? sa : wave == 1 ? sa + 4096 : wave == 2 ? sb : sb + 4096);
-    const int col = col_w + (lane & 15) * 4;
-    const bool col_ok = col < s.cols;
-    int c_in = col, tab = b;
-    if (o.out_mode == CANZ_OUT_DELTA) {
-      const int f = col_ok ? col / ld : 0;
-      c_in = col - f * ld;
-      tab = b * s.tp + f;
-    }
-    char* base = static_cast<char*>(o.out.p[col_ok ? tab : b * (o.out_mode == CANZ_OUT_DELTA ? s.tp : 1)]);
-    const int esz = o.out_dtype == CANZ_DT_F32 ? 4 : 2;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sf[(8 * (r >> 2) + 4 * lh + (r & 3)) * 64 + 32 * j + lj] = acc[i][j][r];
-#pragma unroll
-      for (int x = 0; x < 8; ++x) {
-        const int row_l = 4 * x + (lane >> 4);
-        const f32x4 v = *reinterpret_cast<const f32x4*>(sf + row_l * 64 + (lane & 15) * 4);
-        const int row = row_w + 32 * i + row_l;
-        if (!col_ok || row >= s.rows) continue;
-        char* ptr = base + (static_cast<int64_t>(row) * ld + c_in) * esz;
-        f32x4 res;
-        if (o.out_mode == CANZ_OUT_PARAM) {
-          f32x4 old;
-          if (o.out_dtype == CANZ_DT_F32) {
-            old = *reinterpret_cast<const f32x4*>(ptr);
-          } else {
-            const bf16x4 ob = *reinterpret_cast<const bf16x4*>(ptr);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) old[q] = static_cast<float>(ob[q]);
-          }
-#pragma unroll
-          for (int q = 0; q < 4; ++q) res[q] = apply_update(old[q], o.decay, o.neg_lr_scale, v[q]);
-        } else {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) res[q] = o.neg_lr_scale * v[q];
-        }
-        if (o.out_dtype == CANZ_DT_F32) {
-          *reinterpret_cast<f32x4*>(ptr) = res;
-        } else {
-          bf16x4 rb;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) rb[q] = static_cast<__bf16>(res[q]);
-          *reinterpret_cast<bf16x4*>(ptr) = rb;
-        }
+    float* sf = reinterpret_cast<float*>((wave < 2 ? sa : sb) + (wave & 1) * (S_STAGE / 2));
+    const int rows = static_cast<int>(s.rows), cols = static_cast<int>(s.cols);
+    const int col = col_w + (lane % LPR) * 4;
+    if (row_w >= rows || col_w >= cols) return;
+    const bool col_ok = col + 4 <= cols;             // all four columns
+    const int n_tail = col_ok ? 0 : max(cols - col, 0);
+    const bool all_rows = row_w + 32 * TI <= rows;   // uniform
+    auto run = [&](auto mode_tag, auto dtype_tag) {
+      constexpr bool PARAM = decltype(mode_tag)::value == CANZ_OUT_PARAM, F32 = decltype(dtype_tag)::value == CANZ_DT_F32;
+      constexpr int ESZ = F32 ? 4 : 2;
+      typedef typename std::conditional<F32, f32x4_any, bf16x4_any>::type vec;
+      int c_in = col < cols ? col : 0;
+      char* base = static_cast<char*>(o.out.p[PARAM ? b : b * s.tp]);
+      if (!PARAM && s.tp > 1) {
+        const int f = c_in / ld;
+        c_in -= f * ld;
+        base = static_cast<char*>(o.out.p[b * s.tp + f]);
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the pointer is there, or every store below would wait for the one before
       }
-      // the second half is staged in the same area (this wavefront's own: no barrier needed)
-      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+#pragma unroll
+      for (int i = 0; i < TI; ++i) {
+        const int row0 = row_w + 32 * i + lane / LPR;
+        vec res[NX];   // first the old values
+        if (PARAM && col_ok)
+#pragma unroll
+          for (int x = 0; x < NX; ++x)
+            res[x] = *reinterpret_cast<const vec*>(base + (static_cast<int64_t>(min(row0 + RPP * x, rows - 1)) * ld + c_in) * ESZ);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < TI; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sf[(8 * (r >> 2) + 4 * lh + (r & 3)) * W + 32 * j + lj] = acc[i][j][r];
+        __builtin_amdgcn_sched_barrier(0);
+        if (col_ok) {
+#pragma unroll
+          for (int x = 0; x < NX; ++x) {
+            const f32x4 v = *reinterpret_cast<const f32x4*>(sf + (RPP * x + lane / LPR) * W + (lane % LPR) * 4);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const float val = PARAM ? apply_update(static_cast<float>(res[x][q]), o.decay, o.neg_lr_scale, v[q]) : o.neg_lr_scale * v[q];
+              if constexpr (F32) res[x][q] = val; else res[x][q] = static_cast<__bf16>(val);
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          char* const to = base + (static_cast<int64_t>(row0) * ld + c_in) * ESZ;
+          const int64_t pitch = static_cast<int64_t>(RPP) * ld * ESZ;
+          if (all_rows) {
+#pragma unroll
+            for (int x = 0; x < NX; ++x) *reinterpret_cast<vec*>(to + x * pitch) = res[x];
+          } else {
+#pragma unroll
+            for (int x = 0; x < NX; ++x)
+              if (row0 + RPP * x < rows) *reinterpret_cast<vec*>(to + x * pitch) = res[x];
+          }
+        } else {
+          for (int q = 0; q < n_tail; ++q)
+#pragma unroll 1
+            for (int x = 0; x < NX; ++x) {
+              const int row = row0 + RPP * x;
+              if (row >= rows) break;
+              typedef typename std::conditional<F32, float, __bf16>::type elem;
+              elem* const at = reinterpret_cast<elem*>(base) + static_cast<int64_t>(row) * ld + c_in + q;
+              const float v = sf[(RPP * x + lane / LPR) * W + (lane % LPR) * 4 + q];
+              *at = static_cast<elem>(PARAM ? apply_update(static_cast<float>(*at), o.decay, o.neg_lr_scale, v) : o.neg_lr_scale * v);
+            }
+        }
+        // the second half is staged in the same area (this wavefront's own: no barrier needed)
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+      }
+    };
+    using P_ = std::integral_constant<int, CANZ_OUT_PARAM>;
+    using D_ = std::integral_constant<int, CANZ_OUT_DELTA>;
+    using F_ = std::integral_constant<int, CANZ_DT_F32>;
+    using B_ = std::integral_constant<int, CANZ_DT_BF16>;
+    if (o.out_mode == CANZ_OUT_PARAM) {
+      if (o.out_dtype == CANZ_DT_F32) run(P_{}, F_{}); else run(P_{}, B_{});
+    } else {
+      if (o.out_dtype == CANZ_DT_F32) run(D_{}, F_{}); else run(D_{}, B_{});
     }
     return;
   }
@@ -1433,9 +1551,9 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
   // lane holds two consecutive columns of one row: the even lane of row 2 rp, the odd lane of row 2 rp + 1.
   const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < TI; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < TI; ++j) {
       const int col = col_w + 32 * j + (lj & ~1);
 #pragma unroll
       for (int rp = 0; rp < 8; ++rp) {
@@ -1447,12 +1565,12 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_gemm_nt_bf16_small(Args args, E
       }
     }
   // transposed image: (row j, k = i) of CT (UPDATE) or of the mirror tile of C (symmetric products)
-  if (!symmetric || tm != tn) {
+  if (!symmetric || mirrored) {
     __bf16* CT = symmetric ? C : static_cast<__bf16*>(e.ct) + static_cast<int64_t>(b) * d.M * d.N;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < TI; ++j) {
         const int col = col_w + 32 * j + lj;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -1491,8 +1609,8 @@ constexpr int64_t SMALL_MAX_K_MSPACE = 8192;
 constexpr int64_t SMALL_ALL_MAX_K = 2048;   // polynomial products up to this k and under two rounds: small tiles only
 
 template <int EPI>
-int64_t tile_count(const GemmDims& d) {
-  const int64_t tm = d.M / BM, tn = d.N / BN;
+int64_t tile_count(const GemmDims& d, int tile = BM) {
+  const int64_t tm = d.M / tile, tn = d.N / tile;
   return (epi_symmetric(EPI) ? tm * (tm + 1) / 2 : tm * tn) * d.nb;
 }
 
@@ -1500,6 +1618,7 @@ int64_t tile_count(const GemmDims& d) {
 template <int EPI>
 int64_t large_share(int64_t tiles, int64_t cus, int64_t longest_k) {
   const int64_t left = tiles % cus;
+  if (2 * tiles <= cus) return 0;   // no round to fill, whatever k
   constexpr bool msquare = EPI == EPI_POLY || epi_f16_in(EPI);
   if (!epi_terms(EPI) && longest_k > (epi_f16_in(EPI) ? SMALL_MAX_K_MSPACE : SMALL_MAX_K)) return tiles;
   // a polynomial product (k = m, the shortest k range of the step) of less than two rounds runs faster on small
@@ -1507,6 +1626,49 @@ int64_t large_share(int64_t tiles, int64_t cus, int64_t longest_k) {
   if (msquare && tiles < 2 * cus && longest_k <= SMALL_ALL_MAX_K) return 0;
   if (left == 0 || 2 * left > cus) return tiles;
   return tiles - left;
+}
+
+// The numbers of a launch of SM x SM tiles alone: how many, and where each problem's begin.
+template <int EPI, int SM>
+int64_t small_tiles(const GemmDims& d) {
+  return epi_two_factors(EPI) && SM == 64 ? 4 * tile_count<EPI>(d, 128) : tile_count<EPI>(d, SM);
+}
+template <int EPI, int SM>
+int64_t renumber(OneProblem& args) {
+  return small_tiles<EPI, SM>(args.d);
+}
+template <int EPI, int SM, int MAX>
+int64_t renumber(ManyProblemsOf<MAX>& args) {
+  int64_t tiles = 0;
+  // in the numbers that the kernel compares: of 128 x 128 tiles where 64 x 64 ones are their quarters
+  constexpr int per = epi_two_factors(EPI) && SM == 64 ? 4 : 1;
+  for (int j = 0; j < args.n; ++j) args.begin[j] = static_cast<int>(tiles / per), tiles += small_tiles<EPI, SM>(args.pr[j].d);
+  for (int j = args.n; j <= MAX; ++j) args.begin[j] = static_cast<int>(tiles / per);
+  return tiles;
+}
+template <int EPI, int SM, int NST, typename Args>
+void launch_small_as(Args args, EpiArgs e, int64_t first, int64_t tiles, const Shape& s, const OutSpec& o, hipStream_t st) {
+  constexpr int R = BM / SM;
+  const int64_t blocks = first > 0 ? R * R * (tiles - first) : renumber<EPI, SM>(args);
+  e.main_grid = static_cast<int>(first);
+  hipLaunchKernelGGL((k_gemm_nt_bf16_small<EPI, SM, NST, Args>), dim3(static_cast<unsigned>(blocks)), dim3(NTHREADS), 0, st, args, e, s, o);
+}
+// Tiles [first, tiles) of the large kernel's numbering on the small one (k_gemm_nt_bf16_small says what the variants are for).  64 x 64
+// up to two blocks per CU: behind that they move twice the bytes for nothing (544 against 144 blocks of 128 x 128 at k = 4096: 33
+// us against 30; 1088 against 288: 52 and 50).  Eight stages up to one block per CU (288 blocks on 256 CUs: 1.1 times the three-stage
+// time) and from k = 1024 on, below which there is nothing to run ahead of (160 blocks, k 512: 9.9 us, three stages 9.4).
+template <int EPI, typename Args>
+void launch_small(const Args& args, const EpiArgs& e, int64_t first, int64_t tiles, int64_t longest_k, int64_t cus, const Shape& s,
+                  const OutSpec& o, hipStream_t st) {
+  Args numbered = args;
+  const int64_t n128 = first > 0 ? 4 * (tiles - first) : renumber<EPI, 128>(numbered);
+  const int64_t n64 = first > 0 ? 16 * (tiles - first) : renumber<EPI, 64>(numbered);
+  if (n64 <= 2 * cus)
+    launch_small_as<EPI, 64, 8>(args, e, first, tiles, s, o, st);
+  else if (n128 <= cus && longest_k >= 1024)
+    launch_small_as<EPI, 128, 8>(args, e, first, tiles, s, o, st);
+  else
+    launch_small_as<EPI, 128, 3>(args, e, first, tiles, s, o, st);
 }
 
 template <int EPI>
@@ -1526,9 +1688,7 @@ hipError_t launch(const GemmDims& d, const void* P, const void* Q, EpiArgs e, co
       hipLaunchKernelGGL((k_gemm_nt_bf16<EPI, false, OneProblem>), dim3(static_cast<unsigned>(cus)), dim3(NTHREADS), 0, st,
                          one, e, s, o);
     }
-    e.main_grid = static_cast<int>(whole_large);   // first tile of the small kernel
-    hipLaunchKernelGGL((k_gemm_nt_bf16_small<EPI, OneProblem>), dim3(static_cast<unsigned>(4 * (tiles - whole_large))),
-                       dim3(NTHREADS), 0, st, one, e, s, o);
+    launch_small<EPI>(one, e, whole_large, tiles, epi_terms(EPI) ? d.K * d.nseg : d.K, cus, s, o, st);
     return hipGetLastError();
   }
   // full rounds of one tile per block, then the left-over tiles cut into k-slices (each at
@@ -1588,11 +1748,7 @@ hipError_t launch_multi(const GemmBatch& g, EpiArgs e, hipStream_t st) {
     hipLaunchKernelGGL((k_gemm_nt_bf16<EPI, false, ManyProblems<EPI>>), dim3(static_cast<unsigned>(e.main_grid)), dim3(NTHREADS),
                        0, st, many, e, Shape{}, OutSpec{});
   }
-  if (whole_large < tiles) {
-    e.main_grid = static_cast<int>(whole_large);   // first tile of the small kernel
-    hipLaunchKernelGGL((k_gemm_nt_bf16_small<EPI, ManyProblems<EPI>>), dim3(static_cast<unsigned>(4 * (tiles - whole_large))),
-                       dim3(NTHREADS), 0, st, many, e, Shape{}, OutSpec{});
-  }
+  if (whole_large < tiles) launch_small<EPI>(many, e, whole_large, tiles, longest_k, cus, Shape{}, OutSpec{}, st);
   return hipGetLastError();
 }
 
