@@ -34,7 +34,7 @@ inline size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 enum { SE_STAT = 0, SE_PLAIN = 1, SE_MT = 2, SE_OUT = 3, SE_SUB = 4 };
 
 struct ShGemm {
-  int64_t M, N, K;      // multiples of 128, 128, 32
+  int64_t M, N, K;      // multiples of 128
   int64_t ldp, ldq;     // row strides of P [M][K] and Q [N][K]
   int64_t sp, sq;       // batch strides: matrix b reads P + b sp and Q + b sq
   const float* P;
@@ -64,22 +64,21 @@ __device__ __forceinline__ void put16(float* C, int64_t ld, int row0, int col, c
   }
 }
 
-// BN = 128: 128 x 128 tiles, each wavefront a 64 x 64 quarter.  BN = 32 (for products whose N is 32, the
-// width of a QR panel): 128 x 32 tiles, each wavefront a 32 x 32 block of rows.
+// 128 x 128 tiles, each wavefront a 64 x 64 quarter.
 // SHARE is a variant of its own (the SOAP rotations of G and M): with the division of the problem number in every launch
 // the refresh, some 300 launches of 4 to 50 us, took 18.00 ms on 4 x 2048x1024, with a shift 17.93, without either 17.83.
-template <int EPI, bool SYM, int BN, bool SHARE>
-__device__ __forceinline__ void sh_gemm_body(const ShGemm& g, const PtrTable& stat, const Shape& s, const OutSpec& o) {
-  static_assert(BN == SB || (BN == 32 && !SYM), "tile widths: 128, or 32 for plain products");
-  constexpr int NI = BN == SB ? 2 : 1;   // 32 x 32 MFMA tiles per wavefront, along M and along N
-  constexpr int QX = BN / 32;            // 32-row groups of the Q tile
+// QT: the second operand as [K][N] (the reflectors of the refresh), which goes into LDS as it is.
+template <int EPI, bool SYM, bool SHARE, bool QT>
+__device__ __forceinline__ void sh_gemm_body(const ShGemm& g, int block, const PtrTable& stat, const Shape& s, const OutSpec& o) {
+  constexpr int NI = 2;                // 32 x 32 MFMA tiles per wavefront, along M and along N
+  constexpr int LQ = QT ? SB + 4 : LDS_LD;
   __shared__ float sP[2][SK][LDS_LD];  // k-major: the lanes of one MFMA operand read consecutive rows
-  __shared__ float sQ[2][SK][LDS_LD];
+  __shared__ __attribute__((aligned(16))) float sQ[2][SK][LQ];
 
-  const int tiles_m = static_cast<int>(g.M / SB), tiles_n = static_cast<int>(g.N / BN);
+  const int tiles_m = static_cast<int>(g.M / SB), tiles_n = static_cast<int>(g.N / SB);
   const int per = SYM ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
-  const int b = blockIdx.x / per;
-  int tix = blockIdx.x - b * per;
+  const int b = block / per;
+  int tix = block - b * per;
   int tm, tn;
   if (SYM) {
     // upper triangle row by row: row tm holds the columns tm .. tiles_m - 1
@@ -93,11 +92,12 @@ __device__ __forceinline__ void sh_gemm_body(const ShGemm& g, const PtrTable& st
 
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
-  const int wm = BN == SB ? wave >> 1 : wave, wn = BN == SB ? wave & 1 : 0;
+  const int wm = wave >> 1, wn = wave & 1;
   const float* Pg = g.P + static_cast<int64_t>(SHARE ? b >> g.pshare : b) * g.sp + static_cast<int64_t>(tm) * SB * g.ldp;
-  const float* Qg = g.Q + static_cast<int64_t>(SHARE ? b >> g.qshare : b) * g.sq + static_cast<int64_t>(tn) * BN * g.ldq;
+  const float* Qg = g.Q + static_cast<int64_t>(SHARE ? b >> g.qshare : b) * g.sq + static_cast<int64_t>(tn) * SB * (QT ? 1 : g.ldq);
 
   const int ld_row = t >> 3, ld_k = (t & 7) * 4;  // rows ld_row + 32 x (x = 0..3), 4 consecutive k
+  const int qt_k = t >> 5, qt_n = (t & 31) * 4;   // QT: k qt_k + 8 x, 4 consecutive columns
   // Long sums of the statistics (k up to the other extent of the matrix, terms of one sign on the
   // diagonal) are folded into a second accumulator every FLUSH stages; the products of the root
   // iteration and the preconditioning accumulate in one go (their rounding, about 1e-5 relative,
@@ -119,20 +119,23 @@ __device__ __forceinline__ void sh_gemm_body(const ShGemm& g, const PtrTable& st
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
       pv[set][x] = *reinterpret_cast<const f32x4*>(Pg + static_cast<int64_t>(ld_row + 32 * x) * g.ldp + k0);
-      if (x < QX) qv[set][x] = *reinterpret_cast<const f32x4*>(Qg + static_cast<int64_t>(ld_row + 32 * x) * g.ldq + k0);
+      qv[set][x] = *reinterpret_cast<const f32x4*>(QT ? Qg + (static_cast<int64_t>(kt) * SK + qt_k + 8 * x) * g.ldq + qt_n
+                                                      : Qg + static_cast<int64_t>(ld_row + 32 * x) * g.ldq + k0);
     }
   };
   auto stash = [&](int buf, int set) {
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+    for (int x = 0; x < 4; ++x) {
+      if (QT) *reinterpret_cast<f32x4*>(&sQ[buf][qt_k + 8 * x][qt_n]) = qv[set][x];
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         sP[buf][ld_k + c][ld_row + 32 * x] = pv[set][x][c];
-        if (x < QX) sQ[buf][ld_k + c][ld_row + 32 * x] = qv[set][x][c];
+        if (!QT) sQ[buf][ld_k + c][ld_row + 32 * x] = qv[set][x][c];
       }
+    }
   };
   // one stage: LDS buffer `buf` holds stage kt, register set `other` stage kt + 1, set `mine` is free
-  const int nk = static_cast<int>(g.K / SK);   // >= 1
+  const int nk = static_cast<int>(g.K / SK);   // a multiple of 4
   auto stage = [&](int kt, int buf, int mine, int other) {
     if (kt + 2 < nk) fetch(kt + 2, mine);
 #pragma unroll
@@ -159,15 +162,13 @@ __device__ __forceinline__ void sh_gemm_body(const ShGemm& g, const PtrTable& st
     __syncthreads();  // stage kt + 1 is complete in LDS; every wavefront is done reading stage kt
   };
   fetch(0, 0);
-  if (nk > 1) fetch(1, 1);
+  fetch(1, 1);
   stash(0, 0);
   __syncthreads();
-  int kt = 0;
-  for (; kt + 1 < nk; kt += 2) {   // pairs of stages without a test between them: the two halves schedule as one body
+  for (int kt = 0; kt < nk; kt += 2) {   // pairs of stages without a test between them: the two halves schedule as one body
     stage(kt, 0, 0, 1);
     stage(kt + 1, 1, 1, 0);
   }
-  if (kt < nk) stage(kt, 0, 0, 1);   // odd stage count (k = 32 (2 j + 1)): only the products of a QR panel
   if (!FOLD) {
 #pragma unroll
     for (int i = 0; i < NI; ++i)
@@ -176,7 +177,7 @@ __device__ __forceinline__ void sh_gemm_body(const ShGemm& g, const PtrTable& st
   }
 
   const int row_base = tm * SB + wm * 32 * NI + 4 * (lane >> 5);
-  const int col_base = tn * BN + wn * 64 + (lane & 31);
+  const int col_base = tn * SB + wn * 64 + (lane & 31);
   const bool mirror = SYM && tm != tn;
   const int64_t cb = static_cast<int64_t>(b) * g.sc;
 #pragma unroll
@@ -236,31 +237,31 @@ __device__ __forceinline__ void sh_gemm_body(const ShGemm& g, const PtrTable& st
   }
 }
 
-template <int EPI, bool SYM, int BN = SB, bool SHARE = false>
+template <int EPI, bool SYM, bool SHARE = false>
 __global__ __launch_bounds__(NTH) void k_sh_gemm(ShGemm g, PtrTable stat, Shape s, OutSpec o) {
-  sh_gemm_body<EPI, SYM, BN, SHARE>(g, stat, s, o);
+  sh_gemm_body<EPI, SYM, SHARE, false>(g, static_cast<int>(blockIdx.x), stat, s, o);
 }
 // The statistics variant carries a second set of accumulators; left to itself the register allocator takes
 // more than half of a SIMD's registers for it, which leaves one block per CU and nothing to cover its
 // barriers and epilogue with (MFMA pipe 40 % busy).  Held to two wavefronts per SIMD it fits without spills.
 // The other variants are left alone: under the same limit they lose their AGPR accumulators and 5 % of their rate.
-template <int EPI, bool SYM, int BN = SB, bool SHARE = false>
+template <int EPI, bool SYM, bool SHARE = false>
 __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_sh_gemm_2w(ShGemm g, PtrTable stat, Shape s,
                                                                                              OutSpec o) {
-  sh_gemm_body<EPI, SYM, BN, SHARE>(g, stat, s, o);
+  sh_gemm_body<EPI, SYM, SHARE, false>(g, static_cast<int>(blockIdx.x), stat, s, o);
 }
 
-template <int EPI, bool SYM, int BN = SB, bool SHARE = false>
+template <int EPI, bool SYM, bool SHARE = false>
 hipError_t launch_gemm(ShGemm g, int nb, const PtrTable& stat, const Shape& s, const OutSpec& o, hipStream_t st) {
-  if (g.M < SB || g.N < BN || g.K < SK || g.M % SB || g.N % BN || g.K % SK || (SYM && g.M != g.N) ||
+  if (g.M < SB || g.N < SB || g.K < SB || g.M % SB || g.N % SB || g.K % SB || (SYM && g.M != g.N) ||
       (g.pshare | g.qshare) >> (SHARE ? 1 : 0)) return hipErrorInvalidValue;
   if (g.ldc == 0) g.ldc = g.N, g.sc = g.M * g.N;
-  const int64_t tm = g.M / SB, tn = g.N / BN;
+  const int64_t tm = g.M / SB, tn = g.N / SB;
   const int64_t blocks = (SYM ? tm * (tm + 1) / 2 : tm * tn) * nb;
   if constexpr (EPI == SE_STAT)
-    hipLaunchKernelGGL((k_sh_gemm_2w<EPI, SYM, BN, SHARE>), dim3(static_cast<unsigned>(blocks)), dim3(NTH), 0, st, g, stat, s, o);
+    hipLaunchKernelGGL((k_sh_gemm_2w<EPI, SYM, SHARE>), dim3(static_cast<unsigned>(blocks)), dim3(NTH), 0, st, g, stat, s, o);
   else
-    hipLaunchKernelGGL((k_sh_gemm<EPI, SYM, BN, SHARE>), dim3(static_cast<unsigned>(blocks)), dim3(NTH), 0, st, g, stat, s, o);
+    hipLaunchKernelGGL((k_sh_gemm<EPI, SYM, SHARE>), dim3(static_cast<unsigned>(blocks)), dim3(NTH), 0, st, g, stat, s, o);
   return hipGetLastError();
 }
 

@@ -18,14 +18,11 @@
 // the same way round.  G is rotated first, then M; with a rotated momentum kept by the caller (mom_rot) only G is rotated
 // and M' follows M' <- beta1 M' + (1 - beta1) G' in the Adam kernel.
 //
-// QR refresh: blocked Householder factorisation with panels of 32 columns, on the transposed
-// matrix (a column of S = L Q is a contiguous row of the working copy).  Per panel: one workgroup
-// per matrix finds the 32 reflectors (each wavefront owns whole columns of the panel, so the only
-// block-wide synchronisation is two barriers per column), a second kernel forms the compact WY
-// factors H = I - V T V^T, Y = V T^T, Y2 = V T, and two products update the trailing columns:
-//   W = (columns) V,  (columns) -= W Y^T.
-// Afterwards the orthogonal factor is accumulated from the last panel to the first with the same
-// two products (and Y2).  Tile boundaries of these products are rounded down to multiples of 128;
+// QR refresh: blocked Householder factorisation with panels of 32 columns in blocks of 128, on the transposed
+// matrix (a column of S = L Q is a contiguous row of the working copy), both sides of a batch in the same launches.  One workgroup
+// per matrix finds the 32 reflectors of a panel (each wavefront owns whole columns); the products with them, and with the 128 of a
+// block (compact WY form H = I - V T V^T), run on the whole chip.  Afterwards the orthogonal factor is accumulated from the last block
+// to the first with the same two products (and T^T).  Tile boundaries of these products are rounded down to multiples of 128;
 // the extra rows and columns they touch either hold zeros in V (no effect) or are columns the
 // factorisation has finished with (R is never needed: only Q is).
 #include <hip/hip_runtime.h>
@@ -33,6 +30,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 #include <vector>
 
 #include "canz.h"
@@ -351,52 +349,53 @@ __global__ __launch_bounds__(NTH) void k_soap_store_q(PtrTable q, const float* _
   }
 }
 
-// One panel of the Householder QR factorisation: columns j0 .. j0 + 31 of the matrix whose
-// column c is row c of wk (row length dp).  One workgroup of 16 wavefronts per matrix, two kernels.
-// The first finds the reflectors:
-//   vall row j0 + c  <- reflector v_c (zero before row j0 + c, 1 there),   tau[c] <- tau_c
-// updating the panel's later columns as each reflector is found.  Columns at or beyond d (padding)
-// and columns that are already zero below the diagonal get tau = 0 (H = I).  The second
-// (k_qr_tfactor) accumulates V V^T (32 x 32, which T needs) on the matrix cores, each wavefront
-// taking every 16th group of 32 rows, sums over the wavefronts in a fixed order, forms T column by
-// column (H_0 ... H_31 = I - V T V^T), and writes
-//   ybuf [dp][128]   <- Y  = V T^T, rows klo .. dp - 1   (H^T A = A - Y (V^T A))
-//   y2   [dp][128]   <- Y2 = V T                          (H A = A - Y2 (V^T A)),
-// both into the 32 columns `ycol`.. of a strip that holds the four panels of a block of 128 columns side by side.
-//
-// Blocks.  The four panels of a block are applied to the rows beyond the block in one go: with W_raw = X [V_0 .. V_3]
-// (X: the rows to update), the W of panel b applied after panels a < b is W_b = W_raw,b - sum_{a<b} W_a C_ab,
-// C_ab = Y_a^T V_b = T_a (V_a^T V_b), i.e. W = W_raw U with U = (I + C)^(-1), C strictly block upper triangular; then
-// X -= W [Y_0 .. Y_3]^T.  When the orthogonal factor is accumulated the panels are applied last to first with Y2:
-// W = W_raw U2, U2 = (I + C2)^(-1), C2_ab = Y2_a^T V_b = T_a^T (V_a^T V_b) for a > b.  k_qr_tfactor of panel `pos`
-// of a block also forms V_a^T V_pos for the earlier panels a of the block and writes the blocks C_a,pos and
-// C2_pos,a (it reads T_a from tbuf, where every panel leaves its T); k_qr_block_u turns them into U^T and U2^T.
-//
-// Column c2 of the panel belongs to wavefront (c2 - 1) mod 16 for the whole kernel: it alone reads and
-// writes that column, so the columns need no synchronisation between wavefronts.  What the others
-// need of step c is the reflector v_c, which its owner leaves in LDS (a basis has at most VMAX rows)
-// together with tau_c.  Per step: every wavefront applies H_c to its own
-// later columns; barrier; the owner of column c + 1 turns it into v_(c+1); barrier.  With v in LDS the
-// barriers only have to order LDS traffic, so they do not wait for the stores in flight.
-// Up to 3072 remaining rows the columns stay in registers for the whole kernel (k_qr_panel_regs);
-// k_qr_panel_hybrid, for longer panels, keeps the first 2048 rows there and streams the rest from memory (L2) on every step.
+// The QR refresh: blocked Householder factorisation of S Q_old, on the transposed matrix (column c is row c of wk, row length
+// dp), and the accumulation of its orthogonal factor.  Blocks of 128 columns, four panels of 32 each:
+//   k_qr_panel_*   one workgroup per matrix finds the 32 reflectors of a panel,  vall row j0 + c <- v_c,  tau
+//   k_qr_gram      V_a^T V for the panels a of the block so far and W = (later columns of the block)^T V, in pieces of k
+//   k_qr_panel_sub sums the pieces and applies the panel to the block's later columns:  X -= W' V^T
+//   k_qr_block_t   (after the fourth panel) T of the whole block from the V_a^T V:  H_0 ... H_127 = I - V T V^T
+//   k_qr_block_w   W' = (X V) T of the rows X beyond the block, k_qr_sub  X -= W' V^T: the trailing matrix goes through memory once per block
+// and, from the last block to the first, the latter two again on Q^T with T^T.  For a row x of X, x H_0 H_1 ... = x - w' V^T, where w' = (x V) T
+// solves w'_c = tau_c (w_c - sum_{l < c} w'_l v_l^T v_c), w = x V: 32 steps by a thread per row inside the block.
+// Both sides of a batch run in the same launches: the chain of panels is a chain of latencies, with a workgroup per matrix busy.
+// 4 x 2048x1024, both sides: 17.9 ms with the sides one after the other, T, Y = V T^T and V T formed by one workgroup per matrix and panel
+// (33 us each, the panel itself 47), and the products W on one workgroup per 128 rows (60 of 256 CUs in the longest: 129 us).
 constexpr int QBLK = 128;   // columns of a block: four panels
-struct QrPanel {
-  float* wk;
-  float* vall;
-  float* ybuf;     // this block's Y strip  [dp][128]
-  float* y2;       // this block's Y2 strip [dp][128]
-  float* tau;      // [nb][32] handed from the first kernel of a panel to the second
-  float* tbuf;     // [nb][dp / 32][32][32]: T of every panel
-  float* cbuf;     // [nb][2][128][128]: C (blocks above the diagonal) and C2 (below) of the block under way
-  int64_t dp, d;
-  int64_t s_wk, s_vall, s_y, s_y2, s_t;   // batch strides
-  int j0, klo;
-  int ycol;        // 32 * (position of the panel in its block)
+constexpr int QCHUNKS = 16; // pieces of k in the products with one panel: at most this many, of 128 or more
+struct QrSide {
+  float* wk;       // [nb][dp][dp]
+  float* vall;     // [nb][dp][dp]
+  float* qt;       // [nb][dp][dp]  Q^T
+  float* tau;      // [nb][128] of the block under way
+  float* strip;    // [nb][dp][128]: pieces of the products with one panel, W' of a block
+  float* gram;     // [nb][128][128]: V_a^T V_b of the block under way (a <= b), then its T
+  float* tt;       // [nb][dp / 128][128][128]: T^T of every block
+  int dp, d;
 };
+struct QrArgs {
+  QrSide side[2];
+  int nb;          // matrices of a side; matrix m of a launch is number m % nb of side m / nb
+  int jb;          // first column of the block
+  int pos;         // panel of the block
+};
+struct QrMatrix {  // one matrix of a launch
+  float *wk, *vall, *qt, *tau, *strip, *gram, *tt;
+  int dp, d;
+};
+__device__ __forceinline__ QrMatrix qr_matrix(const QrArgs& a, int m) {
+  const QrSide& s = a.side[m >= a.nb ? 1 : 0];
+  const int64_t b = m >= a.nb ? m - a.nb : m, dd = static_cast<int64_t>(s.dp) * s.dp;
+  return QrMatrix{s.wk + b * dd, s.vall + b * dd, s.qt + b * dd, s.tau + b * QBLK, s.strip + b * s.dp * QBLK,
+                  s.gram + b * QBLK * QBLK, s.tt + b * s.dp * QBLK, s.dp, s.d};
+}
+// the pieces of k that the products with one panel of the block are cut into
+__device__ __forceinline__ void qr_chunks(int dp, int jb, int& count, int& len) {
+  const int units = (dp - jb) / 128, per = (units + QCHUNKS - 1) / QCHUNKS;
+  count = (units + per - 1) / per, len = per * 128;
+}
 
 constexpr int VMAX = 12288;   // rows of a reflector kept in LDS: the largest extent a side with a basis may have
-constexpr int TLD = QB + 4;   // row length of the T factor in LDS (rows 16-byte aligned)
 
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
@@ -476,35 +475,42 @@ __device__ __forceinline__ void apply_reflector(f32x4 (&ka)[XS], f32x4 (&kb)[XS]
   }
 }
 
-// The first kernel of a panel with at most 256 XS remaining rows (XS = 8: 2048, XS = 12: 3072): every
-// wavefront loads its two columns (wave + 1 and wave + 17) into registers once and keeps them there; a step
-// reads v_c from LDS, and the owner of column c + 1 writes v_(c+1) to LDS and to the reflector array.  The
+// The panel kernels.  Column c2 of the panel belongs to wavefront (c2 - 1) mod 16 for the whole kernel: it alone reads and
+// writes that column, so the columns need no synchronisation between wavefronts.  What the others
+// need of step c is the reflector v_c, which its owner leaves in LDS together with tau_c.  Two copies of v in turn: while all
+// apply H_c to their later columns, the owner of column c + 1 does that one first, turns it into v_(c+1) and leaves that in the other
+// copy; one barrier per step, and the chain of a step is that one column.  With v in LDS the
+// barriers only have to order LDS traffic, so they do not wait for the stores in flight.
+// Columns at or beyond d (padding) and columns that are already zero below the diagonal get tau = 0 (H = I).
+// Bound by that chain (LDS round trips, two wave sums, a root and two divisions, about 0.4 us a column).
+//
+// At most 256 XS remaining rows (XS = 2 .. 12: 512 .. 3072): every
+// wavefront loads its two columns (wave + 1 and wave + 17) into registers once and keeps them there.  The
 // columns are never written back: what the factorisation leaves in them is R, which nothing uses.
-// With XS = 8 there is room to hold v_c in registers between the dot products and the updates.
+// Up to XS = 8 there is room to hold v_c in registers between the dot products and the updates.
 template <int XS>
-__global__ __launch_bounds__(QTH) void k_qr_panel_regs(QrPanel a) {
-  __shared__ f32x4 s_v4[64 * XS];
+__global__ __launch_bounds__(QTH) void k_qr_panel_regs(QrArgs args) {
+  __shared__ f32x4 s_v4[2][64 * XS];
   __shared__ float s_tau[QB];
-  const int b = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const QrMatrix a = qr_matrix(args, blockIdx.x);
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t dp = a.dp;
-  const int j0 = a.j0;
-  const int nvec = (static_cast<int>(dp) - j0) / 4;   // <= 64 XS
-  const float* wk = a.wk + static_cast<int64_t>(b) * a.s_wk;
-  float* vrows = a.vall + static_cast<int64_t>(b) * a.s_vall;
+  const int j0 = args.jb + args.pos * QB;
+  const int nvec = (a.dp - j0) / 4;                   // <= 64 XS
   const int ca = wave + 1, cb = wave + 1 + QWAVES;    // this wavefront's columns (cb only if < 32)
   f32x4 ka[XS], kb[XS];
 
   auto load_col = [&](f32x4 (&k)[XS], int c) {
-    const f32x4* x = reinterpret_cast<const f32x4*>(wk + static_cast<int64_t>(j0 + c) * dp + j0);
+    const f32x4* x = reinterpret_cast<const f32x4*>(a.wk + static_cast<int64_t>(j0 + c) * dp + j0);
 #pragma unroll
     for (int sl = 0; sl < XS; ++sl) {
       const int q = lane + 64 * sl;
       if (q < nvec) k[sl] = x[q];
     }
   };
-  // sum of squares below row c and the element at row c, over the wavefront
-  auto head = [&](const f32x4 (&k)[XS], int c, float& ss, float& al) {
-    ss = 0.f, al = 0.f;
+  // column c (in k) becomes the reflector v_c: to LDS, to the reflector array, tau to LDS
+  auto make_v = [&](const f32x4 (&k)[XS], int c) {
+    float ss = 0.f, al = 0.f;   // sum of squares below row c and the element at row c, over the wavefront
 #pragma unroll
     for (int sl = 0; sl < XS; ++sl) {
       const int q = lane + 64 * sl;
@@ -518,83 +524,75 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_regs(QrPanel a) {
       }
     }
     ss = wave_sum_dpp(ss), al = wave_sum_dpp(al);
-  };
-  // column c (in k), whose head is (ss, al), becomes the reflector v_c: to LDS, to the reflector array, tau to LDS
-  auto make_v = [&](const f32x4 (&k)[XS], int c, float ss, float al) {
     float tau, scale;
     reflector_of(j0 + c < a.d, ss, al, tau, scale);
-    f32x4* vg = reinterpret_cast<f32x4*>(vrows + static_cast<int64_t>(j0 + c) * dp + j0);
+    f32x4* vg = reinterpret_cast<f32x4*>(a.vall + static_cast<int64_t>(j0 + c) * dp + j0);
+    if (lane == 0) s_tau[c] = tau;
 #pragma unroll
     for (int sl = 0; sl < XS; ++sl) {
       const int q = lane + 64 * sl;
       if (q < nvec) {
         const f32x4 o = v_of(k[sl], q, c, scale);
-        s_v4[q] = o;
+        s_v4[c & 1][q] = o;
         vg[q] = o;
       }
     }
-    if (lane == 0) s_tau[c] = tau;
   };
 
   if (wave == 0) {
-    float ss, al;
     load_col(ka, 0);
-    head(ka, 0, ss, al);
-    make_v(ka, 0, ss, al);
+    make_v(ka, 0);
   }
   load_col(ka, ca);
   if (cb < QB) load_col(kb, cb);
-  lds_barrier();
-
-  for (int c = 0; c < QB; ++c) {
-    const float tau = s_tau[c];
-    const bool do_a = ca > c, do_b = cb < QB && cb > c;
-    if (tau != 0.f) {   // columns that have become reflectors are left alone
-      if (do_a && do_b)
-        apply_reflector<XS, true, true>(ka, kb, s_v4, nvec, lane, tau);
-      else if (do_a)
-        apply_reflector<XS, true, false>(ka, kb, s_v4, nvec, lane, tau);
-      else if (do_b)
-        apply_reflector<XS, false, true>(ka, kb, s_v4, nvec, lane, tau);
-    }
-    // the owner of column c + 1 takes its head while the others are still busy with their columns
-    const bool owner = c + 1 < QB && wave == c % QWAVES;
-    float ss = 0.f, al = 0.f;
-    if (owner) {
-      if (c + 1 == ca)
-        head(ka, c + 1, ss, al);
-      else
-        head(kb, c + 1, ss, al);
-    }
-    lds_barrier();   // every wavefront has finished with v_c
-    if (owner) {
-      if (c + 1 == ca)
-        make_v(ka, c + 1, ss, al);
-      else
-        make_v(kb, c + 1, ss, al);
-    }
-    lds_barrier();   // v_(c+1) and tau_(c+1) are in place
+  // the products of the block run over the rows of the reflectors from the block's first column on: zero before the panel
+  for (int e = t; e < QB * QB * args.pos; e += QTH) {
+    const int r = e / (QB * args.pos), q = e - r * (QB * args.pos);
+    a.vall[static_cast<int64_t>(j0 + r) * dp + args.jb + q] = 0.f;
   }
-  if (t < QB) (a.tau + static_cast<int64_t>(b) * QB)[t] = s_tau[t];
+
+  for (int c = 0; c + 1 < QB; ++c) {
+    lds_barrier();   // v_c and tau_c are in place, and every wavefront has finished with v_(c-1)
+    const float tau = s_tau[c];
+    const f32x4* v = s_v4[c & 1];
+    const bool live = tau != 0.f;
+    if (c + 1 == ca) {
+      if (live) apply_reflector<XS, true, false>(ka, kb, v, nvec, lane, tau);
+      make_v(ka, c + 1);
+      if (live && cb < QB) apply_reflector<XS, false, true>(ka, kb, v, nvec, lane, tau);
+    } else if (c + 1 == cb) {
+      if (live) apply_reflector<XS, false, true>(ka, kb, v, nvec, lane, tau);
+      make_v(kb, c + 1);
+    } else if (live) {   // columns that have become reflectors are left alone
+      const bool do_a = ca > c, do_b = cb < QB && cb > c;
+      if (do_a && do_b)
+        apply_reflector<XS, true, true>(ka, kb, v, nvec, lane, tau);
+      else if (do_b)
+        apply_reflector<XS, false, true>(ka, kb, v, nvec, lane, tau);
+      else if (do_a)
+        apply_reflector<XS, true, false>(ka, kb, v, nvec, lane, tau);
+    }
+  }
+  lds_barrier();
+  if (t < QB) a.tau[args.pos * QB + t] = s_tau[t];
 }
 
-// The first kernel of a panel with more remaining rows than the registers hold: as k_qr_panel_regs, every wavefront
+// More remaining rows than the registers hold: as k_qr_panel_regs, every wavefront
 // keeps the first 256 XS rows of its two columns in registers for the whole kernel; the rows beyond are streamed
 // from the working copy on every step (read for the dot product, read and written for the update: the wavefront's
 // own stores, which it reads back itself).  v_c is in LDS at full length.
 template <int XS>
-__global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrPanel a) {
-  __shared__ f32x4 s_v4[VMAX / 4];
+__global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrArgs args) {
+  __shared__ f32x4 s_v4[2][VMAX / 4];
   __shared__ float s_tau[QB];
   constexpr int NR = 64 * XS;   // float4 of a column kept in registers
   constexpr int TU = 2;         // loads in flight per lane in the streaming loops
-  const int b = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const QrMatrix a = qr_matrix(args, blockIdx.x);
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t dp = a.dp;
-  const int j0 = a.j0;
-  const int nvec = (static_cast<int>(dp) - j0) / 4;   // > NR
-  float* wk = a.wk + static_cast<int64_t>(b) * a.s_wk;
-  float* vrows = a.vall + static_cast<int64_t>(b) * a.s_vall;
-  auto col = [&](int c) { return reinterpret_cast<f32x4*>(wk + static_cast<int64_t>(j0 + c) * dp + j0); };
+  const int j0 = args.jb + args.pos * QB;
+  const int nvec = (a.dp - j0) / 4;   // > NR
+  auto col = [&](int c) { return reinterpret_cast<f32x4*>(a.wk + static_cast<int64_t>(j0 + c) * dp + j0); };
   const int ca = wave + 1, cb = wave + 1 + QWAVES;    // this wavefront's columns (cb only if < 32)
   f32x4 ka[XS], kb[XS];
 
@@ -603,9 +601,9 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrPanel a) {
 #pragma unroll
     for (int sl = 0; sl < XS; ++sl) k[sl] = x[lane + 64 * sl];
   };
-  // sum of squares below row c and the element at row c (c < 32: it lies in the registers), over the wavefront
-  auto head = [&](const f32x4 (&k)[XS], int c, float& ss, float& al) {
-    ss = 0.f, al = 0.f;
+  // column c becomes the reflector v_c: to LDS, to the reflector array, tau to LDS
+  auto make_v = [&](const f32x4 (&k)[XS], int c) {
+    float ss = 0.f, al = 0.f;   // sum of squares below row c and the element at row c (c < 32: it lies in the registers)
 #pragma unroll
     for (int sl = 0; sl < XS; ++sl) {
 #pragma unroll
@@ -627,36 +625,33 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrPanel a) {
           for (int e = 0; e < 4; ++e) ss += xv[u][e] * xv[u][e];
     }
     ss = wave_sum_dpp(ss), al = wave_sum_dpp(al);
-  };
-  // column c, whose head is (ss, al), becomes the reflector v_c: to LDS, to the reflector array, tau to LDS
-  auto make_v = [&](const f32x4 (&k)[XS], int c, float ss, float al) {
     float tau, scale;
     reflector_of(j0 + c < a.d, ss, al, tau, scale);
-    f32x4* vg = reinterpret_cast<f32x4*>(vrows + static_cast<int64_t>(j0 + c) * dp + j0);
+    if (lane == 0) s_tau[c] = tau;
+    f32x4* vg = reinterpret_cast<f32x4*>(a.vall + static_cast<int64_t>(j0 + c) * dp + j0);
+    f32x4* sv = s_v4[c & 1];
 #pragma unroll
     for (int sl = 0; sl < XS; ++sl) {
       const int q = lane + 64 * sl;
       const f32x4 o = v_of(k[sl], q, c, scale);
-      s_v4[q] = o;
+      sv[q] = o;
       vg[q] = o;
     }
-    const f32x4* x = col(c);
     for (int q = NR + lane; q < nvec; q += 64) {
       f32x4 o = x[q];
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[e] *= scale;
-      s_v4[q] = o;
+      sv[q] = o;
       vg[q] = o;
     }
-    if (lane == 0) s_tau[c] = tau;
   };
   // H_c applied to column c2, held in k and, beyond the registers, in memory
-  auto apply = [&](f32x4 (&k)[XS], int c2, float tau) {
+  auto apply = [&](f32x4 (&k)[XS], int c2, const f32x4* sv, float tau) {
     f32x4* x = col(c2);
     float dot = 0.f;
 #pragma unroll
     for (int sl = 0; sl < XS; ++sl) {
-      const f32x4 y = s_v4[lane + 64 * sl];
+      const f32x4 y = sv[lane + 64 * sl];
 #pragma unroll
       for (int e = 0; e < 4; ++e) dot = __builtin_fmaf(k[sl][e], y[e], dot);
     }
@@ -668,7 +663,7 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrPanel a) {
       for (int u = 0; u < TU; ++u) {
         const int q = q0 + 64 * u;
         if (q < nvec) {
-          const f32x4 y = s_v4[q];
+          const f32x4 y = sv[q];
 #pragma unroll
           for (int e = 0; e < 4; ++e) dot = __builtin_fmaf(xv[u][e], y[e], dot);
         }
@@ -677,7 +672,7 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrPanel a) {
     const float f = tau * wave_sum_dpp(dot);
 #pragma unroll
     for (int sl = 0; sl < XS; ++sl) {
-      const f32x4 y = s_v4[lane + 64 * sl];
+      const f32x4 y = sv[lane + 64 * sl];
 #pragma unroll
       for (int e = 0; e < 4; ++e) k[sl][e] = __builtin_fmaf(-f, y[e], k[sl][e]);
     }
@@ -689,7 +684,7 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrPanel a) {
       for (int u = 0; u < TU; ++u) {
         const int q = q0 + 64 * u;
         if (q < nvec) {
-          const f32x4 y = s_v4[q];
+          const f32x4 y = sv[q];
 #pragma unroll
           for (int e = 0; e < 4; ++e) xv[u][e] = __builtin_fmaf(-f, y[e], xv[u][e]);
           x[q] = xv[u];
@@ -699,204 +694,308 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrPanel a) {
   };
 
   if (wave == 0) {
-    float ss, al;
     load_col(ka, 0);
-    head(ka, 0, ss, al);
-    make_v(ka, 0, ss, al);
+    make_v(ka, 0);
   }
   load_col(ka, ca);
   if (cb < QB) load_col(kb, cb);
-  lds_barrier();
-
-  for (int c = 0; c < QB; ++c) {
-    const float tau = s_tau[c];
-    if (tau != 0.f) {   // columns that have become reflectors are left alone
-      if (ca > c) apply(ka, ca, tau);
-      if (cb < QB && cb > c) apply(kb, cb, tau);
-    }
-    // the owner of column c + 1 takes its head while the others are still busy with their columns
-    const bool owner = c + 1 < QB && wave == c % QWAVES;
-    float ss = 0.f, al = 0.f;
-    if (owner) {
-      if (c + 1 == ca)
-        head(ka, c + 1, ss, al);
-      else
-        head(kb, c + 1, ss, al);
-    }
-    lds_barrier();   // every wavefront has finished with v_c
-    if (owner) {
-      if (c + 1 == ca)
-        make_v(ka, c + 1, ss, al);
-      else
-        make_v(kb, c + 1, ss, al);
-    }
-    lds_barrier();   // v_(c+1) and tau_(c+1) are in place
+  for (int e = t; e < QB * QB * args.pos; e += QTH) {
+    const int r = e / (QB * args.pos), q = e - r * (QB * args.pos);
+    a.vall[static_cast<int64_t>(j0 + r) * dp + args.jb + q] = 0.f;
   }
-  if (t < QB) (a.tau + static_cast<int64_t>(b) * QB)[t] = s_tau[t];
+
+  for (int c = 0; c + 1 < QB; ++c) {
+    lds_barrier();   // v_c and tau_c are in place, and every wavefront has finished with v_(c-1)
+    const float tau = s_tau[c];
+    const f32x4* v = s_v4[c & 1];
+    const bool live = tau != 0.f;
+    if (c + 1 == cb) {
+      if (live) apply(kb, cb, v, tau);
+      make_v(kb, cb);
+    } else {
+      if (live && ca > c) apply(ka, ca, v, tau);
+      if (c + 1 == ca) make_v(ka, ca);
+      if (live && cb < QB && cb > c) apply(kb, cb, v, tau);
+    }
+  }
+  lds_barrier();
+  if (t < QB) a.tau[args.pos * QB + t] = s_tau[t];
 }
 
-// Second kernel of a panel: T from the reflectors and their tau, then Y and Y2 (see above).
-__global__ __launch_bounds__(QTH) void k_qr_tfactor(QrPanel a) {
-  __shared__ float s_part[8 * 1024];
-  __shared__ float s_g[QB][QB + 1];
-  __shared__ __attribute__((aligned(16))) float s_t[QB][TLD], s_tt[QB][TLD];
-  __shared__ float s_tau[QB];
-  const int b = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+// Piece blockIdx.x of k of the products with panel `pos` of the block, V its reflectors: 32 x 32 blocks
+//   a <= pos:  V_a^T V  (V_a: panel a of the block),      a > pos:  W = (columns of panel a)^T V.
+// One wavefront per block; the pieces lie in the strip, [piece][128][32].  Rows through LDS k-major, all loads of 128 k at once.
+constexpr int GLD = 32 + 1, GRD = 128 + 5;   // row lengths in LDS: the stores of a stage spread over the banks
+__global__ __launch_bounds__(NTH) void k_qr_gram(QrArgs args) {
+  __shared__ float s_r[32][GRD], s_v[32][GLD];
+  const QrMatrix a = qr_matrix(args, blockIdx.y);
+  int chunks, len;
+  qr_chunks(a.dp, args.jb, chunks, len);
+  if (static_cast<int>(blockIdx.x) >= chunks) return;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, pos = args.pos;
   const int64_t dp = a.dp;
-  const int j0 = a.j0;
-  const int len = static_cast<int>(dp) - j0;
-  const float* vrows = a.vall + static_cast<int64_t>(b) * a.s_vall;
-  if (t < QB) s_tau[t] = (a.tau + static_cast<int64_t>(b) * QB)[t];
-  // The products of a whole block run over the rows of the reflectors from the block's first column on: this panel's
-  // reflectors are zero there, which the panel kernel (it writes them from column j0 on) has not stored.
-  for (int e = t; e < QB * a.ycol; e += QTH) {
-    const int r = e / a.ycol, q = e - r * a.ycol;
-    (a.vall + static_cast<int64_t>(b) * a.s_vall)[static_cast<int64_t>(j0 + r) * dp + (j0 - a.ycol) + q] = 0.f;
-  }
-
-  // s_g <- U^T V on the matrix cores, V this panel's reflectors, U those of the panel that starts at row `ju` (this
-  // panel itself for V V^T), summed over the rows j0 .. dp - 1 (V is zero before): lane l supplies rows l % 32 at k
-  // and k + 4 (l / 32), four k per load
-  auto gram = [&](int ju) {
-    f32x16 acc;
+  const int j0 = args.jb + pos * QB;
+  const int k_end = min(args.jb + (static_cast<int>(blockIdx.x) + 1) * len, a.dp);
+  const int k_begin = args.jb + static_cast<int>(blockIdx.x) * len;
+  // thread t loads rows t / 8 + 32 x of the four blocks and row t / 8 of V, 4 k at 4 (t % 8)
+  const int row = t >> 3, kq = (t & 7) * 4;
+  const float* src[5];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    const float* vbase = vrows + static_cast<int64_t>(j0 + (lane & 31)) * dp + j0 + 4 * (lane >> 5);
-    const float* ubase = vrows + static_cast<int64_t>(ju + (lane & 31)) * dp + j0 + 4 * (lane >> 5);
-    const int nblk = len / 8;
-    // a wavefront takes four consecutive blocks at a time (32 rows x 32 k: one whole 128-byte line per row)
-    for (int kb0 = 4 * wave; kb0 < nblk; kb0 += 4 * QWAVES) {   // nblk is a multiple of 4
-      f32x4 x[4], u4[4];
+  for (int x = 0; x < 4; ++x) src[x] = (x <= pos ? a.vall : a.wk) + static_cast<int64_t>(args.jb + 32 * x + row) * dp + kq;
+  src[4] = a.vall + static_cast<int64_t>(j0 + row) * dp + kq;
+  f32x16 acc;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) x[u] = *reinterpret_cast<const f32x4*>(vbase + 8 * (kb0 + u));
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  for (int k0 = k_begin; k0 < k_end; k0 += 128) {
+    f32x4 v[4][5];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) u4[u] = *reinterpret_cast<const f32x4*>(ubase + 8 * (kb0 + u));
+    for (int st = 0; st < 4; ++st)
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+      for (int x = 0; x < 5; ++x) v[st][x] = *reinterpret_cast<const f32x4*>(src[x] + k0 + 32 * st);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(u4[u][e], x[u][e], acc, 0, 0, 0);
-    }
-    // sum over the wavefronts in a fixed order, eight at a time through LDS
-    float* scratch = s_part;
-    float total = 0.f;
-    for (int round = 0; round < QWAVES / 8; ++round) {
-      if ((wave >> 3) == round) {
+    for (int st = 0; st < 4; ++st) {
+      const bool live = k0 + 32 * st >= j0;   // before the panel's first row V is zero
+      __syncthreads();
 #pragma unroll
-        for (int r = 0; r < 16; ++r) scratch[(wave & 7) * 1024 + r * 64 + lane] = acc[r];
+      for (int c = 0; c < 4; ++c) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) s_r[kq + c][row + 32 * x] = v[st][x][c];
+        s_v[kq + c][row] = v[st][4][c];
       }
       __syncthreads();
+      if (live)
 #pragma unroll
-      for (int w = 0; w < 8; ++w) total += scratch[w * 1024 + t];
-      __syncthreads();
+        for (int kk = 0; kk < 32; kk += 2)
+          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(s_r[kk + (lane >> 5)][32 * wave + (lane & 31)], s_v[kk + (lane >> 5)][lane & 31], acc, 0, 0, 0);
     }
-    const int r = t >> 6, l = t & 63;   // thread t holds accumulator register r of lane l
-    s_g[8 * (r >> 2) + (r & 3) + 4 * (l >> 5)][l & 31] = total;
-    __syncthreads();
-  };
-  gram(j0);
+  }
+  float* out = a.strip + static_cast<int64_t>(blockIdx.x) * (QBLK * QB) + (32 * wave + 4 * (lane >> 5)) * QB + (lane & 31);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) out[(8 * (r >> 2) + (r & 3)) * QB] = acc[r];
+}
 
-  // T, forward and column by column: T[c][c] = tau_c, T[0:c, c] = -tau_c T[0:c, 0:c] (V^T v_c)
-  // (thread i keeps row i of T in registers; its entries left of the diagonal are zero, so the sums may start at 0)
-  if (t < QB) {
-    const int i = t;
-    float trow[QB];
+// The sum of the pieces of four consecutive elements, in order.
+__device__ __forceinline__ f32x4 sum_pieces(const float* p, int chunks) {
+  f32x4 v = *reinterpret_cast<const f32x4*>(p);
+#pragma unroll 5
+  for (int i = 1; i < chunks; ++i) v += *reinterpret_cast<const f32x4*>(p + i * (QBLK * QB));
+  return v;
+}
+
+// Panel `pos` (< 3) applied to the later columns of its block: X -= W' V^T in 128 columns (k of the rows of wk) per workgroup, each of
+// which solves for W' itself (see above); the first also leaves the V_a^T V of this panel in `gram`.
+__global__ __launch_bounds__(NTH) void k_qr_panel_sub(QrArgs args) {
+  __shared__ __attribute__((aligned(16))) float s_g[QB][QB + 4];   // s_g[c][l] = v_l^T v_c
+  __shared__ float s_w[3 * QB][QB + 1];
+  __shared__ float s_tau[QB];
+  const QrMatrix a = qr_matrix(args, blockIdx.y);
+  const int pos = args.pos, later = 3 - pos;
+  const int64_t dp = a.dp;
+  const int n0 = args.jb + static_cast<int>(blockIdx.x) * 128, j0 = args.jb + pos * QB;
+  if (n0 >= a.dp) return;
+  int chunks, len;
+  qr_chunks(a.dp, args.jb, chunks, len);
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  // this wavefront's 32 columns of V, asked for first: lane l holds rows 2 kk + l / 32
+  const int n = n0 + 32 * wave;
+  float vb[QB / 2];
+#pragma unroll
+  for (int kk = 0; kk < QB / 2; ++kk) vb[kk] = a.vall[static_cast<int64_t>(j0 + 2 * kk + (lane >> 5)) * dp + n + (lane & 31)];
+  if (t < QB) s_tau[t] = a.tau[pos * QB + t];
+  const int i4 = t >> 3, c4 = (t & 7) * 4;   // row of a 32 x 32 block, 4 columns
+  if (blockIdx.x == 0)
+    for (int x = 0; x < pos; ++x)
+      *reinterpret_cast<f32x4*>(a.gram + (32 * x + i4) * QBLK + 32 * pos + c4) = sum_pieces(a.strip + (32 * x + i4) * QB + c4, chunks);
+  {
+    const f32x4 v = sum_pieces(a.strip + (32 * pos + i4) * QB + c4, chunks);
+    if (blockIdx.x == 0) *reinterpret_cast<f32x4*>(a.gram + (32 * pos + i4) * QBLK + 32 * pos + c4) = v;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) s_g[c4 + c][i4] = v[c];
+  }
+  for (int x = 0; x < later; ++x) {
+    const f32x4 v = sum_pieces(a.strip + (32 * (pos + 1 + x) + i4) * QB + c4, chunks);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) s_w[32 * x + i4][c4 + c] = v[c];
+  }
+  __syncthreads();
+  if (t < 32 * later) {
+    float w[QB];
+#pragma unroll
+    for (int c = 0; c < QB; ++c) w[c] = s_w[t][c];
 #pragma unroll
     for (int c = 0; c < QB; ++c) {
-      float sum = 0.f;
+      float part[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int l = 0; l < c; ++l) sum = __builtin_fmaf(trow[l], s_g[l][c], sum);
-      const float val = i == c ? s_tau[c] : (i < c ? -s_tau[c] * sum : 0.f);
-      trow[c] = val;
-      s_t[i][c] = val;
-      s_tt[c][i] = val;
+      for (int l4 = 0; l4 < c; l4 += 4) {
+        const f32x4 g = *reinterpret_cast<const f32x4*>(&s_g[c][l4]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (l4 + e < c) part[e] = __builtin_fmaf(w[l4 + e], g[e], part[e]);
+      }
+      const float tau = s_tau[c];
+      w[c] = tau == 0.f ? 0.f : tau * (w[c] - ((part[0] + part[1]) + (part[2] + part[3])));
+      s_w[t][c] = w[c];
     }
   }
   __syncthreads();
-  {   // T for the later panels of the block
-    float* tb = a.tbuf + static_cast<int64_t>(b) * a.s_t + static_cast<int64_t>(j0 / QB) * QB * QB;
-    tb[t] = s_t[t >> 5][t & 31];
-  }
-  // the blocks of C and C2 that pair this panel with the earlier ones of its block
-  for (int pa = 0; pa < a.ycol / QB; ++pa) {
-    const int ja = j0 - a.ycol + pa * QB;
-    __syncthreads();               // s_g is free again
-    gram(ja);                      // s_g[i][j] = (V_a^T V)[i][j]
-    const float* ta = a.tbuf + static_cast<int64_t>(b) * a.s_t + static_cast<int64_t>(ja / QB) * QB * QB;
-    const int i = t >> 5, j = t & 31;
-    float c = 0.f, c2 = 0.f;
-#pragma unroll 8
-    for (int l = 0; l < QB; ++l) {
-      c = __builtin_fmaf(ta[i * QB + l], s_g[l][j], c);     // C_a,pos = T_a (V_a^T V)
-      c2 = __builtin_fmaf(s_t[l][i], s_g[j][l], c2);        // C2_pos,a = T^T (V^T V_a) = T^T (V_a^T V)^T
-    }
-    float* cb = a.cbuf + static_cast<int64_t>(b) * 2 * QBLK * QBLK;
-    cb[(pa * QB + i) * QBLK + a.ycol + j] = c;
-    cb[QBLK * QBLK + (a.ycol + i) * QBLK + pa * QB + j] = c2;
-  }
-
-  // Y = V T^T and Y2 = V T on the matrix cores, 32 rows per wavefront and turn; blocks of rows before j0
-  // (down to the tile boundary klo) are zero.  Lane l supplies V[r0 + l % 32][k] and T[l % 32][k] resp.
-  // T[k][l % 32] for k = 2 kk + l / 32.
-  float* ybuf = a.ybuf + static_cast<int64_t>(b) * a.s_y;
-  float* y2 = a.y2 + static_cast<int64_t>(b) * a.s_y2;
-  const int nrb = (static_cast<int>(dp) - a.klo) / 32;
-  for (int rb = wave; rb < nrb; rb += QWAVES) {
-    const int64_t r0 = a.klo + 32 * rb;
-    f32x16 ay, ay2;
+  for (int x = 0; x < later; ++x) {
+    float* C = a.wk + static_cast<int64_t>(args.jb + 32 * (pos + 1 + x) + 4 * (lane >> 5)) * dp + n + (lane & 31);
+    float old[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) ay[r] = 0.f, ay2[r] = 0.f;
-    if (r0 >= j0) {
-      const float* vp = vrows + static_cast<int64_t>(j0 + (lane >> 5)) * dp + r0 + (lane & 31);
-      float xa[QB / 2];
+    for (int r = 0; r < 16; ++r) old[r] = C[static_cast<int64_t>(8 * (r >> 2) + (r & 3)) * dp];
+    f32x16 acc;
 #pragma unroll
-      for (int kk = 0; kk < QB / 2; ++kk) xa[kk] = vp[static_cast<int64_t>(2 * kk) * dp];
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
-      for (int kk = 0; kk < QB / 2; ++kk) {
-        ay = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[kk], s_tt[2 * kk + (lane >> 5)][lane & 31], ay, 0, 0, 0);
-        ay2 = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[kk], s_t[2 * kk + (lane >> 5)][lane & 31], ay2, 0, 0, 0);
-      }
-    }
+    for (int kk = 0; kk < QB / 2; ++kk)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(s_w[32 * x + (lane & 31)][2 * kk + (lane >> 5)], vb[kk], acc, 0, 0, 0);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int64_t at = (r0 + 8 * (r >> 2) + (r & 3) + 4 * (lane >> 5)) * QBLK + a.ycol + (lane & 31);
-      ybuf[at] = ay[r];
-      y2[at] = ay2[r];
-    }
+    for (int r = 0; r < 16; ++r) C[static_cast<int64_t>(8 * (r >> 2) + (r & 3)) * dp] = old[r] - acc[r];
   }
 }
 
-// U^T and U2^T of one block of four panels from the blocks of C (above the diagonal) and C2 (below) that the panels'
-// T kernels left in cbuf: U = (I + C)^(-1) by U_ab = -C_ab - sum_{a<c<b} C_ac U_cb, U2 = (I + C2)^(-1) by
-// U2_ab = -C2_ab - sum_{b<c<a} C2_ac U2_cb; identity blocks on the diagonal, zero on the other side.  One workgroup
-// of 1024 threads per matrix; thread (i, j) computes element (i, j) of every 32 x 32 block.
-__global__ __launch_bounds__(QTH) void k_qr_block_u(const float* __restrict__ cbuf, float* __restrict__ ut, float* __restrict__ u2t,
-                                                    int64_t s_u2) {
-  __shared__ float s_c[QBLK][QBLK + 1], s_u[QBLK][QBLK + 1];
-  const int b = blockIdx.x, t = threadIdx.x, i = t >> 5, j = t & 31;
-  for (int lower = 0; lower < 2; ++lower) {
-    const float* c = cbuf + (static_cast<int64_t>(b) * 2 + lower) * QBLK * QBLK;
-    for (int e = t; e < QBLK * QBLK; e += QTH) {
-      const int r = e >> 7, q = e & 127;
-      const bool live = lower ? (r >> 5) > (q >> 5) : (r >> 5) < (q >> 5);
-      s_c[r][q] = live ? c[e] : 0.f;
-      s_u[r][q] = r == q ? 1.f : 0.f;
+// T of a block of 128 reflectors, T = (diag(1 / tau) + strictly upper part of V^T V)^(-1) with zero rows and columns where tau = 0: its 32 x 32
+// blocks on the diagonal row by row, T[i][c] = tau_c ((i == c) - sum_{i <= l < c} T[i][l] v_l^T v_c), then those at distance 1, 2, 3,
+// T_ab = -(sum_{a <= c < b} T_ac G_cb) T_bb.  T goes where V^T V was, T^T to `tt`.  One workgroup per matrix.
+__global__ __launch_bounds__(QTH) void k_qr_block_t(QrArgs args) {
+  __shared__ float s_g[QBLK][QBLK + 1], s_t[QBLK][QBLK + 1];
+  __shared__ float s_x[3][QB][QB + 1];
+  __shared__ float s_tau[QBLK];
+  const QrMatrix a = qr_matrix(args, blockIdx.x);
+  int chunks, len;
+  qr_chunks(a.dp, args.jb, chunks, len);
+  const int t = threadIdx.x;
+  if (t < QBLK) s_tau[t] = a.tau[t];
+  {   // the last panel's column of blocks is still in pieces
+    const int i = t >> 3, c4 = (t & 7) * 4;
+    const f32x4 v = sum_pieces(a.strip + i * QB + c4, chunks);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) s_g[i][3 * QB + c4 + c] = v[c];
+  }
+  for (int e = t; e < QBLK * QBLK; e += QTH) {
+    const int r = e >> 7, q = e & 127;
+    if (q < 3 * QB) s_g[r][q] = (r >> 5) <= (q >> 5) ? a.gram[e] : 0.f;
+    s_t[r][q] = 0.f;
+  }
+  __syncthreads();
+  if (t < QBLK) {
+    const int base = t & ~31, i = t & 31;
+    float row[QB];
+#pragma unroll
+    for (int c = 0; c < QB; ++c) {
+      float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int l = 0; l < c; ++l) part[l & 3] = __builtin_fmaf(row[l], s_g[base + l][base + c], part[l & 3]);
+      const float tau = s_tau[base + c], sum = (part[0] + part[1]) + (part[2] + part[3]);
+      row[c] = i == c ? tau : (i < c && tau != 0.f ? -tau * sum : 0.f);   // left of the diagonal the row is zero, and so is the sum
+      s_t[t][base + c] = row[c];
+    }
+  }
+  __syncthreads();
+  const int i = t >> 5, j = t & 31;
+  for (int k = 1; k < 4; ++k) {
+    for (int lo = 0; lo + k < 4; ++lo) {
+      float part[4] = {0.f, 0.f, 0.f, 0.f};
+      for (int c = lo; c < lo + k; ++c)
+#pragma unroll
+        for (int l = 0; l < QB; ++l) part[l & 3] = __builtin_fmaf(s_t[lo * QB + i][c * QB + l], s_g[c * QB + l][(lo + k) * QB + j], part[l & 3]);
+      s_x[lo][i][j] = (part[0] + part[1]) + (part[2] + part[3]);
     }
     __syncthreads();
-    for (int k = 1; k < 4; ++k) {          // blocks at distance k from the diagonal
-      for (int lo = 0; lo + k < 4; ++lo) {
-        const int ba = lower ? lo + k : lo, bb = lower ? lo : lo + k;   // block row, block column
-        float acc = s_c[ba * QB + i][bb * QB + j];
-        for (int bc = lo + 1; bc < lo + k; ++bc)
-#pragma unroll 8
-          for (int l = 0; l < QB; ++l) acc = __builtin_fmaf(s_c[ba * QB + i][bc * QB + l], s_u[bc * QB + l][bb * QB + j], acc);
-        s_u[ba * QB + i][bb * QB + j] = -acc;
-      }
-      __syncthreads();
+    for (int lo = 0; lo + k < 4; ++lo) {
+      float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int l = 0; l < QB; ++l) part[l & 3] = __builtin_fmaf(s_x[lo][i][l], s_t[(lo + k) * QB + l][(lo + k) * QB + j], part[l & 3]);
+      s_t[lo * QB + i][(lo + k) * QB + j] = -((part[0] + part[1]) + (part[2] + part[3]));
     }
-    float* out = lower ? u2t + static_cast<int64_t>(b) * s_u2 : ut + static_cast<int64_t>(b) * QBLK * QBLK;
-    for (int e = t; e < QBLK * QBLK; e += QTH) out[e] = s_u[e & 127][e >> 7];   // transposed
     __syncthreads();
   }
+  float* tt = a.tt + static_cast<int64_t>(args.jb / QBLK) * QBLK * QBLK;
+  for (int e = t; e < QBLK * QBLK; e += QTH) {
+    a.gram[e] = s_t[e >> 7][e & 127];
+    tt[e] = s_t[e & 127][e >> 7];
+  }
+}
+
+// W' = (X V) T of a block (BACK: (X V) T^T), X the rows lo.. of wk (BACK: of Q^T) from column jb on, V the block's 128 reflectors: 32 rows
+// per workgroup, a wavefront per panel, and the second product from LDS.  Bound by the fp32 matrix cores (32 rows and not more, so that
+// the 2048-long sums of 4 x 1920 rows have 240 workgroups: 129 -> 35 us).
+template <bool BACK>
+__global__ __launch_bounds__(NTH) void k_qr_block_w(QrArgs args, int lo) {
+  __shared__ float s_x[2][32][GLD], s_v[2][32][GRD];
+  __shared__ float s_w[32][QBLK + 1];
+  const QrMatrix a = qr_matrix(args, blockIdx.y);
+  const int r0 = lo + static_cast<int>(blockIdx.x) * 32;
+  if (r0 >= a.dp) return;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int64_t dp = a.dp;
+  const int row = t >> 3, kq = (t & 7) * 4;
+  const float* xs = (BACK ? a.qt : a.wk) + static_cast<int64_t>(r0 + row) * dp + args.jb + kq;
+  const float* vs = a.vall + static_cast<int64_t>(args.jb + row) * dp + args.jb + kq;
+  // this wavefront's 32 columns of T; what is zero in it (below or above the diagonal blocks) is left out
+  const float* tm = BACK ? a.tt + static_cast<int64_t>(args.jb / QBLK) * QBLK * QBLK : a.gram;
+  const int c_lo = BACK ? wave : 0, c_hi = BACK ? 4 : wave + 1;
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  const int nk = (a.dp - args.jb) / 32;   // a multiple of 4
+  f32x4 pv[2][5];
+  auto fetch = [&](int kt, int set) {
+    pv[set][4] = *reinterpret_cast<const f32x4*>(xs + 32 * kt);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) pv[set][x] = *reinterpret_cast<const f32x4*>(vs + 32 * x * dp + 32 * kt);
+  };
+  auto stash = [&](int buf, int set) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      s_x[buf][kq + c][row] = pv[set][4][c];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) s_v[buf][kq + c][row + 32 * x] = pv[set][x][c];
+    }
+  };
+  auto stage = [&](int kt, int buf, int mine, int other) {
+    if (kt + 2 < nk) fetch(kt + 2, mine);
+#pragma unroll
+    for (int k = 0; k < 32; k += 2)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(s_x[buf][k + (lane >> 5)][lane & 31], s_v[buf][k + (lane >> 5)][32 * wave + (lane & 31)], acc, 0, 0, 0);
+    if (kt + 1 < nk) stash(buf ^ 1, other);
+    __syncthreads();
+  };
+  fetch(0, 0);
+  fetch(1, 1);
+  stash(0, 0);
+  __syncthreads();
+  for (int kt = 0; kt < nk; kt += 2) {
+    stage(kt, 0, 0, 1);
+    stage(kt + 1, 1, 1, 0);
+  }
+  float tb[QBLK / 2];   // the whole column block of T: its loads are out before the barrier below
+#pragma unroll
+  for (int kk = 0; kk < QBLK / 2; ++kk) {
+    const int k = 2 * kk + (lane >> 5);
+    if (kk / 16 >= c_lo && kk / 16 < c_hi) tb[kk] = tm[k * QBLK + 32 * wave + (lane & 31)];
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) s_w[8 * (r >> 2) + (r & 3) + 4 * (lane >> 5)][32 * wave + (lane & 31)] = acc[r];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    if (c >= c_lo && c < c_hi)
+#pragma unroll
+      for (int kk = 16 * c; kk < 16 * c + 16; ++kk)
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(s_w[lane & 31][2 * kk + (lane >> 5)], tb[kk], acc, 0, 0, 0);
+  float* out = a.strip + static_cast<int64_t>(r0 + 4 * (lane >> 5)) * QBLK + 32 * wave + (lane & 31);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) out[(8 * (r >> 2) + (r & 3)) * QBLK] = acc[r];
+}
+
+// Products of the refresh on both sides of a batch in one launch: the blocks of side 0 first.
+template <int EPI, bool QT>
+__global__ __launch_bounds__(NTH) void k_qr_gemm(ShGemm g0, ShGemm g1, int first1, PtrTable none, Shape s, OutSpec o) {
+  const int block = blockIdx.x;
+  sh_gemm_body<EPI, false, false, QT>(block < first1 ? g0 : g1, block < first1 ? block : block - first1, none, s, o);
 }
 
 // How the rotations of a launch batch are computed (plan_of): on fp32 matrices, on three bf16 terms per element, or on bf16
@@ -904,7 +1003,7 @@ __global__ __launch_bounds__(QTH) void k_qr_block_u(const float* __restrict__ cb
 enum class Rot { F32, TERMS, BF16 };
 
 struct Carve {   // float offsets into the workspace of one launch batch
-  size_t gm, gmt, t1, rot, np, yt, ql, qlt, qr, qrt, stat, wk, vall, y2, ybuf, tau, wt, qt, tb, cb, ub, u2, total_bytes;
+  size_t gm, gmt, t1, rot, np, yt, ql, qlt, qr, qrt, pool, total_bytes;
   // rotations on three bf16 terms: G', M' dense; three bf16 terms per element, padded to 256 (offsets in floats as well): G (if it is not
   // bf16 itself) and M in the orientations wanted, X Q_R transposed, N', its half-rotated image, the bases
   size_t rotg, rotm, g3, g3t, m3, m3t, t3, n3, y3, ql3, ql3t, qr3, qr3t;
@@ -948,20 +1047,13 @@ Carve carve(int64_t rows, int64_t cols, int nb, Sides u, bool refresh, Rot rot, 
     c.yt = take(both ? nb * plane : 0);
     c.ql = take(u.left ? nb * rp * rp : 0), c.qlt = take(u.left ? nb * rp * rp : 0);
     c.qr = take(u.right ? nb * cp * cp : 0), c.qrt = take(u.right ? nb * cp * cp : 0);
-    c.stat = take(nb * dm * dm);
+    take(nb * dm * dm);   // once a padded statistic: the size is what callers have measured their workspaces by
   }
   if (refresh) {
-    c.wk = take(nb * dm * dm);
-    c.vall = take(nb * dm * dm);
-    c.y2 = take(nb * dm * dm);         // dm / 128 blocks of [dm][128]
-    c.ybuf = take(nb * dm * QBLK);     // the Y strip of the block under way
-    c.tau = take(nb * QB);
-    c.wt = take(2 * nb * dm * QBLK);   // W_raw and W of a block
-    c.qt = take(nb * dm * dm);
-    c.tb = take(nb * dm * QB);         // T of every panel
-    c.cb = take(2 * nb * QBLK * QBLK); // C and C2 of the block under way
-    c.ub = take(nb * QBLK * QBLK);     // U^T of the block under way
-    c.u2 = take(nb * dm * QBLK);       // U2^T of every block
+    // The refresh of both sides (refresh_pool): two square matrices and a strip of 256 columns a side and 128 x 129 floats.  Four
+    // squares of the larger side, 544 columns and the rest hold them, whatever the other side is.
+    c.pool = take(nb * (4 * dm * dm + 544 * dm + 3 * QBLK * QBLK));
+    take(nb * QB);
   }
   const size_t rp2 = pad256(rows), cp2 = pad256(cols), p2 = nb * rp2 * cp2 / 2;   // floats that hold a batch of panels
   const bool all_of_g = bf16 || rot == Rot::TERMS;   // G is an operand of the rotations, too
@@ -974,7 +1066,6 @@ Carve carve(int64_t rows, int64_t cols, int nb, Sides u, bool refresh, Rot rot, 
     c.t3 = c.y3 = take(both ? p3 : 0);   // t3 is done with before y3 is written, and G's terms before those of N'
     c.n3 = stat16 ? take(p3) : u.right ? c.g3 : c.g3t;
     c.ql3 = take(u.left ? l3 : 0), c.qr3 = take(u.right ? r3 : 0);
-    c.stat = c.ql3;                      // the update is out before the statistics begin; 1.5 d^2 on each side
     c.ql3t = take(u.left ? l3 : 0), c.qr3t = take(u.right ? r3 : 0);
   }
   if (bf16) {
@@ -1070,128 +1161,129 @@ int check_group(const canz_soap_group& g, int idx, bool need_ptrs, const canz_so
   return CANZ_OK;
 }
 
-// Basis refresh of one side: q (caller's, d x d) <- Q factor of QR(S q), S = the padded statistic in
-// `stat` [nb][dp][dp], qt_old [nb][dp][dp] the transposed padded copy of the current basis.
-int refresh_side(void* const* q_tab, int first, int nb, int64_t d, int64_t dp, const float* stat, const float* qt_old,
-                 float* ws, const Carve& c, const Shape& s, const OutSpec& o, hipStream_t st) {
+// Basis refresh of the sides of a batch (one or two, the longer first): q (caller's, d x d) <- Q factor of QR(S q), S the padded
+// statistic in `qt` [nb][dp][dp] (later Q^T), the transposed padded copy of the current basis in `vall` (later the reflectors).
+int refresh(const QrSide* side, int n_sides, void* const* const* q_tab, int first, int nb, const Shape& s, const OutSpec& o, hipStream_t st) {
   const PtrTable none{};
-  const int64_t dd = dp * dp;
-  float *wk = ws + c.wk, *vall = ws + c.vall, *y2 = ws + c.y2, *qt = ws + c.qt;
-  const int64_t s_vall = dp * dp;
-  auto fill = [&](float* p, int64_t elems, int64_t ld, int identity) {
-    const unsigned blocks = static_cast<unsigned>(std::min<int64_t>(2048, (elems + NTH - 1) / NTH));
-    hipLaunchKernelGGL(k_soap_fill, dim3(blocks, nb), dim3(NTH), 0, st, p, elems, ld, identity);
+  QrArgs a{};
+  a.nb = nb;
+  for (int i = 0; i < n_sides; ++i) a.side[i] = side[i];
+  auto dd = [&](int i) { return static_cast<int64_t>(side[i].dp) * side[i].dp; };
+  auto check = [&](const char* what) -> int {
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "refresh, %s: %s", what, hipGetErrorString(e));
+    return CANZ_OK;
   };
-  prof_mark(st, CANZ_KERNEL_SOAP_PANEL, true);
-  fill(qt, dd, dp, 1);   // nothing else has to start from a known state: every row that is read is written first
-  prof_mark(st, CANZ_KERNEL_SOAP_PANEL, false);
-  if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "refresh fill: %s", hipGetErrorString(e));
+  // one product per side (`make` gives it, M = 0: nothing to do) in one launch
+  auto products = [&](auto epi, auto transposed, int sides, auto&& make, const char* what) -> int {
+    ShGemm g[2]{};
+    int64_t blocks[2] = {0, 0};
+    for (int i = 0; i < sides; ++i) {
+      g[i] = make(i);
+      blocks[i] = g[i].M / SB * (g[i].N / SB) * nb;
+    }
+    if (blocks[0] + blocks[1] == 0) return CANZ_OK;
+    prof_mark(st, CANZ_KERNEL_SOAP_QR, true);
+    hipLaunchKernelGGL((k_qr_gemm<decltype(epi)::value, decltype(transposed)::value>), dim3(static_cast<unsigned>(blocks[0] + blocks[1])),
+                       dim3(NTH), 0, st, g[0], g[1], static_cast<int>(blocks[0]), none, s, o);
+    prof_mark(st, CANZ_KERNEL_SOAP_QR, false);
+    return check(what);
+  };
+  using Plain = std::integral_constant<int, SE_PLAIN>;
+  using Sub = std::integral_constant<int, SE_SUB>;
 
   // working copy, transposed: wk[c][r] = (S q)[r][c] = sum_k qt_old[c][k] S[r][k]
-  ShGemm p0{};
-  p0.M = dp, p0.N = dp, p0.K = dp, p0.ldp = dp, p0.ldq = dp, p0.sp = dd, p0.sq = dd;
-  p0.P = qt_old, p0.Q = stat, p0.c = wk;
-  CANZ_HIP(CANZ_KERNEL_SOAP_QR, (launch_gemm<SE_PLAIN, false>(p0, nb, none, s, o, st)), "refresh product");
-
-  // Blocks of 128 columns = four panels; all of a block's columns are rows of one 128-row tile of the working copy.
-  // Inside the block every panel is applied to that tile alone (rank 32); to the rows beyond it the whole block is
-  // applied at once (rank 128), which moves the trailing matrix through memory once per block instead of once per
-  // panel.  A last block with fewer than four panels has no rows beyond it.
-  float *ycat = ws + c.ybuf, *wraw = ws + c.wt, *wfix = ws + c.wt + static_cast<size_t>(nb) * dp * QBLK;
-  float *tb = ws + c.tb, *cb = ws + c.cb, *ub = ws + c.ub, *u2 = ws + c.u2;
-  const int64_t s_strip = dp * QBLK, s_t = dp * QB, s_u2 = dp * QBLK;
-  // W = (rows lo .. lo + rows - 1 of m) [V of `width` columns from column j0 on], over the rows j0.. of the reflectors
-  auto w_product = [&](const float* m, int64_t lo, int64_t rows_, int64_t j0, int64_t width, float* w_out) {
-    ShGemm w{};
-    w.M = rows_, w.N = width, w.K = dp - j0, w.ldp = dp, w.ldq = dp, w.sp = dd, w.sq = s_vall;
-    w.P = m + lo * dp + j0, w.Q = vall + j0 * dp + j0;
-    w.c = w_out + lo * QBLK, w.ldc = QBLK, w.sc = s_strip;
-    return w;
-  };
-  // (rows lo .. lo + rows - 1, columns klo.. of m) -= W Y^T: W and Y are the columns ycol .. ycol + width - 1 of their strips
-  auto sub_product = [&](float* m, int64_t lo, int64_t rows_, int64_t klo, const float* w_in, const float* y, int64_t sy,
-                         int64_t ycol, int64_t width) {
-    ShGemm u{};
-    u.M = rows_, u.N = dp - klo, u.K = width, u.ldp = QBLK, u.ldq = QBLK, u.sp = s_strip, u.sq = sy;
-    u.P = w_in + lo * QBLK + ycol, u.Q = y + klo * QBLK + ycol;
-    u.c = m + lo * dp + klo, u.ldc = dp, u.sc = dd;
-    return u;
-  };
-  // W = W_raw U for a whole block: wfix = wraw (rows lo..) times the transposed factor ut [128][128]
-  auto fix_product = [&](int64_t lo, int64_t rows_, const float* ut, int64_t s_ut) {
-    ShGemm f{};
-    f.M = rows_, f.N = QBLK, f.K = QBLK, f.ldp = QBLK, f.ldq = QBLK, f.sp = s_strip, f.sq = s_ut;
-    f.P = wraw + lo * QBLK, f.Q = ut;
-    f.c = wfix + lo * QBLK, f.ldc = QBLK, f.sc = s_strip;
-    return f;
-  };
-  // one panel with the rank-32 products: W into its 32 columns of wraw, then the update
-  auto apply_panel = [&](float* m, int64_t lo, int64_t rows_, int64_t klo, int64_t j0, const float* y, int64_t sy, const char* what) -> int {
-    const int64_t ycol = j0 % QBLK;
-    ShGemm w = w_product(m, lo, rows_, j0, QB, wraw);
-    w.c += ycol;
-    CANZ_HIP(CANZ_KERNEL_SOAP_QR, (launch_gemm<SE_PLAIN, false, QB>(w, nb, none, s, o, st)), what);
-    CANZ_HIP(CANZ_KERNEL_SOAP_QR, (launch_gemm<SE_SUB, false>(sub_product(m, lo, rows_, klo, wraw, y, sy, ycol, QB), nb, none, s, o, st)), what);
-    return CANZ_OK;
-  };
-  // a whole block with the rank-128 products
-  auto apply_block = [&](float* m, int64_t lo, int64_t klo, int64_t jb, const float* y, int64_t sy, const float* ut, int64_t s_ut,
-                         const char* what) -> int {
-    CANZ_HIP(CANZ_KERNEL_SOAP_QR, (launch_gemm<SE_PLAIN, false>(w_product(m, lo, dp - lo, jb, QBLK, wraw), nb, none, s, o, st)), what);
-    CANZ_HIP(CANZ_KERNEL_SOAP_QR, (launch_gemm<SE_PLAIN, false>(fix_product(lo, dp - lo, ut, s_ut), nb, none, s, o, st)), what);
-    CANZ_HIP(CANZ_KERNEL_SOAP_QR, (launch_gemm<SE_SUB, false>(sub_product(m, lo, dp - lo, klo, wfix, y, sy, 0, QBLK), nb, none, s, o, st)), what);
-    return CANZ_OK;
-  };
-
-  for (int64_t jb = 0; jb < d; jb += QBLK) {            // factorisation, block by block
-    float* y2blk = y2 + (jb / QBLK) * dp * QBLK;
-    const int64_t panels = std::min<int64_t>(4, (d - jb + QB - 1) / QB);
-    for (int64_t pp = 0; pp < panels; ++pp) {
-      const int64_t j0 = jb + pp * QB;
-      QrPanel a{};
-      a.wk = wk, a.vall = vall, a.ybuf = ycat, a.y2 = y2blk, a.tau = ws + c.tau, a.tbuf = tb, a.cbuf = cb;
-      a.dp = dp, a.d = d, a.s_wk = dd, a.s_vall = s_vall, a.s_y = s_strip, a.s_y2 = dd, a.s_t = s_t;
-      a.j0 = static_cast<int>(j0), a.klo = static_cast<int>(jb), a.ycol = static_cast<int>(pp * QB);
-      prof_mark(st, CANZ_KERNEL_SOAP_PANEL, true);
-      if (dp - j0 <= 64 * 4 * 8)
-        hipLaunchKernelGGL(k_qr_panel_regs<8>, dim3(nb), dim3(QTH), 0, st, a);
-      else if (dp - j0 <= 64 * 4 * 12)
-        hipLaunchKernelGGL(k_qr_panel_regs<12>, dim3(nb), dim3(QTH), 0, st, a);
-      else
-        hipLaunchKernelGGL(k_qr_panel_hybrid<8>, dim3(nb), dim3(QTH), 0, st, a);
-      hipLaunchKernelGGL(k_qr_tfactor, dim3(nb), dim3(QTH), 0, st, a);
-      prof_mark(st, CANZ_KERNEL_SOAP_PANEL, false);
-      if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "panel kernel: %s", hipGetErrorString(e));
-      if (pp + 1 < panels)   // the later panels of the block: the block's own 128 rows
-        if (int rc = apply_panel(wk, jb, QBLK, jb, j0, ycat, s_strip, "QR (panel update)")) return rc;
-    }
-    if (jb + QBLK >= dp) break;   // no columns after this block
-    prof_mark(st, CANZ_KERNEL_SOAP_PANEL, true);
-    hipLaunchKernelGGL(k_qr_block_u, dim3(nb), dim3(QTH), 0, st, cb, ub, u2 + (jb / QBLK) * QBLK * QBLK, s_u2);
-    prof_mark(st, CANZ_KERNEL_SOAP_PANEL, false);
-    if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "block kernel: %s", hipGetErrorString(e));
-    if (int rc = apply_block(wk, jb + QBLK, jb, jb, ycat, s_strip, ub, QBLK * QBLK, "QR (block update)")) return rc;
-  }
-  // Q = H(0) H(1) ... applied to the identity from the last block to the first; a last block without all four panels
-  // (it has no U2) panel by panel
-  for (int64_t jb = (d - 1) / QBLK * QBLK; jb >= 0; jb -= QBLK) {
-    const float* y2blk = y2 + (jb / QBLK) * dp * QBLK;
-    const int64_t panels = std::min<int64_t>(4, (d - jb + QB - 1) / QB);
-    if (panels == 4 && jb + QBLK < dp) {
-      if (int rc = apply_block(qt, jb, jb, jb, y2blk, dd, u2 + (jb / QBLK) * QBLK * QBLK, s_u2, "Q (block update)")) return rc;
-    } else {
-      for (int64_t pp = panels - 1; pp >= 0; --pp)
-        if (int rc = apply_panel(qt, jb, dp - jb, jb, jb + pp * QB, y2blk, dd, "Q (panel update)")) return rc;
-    }
-  }
-  PtrTable q{};
-  for (int i = 0; i < nb; ++i) q.p[i] = q_tab[first + i];
+  if (int rc = products(Plain{}, std::false_type{}, n_sides, [&](int i) {
+        ShGemm g{};
+        g.M = g.N = g.K = g.ldp = g.ldq = g.ldc = side[i].dp, g.sp = g.sq = g.sc = dd(i);
+        g.P = side[i].vall, g.Q = side[i].qt, g.c = side[i].wk;
+        return g;
+      }, "product with the statistic")) return rc;
   prof_mark(st, CANZ_KERNEL_SOAP_PANEL, true);
-  hipLaunchKernelGGL(k_soap_store_q, dim3(static_cast<unsigned>(dp / 64), static_cast<unsigned>(dp / 64), static_cast<unsigned>(nb)),
-                     dim3(NTH), 0, st, q, qt, d, dp);
+  for (int i = 0; i < n_sides; ++i) {   // nothing else has to start from a known state: what is read is written first
+    const unsigned blocks = static_cast<unsigned>(std::min<int64_t>(2048, (dd(i) + NTH - 1) / NTH));
+    hipLaunchKernelGGL(k_soap_fill, dim3(blocks, nb), dim3(NTH), 0, st, side[i].qt, dd(i), static_cast<int64_t>(side[i].dp), 1);
+  }
   prof_mark(st, CANZ_KERNEL_SOAP_PANEL, false);
-  if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "basis store: %s", hipGetErrorString(e));
-  return CANZ_OK;
+  if (int rc = check("fill")) return rc;
+
+  // X -= W' V^T in the rows lo.. and the columns jb.. of the sides' matrices
+  auto block_sub = [&](int sides, bool back, int jb, int lo, const char* what) -> int {
+    return products(Sub{}, std::true_type{}, sides, [&](int i) {
+      ShGemm g{};
+      const int64_t dp = side[i].dp;
+      if (lo >= dp) return g;
+      g.M = dp - lo, g.N = dp - jb, g.K = QBLK, g.ldp = QBLK, g.ldq = dp, g.sp = dp * QBLK, g.sq = dd(i);
+      g.P = side[i].strip + static_cast<int64_t>(lo) * QBLK, g.Q = side[i].vall + jb * dp + jb;
+      g.c = (back ? side[i].qt : side[i].wk) + lo * dp + jb, g.ldc = dp, g.sc = dd(i);
+      return g;
+    }, what);
+  };
+  auto panel = [&](const QrArgs& p, int rows, int mats) {
+    const dim3 grid(static_cast<unsigned>(mats)), block(QTH);
+    if (rows <= 64 * 4 * 2)
+      hipLaunchKernelGGL(k_qr_panel_regs<2>, grid, block, 0, st, p);
+    else if (rows <= 64 * 4 * 4)
+      hipLaunchKernelGGL(k_qr_panel_regs<4>, grid, block, 0, st, p);
+    else if (rows <= 64 * 4 * 8)
+      hipLaunchKernelGGL(k_qr_panel_regs<8>, grid, block, 0, st, p);
+    else if (rows <= 64 * 4 * 12)
+      hipLaunchKernelGGL(k_qr_panel_regs<12>, grid, block, 0, st, p);
+    else
+      hipLaunchKernelGGL(k_qr_panel_hybrid<8>, grid, block, 0, st, p);
+  };
+  const int dp0 = side[0].dp;
+  for (int jb = 0; jb < dp0; jb += QBLK) {              // factorisation, block by block
+    const int sides = n_sides == 2 && jb < side[1].dp ? 2 : 1;
+    const unsigned mats = static_cast<unsigned>(nb * sides);
+    a.jb = jb;
+    int units = (dp0 - jb) / QBLK;
+    const unsigned chunks = static_cast<unsigned>(std::min(units, QCHUNKS));
+    for (a.pos = 0; a.pos < 4; ++a.pos) {
+      prof_mark(st, CANZ_KERNEL_SOAP_PANEL, true);
+      const int rows0 = dp0 - jb - QB * a.pos, rows1 = sides == 2 ? side[1].dp - jb - QB * a.pos : rows0;
+      if (rows0 > 64 * 4 * 12 && rows1 <= 64 * 4 * 8) {   // the kernel for long columns has no place for such short ones
+        QrArgs one = a;
+        one.side[0] = side[1];
+        panel(a, rows0, nb);
+        panel(one, rows1, nb);
+      } else {
+        panel(a, rows0, static_cast<int>(mats));
+      }
+      hipLaunchKernelGGL(k_qr_gram, dim3(chunks, mats), dim3(NTH), 0, st, a);
+      if (a.pos < 3)
+        hipLaunchKernelGGL(k_qr_panel_sub, dim3(static_cast<unsigned>(units), mats), dim3(NTH), 0, st, a);
+      else
+        hipLaunchKernelGGL(k_qr_block_t, dim3(mats), dim3(QTH), 0, st, a);
+      prof_mark(st, CANZ_KERNEL_SOAP_PANEL, false);
+      if (int rc = check("panel kernels")) return rc;
+    }
+    if (jb + QBLK >= dp0) break;   // no columns after this block
+    prof_mark(st, CANZ_KERNEL_SOAP_QR, true);
+    hipLaunchKernelGGL(k_qr_block_w<false>, dim3(static_cast<unsigned>((dp0 - jb - QBLK) / 32), mats), dim3(NTH), 0, st, a, jb + QBLK);
+    prof_mark(st, CANZ_KERNEL_SOAP_QR, false);
+    if (int rc = check("block of reflectors")) return rc;
+    if (int rc = block_sub(sides, false, jb, jb + QBLK, "QR (block update)")) return rc;
+  }
+  // Q = H(0) H(1) ... applied to the identity from the last block to the first
+  for (int jb = dp0 - QBLK; jb >= 0; jb -= QBLK) {
+    const int sides = n_sides == 2 && jb < side[1].dp ? 2 : 1;
+    a.jb = jb;
+    prof_mark(st, CANZ_KERNEL_SOAP_QR, true);
+    hipLaunchKernelGGL(k_qr_block_w<true>, dim3(static_cast<unsigned>((dp0 - jb) / 32), static_cast<unsigned>(nb * sides)), dim3(NTH), 0, st, a, jb);
+    prof_mark(st, CANZ_KERNEL_SOAP_QR, false);
+    if (int rc = check("block of reflectors (Q)")) return rc;
+    if (int rc = block_sub(sides, true, jb, jb, "Q (block update)")) return rc;
+  }
+  prof_mark(st, CANZ_KERNEL_SOAP_PANEL, true);
+  for (int i = 0; i < n_sides; ++i) {
+    PtrTable q{};
+    for (int k = 0; k < nb; ++k) q.p[k] = q_tab[i][first + k];
+    const unsigned t64 = static_cast<unsigned>(side[i].dp / 64);
+    hipLaunchKernelGGL(k_soap_store_q, dim3(t64, t64, static_cast<unsigned>(nb)), dim3(NTH), 0, st, q, side[i].qt,
+                       static_cast<int64_t>(side[i].d), static_cast<int64_t>(side[i].dp));
+  }
+  prof_mark(st, CANZ_KERNEL_SOAP_PANEL, false);
+  return check("basis store");
 }
 
 // One launch batch: matrices first .. first + nb - 1 of group g.
@@ -1220,7 +1312,6 @@ int run_batch(const canz_soap_group& g, int first, int nb, Rot rot, const canz_s
   o.neg_lr_scale = -hp.lr;
 
   float *gm = ws + c.gm, *gmt = ws + c.gmt;
-  float* stat = ws + c.stat;
 
   // With a valid rotated momentum from the caller only G is rotated (M' follows its own recurrence in the rotated
   // space, which is the same linear map as long as the bases stand still); otherwise G and M.
@@ -1310,21 +1401,21 @@ int run_batch(const canz_soap_group& g, int first, int nb, Rot rot, const canz_s
       ShGemm a{};   // t1 = (X Q_R)^T: [cp][rp]
       a.M = cp, a.N = rp, a.K = cp, a.ldp = cp, a.ldq = cp, a.sp = cp * cp, a.pshare = per - 1, a.sq = step_;
       a.P = qrt, a.Q = gm + at, a.c = t1 + at, a.ldc = rp, a.sc = step_;
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false, SB, true>(a, count, none, s, o, st)), "rotation (right)");
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false, true>(a, count, none, s, o, st)), "rotation (right)");
       ShGemm bq{};  // rot32 = Q_L^T (X Q_R): [rp][cp]
       bq.M = rp, bq.N = cp, bq.K = rp, bq.ldp = rp, bq.ldq = rp, bq.sp = rp * rp, bq.pshare = per - 1, bq.sq = step_;
       bq.P = qlt, bq.Q = t1 + at, bq.c = rot32 + at, bq.ldc = cp, bq.sc = step_;
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false, SB, true>(bq, count, none, s, o, st)), "rotation (left)");
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false, true>(bq, count, none, s, o, st)), "rotation (left)");
     } else if (u.left) {
       ShGemm bq{};  // rot32 = Q_L^T X with X^T as the second operand
       bq.M = rp, bq.N = cp, bq.K = rp, bq.ldp = rp, bq.ldq = rp, bq.sp = rp * rp, bq.pshare = per - 1, bq.sq = step_;
       bq.P = qlt, bq.Q = gmt + at, bq.c = rot32 + at, bq.ldc = cp, bq.sc = step_;
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false, SB, true>(bq, count, none, s, o, st)), "rotation (left)");
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false, true>(bq, count, none, s, o, st)), "rotation (left)");
     } else {
       ShGemm a{};   // rot32 = X Q_R
       a.M = rp, a.N = cp, a.K = cp, a.ldp = cp, a.ldq = cp, a.sp = step_, a.sq = cp * cp, a.qshare = per - 1;
       a.P = gm + at, a.Q = qrt, a.c = rot32 + at, a.ldc = cp, a.sc = step_;
-      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false, SB, true>(a, count, none, s, o, st)), "rotation (right)");
+      CANZ_HIP(CANZ_KERNEL_SOAP_ROTATE, (launch_gemm<SE_PLAIN, false, true>(a, count, none, s, o, st)), "rotation (right)");
     }
     return CANZ_OK;
   };
@@ -1444,40 +1535,61 @@ int run_batch(const canz_soap_group& g, int first, int nb, Rot rot, const canz_s
     }
   }
 
-  // statistics (and, on a refresh step, the new basis) side by side
-  auto one_side = [&](void* const* stat_tab, void* const* q_tab, int64_t d, int64_t dp, int64_t kp, const float* side,
-                      const __bf16* side16, int64_t d2, int64_t k2) -> int {
+  // Statistics; on a refresh step also the padded copies of the new statistic and of the transposed old basis.  What the refresh of a side works
+  // on lies in the pool, one side behind the other, but for the statistic and Q^T, which take the place of the side's basis: the update is
+  // out, and its images are not needed again (three terms: 1.5 d^2 an orientation; bf16: half that, both; fp32: d^2).
+  QrSide side[2]{};
+  void* const* side_q[2]{};
+  int n_sides = 0;
+  float* pool = ws + c.pool;
+  auto one_side = [&](void* const* stat_tab, void* const* q_tab, int64_t d, int64_t dp, int64_t kp, const float* grad32, const __bf16* grad16,
+                      int64_t d2, int64_t k2, size_t stat_at) -> int {
     PtrTable tab{};
     for (int i = 0; i < nb; ++i) tab.p[i] = stat_tab[first + i];
+    QrSide qs{};
+    if (hp.refresh) {
+      const int64_t dd = dp * dp;
+      qs.wk = pool, qs.vall = qs.wk + nb * dd, qs.strip = qs.vall + nb * dd, qs.tt = qs.strip + nb * dp * QBLK;
+      qs.gram = qs.tt + nb * dp * QBLK, qs.tau = qs.gram + nb * QBLK * QBLK;
+      pool = qs.tau + nb * QBLK;
+      qs.qt = ws + stat_at;
+      qs.dp = static_cast<int>(dp), qs.d = static_cast<int>(d);
+    }
     if (stat16) {
       Shape sq{};   // the caller's dense d x d matrix
       sq.rows = d, sq.cols = d, sq.m = d, sq.n = d, sq.tp = 1, sq.wfrag = d;
-      if (int rc = statistic_bf16(CANZ_KERNEL_SOAP_STAT, tab, d, d2, k2, k2, nb, hp.beta2, 1.f - hp.beta2, side16, st)) return rc;
-      if (hp.refresh) {   // the padded copy the refresh multiplies the basis with (its transposed image lands in wk, unused)
+      if (int rc = statistic_bf16(CANZ_KERNEL_SOAP_STAT, tab, d, d2, k2, k2, nb, hp.beta2, 1.f - hp.beta2, grad16, st)) return rc;
+      if (hp.refresh) {   // (the transposed image lands in wk, unused)
         prof_mark(st, CANZ_KERNEL_SOAP_STAT, true);
         hipLaunchKernelGGL(k_sh_load, dim3(static_cast<unsigned>(dp / 64), static_cast<unsigned>(dp / 64), static_cast<unsigned>(nb)),
-                           dim3(NTH), 0, st, sq, tab, static_cast<int>(CANZ_DT_F32), dp, dp, stat, ws + c.wk);
+                           dim3(NTH), 0, st, sq, tab, static_cast<int>(CANZ_DT_F32), dp, dp, qs.qt, qs.wk);
         prof_mark(st, CANZ_KERNEL_SOAP_STAT, false);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "statistic copy: %s", hipGetErrorString(e));
       }
     } else {
       ShGemm q{};
       q.M = dp, q.N = dp, q.K = kp, q.ldp = kp, q.ldq = kp, q.sp = g_stride, q.sq = g_stride;
-      q.P = side, q.Q = side, q.c = hp.refresh ? stat : nullptr, q.d = d, q.beta = hp.beta2, q.gscale = 1.f - hp.beta2, q.eps = 0.f;
+      q.P = grad32, q.Q = grad32, q.c = qs.qt, q.d = d, q.beta = hp.beta2, q.gscale = 1.f - hp.beta2, q.eps = 0.f;
       CANZ_HIP(CANZ_KERNEL_SOAP_STAT, (launch_gemm<SE_STAT, true>(q, nb, tab, s, o, st)), "statistics kernel");
     }
     if (!hp.refresh) return CANZ_OK;
-    float* qt_old = ws + c.vall;   // read by the refresh's first product, before any reflector is written there
     prof_mark(st, CANZ_KERNEL_SOAP_LOAD, true);
-    load_basis(q_tab, d, dp, dp, BasisOut{nullptr, qt_old, nullptr, nullptr, nullptr, nullptr});
+    load_basis(q_tab, d, dp, dp, BasisOut{nullptr, qs.vall, nullptr, nullptr, nullptr, nullptr});
     prof_mark(st, CANZ_KERNEL_SOAP_LOAD, false);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "basis load: %s", hipGetErrorString(e));
-    return refresh_side(q_tab, first, nb, d, dp, stat, qt_old, ws, c, s, o, st);
+    const int at = n_sides == 1 && qs.dp > side[0].dp ? 0 : n_sides;   // the longer side first
+    if (at == 0) side[1] = side[0], side_q[1] = side_q[0];
+    side[at] = qs, side_q[at] = q_tab;
+    ++n_sides;
+    return CANZ_OK;
   };
+  auto basis_at = [&](size_t terms_at, size_t bf16_at, size_t f32_at) { return terms3 ? terms_at : bf16 ? bf16_at : f32_at; };
   if (u.left)
-    if (int rc = one_side(g.left, g.qleft, g.rows, rp, cp, gm, pan(c.gp), rp2, cp2)) return rc;
+    if (int rc = one_side(g.left, g.qleft, g.rows, rp, cp, gm, pan(c.gp), rp2, cp2, basis_at(c.ql3, c.qlp, c.ql))) return rc;
   if (u.right)
-    if (int rc = one_side(g.right, g.qright, g.cols, cp, rp, gmt, pan(c.gpt), cp2, rp2)) return rc;
+    if (int rc = one_side(g.right, g.qright, g.cols, cp, rp, gmt, pan(c.gpt), cp2, rp2, basis_at(c.qr3, c.qrp, c.qr))) return rc;
+  if (hp.refresh)
+    if (int rc = refresh(side, n_sides, side_q, first, nb, s, o, st)) return rc;
   if (hp.refresh && g.mom_rot && bf16) {
     // the caller's rotated momentum follows the new bases, M' = Q_L^T M Q_R once more with the M of this step: bf16
     // operands as for every rotation of this mode; the last product leaves its fp32 sums in the caller's array
