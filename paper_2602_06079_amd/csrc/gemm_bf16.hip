@@ -1038,7 +1038,7 @@ __global__ __launch_bounds__(NTHREADS) void k_split_finish(GemmDims d, EpiArgs e
 }
 
 // ---------------------------------------------------------------------------------------
-// Small-product variant: 128 x 128 or 64 x 64 tiles, one block per tile, up to three resident blocks per CU.
+// Small-product variant: 128 x 128, 64 x 64 or 256 x 128 tiles, one block per tile, up to three resident blocks per CU.
 //
 // The persistent 256 x 256 kernel above is built for products with many rounds of long tiles.
 // A launch with few tiles (the 0.6B-shaped shares: 260 Gram tiles for 256 CUs) leaves most
@@ -1066,22 +1066,25 @@ __global__ __launch_bounds__(NTHREADS) void k_split_finish(GemmDims d, EpiArgs e
 // 64 x 64: four times as many blocks, two on a CU.  us a launch, 128 x 128 with three stages -> the variant that now runs:
 //   64 x 64, 8 stages     8 x 256^2, k 512: 7.9 -> 5.0;  2 x 512^2, k 4096: 38 -> 22;  a 1024 x 2048 update: 12.8 -> 9.3
 //   128 x 128, 8 stages   2048^2, k 4096: 38 -> 29.5;  seven 1024^2 with k 1024 to 3072: 38 -> 33
+// Left-over tiles for half of the CUs, and launches of no more, are 256 x 128 where k is long: one per CU, with six stages and three
+// quarters of the bytes per FLOP: 128 tiles of 3072 x 1024 with k 18432 385 -> 325, 96 of the Shampoo roots 310 -> 276.
 // blocks that share a CU:
 constexpr int small_blocks(int sm, int nst) { return nst == 3 ? 3 : sm == 64 ? 2 : 1; }
 
 template <int EPI, int SM, int NST, typename Args>
 __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf16_small(Args args, EpiArgs e_launch, Shape s, OutSpec o) {
-  static_assert((SM == 128 && NST == 3) || NST == 8, "variants");
-  constexpr int S_STAGE = 2 * SM * BK;   // elements per stage: the P and the Q part of a panel
-  constexpr int R = BM / SM;             // tiles per 256 rows
-  constexpr int TI = SM / 64;            // 32 x 32 MFMA tiles of a wavefront, along either side
-  constexpr int LPK = 2 * TI;            // direct loads of a wavefront per stage
+  static_assert((SM == 128 && NST == 3) || (SM == 256 && NST == 6) || (SM <= 128 && NST == 8), "variants");
+  constexpr int SN = SM == 256 ? 128 : SM;
+  constexpr int S_STAGE = (SM + SN) * BK;        // elements per stage: the P and the Q part of a panel
+  constexpr int RM = BM / SM, RN = BN / SN;      // tiles per 256 rows, columns
+  constexpr int TI = SM / 64, TJ = SN / 64;      // 32 x 32 MFMA tiles of a wavefront
+  constexpr int LPK = TI + TJ;                   // direct loads of a wavefront per stage
   // one array per stage, as in the large kernel
   __shared__ __attribute__((aligned(1024))) __bf16 sa[S_STAGE];
   __shared__ __attribute__((aligned(1024))) __bf16 sb[S_STAGE];
   __shared__ __attribute__((aligned(1024))) __bf16 sc[S_STAGE];
   __shared__ __attribute__((aligned(1024))) __bf16 sd[NST > 3 ? S_STAGE : 8], se[NST > 3 ? S_STAGE : 8], sf_[NST > 3 ? S_STAGE : 8],
-      sg[NST > 3 ? S_STAGE : 8], sh[NST > 3 ? S_STAGE : 8];
+      sg[NST > 6 ? S_STAGE : 8], sh[NST > 6 ? S_STAGE : 8];
 
   GemmDims d{};
   const __bf16 *P = nullptr, *Q = nullptr;
@@ -1095,14 +1098,15 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
     logical = xcd < rem ? xcd * (per + 1) + q : rem * (per + 1) + (xcd - rem) * per + q;
   }
   // A launch of small tiles alone (e.main_grid = 0) numbers those that there are, one block each.  Behind a launch of the
-  // large kernel R * R consecutive blocks are the parts of one 256 x 256 tile of its numbering, from tile e.main_grid on.
+  // large kernel consecutive blocks are the parts of one 256 x 256 tile of its numbering, from tile e.main_grid on; 256 x 128 tiles
+  // always are.
   // A product of two symmetric matrices is symmetric only to rounding, and within 128 x 128 elements on the diagonal all of it is
   // computed, here as in the large kernel: 64 x 64 tiles are then numbered as the quarters of 128 x 128 ones.
   const bool behind = e.main_grid > 0;
   constexpr bool QUARTERS = epi_two_factors(EPI) && SM == 64;
-  const int parts = behind ? R : QUARTERS ? 2 : 1;
-  const int part = logical % (parts * parts);
-  logical = e.main_grid + logical / (parts * parts);
+  const int parts_m = behind ? RM : QUARTERS ? 2 : 1, parts_n = behind || SM == 256 ? RN : QUARTERS ? 2 : 1;
+  const int part = logical % (parts_m * parts_n);
+  logical = e.main_grid + logical / (parts_m * parts_n);
   if constexpr (Args::multi) {
     int j = 0;
     while (j + 1 < args.n && logical >= args.begin[j + 1]) ++j;
@@ -1114,7 +1118,7 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
   } else {
     d = args.d, P = args.P, Q = args.Q;
   }
-  const int tile = parts * SM;
+  const int tile = parts_m * SM;
   const int tiles_m = static_cast<int>(d.M) / tile, tiles_n = static_cast<int>(d.N) / tile;
   const bool symmetric = epi_symmetric(EPI);
   const int per_batch = symmetric ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
@@ -1122,56 +1126,64 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
   decode_tile<EPI>(logical, tiles_m, tiles_n, per_batch, b, tm, tn);
   // in a diagonal tile of a symmetric product what is below the diagonal is the mirror of what is above
   constexpr int LEVEL = QUARTERS ? 1 : 0;   // what lies on the diagonal is counted in tiles of SM << LEVEL
-  tm = parts * tm + part / parts, tn = parts * tn + part % parts;
-  if (symmetric && tm >> LEVEL > tn >> LEVEL) return;
-  const bool mirrored = symmetric && tm >> LEVEL != tn >> LEVEL;
+  tm = parts_m * tm + part / parts_n, tn = parts_n * tn + part % parts_n;
+  if (SM < 256 && symmetric && tm >> LEVEL > tn >> LEVEL) return;
 
   const int t = threadIdx.x;
   const int lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = wave >> 1, wn = wave & 1;
+  // (of a 256 x 128 tile, which may hold both, in 128 x 128 elements: the rows of a wavefront and the columns of the tile)
+  const bool mirrored = symmetric && (SM == 256 ? 2 * tm + wm != tn : tm >> LEVEL != tn >> LEVEL);
+  const bool below = SM == 256 && symmetric && 2 * tm + wm > tn;
   const int64_t nkb = d.K / BK;
   const int nk = static_cast<int>(nkb) * (epi_terms(EPI) ? d.nseg : 1);
   // panels per row block (operands that are a part of longer rows: only of the last products and those of several terms)
   const int64_t nkp = epi_terms(EPI) || epi_final(EPI) ? d.ldp / BK : nkb, nkq = epi_terms(EPI) || epi_final(EPI) ? d.ldq / BK : nkb;
 
-  // global -> LDS: the part of a panel is SM / 16 pieces of 1 KiB; wavefront w copies the pieces w (and w + 4) of both
-  // operands, lane l the 16 bytes at l * 16
-  const __bf16* pl = P + static_cast<int64_t>(b) * d.sp + (static_cast<int64_t>(tm / R) * nkp) * PANEL_ELEMS +
-                     (tm % R) * (SM * BK) + wave * 512 + lane * 8;
-  const __bf16* ql = Q + static_cast<int64_t>(b) * d.sq + (static_cast<int64_t>(tn / R) * nkq) * PANEL_ELEMS +
-                     (tn % R) * (SM * BK) + wave * 512 + lane * 8;
+  // global -> LDS: the part of a panel is SM / 16 (SN / 16) pieces of 1 KiB; wavefront w copies the pieces w, w + 4, ..
+  // lane l the 16 bytes at l * 16
+  const __bf16* pl = P + static_cast<int64_t>(b) * d.sp + (static_cast<int64_t>(tm / RM) * nkp) * PANEL_ELEMS +
+                     (tm % RM) * (SM * BK) + wave * 512 + lane * 8;
+  const __bf16* ql = Q + static_cast<int64_t>(b) * d.sq + (static_cast<int64_t>(tn / RN) * nkq) * PANEL_ELEMS +
+                     (tn % RN) * (SN * BK) + wave * 512 + lane * 8;
   TermWalk wp(d.pseg, nkb), wq(d.qseg, nkb);
-  auto fetch = [&](__bf16* st, int kt) {
+  auto fetch_one = [&](__bf16* st, int kt, int idx) {   // idx 0 .. TI - 1: pieces of P, then those of Q
     const int64_t off = static_cast<int64_t>(kt < nk ? kt : nk - 1) * PANEL_ELEMS;  // past the end: a harmless re-read
-    const int64_t po = epi_terms(EPI) ? wp.off : off, qo = epi_terms(EPI) ? wq.off : off;
-#pragma unroll
-    for (int g = 0; g < TI; ++g) {
-      __builtin_amdgcn_global_load_lds(CANZ_GLB(pl + po + g * 2048), CANZ_LDS(st + wave * 512 + g * 2048), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds(CANZ_GLB(ql + qo + g * 2048), CANZ_LDS(st + SM * BK + wave * 512 + g * 2048), 16, 0, 0);
+    if (idx < TI) {
+      const int64_t po = epi_terms(EPI) ? wp.off : off;
+      __builtin_amdgcn_global_load_lds(CANZ_GLB(pl + po + idx * 2048), CANZ_LDS(st + wave * 512 + idx * 2048), 16, 0, 0);
+      if (epi_terms(EPI) && idx == TI - 1) wp.next();
+    } else {
+      const int64_t qo = epi_terms(EPI) ? wq.off : off;
+      __builtin_amdgcn_global_load_lds(CANZ_GLB(ql + qo + (idx - TI) * 2048), CANZ_LDS(st + SM * BK + wave * 512 + (idx - TI) * 2048), 16, 0, 0);
+      if (epi_terms(EPI) && idx == LPK - 1) wq.next();
     }
-    if (epi_terms(EPI)) wp.next(), wq.next();
+  };
+  auto fetch = [&](__bf16* st, int kt) {
+#pragma unroll
+    for (int idx = 0; idx < LPK; ++idx) fetch_one(st, kt, idx);
   };
 
-  f32x16 acc[TI][TI];
+  f32x16 acc[TI][TJ];
 #pragma unroll
   for (int i = 0; i < TI; ++i)
 #pragma unroll
-    for (int j = 0; j < TI; ++j)
+    for (int j = 0; j < TJ; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   const int frag_row = lane & 31, frag_kg = lane >> 5;
-  bf16x8 fa[2][TI], fb[2][TI];
+  bf16x8 fa[2][TI], fb[2][TJ];
   auto frag = [&](const __bf16* st, int kk, int idx) {   // idx 0 .. TI - 1: rows of P, then those of Q
-    const int chunk = kk * 2 + frag_kg, i = idx % TI;
+    const int chunk = kk * 2 + frag_kg;
     if (idx < TI)
-      fa[kk][i] = *reinterpret_cast<const bf16x8*>(st + swz((wm * TI + i) * 32 + frag_row, chunk));
+      fa[kk][idx] = *reinterpret_cast<const bf16x8*>(st + swz((wm * TI + idx) * 32 + frag_row, chunk));
     else
-      fb[kk][i] = *reinterpret_cast<const bf16x8*>(st + SM * BK + swz((wn * TI + i) * 32 + frag_row, chunk));
+      fb[kk][idx - TI] = *reinterpret_cast<const bf16x8*>(st + SM * BK + swz((wn * TJ + idx - TI) * 32 + frag_row, chunk));
   };
   auto mma = [&](int kk, int idx) {
-    const int i = idx / TI, j = idx % TI;
+    const int i = idx / TJ, j = idx % TJ;
     acc[i][j] = mfma<EPI>(fa[kk][i], fb[kk][j], acc[i][j]);
   };
   if constexpr (NST == 3) {
@@ -1179,11 +1191,11 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-        for (int i = 0; i < TI; ++i) frag(st, kk, i), frag(st, kk, TI + i);
+        for (int idx = 0; idx < LPK; ++idx) frag(st, kk, idx);
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-        for (int idx = 0; idx < TI * TI; ++idx) mma(kk, idx);
+        for (int idx = 0; idx < TI * TJ; ++idx) mma(kk, idx);
     };
     // One k-step on stage `cur`: the 4 loads of the following step may stay in flight; after the
     // barrier every wavefront has finished the step before, whose stage `nxt2` then receives step kt + 2.
@@ -1206,20 +1218,20 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
     __builtin_amdgcn_s_waitcnt(0x0070);  // the re-reads past the end have landed before the block leaves
   } else {
     // As in the large kernel: the operands are double-buffered in registers, those of a half-step read under the MFMAs of
-    // the one before.  In the middle of step kt every wavefront has read all of `cur`, which then receives step kt + 8, and
-    // step kt + 1 has landed, `younger` later ones still in flight.  nk is a multiple of 8; the last eight steps request nothing and
-    // the queue drains.
+    // the one before.  In the middle of step kt every wavefront has read all of `cur`, which then receives step kt + NST, and
+    // step kt + 1 has landed, `younger` later ones still in flight.
     using Yes = std::true_type;
     using No = std::false_type;
+    constexpr int NM = TI * TJ, NF = TI + TJ;   // MFMAs and operands of a half-step
 #define CANZ_FENCE() __builtin_amdgcn_sched_barrier(0)
     auto k_step = [&](auto fetches, auto younger, __bf16* cur, const __bf16* nxt, int kt) {
       constexpr int left = decltype(younger)::value;   // -1: the last step
 #pragma unroll
-      for (int idx = 0; idx < TI * TI; ++idx) {
+      for (int idx = 0; idx < NM; ++idx) {
         mma(0, idx);
         CANZ_FENCE();
 #pragma unroll
-        for (int x = 0; x < 2 / TI; ++x) frag(cur, 1, idx * (2 / TI) + x);
+        for (int x = idx * NF / NM; x < (idx + 1) * NF / NM; ++x) frag(cur, 1, x);
         CANZ_FENCE();
       }
       if constexpr (left >= 0) {
@@ -1229,51 +1241,71 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
         CANZ_FENCE();
       }
 #pragma unroll
-      for (int idx = 0; idx < TI * TI; ++idx) {
+      for (int idx = 0; idx < NM; ++idx) {
         mma(1, idx);
         CANZ_FENCE();
         if (left >= 0)
 #pragma unroll
-          for (int x = 0; x < 2 / TI; ++x) frag(nxt, 0, idx * (2 / TI) + x);
+          for (int x = idx * NF / NM; x < (idx + 1) * NF / NM; ++x) frag(nxt, 0, x);
         CANZ_FENCE();
-        if (decltype(fetches)::value && idx == 0) fetch(cur, kt + 8);
+        if (decltype(fetches)::value)
+#pragma unroll
+          for (int x = idx * NF / NM; x < (idx + 1) * NF / NM; ++x) fetch_one(cur, kt + NST, x);
         CANZ_FENCE();
       }
     };
 #undef CANZ_FENCE
 #define CANZ_LEFT(n) std::integral_constant<int, n> {}
-    fetch(sa, 0), fetch(sb, 1), fetch(sc, 2), fetch(sd, 3), fetch(se, 4), fetch(sf_, 5), fetch(sg, 6), fetch(sh, 7);
-    constexpr int vm0 = 7 * LPK;
+    fetch(sa, 0), fetch(sb, 1), fetch(sc, 2), fetch(sd, 3), fetch(se, 4), fetch(sf_, 5);
+    if constexpr (NST == 8) fetch(sg, 6), fetch(sh, 7);
+    constexpr int vm0 = (NST - 1) * LPK;
     __builtin_amdgcn_s_waitcnt((vm0 & 15) | 0x70 | (vm0 >> 4) << 14);
     __builtin_amdgcn_s_barrier();
 #pragma unroll
-    for (int idx = 0; idx < 2 * TI; ++idx) frag(sa, 0, idx);
+    for (int idx = 0; idx < NF; ++idx) frag(sa, 0, idx);
     int kt = 0;
-    for (; kt + 8 < nk; kt += 8) {
-      k_step(Yes{}, CANZ_LEFT(6), sa, sb, kt);
-      k_step(Yes{}, CANZ_LEFT(6), sb, sc, kt + 1);
-      k_step(Yes{}, CANZ_LEFT(6), sc, sd, kt + 2);
-      k_step(Yes{}, CANZ_LEFT(6), sd, se, kt + 3);
-      k_step(Yes{}, CANZ_LEFT(6), se, sf_, kt + 4);
-      k_step(Yes{}, CANZ_LEFT(6), sf_, sg, kt + 5);
-      k_step(Yes{}, CANZ_LEFT(6), sg, sh, kt + 6);
-      k_step(Yes{}, CANZ_LEFT(6), sh, sa, kt + 7);
+    if constexpr (NST == 8) {   // nk is a multiple of 8; the last eight steps request nothing and the queue drains
+      for (; kt + 8 < nk; kt += 8) {
+        k_step(Yes{}, CANZ_LEFT(6), sa, sb, kt);
+        k_step(Yes{}, CANZ_LEFT(6), sb, sc, kt + 1);
+        k_step(Yes{}, CANZ_LEFT(6), sc, sd, kt + 2);
+        k_step(Yes{}, CANZ_LEFT(6), sd, se, kt + 3);
+        k_step(Yes{}, CANZ_LEFT(6), se, sf_, kt + 4);
+        k_step(Yes{}, CANZ_LEFT(6), sf_, sg, kt + 5);
+        k_step(Yes{}, CANZ_LEFT(6), sg, sh, kt + 6);
+        k_step(Yes{}, CANZ_LEFT(6), sh, sa, kt + 7);
+      }
+      k_step(No{}, CANZ_LEFT(6), sa, sb, kt);
+      k_step(No{}, CANZ_LEFT(5), sb, sc, kt);
+      k_step(No{}, CANZ_LEFT(4), sc, sd, kt);
+      k_step(No{}, CANZ_LEFT(3), sd, se, kt);
+      k_step(No{}, CANZ_LEFT(2), se, sf_, kt);
+      k_step(No{}, CANZ_LEFT(1), sf_, sg, kt);
+      k_step(No{}, CANZ_LEFT(0), sg, sh, kt);
+      k_step(No{}, CANZ_LEFT(-1), sh, sa, kt);
+    } else {
+      for (; kt + 6 <= nk; kt += 6) {
+        k_step(Yes{}, CANZ_LEFT(4), sa, sb, kt);
+        k_step(Yes{}, CANZ_LEFT(4), sb, sc, kt + 1);
+        k_step(Yes{}, CANZ_LEFT(4), sc, sd, kt + 2);
+        k_step(Yes{}, CANZ_LEFT(4), sd, se, kt + 3);
+        k_step(Yes{}, CANZ_LEFT(4), se, sf_, kt + 4);
+        k_step(Yes{}, CANZ_LEFT(4), sf_, sa, kt + 5);
+      }
+      if (kt < nk) k_step(Yes{}, CANZ_LEFT(4), sa, sb, kt), ++kt;
+      if (kt < nk) k_step(Yes{}, CANZ_LEFT(4), sb, sc, kt), ++kt;
+      if (kt < nk) k_step(Yes{}, CANZ_LEFT(4), sc, sd, kt), ++kt;
+      if (kt < nk) k_step(Yes{}, CANZ_LEFT(4), sd, se, kt), ++kt;
+      if (kt < nk) k_step(Yes{}, CANZ_LEFT(4), se, sf_, kt), ++kt;
+      __builtin_amdgcn_s_waitcnt(0x0070);  // the re-reads past the end have landed
     }
-    k_step(No{}, CANZ_LEFT(6), sa, sb, kt);
-    k_step(No{}, CANZ_LEFT(5), sb, sc, kt);
-    k_step(No{}, CANZ_LEFT(4), sc, sd, kt);
-    k_step(No{}, CANZ_LEFT(3), sd, se, kt);
-    k_step(No{}, CANZ_LEFT(2), se, sf_, kt);
-    k_step(No{}, CANZ_LEFT(1), sf_, sg, kt);
-    k_step(No{}, CANZ_LEFT(0), sg, sh, kt);
-    k_step(No{}, CANZ_LEFT(-1), sh, sa, kt);
 #undef CANZ_LEFT
   }
 
   // ---- epilogue.  Accumulator register r of lane l in MFMA tile (i, j): row 32 i + 8 (r / 4) + 4 (l / 32) + (r % 4),
   //      column 32 j + (l % 32) of the wavefront's part, a quarter of the tile.
   const int lj = lane & 31, lh = lane >> 5;
-  const int row_w = tm * SM + wm * 32 * TI, col_w = tn * SM + wn * 32 * TI;
+  const int row_w = tm * SM + wm * 32 * TI, col_w = tn * SN + wn * 32 * TJ;
   // Where the elements of 32 x 32 tile (i, j) of the wavefront's part lie in a panel image: a part that is the same for
   // all lanes, a lane's own offset (two for the straight image, by the parity of the group of 8 rows; four for the
   // transposed one, by group) and a constant.
@@ -1293,7 +1325,7 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int j = 0; j < TI; ++j) {
+      for (int j = 0; j < TJ; ++j) {
         const int col = col_w + 32 * j + lj;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -1315,7 +1347,7 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
 #pragma unroll
       for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < TI; ++j)
+        for (int j = 0; j < TJ; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[i][j][r] *= f;
     } else if (const __bf16* const m1 = static_cast<const __bf16*>(e.sym.aux) + static_cast<int64_t>(b) * d.M * d.N; m1 != nullptr) {
@@ -1327,7 +1359,7 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
 #pragma unroll
       for (int i = 0; i < TI; ++i) {
 #pragma unroll
-        for (int j = 0; j < TI; ++j) {
+        for (int j = 0; j < TJ; ++j) {
           asm volatile("" ::: "memory");   // or the compiler brings the loads of all four tiles together and spills
           vec4 v1[4], v3[4];
           f32x4 rw[4];
@@ -1373,7 +1405,7 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
 #pragma unroll
       for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < TI; ++j)
+        for (int j = 0; j < TJ; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[i][j][r] *= inv;
     }
@@ -1381,14 +1413,14 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
 #pragma unroll
       for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < TI; ++j) asm volatile("" : "+v"(acc[i][j]));
+        for (int j = 0; j < TJ; ++j) asm volatile("" : "+v"(acc[i][j]));
     }
   } else if (e.scale) {
     const float sc1 = e.scale[b];
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int j = 0; j < TI; ++j)
+      for (int j = 0; j < TJ; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] *= sc1;
   }
@@ -1400,21 +1432,25 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
     const int64_t nkb = d.N >> 5, elems = NT * d.M * d.N;
     __bf16* const C = static_cast<__bf16*>(e.c) + static_cast<int64_t>(b) * elems;
     __bf16* const T = EPI == EPI_B3_SYM && e.ct ? static_cast<__bf16*>(e.ct) + static_cast<int64_t>(b) * elems : nullptr;
-    const bool diagonal = SYM && tm == tn && wm == wn;
-    float dv[TI];
+    if (below) return;
+    const bool diagonal = SYM && col_w >= row_w && col_w < row_w + 32 * TI;   // the part holds the diagonal elements of its columns
+    float dv[TJ];
     if (T && diagonal) {
 #pragma unroll
-      for (int i = 0; i < TI; ++i)
+      for (int j = 0; j < TJ; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (8 * (r >> 2) + (r & 3) + 4 * lh == lj) dv[i] = acc[i][i][r];
+        for (int i = 0; i < TI; ++i)
+          if (row_w + 32 * i == col_w + 32 * j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              if (8 * (r >> 2) + (r & 3) + 4 * lh == lj) dv[j] = acc[i][j][r];
     }
 #pragma unroll 1
     for (int term = 0; term < NT; ++term)
 #pragma unroll
       for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < TI; ++j) {
+        for (int j = 0; j < TJ; ++j) {
           const int64_t at = ((row_w >> 8) * NT * nkb + term * nkb + ((col_w + 32 * j) >> 5)) * PANEL_ELEMS + ((row_w & 255) + 32 * i) * PANEL_K;
           const int64_t tt = ((col_w >> 8) * NT * nkb + term * nkb + ((row_w + 32 * i) >> 5)) * PANEL_ELEMS + ((col_w & 255) + 32 * j) * PANEL_K;
           unsigned mine[8];
@@ -1446,9 +1482,9 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
     if (T && diagonal && ((lj >> 2) & 1) == lh) {
       __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0): the images are written, these elements go over theirs
 #pragma unroll
-      for (int i = 0; i < TI; ++i) {
-        const int64_t at = row_w + 32 * i + lj;
-        put_three_terms(T + panel_chunk_off(at, at & ~7, 3 * d.N) + (at & 7), nkb * PANEL_ELEMS, 1.25f - 0.25f * dv[i]);
+      for (int j = 0; j < TJ; ++j) {
+        const int64_t at = col_w + 32 * j + lj;
+        put_three_terms(T + panel_chunk_off(at, at & ~7, 3 * d.N) + (at & 7), nkb * PANEL_ELEMS, 1.25f - 0.25f * dv[j]);
       }
     }
     return;
@@ -1461,13 +1497,13 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
     // they are aligned to an element only, and the last columns go one by one).  All old values of 32 rows are requested
     // at once, from clamped addresses: a predicate or a switch of the type at each load would wait for it there and make the
     // epilogue a chain of 16 memory latencies.
-    constexpr int W = 32 * TI, LPR = W / 4, RPP = 64 / LPR, NX = 32 / RPP;
+    constexpr int W = 32 * TJ, LPR = W / 4, RPP = 64 / LPR, NX = 32 / RPP;
     const int ld = static_cast<int>(o.out_mode == CANZ_OUT_DELTA ? s.wfrag : s.cols);
     __syncthreads();
     float* sf = reinterpret_cast<float*>((wave < 2 ? sa : sb) + (wave & 1) * (S_STAGE / 2));
     const int rows = static_cast<int>(s.rows), cols = static_cast<int>(s.cols);
     const int col = col_w + (lane % LPR) * 4;
-    if (row_w >= rows || col_w >= cols) return;
+    if (row_w >= rows || col_w >= cols || below) return;
     const bool col_ok = col + 4 <= cols;             // all four columns
     const int n_tail = col_ok ? 0 : max(cols - col, 0);
     const bool all_rows = row_w + 32 * TI <= rows;   // uniform
@@ -1493,7 +1529,7 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
             res[x] = *reinterpret_cast<const vec*>(base + (static_cast<int64_t>(min(row0 + RPP * x, rows - 1)) * ld + c_in) * ESZ);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int j = 0; j < TI; ++j)
+        for (int j = 0; j < TJ; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r) sf[(8 * (r >> 2) + 4 * lh + (r & 3)) * W + 32 * j + lj] = acc[i][j][r];
         __builtin_amdgcn_sched_barrier(0);
@@ -1553,7 +1589,7 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
 #pragma unroll
   for (int i = 0; i < TI; ++i)
 #pragma unroll
-    for (int j = 0; j < TI; ++j) {
+    for (int j = 0; j < TJ; ++j) {
       const int col = col_w + 32 * j + (lj & ~1);
 #pragma unroll
       for (int rp = 0; rp < 8; ++rp) {
@@ -1570,7 +1606,7 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int j = 0; j < TI; ++j) {
+      for (int j = 0; j < TJ; ++j) {
         const int col = col_w + 32 * j + lj;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -1649,24 +1685,30 @@ int64_t renumber(ManyProblemsOf<MAX>& args) {
 template <int EPI, int SM, int NST, typename Args>
 void launch_small_as(Args args, EpiArgs e, int64_t first, int64_t tiles, const Shape& s, const OutSpec& o, hipStream_t st) {
   constexpr int R = BM / SM;
-  const int64_t blocks = first > 0 ? R * R * (tiles - first) : renumber<EPI, SM>(args);
+  const int64_t blocks = SM == 256 ? 2 * (tiles - first) : first > 0 ? R * R * (tiles - first) : renumber<EPI, SM>(args);
   e.main_grid = static_cast<int>(first);
   hipLaunchKernelGGL((k_gemm_nt_bf16_small<EPI, SM, NST, Args>), dim3(static_cast<unsigned>(blocks)), dim3(NTHREADS), 0, st, args, e, s, o);
 }
+// (the epilogues of matrices with their diagonal apart are written for square parts)
+constexpr bool epi_256x128(int epi) { return epi_terms(epi) || epi == EPI_UPDATE || epi_final(epi); }
 // Tiles [first, tiles) of the large kernel's numbering on the small one (k_gemm_nt_bf16_small says what the variants are for).  64 x 64
 // up to two blocks per CU: behind that they move twice the bytes for nothing (544 against 144 blocks of 128 x 128 at k = 4096: 33
 // us against 30; 1088 against 288: 52 and 50).  Eight stages up to one block per CU (288 blocks on 256 CUs: 1.1 times the three-stage
-// time) and from k = 1024 on, below which there is nothing to run ahead of (160 blocks, k 512: 9.9 us, three stages 9.4).
+// time) and from k = 1024 on, below which there is nothing to run ahead of (160 blocks, k 512: 9.9 us, three stages 9.4).  256 x 128 from 2048 on
+// (k = 1024, 88 tiles: 24 us against 22) and only where every one has a CU.
 template <int EPI, typename Args>
 void launch_small(const Args& args, const EpiArgs& e, int64_t first, int64_t tiles, int64_t longest_k, int64_t cus, const Shape& s,
                   const OutSpec& o, hipStream_t st) {
   Args numbered = args;
   const int64_t n128 = first > 0 ? 4 * (tiles - first) : renumber<EPI, 128>(numbered);
   const int64_t n64 = first > 0 ? 16 * (tiles - first) : renumber<EPI, 64>(numbered);
+  const bool wide = epi_256x128(EPI) && 2 * (tiles - first) <= cus && longest_k >= 2048;
   if (n64 <= 2 * cus)
     launch_small_as<EPI, 64, 8>(args, e, first, tiles, s, o, st);
   else if (n128 <= cus && longest_k >= 1024)
     launch_small_as<EPI, 128, 8>(args, e, first, tiles, s, o, st);
+  else if (wide)
+    launch_small_as<EPI, epi_256x128(EPI) ? 256 : 128, epi_256x128(EPI) ? 6 : 3>(args, e, first, tiles, s, o, st);
   else
     launch_small_as<EPI, 128, 3>(args, e, first, tiles, s, o, st);
 }

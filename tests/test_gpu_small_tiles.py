@@ -20,6 +20,7 @@ SHAPES = [
     (4, 515, 1537),                          # Gram 60 blocks of 128, update 280
     (9, 777, 1022),                          # Gram 324 blocks: three stages
     (3, 1029, 1283),                         # Gram 135 blocks, k = 1536: eight stages of 128
+    (1, 2050, 2563),                         # update 99 tiles, k = 2304: 256 x 128
 ]
 OUTS = ["param_f32", "param_bf16", "delta_f32", "delta_bf16"]
 
