@@ -32,23 +32,22 @@ struct alignas(16) Vec8<__bf16> {
 // Step 2 of the operator: M <- beta M + G, U = M (or G + beta M); step 1 (TP gather) is
 // the fragment lookup on the load.
 template <typename T, bool VEC>
-__global__ __launch_bounds__(NTHREADS) void k_momentum(Shape s, PtrTable grad, int grad_dtype, PtrTable mom,
-                                                        float beta, int nesterov, T* __restrict__ xw,
-                                                        T* __restrict__ xt, float* __restrict__ partial) {
+__device__ __forceinline__ void momentum_tile(const Shape& s, const void* const* grad, int grad_dtype, void* const* mom, float beta,
+                                              int nesterov, T* __restrict__ xw, T* __restrict__ xt, float* __restrict__ partial,
+                                              int bx, int by, int b, int tiles_x, int tiles_y) {
   typedef typename std::conditional<VEC, f32x4, f32x4_any>::type f32x4v;
   typedef typename std::conditional<VEC, bf16x8, bf16x8_any>::type bf16x8v;
   __shared__ float tile[TILE][TILE + 1];
   __shared__ float wsum[NTHREADS / 64];
 
-  const int b = blockIdx.z;
-  const int r0 = blockIdx.y * TILE, c0 = blockIdx.x * TILE;
+  const int r0 = by * TILE, c0 = bx * TILE;
   const int rows = static_cast<int>(s.rows), cols = static_cast<int>(s.cols);
   const int wf = static_cast<int>(s.wfrag);
   // straight = same orientation as the caller's matrix; transposed = the other one
   const int64_t pr = s.tall ? s.np : s.mp, pc = s.tall ? s.mp : s.np;
   T* straight = (s.tall ? xt : xw) + static_cast<int64_t>(b) * pr * pc;
   T* transposed = (s.tall ? xw : xt) + static_cast<int64_t>(b) * pr * pc;
-  float* mptr = static_cast<float*>(mom.p[b]);
+  float* mptr = static_cast<float*>(mom[b]);
 
   const int t = threadIdx.x;
   const int cv = (t & 7) * 8;
@@ -69,11 +68,11 @@ __global__ __launch_bounds__(NTHREADS) void k_momentum(Shape s, PtrTable grad, i
     const int64_t gi = static_cast<int64_t>(row) * wf + (col - f * wf);
     if (VEC || col + 8 <= cols) {
       if (grad_dtype == CANZ_DT_BF16) {
-        const bf16x8 gv = *reinterpret_cast<const bf16x8v*>(static_cast<const __bf16*>(grad.p[b * s.tp + f]) + gi);
+        const bf16x8 gv = *reinterpret_cast<const bf16x8v*>(static_cast<const __bf16*>(grad[b * s.tp + f]) + gi);
 #pragma unroll
         for (int e = 0; e < 8; ++e) g[half][e] = static_cast<float>(gv[e]);
       } else {
-        const f32x4v* gp = reinterpret_cast<const f32x4v*>(static_cast<const float*>(grad.p[b * s.tp + f]) + gi);
+        const f32x4v* gp = reinterpret_cast<const f32x4v*>(static_cast<const float*>(grad[b * s.tp + f]) + gi);
         const f32x4 g0 = gp[0], g1 = gp[1];
 #pragma unroll
         for (int e = 0; e < 4; ++e) g[half][e] = g0[e], g[half][4 + e] = g1[e];
@@ -86,8 +85,8 @@ __global__ __launch_bounds__(NTHREADS) void k_momentum(Shape s, PtrTable grad, i
 #pragma unroll
       for (int e = 0; e < 7; ++e) {
         if (col + e >= cols) break;
-        g[half][e] = grad_dtype == CANZ_DT_BF16 ? static_cast<float>(static_cast<const __bf16*>(grad.p[b])[gi + e])
-                                                : static_cast<const float*>(grad.p[b])[gi + e];
+        g[half][e] = grad_dtype == CANZ_DT_BF16 ? static_cast<float>(static_cast<const __bf16*>(grad[b])[gi + e])
+                                                : static_cast<const float*>(grad[b])[gi + e];
         mo[half][e] = mptr[static_cast<int64_t>(row) * cols + col + e];
       }
     }
@@ -140,18 +139,47 @@ __global__ __launch_bounds__(NTHREADS) void k_momentum(Shape s, PtrTable grad, i
   if ((t & 63) == 0) wsum[t >> 6] = ss;
   __syncthreads();
   if (t == 0) {
-    const int tiles = gridDim.x * gridDim.y;
-    partial[static_cast<int64_t>(b) * tiles + blockIdx.y * gridDim.x + blockIdx.x] =
-        (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+    partial[static_cast<int64_t>(b) * tiles_x * tiles_y + by * tiles_x + bx] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
   }
+}
+template <typename T, bool VEC>
+__global__ __launch_bounds__(NTHREADS) void k_momentum(Shape s, PtrTable grad, int grad_dtype, PtrTable mom,
+                                                        float beta, int nesterov, T* __restrict__ xw,
+                                                        T* __restrict__ xt, float* __restrict__ partial) {
+  momentum_tile<T, VEC>(s, grad.p, grad_dtype, mom.p, beta, nesterov, xw, xt, partial, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.x,
+                        gridDim.y);
+}
+// Several parts in one launch: the tiles of part 0, then of part 1, ...
+struct MomentumParts {
+  int n;
+  int begin[MAX_PARTS + 1];
+  MomentumPart<__bf16> part[MAX_PARTS];
+};
+template <bool VEC>
+__global__ __launch_bounds__(NTHREADS) void k_momentum_parts(MomentumParts a, PtrTable grad, PtrTable mom, float beta, int nesterov) {
+  int j = 0, tile = blockIdx.x;
+  while (j + 1 < a.n && tile >= a.begin[j + 1]) ++j;
+  const MomentumPart<__bf16>& p = a.part[j];
+  const Shape s = p.s;
+  tile -= a.begin[j];
+  const int tiles_x = static_cast<int>((s.tall ? s.mp : s.np) / TILE), tiles_y = static_cast<int>((s.tall ? s.np : s.mp) / TILE);
+  const int by = tile / tiles_x, bx = tile - by * tiles_x, b = by / tiles_y;
+  momentum_tile<__bf16, VEC>(s, grad.p + p.first_grad, p.grad_dtype, mom.p + p.first_mom, beta, nesterov, p.xw, p.xt, p.partial, bx,
+                             by - b * tiles_y, b, tiles_x, tiles_y);
 }
 
 // Step 3 of the operator, as a scalar: 1 / (||U||_F + eps).  One block per matrix; the
 // tile sums are added in fp64 in a fixed order, so the result does not depend on timing.
-__global__ __launch_bounds__(NTHREADS) void k_norm_scale(int n_partial, const float* __restrict__ partial, float eps,
-                                                          float* __restrict__ scale, float* __restrict__ scale2) {
+struct NormBatches {
+  int n;
+  NormBatch b[MAX_KINDS];
+};
+__global__ __launch_bounds__(NTHREADS) void k_norm_scale(NormBatches batches, float eps) {
   __shared__ double red[NTHREADS];
-  const int b = blockIdx.x, t = threadIdx.x;
+  int b = blockIdx.x, j = 0;
+  while (j + 1 < batches.n && b >= batches.b[j].nb) b -= batches.b[j].nb, ++j;
+  const int n_partial = batches.b[j].n_partial, t = threadIdx.x;
+  const float* __restrict__ partial = batches.b[j].partial;
   double acc = 0.0;
   for (int i = t; i < n_partial; i += NTHREADS) acc += static_cast<double>(partial[static_cast<int64_t>(b) * n_partial + i]);
   red[t] = acc;
@@ -162,8 +190,8 @@ __global__ __launch_bounds__(NTHREADS) void k_norm_scale(int n_partial, const fl
   }
   if (t == 0) {
     const float sc = static_cast<float>(1.0 / (sqrt(red[0]) + static_cast<double>(eps)));
-    scale[b] = sc;
-    scale2[b] = sc * sc;
+    batches.b[j].scale[b] = sc;
+    batches.b[j].scale2[b] = sc * sc;
   }
 }
 
@@ -207,7 +235,38 @@ template hipError_t launch_momentum<float>(const Shape&, int, const PtrTable&, i
 
 hipError_t launch_norm_scale(int nb, int n_partial, const float* partial, float eps, float* scale, float* scale2,
                              hipStream_t st) {
-  hipLaunchKernelGGL(k_norm_scale, dim3(nb), dim3(NTHREADS), 0, st, n_partial, partial, eps, scale, scale2);
+  const NormBatch one{nb, n_partial, partial, scale, scale2};
+  return launch_norm_scale_batches(1, &one, eps, st);
+}
+
+hipError_t launch_norm_scale_batches(int n, const NormBatch* batches, float eps, hipStream_t st) {
+  if (n < 1 || n > MAX_KINDS) return hipErrorInvalidValue;
+  NormBatches a{};
+  a.n = n;
+  int blocks = 0;
+  for (int i = 0; i < n; ++i) a.b[i] = batches[i], blocks += batches[i].nb;
+  hipLaunchKernelGGL(k_norm_scale, dim3(static_cast<unsigned>(blocks)), dim3(NTHREADS), 0, st, a, eps);
+  return hipGetLastError();
+}
+
+hipError_t launch_momentum_parts(int n, const MomentumPart<__bf16>* parts, const PtrTable& grad, const PtrTable& mom, float beta,
+                                 int nesterov, hipStream_t st) {
+  if (n < 1 || n > MAX_PARTS) return hipErrorInvalidValue;
+  MomentumParts a{};
+  a.n = n;
+  int64_t tiles = 0;
+  bool vec = true;
+  for (int i = 0; i < n; ++i) {
+    a.part[i] = parts[i];
+    a.begin[i] = static_cast<int>(tiles);
+    tiles += static_cast<int64_t>(momentum_tiles(parts[i].s)) * parts[i].nb;
+    vec = vec && parts[i].s.cols % 8 == 0 && parts[i].s.wfrag % 8 == 0;
+  }
+  for (int i = n; i <= MAX_PARTS; ++i) a.begin[i] = static_cast<int>(tiles);
+  if (vec)
+    hipLaunchKernelGGL(k_momentum_parts<true>, dim3(static_cast<unsigned>(tiles)), dim3(NTHREADS), 0, st, a, grad, mom, beta, nesterov);
+  else
+    hipLaunchKernelGGL(k_momentum_parts<false>, dim3(static_cast<unsigned>(tiles)), dim3(NTHREADS), 0, st, a, grad, mom, beta, nesterov);
   return hipGetLastError();
 }
 

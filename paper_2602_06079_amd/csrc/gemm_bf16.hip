@@ -746,18 +746,25 @@ struct TermWalk {
 
 // Operands of a launch: one product (the usual case), or several of different shapes.
 struct OneProblem {
-  static constexpr bool multi = false;
+  static constexpr bool multi = false, finals = false;
   GemmDims d;
   const __bf16* P;
   const __bf16* Q;
 };
 template <int MAX>
 struct ManyProblemsOf {
-  static constexpr bool multi = true;
+  static constexpr bool multi = true, finals = false;
   static constexpr int max = MAX;
   int n;
   int begin[MAX + 1];  // first logical tile of each problem, then the total
   GemmProblem pr[MAX];
+};
+// Last products of several parts of a call.
+struct FinalParts {
+  static constexpr bool multi = true, finals = true;
+  int n;
+  int begin[MAX_PARTS + 1];
+  FinalPart pr[MAX_PARTS];
 };
 // Room for two problems of each shape class only where a launch holds two: every block reads the descriptor first.
 template <int EPI>
@@ -1107,13 +1114,20 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
   const int parts_m = behind ? RM : QUARTERS ? 2 : 1, parts_n = behind || SM == 256 ? RN : QUARTERS ? 2 : 1;
   const int part = logical % (parts_m * parts_n);
   logical = e.main_grid + logical / (parts_m * parts_n);
+  float neg_lr_scale = o.neg_lr_scale;
+  int out_dtype = o.out_dtype, first_out = 0;
   if constexpr (Args::multi) {
     int j = 0;
     while (j + 1 < args.n && logical >= args.begin[j + 1]) ++j;
-    const GemmProblem& pr = args.pr[j];
+    const auto& pr = args.pr[j];
     d = pr.d;
     P = static_cast<const __bf16*>(pr.p), Q = static_cast<const __bf16*>(pr.q);
-    e.c = pr.c, e.ct = pr.ct, e.sym = pr.sym, e.scale = pr.scale;
+    if constexpr (Args::finals) {
+      s = pr.s, neg_lr_scale = pr.neg_lr_scale, out_dtype = pr.out_dtype, first_out = pr.first_out;
+    } else {
+      e.c = pr.c, e.ct = pr.ct, e.sym = pr.sym;
+    }
+    e.scale = pr.scale;
     logical -= args.begin[j];
   } else {
     d = args.d, P = args.P, Q = args.Q;
@@ -1512,11 +1526,11 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
       constexpr int ESZ = F32 ? 4 : 2;
       typedef typename std::conditional<F32, f32x4_any, bf16x4_any>::type vec;
       int c_in = col < cols ? col : 0;
-      char* base = static_cast<char*>(o.out.p[PARAM ? b : b * s.tp]);
+      char* base = static_cast<char*>(o.out.p[first_out + (PARAM ? b : b * s.tp)]);
       if (!PARAM && s.tp > 1) {
         const int f = c_in / ld;
         c_in -= f * ld;
-        base = static_cast<char*>(o.out.p[b * s.tp + f]);
+        base = static_cast<char*>(o.out.p[first_out + b * s.tp + f]);
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the pointer is there, or every store below would wait for the one before
       }
 #pragma unroll
@@ -1539,7 +1553,7 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
             const f32x4 v = *reinterpret_cast<const f32x4*>(sf + (RPP * x + lane / LPR) * W + (lane % LPR) * 4);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              const float val = PARAM ? apply_update(static_cast<float>(res[x][q]), o.decay, o.neg_lr_scale, v[q]) : o.neg_lr_scale * v[q];
+              const float val = PARAM ? apply_update(static_cast<float>(res[x][q]), o.decay, neg_lr_scale, v[q]) : neg_lr_scale * v[q];
               if constexpr (F32) res[x][q] = val; else res[x][q] = static_cast<__bf16>(val);
             }
           }
@@ -1563,7 +1577,7 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
               typedef typename std::conditional<F32, float, __bf16>::type elem;
               elem* const at = reinterpret_cast<elem*>(base) + static_cast<int64_t>(row) * ld + c_in + q;
               const float v = sf[(RPP * x + lane / LPR) * W + (lane % LPR) * 4 + q];
-              *at = static_cast<elem>(PARAM ? apply_update(static_cast<float>(*at), o.decay, o.neg_lr_scale, v) : o.neg_lr_scale * v);
+              *at = static_cast<elem>(PARAM ? apply_update(static_cast<float>(*at), o.decay, neg_lr_scale, v) : neg_lr_scale * v);
             }
         }
         // the second half is staged in the same area (this wavefront's own: no barrier needed)
@@ -1575,9 +1589,9 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
     using F_ = std::integral_constant<int, CANZ_DT_F32>;
     using B_ = std::integral_constant<int, CANZ_DT_BF16>;
     if (o.out_mode == CANZ_OUT_PARAM) {
-      if (o.out_dtype == CANZ_DT_F32) run(P_{}, F_{}); else run(P_{}, B_{});
+      if (out_dtype == CANZ_DT_F32) run(P_{}, F_{}); else run(P_{}, B_{});
     } else {
-      if (o.out_dtype == CANZ_DT_F32) run(D_{}, F_{}); else run(D_{}, B_{});
+      if (out_dtype == CANZ_DT_F32) run(D_{}, F_{}); else run(D_{}, B_{});
     }
     return;
   }
@@ -1660,6 +1674,9 @@ int64_t large_share(int64_t tiles, int64_t cus, int64_t longest_k) {
   // a polynomial product (k = m, the shortest k range of the step) of less than two rounds runs faster on small
   // tiles throughout: 59.6 -> 52.4 us on 26 matrices of 1024 x 1024; the same rule costs the Gram product 7 %
   if (msquare && tiles < 2 * cus && longest_k <= SMALL_ALL_MAX_K) return 0;
+  // a last product with a short k waits for memory, which the blocks of small tiles that share a CU hide from each other, up to a
+  // few rounds (us, large -> small: 512 tiles with k 1024 99 -> 82, 832 with its left-over ones 183 -> 167, 1024 203 -> 221)
+  if (EPI == EPI_FINAL && longest_k <= 1024 && 4 * tiles <= 13 * cus) return 0;
   if (left == 0 || 2 * left > cus) return tiles;
   return tiles - left;
 }
@@ -1673,13 +1690,13 @@ template <int EPI, int SM>
 int64_t renumber(OneProblem& args) {
   return small_tiles<EPI, SM>(args.d);
 }
-template <int EPI, int SM, int MAX>
-int64_t renumber(ManyProblemsOf<MAX>& args) {
+template <int EPI, int SM, typename Args>
+int64_t renumber(Args& args) {
   int64_t tiles = 0;
   // in the numbers that the kernel compares: of 128 x 128 tiles where 64 x 64 ones are their quarters
   constexpr int per = epi_two_factors(EPI) && SM == 64 ? 4 : 1;
   for (int j = 0; j < args.n; ++j) args.begin[j] = static_cast<int>(tiles / per), tiles += small_tiles<EPI, SM>(args.pr[j].d);
-  for (int j = args.n; j <= MAX; ++j) args.begin[j] = static_cast<int>(tiles / per);
+  for (int j = args.n; j < static_cast<int>(sizeof(args.begin) / sizeof(args.begin[0])); ++j) args.begin[j] = static_cast<int>(tiles / per);
   return tiles;
 }
 template <int EPI, int SM, int NST, typename Args>
@@ -1702,13 +1719,14 @@ void launch_small(const Args& args, const EpiArgs& e, int64_t first, int64_t til
   Args numbered = args;
   const int64_t n128 = first > 0 ? 4 * (tiles - first) : renumber<EPI, 128>(numbered);
   const int64_t n64 = first > 0 ? 16 * (tiles - first) : renumber<EPI, 64>(numbered);
-  const bool wide = epi_256x128(EPI) && 2 * (tiles - first) <= cus && longest_k >= 2048;
+  constexpr bool can_be_wide = epi_256x128(EPI) && !Args::finals;
+  const bool wide = can_be_wide && 2 * (tiles - first) <= cus && longest_k >= 2048;
   if (n64 <= 2 * cus)
     launch_small_as<EPI, 64, 8>(args, e, first, tiles, s, o, st);
   else if (n128 <= cus && longest_k >= 1024)
     launch_small_as<EPI, 128, 8>(args, e, first, tiles, s, o, st);
   else if (wide)
-    launch_small_as<EPI, epi_256x128(EPI) ? 256 : 128, epi_256x128(EPI) ? 6 : 3>(args, e, first, tiles, s, o, st);
+    launch_small_as<EPI, can_be_wide ? 256 : 128, can_be_wide ? 6 : 3>(args, e, first, tiles, s, o, st);
   else
     launch_small_as<EPI, 128, 3>(args, e, first, tiles, s, o, st);
 }
@@ -1858,6 +1876,30 @@ hipError_t launch_final_bf16(const GemmDims& d, const void* p, const void* q, co
   EpiArgs e{};
   e.scale = scale;
   return launch<EPI_FINAL>(d, p, q, e, w, s, o, st);
+}
+
+// Small tiles throughout: up to two rounds of 256 x 256 ones, and no k that the large tile is for.  Seven matrices of four shape classes
+// (208 tiles, k 1024): four launches 73 us, one 50.
+bool final_parts_fit(int n, const FinalPart* parts) {
+  int64_t tiles = 0, longest_k = 0;
+  for (int i = 0; i < n; ++i) tiles += tile_count<EPI_FINAL>(parts[i].d), longest_k = std::max(longest_k, parts[i].d.K);
+  return n <= MAX_PARTS && tiles <= 2 * cu_count() && longest_k <= 2048;
+}
+hipError_t launch_final_parts_bf16(int n, const FinalPart* parts, const OutSpec& o, hipStream_t st) {
+  if (n < 1 || n > MAX_PARTS) return hipErrorInvalidValue;
+  FinalParts many{};
+  many.n = n;
+  int64_t tiles = 0, longest_k = 0;
+  for (int i = 0; i < n; ++i) {
+    const GemmDims& d = parts[i].d;
+    if (d.K < 8 * BK || d.K % (8 * BK) || d.M % BM || d.N % BN) return hipErrorInvalidValue;
+    many.pr[i] = parts[i];
+    tiles += tile_count<EPI_FINAL>(d), longest_k = std::max(longest_k, d.K);
+  }
+  EpiArgs e{};
+  e.splits = 1;
+  launch_small<EPI_FINAL>(many, e, 0, tiles, longest_k, cu_count(), Shape{}, o, st);
+  return hipGetLastError();
 }
 
 hipError_t launch_final_sym_bf16(const GemmDims& d, const void* x, const SplitWs& w, const Shape& s, const OutSpec& o,

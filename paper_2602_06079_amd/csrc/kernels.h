@@ -61,9 +61,30 @@ hipError_t launch_momentum(const Shape& s, int nb, const PtrTable& grad, int gra
                            float* partial, hipStream_t st);
 int momentum_tiles(const Shape& s);  // partial sums per matrix
 
+// The same for several parts of one call (matrices of one shape and orientation each) in one launch: the buffers of part i are
+// number first_grad (first_mom) and on of the tables.
+constexpr int MAX_PARTS = 8;   // two orientations of MAX_KINDS shape classes
+template <typename T>
+struct MomentumPart {
+  Shape s;
+  int nb, grad_dtype, first_grad, first_mom;
+  T *xw, *xt;
+  float* partial;
+};
+hipError_t launch_momentum_parts(int n, const MomentumPart<__bf16>* parts, const PtrTable& grad, const PtrTable& mom, float beta,
+                                 int nesterov, hipStream_t st);
+
 // scale[b] = 1 / (sqrt(sum partial[b][*]) + eps), scale2[b] = scale[b]^2
 hipError_t launch_norm_scale(int nb, int n_partial, const float* partial, float eps, float* scale,
                              float* scale2, hipStream_t st);
+// the same for up to MAX_KINDS batches in one launch
+constexpr int MAX_KINDS = 4;                  // shape classes that run side by side
+struct NormBatch {
+  int nb, n_partial;
+  const float* partial;
+  float *scale, *scale2;
+};
+hipError_t launch_norm_scale_batches(int n, const NormBatch* batches, float eps, hipStream_t st);
 
 struct OutSpec {
   PtrTable out;
@@ -119,7 +140,6 @@ struct SymSpec {
 };
 // Several products of one kind in one launch: matrices of different shapes, or independent products of one chain.
 // The persistent blocks walk the tiles of problem 0, then of problem 1, ...
-constexpr int MAX_KINDS = 4;                  // shape classes that run side by side
 constexpr int MAX_PROBLEMS = 2 * MAX_KINDS;   // two independent products of each
 struct GemmProblem {
   GemmDims d;
@@ -153,6 +173,19 @@ hipError_t launch_update_bf16(const GemmDims& d, const void* b_in, const void* x
 // wide matrix: P = B, Q = XT (C = B X);  tall matrix: P = XT, Q = B (C = X^T B = (B X)^T)
 hipError_t launch_final_bf16(const GemmDims& d, const void* p, const void* q, const float* scale, const SplitWs& w,
                              const Shape& s, const OutSpec& o, hipStream_t st);
+// several of them in one launch, on small tiles: part i writes the buffers number first_out and on of o.out with its own type and factor
+// (out_mode and decay are those of o)
+struct FinalPart {
+  GemmDims d;
+  const void *p, *q;
+  const float* scale;
+  Shape s;
+  int out_dtype, first_out;
+  float neg_lr_scale;
+};
+// whether that is the faster way: launches that leave most of the chip idle or end in a round that does
+bool final_parts_fit(int n, const FinalPart* parts);
+hipError_t launch_final_parts_bf16(int n, const FinalPart* parts, const OutSpec& o, hipStream_t st);
 // the same for a symmetric result O = X X^T (M = N): only the tiles on and above the diagonal are computed and
 // written; the elements below the diagonal tiles are left as they were (the caller mirrors them)
 hipError_t launch_final_sym_bf16(const GemmDims& d, const void* x, const SplitWs& w, const Shape& s, const OutSpec& o,

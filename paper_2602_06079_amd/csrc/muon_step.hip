@@ -377,7 +377,20 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
   }
   const SplitWs split{reinterpret_cast<float*>(ws + base), SPLIT_MAX_BLOCKS};
 
-  // momentum (+ gather, cast, both orientations, tile sums of U^2) per part, norm per batch
+  // momentum (+ gather, cast, both orientations, tile sums of U^2) per part, norm per batch; several parts whose buffers fit one
+  // table go in one launch each (four classes of a 0.6B-shaped layer: 55 -> 33 us and 12 -> 4)
+  int n_parts = 0, n_grads = 0, n_outs = 0;
+  for (int k = 0; k < nk; ++k)
+    for (const Part& part : batches[lo + k].part)
+      if (part.n() > 0) ++n_parts, n_grads += static_cast<int>(part.grad.size()), n_outs += static_cast<int>(part.out.size());
+  const bool shared = is_bf16 && n_parts > 1 && n_parts <= MAX_PARTS && n_grads <= MAX_PTRS && n_outs <= MAX_PTRS;
+  PtrTable all_grad{}, all_mom{};
+  OutSpec all_out{};
+  MomentumPart<__bf16> mparts[MAX_PARTS];
+  FinalPart fparts[MAX_PARTS];
+  int first_out[MAX_KINDS][2] = {};
+  n_parts = n_grads = n_outs = 0;
+  int n_moms = 0;
   for (int k = 0; k < nk; ++k) {
     const Batch& bt = batches[lo + k];
     Kind& kd = kind[k];
@@ -399,13 +412,30 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
       o.decay = static_cast<float>(1.0 - static_cast<double>(hp.lr) * static_cast<double>(hp.weight_decay));
       o.neg_lr_scale = static_cast<float>(-static_cast<double>(hp.lr) * update_scale(g, hp.scale_mode));
       const int f = kd.first[h];
+      if constexpr (is_bf16) if (shared) {
+        mparts[n_parts++] = MomentumPart<__bf16>{kd.shape[h], n, g.grad_dtype, n_grads, n_moms, kd.xw + f * kd.x_elems,
+                                                 kd.xt[0] + f * kd.x_elems, kd.partial + static_cast<int64_t>(f) * kd.tiles};
+        first_out[k][h] = n_outs;
+        for (int i = 0; i < n * g.tp; ++i) all_grad.p[n_grads++] = grad.p[i];
+        for (int i = 0; i < n; ++i) all_mom.p[n_moms++] = mom.p[i];
+        for (int i = 0; i < n_out; ++i) all_out.out.p[n_outs++] = o.out.p[i];
+        all_out.out_mode = o.out_mode, all_out.decay = o.decay;
+        continue;
+      }
       CANZ_HIP(CANZ_KERNEL_MOMENTUM,
                launch_momentum<T>(kd.shape[h], n, grad, g.grad_dtype, mom, hp.beta, hp.nesterov, kd.xw + f * kd.x_elems,
                                   kd.xt[0] + f * kd.x_elems, kd.partial + static_cast<int64_t>(f) * kd.tiles, st),
                "momentum kernel");
     }
-    CANZ_HIP(CANZ_KERNEL_NORM, launch_norm_scale(kd.nb, kd.tiles, kd.partial, hp.eps, kd.scale, kd.scale2, st),
-             "norm kernel");
+    if (!shared)
+      CANZ_HIP(CANZ_KERNEL_NORM, launch_norm_scale(kd.nb, kd.tiles, kd.partial, hp.eps, kd.scale, kd.scale2, st),
+               "norm kernel");
+  }
+  if (shared) {
+    NormBatch nb[MAX_KINDS];
+    for (int k = 0; k < nk; ++k) nb[k] = NormBatch{kind[k].nb, kind[k].tiles, kind[k].partial, kind[k].scale, kind[k].scale2};
+    CANZ_HIP(CANZ_KERNEL_MOMENTUM, launch_momentum_parts(n_parts, mparts, all_grad, all_mom, hp.beta, hp.nesterov, st), "momentum kernel");
+    CANZ_HIP(CANZ_KERNEL_NORM, launch_norm_scale_batches(nk, nb, hp.eps, st), "norm kernel");
   }
 
   if (hp.ns_steps == 0) {
@@ -515,6 +545,7 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
         CANZ_HIP(CANZ_KERNEL_UPDATE, launch_update_bf16(gb, split, st), "update kernel");
       }
     }
+    n_parts = 0;
     for (int k = 0; k < nk; ++k) {
       const Kind& kd = kind[k];
       const float* sc1 = first_it ? kd.scale : nullptr;
@@ -547,10 +578,23 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
           (tall ? fin.ldq : fin.ldp) = 2 * s.mp, (tall ? fin.sq : fin.sp) = 2 * kd.a_elems;
           fin.nseg = 2, (tall ? fin.qseg : fin.pseg) = 0x01u;
           CANZ_HIP(CANZ_KERNEL_FINAL, launch_terms_final(fin, P, Q, kd.shape[h], kd.out[h], st), "final kernel");
-        } else if (is_bf16)
+        } else if (is_bf16 && shared)   // below, all parts together if that pays
+          fparts[n_parts++] = FinalPart{fin, P, Q, sk, kd.shape[h], kd.out[h].out_dtype, first_out[k][h], kd.out[h].neg_lr_scale};
+        else if (is_bf16)
           CANZ_HIP(CANZ_KERNEL_FINAL, launch_final_bf16(fin, P, Q, sk, split, kd.shape[h], kd.out[h], st), "final kernel");
         else
           CANZ_HIP(CANZ_KERNEL_FINAL, launch_final_f32(fin, P, Q, sk, kd.shape[h], kd.out[h], st), "final kernel");
+      }
+    }
+    if (n_parts > 0 && final_parts_fit(n_parts, fparts)) {
+      CANZ_HIP(CANZ_KERNEL_FINAL, launch_final_parts_bf16(n_parts, fparts, all_out, st), "final kernel");
+    } else {
+      for (int i = 0; i < n_parts; ++i) {
+        const FinalPart& f = fparts[i];
+        OutSpec o = all_out;
+        o.out_dtype = f.out_dtype, o.neg_lr_scale = f.neg_lr_scale;
+        std::copy(all_out.out.p + f.first_out, all_out.out.p + MAX_PTRS, o.out.p);
+        CANZ_HIP(CANZ_KERNEL_FINAL, launch_final_bf16(f.d, f.p, f.q, f.scale, split, f.s, o, st), "final kernel");
       }
     }
     cur ^= 1;
