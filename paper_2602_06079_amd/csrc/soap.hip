@@ -399,15 +399,51 @@ constexpr int VMAX = 12288;   // rows of a reflector kept in LDS: the largest ex
 
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// tau and the scale of v for a column with diagonal element al and sum of squares ss below it
+// tau and the scale of v for a column with diagonal element al and sum of squares ss below it.  The root and the quotients are on the
+// chain of every column: from the chip's estimates with a step of Newton's method each (and the quotient's remainder), which leaves what rounding
+// leaves, in a third of the time of the library's, except where the squares are close to the smallest numbers there are.
+__device__ __forceinline__ float refined_rcp(float x, float r) { return __builtin_fmaf(__builtin_fmaf(-x, r, 1.f), r, r); }
 __device__ __forceinline__ void reflector_of(bool live, float ss, float al, float& tau, float& scale) {
   tau = 0.f, scale = 0.f;
   if (live && ss > 0.f) {
-    const float nrm = sqrtf(__builtin_fmaf(al, al, ss));
-    const float beta = al >= 0.f ? -nrm : nrm;
-    tau = (beta - al) / beta;
-    scale = 1.f / (al - beta);
+    const float x2 = __builtin_fmaf(al, al, ss);
+    if (x2 > 1e-30f) {
+      const float y = __builtin_amdgcn_rsqf(x2);
+      float nrm = x2 * y;
+      nrm = __builtin_fmaf(__builtin_fmaf(-nrm, nrm, x2), 0.5f * y, nrm);
+      const float inv = refined_rcp(nrm, y);
+      const float sum = nrm + fabsf(al);   // |al - beta|, beta = -sign(al) nrm
+      const float q = sum * inv;
+      tau = __builtin_fmaf(__builtin_fmaf(-nrm, q, sum), inv, q);
+      const float r = refined_rcp(sum, __builtin_amdgcn_rcpf(sum));
+      scale = al >= 0.f ? r : -r;
+    } else {
+      const float nrm = sqrtf(x2);
+      const float beta = al >= 0.f ? -nrm : nrm;
+      tau = (beta - al) / beta;
+      scale = 1.f / (al - beta);
+    }
   }
+}
+// the element at row c < 32 of a column whose lane l holds rows 4 l .. 4 l + 3 in k
+__device__ __forceinline__ float element_of(const f32x4& k, int c) {
+  const float v = (c & 2) ? ((c & 1) ? k[3] : k[2]) : ((c & 1) ? k[1] : k[0]);
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), c >> 2));
+}
+// sum of squares of a lane's elements below row c; the rows up to c < 32 lie in the first slot
+template <int XS>
+__device__ __forceinline__ float squares_below(const f32x4 (&k)[XS], int lane, int c) {
+  float ss = 0.f;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float x = 4 * lane + e > c ? k[0][e] : 0.f;
+    ss = __builtin_fmaf(x, x, ss);
+  }
+#pragma unroll
+  for (int sl = 1; sl < XS; ++sl)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ss = __builtin_fmaf(k[sl][e], k[sl][e], ss);
+  return ss;
 }
 // elements 4 q .. 4 q + 3 of v_c from those of the column
 __device__ __forceinline__ f32x4 v_of(const f32x4& x, int q, int c, float scale) {
@@ -439,39 +475,35 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
-// Columns ka and / or kb (registers) <- H_c applied to them, v_c in LDS.
+// Columns ka and / or kb (registers) <- H_c applied to them, v_c in LDS.  v_c stays in registers between the dot products and the updates
+// where there is room beside the columns.
 template <int XS, bool DO_A, bool DO_B>
-__device__ __forceinline__ void apply_reflector(f32x4 (&ka)[XS], f32x4 (&kb)[XS], const f32x4* s_v4, int nvec, int lane,
-                                                float tau) {
-  constexpr bool HOLD_V = XS <= 8;
+__device__ __forceinline__ void apply_reflector(f32x4 (&ka)[XS], f32x4 (&kb)[XS], const f32x4* s_v4, int lane, float tau) {
+  constexpr bool HOLD_V = XS <= 4;
   f32x4 v[HOLD_V ? XS : 1];
   float da = 0.f, db = 0.f;
 #pragma unroll
   for (int sl = 0; sl < XS; ++sl) {
-    const int q = lane + 64 * sl;
-    if (q < nvec) {
-      const f32x4 y = s_v4[q];
-      if (HOLD_V) v[sl] = y;
+    const f32x4 y = s_v4[lane + 64 * sl];
+    if (HOLD_V) v[sl] = y;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (DO_A) da = __builtin_fmaf(ka[sl][e], y[e], da);
-        if (DO_B) db = __builtin_fmaf(kb[sl][e], y[e], db);
-      }
+    for (int e = 0; e < 4; ++e) {
+      if (DO_A) da = __builtin_fmaf(ka[sl][e], y[e], da);
+      if (DO_B) db = __builtin_fmaf(kb[sl][e], y[e], db);
     }
+    if (!HOLD_V && (sl & 3) == 3) __builtin_amdgcn_sched_barrier(0);   // few reads of v at a time: more would be spilled
   }
   const float fa = DO_A ? tau * wave_sum_dpp(da) : 0.f;
   const float fb = DO_B ? tau * wave_sum_dpp(db) : 0.f;
 #pragma unroll
   for (int sl = 0; sl < XS; ++sl) {
-    const int q = lane + 64 * sl;
-    if (q < nvec) {
-      const f32x4 y = HOLD_V ? v[sl] : s_v4[q];
+    const f32x4 y = HOLD_V ? v[sl] : s_v4[lane + 64 * sl];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (DO_A) ka[sl][e] = __builtin_fmaf(-fa, y[e], ka[sl][e]);
-        if (DO_B) kb[sl][e] = __builtin_fmaf(-fb, y[e], kb[sl][e]);
-      }
+    for (int e = 0; e < 4; ++e) {
+      if (DO_A) ka[sl][e] = __builtin_fmaf(-fa, y[e], ka[sl][e]);
+      if (DO_B) kb[sl][e] = __builtin_fmaf(-fb, y[e], kb[sl][e]);
     }
+    if (!HOLD_V && (sl & 3) == 3) __builtin_amdgcn_sched_barrier(0);
   }
 }
 
@@ -479,15 +511,16 @@ __device__ __forceinline__ void apply_reflector(f32x4 (&ka)[XS], f32x4 (&kb)[XS]
 // writes that column, so the columns need no synchronisation between wavefronts.  What the others
 // need of step c is the reflector v_c, which its owner leaves in LDS together with tau_c.  Two copies of v in turn: while all
 // apply H_c to their later columns, the owner of column c + 1 does that one first, turns it into v_(c+1) and leaves that in the other
-// copy; one barrier per step, and the chain of a step is that one column.  With v in LDS the
-// barriers only have to order LDS traffic, so they do not wait for the stores in flight.
+// copy; one barrier per step, and the chain of a step is that one column, whose wavefront goes before the three others of its SIMD
+// meanwhile.  With v in LDS the barriers only have to order LDS traffic, so they do not wait for the stores in flight.
 // Columns at or beyond d (padding) and columns that are already zero below the diagonal get tau = 0 (H = I).
-// Bound by that chain (LDS round trips, two wave sums, a root and two divisions, about 0.4 us a column).
+// Bound by that chain (LDS round trips, two wave sums, a root and two quotients): us a panel of 512, 1024, 2048 rows 27, 36, 58 with two
+// divisions and a root of the library and every wavefront alike, 20, 25, 41 now.  Fewer wavefronts of more columns are slower (8 of 4 columns:
+// 27, 35, 53): a wavefront on its own does not fill its SIMD.
 //
 // At most 256 XS remaining rows (XS = 2 .. 12: 512 .. 3072): every
 // wavefront loads its two columns (wave + 1 and wave + 17) into registers once and keeps them there.  The
 // columns are never written back: what the factorisation leaves in them is R, which nothing uses.
-// Up to XS = 8 there is room to hold v_c in registers between the dot products and the updates.
 template <int XS>
 __global__ __launch_bounds__(QTH) void k_qr_panel_regs(QrArgs args) {
   __shared__ f32x4 s_v4[2][64 * XS];
@@ -503,39 +536,29 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_regs(QrArgs args) {
   auto load_col = [&](f32x4 (&k)[XS], int c) {
     const f32x4* x = reinterpret_cast<const f32x4*>(a.wk + static_cast<int64_t>(j0 + c) * dp + j0);
 #pragma unroll
-    for (int sl = 0; sl < XS; ++sl) {
+    for (int sl = 0; sl < XS; ++sl) {   // zero beyond the column: stays zero, and so do the reflectors in LDS
       const int q = lane + 64 * sl;
-      if (q < nvec) k[sl] = x[q];
+      k[sl] = q < nvec ? x[q] : f32x4{0.f, 0.f, 0.f, 0.f};
     }
   };
   // column c (in k) becomes the reflector v_c: to LDS, to the reflector array, tau to LDS
   auto make_v = [&](const f32x4 (&k)[XS], int c) {
-    float ss = 0.f, al = 0.f;   // sum of squares below row c and the element at row c, over the wavefront
-#pragma unroll
-    for (int sl = 0; sl < XS; ++sl) {
-      const int q = lane + 64 * sl;
-      if (q < nvec) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = 4 * q + e;
-          if (r > c) ss += k[sl][e] * k[sl][e];
-          if (r == c) al = k[sl][e];
-        }
-      }
-    }
-    ss = wave_sum_dpp(ss), al = wave_sum_dpp(al);
+    const float al = element_of(k[0], c), ss = wave_sum_dpp(squares_below(k, lane, c));
     float tau, scale;
     reflector_of(j0 + c < a.d, ss, al, tau, scale);
     f32x4* vg = reinterpret_cast<f32x4*>(a.vall + static_cast<int64_t>(j0 + c) * dp + j0);
     if (lane == 0) s_tau[c] = tau;
 #pragma unroll
     for (int sl = 0; sl < XS; ++sl) {
-      const int q = lane + 64 * sl;
-      if (q < nvec) {
-        const f32x4 o = v_of(k[sl], q, c, scale);
-        s_v4[c & 1][q] = o;
-        vg[q] = o;
-      }
+      f32x4 o;
+      if (sl == 0)
+        o = v_of(k[0], lane, c, scale);
+      else
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = k[sl][e] * scale;
+      s_v4[c & 1][lane + 64 * sl] = o;
+      if (lane + 64 * sl < nvec) vg[lane + 64 * sl] = o;
+      if (XS > 8) __builtin_amdgcn_sched_barrier(0);   // one at a time: the columns leave few registers
     }
   };
 
@@ -557,20 +580,24 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_regs(QrArgs args) {
     const f32x4* v = s_v4[c & 1];
     const bool live = tau != 0.f;
     if (c + 1 == ca) {
-      if (live) apply_reflector<XS, true, false>(ka, kb, v, nvec, lane, tau);
+      __builtin_amdgcn_s_setprio(3);
+      if (live) apply_reflector<XS, true, false>(ka, kb, v, lane, tau);
       make_v(ka, c + 1);
-      if (live && cb < QB) apply_reflector<XS, false, true>(ka, kb, v, nvec, lane, tau);
+      __builtin_amdgcn_s_setprio(0);
+      if (live && cb < QB) apply_reflector<XS, false, true>(ka, kb, v, lane, tau);
     } else if (c + 1 == cb) {
-      if (live) apply_reflector<XS, false, true>(ka, kb, v, nvec, lane, tau);
+      __builtin_amdgcn_s_setprio(3);
+      if (live) apply_reflector<XS, false, true>(ka, kb, v, lane, tau);
       make_v(kb, c + 1);
+      __builtin_amdgcn_s_setprio(0);
     } else if (live) {   // columns that have become reflectors are left alone
       const bool do_a = ca > c, do_b = cb < QB && cb > c;
       if (do_a && do_b)
-        apply_reflector<XS, true, true>(ka, kb, v, nvec, lane, tau);
+        apply_reflector<XS, true, true>(ka, kb, v, lane, tau);
       else if (do_b)
-        apply_reflector<XS, false, true>(ka, kb, v, nvec, lane, tau);
+        apply_reflector<XS, false, true>(ka, kb, v, lane, tau);
       else if (do_a)
-        apply_reflector<XS, true, false>(ka, kb, v, nvec, lane, tau);
+        apply_reflector<XS, true, false>(ka, kb, v, lane, tau);
     }
   }
   lds_barrier();
@@ -603,16 +630,8 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrArgs args) {
   };
   // column c becomes the reflector v_c: to LDS, to the reflector array, tau to LDS
   auto make_v = [&](const f32x4 (&k)[XS], int c) {
-    float ss = 0.f, al = 0.f;   // sum of squares below row c and the element at row c (c < 32: it lies in the registers)
-#pragma unroll
-    for (int sl = 0; sl < XS; ++sl) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = 4 * (lane + 64 * sl) + e;
-        if (r > c) ss += k[sl][e] * k[sl][e];
-        if (r == c) al = k[sl][e];
-      }
-    }
+    const float al = element_of(k[0], c);   // c < 32: it lies in the registers
+    float ss = squares_below(k, lane, c);
     const f32x4* x = col(c);
     for (int q0 = NR + lane; q0 < nvec; q0 += 64 * TU) {
       f32x4 xv[TU];
@@ -624,7 +643,7 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrArgs args) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) ss += xv[u][e] * xv[u][e];
     }
-    ss = wave_sum_dpp(ss), al = wave_sum_dpp(al);
+    ss = wave_sum_dpp(ss);
     float tau, scale;
     reflector_of(j0 + c < a.d, ss, al, tau, scale);
     if (lane == 0) s_tau[c] = tau;
@@ -633,7 +652,12 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrArgs args) {
 #pragma unroll
     for (int sl = 0; sl < XS; ++sl) {
       const int q = lane + 64 * sl;
-      const f32x4 o = v_of(k[sl], q, c, scale);
+      f32x4 o;
+      if (sl == 0)
+        o = v_of(k[0], q, c, scale);
+      else
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = k[sl][e] * scale;
       sv[q] = o;
       vg[q] = o;
     }
@@ -710,11 +734,15 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrArgs args) {
     const f32x4* v = s_v4[c & 1];
     const bool live = tau != 0.f;
     if (c + 1 == cb) {
+      __builtin_amdgcn_s_setprio(3);
       if (live) apply(kb, cb, v, tau);
       make_v(kb, cb);
+      __builtin_amdgcn_s_setprio(0);
     } else {
+      if (c + 1 == ca) __builtin_amdgcn_s_setprio(3);
       if (live && ca > c) apply(ka, ca, v, tau);
       if (c + 1 == ca) make_v(ka, ca);
+      __builtin_amdgcn_s_setprio(0);
       if (live && cb < QB && cb > c) apply(kb, cb, v, tau);
     }
   }
@@ -858,23 +886,25 @@ __global__ __launch_bounds__(NTH) void k_qr_panel_sub(QrArgs args) {
 // blocks on the diagonal row by row, T[i][c] = tau_c ((i == c) - sum_{i <= l < c} T[i][l] v_l^T v_c), then those at distance 1, 2, 3,
 // T_ab = -(sum_{a <= c < b} T_ac G_cb) T_bb.  T goes where V^T V was, T^T to `tt`.  One workgroup per matrix.
 __global__ __launch_bounds__(QTH) void k_qr_block_t(QrArgs args) {
-  __shared__ float s_g[QBLK][QBLK + 1], s_t[QBLK][QBLK + 1];
+  constexpr int GTLD = QBLK + 4;
+  __shared__ __attribute__((aligned(16))) float s_gt[QBLK][GTLD];   // s_gt[c][l] = v_l^T v_c
+  __shared__ float s_t[QBLK][QBLK + 1];
   __shared__ float s_x[3][QB][QB + 1];
   __shared__ float s_tau[QBLK];
   const QrMatrix a = qr_matrix(args, blockIdx.x);
   int chunks, len;
   qr_chunks(a.dp, args.jb, chunks, len);
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   if (t < QBLK) s_tau[t] = a.tau[t];
   {   // the last panel's column of blocks is still in pieces
     const int i = t >> 3, c4 = (t & 7) * 4;
     const f32x4 v = sum_pieces(a.strip + i * QB + c4, chunks);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) s_g[i][3 * QB + c4 + c] = v[c];
+    for (int c = 0; c < 4; ++c) s_gt[3 * QB + c4 + c][i] = v[c];
   }
   for (int e = t; e < QBLK * QBLK; e += QTH) {
     const int r = e >> 7, q = e & 127;
-    if (q < 3 * QB) s_g[r][q] = (r >> 5) <= (q >> 5) ? a.gram[e] : 0.f;
+    if (q < 3 * QB) s_gt[q][r] = (r >> 5) <= (q >> 5) ? a.gram[e] : 0.f;
     s_t[r][q] = 0.f;
   }
   __syncthreads();
@@ -885,28 +915,37 @@ __global__ __launch_bounds__(QTH) void k_qr_block_t(QrArgs args) {
     for (int c = 0; c < QB; ++c) {
       float part[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int l = 0; l < c; ++l) part[l & 3] = __builtin_fmaf(row[l], s_g[base + l][base + c], part[l & 3]);
+      for (int l4 = 0; l4 < c; l4 += 4) {
+        const f32x4 g = *reinterpret_cast<const f32x4*>(&s_gt[base + c][base + l4]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (l4 + e < c) part[e] = __builtin_fmaf(row[l4 + e], g[e], part[e]);
+      }
       const float tau = s_tau[base + c], sum = (part[0] + part[1]) + (part[2] + part[3]);
       row[c] = i == c ? tau : (i < c && tau != 0.f ? -tau * sum : 0.f);   // left of the diagonal the row is zero, and so is the sum
       s_t[t][base + c] = row[c];
     }
   }
   __syncthreads();
-  const int i = t >> 5, j = t & 31;
+  // a wavefront per block at distance k, on the matrix cores
+  const int lj = lane & 31, lh = lane >> 5;
   for (int k = 1; k < 4; ++k) {
-    for (int lo = 0; lo + k < 4; ++lo) {
-      float part[4] = {0.f, 0.f, 0.f, 0.f};
-      for (int c = lo; c < lo + k; ++c)
+    if (wave + k < 4) {
+      const int lo = wave, hi = wave + k;
+      f32x16 acc;
 #pragma unroll
-        for (int l = 0; l < QB; ++l) part[l & 3] = __builtin_fmaf(s_t[lo * QB + i][c * QB + l], s_g[c * QB + l][(lo + k) * QB + j], part[l & 3]);
-      s_x[lo][i][j] = (part[0] + part[1]) + (part[2] + part[3]);
-    }
-    __syncthreads();
-    for (int lo = 0; lo + k < 4; ++lo) {
-      float part[4] = {0.f, 0.f, 0.f, 0.f};
+      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+      for (int c = lo; c < hi; ++c)
 #pragma unroll
-      for (int l = 0; l < QB; ++l) part[l & 3] = __builtin_fmaf(s_x[lo][i][l], s_t[(lo + k) * QB + l][(lo + k) * QB + j], part[l & 3]);
-      s_t[lo * QB + i][(lo + k) * QB + j] = -((part[0] + part[1]) + (part[2] + part[3]));
+        for (int kk = 0; kk < QB; kk += 2)
+          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(s_t[lo * QB + lj][c * QB + kk + lh], s_gt[hi * QB + lj][c * QB + kk + lh], acc, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s_x[lo][8 * (r >> 2) + (r & 3) + 4 * lh][lj] = acc[r], acc[r] = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < QB; kk += 2)
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(s_x[lo][lj][kk + lh], s_t[hi * QB + kk + lh][hi * QB + lj], acc, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s_t[lo * QB + 8 * (r >> 2) + (r & 3) + 4 * lh][hi * QB + lj] = -acc[r];
     }
     __syncthreads();
   }
@@ -1163,7 +1202,9 @@ int check_group(const canz_soap_group& g, int idx, bool need_ptrs, const canz_so
 
 // Basis refresh of the sides of a batch (one or two, the longer first): q (caller's, d x d) <- Q factor of QR(S q), S the padded
 // statistic in `qt` [nb][dp][dp] (later Q^T), the transposed padded copy of the current basis in `vall` (later the reflectors).
-int refresh(const QrSide* side, int n_sides, void* const* const* q_tab, int first, int nb, const Shape& s, const OutSpec& o, hipStream_t st) {
+// `product`: S q is in `wk` already.
+int refresh(const QrSide* side, int n_sides, bool product, void* const* const* q_tab, int first, int nb, const Shape& s, const OutSpec& o,
+            hipStream_t st) {
   const PtrTable none{};
   QrArgs a{};
   a.nb = nb;
@@ -1192,7 +1233,7 @@ int refresh(const QrSide* side, int n_sides, void* const* const* q_tab, int firs
   using Sub = std::integral_constant<int, SE_SUB>;
 
   // working copy, transposed: wk[c][r] = (S q)[r][c] = sum_k qt_old[c][k] S[r][k]
-  if (int rc = products(Plain{}, std::false_type{}, n_sides, [&](int i) {
+  if (int rc = product ? CANZ_OK : products(Plain{}, std::false_type{}, n_sides, [&](int i) {
         ShGemm g{};
         g.M = g.N = g.K = g.ldp = g.ldq = g.ldc = side[i].dp, g.sp = g.sq = g.sc = dd(i);
         g.P = side[i].vall, g.Q = side[i].qt, g.c = side[i].wk;
@@ -1543,7 +1584,7 @@ int run_batch(const canz_soap_group& g, int first, int nb, Rot rot, const canz_s
   int n_sides = 0;
   float* pool = ws + c.pool;
   auto one_side = [&](void* const* stat_tab, void* const* q_tab, int64_t d, int64_t dp, int64_t kp, const float* grad32, const __bf16* grad16,
-                      int64_t d2, int64_t k2, size_t stat_at) -> int {
+                      int64_t d2, int64_t k2, size_t stat_at, size_t basis_t3) -> int {
     PtrTable tab{};
     for (int i = 0; i < nb; ++i) tab.p[i] = stat_tab[first + i];
     QrSide qs{};
@@ -1559,7 +1600,7 @@ int run_batch(const canz_soap_group& g, int first, int nb, Rot rot, const canz_s
       Shape sq{};   // the caller's dense d x d matrix
       sq.rows = d, sq.cols = d, sq.m = d, sq.n = d, sq.tp = 1, sq.wfrag = d;
       if (int rc = statistic_bf16(CANZ_KERNEL_SOAP_STAT, tab, d, d2, k2, k2, nb, hp.beta2, 1.f - hp.beta2, grad16, st)) return rc;
-      if (hp.refresh) {   // (the transposed image lands in wk, unused)
+      if (hp.refresh && !terms3) {   // (the transposed image lands in wk, unused)
         prof_mark(st, CANZ_KERNEL_SOAP_STAT, true);
         hipLaunchKernelGGL(k_sh_load, dim3(static_cast<unsigned>(dp / 64), static_cast<unsigned>(dp / 64), static_cast<unsigned>(nb)),
                            dim3(NTH), 0, st, sq, tab, static_cast<int>(CANZ_DT_F32), dp, dp, qs.qt, qs.wk);
@@ -1569,14 +1610,29 @@ int run_batch(const canz_soap_group& g, int first, int nb, Rot rot, const canz_s
     } else {
       ShGemm q{};
       q.M = dp, q.N = dp, q.K = kp, q.ldp = kp, q.ldq = kp, q.sp = g_stride, q.sq = g_stride;
-      q.P = grad32, q.Q = grad32, q.c = qs.qt, q.d = d, q.beta = hp.beta2, q.gscale = 1.f - hp.beta2, q.eps = 0.f;
+      q.P = grad32, q.Q = grad32, q.c = terms3 ? nullptr : qs.qt, q.d = d, q.beta = hp.beta2, q.gscale = 1.f - hp.beta2, q.eps = 0.f;
       CANZ_HIP(CANZ_KERNEL_SOAP_STAT, (launch_gemm<SE_STAT, true>(q, nb, tab, s, o, st)), "statistics kernel");
     }
     if (!hp.refresh) return CANZ_OK;
     prof_mark(st, CANZ_KERNEL_SOAP_LOAD, true);
-    load_basis(q_tab, d, dp, dp, BasisOut{nullptr, qs.vall, nullptr, nullptr, nullptr, nullptr});
+    if (terms3)
+      hipLaunchKernelGGL(k_terms3, dim3(static_cast<unsigned>(d2 / 64), static_cast<unsigned>(d2 / 64), static_cast<unsigned>(nb)), dim3(NTH), 0, st,
+                         tab, d, d, d2, reinterpret_cast<__bf16*>(qs.qt));
+    else
+      load_basis(q_tab, d, dp, dp, BasisOut{nullptr, qs.vall, nullptr, nullptr, nullptr, nullptr});
     prof_mark(st, CANZ_KERNEL_SOAP_LOAD, false);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail(CANZ_EHIP, "basis load: %s", hipGetErrorString(e));
+    if (terms3) {
+      // S q, transposed, on three terms as the rotations (4 x 2048^2 and 1024^2: 708 us on the fp32 cores, 440 so): the transposed old
+      // basis is there from the rotation into it, the statistic takes the place of the straight one
+      Shape sq{};
+      sq.rows = sq.cols = sq.m = sq.n = dp, sq.mp = sq.np = d2, sq.tp = 1, sq.wfrag = dp;
+      OutSpec wo{};
+      for (int i = 0; i < nb; ++i) wo.out.p[i] = qs.wk + i * dp * dp;
+      wo.out_dtype = CANZ_DT_F32, wo.out_mode = CANZ_OUT_DELTA, wo.decay = 1.f, wo.neg_lr_scale = 1.f;
+      CANZ_HIP(CANZ_KERNEL_SOAP_QR, launch_terms_final(split3_dims(d2, d2, d2, 3, nb), pan(basis_t3), reinterpret_cast<const __bf16*>(qs.qt), sq, wo, st),
+               "refresh product");
+    }
     const int at = n_sides == 1 && qs.dp > side[0].dp ? 0 : n_sides;   // the longer side first
     if (at == 0) side[1] = side[0], side_q[1] = side_q[0];
     side[at] = qs, side_q[at] = q_tab;
@@ -1585,11 +1641,11 @@ int run_batch(const canz_soap_group& g, int first, int nb, Rot rot, const canz_s
   };
   auto basis_at = [&](size_t terms_at, size_t bf16_at, size_t f32_at) { return terms3 ? terms_at : bf16 ? bf16_at : f32_at; };
   if (u.left)
-    if (int rc = one_side(g.left, g.qleft, g.rows, rp, cp, gm, pan(c.gp), rp2, cp2, basis_at(c.ql3, c.qlp, c.ql))) return rc;
+    if (int rc = one_side(g.left, g.qleft, g.rows, rp, cp, gm, pan(c.gp), rp2, cp2, basis_at(c.ql3, c.qlp, c.ql), c.ql3t)) return rc;
   if (u.right)
-    if (int rc = one_side(g.right, g.qright, g.cols, cp, rp, gmt, pan(c.gpt), cp2, rp2, basis_at(c.qr3, c.qrp, c.qr))) return rc;
+    if (int rc = one_side(g.right, g.qright, g.cols, cp, rp, gmt, pan(c.gpt), cp2, rp2, basis_at(c.qr3, c.qrp, c.qr), c.qr3t)) return rc;
   if (hp.refresh)
-    if (int rc = refresh(side, n_sides, side_q, first, nb, s, o, st)) return rc;
+    if (int rc = refresh(side, n_sides, terms3, side_q, first, nb, s, o, st)) return rc;
   if (hp.refresh && g.mom_rot && bf16) {
     // the caller's rotated momentum follows the new bases, M' = Q_L^T M Q_R once more with the M of this step: bf16
     // operands as for every rotation of this mode; the last product leaves its fp32 sums in the caller's array
