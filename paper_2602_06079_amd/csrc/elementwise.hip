@@ -45,8 +45,11 @@ __device__ __forceinline__ void momentum_tile(const Shape& s, const void* const*
   const int wf = static_cast<int>(s.wfrag);
   // straight = same orientation as the caller's matrix; transposed = the other one
   const int64_t pr = s.tall ? s.np : s.mp, pc = s.tall ? s.mp : s.np;
-  T* straight = (s.tall ? xt : xw) + static_cast<int64_t>(b) * pr * pc;
-  T* transposed = (s.tall ? xw : xt) + static_cast<int64_t>(b) * pr * pc;
+  T* straight = s.tall ? xt : xw;
+  T* transposed = s.tall ? xw : xt;
+  const bool put_straight = straight != nullptr, put_transposed = transposed != nullptr;   // xw is not always asked for
+  straight += static_cast<int64_t>(b) * pr * pc;
+  transposed += static_cast<int64_t>(b) * pr * pc;
   float* mptr = static_cast<float*>(mom[b]);
 
   const int t = threadIdx.x;
@@ -99,8 +102,9 @@ __device__ __forceinline__ void momentum_tile(const Shape& s, const void* const*
     float u[8], mn[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      mn[e] = beta * mo[half][e] + g[half][e];
-      u[e] = nesterov ? g[half][e] + beta * mn[e] : mn[e];
+      // roundings pinned: a matrix has the same bits from either kernel
+      mn[e] = __builtin_fmaf(beta, mo[half][e], g[half][e]);
+      u[e] = nesterov ? __builtin_fmaf(beta, mn[e], g[half][e]) : mn[e];
     }
     if (live[half]) {
       if (VEC || col + 8 <= cols) {
@@ -119,13 +123,18 @@ __device__ __forceinline__ void momentum_tile(const Shape& s, const void* const*
     Vec8<T> o;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      ss += u[e] * u[e];
+      // (the first two squares as one product and one fused multiply-add)
+      if (half == 0 && e < 2)
+        ss = e == 0 ? u[1] * u[1] : __builtin_fmaf(u[0], u[0], ss);
+      else
+        ss = __builtin_fmaf(u[e], u[e], ss);
       o.v[e] = from_f32<T>(u[e]);
-      tile[rl][cv + e] = u[e];
+      if (put_transposed) tile[rl][cv + e] = u[e];
     }
-    *reinterpret_cast<Vec8<T>*>(straight + WorkLayout<T>::chunk_off(row, col, pc)) = o;
+    if (put_straight) *reinterpret_cast<Vec8<T>*>(straight + WorkLayout<T>::chunk_off(row, col, pc)) = o;
   }
-  __syncthreads();
+  if (put_transposed) __syncthreads();
+  if (put_transposed)
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
     const int cl = (t >> 3) + half * 32;  // column of the tile = row of the transposed tile

@@ -54,7 +54,7 @@ constexpr int N_XCD = 8;
 static_assert(BM == PANEL_ROWS && BK == PANEL_K, "tile = panel");
 
 enum { EPI_GRAM = 0, EPI_POLY = 1, EPI_UPDATE = 2, EPI_FINAL = 3, EPI_FINAL_SYM = 4, EPI_MUL = 5, EPI_MUL_Q = 6, EPI_MUL_Q2 = 7,
-       EPI_POLY_APART = 8, EPI_GRAM_APART = 9, EPI_UPDATE_APART = 10, EPI_B3 = 11, EPI_B3_SYM = 12, EPI_OUT_TERMS = 13 };
+       EPI_POLY_APART = 8, EPI_GRAM_APART = 9, EPI_UPDATE_APART = 10, EPI_B3 = 11, EPI_B3_SYM = 12, EPI_OUT_TERMS = 13, EPI_GRAM_T = 14 };
 // EPI_FINAL_SYM: the last-product epilogue (the caller's dense buffers) over the tiles on and above the diagonal of a
 // symmetric result only; the caller mirrors them into the lower triangle afterwards.
 // EPI_*_APART, EPI_MUL*: the diagonals of the symmetric matrices are kept apart and their images are fp16 (kernels.h: SymSpec).
@@ -65,13 +65,17 @@ constexpr bool epi_mul(int epi) { return epi == EPI_MUL || epi == EPI_MUL_Q || e
 constexpr bool epi_f16_in(int epi) { return epi == EPI_POLY_APART || epi_mul(epi); }
 constexpr bool epi_f16_out(int epi) { return epi == EPI_GRAM_APART || epi == EPI_POLY_APART || epi == EPI_MUL; }
 constexpr bool epi_apart(int epi) { return epi_f16_in(epi) || epi == EPI_UPDATE_APART; }   // reads diagonals
-constexpr bool epi_mspace(int epi) { return epi == EPI_GRAM || epi == EPI_GRAM_APART || epi == EPI_POLY || epi == EPI_POLY_APART || epi_mul(epi); }
+constexpr bool epi_mspace(int epi) { return epi == EPI_GRAM || epi == EPI_GRAM_T || epi == EPI_GRAM_APART || epi == EPI_POLY || epi == EPI_POLY_APART || epi_mul(epi); }
 // EPI_B3, EPI_B3_SYM, EPI_OUT_TERMS: products of matrices of up to three bf16 terms (launch_split3*): the result as three
 // terms, the same for symmetric matrices that commute, and the last-product epilogue.
 constexpr bool epi_terms(int epi) { return epi == EPI_B3 || epi == EPI_B3_SYM || epi == EPI_OUT_TERMS; }
 constexpr bool epi_symmetric(int epi) { return epi_mspace(epi) || epi == EPI_FINAL_SYM || epi == EPI_B3_SYM; }
 // symmetric, but element (i, j) not bit for bit (j, i): of two different matrices, or (POLY_APART) with a term of such a product
 constexpr bool epi_two_factors(int epi) { return epi_f16_in(epi) || epi == EPI_B3_SYM; }
+// EPI_GRAM_T, EPI_GRAM_APART: the Gram product reads its operand X from X^T, in which k runs over the rows: 32 x 32 pieces (32 k of 32 rows of
+// X, 2 KiB of a panel) go into LDS as they lie, and the transposing LDS reads turn them into operands (k_major).  X itself is then nobody's
+// operand, and neither the momentum kernel nor the update writes it.  The same products in the same order: an element has the same bits.
+constexpr bool epi_k_major(int epi) { return epi == EPI_GRAM_T || epi == EPI_GRAM_APART; }
 constexpr bool epi_final(int epi) { return epi == EPI_FINAL || epi == EPI_FINAL_SYM || epi == EPI_OUT_TERMS; }
 
 struct EpiArgs {
@@ -98,6 +102,23 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ int swz(int row, int chunk) {
   return (row * CHUNKS + (chunk ^ ((row >> 2) & (CHUNKS - 1)))) * 8;  // element offset in the panel
+}
+
+// The MFMA operand of 32 rows of X and 16 k from a piece of X^T in LDS, 32 k x 32 rows (from its k 0 or 16 on).  ds_read_b64_tr_b16: the 16
+// lanes of a group supply the addresses of 4 k x 16 rows, 4 rows each, and lane j receives the 4 k of row j.  Groups 0 and 1 take
+// rows 0 and 16 of k 0 .. 7, groups 2 and 3 those of k 8 .. 15, in two reads of 4 k (`half`): a half-wave reads 256 bytes of four consecutive k.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ int k_major_lane(int lane, int half) {
+  const int hi = lane >> 5, l = lane & 15, k = 8 * hi + 4 * half + (l >> 2);
+  const int chunk = 2 * ((lane >> 4) & 1) + ((l >> 1) & 1);
+  return k * 32 + ((chunk ^ ((k >> 2) & 3)) << 3) + 4 * (l & 1);
+}
+__device__ __forceinline__ bf16x8 k_major(const __bf16* piece, int lane0, int lane1) {
+  typedef __attribute__((address_space(3))) s16x4 lds_vec;
+  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_vec*)CANZ_LDS(piece + lane0));
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_vec*)CANZ_LDS(piece + lane1));
+  const s16x4 v[2] = {a, b};
+  return __builtin_bit_cast(bf16x8, v);
 }
 
 // value of the neighbouring lane (lane ^ 1), through the DPP quad permute [1, 0, 3, 2]
@@ -506,6 +527,8 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
     // swizzle = (row_l >> 2) & 3 = 2 (g & 1) + lh: lane bits except for g & 1.
     // byte selector of v_perm_b32 over {theirs (bytes 4..7), mine (bytes 0..3)}
     const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
+    const bool diagonal_tile = epi_mspace(EPI) && tm == tn;
+    if (epi_mspace(EPI) || e.c != nullptr) {   // (an update may be asked for the transposed image alone)
     int s_base[2];
 #pragma unroll
     for (int g1 = 0; g1 < 2; ++g1)
@@ -527,8 +550,8 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
         }
     // In a diagonal tile the lower left quarter is the mirror image of the upper right one, as in the small kernel: the
     // two are equal bit for bit when both factors are the same matrix, but only to rounding in a product of two.
-    const bool diagonal_tile = epi_mspace(EPI) && tm == tn;
     if (!diagonal_tile || wm <= wn) flush_stage(C, tm, d.N, 8 * tn + 4 * wn, wm);
+    }
 
     // ---- transposed image: element (i, j) is (row j, k = i) of CT (UPDATE) or of the mirror
     // tile of C (symmetric products).  A lane's 4 consecutive rows are half a chunk.
@@ -744,6 +767,9 @@ struct TermWalk {
   }
 };
 
+// Element offset of k-step k of an operand that is read from X^T (epi_k_major): 32 rows further, 256 of which lie in a row of `panels` panels.
+__device__ __forceinline__ int64_t k_major_off(int k, int64_t panels) { return (k >> 3) * panels * PANEL_ELEMS + (k & 7) * 1024; }
+
 // Operands of a launch: one product (the usual case), or several of different shapes.
 struct OneProblem {
   static constexpr bool multi = false, finals = false;
@@ -855,20 +881,23 @@ __global__ __launch_bounds__(NTHREADS) void k_gemm_nt_bf16(Args args, EpiArgs e_
   const int64_t nkb = d.K / BK;
   // panels per row block (operands that are a part of longer rows: only of the last products and those of several terms)
   const int64_t nkp = epi_terms(EPI) || epi_final(EPI) ? d.ldp / BK : nkb, nkq = epi_terms(EPI) || epi_final(EPI) ? d.ldq / BK : nkb;
-  const __bf16* pl = P + static_cast<int64_t>(b) * d.sp + (static_cast<int64_t>(tm) * nkp + k_begin) * PANEL_ELEMS + wave * 512 + lane * 8;
-  const __bf16* ql = Q + static_cast<int64_t>(b) * d.sq + (static_cast<int64_t>(tn) * nkq + k_begin) * PANEL_ELEMS + wave * 512 + lane * 8;
+  constexpr bool KM = epi_k_major(EPI);
+  constexpr int G_STEP = KM ? 2 * PANEL_ELEMS : 2048;   // from one of a wavefront's 1 KiB pieces of a panel to the next
+  const int64_t km_lane = (wave >> 1) * PANEL_ELEMS + (wave & 1) * 512 + lane * 8;
+  const __bf16* pl = P + static_cast<int64_t>(b) * d.sp + (KM ? 8 * tm * PANEL_ELEMS + km_lane : (static_cast<int64_t>(tm) * nkp + k_begin) * PANEL_ELEMS + wave * 512 + lane * 8);
+  const __bf16* ql = Q + static_cast<int64_t>(b) * d.sq + (KM ? 8 * tn * PANEL_ELEMS + km_lane : (static_cast<int64_t>(tn) * nkq + k_begin) * PANEL_ELEMS + wave * 512 + lane * 8);
   // operands of several terms: where the next panel of each is (the panels are requested in order)
   TermWalk wp(d.pseg, nkb), wq(d.qseg, nkb);
   // one of the 8 direct loads of a stage: idx 0..3 -> P pieces, 4..7 -> Q pieces
   auto fetch_one = [&](__bf16* st, int64_t kt, int idx) {
     const int g = idx & 3;
     if (idx < 4) {
-      const int64_t off = epi_terms(EPI) ? wp.off : kt * PANEL_ELEMS;
-      __builtin_amdgcn_global_load_lds(CANZ_GLB(pl + off + g * 2048), CANZ_LDS(st + wave * 512 + g * 2048), 16, 0, 0);
+      const int64_t off = epi_terms(EPI) ? wp.off : KM ? k_major_off(static_cast<int>(kt) + k_begin, d.M >> 5) : kt * PANEL_ELEMS;
+      __builtin_amdgcn_global_load_lds(CANZ_GLB(pl + off + g * G_STEP), CANZ_LDS(st + wave * 512 + g * 2048), 16, 0, 0);
       if (epi_terms(EPI) && g == 3) wp.next();
     } else {
-      const int64_t off = epi_terms(EPI) ? wq.off : kt * PANEL_ELEMS;
-      __builtin_amdgcn_global_load_lds(CANZ_GLB(ql + off + g * 2048), CANZ_LDS(st + QOFF + wave * 512 + g * 2048), 16, 0, 0);
+      const int64_t off = epi_terms(EPI) ? wq.off : KM ? k_major_off(static_cast<int>(kt) + k_begin, d.M >> 5) : kt * PANEL_ELEMS;
+      __builtin_amdgcn_global_load_lds(CANZ_GLB(ql + off + g * G_STEP), CANZ_LDS(st + QOFF + wave * 512 + g * 2048), 16, 0, 0);
       if (epi_terms(EPI) && g == 3) wq.next();
     }
   };
@@ -883,8 +912,13 @@ __global__ __launch_bounds__(NTHREADS) void k_gemm_nt_bf16(Args args, EpiArgs e_
   // MFMA operand fragments, double-buffered in registers: idx 0..3 -> rows of P, 4..7 -> rows of Q
   const int frag_row = lane & 31, frag_kg = lane >> 5;
   bf16x8 fa[2][4], fb[2][4];
+  const int km0 = k_major_lane(lane, 0), km1 = k_major_lane(lane, 1);
   auto frag_one = [&](const __bf16* st, int kk, int set, int idx) {
-    if (idx < 4)
+    if (KM && idx < 4)
+      fa[set][idx] = k_major(st + (wm * 4 + idx) * 1024 + kk * 512, km0, km1);
+    else if (KM)
+      fb[set][idx - 4] = k_major(st + QOFF + (wn * 4 + idx - 4) * 1024 + kk * 512, km0, km1);
+    else if (idx < 4)
       fa[set][idx] = *reinterpret_cast<const bf16x8*>(st + swz(wm * 128 + idx * 32 + frag_row, kk * 2 + frag_kg));
     else
       fb[set][idx - 4] =
@@ -1162,15 +1196,23 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
   const __bf16* ql = Q + static_cast<int64_t>(b) * d.sq + (static_cast<int64_t>(tn / RN) * nkq) * PANEL_ELEMS +
                      (tn % RN) * (SN * BK) + wave * 512 + lane * 8;
   TermWalk wp(d.pseg, nkb), wq(d.qseg, nkb);
+  constexpr bool KM = epi_k_major(EPI);
+  constexpr int G_STEP = KM ? 2 * PANEL_ELEMS : 2048;
+  if (KM) {   // as in the large kernel
+    const int64_t km_lane = (wave >> 1) * PANEL_ELEMS + (wave & 1) * 512 + lane * 8;
+    pl = P + static_cast<int64_t>(b) * d.sp + tm * (SM / 32) * PANEL_ELEMS + km_lane;
+    ql = Q + static_cast<int64_t>(b) * d.sq + tn * (SN / 32) * PANEL_ELEMS + km_lane;
+  }
   auto fetch_one = [&](__bf16* st, int kt, int idx) {   // idx 0 .. TI - 1: pieces of P, then those of Q
-    const int64_t off = static_cast<int64_t>(kt < nk ? kt : nk - 1) * PANEL_ELEMS;  // past the end: a harmless re-read
+    const int kc = kt < nk ? kt : nk - 1;   // past the end: a harmless re-read
+    const int64_t off = KM ? k_major_off(kc, d.M >> 5) : static_cast<int64_t>(kc) * PANEL_ELEMS;
     if (idx < TI) {
       const int64_t po = epi_terms(EPI) ? wp.off : off;
-      __builtin_amdgcn_global_load_lds(CANZ_GLB(pl + po + idx * 2048), CANZ_LDS(st + wave * 512 + idx * 2048), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(CANZ_GLB(pl + po + idx * G_STEP), CANZ_LDS(st + wave * 512 + idx * 2048), 16, 0, 0);
       if (epi_terms(EPI) && idx == TI - 1) wp.next();
     } else {
       const int64_t qo = epi_terms(EPI) ? wq.off : off;
-      __builtin_amdgcn_global_load_lds(CANZ_GLB(ql + qo + (idx - TI) * 2048), CANZ_LDS(st + SM * BK + wave * 512 + (idx - TI) * 2048), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(CANZ_GLB(ql + qo + (idx - TI) * G_STEP), CANZ_LDS(st + SM * BK + wave * 512 + (idx - TI) * 2048), 16, 0, 0);
       if (epi_terms(EPI) && idx == LPK - 1) wq.next();
     }
   };
@@ -1188,28 +1230,34 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   const int frag_row = lane & 31, frag_kg = lane >> 5;
-  bf16x8 fa[2][TI], fb[2][TJ];
-  auto frag = [&](const __bf16* st, int kk, int idx) {   // idx 0 .. TI - 1: rows of P, then those of Q
-    const int chunk = kk * 2 + frag_kg;
-    if (idx < TI)
-      fa[kk][idx] = *reinterpret_cast<const bf16x8*>(st + swz((wm * TI + idx) * 32 + frag_row, chunk));
+  constexpr int SETS = NST == 3 ? 1 : 2;
+  bf16x8 fa[2 * SETS][TI], fb[2 * SETS][TJ];   // operands of the two half-steps, of this step and of the next
+  const int km0 = k_major_lane(lane, 0), km1 = k_major_lane(lane, 1);
+  auto frag = [&](const __bf16* st, int kk, int set, int idx) {   // idx 0 .. TI - 1: rows of P, then those of Q
+    const int chunk = kk * 2 + frag_kg, to = 2 * set + kk;
+    if (KM && idx < TI)
+      fa[to][idx] = k_major(st + (wm * TI + idx) * 1024 + kk * 512, km0, km1);
+    else if (KM)
+      fb[to][idx - TI] = k_major(st + SM * BK + (wn * TJ + idx - TI) * 1024 + kk * 512, km0, km1);
+    else if (idx < TI)
+      fa[to][idx] = *reinterpret_cast<const bf16x8*>(st + swz((wm * TI + idx) * 32 + frag_row, chunk));
     else
-      fb[kk][idx - TI] = *reinterpret_cast<const bf16x8*>(st + SM * BK + swz((wn * TJ + idx - TI) * 32 + frag_row, chunk));
+      fb[to][idx - TI] = *reinterpret_cast<const bf16x8*>(st + SM * BK + swz((wn * TJ + idx - TI) * 32 + frag_row, chunk));
   };
-  auto mma = [&](int kk, int idx) {
+  auto mma = [&](int kk, int set, int idx) {
     const int i = idx / TJ, j = idx % TJ;
-    acc[i][j] = mfma<EPI>(fa[kk][i], fb[kk][j], acc[i][j]);
+    acc[i][j] = mfma<EPI>(fa[2 * set + kk][i], fb[2 * set + kk][j], acc[i][j]);
   };
   if constexpr (NST == 3) {
     auto multiply = [&](const __bf16* st) {
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-        for (int idx = 0; idx < LPK; ++idx) frag(st, kk, idx);
+        for (int idx = 0; idx < LPK; ++idx) frag(st, kk, 0, idx);
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-        for (int idx = 0; idx < TI * TJ; ++idx) mma(kk, idx);
+        for (int idx = 0; idx < TI * TJ; ++idx) mma(kk, 0, idx);
     };
     // One k-step on stage `cur`: the 4 loads of the following step may stay in flight; after the
     // barrier every wavefront has finished the step before, whose stage `nxt2` then receives step kt + 2.
@@ -1231,89 +1279,79 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
     if (kt < nk) k_step(sb, sa, kt), ++kt;
     __builtin_amdgcn_s_waitcnt(0x0070);  // the re-reads past the end have landed before the block leaves
   } else {
-    // As in the large kernel: the operands are double-buffered in registers, those of a half-step read under the MFMAs of
-    // the one before.  In the middle of step kt every wavefront has read all of `cur`, which then receives step kt + NST, and
-    // step kt + 1 has landed, `younger` later ones still in flight.
+    // The operands are double-buffered in registers, those of a step read under the MFMAs of the one before.  At the start of
+    // step kt every wavefront has read all of `cur`, which then receives step kt + NST, and
+    // step kt + 1 has landed in `nxt`, `younger` later ones still in flight.
     using Yes = std::true_type;
     using No = std::false_type;
-    constexpr int NM = TI * TJ, NF = TI + TJ;   // MFMAs and operands of a half-step
+    constexpr int NM = 2 * TI * TJ, NF = 2 * (TI + TJ);   // MFMAs and operands of a step
 #define CANZ_FENCE() __builtin_amdgcn_sched_barrier(0)
-    auto k_step = [&](auto fetches, auto younger, __bf16* cur, const __bf16* nxt, int kt) {
-      constexpr int left = decltype(younger)::value;   // -1: the last step
+    auto k_step = [&](auto fetches, auto younger, auto parity, __bf16* cur, const __bf16* nxt, int kt) {
+      constexpr int left = decltype(younger)::value, set = decltype(parity)::value;   // left -1: the last step
+      constexpr int vm = left < 0 ? 0 : left * LPK;
+      __builtin_amdgcn_s_waitcnt((vm & 15) | 0x70 | (vm >> 4) << 14);  // vmcnt(vm) lgkmcnt(0)
+      if (left >= 0) __builtin_amdgcn_s_barrier();
+      CANZ_FENCE();
 #pragma unroll
       for (int idx = 0; idx < NM; ++idx) {
-        mma(0, idx);
-        CANZ_FENCE();
-#pragma unroll
-        for (int x = idx * NF / NM; x < (idx + 1) * NF / NM; ++x) frag(cur, 1, x);
-        CANZ_FENCE();
-      }
-      if constexpr (left >= 0) {
-        constexpr int vm = left * LPK;
-        __builtin_amdgcn_s_waitcnt((vm & 15) | 0x70 | (vm >> 4) << 14);  // vmcnt(vm) lgkmcnt(0)
-        __builtin_amdgcn_s_barrier();
-        CANZ_FENCE();
-      }
-#pragma unroll
-      for (int idx = 0; idx < NM; ++idx) {
-        mma(1, idx);
+        mma(idx / (NM / 2), set, idx % (NM / 2));
         CANZ_FENCE();
         if (left >= 0)
 #pragma unroll
-          for (int x = idx * NF / NM; x < (idx + 1) * NF / NM; ++x) frag(nxt, 0, x);
+          for (int x = idx * NF / NM; x < (idx + 1) * NF / NM; ++x) frag(nxt, x / (NF / 2), set ^ 1, x % (NF / 2));
         CANZ_FENCE();
         if (decltype(fetches)::value)
 #pragma unroll
-          for (int x = idx * NF / NM; x < (idx + 1) * NF / NM; ++x) fetch_one(cur, kt + NST, x);
+          for (int x = idx * LPK / NM; x < (idx + 1) * LPK / NM; ++x) fetch_one(cur, kt + NST, x);
         CANZ_FENCE();
       }
     };
 #undef CANZ_FENCE
-#define CANZ_LEFT(n) std::integral_constant<int, n> {}
+#define CANZ_INT(n) std::integral_constant<int, n> {}
     fetch(sa, 0), fetch(sb, 1), fetch(sc, 2), fetch(sd, 3), fetch(se, 4), fetch(sf_, 5);
     if constexpr (NST == 8) fetch(sg, 6), fetch(sh, 7);
     constexpr int vm0 = (NST - 1) * LPK;
     __builtin_amdgcn_s_waitcnt((vm0 & 15) | 0x70 | (vm0 >> 4) << 14);
     __builtin_amdgcn_s_barrier();
 #pragma unroll
-    for (int idx = 0; idx < NF; ++idx) frag(sa, 0, idx);
+    for (int x = 0; x < NF; ++x) frag(sa, x / (NF / 2), 0, x % (NF / 2));
     int kt = 0;
     if constexpr (NST == 8) {   // nk is a multiple of 8; the last eight steps request nothing and the queue drains
       for (; kt + 8 < nk; kt += 8) {
-        k_step(Yes{}, CANZ_LEFT(6), sa, sb, kt);
-        k_step(Yes{}, CANZ_LEFT(6), sb, sc, kt + 1);
-        k_step(Yes{}, CANZ_LEFT(6), sc, sd, kt + 2);
-        k_step(Yes{}, CANZ_LEFT(6), sd, se, kt + 3);
-        k_step(Yes{}, CANZ_LEFT(6), se, sf_, kt + 4);
-        k_step(Yes{}, CANZ_LEFT(6), sf_, sg, kt + 5);
-        k_step(Yes{}, CANZ_LEFT(6), sg, sh, kt + 6);
-        k_step(Yes{}, CANZ_LEFT(6), sh, sa, kt + 7);
+        k_step(Yes{}, CANZ_INT(6), CANZ_INT(0), sa, sb, kt);
+        k_step(Yes{}, CANZ_INT(6), CANZ_INT(1), sb, sc, kt + 1);
+        k_step(Yes{}, CANZ_INT(6), CANZ_INT(0), sc, sd, kt + 2);
+        k_step(Yes{}, CANZ_INT(6), CANZ_INT(1), sd, se, kt + 3);
+        k_step(Yes{}, CANZ_INT(6), CANZ_INT(0), se, sf_, kt + 4);
+        k_step(Yes{}, CANZ_INT(6), CANZ_INT(1), sf_, sg, kt + 5);
+        k_step(Yes{}, CANZ_INT(6), CANZ_INT(0), sg, sh, kt + 6);
+        k_step(Yes{}, CANZ_INT(6), CANZ_INT(1), sh, sa, kt + 7);
       }
-      k_step(No{}, CANZ_LEFT(6), sa, sb, kt);
-      k_step(No{}, CANZ_LEFT(5), sb, sc, kt);
-      k_step(No{}, CANZ_LEFT(4), sc, sd, kt);
-      k_step(No{}, CANZ_LEFT(3), sd, se, kt);
-      k_step(No{}, CANZ_LEFT(2), se, sf_, kt);
-      k_step(No{}, CANZ_LEFT(1), sf_, sg, kt);
-      k_step(No{}, CANZ_LEFT(0), sg, sh, kt);
-      k_step(No{}, CANZ_LEFT(-1), sh, sa, kt);
+      k_step(No{}, CANZ_INT(6), CANZ_INT(0), sa, sb, kt);
+      k_step(No{}, CANZ_INT(5), CANZ_INT(1), sb, sc, kt);
+      k_step(No{}, CANZ_INT(4), CANZ_INT(0), sc, sd, kt);
+      k_step(No{}, CANZ_INT(3), CANZ_INT(1), sd, se, kt);
+      k_step(No{}, CANZ_INT(2), CANZ_INT(0), se, sf_, kt);
+      k_step(No{}, CANZ_INT(1), CANZ_INT(1), sf_, sg, kt);
+      k_step(No{}, CANZ_INT(0), CANZ_INT(0), sg, sh, kt);
+      k_step(No{}, CANZ_INT(-1), CANZ_INT(1), sh, sa, kt);
     } else {
       for (; kt + 6 <= nk; kt += 6) {
-        k_step(Yes{}, CANZ_LEFT(4), sa, sb, kt);
-        k_step(Yes{}, CANZ_LEFT(4), sb, sc, kt + 1);
-        k_step(Yes{}, CANZ_LEFT(4), sc, sd, kt + 2);
-        k_step(Yes{}, CANZ_LEFT(4), sd, se, kt + 3);
-        k_step(Yes{}, CANZ_LEFT(4), se, sf_, kt + 4);
-        k_step(Yes{}, CANZ_LEFT(4), sf_, sa, kt + 5);
+        k_step(Yes{}, CANZ_INT(4), CANZ_INT(0), sa, sb, kt);
+        k_step(Yes{}, CANZ_INT(4), CANZ_INT(1), sb, sc, kt + 1);
+        k_step(Yes{}, CANZ_INT(4), CANZ_INT(0), sc, sd, kt + 2);
+        k_step(Yes{}, CANZ_INT(4), CANZ_INT(1), sd, se, kt + 3);
+        k_step(Yes{}, CANZ_INT(4), CANZ_INT(0), se, sf_, kt + 4);
+        k_step(Yes{}, CANZ_INT(4), CANZ_INT(1), sf_, sa, kt + 5);
       }
-      if (kt < nk) k_step(Yes{}, CANZ_LEFT(4), sa, sb, kt), ++kt;
-      if (kt < nk) k_step(Yes{}, CANZ_LEFT(4), sb, sc, kt), ++kt;
-      if (kt < nk) k_step(Yes{}, CANZ_LEFT(4), sc, sd, kt), ++kt;
-      if (kt < nk) k_step(Yes{}, CANZ_LEFT(4), sd, se, kt), ++kt;
-      if (kt < nk) k_step(Yes{}, CANZ_LEFT(4), se, sf_, kt), ++kt;
+      if (kt < nk) k_step(Yes{}, CANZ_INT(4), CANZ_INT(0), sa, sb, kt), ++kt;
+      if (kt < nk) k_step(Yes{}, CANZ_INT(4), CANZ_INT(1), sb, sc, kt), ++kt;
+      if (kt < nk) k_step(Yes{}, CANZ_INT(4), CANZ_INT(0), sc, sd, kt), ++kt;
+      if (kt < nk) k_step(Yes{}, CANZ_INT(4), CANZ_INT(1), sd, se, kt), ++kt;
+      if (kt < nk) k_step(Yes{}, CANZ_INT(4), CANZ_INT(0), se, sf_, kt), ++kt;
       __builtin_amdgcn_s_waitcnt(0x0070);  // the re-reads past the end have landed
     }
-#undef CANZ_LEFT
+#undef CANZ_INT
   }
 
   // ---- epilogue.  Accumulator register r of lane l in MFMA tile (i, j): row 32 i + 8 (r / 4) + 4 (l / 32) + (r % 4),
@@ -1600,6 +1638,7 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
   // straight image: (row i, k = j).  Neighbouring lanes exchange their packed pairs so that each
   // lane holds two consecutive columns of one row: the even lane of row 2 rp, the odd lane of row 2 rp + 1.
   const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
+  if (symmetric || e.c != nullptr)
 #pragma unroll
   for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -1824,9 +1863,9 @@ hipError_t launch_problems(const GemmBatch& g, EpiArgs e, const SplitWs& w, hipS
 }
 }  // namespace
 
-hipError_t launch_gram_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st) {
-  return g.n > 0 && g.pr[0].sym.diag ? launch_problems<EPI_GRAM_APART>(g, EpiArgs{}, w, st)
-                                     : launch_problems<EPI_GRAM>(g, EpiArgs{}, w, st);
+hipError_t launch_gram_bf16(const GemmBatch& g, bool from_xt, const SplitWs& w, hipStream_t st) {
+  if (g.n > 0 && g.pr[0].sym.diag) return from_xt ? launch_problems<EPI_GRAM_APART>(g, EpiArgs{}, w, st) : hipErrorInvalidValue;
+  return from_xt ? launch_problems<EPI_GRAM_T>(g, EpiArgs{}, w, st) : launch_problems<EPI_GRAM>(g, EpiArgs{}, w, st);
 }
 
 hipError_t launch_poly_bf16(const GemmBatch& g, float ca, float cb, float cc, const SplitWs& w, hipStream_t st) {

@@ -2,13 +2,13 @@
 //
 // Working layout of one sub-batch of nb same-shape matrices (m = min(rows, cols),
 // n = max(rows, cols), mp / np = m / n rounded up to PAD):
-//   XW  [nb][mp][np]  the iterate X in its wide orientation, row-major
-//   XT  [nb][np][mp]  the same values transposed (two buffers, ping-pong)
+//   XT  [nb][np][mp]  the iterate X, transposed from its wide orientation (two buffers, ping-pong)
+//   XW  [nb][mp][np]  the same values in the wide orientation, where they are wanted (muon_step.hip: wants_x)
 //   A,B [nb][mp][mp]  Gram matrix and the polynomial aI + bA + cAA
 // Padding rows / columns hold zeros; zeros stay zero under the iteration, so the GEMM
-// kernels run on the padded extents without bounds checks.  Both orientations are kept
-// because every product then contracts over a contiguous index of both operands
-// (C[i][j] = sum_k P[i][k] Q[j][k]), which is the operand form of the bf16 MFMA.
+// kernels run on the padded extents without bounds checks.  Every product but one contracts over a contiguous index of both operands
+// (C[i][j] = sum_k P[i][k] Q[j][k]), which is the operand form of the bf16 MFMA; the Gram product can also contract over the rows of
+// X^T, through transposing LDS reads, so that X need not be written in both orientations.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -53,7 +53,7 @@ void prof_mark(hipStream_t st, int kind, bool begin);
   } while (0)
 
 // ---- elementwise -----------------------------------------------------------------
-// M <- beta M + G; U = M or G + beta M; U written (type T = bf16 or float) to XW and XT
+// M <- beta M + G; U = M or G + beta M; U written (type T = bf16 or float) to XW (unless null) and XT
 // (padding zero-filled); per-tile sums of U^2 to partial[b][tile].
 template <typename T>
 hipError_t launch_momentum(const Shape& s, int nb, const PtrTable& grad, int grad_dtype,
@@ -154,15 +154,16 @@ struct GemmBatch {
   int n;
   GemmProblem pr[MAX_PROBLEMS];
 };
-// A = scale2[b] * X X^T                      (P = Q = XW); all problems with sym.diag, or none
-hipError_t launch_gram_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st);
+// A = scale2[b] * X X^T, from XW or from XT  (P = Q = XW [nb][M][K] or XT [nb][K][M]); all problems with sym.diag (from XT), or none
+hipError_t launch_gram_bf16(const GemmBatch& g, bool from_xt, const SplitWs& w, hipStream_t st);
 // B = ca I + cb A + cc A A                   (P = Q = A, symmetric); all problems with sym.x and sym.y, or none
 hipError_t launch_poly_bf16(const GemmBatch& g, float ca, float cb, float cc, const SplitWs& w, hipStream_t st);
 // C = P Y, P and Y symmetric and commuting   (Q = Y).  The result leaves as fp16 image and diagonal (CHAIN), as bf16 image and
 // diagonal for the update (Q), or as two bf16 terms [nb][M][2 M] for the last product (Q2)
 enum class MulResult { CHAIN, Q, Q2 };
 hipError_t launch_mul_f16(const GemmBatch& g, MulResult result, const SplitWs& w, hipStream_t st);
-// as launch_update_bf16 below, for several problems; with sym.x: Q's diagonal apart (and sym.aux = X^T)
+// as launch_update_bf16 below, for several problems (c null: the transposed image alone); with sym.x: Q's diagonal apart (and
+// sym.aux = X^T)
 hipError_t launch_update_bf16(const GemmBatch& g, const SplitWs& w, hipStream_t st);
 
 // X' = scale[b] * B X: XW' [mp][np] straight and XT' [np][mp] transposed  (P = B, Q = XT)

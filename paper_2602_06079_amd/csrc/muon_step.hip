@@ -376,6 +376,14 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
     kd.upd = GemmDims{s.mp, s.np, s.mp, s.mp, s.mp, kd.a_elems, kd.x_elems, bt.nb};
   }
   const SplitWs split{reinterpret_cast<float*>(ws + base), SPLIT_MAX_BLOCKS};
+  // X itself, beside X^T: in fp32 mode, for the update without a Newton-Schulz step, and for Gram products of few tiles.  From X^T those take
+  // longer (the transposing LDS reads run at half the rate: 1 x 25600x128 65 us -> 80, 26 x 2048x1024 76 -> 85), which a second image of
+  // few rows in all, written by the momentum kernel and every update, does not outweigh.  us a step, with X -> without: 1 x 25600x128 431 ->
+  // 513, 2 x 12706x160 278 -> 313, 1 x 20480x1024 681 -> 721; 1 x 2048x8192 677 -> 667, 8 x 512x8192 628 -> 598, 26 x 2048x1024 1460 -> 1363,
+  // 4 x 25600x5120 26500 -> 26100.
+  int64_t all_rows = 0;
+  for (int k = 0; k < nk; ++k) all_rows += kind[k].s0.mp * kind[k].nb;
+  const bool wants_x = !is_bf16 || hp.ns_steps == 0 || (all_rows < 2048 && !stages.first && !stages.last);
 
   // momentum (+ gather, cast, both orientations, tile sums of U^2) per part, norm per batch; several parts whose buffers fit one
   // table go in one launch each (four classes of a 0.6B-shaped layer: 55 -> 33 us and 12 -> 4)
@@ -413,7 +421,7 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
       o.neg_lr_scale = static_cast<float>(-static_cast<double>(hp.lr) * update_scale(g, hp.scale_mode));
       const int f = kd.first[h];
       if constexpr (is_bf16) if (shared) {
-        mparts[n_parts++] = MomentumPart<__bf16>{kd.shape[h], n, g.grad_dtype, n_grads, n_moms, kd.xw + f * kd.x_elems,
+        mparts[n_parts++] = MomentumPart<__bf16>{kd.shape[h], n, g.grad_dtype, n_grads, n_moms, wants_x ? reinterpret_cast<__bf16*>(kd.xw) + f * kd.x_elems : nullptr,
                                                  kd.xt[0] + f * kd.x_elems, kd.partial + static_cast<int64_t>(f) * kd.tiles};
         first_out[k][h] = n_outs;
         for (int i = 0; i < n * g.tp; ++i) all_grad.p[n_grads++] = grad.p[i];
@@ -423,7 +431,7 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
         continue;
       }
       CANZ_HIP(CANZ_KERNEL_MOMENTUM,
-               launch_momentum<T>(kd.shape[h], n, grad, g.grad_dtype, mom, hp.beta, hp.nesterov, kd.xw + f * kd.x_elems,
+               launch_momentum<T>(kd.shape[h], n, grad, g.grad_dtype, mom, hp.beta, hp.nesterov, wants_x ? kd.xw + f * kd.x_elems : nullptr,
                                   kd.xt[0] + f * kd.x_elems, kd.partial + static_cast<int64_t>(f) * kd.tiles, st),
                "momentum kernel");
     }
@@ -474,10 +482,10 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
     for (int k = 0; k < nk; ++k) {
       const Kind& kd = kind[k];
       GemmProblem& pr = gb.pr[k] = GemmProblem{};
-      pr.d = kd.gram, pr.p = kd.xw, pr.q = kd.xw, pr.c = kd.a, pr.scale = first ? kd.scale2 : nullptr;
+      pr.d = kd.gram, pr.p = pr.q = wants_x ? kd.xw : kd.xt[cur], pr.c = kd.a, pr.scale = first ? kd.scale2 : nullptr;
       pr.sym.diag = apart ? kd.da : nullptr;
     }
-    CANZ_HIP(CANZ_KERNEL_GRAM, launch_gram_bf16(gb, split, st), "gram kernel");
+    CANZ_HIP(CANZ_KERNEL_GRAM, launch_gram_bf16(gb, !wants_x, split, st), "gram kernel");
     // the product of the symmetric images P (index ip of b, unit B) and Y with their diagonals
     auto mul = [&](const Kind& kd, int ip, const void* y, const float* dy, float unit, void* c, float* dc) {
       GemmProblem pr{};
@@ -538,7 +546,7 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
         for (int k = 0; k < nk; ++k) {
           const Kind& kd = kind[k];
           GemmProblem& pr = gb.pr[k] = GemmProblem{};
-          pr.d = kd.upd, pr.p = q[k], pr.q = kd.xt[cur], pr.c = kd.xw, pr.ct = kd.xt[cur ^ 1];
+          pr.d = kd.upd, pr.p = q[k], pr.q = kd.xt[cur], pr.c = wants_x ? kd.xw : nullptr, pr.ct = kd.xt[cur ^ 1];
           pr.scale = first_it ? kd.scale : nullptr;
           pr.sym.x = dq[k], pr.sym.aux = kd.xt[cur];
         }

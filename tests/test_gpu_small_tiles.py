@@ -75,3 +75,29 @@ def test_variants_agree_bit_for_bit(canz, shape):
         one = DeviceGroup(canz, rows, cols, grads[i:i + 1], zeros[:1])
         run_step(canz, [one], hp)
         assert np.array_equal(to_host64(one.out_t[0]), to_host64(many.out_t[i]))
+
+
+@pytest.mark.parametrize("shapes", [[(2, 432, 640), (2, 181, 192)], [(3, 64, 520), (1, 130, 66), (5, 97, 257)],
+                                    [(2, 1024, 1024), (1, 700, 1300)]],
+                         ids=lambda s: "+".join("%dx%dx%d" % x for x in s))
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_classes_of_a_call_as_each_alone(canz, shapes, dtype):
+    """Classes that share their launches (momentum, norm, last product; the Gram product from X^T once the rows together
+    reach 2048): every matrix has the bits that it has in a call of its own."""
+    hp = canz.Hparams(out_mode=canz.OUT_DELTA)
+    made = []
+    for c, (n, rows, cols) in enumerate(shapes):
+        grads = [W.gen_grad(97, 16 * c + i, rows, cols)[0] for i in range(n)]
+        if dtype == "bf16":
+            grads = [W.f32_to_bf16_bits(widen(g).astype(np.float32)) for g in grads]
+        else:
+            grads = [widen(g).astype(np.float32) for g in grads]
+        made.append((rows, cols, grads, [W.gen_normal_f32(97, 16 * c + i, 3, rows, cols, 0.01) for i in range(n)]))
+    together = [DeviceGroup(canz, r, k, g, m) for r, k, g, m in made]
+    run_step(canz, together, hp)
+    for dg, (rows, cols, grads, moms) in zip(together, made):
+        for i in range(len(grads)):
+            one = DeviceGroup(canz, rows, cols, grads[i:i + 1], moms[i:i + 1])
+            run_step(canz, [one], hp)
+            assert np.array_equal(to_host64(one.out_t[0]), to_host64(dg.out_t[i]))
+            assert np.array_equal(one.mom_host(0), dg.mom_host(i))
