@@ -25,8 +25,9 @@ struct alignas(16) Vec8<__bf16> {
   __bf16 v[8];
 };
 
-// VEC: rows and fragments of a multiple of 8 elements.  Otherwise (one fragment then: those of several are multiples of 8) the same
-// accesses, aligned to an element only, and element by element where the edge of the matrix cuts the eight.
+// VEC: rows and fragments of a multiple of 8 elements.  Otherwise the same accesses, aligned to an element only, and element by element
+// where the edge of the matrix cuts the eight.  Either way eight columns lie in one fragment: those of several fragments are multiples
+// of 8, whatever shares the launch (its parts may differ in tp, and one ragged part sends all of them here without VEC).
 // One block = one 64 x 64 tile of one matrix in the caller's orientation, extended over
 // the padded extents (elements outside rows x cols are zeros and touch no caller memory).
 // Step 2 of the operator: M <- beta M + G, U = M (or G + beta M); step 1 (TP gather) is
@@ -67,7 +68,7 @@ __device__ __forceinline__ void momentum_tile(const Shape& s, const void* const*
 #pragma unroll
     for (int e = 0; e < 8; ++e) g[half][e] = 0.f, mo[half][e] = 0.f;
     if (!live[half]) continue;
-    const int f = VEC ? col / wf : 0;
+    const int f = s.tp > 1 ? col / wf : 0;
     const int64_t gi = static_cast<int64_t>(row) * wf + (col - f * wf);
     if (VEC || col + 8 <= cols) {
       if (grad_dtype == CANZ_DT_BF16) {
@@ -88,8 +89,8 @@ __device__ __forceinline__ void momentum_tile(const Shape& s, const void* const*
 #pragma unroll
       for (int e = 0; e < 7; ++e) {
         if (col + e >= cols) break;
-        g[half][e] = grad_dtype == CANZ_DT_BF16 ? static_cast<float>(static_cast<const __bf16*>(grad[b])[gi + e])
-                                                : static_cast<const float*>(grad[b])[gi + e];
+        g[half][e] = grad_dtype == CANZ_DT_BF16 ? static_cast<float>(static_cast<const __bf16*>(grad[b * s.tp + f])[gi + e])
+                                                : static_cast<const float*>(grad[b * s.tp + f])[gi + e];
         mo[half][e] = mptr[static_cast<int64_t>(row) * cols + col + e];
       }
     }
