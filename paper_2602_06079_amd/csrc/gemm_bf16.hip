@@ -1686,11 +1686,10 @@ int cu_count() {
   return cached[dev];
 }
 
-// How a launch is divided between the two kernels.  Long products (k above SMALL_MAX_K; the small
-// tile moves twice the bytes per FLOP) stay with the large kernel and its k-split.  Otherwise
-// the large kernel runs the full rounds of one tile per CU, and the left-over tiles go to the
-// small kernel when they would leave at least half of the chip idle for a whole tile time -
-// which includes launches with no full round at all.
+// How a launch is divided between the two kernels.  Launches of at most half a round run on small tiles, unless a k-split pays
+// (split_pays).  Of the others long products (k above SMALL_MAX_K; the small tile moves twice the bytes per FLOP) stay with the large
+// kernel and its k-split.  Otherwise the large kernel runs the full rounds of one tile per CU, and the left-over tiles go to the
+// small kernel when they would leave at least half of the chip idle for a whole tile time.
 constexpr int64_t SMALL_MAX_K = 4096;
 // ... except the products of m x m matrices of merged steps, whose left-over tiles gain up to here (4 x 5120^2, 840 tiles on 256
 // CUs)
@@ -1707,7 +1706,7 @@ int64_t tile_count(const GemmDims& d, int tile = BM) {
 template <int EPI>
 int64_t large_share(int64_t tiles, int64_t cus, int64_t longest_k) {
   const int64_t left = tiles % cus;
-  if (2 * tiles <= cus) return 0;   // no round to fill, whatever k
+  if (2 * tiles <= cus) return 0;   // no round to fill
   constexpr bool msquare = EPI == EPI_POLY || epi_f16_in(EPI);
   if (!epi_terms(EPI) && longest_k > (epi_f16_in(EPI) ? SMALL_MAX_K_MSPACE : SMALL_MAX_K)) return tiles;
   // a polynomial product (k = m, the shortest k range of the step) of less than two rounds runs faster on small
@@ -1725,6 +1724,29 @@ template <int EPI, int SM>
 int64_t small_tiles(const GemmDims& d) {
   return epi_two_factors(EPI) && SM == 64 ? 4 * tile_count<EPI>(d, 128) : tile_count<EPI>(d, SM);
 }
+// Left-over tiles cut into k-slices (each at least 8 k-steps long) so that they occupy as many blocks as fit: how many slices a tile, or 1.
+// Splitting costs two more launches plus parking and re-reading the accumulators, about 0.2 ms all told; a k-step takes about 0.65 us.
+// Split only where the part of a tile time it saves, (1 - 1/sp) * k-steps, is clearly longer than that.
+template <int EPI>
+int64_t k_slices(int64_t left, int64_t steps, int64_t cus, const SplitWs& w) {
+  if (left == 0 || !w.partial || epi_terms(EPI)) return 1;
+  const int64_t sp = std::max<int64_t>(1, std::min<int64_t>({std::min<int64_t>(cus, w.max_blocks) / left, steps / 8, 8}));
+  return sp > 1 && steps * (sp - 1) / sp >= 400 ? sp : 1;
+}
+// Whether a launch of at most half a round, whose tiles can be split, is faster so than on small tiles (launch_small): from a length of k on
+// that depends on how many of those share a CU.  us of a Gram product, small tiles / split:
+//   64 x 64, a CU each (0.08 to 0.11 us a k-step)     1 x 256, k 131072: 313 / 366, 196352: 474 / 482, 262144: 652 / 617;  1 x 1024, k 196608: 586 / 551
+//   64 x 64, or 128 x 128 with eight stages (0.17 to 0.21)   1536, k 32768: 181 / 216, 45056: 251 / 234;  2048, k 32768: 197 / 231, 45056: 272 / 261,
+//                                                            65536: 386 / 324;  2560, k 45056: 297 / 303, 65536: 432 / 410
+//   128 x 128 with three stages (0.40 to 0.48)        3072, k 16384: 205 / 266, 24576: 308 / 235;  3840, k 16384: 237 / 268, 25600: 376 / 321
+// The last ones cross where k_slices begins to split them.
+template <int EPI>
+bool split_pays(const GemmDims& d, int64_t steps, int64_t cus) {
+  if (small_tiles<EPI, 64>(d) <= cus) return steps >= 6144;
+  const bool three_stages = small_tiles<EPI, 64>(d) > 2 * cus && small_tiles<EPI, 128>(d) > cus;
+  return three_stages || steps >= 1408;
+}
+
 template <int EPI, int SM>
 int64_t renumber(OneProblem& args) {
   return small_tiles<EPI, SM>(args.d);
@@ -1779,7 +1801,9 @@ hipError_t launch(const GemmDims& d, const void* P, const void* Q, EpiArgs e, co
   const int64_t tiles = tile_count<EPI>(d);
   const int64_t cus = cu_count();
   const OneProblem one{d, static_cast<const __bf16*>(P), static_cast<const __bf16*>(Q)};
-  const int64_t whole_large = large_share<EPI>(tiles, cus, d.K);
+  const int64_t left = tiles % cus, splits = k_slices<EPI>(left, d.K / BK, cus, w);
+  const bool split_all = 2 * tiles <= cus && splits > 1 && split_pays<EPI>(d, d.K / BK, cus);
+  const int64_t whole_large = split_all ? tiles : large_share<EPI>(tiles, cus, d.K);
   if (whole_large < tiles) {
     if (whole_large > 0) {
       e.full_rounds = static_cast<int>(whole_large / cus), e.left = 0, e.splits = 1, e.partial = nullptr;
@@ -1790,20 +1814,10 @@ hipError_t launch(const GemmDims& d, const void* P, const void* Q, EpiArgs e, co
     launch_small<EPI>(one, e, whole_large, tiles, epi_terms(EPI) ? d.K * d.nseg : d.K, cus, s, o, st);
     return hipGetLastError();
   }
-  // full rounds of one tile per block, then the left-over tiles cut into k-slices (each at
-  // least 8 k-steps long) so that they occupy as many blocks as fit
+  // full rounds of one tile per block, then the left-over tiles cut into k-slices
   e.full_rounds = static_cast<int>(tiles / cus);
-  e.left = static_cast<int>(tiles % cus);
-  e.splits = 1;
-  if (e.left > 0 && w.partial && !epi_terms(EPI)) {
-    const int64_t by_blocks = std::min<int64_t>(cus, w.max_blocks) / e.left;
-    const int64_t by_k = (d.K / BK) / 8;
-    const int64_t sp = std::max<int64_t>(1, std::min<int64_t>({by_blocks, by_k, 8}));
-    // Splitting costs two more launches plus parking and re-reading the accumulators, about
-    // 0.2 ms all told; a k-step takes about 0.65 us.  Split only where the part of a tile
-    // time it saves, (1 - 1/sp) * k-steps, is clearly longer than that.
-    if (sp > 1 && (d.K / BK) * (sp - 1) / sp >= 400) e.splits = static_cast<int>(sp);
-  }
+  e.left = static_cast<int>(left);
+  e.splits = static_cast<int>(splits);
   e.partial = w.partial;
   // whole tiles: one persistent block per CU (fewer if there are fewer tiles)
   const int64_t whole = e.splits > 1 ? e.full_rounds * cus : tiles;
