@@ -147,6 +147,48 @@ def ns_flops(rows, cols, steps):
     return steps * (4 * m * m * n + 2 * m ** 3)
 
 
+def stage_lengths(m, n, ns_steps, bf16):
+    """Newton-Schulz steps per stage, as the library merges those of an m x n matrix (m <= n)."""
+    wide = m >= 1536 and m * n >= 1 << 24 and (2 * m <= n if m >= 5120 else 20 * m <= 9 * n)
+    merge, lens = bf16 and ns_steps >= 3 and wide, []
+    while sum(lens) < ns_steps:
+        left = ns_steps - sum(lens)
+        lens.append((3 if left >= 4 else 2) if merge and not lens else 2 if merge and left == 2 else 1)
+    return lens
+
+
+def momentum_bytes(shapes, tp, grad_bytes, ns_steps, bf16):
+    """Bytes that the momentum kernels of one library call read and write: gradient, momentum in and out, and U as X^T, and as
+    X too where the library wants it (fp32 mode, no Newton-Schulz step, or single steps of fewer than 2048 padded rows in a run).
+    shapes: (rows, cols) of the call's matrices in order.  Matrices of one shape up to a transpose make a batch; up to four
+    consecutive batches of fewer than 2048 tiles make a run, parted by whether their steps are merged."""
+    def pad(x):
+        return (x + 255) // 256 * 256
+
+    batches = []   # (m, n), count
+    for r, c in shapes:
+        key = (min(r, c), max(r, c))
+        cap = min(128 // tp, max(1, (1 << 30) // (pad(key[0]) * pad(key[1]))))
+        if batches and batches[-1][0] == key and batches[-1][1] < cap:
+            batches[-1][1] += 1
+        else:
+            batches.append([key, 1])
+    elems = [pad(k[0]) * pad(k[1]) * n for k, n in batches]
+    small = [bf16 and e < 2048 * 65536 for e in elems]
+    total, i = 0.0, 0
+    while i < len(batches):
+        j = i + 1
+        while small[i] and j < len(batches) and j - i < 4 and small[j] and sum(elems[i:j + 1]) <= 1 << 30:
+            j += 1
+        for merged in (False, True):
+            run = [(k, n) for k, n in batches[i:j] if (max(stage_lengths(*k, ns_steps, bf16), default=1) > 1) == merged]
+            rows = sum(pad(k[0]) * n for k, n in run)
+            images = 2 if not bf16 or ns_steps == 0 or (rows < 2048 and not merged) else 1
+            total += sum(k[0] * k[1] * n for k, n in run) * (grad_bytes + 8 + images * (2 if bf16 else 4))
+        i = j
+    return total
+
+
 def main_shampoo(args, canz, W, np, torch):
     """One rank's Shampoo step (canz_shampoo_step): Algorithm 1 with W(p) = Shampoo FLOPs
     (App. D.5) on the set of --config, alpha = 1, the most loaded rank's share."""
@@ -665,12 +707,7 @@ def main():
     # steps (canz.h: the quintic of this benchmark keeps its iteration bounded) there is one Gram product and one product with X
     # per stage, and n merged steps take n polynomials and n - 1 times B A, B A B and Q.
     def stages(m, n):
-        wide = m >= 1536 and m * n >= 1 << 24 and (2 * m <= n if m >= 5120 else 20 * m <= 9 * n)
-        lens = []
-        while sum(lens) < hp.ns_steps:
-            left = hp.ns_steps - sum(lens)
-            merge = bf16 and hp.ns_steps >= 3 and wide
-            lens.append((3 if left >= 4 else 2) if merge and not lens else 2 if merge and left == 2 else 1)
+        lens = stage_lengths(m, n, hp.ns_steps, bf16)
         return len(lens), sum(x + 3 * (x - 1) for x in lens), lens[-1] if lens else 0
 
     def pad(x):
@@ -730,8 +767,8 @@ def main():
                     avg_launch_ms=kernels[dom]["avg_ms"])
     if "momentum" in kernels:
         grad_b = 2 if s["grad_dtype"] == W.DT_BF16 else 4
-        esz = 2 if args.precision == "bf16" else 4
-        bytes_step = total_elems * (grad_b + 8 + 2 * esz)
+        bytes_step = sum(momentum_bytes([(s["rows"][p], s["cols"][p]) for g in groups[lo:hi] for p in g], tp, grad_b, hp.ns_steps, bf16)
+                         for lo, hi in calls)
         kernels["momentum"]["gbs"] = bytes_step / (kernels["momentum"]["ms_per_step"] * 1e-3) / 1e9
         kernels["momentum"]["frac_hbm_peak"] = kernels["momentum"]["gbs"] / PEAK_HBM_GBS
 
