@@ -401,13 +401,15 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 
 // tau and the scale of v for a column with diagonal element al and sum of squares ss below it.  The root and the quotients are on the
 // chain of every column: from the chip's estimates with a step of Newton's method each (and the quotient's remainder), which leaves what rounding
-// leaves, in a third of the time of the library's, except where the squares are close to the smallest numbers there are.
+// leaves, in a third of the time of the library's, except where the squares are close to the smallest numbers there are.  Not in the
+// kernels for long columns (REFINED = false), which have no registers for it.
 __device__ __forceinline__ float refined_rcp(float x, float r) { return __builtin_fmaf(__builtin_fmaf(-x, r, 1.f), r, r); }
+template <bool REFINED = true>
 __device__ __forceinline__ void reflector_of(bool live, float ss, float al, float& tau, float& scale) {
   tau = 0.f, scale = 0.f;
   if (live && ss > 0.f) {
     const float x2 = __builtin_fmaf(al, al, ss);
-    if (x2 > 1e-30f) {
+    if (REFINED && x2 > 1e-30f) {
       const float y = __builtin_amdgcn_rsqf(x2);
       float nrm = x2 * y;
       nrm = __builtin_fmaf(__builtin_fmaf(-nrm, nrm, x2), 0.5f * y, nrm);
@@ -476,14 +478,15 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
 }
 
 // Columns ka and / or kb (registers) <- H_c applied to them, v_c in LDS.  v_c stays in registers between the dot products and the updates
-// where there is room beside the columns.
+// where there is room beside the columns.  Long columns leave 32 registers: a test before every slot keeps the reads of v apart.
 template <int XS, bool DO_A, bool DO_B>
-__device__ __forceinline__ void apply_reflector(f32x4 (&ka)[XS], f32x4 (&kb)[XS], const f32x4* s_v4, int lane, float tau) {
-  constexpr bool HOLD_V = XS <= 4;
+__device__ __forceinline__ void apply_reflector(f32x4 (&ka)[XS], f32x4 (&kb)[XS], const f32x4* s_v4, int nvec, int lane, float tau) {
+  constexpr bool HOLD_V = XS <= 4, LONG = XS > 8;
   f32x4 v[HOLD_V ? XS : 1];
   float da = 0.f, db = 0.f;
 #pragma unroll
   for (int sl = 0; sl < XS; ++sl) {
+    if (LONG && lane + 64 * sl >= nvec) continue;
     const f32x4 y = s_v4[lane + 64 * sl];
     if (HOLD_V) v[sl] = y;
 #pragma unroll
@@ -491,19 +494,29 @@ __device__ __forceinline__ void apply_reflector(f32x4 (&ka)[XS], f32x4 (&kb)[XS]
       if (DO_A) da = __builtin_fmaf(ka[sl][e], y[e], da);
       if (DO_B) db = __builtin_fmaf(kb[sl][e], y[e], db);
     }
-    if (!HOLD_V && (XS > 8 || (sl & 3) == 3)) __builtin_amdgcn_sched_barrier(0);   // few reads of v at a time: more would be spilled
+    if (!HOLD_V && !LONG && (sl & 3) == 3) __builtin_amdgcn_sched_barrier(0);   // few reads of v at a time: more would be spilled
   }
   const float fa = DO_A ? tau * wave_sum_dpp(da) : 0.f;
   const float fb = DO_B ? tau * wave_sum_dpp(db) : 0.f;
 #pragma unroll
   for (int sl = 0; sl < XS; ++sl) {
+    if (LONG && lane + 64 * sl >= nvec) continue;
     const f32x4 y = HOLD_V ? v[sl] : s_v4[lane + 64 * sl];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       if (DO_A) ka[sl][e] = __builtin_fmaf(-fa, y[e], ka[sl][e]);
       if (DO_B) kb[sl][e] = __builtin_fmaf(-fb, y[e], kb[sl][e]);
     }
-    if (!HOLD_V && (XS > 8 || (sl & 3) == 3)) __builtin_amdgcn_sched_barrier(0);
+    if (!HOLD_V && !LONG && (sl & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// The products of the block run over the rows of the reflectors from the block's first column on: zero before the panel.
+__device__ __forceinline__ void zero_before_panel(const QrMatrix& a, const QrArgs& args, int t) {
+  const int before = QB * args.pos;
+  for (int e = t; e < QB * before; e += QTH) {
+    const int r = e / before, q = e - r * before;
+    a.vall[static_cast<int64_t>(args.jb + before + r) * a.dp + args.jb + q] = 0.f;
   }
 }
 
@@ -518,7 +531,7 @@ __device__ __forceinline__ void apply_reflector(f32x4 (&ka)[XS], f32x4 (&kb)[XS]
 // divisions and a root of the library and every wavefront alike, 20, 25, 41 now.  Fewer wavefronts of more columns are slower (8 of 4 columns:
 // 27, 35, 53): a wavefront on its own does not fill its SIMD.
 //
-// At most 256 XS remaining rows (XS = 2 .. 12: 512 .. 3072): every
+// At most 256 XS remaining rows (XS = 2, 4, 8: 512 .. 2048): every
 // wavefront loads its two columns (wave + 1 and wave + 17) into registers once and keeps them there.  The
 // columns are never written back: what the factorisation leaves in them is R, which nothing uses.
 template <int XS>
@@ -557,10 +570,7 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_regs(QrArgs args) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = k[sl][e] * scale;
       s_v4[c & 1][lane + 64 * sl] = o;
-      if (XS > 8) {   // (base in scalar registers)
-        if (lane + 64 * sl < nvec) *reinterpret_cast<f32x4*>(reinterpret_cast<char*>(vg + 64 * sl) + 16u * lane) = o;
-      } else if (lane + 64 * sl < nvec) vg[lane + 64 * sl] = o;
-      if (XS > 8) __builtin_amdgcn_sched_barrier(0);   // one at a time: the columns leave few registers
+      if (lane + 64 * sl < nvec) vg[lane + 64 * sl] = o;
     }
   };
 
@@ -570,60 +580,148 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_regs(QrArgs args) {
   }
   load_col(ka, ca);
   if (cb < QB) load_col(kb, cb);
-  // the products of the block run over the rows of the reflectors from the block's first column on: zero before the panel
-  for (int e = t; e < QB * QB * args.pos; e += QTH) {
-    const int r = e / (QB * args.pos), q = e - r * (QB * args.pos);
-    a.vall[static_cast<int64_t>(j0 + r) * dp + args.jb + q] = 0.f;
-  }
+  zero_before_panel(a, args, t);
 
   for (int c = 0; c + 1 < QB; ++c) {
     lds_barrier();   // v_c and tau_c are in place, and every wavefront has finished with v_(c-1)
     const float tau = s_tau[c];
     const f32x4* v = s_v4[c & 1];
     const bool live = tau != 0.f;
-    // Long columns leave 32 registers: every part stands once and its reads and addresses go one at a time (46 spilled registers -> 12,
-    // a panel of 3072 rows 125 -> 98 us)
-    if constexpr (XS > 8) {
-      const bool next = c + 1 == ca || c + 1 == cb;
-      if (next) __builtin_amdgcn_s_setprio(3);
-      if (live && ca > c) apply_reflector<XS, true, false>(ka, kb, v, lane, tau);
-      if (c + 1 == ca) make_v(ka, c + 1);
-      if (live && cb < QB && cb > c) apply_reflector<XS, false, true>(ka, kb, v, lane, tau);
-      if (c + 1 == cb) make_v(kb, c + 1);
-      __builtin_amdgcn_s_setprio(0);
-    } else
     if (c + 1 == ca) {
       __builtin_amdgcn_s_setprio(3);
-      if (live) apply_reflector<XS, true, false>(ka, kb, v, lane, tau);
+      if (live) apply_reflector<XS, true, false>(ka, kb, v, nvec, lane, tau);
       make_v(ka, c + 1);
       __builtin_amdgcn_s_setprio(0);
-      if (live && cb < QB) apply_reflector<XS, false, true>(ka, kb, v, lane, tau);
+      if (live && cb < QB) apply_reflector<XS, false, true>(ka, kb, v, nvec, lane, tau);
     } else if (c + 1 == cb) {
       __builtin_amdgcn_s_setprio(3);
-      if (live) apply_reflector<XS, false, true>(ka, kb, v, lane, tau);
+      if (live) apply_reflector<XS, false, true>(ka, kb, v, nvec, lane, tau);
       make_v(kb, c + 1);
       __builtin_amdgcn_s_setprio(0);
     } else if (live) {   // columns that have become reflectors are left alone
       const bool do_a = ca > c, do_b = cb < QB && cb > c;
       if (do_a && do_b)
-        apply_reflector<XS, true, true>(ka, kb, v, lane, tau);
+        apply_reflector<XS, true, true>(ka, kb, v, nvec, lane, tau);
       else if (do_b)
-        apply_reflector<XS, false, true>(ka, kb, v, lane, tau);
+        apply_reflector<XS, false, true>(ka, kb, v, nvec, lane, tau);
       else if (do_a)
-        apply_reflector<XS, true, false>(ka, kb, v, lane, tau);
+        apply_reflector<XS, true, false>(ka, kb, v, nvec, lane, tau);
     }
   }
   lds_barrier();
   if (t < QB) a.tau[args.pos * QB + t] = s_tau[t];
 }
 
-// More remaining rows than the registers hold: as k_qr_panel_regs, every wavefront
+// Longer columns.  A second copy of v_c and the pipelined chain of k_qr_panel_regs cost these more in spilled registers than they save
+// (us a panel, pipelined / with two barriers a step, one copy and the library's root and quotients: 2049 to 3072 rows 100 / 70, 3073 to 8192
+// on average 420 / 380), so: every wavefront applies H_c to its later columns and the owner of column c + 1 takes that one's head; barrier;
+// the owner writes v_(c+1); barrier.
+//
+// Up to 3072 remaining rows (XS = 12) the columns stay in registers.
+template <int XS>
+__global__ __launch_bounds__(QTH) void k_qr_panel_long(QrArgs args) {
+  __shared__ f32x4 s_v4[64 * XS];
+  __shared__ float s_tau[QB];
+  const QrMatrix a = qr_matrix(args, blockIdx.x);
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int64_t dp = a.dp;
+  const int j0 = args.jb + args.pos * QB;
+  const int nvec = (a.dp - j0) / 4;                   // <= 64 XS
+  const int ca = wave + 1, cb = wave + 1 + QWAVES;    // this wavefront's columns (cb only if < 32)
+  f32x4 ka[XS], kb[XS];
+
+  auto load_col = [&](f32x4 (&k)[XS], int c) {
+    const f32x4* x = reinterpret_cast<const f32x4*>(a.wk + static_cast<int64_t>(j0 + c) * dp + j0);
+#pragma unroll
+    for (int sl = 0; sl < XS; ++sl) {   // beyond the column nothing is read, here and below
+      const int q = lane + 64 * sl;
+      if (q < nvec) k[sl] = x[q];
+    }
+  };
+  // sum of squares below row c and the element at row c, over the wavefront
+  auto head = [&](const f32x4 (&k)[XS], int c, float& ss, float& al) {
+    ss = 0.f, al = 0.f;
+#pragma unroll
+    for (int sl = 0; sl < XS; ++sl) {
+      const int q = lane + 64 * sl;
+      if (q < nvec) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = 4 * q + e;
+          if (r > c) ss += k[sl][e] * k[sl][e];
+          if (r == c) al = k[sl][e];
+        }
+      }
+    }
+    ss = wave_sum_dpp(ss), al = wave_sum_dpp(al);
+  };
+  // column c (in k), whose head is (ss, al), becomes the reflector v_c: to LDS, to the reflector array, tau to LDS
+  auto make_v = [&](const f32x4 (&k)[XS], int c, float ss, float al) {
+    float tau, scale;
+    reflector_of<false>(j0 + c < a.d, ss, al, tau, scale);
+    f32x4* vg = reinterpret_cast<f32x4*>(a.vall + static_cast<int64_t>(j0 + c) * dp + j0);
+#pragma unroll
+    for (int sl = 0; sl < XS; ++sl) {
+      const int q = lane + 64 * sl;
+      if (q < nvec) {
+        const f32x4 o = v_of(k[sl], q, c, scale);
+        s_v4[q] = o;
+        vg[q] = o;
+      }
+    }
+    if (lane == 0) s_tau[c] = tau;
+  };
+
+  if (wave == 0) {
+    float ss, al;
+    load_col(ka, 0);
+    head(ka, 0, ss, al);
+    make_v(ka, 0, ss, al);
+  }
+  load_col(ka, ca);
+  if (cb < QB) load_col(kb, cb);
+  lds_barrier();
+
+  for (int c = 0; c < QB; ++c) {
+    const float tau = s_tau[c];
+    const bool do_a = ca > c, do_b = cb < QB && cb > c;
+    if (tau != 0.f) {   // columns that have become reflectors are left alone
+      if (do_a && do_b)
+        apply_reflector<XS, true, true>(ka, kb, s_v4, nvec, lane, tau);
+      else if (do_a)
+        apply_reflector<XS, true, false>(ka, kb, s_v4, nvec, lane, tau);
+      else if (do_b)
+        apply_reflector<XS, false, true>(ka, kb, s_v4, nvec, lane, tau);
+    }
+    // the owner of column c + 1 takes its head while the others are still busy with their columns
+    const bool owner = c + 1 < QB && wave == c % QWAVES;
+    float ss = 0.f, al = 0.f;
+    if (owner) {
+      if (c + 1 == ca)
+        head(ka, c + 1, ss, al);
+      else
+        head(kb, c + 1, ss, al);
+    }
+    lds_barrier();   // every wavefront has finished with v_c
+    if (owner) {
+      if (c + 1 == ca)
+        make_v(ka, c + 1, ss, al);
+      else
+        make_v(kb, c + 1, ss, al);
+    }
+    lds_barrier();   // v_(c+1) and tau_(c+1) are in place
+  }
+  zero_before_panel(a, args, t);
+  if (t < QB) a.tau[args.pos * QB + t] = s_tau[t];
+}
+
+// Beyond 3072 remaining rows every wavefront
 // keeps the first 256 XS rows of its two columns in registers for the whole kernel; the rows beyond are streamed
 // from the working copy on every step (read for the dot product, read and written for the update: the wavefront's
 // own stores, which it reads back itself).  v_c is in LDS at full length.
 template <int XS>
 __global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrArgs args) {
-  __shared__ f32x4 s_v4[2][VMAX / 4];
+  __shared__ f32x4 s_v4[VMAX / 4];
   __shared__ float s_tau[QB];
   constexpr int NR = 64 * XS;   // float4 of a column kept in registers
   constexpr int TU = 2;         // loads in flight per lane in the streaming loops
@@ -641,10 +739,18 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrArgs args) {
 #pragma unroll
     for (int sl = 0; sl < XS; ++sl) k[sl] = x[lane + 64 * sl];
   };
-  // column c becomes the reflector v_c: to LDS, to the reflector array, tau to LDS
-  auto make_v = [&](const f32x4 (&k)[XS], int c) {
-    const float al = element_of(k[0], c);   // c < 32: it lies in the registers
-    float ss = squares_below(k, lane, c);
+  // sum of squares below row c and the element at row c (c < 32: it lies in the registers), over the wavefront
+  auto head = [&](const f32x4 (&k)[XS], int c, float& ss, float& al) {
+    ss = 0.f, al = 0.f;
+#pragma unroll
+    for (int sl = 0; sl < XS; ++sl) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = 4 * (lane + 64 * sl) + e;
+        if (r > c) ss += k[sl][e] * k[sl][e];
+        if (r == c) al = k[sl][e];
+      }
+    }
     const f32x4* x = col(c);
     for (int q0 = NR + lane; q0 < nvec; q0 += 64 * TU) {
       f32x4 xv[TU];
@@ -656,39 +762,37 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrArgs args) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) ss += xv[u][e] * xv[u][e];
     }
-    ss = wave_sum_dpp(ss);
+    ss = wave_sum_dpp(ss), al = wave_sum_dpp(al);
+  };
+  // column c, whose head is (ss, al), becomes the reflector v_c: to LDS, to the reflector array, tau to LDS
+  auto make_v = [&](const f32x4 (&k)[XS], int c, float ss, float al) {
     float tau, scale;
-    reflector_of(j0 + c < a.d, ss, al, tau, scale);
-    if (lane == 0) s_tau[c] = tau;
+    reflector_of<false>(j0 + c < a.d, ss, al, tau, scale);
     f32x4* vg = reinterpret_cast<f32x4*>(a.vall + static_cast<int64_t>(j0 + c) * dp + j0);
-    f32x4* sv = s_v4[c & 1];
 #pragma unroll
     for (int sl = 0; sl < XS; ++sl) {
       const int q = lane + 64 * sl;
-      f32x4 o;
-      if (sl == 0)
-        o = v_of(k[0], q, c, scale);
-      else
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = k[sl][e] * scale;
-      sv[q] = o;
+      const f32x4 o = v_of(k[sl], q, c, scale);
+      s_v4[q] = o;
       vg[q] = o;
     }
+    const f32x4* x = col(c);
     for (int q = NR + lane; q < nvec; q += 64) {
       f32x4 o = x[q];
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[e] *= scale;
-      sv[q] = o;
+      s_v4[q] = o;
       vg[q] = o;
     }
+    if (lane == 0) s_tau[c] = tau;
   };
   // H_c applied to column c2, held in k and, beyond the registers, in memory
-  auto apply = [&](f32x4 (&k)[XS], int c2, const f32x4* sv, float tau) {
+  auto apply = [&](f32x4 (&k)[XS], int c2, float tau) {
     f32x4* x = col(c2);
     float dot = 0.f;
 #pragma unroll
     for (int sl = 0; sl < XS; ++sl) {
-      const f32x4 y = sv[lane + 64 * sl];
+      const f32x4 y = s_v4[lane + 64 * sl];
 #pragma unroll
       for (int e = 0; e < 4; ++e) dot = __builtin_fmaf(k[sl][e], y[e], dot);
     }
@@ -700,7 +804,7 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrArgs args) {
       for (int u = 0; u < TU; ++u) {
         const int q = q0 + 64 * u;
         if (q < nvec) {
-          const f32x4 y = sv[q];
+          const f32x4 y = s_v4[q];
 #pragma unroll
           for (int e = 0; e < 4; ++e) dot = __builtin_fmaf(xv[u][e], y[e], dot);
         }
@@ -709,7 +813,7 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrArgs args) {
     const float f = tau * wave_sum_dpp(dot);
 #pragma unroll
     for (int sl = 0; sl < XS; ++sl) {
-      const f32x4 y = sv[lane + 64 * sl];
+      const f32x4 y = s_v4[lane + 64 * sl];
 #pragma unroll
       for (int e = 0; e < 4; ++e) k[sl][e] = __builtin_fmaf(-f, y[e], k[sl][e]);
     }
@@ -721,7 +825,7 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrArgs args) {
       for (int u = 0; u < TU; ++u) {
         const int q = q0 + 64 * u;
         if (q < nvec) {
-          const f32x4 y = sv[q];
+          const f32x4 y = s_v4[q];
 #pragma unroll
           for (int e = 0; e < 4; ++e) xv[u][e] = __builtin_fmaf(-f, y[e], xv[u][e]);
           x[q] = xv[u];
@@ -731,35 +835,40 @@ __global__ __launch_bounds__(QTH) void k_qr_panel_hybrid(QrArgs args) {
   };
 
   if (wave == 0) {
+    float ss, al;
     load_col(ka, 0);
-    make_v(ka, 0);
+    head(ka, 0, ss, al);
+    make_v(ka, 0, ss, al);
   }
   load_col(ka, ca);
   if (cb < QB) load_col(kb, cb);
-  for (int e = t; e < QB * QB * args.pos; e += QTH) {
-    const int r = e / (QB * args.pos), q = e - r * (QB * args.pos);
-    a.vall[static_cast<int64_t>(j0 + r) * dp + args.jb + q] = 0.f;
-  }
-
-  for (int c = 0; c + 1 < QB; ++c) {
-    lds_barrier();   // v_c and tau_c are in place, and every wavefront has finished with v_(c-1)
-    const float tau = s_tau[c];
-    const f32x4* v = s_v4[c & 1];
-    const bool live = tau != 0.f;
-    if (c + 1 == cb) {
-      __builtin_amdgcn_s_setprio(3);
-      if (live) apply(kb, cb, v, tau);
-      make_v(kb, cb);
-      __builtin_amdgcn_s_setprio(0);
-    } else {
-      if (c + 1 == ca) __builtin_amdgcn_s_setprio(3);
-      if (live && ca > c) apply(ka, ca, v, tau);
-      if (c + 1 == ca) make_v(ka, ca);
-      __builtin_amdgcn_s_setprio(0);
-      if (live && cb < QB && cb > c) apply(kb, cb, v, tau);
-    }
-  }
   lds_barrier();
+
+  for (int c = 0; c < QB; ++c) {
+    const float tau = s_tau[c];
+    if (tau != 0.f) {   // columns that have become reflectors are left alone
+      if (ca > c) apply(ka, ca, tau);
+      if (cb < QB && cb > c) apply(kb, cb, tau);
+    }
+    // the owner of column c + 1 takes its head while the others are still busy with their columns
+    const bool owner = c + 1 < QB && wave == c % QWAVES;
+    float ss = 0.f, al = 0.f;
+    if (owner) {
+      if (c + 1 == ca)
+        head(ka, c + 1, ss, al);
+      else
+        head(kb, c + 1, ss, al);
+    }
+    lds_barrier();   // every wavefront has finished with v_c
+    if (owner) {
+      if (c + 1 == ca)
+        make_v(ka, c + 1, ss, al);
+      else
+        make_v(kb, c + 1, ss, al);
+    }
+    lds_barrier();   // v_(c+1) and tau_(c+1) are in place
+  }
+  zero_before_panel(a, args, t);
   if (t < QB) a.tau[args.pos * QB + t] = s_tau[t];
 }
 
@@ -1281,7 +1390,7 @@ int refresh(const QrSide* side, int n_sides, bool product, void* const* const* q
     else if (rows <= 64 * 4 * 8)
       hipLaunchKernelGGL(k_qr_panel_regs<8>, grid, block, 0, st, p);
     else if (rows <= 64 * 4 * 12)
-      hipLaunchKernelGGL(k_qr_panel_regs<12>, grid, block, 0, st, p);
+      hipLaunchKernelGGL(k_qr_panel_long<12>, grid, block, 0, st, p);
     else
       hipLaunchKernelGGL(k_qr_panel_hybrid<8>, grid, block, 0, st, p);
   };

@@ -21,3 +21,17 @@ def test_refresh_of_two_sides(canz, shape, bf16_rot):
     run(canz, [dev], hp)
     tol = dict(tol_update=TOL16_UPDATE, tol_var=TOL16_VAR) if bf16_rot else {}
     check(dev, grads, states, None, hp, "refresh of two sides %dx%d" % shape, **tol)
+
+
+@pytest.mark.parametrize("shape", [(3201, 2060), (2060, 3201)], ids=lambda s: "%dx%d" % s)
+def test_refresh_of_two_long_sides(canz, shape):
+    """Both sides beyond the 2048 rows of the shorter panel kernels: panels that stream their rows beyond the registers (3328 and 2176
+    remaining rows in one launch, then 3200 beside 2048, a launch each), panels of up to 3072 rows beside short ones of the other side,
+    in either order of the sides."""
+    rows, cols = shape
+    grads = [W.gen_grad(99, 0, rows, cols)[0]]
+    states = [W.gen_soap_state(99, 0, rows, cols)]
+    hp = canz.SoapHparams(lr=0.01, eps=1e-8, step=10, refresh=True, out_mode=canz.OUT_DELTA)
+    dev = SoapDevice(canz, rows, cols, grads, states)
+    run(canz, [dev], hp)
+    check(dev, grads, states, None, hp, "refresh of two long sides %dx%d" % shape)
