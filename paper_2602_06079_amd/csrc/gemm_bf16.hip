@@ -1702,6 +1702,12 @@ int64_t tile_count(const GemmDims& d, int tile = BM) {
   return (epi_symmetric(EPI) ? tm * (tm + 1) / 2 : tm * tn) * d.nb;
 }
 
+// the length of k that a tile walks: of all segments, where there are several
+template <int EPI>
+int64_t k_length(const GemmDims& d) {
+  return epi_terms(EPI) ? d.K * d.nseg : d.K;
+}
+
 // number of tiles [0, whole) for the large kernel; the rest, if any, for the small one
 template <int EPI>
 int64_t large_share(int64_t tiles, int64_t cus, int64_t longest_k) {
@@ -1773,7 +1779,9 @@ constexpr bool epi_256x128(int epi) { return epi_terms(epi) || epi == EPI_UPDATE
 // up to two blocks per CU: behind that they move twice the bytes for nothing (544 against 144 blocks of 128 x 128 at k = 4096: 33
 // us against 30; 1088 against 288: 52 and 50).  Eight stages up to one block per CU (288 blocks on 256 CUs: 1.1 times the three-stage
 // time) and from k = 1024 on, below which there is nothing to run ahead of (160 blocks, k 512: 9.9 us, three stages 9.4).  256 x 128 from 2048 on
-// (k = 1024, 88 tiles: 24 us against 22) and only where every one has a CU.
+// (k = 1024, 88 tiles: 24 us against 22) and only where every one has a CU.  k is that of all segments together, whether a launch holds one
+// product or several (Shampoo roots of both sides in one launch, k of one segment / of all six, ms a step: 4 x 1024x1024 7.58 / 7.17,
+// 2 x 1537x1025 12.05 / 11.1, 8 x 512x512 3.13 / 2.85).
 template <int EPI, typename Args>
 void launch_small(const Args& args, const EpiArgs& e, int64_t first, int64_t tiles, int64_t longest_k, int64_t cus, const Shape& s,
                   const OutSpec& o, hipStream_t st) {
@@ -1811,7 +1819,7 @@ hipError_t launch(const GemmDims& d, const void* P, const void* Q, EpiArgs e, co
       hipLaunchKernelGGL((k_gemm_nt_bf16<EPI, false, OneProblem>), dim3(static_cast<unsigned>(cus)), dim3(NTHREADS), 0, st,
                          one, e, s, o);
     }
-    launch_small<EPI>(one, e, whole_large, tiles, epi_terms(EPI) ? d.K * d.nseg : d.K, cus, s, o, st);
+    launch_small<EPI>(one, e, whole_large, tiles, k_length<EPI>(d), cus, s, o, st);
     return hipGetLastError();
   }
   // full rounds of one tile per block, then the left-over tiles cut into k-slices
@@ -1847,7 +1855,7 @@ hipError_t launch_multi(const GemmBatch& g, EpiArgs e, hipStream_t st) {
     const GemmDims& d = g.pr[j].d;
     if (d.K < 8 * BK || d.K % (8 * BK) || d.M % BM || d.N % BN) return hipErrorInvalidValue;
     tiles += tile_count<EPI>(d);
-    longest_k = std::max(longest_k, d.K);
+    longest_k = std::max(longest_k, k_length<EPI>(d));
   }
   for (int j = g.n; j <= many.max; ++j) many.begin[j] = static_cast<int>(tiles);
   if (tiles == 0) return hipSuccess;
