@@ -49,8 +49,9 @@ __device__ __forceinline__ void momentum_tile(const Shape& s, const void* const*
   T* straight = s.tall ? xt : xw;
   T* transposed = s.tall ? xw : xt;
   const bool put_straight = straight != nullptr, put_transposed = transposed != nullptr;   // xw is not always asked for
-  straight += static_cast<int64_t>(b) * pr * pc;
-  transposed += static_cast<int64_t>(b) * pr * pc;
+  const int64_t at = static_cast<int64_t>(b) * pr * pc;
+  if (put_straight) straight += at;
+  if (put_transposed) transposed += at;
   float* mptr = static_cast<float*>(mom[b]);
 
   const int t = threadIdx.x;

@@ -519,7 +519,8 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
     // A 16-byte chunk is 8 consecutive j of one row, i.e. one value from each of 8 lanes:
     // neighbouring lanes exchange their packed pairs so that every lane writes two bf16 of
     // one row.
-    __bf16* C = static_cast<__bf16*>(e.c) + static_cast<int64_t>(b) * d.M * d.N;
+    __bf16* C = static_cast<__bf16*>(e.c);   // null: an update that is asked for the transposed image alone
+    if (epi_symmetric(EPI) || C != nullptr) C += static_cast<int64_t>(b) * d.M * d.N;
     // Staging offset = (lane-only base) + (compile-time part), so that the compiler keeps two
     // address registers instead of one per store.  Element (row_l, col_l) of the wavefront's
     // part, row_l = 32 it + 8 g + 2 p + 4 lh + odd (rp = 2 g + p), col_l = 32 jt + lj, lies in
@@ -528,7 +529,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
     // byte selector of v_perm_b32 over {theirs (bytes 4..7), mine (bytes 0..3)}
     const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
     const bool diagonal_tile = epi_mspace(EPI) && tm == tn;
-    if (epi_mspace(EPI) || e.c != nullptr) {   // (an update may be asked for the transposed image alone)
+    if (epi_mspace(EPI) || C != nullptr) {
     int s_base[2];
 #pragma unroll
     for (int g1 = 0; g1 < 2; ++g1)
@@ -1634,11 +1635,12 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
     return;
   }
 
-  __bf16* C = static_cast<__bf16*>(e.c) + static_cast<int64_t>(b) * d.M * d.N;
+  __bf16* C = static_cast<__bf16*>(e.c);   // null: an update that is asked for the transposed image alone
+  if (epi_symmetric(EPI) || C != nullptr) C += static_cast<int64_t>(b) * d.M * d.N;
   // straight image: (row i, k = j).  Neighbouring lanes exchange their packed pairs so that each
   // lane holds two consecutive columns of one row: the even lane of row 2 rp, the odd lane of row 2 rp + 1.
   const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
-  if (symmetric || e.c != nullptr)
+  if (symmetric || C != nullptr)
 #pragma unroll
   for (int i = 0; i < TI; ++i)
 #pragma unroll
