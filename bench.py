@@ -159,7 +159,7 @@ def stage_lengths(m, n, ns_steps, bf16):
 
 def momentum_bytes(shapes, tp, grad_bytes, ns_steps, bf16):
     """Bytes that the momentum kernels of one library call read and write: gradient, momentum in and out, and U as X^T, and as
-    X too where the library wants it (fp32 mode, no Newton-Schulz step, or single steps of fewer than 2048 padded rows in a run).
+    X too where the library wants it (fp32 mode, no Newton-Schulz step, or single steps of fewer than 1536 padded rows in a run).
     shapes: (rows, cols) of the call's matrices in order.  Matrices of one shape up to a transpose make a batch; up to four
     consecutive batches of fewer than 2048 tiles make a run, parted by whether their steps are merged."""
     def pad(x):
@@ -183,7 +183,7 @@ def momentum_bytes(shapes, tp, grad_bytes, ns_steps, bf16):
         for merged in (False, True):
             run = [(k, n) for k, n in batches[i:j] if (max(stage_lengths(*k, ns_steps, bf16), default=1) > 1) == merged]
             rows = sum(pad(k[0]) * n for k, n in run)
-            images = 2 if not bf16 or ns_steps == 0 or (rows < 2048 and not merged) else 1
+            images = 2 if not bf16 or ns_steps == 0 or (rows < 1536 and not merged) else 1
             total += sum(k[0] * k[1] * n for k, n in run) * (grad_bytes + 8 + images * (2 if bf16 else 4))
         i = j
     return total

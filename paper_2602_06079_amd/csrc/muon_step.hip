@@ -378,12 +378,16 @@ int run_batches(const std::vector<Batch>& batches, int lo, int hi, const canz_mu
   const SplitWs split{reinterpret_cast<float*>(ws + base), SPLIT_MAX_BLOCKS};
   // X itself, beside X^T: in fp32 mode, for the update without a Newton-Schulz step, and for Gram products of few tiles.  From X^T those take
   // longer (the transposing LDS reads run at half the rate: 1 x 25600x128 65 us -> 80, 26 x 2048x1024 76 -> 85), which a second image of
-  // few rows in all, written by the momentum kernel and every update, does not outweigh.  us a step, with X -> without: 1 x 25600x128 431 ->
-  // 513, 2 x 12706x160 278 -> 313, 1 x 20480x1024 681 -> 721; 1 x 2048x8192 677 -> 667, 8 x 512x8192 628 -> 598, 26 x 2048x1024 1460 -> 1363,
-  // 4 x 25600x5120 26500 -> 26100.
+  // few rows in all, written by the momentum kernel and every update, does not outweigh.  us a step, with X -> without, by rows in all and length:
+  //    256   x 4096 127 -> 134, x 25600 421 -> 451                    512   2 x 256x4096 143 -> 143, x 16384 326 -> 344; 1 x 512x4096 157 -> 152
+  //   1024   4 x 256x2048 110 -> 112, x 8192 225 -> 235; 2 x 512x2048 131 -> 127, x 8192 253 -> 256; 1 x 1024x2048 144 -> 142, x 12288 383 -> 388
+  //   1536   3 x 512x1024 119 -> 113, x 25600 844 -> 812; 1 x 1536x2048 225 -> 219, x 8192 529 -> 510
+  //   1792   7 x 256x1024 99 -> 97, x 8192 274 -> 269, x 16384 539 -> 513
+  // and beyond: 8 x 512x1024 153 -> 143, 1 x 2048x8192 677 -> 667, 8 x 512x8192 628 -> 598, 26 x 2048x1024 1460 -> 1363, 4 x 25600x5120
+  // 26500 -> 26100.  Up to 1024 rows either may win, from 1536 on it never pays.
   int64_t all_rows = 0;
   for (int k = 0; k < nk; ++k) all_rows += kind[k].s0.mp * kind[k].nb;
-  const bool wants_x = !is_bf16 || hp.ns_steps == 0 || (all_rows < 2048 && !stages.first && !stages.last);
+  const bool wants_x = !is_bf16 || hp.ns_steps == 0 || (all_rows < 1536 && !stages.first && !stages.last);
 
   // momentum (+ gather, cast, both orientations, tile sums of U^2) per part, norm per batch; several parts whose buffers fit one
   // table go in one launch each (four classes of a 0.6B-shaped layer: 55 -> 33 us and 12 -> 4)

@@ -83,7 +83,7 @@ def test_variants_agree_bit_for_bit(canz, shape):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_classes_of_a_call_as_each_alone(canz, shapes, dtype):
     """Classes that share their launches (momentum, norm, last product; the Gram product from X^T once the rows together
-    reach 2048): every matrix has the bits that it has in a call of its own."""
+    reach 1536): every matrix has the bits that it has in a call of its own."""
     hp = canz.Hparams(out_mode=canz.OUT_DELTA)
     made = []
     for c, (n, rows, cols) in enumerate(shapes):
