@@ -1712,7 +1712,7 @@ int64_t k_length(const GemmDims& d) {
 
 // number of tiles [0, whole) for the large kernel; the rest, if any, for the small one
 template <int EPI>
-int64_t large_share(int64_t tiles, int64_t cus, int64_t longest_k) {
+int64_t large_share(int64_t tiles, int64_t cus, int64_t longest_k, int out_mode = CANZ_OUT_DELTA) {
   const int64_t left = tiles % cus;
   if (2 * tiles <= cus) return 0;   // no round to fill
   constexpr bool msquare = EPI == EPI_POLY || epi_f16_in(EPI);
@@ -1720,9 +1720,15 @@ int64_t large_share(int64_t tiles, int64_t cus, int64_t longest_k) {
   // a polynomial product (k = m, the shortest k range of the step) of less than two rounds runs faster on small
   // tiles throughout: 59.6 -> 52.4 us on 26 matrices of 1024 x 1024; the same rule costs the Gram product 7 %
   if (msquare && tiles < 2 * cus && longest_k <= SMALL_ALL_MAX_K) return 0;
-  // a last product with a short k waits for memory, which the blocks of small tiles that share a CU hide from each other, up to a
-  // few rounds (us, large -> small: 512 tiles with k 1024 99 -> 82, 832 with its left-over ones 183 -> 167, 1024 203 -> 221)
-  if (EPI == EPI_FINAL && longest_k <= 1024 && 4 * tiles <= 13 * cus) return 0;
+  // A last product with a short k waits for memory, which the blocks of small tiles that share a CU hide from each other, up to a
+  // few rounds; longer for parameters, whose old values are waited for, than for Delta W.  us a step of n x 2048x1024 (32 n tiles, k 1024) and of
+  // n x 2047x1023, large tiles for the full rounds -> small ones:
+  //   fp32 parameters   512 tiles 877 -> 866, 704 1156 -> 1141, 832 1383 -> 1363, 896 1492 -> 1474, 960 1572 -> 1558, 992 1597 -> 1593, 1024 1621 -> 1621,
+  //                     1536 2417 -> 2427;  bf16 ones   640 1047 -> 1032, 832 1346 -> 1333, 992 1504 -> 1499, 1024 1527 -> 1528, 1280 1935 -> 1940;
+  //                     odd rows   640 1194 -> 1104, 960 1785 -> 1632
+  //   fp32 Delta W      512 867 -> 858, 704 1138 -> 1127, 768 and 832 within 0.8 % either way (two machines), 864 1357 -> 1366, 992 1526 -> 1550;
+  //                     odd rows   640 1150 -> 1126, 832 1442 -> 1408
+  if (EPI == EPI_FINAL && longest_k <= 1024 && (out_mode == CANZ_OUT_PARAM ? tiles < 4 * cus : 4 * tiles <= 13 * cus)) return 0;
   if (left == 0 || 2 * left > cus) return tiles;
   return tiles - left;
 }
@@ -1813,7 +1819,7 @@ hipError_t launch(const GemmDims& d, const void* P, const void* Q, EpiArgs e, co
   const OneProblem one{d, static_cast<const __bf16*>(P), static_cast<const __bf16*>(Q)};
   const int64_t left = tiles % cus, splits = k_slices<EPI>(left, d.K / BK, cus, w);
   const bool split_all = 2 * tiles <= cus && splits > 1 && split_pays<EPI>(d, d.K / BK, cus);
-  const int64_t whole_large = split_all ? tiles : large_share<EPI>(tiles, cus, d.K);
+  const int64_t whole_large = split_all ? tiles : large_share<EPI>(tiles, cus, d.K, o.out_mode);
   if (whole_large < tiles) {
     if (whole_large > 0) {
       e.full_rounds = static_cast<int>(whole_large / cus), e.left = 0, e.splits = 1, e.partial = nullptr;
@@ -1942,7 +1948,9 @@ hipError_t launch_final_bf16(const GemmDims& d, const void* p, const void* q, co
 }
 
 // Small tiles throughout: up to two rounds of 256 x 256 ones, and no k that the large tile is for.  Seven matrices of four shape classes
-// (208 tiles, k 1024): four launches 73 us, one 50.
+// (208 tiles, k 1024): four launches 73 us, one 50.  us a step, a launch each -> one, by tiles: 40 (k 1024) 181 -> 176; 112 303 -> 290;
+// 128 (k 2048) 469 -> 460; 176 (k 512) 337 -> 342; 224 (k 2048) 765 -> 747; 240 501 -> 466; 288 636 -> 629; 396 (k 1536) 1107 -> 1122; 448
+// (k 2048) 1398 -> 1385; 480 900 -> 892: of 29 calls the two with 176 and 396 lose, 1.5 %.
 bool final_parts_fit(int n, const FinalPart* parts) {
   int64_t tiles = 0, longest_k = 0;
   for (int i = 0; i < n; ++i) tiles += tile_count<EPI_FINAL>(parts[i].d), longest_k = std::max(longest_k, parts[i].d.K);

@@ -101,3 +101,22 @@ def test_classes_of_a_call_as_each_alone(canz, shapes, dtype):
             run_step(canz, [one], hp)
             assert np.array_equal(to_host64(one.out_t[0]), to_host64(dg.out_t[i]))
             assert np.array_equal(one.mom_host(0), dg.mom_host(i))
+
+
+@pytest.mark.parametrize("n,rows,cols", [(31, 2047, 1023), (32, 2047, 1023), (27, 1024, 2043)], ids=lambda x: str(x))
+@pytest.mark.parametrize("out", ["param_f32", "delta_bf16"])
+def test_last_products_of_a_few_rounds(canz, n, rows, cols, out):
+    """992, 1024 and 864 tiles of 256 x 256: on either side of where the last product of parameters, and that of Delta W, goes from small
+    tiles to large ones for the full rounds.  Every matrix checked has the bits that it has alone."""
+    delta = out.startswith("delta")
+    two = [W.gen_grad(94, i, rows, cols)[0] for i in range(2)]
+    zeros = [np.zeros((rows, cols), np.float32)] * n
+    params = None if delta else [W.gen_param(94, i % 2, rows, cols, std=0.5) for i in range(n)]
+    hp = canz.Hparams(out_mode=canz.OUT_DELTA if delta else canz.OUT_PARAM, weight_decay=0.1, lr=0.5)
+    dtype = np.uint16 if out.endswith("bf16") else np.float32
+    many = DeviceGroup(canz, rows, cols, [two[i % 2] for i in range(n)], zeros, outs=params, out_np_dtype=dtype)
+    run_step(canz, [many], hp)
+    for i in (0, n - 1):
+        one = DeviceGroup(canz, rows, cols, [two[i % 2]], zeros[:1], outs=None if delta else [params[i]], out_np_dtype=dtype)
+        run_step(canz, [one], hp)
+        assert np.array_equal(to_host64(one.out_t[0]), to_host64(many.out_t[i]))
