@@ -10,7 +10,8 @@
 // the rotations, on fp32 values held as three bf16 terms (or, if the caller asks for it with bf16_rotations, with the
 // bases, M and N' rounded to bf16), and the statistics of gradients that arrive as bf16 (their own values are the
 // operands, every product is exact in fp32).  The statistics of fp32 gradients and the refresh run on
-// v_mfma_f32_32x32x2_f32.
+// v_mfma_f32_32x32x2_f32, but for the refresh's product S Q, which runs on three bf16 terms where the rotations do (an infinity in a
+// statistic gives NaN there).
 //
 // The products all take the form C[i][j] = sum_k P[i][k] Q[j][k].  The rotation into the basis
 // runs right side first with its result written transposed, (G Q_R)^T = Q_R^T-rows times G-rows,
@@ -1208,13 +1209,14 @@ Carve carve(int64_t rows, int64_t cols, int nb, Sides u, bool refresh, Rot rot, 
     c.yt = take(both ? nb * plane : 0);
     c.ql = take(u.left ? nb * rp * rp : 0), c.qlt = take(u.left ? nb * rp * rp : 0);
     c.qr = take(u.right ? nb * cp * cp : 0), c.qrt = take(u.right ? nb * cp * cp : 0);
-    take(nb * dm * dm);   // once a padded statistic: the size is what callers have measured their workspaces by
+    take(nb * dm * dm);   // not used (once a padded statistic): with less a matrix, batches would hold more of them and could need more in all
+                          // than a workspace that was measured by this sum
   }
   if (refresh) {
-    // The refresh of both sides (refresh_pool): two square matrices and a strip of 256 columns a side and 128 x 129 floats.  Four
+    // The refresh of both sides (one_side lays them out): two square matrices and a strip of 256 columns a side and 128 x 129 floats.  Four
     // squares of the larger side, 544 columns and the rest hold them, whatever the other side is.
     c.pool = take(nb * (4 * dm * dm + 544 * dm + 3 * QBLK * QBLK));
-    take(nb * QB);
+    take(nb * QB);   // not used, as above
   }
   const size_t rp2 = pad256(rows), cp2 = pad256(cols), p2 = nb * rp2 * cp2 / 2;   // floats that hold a batch of panels
   const bool all_of_g = bf16 || rot == Rot::TERMS;   // G is an operand of the rotations, too
