@@ -519,8 +519,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
     // A 16-byte chunk is 8 consecutive j of one row, i.e. one value from each of 8 lanes:
     // neighbouring lanes exchange their packed pairs so that every lane writes two bf16 of
     // one row.
-    __bf16* C = static_cast<__bf16*>(e.c);   // null: an update that is asked for the transposed image alone
-    if (epi_symmetric(EPI) || C != nullptr) C += static_cast<int64_t>(b) * d.M * d.N;
+    const int64_t image = static_cast<int64_t>(b) * d.M * d.N;
     // Staging offset = (lane-only base) + (compile-time part), so that the compiler keeps two
     // address registers instead of one per store.  Element (row_l, col_l) of the wavefront's
     // part, row_l = 32 it + 8 g + 2 p + 4 lh + odd (rp = 2 g + p), col_l = 32 jt + lj, lies in
@@ -529,7 +528,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
     // byte selector of v_perm_b32 over {theirs (bytes 4..7), mine (bytes 0..3)}
     const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
     const bool diagonal_tile = epi_mspace(EPI) && tm == tn;
-    if (epi_mspace(EPI) || C != nullptr) {
+    if (epi_mspace(EPI) || e.c != nullptr) {   // (an update may be asked for the transposed image alone)
     int s_base[2];
 #pragma unroll
     for (int g1 = 0; g1 < 2; ++g1)
@@ -551,14 +550,14 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[4][4], __bf16* stage
         }
     // In a diagonal tile the lower left quarter is the mirror image of the upper right one, as in the small kernel: the
     // two are equal bit for bit when both factors are the same matrix, but only to rounding in a product of two.
-    if (!diagonal_tile || wm <= wn) flush_stage(C, tm, d.N, 8 * tn + 4 * wn, wm);
+    if (!diagonal_tile || wm <= wn) flush_stage(static_cast<__bf16*>(e.c) + image, tm, d.N, 8 * tn + 4 * wn, wm);
     }
 
     // ---- transposed image: element (i, j) is (row j, k = i) of CT (UPDATE) or of the mirror
     // tile of C (symmetric products).  A lane's 4 consecutive rows are half a chunk.
     const bool mirror = epi_mspace(EPI);
     if (!diagonal_tile || wm < wn) {
-      __bf16* CT = mirror ? C : static_cast<__bf16*>(e.ct) + static_cast<int64_t>(b) * d.M * d.N;
+      __bf16* const CT = static_cast<__bf16*>(mirror ? e.c : e.ct) + image;
       // element (i_l, j_l) goes to row j_l = 32 jt + lj, k = i_l = 32 it + 8 g + 4 lh + q:
       // k-block it, chunk g, swizzle (lj >> 2) & 3: one lane base per g, the rest immediate
       int t_base[4];
@@ -1635,12 +1634,12 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
     return;
   }
 
-  __bf16* C = static_cast<__bf16*>(e.c);   // null: an update that is asked for the transposed image alone
-  if (epi_symmetric(EPI) || C != nullptr) C += static_cast<int64_t>(b) * d.M * d.N;
+  const int64_t image = static_cast<int64_t>(b) * d.M * d.N;
   // straight image: (row i, k = j).  Neighbouring lanes exchange their packed pairs so that each
   // lane holds two consecutive columns of one row: the even lane of row 2 rp, the odd lane of row 2 rp + 1.
   const unsigned pair_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
-  if (symmetric || C != nullptr)
+  if (symmetric || e.c != nullptr) {   // (an update may be asked for the transposed image alone)
+    __bf16* const C = static_cast<__bf16*>(e.c) + image;
 #pragma unroll
   for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -1655,9 +1654,10 @@ __global__ __launch_bounds__(NTHREADS, small_blocks(SM, NST)) void k_gemm_nt_bf1
         *reinterpret_cast<unsigned*>(C + panel_chunk_off(row, col & ~7, d.N) + (col & 7)) = pk;
       }
     }
+  }
   // transposed image: (row j, k = i) of CT (UPDATE) or of the mirror tile of C (symmetric products)
   if (!symmetric || mirrored) {
-    __bf16* CT = symmetric ? C : static_cast<__bf16*>(e.ct) + static_cast<int64_t>(b) * d.M * d.N;
+    __bf16* const CT = static_cast<__bf16*>(symmetric ? e.c : e.ct) + image;
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
